@@ -36,10 +36,13 @@ PEAK_FP64_TFLOPS = 78.6
 # Algorithmic work of the product basis per evaluated atom: the nonzero real Gaunt entries
 # of the direct B3 contraction sum_m G A A A (B1 and B2 add under 1 %).  The energy costs
 # about 6 flops per entry, the adjoint about 10 (the three factors' adjoints).  The library
-# recouples the triples through pair couplings and executes fewer flops than this count
+# evaluates both from the products of label pairs and executes fewer flops than this count
 # (kernel_models gives the executed count next to it).
 GAUNT_TERMS = {(10, 4): 211610, (8, 3): 33168}
-ALGO_FLOP_PER_TERM = {"ace.energy": 6.0, "ace.adjoint": 10.0}
+ALGO_FLOP_PER_TERM = {"ace.products": 16.0}
+# As executed at (10, 4): products P_LM of unordered label pairs (each multiplied with the 2 n_max
+# coefficients of its third blocks) and vector operations that form them.
+SYM_PRODUCTS, SYM_VECTOR_OPS = 11760, 67915
 
 # Hardware counters per launch of each kernel class on the indentation block (rocprofv3
 # --pmc FETCH_SIZE, then WRITE_SIZE; KiB per launch, a class launch being one step of its
@@ -50,21 +53,6 @@ ALGO_FLOP_PER_TERM = {"ace.energy": 6.0, "ace.adjoint": 10.0}
 # `source_sha256` is checked at run time and the traffic is reported as null when the
 # source has changed since.
 COUNTERS = {
-    "ace.adjoint": {"fetch_kib": 3607605.0, "write_kib": 20966484.5, "units": 1137181,
-        "source": "paper_2411_03002_amd/csrc/ace.hip",
-        "source_sha256": "5f9370f6cb936839c61624ac7032b0f06b53118e2e38365273338e5a8f75b3df"},
-    "ace.energy": {"fetch_kib": 582437.3, "write_kib": 83597.8, "units": 1137181,
-        "source": "paper_2411_03002_amd/csrc/ace.hip",
-        "source_sha256": "5f9370f6cb936839c61624ac7032b0f06b53118e2e38365273338e5a8f75b3df"},
-    "ace.basis": {"fetch_kib": 394950.7, "write_kib": 1128297.9, "units": 1137181,
-        "source": "paper_2411_03002_amd/csrc/ace.hip",
-        "source_sha256": "5f9370f6cb936839c61624ac7032b0f06b53118e2e38365273338e5a8f75b3df"},
-    "ace.force": {"fetch_kib": 976031.9, "write_kib": 2774215.6, "units": 1137181,
-        "source": "paper_2411_03002_amd/csrc/ace.hip",
-        "source_sha256": "5f9370f6cb936839c61624ac7032b0f06b53118e2e38365273338e5a8f75b3df"},
-    "ace.backproject": {"fetch_kib": 555339.0, "write_kib": 1110562.5, "units": 1137181,
-        "source": "paper_2411_03002_amd/csrc/ace.hip",
-        "source_sha256": "5f9370f6cb936839c61624ac7032b0f06b53118e2e38365273338e5a8f75b3df"},
     "eam.density": {"fetch_kib": 623496.4, "write_kib": 125000.0, "units": 4000000,
         "source": "paper_2411_03002_amd/csrc/eam.hip",
         "source_sha256": "183e44649344ca6889755f53585469a4634af1bab88d6b2cf9810c9fd5ba6970"},
@@ -126,26 +114,16 @@ def kernel_models(stats, n, n_act, nb_avg, nb_act_avg, avg_samples=1):
     neighbour row once, gathered neighbour data assumed cached); ALU kernels count the
     floating-point operations of the algorithm as implemented (fma = 2 flops).
     """
-    Tc, Tw, Nt = stats["coupling_terms"], stats["triple_width"], stats["triples"]
-    # energy: coupling 3/term, triples 2 per (2L+1) and 4 per triple; adjoint: coupling
-    # recompute 3/term and back-propagation 5/term, triples 4 per (2L+1) and 2 per triple
-    f_energy = 3.0 * Tc + 2.0 * Tw + 4.0 * Nt
-    f_adjoint = 8.0 * Tc + 4.0 * Tw + 2.0 * Nt
-    f_products = f_energy + f_adjoint
     K, LM = 10, 25
+    # the projection on the radial functions (2 K flop per atomic-base value) ends the products
+    f_products = 4.0 * K * SYM_PRODUCTS + 2.0 * SYM_VECTOR_OPS + 2.0 * K * stats["n_atomic_base"]
     f_basis = nb_act_avg * (3 * K + 4 * LM + 2 * K * LM) + 2.0 * K * stats["n_atomic_base"]
-    # the float32 path back-projects the adjoint in its own tile kernel (2 K flop per
-    # atomic-base value); the force kernel then evaluates the neighbour gradients
-    f_backproject = 2.0 * K * stats["n_atomic_base"]
     f_force = nb_act_avg * (4 * K * LM + 12 * LM + 6 * K)
     row = 4.0 + 4.0 * nb_avg
     return {
         "ace.products": ("alu_fp32", n_act * f_products, "flop"),
-        "ace.energy": ("alu_fp32", n_act * f_energy, "flop"),
-        "ace.adjoint": ("alu_fp32", n_act * f_adjoint, "flop"),
         "ace.basis": ("alu_fp32", n_act * f_basis, "flop"),
         "ace.force": ("alu_fp32", n_act * f_force, "flop"),
-        "ace.backproject": ("alu_fp32", n_act * f_backproject, "flop"),
         "eam.density": ("hbm", n * (row + 24 + 8 + 32), "byte"),
         "eam.force": ("hbm", n * (row + 24 + 16 + 24), "byte"),
         "nbr.build": ("hbm", n * (24 + row), "byte"),
@@ -733,10 +711,10 @@ def main():
         result["adaptive_over_full_ace"] = adaptive / full
         n_f = st_f["prof"]["ace_atoms"] / st_f["prof"]["steps"]
         mf = kernel_models(stats, n, n_f, nb_avg, 42.0)
-        for k in ("ace.energy", "ace.adjoint"):
-            if k in prof_f:
-                result[f"roofline_full_ace_{k.split('.')[1]}"] = roofline_for(k, mf[k], *prof_f[k],
-                                                                            algo=algo_work(k, n_f), units=n_f)
+        if "ace.products" in prof_f:
+            result["roofline_full_ace_products"] = roofline_for("ace.products", mf["ace.products"],
+                                                                *prof_f["ace.products"],
+                                                                algo=algo_work("ace.products", n_f), units=n_f)
         result["kernels_full_ace"] = {k: {"launches": v[0], "total_ms": v[1], "avg_ms": v[1] / max(v[0], 1)}
                                       for k, v in prof_f.items()}
         log(f"full ACE {dt_f / KF * 1e3:.2f} ms/step, {full:.4g} atom-steps/s, ratio {adaptive / full:.2f}")

@@ -1,29 +1,29 @@
 // Atomic cluster expansion on the active atoms: atomic base, product basis with energy
 // and adjoint, force scatter.
 //
-// Three kernels per evaluation (Sec. III A form E = phi1 + F_eps(phi2), basis defined in
-// the ABI header):
+// Kernels of an evaluation (Sec. III A form E = phi1 + F_eps(phi2), basis defined in the ABI
+// header):
 //  1. k_ace_basis    one wave per active atom: per neighbour the Chebyshev radial values
 //                    and real solid harmonics, A'[k][lm] = sum_j g_k S_lm, then the radial
 //                    mixing A[n][lm] = sum_k Wp[l][n][k] A'[k][lm] (Wp folds W, N_l, 1/s_a).
-//  2. k_ace_products lane = atom, 64 (fp32) or 32 (fp64) atoms per block held in LDS,
-//                    16 (fp32) or 8 (fp64) waves dealt the coupling list round-robin;
-//                    the list is sorted by coupling type for instruction-cache locality.  B3 is evaluated by recoupling:
-//                    for a label pair (p1, p2) the coupled product
-//                    P_LM = sum G(l1 l2 L; m1 m2 M) A_p1m1 A_p2m2 is formed once and every
-//                    third block p3 >= p2 of degree L contributes B = sum_M P_LM A_p3M.
+//  2. ace_sym.hip    energies and the adjoint projected back on the radial functions (float32);
+//     k_ace_products float64 and coefficient gradients: lane = atom, the tile held in LDS,
+//                    the coupling list dealt round-robin.  For a label pair (p1, p2) the coupled
+//                    product P_LM = sum G(l1 l2 L; m1 m2 M) A_p1m1 A_p2m2 is formed once and
+//                    every third block p3 >= p2 of degree L contributes B = sum_M P_LM A_p3M.
 //                    The adjoint pass reuses the same structure with
 //                    d = c1 + F_eps'(phi2) c2: Abar_p3 += d P, Pbar += d A_p3, then Pbar
 //                    is pushed back through the coupling into Abar_p1, Abar_p2.
-//  3. k_ace_force    one wave per active atom: back-projection of Abar through Wp, then
-//                    per neighbour the gradient of sum Abar'' g_k S_lm, scattered as
-//                    F_j -= w_i dE_i/dr_ij, F_i += w_i dE_i/dr_ij (float64 atomics).
+//  3. k_ace_force    one wave per active atom: per neighbour the gradient of sum Abar'' g_k
+//                    S_lm, scattered as F_j -= w_i dE_i/dr_ij, F_i += w_i dE_i/dr_ij (float64
+//                    atomics).
 #include <algorithm>
 #include <cmath>
 #include <type_traits>
 
 #include "ace_coupling_gen.h"
 #include "ace_model.h"
+#include "ace_sym.h"
 #include "device_util.h"
 
 namespace apx {
@@ -35,23 +35,14 @@ struct AnchorDev {
 
 template <class T>
 struct AceScratch {
-  T* A;             // [n_act][na]
-  T* Ab;            // [n_act][na], or [tile][na][tile_size] when tile_size > 0
-  int tile_size;
+  T* A;             // [n_act][stride] atomic base
+  int stride;
+  T* Ab;            // [n_act][na] adjoint, or null: A then holds the projected adjoint B'[lm][k]
   double* e_anch;   // [n_act]
   double* fp_anch;  // [n_act]
-  T* fp;            // [tiles * tile_size] embedding slope F_eps'(phi2) per atom (float32 path)
 };
 
 // ------------------------------------------------------------ shared helpers
-// Reads a read-only table entry (a scalar type) through the constant address space.  The
-// product kernels store to global memory, so the compiler cannot prove their table reads
-// unclobbered and would issue vector loads; constant-space reads let it use scalar loads.
-template <class X>
-__device__ __forceinline__ X cld(const X* p) {
-  return *(const __attribute__((address_space(4))) X*)p;
-}
-
 template <class T, int LMAX, bool GRAD>
 __device__ __forceinline__ void solid_harmonics(T x, T y, T z, T* S, T* Sx, T* Sy, T* Sz) {
   S[0] = T(1);
@@ -287,7 +278,7 @@ __global__ void __launch_bounds__(64) k_ace_basis(const double* __restrict__ pos
   }
   __syncthreads();
   const int na = K * LM;
-  T* Arow = sc.A + (size_t)q * na;
+  T* Arow = sc.A + (size_t)q * sc.stride;
   for (int o = lane; o < na; o += 64) {
     const int nn = o / LM, lm = o - nn * LM;
     int l = 0;
@@ -334,19 +325,6 @@ __device__ __forceinline__ void acc_add(T& s, T& e, T c, T B) {
   }
 }
 
-// Adds x to the compensated sum (s, e): TwoSum, the rounding error kept in e.
-template <class T, bool COMP>
-__device__ __forceinline__ void acc_sum(T& s, T& e, T x) {
-  if constexpr (COMP) {
-    const T sn = s + x;
-    const T bp = sn - s;
-    e += (s - (sn - bp)) + (x - bp);
-    s = sn;
-  } else {
-    s += x;
-  }
-}
-
 template <class T, int TILE>
 __device__ __forceinline__ void lds_add(T* p, T v, bool on) {
   if (on) atomicAdd(p, v);
@@ -384,72 +362,6 @@ __device__ __forceinline__ void pair_fwd(const T* __restrict__ As, const int* re
       }
     }
   }
-}
-
-// Energy contribution of one label pair with the third-block loop unrolled over the
-// radial index (coefficient loads of a segment issued together).  The pair's terms c.B
-// (at most (l_max + 1) n_max of them) are summed by fused multiply-adds, and the pair's
-// two partial sums enter the running sums with compensation.
-// The pair's third blocks of degree L: P_LM by the per-degree coupling, then B = P.A_n3L
-// for the pair's run of n3 (wave-uniform bounds; the loop is unrolled over NMAX).
-template <class T, int LMAX, int NMAX, int TILE, int L1, int L2, int L>
-__device__ __forceinline__ void pair_fwd_deg(const T* __restrict__ As, const int* rec, const AceTables<T>& tb, int t,
-                                             const T* a, const T* bb, T& p1, T& p2) {
-  if constexpr ((L1 + L2 + L) % 2 == 0 && L >= (L1 > L2 ? L1 - L2 : L2 - L1) && L <= L1 + L2 && L <= LMAX) {
-    constexpr int P2 = (LMAX + 1) * (LMAX + 1);
-    constexpr int ST = TILE + 1;
-    const int q0 = __builtin_amdgcn_readfirstlane(rec[4 + L]);
-    const int q1 = __builtin_amdgcn_readfirstlane(rec[5 + L]);
-    if (q0 < q1) {
-      const int n30 = __builtin_amdgcn_readfirstlane((rec[10 + L] - L * L) / P2);
-      const int n3e = n30 + (q1 - q0);
-      // the coefficients of n3 = 0 .. NMAX-1 around the run, read at once (scalar loads
-      // from a uniform base; the table is padded on both sides), and the run as a bit mask
-      static_assert(NMAX <= kTcPad, "the coefficient table is padded by kTcPad entries");
-      const Coef2<T>* cb = tb.tc + (q0 - n30);
-      T c1v[NMAX], c2v[NMAX];
-#pragma unroll
-      for (int n3 = 0; n3 < NMAX; ++n3) {
-        c1v[n3] = cld(&cb[n3].c1);
-        c2v[n3] = cld(&cb[n3].c2);
-      }
-      const unsigned run = ((1u << n3e) - 1u) & ~((1u << n30) - 1u);
-      T P[2 * L + 1];
-#pragma unroll
-      for (int m = 0; m < 2 * L + 1; ++m) P[m] = T(0);
-      Couple3<LMAX, L1, L2, L>::template fwd<T>(a, bb, P);
-#pragma unroll
-      for (int n3 = 0; n3 < NMAX; ++n3) {
-        if (run & (1u << n3)) {
-          T B = T(0);
-#pragma unroll
-          for (int mm = 0; mm < 2 * L + 1; ++mm) B = fma(P[mm], As[(n3 * P2 + L * L + mm) * ST + t], B);
-          p1 = fma(c1v[n3], B, p1);
-          p2 = fma(c2v[n3], B, p2);
-        }
-      }
-    }
-  }
-}
-
-template <class T, int LMAX, int NMAX, int TILE, bool COMP, int L1, int L2>
-__device__ __forceinline__ void pair_fwd_n(const T* __restrict__ As, const int* rec, const AceTables<T>& tb, int t,
-                                           int n_max, Acc<T>& acc) {
-  constexpr int ST = TILE + 1;
-  const int o1 = rec[0], o2 = rec[1];
-  T a[2 * L1 + 1], bb[2 * L2 + 1];
-#pragma unroll
-  for (int m = 0; m < 2 * L1 + 1; ++m) a[m] = As[(o1 + m) * ST + t];
-#pragma unroll
-  for (int m = 0; m < 2 * L2 + 1; ++m) bb[m] = As[(o2 + m) * ST + t];
-  T p1 = T(0), p2 = T(0);
-  pair_fwd_deg<T, LMAX, NMAX, TILE, L1, L2, 0>(As, rec, tb, t, a, bb, p1, p2);
-  pair_fwd_deg<T, LMAX, NMAX, TILE, L1, L2, 1>(As, rec, tb, t, a, bb, p1, p2);
-  pair_fwd_deg<T, LMAX, NMAX, TILE, L1, L2, 2>(As, rec, tb, t, a, bb, p1, p2);
-  pair_fwd_deg<T, LMAX, NMAX, TILE, L1, L2, 3>(As, rec, tb, t, a, bb, p1, p2);
-  pair_fwd_deg<T, LMAX, NMAX, TILE, L1, L2, 4>(As, rec, tb, t, a, bb, p1, p2);
-  acc_sum<T, COMP>(acc.s1, acc.e1, p1);
-  acc_sum<T, COMP>(acc.s2, acc.e2, p2);
 }
 
 template <class T, int LMAX, int TILE, bool DC, int L1, int L2>
@@ -705,53 +617,6 @@ __global__ void __launch_bounds__(NW * 64) k_ace_products(const T* __restrict__ 
   }
 }
 
-// Back-projection of the adjoint of the float32 unit path, one tile of 64 atoms per block
-// (lane = atom): B[k][lm] = sum_n Wp[l][n][k] Abar[n][lm], read and written tile-major
-// [tile][a][64], so every load and store of a wave is one coalesced 256-byte segment.  A
-// wave takes columns lm = wave, wave + 4, ...; a column's K adjoint values are loaded once
-// and serve its K outputs, which are summed in registers; the weights are staged in LDS
-// once per block.  The sum runs over n in ascending order.
-template <class T, int LMAX>
-__global__ void __launch_bounds__(256) k_ace_backproject(const T* __restrict__ Abg, T* __restrict__ Bg,
-                                                         const T* __restrict__ Wp, int K, int na) {
-  constexpr int LM = (LMAX + 1) * (LMAX + 1);
-  constexpr int TILE = 64;
-  constexpr int kMaxK = 12;
-  // the wave index is uniform across the wave: said so, the column's l is too and the
-  // weights become scalar loads (otherwise every lane loads the same weight)
-  const int t = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  // the weights of every l, rows padded to kMaxK (zeros), read by broadcast LDS loads
-  __shared__ T ws[(LMAX + 1) * kMaxK * kMaxK];
-  for (int e = threadIdx.x; e < (LMAX + 1) * kMaxK * kMaxK; e += 256) {
-    const int l = e / (kMaxK * kMaxK), r = e - l * kMaxK * kMaxK, nn = r / kMaxK, kk = r - nn * kMaxK;
-    ws[e] = nn < K && kk < K ? Wp[((size_t)l * K + nn) * K + kk] : T(0);
-  }
-  __syncthreads();
-  const T* Ab = Abg + (size_t)blockIdx.x * na * TILE;
-  T* B = Bg + (size_t)blockIdx.x * na * TILE;
-  for (int lm = wv; lm < LM; lm += 4) {
-    int l = 0;
-    while ((l + 1) * (l + 1) <= lm) ++l;
-    T a[kMaxK];
-#pragma unroll
-    for (int nn = 0; nn < kMaxK; ++nn) a[nn] = nn < K ? Ab[(size_t)(nn * LM + lm) * TILE + t] : T(0);
-    T v[kMaxK];
-#pragma unroll
-    for (int kk = 0; kk < kMaxK; ++kk) v[kk] = T(0);
-#pragma unroll
-    for (int nn = 0; nn < kMaxK; ++nn) {
-      if (nn < K) {
-        const T* w = ws + (l * kMaxK + nn) * kMaxK;
-#pragma unroll
-        for (int kk = 0; kk < kMaxK; ++kk) v[kk] += w[kk] * a[nn];
-      }
-    }
-#pragma unroll
-    for (int kk = 0; kk < kMaxK; ++kk)
-      if (kk < K) B[(size_t)(kk * LM + lm) * TILE + t] = v[kk];
-  }
-}
-
 // ------------------------------------------------------------------ kernel 3
 // Ā' of one atom in LDS: lm-major rows of KP radial values (K rounded up to whole 16-byte
 // groups, the padding zero), so that a row is read by a few wide broadcast loads.
@@ -785,21 +650,19 @@ __global__ void __launch_bounds__(64, sizeof(T) == 4 ? 4 : 1) k_ace_force(const 
   // second weight set (the integrator's weight difference): scattered only where non-zero
   const double w2i = f2 ? w2[i] : 0.0;
   const int na = K * LM;
-  const int ts = sc.tile_size;
-  const T* Abr = ts > 0 ? sc.Ab + (size_t)(q / ts) * na * ts + (q % ts) : sc.Ab + (size_t)q * na;
-  const int as = ts > 0 ? ts : 1;
-  // back-projection: Ab2[k][lm] = sum_n Wp[l][n][k] Abar[n][lm]; the float32 unit path
-  // has it precomputed tile-major in sc.A by k_ace_backproject
+  // the projected adjoint B'[lm][k] = sum_n Wp[l][n][k] Abar[n][lm], as the product kernels left
+  // it, or from the adjoint
   for (int o = lane; o < LM * KP; o += 64) Ab2[o] = T(0);
   __syncthreads();
-  if (ts > 0) {
-    const T* B = sc.A + (size_t)(q / ts) * na * ts + (q % ts);
-    for (int o = lane; o < K * LM; o += 64) {
-      const int kk = o / LM, lm = o - kk * LM;
-      Ab2[lm * KP + kk] = B[(size_t)o * ts];
+  if (!sc.Ab) {
+    const T* B = sc.A + (size_t)q * sc.stride;
+    for (int o = lane; o < na; o += 64) {
+      const int lm = o / K;
+      Ab2[lm * KP + o - lm * K] = B[o];
     }
   }
-  for (int o = lane; o < K * LM && ts == 0; o += 64) {
+  const T* Abr = sc.Ab + (size_t)q * na;
+  for (int o = lane; o < na && sc.Ab; o += 64) {
     const int kk = o / LM, lm = o - kk * LM;
     int l = 0;
     while ((l + 1) * (l + 1) <= lm) ++l;
@@ -808,7 +671,7 @@ __global__ void __launch_bounds__(64, sizeof(T) == 4 ? 4 : 1) k_ace_force(const 
 #pragma unroll
     for (int nn = 0; nn < kMaxK; ++nn) {
       wv_[nn] = nn < K ? Wp[((size_t)l * K + nn) * K + kk] : T(0);
-      av_[nn] = nn < K ? Abr[(size_t)(nn * LM + lm) * as] : T(0);
+      av_[nn] = nn < K ? Abr[nn * LM + lm] : T(0);
     }
     T v = T(0);
 #pragma unroll
@@ -954,426 +817,6 @@ __global__ void __launch_bounds__(64, sizeof(T) == 4 ? 4 : 1) k_ace_force(const 
   }
 }
 
-// ------------------------------------------------- kernel 2b (float32, unit adjoint)
-// Same energy pass as k_ace_products; the adjoint is reorganised so that no LDS atomics
-// are needed.  The adjoint work is cut into units (l1, l2, L): all pairs of one coupling
-// type, restricted to third blocks of degree L.  A unit is owned by one wave, which keeps
-//   acc3[n3][M]  the adjoint of every third block (n3, L)            (registers)
-//   accR[m]      the adjoint of the pair label with the larger degree, accumulated over
-//                the run of pairs sharing it (pairs are sorted by it)
-//   accO[h][m]   the adjoint of the other pair label (one of at most unit_width values in
-//                the unit's range of other labels)
-// and adds them to the tile's adjoint in global memory with float atomics when a run or
-// the unit ends.
-// Every lane adds, padded lanes (beyond the last active atom) included: their slots lie
-// inside the tile's region and are never read back.
-template <class T, int TILE>
-__device__ __forceinline__ void gadd(T* __restrict__ Abt, int a, int t, T v) {
-  unsafeAtomicAdd(&Abt[(size_t)a * TILE + t], v);
-}
-
-
-// The third blocks of degree L in registers, and the flush of their adjoint.
-template <class T, int LMAX, int NMAX, int TILE, int L>
-__device__ __forceinline__ void third_load(const T* __restrict__ As, int n_max, int t, T (&A3)[NMAX][2 * L + 1],
-                                           T (&acc3)[NMAX][2 * L + 1]) {
-  constexpr int ST = TILE + 1;
-  constexpr int P2 = (LMAX + 1) * (LMAX + 1);
-#pragma unroll
-  for (int n = 0; n < NMAX; ++n) {
-#pragma unroll
-    for (int m = 0; m < 2 * L + 1; ++m) {
-      acc3[n][m] = T(0);
-      A3[n][m] = n < n_max ? As[(n * P2 + L * L + m) * ST + t] : T(0);
-    }
-  }
-}
-
-// The block's waves sum their third-block adjoints through LDS (the upper half of the
-// waves hands its sums to the lower half, which stores the partial sums), then every
-// wave adds a share of the elements to global memory: one atomic per element and block.
-// lds holds (NW/2) * NMAX * (2L+1) * 64 values; the caller has finished with it.
-template <class T, int LMAX, int NMAX, int TILE, int NW, int L>
-__device__ __forceinline__ void third_flush(T* __restrict__ Abt, T* lds, int n_max, int t, int wv, int lane,
-                                            T (&acc3)[NMAX][2 * L + 1]) {
-  constexpr int P2 = (LMAX + 1) * (LMAX + 1);
-  constexpr int NL = 2 * L + 1, NE = NMAX * NL, H = NW / 2;
-  static_assert(NW % 2 == 0, "waves pair up");
-  __syncthreads();
-  if (wv >= H) {
-#pragma unroll
-    for (int n = 0; n < NMAX; ++n)
-#pragma unroll
-      for (int m = 0; m < NL; ++m) lds[((wv - H) * NE + n * NL + m) * 64 + lane] = acc3[n][m];
-  }
-  __syncthreads();
-  if (wv < H) {
-#pragma unroll
-    for (int n = 0; n < NMAX; ++n)
-#pragma unroll
-      for (int m = 0; m < NL; ++m) {
-        T* q = &lds[(wv * NE + n * NL + m) * 64 + lane];
-        *q = *q + acc3[n][m];
-      }
-  }
-  __syncthreads();
-  for (int e = wv; e < NE; e += NW) {
-    const int n = e / NL, m = e - n * NL;
-    if (n >= n_max) continue;
-    T s = T(0);
-#pragma unroll
-    for (int h = 0; h < H; ++h) s += lds[(h * NE + e) * 64 + lane];
-    gadd<T, TILE>(Abt, n * P2 + L * L + m, t, s);
-  }
-}
-
-// The pairs of one unit (l1, l2, L) for a range of the other label; the third-block
-// registers A3 and their adjoint acc3 are the caller's (shared by the units of one degree).
-template <class T, int LMAX, int NMAX, int TILE, int L1, int L2, int L>
-__device__ __forceinline__ void unit_bwd(const T* __restrict__ As, T* __restrict__ Abt, const AceTables<T>& tb,
-                                         int eb, int ee, int obase, int oend, int t, T fp,
-                                         const T (&A3)[NMAX][2 * L + 1], T (&acc3)[NMAX][2 * L + 1]) {
-  using C = Couple3<LMAX, L1, L2, L>;
-  constexpr int ST = TILE + 1;
-  constexpr int P2 = (LMAX + 1) * (LMAX + 1);
-  constexpr int N1 = 2 * L1 + 1, N2 = 2 * L2 + 1, NL = 2 * L + 1;
-  constexpr bool RUN1 = L1 >= L2;
-  constexpr int NR = RUN1 ? N1 : N2;
-  constexpr int NO = RUN1 ? N2 : N1;
-  constexpr int LR = RUN1 ? L1 : L2;
-  constexpr int LO = RUN1 ? L2 : L1;
-  static_assert(NMAX <= kAdjC2 - kAdjC1, "the pair stream holds coefficients for n3 < 12");
-  // this unit covers the pairs whose other label lies in [obase, oend), at most
-  // unit_width(L, n_max) <= NH labels
-  constexpr int NH = unit_width(L, NMAX);
-  T accR[NR];
-  T accO[NH][NO];  // adjoint of the other label, by its position in the range
-#pragma unroll
-  for (int h = 0; h < NH; ++h) {
-#pragma unroll
-    for (int m = 0; m < NO; ++m) accO[h][m] = T(0);
-  }
-#pragma unroll
-  for (int m = 0; m < NR; ++m) accR[m] = T(0);
-  int run_n = -1;
-  // PF: the next entry's words are loaded while this entry computes (issued once this
-  // entry's LDS operands have arrived, so that their wait does not cover the prefetch)
-  constexpr bool PF = L <= kAdjPrefetchMaxL;
-  int nx_o1 = 0, nx_o2 = 0, nx_run = 0, nx_oth = 0;
-  T nx_c1[NMAX], nx_c2[NMAX];
-  auto fetch = [&](int e) {
-    const int* E = tb.adj_i + (size_t)e * kAdjRec;
-    const T* Ec = reinterpret_cast<const T*>(tb.adj_f) + (size_t)e * kAdjRec;
-    nx_o1 = cld(E);
-    nx_o2 = cld(E + 1);
-    nx_run = cld(E + 2);
-    nx_oth = cld(E + 3);
-#pragma unroll
-    for (int n3 = 0; n3 < NMAX; ++n3) {
-      nx_c1[n3] = cld(Ec + kAdjC1 + n3);
-      nx_c2[n3] = cld(Ec + kAdjC2 + n3);
-    }
-  };
-  if (PF && eb < ee) fetch(eb);
-  for (int e = eb; e < ee; ++e) {
-    if (!PF) fetch(e);
-    const int nrun = nx_run;
-    const int noth = nx_oth;
-    T c1[NMAX], c2[NMAX];
-#pragma unroll
-    for (int n3 = 0; n3 < NMAX; ++n3) {
-      c1[n3] = nx_c1[n3];
-      c2[n3] = nx_c2[n3];
-    }
-    if (nrun != run_n) {
-      if (run_n >= 0) {
-#pragma unroll
-        for (int m = 0; m < NR; ++m) gadd<T, TILE>(Abt, run_n * P2 + LR * LR + m, t, accR[m]);
-      }
-#pragma unroll
-      for (int m = 0; m < NR; ++m) accR[m] = T(0);
-      run_n = nrun;
-    }
-    const int o1 = nx_o1, o2 = nx_o2;
-    T a[N1], b[N2], P[NL], Pb[NL];
-#pragma unroll
-    for (int m = 0; m < N1; ++m) a[m] = As[(o1 + m) * ST + t];
-#pragma unroll
-    for (int m = 0; m < N2; ++m) b[m] = As[(o2 + m) * ST + t];
-#pragma unroll
-    for (int m = 0; m < NL; ++m) {
-      P[m] = T(0);
-      Pb[m] = T(0);
-    }
-    C::template fwd<T>(a, b, P);
-    if constexpr (PF) {
-      __builtin_amdgcn_sched_barrier(0);
-      if (e + 1 < ee) fetch(e + 1);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-#pragma unroll
-    for (int n3 = 0; n3 < NMAX; ++n3) {
-      // the stream's coefficients are zero outside the pair's run of n3 and A3 is zero
-      // beyond n_max: those terms add exact zeros, which costs less than branching on them
-      {
-        const T d = fma(fp, c2[n3], c1[n3]);
-#pragma unroll
-        for (int m = 0; m < NL; ++m) {
-          Pb[m] = fma(d, A3[n3][m], Pb[m]);
-          acc3[n3][m] = fma(d, P[m], acc3[n3][m]);
-        }
-      }
-    }
-    T ga[N1], gb[N2];
-#pragma unroll
-    for (int m = 0; m < N1; ++m) ga[m] = T(0);
-#pragma unroll
-    for (int m = 0; m < N2; ++m) gb[m] = T(0);
-    C::template bwd<T>(a, b, Pb, ga, gb);
-#pragma unroll
-    for (int m = 0; m < NR; ++m) accR[m] += RUN1 ? ga[m] : gb[m];
-    // the other label is wave-uniform: a scalar branch picks its accumulator
-    const int oh = noth - obase;
-#pragma unroll
-    for (int h = 0; h < NH; ++h) {
-      if (h == oh) {
-#pragma unroll
-        for (int m = 0; m < NO; ++m) accO[h][m] += RUN1 ? gb[m] : ga[m];
-      }
-    }
-  }
-  if (run_n >= 0) {
-#pragma unroll
-    for (int m = 0; m < NR; ++m) gadd<T, TILE>(Abt, run_n * P2 + LR * LR + m, t, accR[m]);
-  }
-#pragma unroll
-  for (int h = 0; h < NH; ++h) {
-    if (obase + h < oend) {
-#pragma unroll
-      for (int m = 0; m < NO; ++m) gadd<T, TILE>(Abt, (obase + h) * P2 + LO * LO + m, t, accO[h][m]);
-    }
-  }
-}
-
-// B1 and B2 adjoint of one label n, output-stationary.  B2_(n1 n2 l) = sum_m A_n1lm A_n2lm
-// (n1 <= n2, entries stored in catalogue order (n1, n2, l)), so
-//   dE/dA_nlm = sum_n' D_nn'l A_n'lm,  D_nn'l = d_(min, max, l) for n' != n, 2 d_(n n l) for n' = n,
-// with d = c1 + F'(phi2) c2 of the entry; plus the B1 entry of label n.  The label's
-// adjoint is accumulated in registers and added once per (l, m).
-template <class T, int LMAX, int TILE>
-__device__ __forceinline__ void low_order_unit(const T* __restrict__ As, T* __restrict__ Abt, const AceTables<T>& tb,
-                                               int nb1, int n_max, int n, int t, T fp) {
-  constexpr int ST = TILE + 1;
-  constexpr int P2 = (LMAX + 1) * (LMAX + 1);
-  // first entry of the labels n1: sum over n' < n1 of (n_max - n')(l_max + 1)
-  auto base = [&](int n1) { return (LMAX + 1) * (n1 * n_max - n1 * (n1 - 1) / 2); };
-#pragma unroll
-  for (int l = 0; l <= LMAX; ++l) {
-    T acc[2 * l + 1];
-#pragma unroll
-    for (int m = 0; m < 2 * l + 1; ++m) acc[m] = T(0);
-    for (int np = 0; np < n_max; ++np) {
-      const int n1 = np < n ? np : n, n2 = np < n ? n : np;
-      const int e = base(n1) + (n2 - n1) * (LMAX + 1) + l;
-      T d = fma(fp, cld(tb.b2_c2 + e), cld(tb.b2_c1 + e));
-      if (np == n) d += d;
-      const int o = np * P2 + l * l;
-#pragma unroll
-      for (int m = 0; m < 2 * l + 1; ++m) acc[m] = fma(d, As[(o + m) * ST + t], acc[m]);
-    }
-    if (l == 0 && n < nb1) acc[0] += fma(fp, cld(tb.b1_c2 + n), cld(tb.b1_c1 + n));
-#pragma unroll
-    for (int m = 0; m < 2 * l + 1; ++m) gadd<T, TILE>(Abt, n * P2 + l * l + m, t, acc[m]);
-  }
-}
-
-// coupled degree triples (l1, l2, L) for l_max 3 and 4
-#define APX_UNIT_CASES_3(X) \
-  X(0, 0, 0) X(0, 1, 1) X(0, 2, 2) X(0, 3, 3) X(1, 0, 1) X(1, 1, 0) X(1, 1, 2) X(1, 2, 1) \
-  X(1, 2, 3) X(1, 3, 2) X(2, 0, 2) X(2, 1, 1) X(2, 1, 3) X(2, 2, 0) X(2, 2, 2) X(2, 3, 1) \
-  X(2, 3, 3) X(3, 0, 3) X(3, 1, 2) X(3, 2, 1) X(3, 2, 3) X(3, 3, 0) X(3, 3, 2)
-#define APX_UNIT_CASES_4(X) \
-  X(0, 0, 0) X(0, 1, 1) X(0, 2, 2) X(0, 3, 3) X(0, 4, 4) X(1, 0, 1) X(1, 1, 0) X(1, 1, 2) \
-  X(1, 2, 1) X(1, 2, 3) X(1, 3, 2) X(1, 3, 4) X(1, 4, 3) X(2, 0, 2) X(2, 1, 1) X(2, 1, 3) \
-  X(2, 2, 0) X(2, 2, 2) X(2, 2, 4) X(2, 3, 1) X(2, 3, 3) X(2, 4, 2) X(2, 4, 4) X(3, 0, 3) \
-  X(3, 1, 2) X(3, 1, 4) X(3, 2, 1) X(3, 2, 3) X(3, 3, 0) X(3, 3, 2) X(3, 3, 4) X(3, 4, 1) \
-  X(3, 4, 3) X(4, 0, 4) X(4, 1, 3) X(4, 2, 2) X(4, 2, 4) X(4, 3, 1) X(4, 3, 3) X(4, 4, 0) \
-  X(4, 4, 2) X(4, 4, 4)
-
-// Stages the tile's atomic base into LDS, [a][TILE + 1] (atom fastest; the padding
-// column keeps the stride odd).  The tile is one contiguous block of the atom-major
-// global array (the buffer holds whole tiles); float32 tiles are read 16 bytes at a
-// time and transposed on the way, values of atoms beyond n_act are zero.
-template <class T, int TILE>
-__device__ __forceinline__ void stage_tile(const T* __restrict__ Ag, T* As, int q0, int n_act, int na, int nthr) {
-  constexpr int ST = TILE + 1;
-  if constexpr (sizeof(T) == 4) {
-    const T* src = Ag + (size_t)q0 * na;
-    const int total = TILE * na;
-    const int rem = n_act - q0;
-    const int valid = (rem < TILE ? rem : TILE) * na;
-    for (int e4 = threadIdx.x * 4; e4 < total; e4 += nthr * 4) {
-      float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (e4 + 3 < valid) {
-        v = *reinterpret_cast<const float4*>(src + e4);
-      } else {
-        if (e4 < valid) v.x = src[e4];
-        if (e4 + 1 < valid) v.y = src[e4 + 1];
-        if (e4 + 2 < valid) v.z = src[e4 + 2];
-      }
-      int t = e4 / na, a = e4 - t * na;
-      const T vv[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        if (e4 + k < total) As[a * ST + t] = vv[k];
-        if (++a == na) {
-          a = 0;
-          ++t;
-        }
-      }
-    }
-  } else {
-    for (int e = threadIdx.x; e < TILE * na; e += nthr) {
-      const int t = e / na, a = e - t * na;
-      const int q = q0 + t;
-      As[a * ST + t] = q < n_act ? Ag[(size_t)q * na + a] : T(0);
-    }
-  }
-}
-
-// Energy pass of the float32 product basis: 64 active atoms per block (lane = atom), the
-// label pairs dealt round-robin to the waves, compensated sums of c1.B and c2.B, then
-// E_i = phi1 + F_eps(phi2) (+ anchor) and the embedding slope F_eps'(phi2) for the adjoint.
-template <class T, int LMAX, int NMAX, int TILE, int NW, bool COMP>
-__global__ void __launch_bounds__(NW * 64, NW / 2) k_ace_energy(const T* __restrict__ Ag, int n_act, int na, int n_max,
-                                                        AceTables<T> tb, int nb1, int nb2, T eps,
-                                                        const double* __restrict__ e_anch,
-                                                        const int* __restrict__ active, double* __restrict__ e_site,
-                                                        T* __restrict__ fp_out) {
-  extern __shared__ double smem_raw[];
-  T* As = reinterpret_cast<T*>(smem_raw);
-  T* red = As;  // [NW][4][TILE], over the tile once every wave is done with it
-  const int tid = threadIdx.x;
-  const int q0 = blockIdx.x * TILE;
-  stage_tile<T, TILE>(Ag, As, q0, n_act, na, NW * 64);
-  __syncthreads();
-  const int lane = tid & 63;
-  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);  // uniform across the wave
-  const int t = lane % TILE;
-  Acc<T> acc{T(0), T(0), T(0), T(0)};
-  // lane k < kPairRec holds word k of the wave's next pair record: one vector load per pair,
-  // issued a pair ahead and waited for only when the next pair reads it out
-  int rv = 0;
-  if (wv < tb.npairs && lane < kPairRec) rv = tb.pairs[wv * kPairRec + lane];
-  if (wv == 0) low_order_fwd<T, TILE, COMP>(As, tb, nb1, nb2, t, acc);
-  for (int pi = wv; pi < tb.npairs; pi += NW) {
-    int rec[kPairRec];
-#pragma unroll
-    for (int k = 0; k < kPairRec; ++k) rec[k] = __builtin_amdgcn_readlane(rv, k);
-    if (pi + NW < tb.npairs && lane < kPairRec) rv = tb.pairs[(pi + NW) * kPairRec + lane];
-    const int type = rec[2];
-#define APX_FWD(A_, B_) \
-  case A_ * (LMAX + 1) + B_: pair_fwd_n<T, LMAX, NMAX, TILE, COMP, A_, B_>(As, rec, tb, t, n_max, acc); break;
-    if constexpr (LMAX == 3) {
-      switch (type) { APX_PAIR_CASES_3(APX_FWD) default: break; }
-    } else {
-      switch (type) { APX_PAIR_CASES_4(APX_FWD) default: break; }
-    }
-#undef APX_FWD
-  }
-  __syncthreads();
-  if (lane < TILE) {
-    red[(wv * 4 + 0) * TILE + t] = acc.s1;
-    red[(wv * 4 + 1) * TILE + t] = acc.e1;
-    red[(wv * 4 + 2) * TILE + t] = acc.s2;
-    red[(wv * 4 + 3) * TILE + t] = acc.e2;
-  }
-  __syncthreads();
-  if (wv == 0 && lane < TILE) {
-    T s1 = T(0), e1 = T(0), s2 = T(0), e2 = T(0);
-    for (int v = 0; v < NW; ++v) {
-      acc_add<T, COMP>(s1, e1, T(1), red[(v * 4 + 0) * TILE + t]);
-      e1 += red[(v * 4 + 1) * TILE + t];
-      acc_add<T, COMP>(s2, e2, T(1), red[(v * 4 + 2) * TILE + t]);
-      e2 += red[(v * 4 + 3) * TILE + t];
-    }
-    T dfdx;
-    const T f2 = feps<T>(s2 + e2, eps, dfdx);
-    const int q = q0 + t;
-    fp_out[q] = q < n_act ? dfdx : T(0);
-    if (q < n_act) e_site[active[q]] = (double)(s1 + e1) + (double)f2 + e_anch[q];
-  }
-}
-
-// Degrees 0..3 run at two waves per SIMD (their units hold at most 3 and 2 other labels in
-// degrees 2 and 3); degree 4 needs one wave per SIMD.
-// Adjoint of the product basis for the units of one launch group G: the tile's atomic
-// base is staged again, the embedding slope is read from the energy pass, and every
-// wave runs its units (see unit_bwd), adding to the tile's adjoint in global memory.
-template <class T, int LMAX, int NMAX, int TILE, int NW, int G>
-__global__ void __launch_bounds__(NW * 64, G <= 3 ? 2 : 1) k_ace_adjoint(const T* __restrict__ Ag, T* __restrict__ Abg,
-                                                            int n_act, int na, int n_max, AceTables<T> tb, int nb1,
-                                                            const T* __restrict__ fp_in) {
-  static_assert(NW == kUnitWaves, "the unit tables are dealt to kUnitWaves waves");
-  extern __shared__ double smem_raw[];
-  T* As = reinterpret_cast<T*>(smem_raw);
-  const int tid = threadIdx.x;
-  const int q0 = blockIdx.x * TILE;
-  stage_tile<T, TILE>(Ag, As, q0, n_act, na, NW * 64);
-  __syncthreads();
-  const int lane = tid & 63;
-  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);  // uniform across the wave
-  const int t = lane % TILE;
-  const T fp = fp_in[q0 + t];
-  T* Abt = Abg + (size_t)blockIdx.x * na * TILE;
-  const int* wu = tb.wave_units;
-  const int* lst = wu + kUnitGroups * (NW + 1);
-  // the third-block degree of the group's units
-  constexpr int LG = G;
-  T A3[NMAX][2 * LG + 1], acc3[NMAX][2 * LG + 1];
-  third_load<T, LMAX, NMAX, TILE, LG>(As, n_max, t, A3, acc3);
-  const int ub = __builtin_amdgcn_readfirstlane(cld(wu + G * (NW + 1) + wv));
-  const int ue = __builtin_amdgcn_readfirstlane(cld(wu + G * (NW + 1) + wv + 1));
-  for (int k = ub; k < ue; ++k) {
-    const int u = cld(lst + k);
-    const int* ur = tb.units + u * kUnitRec;
-    const int type = cld(ur);
-    const int L = cld(ur + 1);
-    const int pb = cld(ur + 2);
-    const int obase = cld(ur + 4);
-    const int eb = cld(ur + 5);
-    const int ee = cld(ur + 6);
-    const int oend = cld(ur + 7);
-    if (L < 0) {
-      if constexpr (G == 0) low_order_unit<T, LMAX, TILE>(As, Abt, tb, nb1, n_max, pb, t, fp);
-      continue;
-    }
-    const int key = type * (LMAX + 1) + L;
-    // every unit of the group has degree LG; the third-block registers persist across the
-    // wave's units
-#define APX_UNIT(A_, B_, C_)                                                                              \
-  case (A_ * (LMAX + 1) + B_) * (LMAX + 1) + C_:                                                          \
-    if constexpr (C_ == LG)                                                                               \
-      unit_bwd<T, LMAX, NMAX, TILE, A_, B_, C_>(As, Abt, tb, eb, ee, obase, oend, t, fp, A3, acc3);       \
-    break;
-    if constexpr (LMAX == 3) {
-      switch (key) { APX_UNIT_CASES_3(APX_UNIT) default: break; }
-    } else {
-      switch (key) { APX_UNIT_CASES_4(APX_UNIT) default: break; }
-    }
-#undef APX_UNIT
-  }
-  third_flush<T, LMAX, NMAX, TILE, NW, LG>(Abt, As, n_max, t, wv, lane, acc3);
-}
-
-// Clears m values of T at p with 16-byte stores (p 16-byte aligned, m * sizeof(T) a multiple
-// of 16: the adjoint's tile regions).
-template <class T>
-__global__ void k_fill_zero_t(T* __restrict__ p, long long m) {
-  const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < m * (long long)sizeof(T) / 16) reinterpret_cast<float4*>(p)[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-}
-
 __global__ void k_fill_zero(double* __restrict__ p, long long m) {
   long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < m) p[i] = 0.0;
@@ -1404,18 +847,21 @@ apx_status ace_run(apx_ctx* ctx, const apx_atoms* atoms, const apx_nlist* nl, co
   constexpr int LM = (LMAX + 1) * (LMAX + 1);
   const int n = (int)atoms->n;
   const int na = m->na;
+  // float32 without coefficient gradients: the symmetric product kernels
+  const bool sym = sizeof(T) == 4 && dc1 == nullptr;
   const long long n_pad = (long long)((n_act + TILE - 1) / TILE) * TILE;
-  const size_t bytes_A = sizeof(T) * (size_t)n_pad * na;
-  APX_ALLOC(ctx, buf, 2 * bytes_A + 2 * sizeof(double) * (size_t)n_act + sizeof(T) * (size_t)n_pad + 512);
   AceScratch<T> sc;
-  sc.A = buf.as<T>();
-  sc.Ab = reinterpret_cast<T*>(reinterpret_cast<char*>(buf.p) + bytes_A);
-  sc.e_anch = reinterpret_cast<double*>(reinterpret_cast<char*>(buf.p) + 2 * bytes_A);
+  sc.stride = sym ? sym_stride(na) : na;
+  const size_t bytes_A = sizeof(T) * (size_t)n_pad * sc.stride;
+  const size_t bytes_anch = sizeof(double) * 2 * (((size_t)n_act + 31) / 32 * 32);
+  const size_t bytes_more = sym ? sym_scratch<float>(m, n_act) : bytes_A;
+  APX_ALLOC(ctx, buf, bytes_A + bytes_anch + bytes_more);
+  char* base = static_cast<char*>(buf.p);
+  void* more = base + bytes_A + bytes_anch;
+  sc.A = reinterpret_cast<T*>(base);
+  sc.Ab = sym ? nullptr : static_cast<T*>(more);
+  sc.e_anch = reinterpret_cast<double*>(base + bytes_A);
   sc.fp_anch = sc.e_anch + n_act;
-  sc.fp = reinterpret_cast<T*>(sc.fp_anch + n_act + 32);
-  // float32 without coefficient gradients: unit adjoint with register accumulation
-  const bool use_units = sizeof(T) == 4 && dc1 == nullptr;
-  sc.tile_size = use_units ? TILE : 0;
   BoxDev b = make_box(atoms);
   AnchorDev an{};
   an.on = m->anchored;
@@ -1440,79 +886,12 @@ apx_status ace_run(apx_ctx* ctx, const apx_atoms* atoms, const apx_nlist* nl, co
   int lds_max = 0;
   APX_HIP(ctx, hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, ctx->device));
   if constexpr (sizeof(T) == 4) {
-  if (use_units) {
-    constexpr int NWU = kUnitWaves;
-    const size_t ldsu = sizeof(T) * ((size_t)na * (TILE + 1) + NWU * 4 * TILE + TILE);
-    if (ldsu > (size_t)lds_max)
-      return fail(ctx, APX_EINVAL, "ACE tile needs %zu bytes of LDS, the device allows %d (reduce n_max)", ldsu, lds_max);
-    const long long nab = n_pad * na;
-    {
-      ProfScope ps(ctx, "ace.zero");
-      static_assert(TILE * sizeof(T) % 16 == 0, "tile regions are whole 16-byte groups");
-      k_fill_zero_t<T><<<blocks_for(nab * (long long)sizeof(T) / 16, 256), 256, 0, ctx->stream>>>(sc.Ab, nab);
-      APX_LAUNCH_CHECK(ctx);
+    if (sym) {
+      const apx_status s = sym_products<T>(ctx, m, sc.A, n_act, sc.e_anch, active, e_site, more);
+      if (s != APX_OK) return s;
     }
-    const unsigned nblk = (unsigned)((n_act + TILE - 1) / TILE);
-    // the energy pass needs few registers: 16 waves share a staged tile (at most 64 VGPRs,
-    // two tiles per CU, eight waves per SIMD at n_max 10, l_max 4; the reduction buffer
-    // reuses the tile)
-    constexpr int NWE = 16;
-    const size_t ldse = sizeof(T) * std::max((size_t)na * (TILE + 1), (size_t)NWE * 4 * TILE);
-    const size_t ldsa = sizeof(T) * (size_t)na * (TILE + 1);
-    auto energy = [&](auto kern) -> apx_status {
-      if (ensure_lds(ctx, (const void*)kern, ldse) != APX_OK) return APX_EDEVICE;
-      ProfScope ps(ctx, "ace.energy");
-      kern<<<nblk, NWE * 64, ldse, ctx->stream>>>(sc.A, n_act, na, m->n_max, tb, m->nb1, m->nb2, (T)m->eps,
-                                                  sc.e_anch, active, e_site, sc.fp);
-      APX_LAUNCH_CHECK(ctx);
-      return APX_OK;
-    };
-    auto adjoint = [&](int nmax_t, auto k0, auto k1, auto k2, auto k3, auto k4) -> apx_status {
-      ProfScope ps(ctx, "ace.adjoint");
-      static_assert(kUnitGroups == 5, "one kernel per launch group");
-      const void* ks[kUnitGroups] = {(const void*)k0, (const void*)k1, (const void*)k2, (const void*)k3,
-                                     (const void*)k4};
-      for (int g = 0; g < kUnitGroups; ++g) {
-        if (m->group_units[g] == 0) continue;
-        // the staged tile, or the third-block reduction of the group if larger
-        const size_t red = sizeof(T) * (size_t)(NWU / 2) * nmax_t * (2 * g + 1) * 64;
-        const size_t ldsg = ldsa > red ? ldsa : red;
-        if (ldsg > (size_t)lds_max) return fail(ctx, APX_EINVAL, "ACE adjoint needs %zu bytes of LDS", ldsg);
-        if (ensure_lds(ctx, ks[g], ldsg) != APX_OK) return APX_EDEVICE;
-        if (g == 0) k0<<<nblk, NWU * 64, ldsg, ctx->stream>>>(sc.A, sc.Ab, n_act, na, m->n_max, tb, m->nb1, sc.fp);
-        if (g == 1) k1<<<nblk, NWU * 64, ldsg, ctx->stream>>>(sc.A, sc.Ab, n_act, na, m->n_max, tb, m->nb1, sc.fp);
-        if (g == 2) k2<<<nblk, NWU * 64, ldsg, ctx->stream>>>(sc.A, sc.Ab, n_act, na, m->n_max, tb, m->nb1, sc.fp);
-        if (g == 3) k3<<<nblk, NWU * 64, ldsg, ctx->stream>>>(sc.A, sc.Ab, n_act, na, m->n_max, tb, m->nb1, sc.fp);
-        if (g == 4) k4<<<nblk, NWU * 64, ldsg, ctx->stream>>>(sc.A, sc.Ab, n_act, na, m->n_max, tb, m->nb1, sc.fp);
-        APX_LAUNCH_CHECK(ctx);
-      }
-      return APX_OK;
-    };
-    apx_status s;
-#define APX_PRODUCTS(LM_, NM_)                                                                          \
-  s = energy(k_ace_energy<T, LM_, NM_, TILE, NWE, true>);                                               \
-  if (s == APX_OK)                                                                                      \
-    s = adjoint(NM_, k_ace_adjoint<T, LM_, NM_, TILE, NWU, 0>, k_ace_adjoint<T, LM_, NM_, TILE, NWU, 1>, \
-                k_ace_adjoint<T, LM_, NM_, TILE, NWU, 2>, k_ace_adjoint<T, LM_, NM_, TILE, NWU, 3>,     \
-                k_ace_adjoint<T, LM_, NM_, TILE, NWU, 4>);
-    if constexpr (LMAX == 3) {
-      if (m->n_max <= 8) {
-        APX_PRODUCTS(3, 8)
-      } else {
-        APX_PRODUCTS(3, 12)
-      }
-    } else {
-      if (m->n_max <= 10) {
-        APX_PRODUCTS(4, 10)
-      } else {
-        APX_PRODUCTS(4, 12)
-      }
-    }
-#undef APX_PRODUCTS
-    if (s != APX_OK) return s;
   }
-  }
-  if (!use_units) {
+  if (!sym) {
     // the LDS version (float64, or float32 with coefficient gradients) stages the tile's
     // A and its adjoint; for large bases the tile is halved so that both fit
     constexpr int NW = sizeof(T) == 4 ? kAceWaves32 : kAceWaves64;
@@ -1545,11 +924,6 @@ apx_status ace_run(apx_ctx* ctx, const apx_atoms* atoms, const apx_nlist* nl, co
       return fail(ctx, APX_EINVAL, "ACE tile needs %zu bytes of LDS, the device allows %d (reduce n_max)",
                   lds_for(TILE / 2), lds_max);
     if (s != APX_OK) return s;
-  }
-  if (use_units) {
-    ProfScope ps(ctx, "ace.backproject");
-    k_ace_backproject<T, LMAX><<<(unsigned)(n_pad / TILE), 256, 0, ctx->stream>>>(sc.Ab, sc.A, tb.Wp, m->n_max, na);
-    APX_LAUNCH_CHECK(ctx);
   }
   ProfScope ps(ctx, "ace.force");
   auto force = [&](auto nmax_c) {

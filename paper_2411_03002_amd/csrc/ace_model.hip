@@ -10,6 +10,7 @@
 
 #include "ace_coupling_gen.h"
 #include "ace_model.h"
+#include "ace_sym_gen.h"
 
 namespace apx {
 namespace {
@@ -70,8 +71,8 @@ int terms3_of(int l_max, int l1, int l2, int L) {
 
 struct Catalogue {
   long long n_basis = 0;
-  std::vector<int> pairs, t_v, b1_off, b1_v, b2_off, b2_v, units, wave_units, adj_ent;
-  int group_units[kUnitGroups] = {};
+  std::vector<int> pairs, t_v, b1_off, b1_v, b2_off, b2_v;
+  std::vector<int> index3;  // basis index of the triple p1 <= p2 <= p3, [p1][p2][p3]
   int ntrip = 0;
   long long coupling_terms = 0, triple_width = 0;
 };
@@ -108,11 +109,13 @@ Catalogue build_catalogue(int n_max, int l_max) {
     double cost;
   };
   auto lkey = [LL](int p) { return std::make_pair(p % LL, p / LL); };
+  c.index3.assign((size_t)P * P * P, -1);
   std::map<std::pair<int, int>, std::vector<std::vector<std::pair<int, int>>>> groups;  // (n3, v) by L
   for (int p1 = 0; p1 < P; ++p1)
     for (int p2 = p1; p2 < P; ++p2)
       for (int p3 = p2; p3 < P; ++p3) {
         if (!coupled(p1 % LL, p2 % LL, p3 % LL)) continue;
+        c.index3[(p1 * P + p2) * P + p3] = (int)v;
         std::array<int, 3> s3 = {p1, p2, p3};
         std::sort(s3.begin(), s3.end(), [&](int a, int b) { return lkey(a) < lkey(b); });
         auto& g = groups[{s3[1], s3[2]}];
@@ -156,7 +159,7 @@ Catalogue build_catalogue(int n_max, int l_max) {
   c.n_basis = v;
   // group the pairs by coupling type so that a wave stays in one specialisation for
   // long runs of pairs (instruction-cache locality); within a type order them by the
-  // label of larger degree (the run label of the adjoint units), then the other label
+  // label of larger degree, then the other label
   auto key = [LL](const PairTmp& a) {
     const int l1 = a.rec[2] / LL, l2 = a.rec[2] % LL;
     const int run = l1 >= l2 ? a.rec[3] : a.rec[15];
@@ -174,119 +177,87 @@ Catalogue build_catalogue(int n_max, int l_max) {
     cost.push_back(pt.cost);
   }
   c.ntrip = base;
-  // adjoint units (type, L) over the contiguous pair range of each type, plus the B1/B2
-  // units, dealt to the waves by longest processing time first
-  std::vector<std::array<int, kUnitRec>> units;
-  std::vector<double> ucost;
-  {
-    // a unit (type, L) covers the pairs whose other label lies in [obase, oend); the
-    // ranges are cut by cost so that every launch group has at least two units per wave
-    int ntypes[kUnitGroups] = {};
-    for (size_t q = 0; q < tmp.size(); ++q) {
-      if (q > 0 && tmp[q].rec[2] == tmp[q - 1].rec[2]) continue;
-      const int l1 = tmp[q].rec[2] / LL, l2 = tmp[q].rec[2] % LL;
-      for (int L = 0; L < LL; ++L) {
-        bool any = false;
-        for (size_t k = q; k < tmp.size() && tmp[k].rec[2] == tmp[q].rec[2]; ++k)
-          any = any || tmp[k].rec[5 + L] > tmp[k].rec[4 + L];
-        if (any && coupled(l1, l2, L)) ++ntypes[unit_group(L)];
-      }
+  return c;
+}
+
+// Tables of the symmetric product kernels for groups of `width` pairs (1: float32, 4: float64):
+// the offsets, the pairs, and per coefficient slot the basis index and its factor (the number of
+// times the output block occurs in the function times the scale of the generated coupling).
+// A group of one pair is a row of 2 NMAX values; of four pairs the operand layout of the float64
+// instructions: 16 rows x 4 pairs with the row fastest, then 4 rows x 4 pairs each.
+struct SymHost {
+  std::vector<int> off, pairs, v;
+  std::vector<double> m;
+};
+
+SymHost build_sym(const Catalogue& c, int n_max, int l_max, int width) {
+  SymHost s;
+  s.off.assign(kSymOff, 0);
+  const int LL = l_max + 1, P = n_max * LL, LM = LL * LL, R = 2 * sym_nmax(n_max);
+  // value(row o, member k) of one group, appended in the group's layout
+  auto group = [&](auto&& value) {
+    auto put = [&](int o, int k) {
+      const std::pair<int, double> e = value(o, k);
+      s.v.push_back(e.first < 0 ? -1 : 2 * e.first + (o & 1));
+      s.m.push_back(e.second);
+    };
+    if (width == 1) {
+      for (int o = 0; o < R; ++o) put(o, 0);
+      return;
     }
-    int q = 0;
-    const int np = (int)tmp.size();
-    while (q < np) {
-      int e = q;
-      while (e < np && tmp[e].rec[2] == tmp[q].rec[2]) ++e;
-      const int type = tmp[q].rec[2];
-      const int l1 = type / LL, l2 = type % LL;
+    for (int k = 0; k < 4; ++k)
+      for (int o = 0; o < 16; ++o) put(o, k);
+    for (int b = 16; b < R; b += 4)
+      for (int k = 0; k < 4; ++k)
+        for (int o = b; o < b + 4; ++o) put(o, k);
+  };
+  for (int l2 = 0; l2 < LL; ++l2)
+    for (int l1 = 0; l1 <= l2; ++l1) {
+      const int t = l2 * (l2 + 1) / 2 + l1;
+      std::vector<std::pair<int, int>> nn;
+      for (int n2 = 0; n2 < n_max; ++n2)
+        for (int n1 = l1 == l2 ? n2 : 0; n1 < n_max; ++n1) nn.push_back({n1, n2});
+      const int ng = ((int)nn.size() + width - 1) / width;
+      s.off[kSymPairs + t] = (int)s.pairs.size();
+      s.off[kSymNg + t] = ng;
+      for (int p = 0; p < ng * width; ++p) {
+        const auto q = p < (int)nn.size() ? nn[p] : std::make_pair(0, 0);
+        s.pairs.push_back((q.first * LM + l1 * l1) | ((q.second * LM + l2 * l2) << 16));
+      }
       for (int L = 0; L < LL; ++L) {
         if (!coupled(l1, l2, L)) continue;
-        std::vector<double> cost_o(n_max, 0.0);
-        for (int k = q; k < e; ++k) {
-          const int noth = l1 >= l2 ? tmp[k].rec[15] : tmp[k].rec[3];
-          const int nt = tmp[k].rec[5 + L] - tmp[k].rec[4 + L];
-          if (nt > 0) cost_o[noth] += 40.0 + 6.0 * nt * (2 * L + 1) + 3.0 * (2 * l1 + 1) * (2 * l2 + 1);
-        }
-        double total = 0.0;
-        for (double x : cost_o) total += x;
-        if (total <= 0.0) continue;
-        const int nt_g = std::max(1, ntypes[unit_group(L)]);
-        const int parts = std::max(2, (2 * kUnitWaves + nt_g - 1) / nt_g);
-        int b = 0;
-        double acc = 0.0;
-        int made = 0;
-        for (int o = 0; o < n_max; ++o) {
-          acc += cost_o[o];
-          const bool cut = o == n_max - 1 || o - b + 1 == unit_width(unit_group(L), n_max) ||
-                           acc >= total * (made + 1) / parts;
-          if (!cut) continue;
-          double cst = 0.0;
-          for (int x = b; x <= o; ++x) cst += cost_o[x];
-          if (cst > 0.0) {
-            units.push_back({type, L, q, e, b, 0, 0, o + 1});
-            ucost.push_back(cst + 30.0 * n_max * (2 * L + 1));
-          }
-          ++made;
-          b = o + 1;
-        }
+        s.off[t * 5 + L] = (int)s.v.size();
+        for (int g = 0; g < ng; ++g)
+          group([&](int o, int k) -> std::pair<int, double> {
+            const int p = g * width + k, n3 = o >> 1;
+            if (p >= (int)nn.size() || n3 >= n_max) return {-1, 0.0};
+            const int r = n3 * LL + L;
+            std::array<int, 3> q = {r, nn[p].first * LL + l1, nn[p].second * LL + l2};
+            const int times = 1 + (q[1] == r) + (q[2] == r);
+            std::sort(q.begin(), q.end());
+            return {c.index3[(q[0] * P + q[1]) * P + q[2]], times * kSymScale[l1][l2][L]};
+          });
       }
-      q = e;
     }
-    // B1/B2: one unit per first label n1 (its B1 entry and its B2 entries n2 >= n1)
-    for (int n1 = 0; n1 < n_max; ++n1) {
-      double cst = 3.0;
-      for (int l = 0; l < LL; ++l) cst += (n_max - n1) * (2 * l + 1) * 6.0 + (2 * l + 1) * 3.0;
-      units.push_back({0, -1, n1, 0, 0, 0, 0, 0});
-      ucost.push_back(cst);
-    }
+  for (int L = 0; L < LL; ++L) {
+    s.off[kSymB2 + L] = (int)s.v.size();
+    for (int g = 0; g * width < n_max; ++g)
+      group([&](int o, int k) -> std::pair<int, double> {
+        const int n = g * width + k, n3 = o >> 1;
+        if (n >= n_max || n3 >= n_max) return {-1, 0.0};
+        const int a = std::min(n, n3), b = std::max(n, n3);
+        // second-order functions follow the n_max first-order ones in the order (n1, n2, l)
+        const int v = n_max + LL * (a * n_max - a * (a - 1) / 2 + b - a) + L;
+        return {v, a == b ? 2.0 : 1.0};
+      });
   }
-  // the pair stream of every (type, L) unit: the pairs of its half that have third blocks
-  // of degree L, in pair order (by run label, then other label)
-  for (auto& u : units) {
-    if (u[1] < 0) continue;
-    const int L = u[1], type = u[0];
-    const int l1 = type / LL, l2 = type % LL;
-    u[5] = (int)(c.adj_ent.size() / kAdjEnt);
-    for (int k = u[2]; k < u[3]; ++k) {
-      const int* r = tmp[k].rec;
-      if (r[5 + L] <= r[4 + L]) continue;
-      const int nrun = l1 >= l2 ? r[3] : r[15];
-      const int noth = l1 >= l2 ? r[15] : r[3];
-      if (noth < u[4] || noth >= u[7]) continue;
-      const int n30 = (r[10 + L] - L * L) / (LL * LL);
-      c.adj_ent.insert(c.adj_ent.end(), {r[0], r[1], nrun, noth, n30, r[4 + L], r[5 + L] - r[4 + L]});
-    }
-    u[6] = (int)(c.adj_ent.size() / kAdjEnt);
+  // the kernels read one group ahead
+  for (int k = 0; k < width * R; ++k) {
+    s.v.push_back(-1);
+    s.m.push_back(0.0);
   }
-  // each launch group is dealt to the waves separately, longest processing time first
-  for (auto& u : units) c.units.insert(c.units.end(), u.begin(), u.end());
-  c.wave_units.assign(kUnitGroups * (kUnitWaves + 1), 0);
-  std::vector<int> order(units.size());
-  for (size_t k = 0; k < order.size(); ++k) order[k] = (int)k;
-  std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return ucost[a] > ucost[b]; });
-  for (int g = 0; g < kUnitGroups; ++g) {
-    std::vector<std::vector<int>> per(kUnitWaves);
-    std::vector<double> load(kUnitWaves, 0.0);
-    for (int u : order) {
-      if (unit_group(units[u][1]) != g) continue;
-      int best = 0;
-      for (int w = 1; w < kUnitWaves; ++w)
-        if (load[w] < load[best]) best = w;
-      per[best].push_back(u);
-      load[best] += ucost[u];
-      ++c.group_units[g];
-    }
-    int* off = c.wave_units.data() + g * (kUnitWaves + 1);
-    off[0] = (int)c.wave_units.size() - kUnitGroups * (kUnitWaves + 1);
-    for (int w = 0; w < kUnitWaves; ++w) {
-      // within a wave, keep units of one type together
-      std::sort(per[w].begin(), per[w].end());
-      c.wave_units.insert(c.wave_units.end(), per[w].begin(), per[w].end());
-      off = c.wave_units.data() + g * (kUnitWaves + 1);
-      off[w + 1] = (int)c.wave_units.size() - kUnitGroups * (kUnitWaves + 1);
-    }
-  }
-  return c;
+  for (int k = 0; k < 2 * width; ++k) s.pairs.push_back(0);
+  return s;
 }
 
 }  // namespace
@@ -337,24 +308,45 @@ static void fill_reals(std::vector<T>& out, const apx_ace_model* m, const Catalo
   offs[7] = out.size();
 }
 
-// The adjoint pair stream with the coefficients of the current model (kAdjRec words per
-// entry; coefficients as float32).
-static std::vector<int32_t> adjoint_stream(const apx_ace_model* m, const double* c1, const double* c2) {
-  const size_t ne = m->adj_ent.size() / kAdjEnt;
-  std::vector<int32_t> out(ne * kAdjRec, 0);
-  for (size_t e = 0; e < ne; ++e) {
-    const int* a = m->adj_ent.data() + kAdjEnt * e;
-    int32_t* o = out.data() + e * kAdjRec;
-    for (int k = 0; k < 5; ++k) o[k] = a[k];
-    const int n30 = a[4], q0 = a[5], nt = a[6];
-    for (int n3 = n30; n3 < n30 + nt; ++n3) {
-      const int v = m->t_v[q0 + n3 - n30];
-      const float f1 = (float)c1[v], f2 = (float)c2[v];
-      std::memcpy(o + kAdjC1 + n3, &f1, 4);
-      std::memcpy(o + kAdjC2 + n3, &f2, 4);
-    }
+// Coefficient rows of the symmetric product kernels, then the first-order pairs [n_max][2].
+template <class T>
+static void fill_sym(std::vector<T>& out, const std::vector<int>& v, const std::vector<double>& mul, int n_max,
+                     const double* c1, const double* c2) {
+  out.resize(v.size() + 2 * (size_t)n_max);
+  for (size_t k = 0; k < v.size(); ++k)
+    out[k] = v[k] < 0 ? T(0) : (T)(mul[k] * (v[k] & 1 ? c2 : c1)[v[k] >> 1]);
+  for (int n = 0; n < n_max; ++n) {
+    out[v.size() + 2 * n] = (T)c1[n];
+    out[v.size() + 2 * n + 1] = (T)c2[n];
   }
-  return out;
+}
+
+template <class T>
+static hipError_t upload(DevBuf& buf, const std::vector<T>& h) {
+  hipError_t e = buf.ensure(h.size() * sizeof(T));
+  return e == hipSuccess ? hipMemcpy(buf.p, h.data(), h.size() * sizeof(T), hipMemcpyHostToDevice) : e;
+}
+
+// Uploads one precision's tables of the symmetric product kernels.
+template <class T>
+static apx_status sym_upload(apx_ctx* ctx, const Catalogue& c, const apx_ace_model* m, int width, const T* Wp,
+                             const double* c1, const double* c2, std::vector<int>& v, std::vector<double>& mul,
+                             DevBuf& bi, DevBuf& br, SymTables<T>& t) {
+  SymHost s = build_sym(c, m->n_max, m->l_max, width);
+  std::vector<int> ints = s.off;
+  ints.insert(ints.end(), s.pairs.begin(), s.pairs.end());
+  std::vector<T> reals;
+  fill_sym(reals, s.v, s.m, m->n_max, c1, c2);
+  if (upload(bi, ints) != hipSuccess || upload(br, reals) != hipSuccess)
+    return fail(ctx, APX_ENOMEM, "ACE table allocation failed");
+  t.Wp = Wp;
+  t.coef = br.template as<T>();
+  t.b1 = t.coef + s.v.size();
+  t.off = bi.as<int>();
+  t.pairs = t.off + kSymOff;
+  v = std::move(s.v);
+  mul = std::move(s.m);
+  return APX_OK;
 }
 
 template <class T>
@@ -371,8 +363,6 @@ static void set_tables(AceTables<T>& t, const T* base, const size_t* offs, const
   t.b1_v = ib + ioffs[3];
   t.b2_off = ib + ioffs[4];
   t.b2_v = ib + ioffs[5];
-  t.units = ib + ioffs[6];
-  t.wave_units = ib + ioffs[7];
 }
 
 extern "C" apx_status apx_ace_model_create(apx_ctx* ctx, const apx_ace_desc* d, apx_ace_model** out) {
@@ -403,7 +393,6 @@ extern "C" apx_status apx_ace_model_create(apx_ctx* ctx, const apx_ace_desc* d, 
   m->nb1 = (int)c.b1_v.size();
   m->nb2 = (int)c.b2_v.size();
   m->coupling_terms = c.coupling_terms;
-  for (int g = 0; g < kUnitGroups; ++g) m->group_units[g] = c.group_units[g];
   m->triple_width = c.triple_width;
   m->r_cut = d->r_cut;
   m->h = d->h;
@@ -415,12 +404,11 @@ extern "C" apx_status apx_ace_model_create(apx_ctx* ctx, const apx_ace_desc* d, 
   m->t_v = c.t_v;
   m->b1_v = c.b1_v;
   m->b2_v = c.b2_v;
-  m->adj_ent = c.adj_ent;
   // integer tables
   std::vector<int> ib;
-  size_t ioffs[8];
-  const std::vector<int>* parts[8] = {&c.pairs, &c.t_v, &c.b1_off, &c.b1_v, &c.b2_off, &c.b2_v, &c.units, &c.wave_units};
-  for (int q = 0; q < 8; ++q) {
+  size_t ioffs[6];
+  const std::vector<int>* parts[6] = {&c.pairs, &c.t_v, &c.b1_off, &c.b1_v, &c.b2_off, &c.b2_v};
+  for (int q = 0; q < 6; ++q) {
     ioffs[q] = ib.size();
     ib.insert(ib.end(), parts[q]->begin(), parts[q]->end());
   }
@@ -445,17 +433,15 @@ extern "C" apx_status apx_ace_model_create(apx_ctx* ctx, const apx_ace_desc* d, 
   set_tables(m->t32, m->reals32.as<float>(), o32, m->ints.as<int>(), ioffs);
   m->t64.npairs = m->npairs;
   m->t32.npairs = m->npairs;
-  const std::vector<int32_t> adj = adjoint_stream(m, d->c1, d->c2);
-  if (m->adj.ensure(adj.size() * 4 + 4) != hipSuccess) {
+  apx_status st = sym_upload<float>(ctx, c, m, 1, m->t32.Wp, d->c1, d->c2, m->sym_v32, m->sym_m32, m->sym_i32,
+                                    m->sym_r32, m->s32);
+  if (st == APX_OK)
+    st = sym_upload<double>(ctx, c, m, 4, m->t64.Wp, d->c1, d->c2, m->sym_v64, m->sym_m64, m->sym_i64, m->sym_r64,
+                            m->s64);
+  if (st != APX_OK) {
     delete m;
-    return fail(ctx, APX_ENOMEM, "ACE table allocation failed");
+    return st;
   }
-  if (hipMemcpy(m->adj.p, adj.data(), adj.size() * 4, hipMemcpyHostToDevice) != hipSuccess) {
-    delete m;
-    return fail(ctx, APX_EDEVICE, "ACE table upload failed");
-  }
-  m->t32.adj_i = m->adj.as<int>();
-  m->t32.adj_f = m->adj.as<float>();
   *out = m;
   return APX_OK;
 }
@@ -477,8 +463,12 @@ extern "C" apx_status apx_ace_model_set_coeffs(apx_ctx* ctx, apx_ace_model* m, c
   APX_HIP(ctx, hipStreamSynchronize(ctx->stream));
   APX_HIP(ctx, hipMemcpy(m->reals64.p, r64.data(), r64.size() * sizeof(double), hipMemcpyHostToDevice));
   APX_HIP(ctx, hipMemcpy(m->reals32.p, r32.data(), r32.size() * sizeof(float), hipMemcpyHostToDevice));
-  const std::vector<int32_t> adj = adjoint_stream(m, c1, c2);
-  APX_HIP(ctx, hipMemcpy(m->adj.p, adj.data(), adj.size() * 4, hipMemcpyHostToDevice));
+  std::vector<float> y32;
+  std::vector<double> y64;
+  fill_sym(y32, m->sym_v32, m->sym_m32, m->n_max, c1, c2);
+  fill_sym(y64, m->sym_v64, m->sym_m64, m->n_max, c1, c2);
+  APX_HIP(ctx, hipMemcpy(m->sym_r32.p, y32.data(), y32.size() * sizeof(float), hipMemcpyHostToDevice));
+  APX_HIP(ctx, hipMemcpy(m->sym_r64.p, y64.data(), y64.size() * sizeof(double), hipMemcpyHostToDevice));
   return APX_OK;
 }
 

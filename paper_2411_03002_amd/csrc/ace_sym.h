@@ -1,0 +1,27 @@
+// Product basis of the atomic cluster expansion: host interface of the symmetric kernels.
+#pragma once
+
+#include "ace_model.h"
+
+namespace apx {
+
+// Atoms per tile of the product kernels: one per lane in float32; in float64 sixteen, with
+// four label pairs side by side in a wave.
+template <class T>
+constexpr int sym_tile() { return sizeof(T) == 4 ? 64 : 16; }
+
+// Row stride of the atomic base (and of its projected adjoint) in elements: 16-byte groups.
+inline int sym_stride(int na) { return (na + 3) & ~3; }
+
+// Device scratch of sym_products beyond the atomic base, in bytes.
+template <class T>
+size_t sym_scratch(const apx_ace_model* m, int n_act);
+
+// For the atoms active[0..n_act): e_site[active[q]] = E_q (random part plus e_anch[q]) and,
+// in place of the atomic base A [n_pad][sym_stride(na)] (n_pad: n_act rounded up to whole
+// tiles), the projected adjoint B'[lm * n_max + k] = sum_n Wp[l][n][k] dE/dA_nlm.
+template <class T>
+apx_status sym_products(apx_ctx* ctx, const apx_ace_model* m, T* A, int n_act, const double* e_anch,
+                        const int* active, double* e_site, void* scratch);
+
+}  // namespace apx
