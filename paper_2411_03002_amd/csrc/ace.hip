@@ -6,8 +6,8 @@
 //  1. k_ace_basis    one wave per active atom: per neighbour the Chebyshev radial values
 //                    and real solid harmonics, A'[k][lm] = sum_j g_k S_lm, then the radial
 //                    mixing A[n][lm] = sum_k Wp[l][n][k] A'[k][lm] (Wp folds W, N_l, 1/s_a).
-//  2. ace_sym.hip    energies and the adjoint projected back on the radial functions (float32);
-//     k_ace_products float64 and coefficient gradients: lane = atom, the tile held in LDS,
+//  2. ace_sym.hip    energies and the adjoint projected back on the radial functions;
+//     k_ace_products the same with coefficient gradients: lane = atom, the tile held in LDS,
 //                    the coupling list dealt round-robin.  For a label pair (p1, p2) the coupled
 //                    product P_LM = sum G(l1 l2 L; m1 m2 M) A_p1m1 A_p2m2 is formed once and
 //                    every third block p3 >= p2 of degree L contributes B = sum_M P_LM A_p3M.
@@ -847,14 +847,15 @@ apx_status ace_run(apx_ctx* ctx, const apx_atoms* atoms, const apx_nlist* nl, co
   constexpr int LM = (LMAX + 1) * (LMAX + 1);
   const int n = (int)atoms->n;
   const int na = m->na;
-  // float32 without coefficient gradients: the symmetric product kernels
-  const bool sym = sizeof(T) == 4 && dc1 == nullptr;
+  // without coefficient gradients: the symmetric product kernels
+  const bool sym = dc1 == nullptr;
   const long long n_pad = (long long)((n_act + TILE - 1) / TILE) * TILE;
+  static_assert(TILE % sym_tile<T>() == 0, "whole tiles of either kind");
   AceScratch<T> sc;
   sc.stride = sym ? sym_stride(na) : na;
   const size_t bytes_A = sizeof(T) * (size_t)n_pad * sc.stride;
   const size_t bytes_anch = sizeof(double) * 2 * (((size_t)n_act + 31) / 32 * 32);
-  const size_t bytes_more = sym ? sym_scratch<float>(m, n_act) : bytes_A;
+  const size_t bytes_more = sym ? sym_scratch<T>(m, n_act) : bytes_A;
   APX_ALLOC(ctx, buf, bytes_A + bytes_anch + bytes_more);
   char* base = static_cast<char*>(buf.p);
   void* more = base + bytes_A + bytes_anch;
@@ -885,14 +886,12 @@ apx_status ace_run(apx_ctx* ctx, const apx_atoms* atoms, const apx_nlist* nl, co
   }
   int lds_max = 0;
   APX_HIP(ctx, hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, ctx->device));
-  if constexpr (sizeof(T) == 4) {
-    if (sym) {
-      const apx_status s = sym_products<T>(ctx, m, sc.A, n_act, sc.e_anch, active, e_site, more);
-      if (s != APX_OK) return s;
-    }
+  if (sym) {
+    const apx_status s = sym_products<T>(ctx, m, sc.A, n_act, sc.e_anch, active, e_site, more);
+    if (s != APX_OK) return s;
   }
   if (!sym) {
-    // the LDS version (float64, or float32 with coefficient gradients) stages the tile's
+    // the LDS version (with coefficient gradients) stages the tile's
     // A and its adjoint; for large bases the tile is halved so that both fit
     constexpr int NW = sizeof(T) == 4 ? kAceWaves32 : kAceWaves64;
     auto lds_for = [&](int tl) { return sizeof(T) * ((size_t)2 * na * (tl + 1) + NW * 4 * tl + tl); };
@@ -901,17 +900,10 @@ apx_status ace_run(apx_ctx* ctx, const apx_atoms* atoms, const apx_nlist* nl, co
       const size_t lds2 = lds_for(TL);
       const unsigned nblk = (unsigned)((n_act + TL - 1) / TL);
       ProfScope ps(ctx, "ace.products");
-      if (dc1) {
-        auto kern = k_ace_products<T, LMAX, TL, NW, sizeof(T) == 4, true>;
-        if (ensure_lds(ctx, (const void*)kern, lds2) != APX_OK) return APX_EDEVICE;
-        kern<<<nblk, NW * 64, lds2, ctx->stream>>>(sc.A, sc.Ab, n_act, na, tb, m->nb1, m->nb2, (T)m->eps,
-                                                   sc.e_anch, active, w, e_site, dc1, dc2);
-      } else {
-        auto kern = k_ace_products<T, LMAX, TL, NW, sizeof(T) == 4, false>;
-        if (ensure_lds(ctx, (const void*)kern, lds2) != APX_OK) return APX_EDEVICE;
-        kern<<<nblk, NW * 64, lds2, ctx->stream>>>(sc.A, sc.Ab, n_act, na, tb, m->nb1, m->nb2, (T)m->eps,
-                                                   sc.e_anch, active, w, e_site, nullptr, nullptr);
-      }
+      auto kern = k_ace_products<T, LMAX, TL, NW, sizeof(T) == 4, true>;
+      if (ensure_lds(ctx, (const void*)kern, lds2) != APX_OK) return APX_EDEVICE;
+      kern<<<nblk, NW * 64, lds2, ctx->stream>>>(sc.A, sc.Ab, n_act, na, tb, m->nb1, m->nb2, (T)m->eps, sc.e_anch,
+                                                 active, w, e_site, dc1, dc2);
       APX_LAUNCH_CHECK(ctx);
       return APX_OK;
     };

@@ -251,12 +251,12 @@ SymHost build_sym(const Catalogue& c, int n_max, int l_max, int width) {
         return {v, a == b ? 2.0 : 1.0};
       });
   }
-  // the kernels read one group ahead
-  for (int k = 0; k < width * R; ++k) {
+  // the kernels read up to two groups ahead
+  for (int k = 0; k < 2 * width * R; ++k) {
     s.v.push_back(-1);
     s.m.push_back(0.0);
   }
-  for (int k = 0; k < 2 * width; ++k) s.pairs.push_back(0);
+  for (int k = 0; k < 3 * width; ++k) s.pairs.push_back(0);
   return s;
 }
 

@@ -20,7 +20,8 @@
 // instruction.  Measured, 821,266 atoms of the indentation block in float32: energy, five
 // adjoint launches, their zero fill and the back-projection took 16.9 ms; this kernel alone,
 // which does all of it, 5.5 ms (instruction issue: 0.47 M matrix and 0.37 M vector cycles a
-// tile of 64, of 0.95 M measured).
+// tile of 64, of 0.95 M measured).  In float64, 29,150 atoms: 2,850 us in the kernel that dealt
+// pairs to waves and added adjoints in LDS, 477 us here (16x16x4 and 4x4x4 instructions).
 //
 // A block holds one tile of atoms in LDS; its eight waves each own a few components (L, M)
 // of every third block, so that sums of products shared by the degrees L of one M are formed
@@ -203,6 +204,75 @@ struct SymAcc<float, NMAX> {
   }
 };
 
+// float64: four pairs per step, lane = (pair lane / 16, atom lane % 16) (P as the B operand of
+// the 16x16x4 and of the four-block 4x4x4 form, which covers the same atoms four columns a
+// block).  d[r] holds row 4 r + lane / 16 of atom lane % 16, e[k] row 16 + 4 k + lane / 16.  A
+// lane's rows thus belong to one sum, p = (lane / 16) % 2.
+template <int NMAX>
+struct SymAcc<double, NMAX> {
+  static constexpr int R = 2 * NMAX, NB = (R - 16) / 4, TA = 16, kPairs = 4;
+  f64x4 d;
+  double e[NB > 0 ? NB : 1];
+  struct Coef {
+    double c, c4[NB > 0 ? NB : 1];
+  };
+  __device__ __forceinline__ void zero() {
+    d = f64x4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int k = 0; k < NB; ++k) e[k] = 0.0;
+  }
+  static __device__ __forceinline__ unsigned lane_bytes(int lane) { return (unsigned)lane; }
+  static __device__ __forceinline__ Coef load(const double* rows, int g, unsigned lane) {
+    const double* r = rows + g * 4 * R;
+    Coef c;
+    c.c = r[lane];
+#pragma unroll
+    for (int k = 0; k < NB; ++k) c.c4[k] = (r + 64 + 16 * k)[(lane >> 4) * 4 + (lane & 3)];
+    return c;
+  }
+  __device__ __forceinline__ void step(const Coef& c, double P) {
+    d = __builtin_amdgcn_mfma_f64_16x16x4f64(c.c, P, d, 0, 0, 0);
+#pragma unroll
+    for (int k = 0; k < NB; ++k) e[k] = __builtin_amdgcn_mfma_f64_4x4x4f64(c.c4[k], P, e[k], 0, 0, 0);
+  }
+  __device__ __forceinline__ void store(double* out, int lane) const {
+    const int sub = lane >> 4, col = lane & 15;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) out[(4 * r + sub) * TA + col] = d[r];
+#pragma unroll
+    for (int k = 0; k < NB; ++k) out[(16 + 4 * k + sub) * TA + col] = e[k];
+  }
+  static constexpr int kFp = 1;
+  static __device__ __forceinline__ void slopes(const double* fp, int lane, double (&f)[kFp]) { f[0] = fp[lane & 15]; }
+  __device__ __forceinline__ void combine(double* out, int step, int n_max, const double (&fp)[kFp], int lane) const {
+    const int sub = lane >> 4, col = lane & 15;
+    auto put = [&](int n3, double v) {
+      v = sub & 1 ? fp[0] * v : v;
+      v += __shfl_xor(v, 16, kWave);
+      if (!(sub & 1) && n3 < n_max) out[n3 * step + col] = v;
+    };
+#pragma unroll
+    for (int r = 0; r < 4; ++r) put(2 * r + (sub >> 1), d[r]);
+#pragma unroll
+    for (int k = 0; k < NB; ++k) put(8 + 2 * k + (sub >> 1), e[k]);
+  }
+  struct Dot {
+    double s;
+  };
+  static __device__ __forceinline__ void dot_scale(Dot& s, double x) { s.s *= x; }
+  __device__ __forceinline__ void dot(Dot& s, const double* a, int step, int n_max, int lane) const {
+    const int sub = lane >> 4, col = lane & 15;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) s.s = fma(a[min(2 * r + (sub >> 1), n_max - 1) * step + col], d[r], s.s);
+#pragma unroll
+    for (int k = 0; k < NB; ++k) s.s = fma(a[min(8 + 2 * k + (sub >> 1), n_max - 1) * step + col], e[k], s.s);
+  }
+  static __device__ __forceinline__ void dot_reduce(const Dot& s, int lane, double* red) {
+    const double v = s.s + __shfl_xor(s.s, 32, kWave);
+    if (lane < 32) red[lane] = v;  // [p][TA]
+  }
+};
+
 // The components of one wave: codes C = 2 M + (parity of L), each standing for every degree L of
 // that parity with |M| <= L <= LMAX.
 template <class T, int LMAX, int NMAX, int... CS>
@@ -321,13 +391,18 @@ struct SymProg {
       const T* al = As + (lane & (TA - 1));
       const int sub = lane / TA;
       int pk = pt[4 * lo + sub];
+      auto blocks = [&](int w) {
+#pragma unroll
+        for (int m = 0; m < N1; ++m) a[m] = al[((w & 0xffff) + m) * TA];
+#pragma unroll
+        for (int m = 0; m < N2; ++m) b[m] = al[((w >> 16) + m) * TA];
+      };
+      blocks(pk);
+      pk = pt[4 * (lo + 1) + sub];
       for (int p = lo; p < hi; ++p) {
-        const int nx = pt[4 * (p + 1) + sub];
-#pragma unroll
-        for (int m = 0; m < N1; ++m) a[m] = al[((pk & 0xffff) + m) * TA];
-#pragma unroll
-        for (int m = 0; m < N2; ++m) b[m] = al[((pk >> 16) + m) * TA];
+        const int nx = pt[4 * (p + 2) + sub];
         products();
+        blocks(pk);  // the next group's, read while the matrix instructions run
         steps(c);
         static_for<0, LMAX + 1>([&](auto L) {
           if constexpr (couples(L1, L2, L) && has(L)) c[L] = Acc::load(rows[L], p + 1, lb);
@@ -477,11 +552,11 @@ __device__ __forceinline__ void sym_waves(const SymArgs<T>& g, T* As, double* re
 #undef APX_SYM
 }
 
-// The radial mixing Wp[l][n][k] in LDS, rows of NMAX, zero beyond n_max.
+// The radial mixing Wp[l][n][k] in LDS as [l][k][n], rows of NMAX, zero beyond n_max.
 template <class T, int LMAX, int NMAX>
 __device__ __forceinline__ void stage_mixing(const T* Wp, int K, T* ws) {
   for (int e = threadIdx.x; e < (LMAX + 1) * NMAX * NMAX; e += blockDim.x) {
-    const int l = e / (NMAX * NMAX), r = e - l * NMAX * NMAX, nn = r / NMAX, kk = r - nn * NMAX;
+    const int l = e / (NMAX * NMAX), r = e - l * NMAX * NMAX, kk = r / NMAX, nn = r - kk * NMAX;
     ws[e] = nn < K && kk < K ? Wp[((size_t)l * K + nn) * K + kk] : T(0);
   }
 }
@@ -492,15 +567,13 @@ __device__ __forceinline__ int degree_of(int lm) {
   return l;
 }
 
-// v[k] = sum_n Wp[l][n][k] d[n]
+// sum_n Wp[l][n][k] d[n], the row w of (l, k)
 template <class T, int NMAX>
-__device__ __forceinline__ void project(const T* wl, const T (&d)[NMAX], T (&v)[NMAX]) {
+__device__ __forceinline__ T project(const T* w, const T (&d)[NMAX]) {
+  T v = T(0);
 #pragma unroll
-  for (int kk = 0; kk < NMAX; ++kk) v[kk] = T(0);
-#pragma unroll
-  for (int n = 0; n < NMAX; ++n)
-#pragma unroll
-    for (int kk = 0; kk < NMAX; ++kk) v[kk] = fma(wl[n * NMAX + kk], d[n], v[kk]);
+  for (int n = 0; n < NMAX; ++n) v = fma(w[n], d[n], v);
+  return v;
 }
 
 // One tile of atoms and one of nsplit shares of its label pairs per block.  Bound by vector
@@ -543,7 +616,7 @@ __global__ void __launch_bounds__(kSymWaves * 64, 4) k_ace_sym(SymArgs<T> g) {
     __syncthreads();
     // projection in place: column lm's n_max rows give way to its n_max projections
     for (int lm = ch; lm < LM; lm += CH) {
-      T d[NMAX], v[NMAX];
+      T d[NMAX];
 #pragma unroll
       for (int n = 0; n < NMAX; ++n) d[n] = n < K ? As[(n * LM + lm) * TA + t] : T(0);
       if (lm == 0) {
@@ -552,10 +625,8 @@ __global__ void __launch_bounds__(kSymWaves * 64, 4) k_ace_sym(SymArgs<T> g) {
         for (int n = 0; n < NMAX; ++n)
           if (n < K) d[n] += fma(f, g.b1[2 * n + 1], g.b1[2 * n]);
       }
-      project<T, NMAX>(ws + degree_of(lm) * NMAX * NMAX, d, v);
-#pragma unroll
-      for (int kk = 0; kk < NMAX; ++kk)
-        if (kk < K) As[(kk * LM + lm) * TA + t] = v[kk];
+      const T* wl = ws + degree_of(lm) * NMAX * NMAX;
+      for (int kk = 0; kk < K; ++kk) As[(kk * LM + lm) * TA + t] = project<T, NMAX>(wl + kk * NMAX, d);
     }
     __syncthreads();
     for (int o = ch * V; o < na; o += CH * V) {
@@ -609,16 +680,13 @@ __global__ void __launch_bounds__(kFinThreads) k_ace_sym_finish(SymArgs<T> g) {
   if (lm == 0 && q < g.n_act) g.e_site[g.active[q]] = phi[0] + (phi[1] < 0.0 ? -f2 : f2) + g.e_anch[q];
   __syncthreads();
   if (lm < LM) {
-    T v[NMAX];
 #pragma unroll
     for (int n = 0; n < NMAX; ++n) {
       D1[n] = fma(fp, D2[n], D1[n]);
       if (lm == 0 && n < K) D1[n] += fma(fp, g.b1[2 * n + 1], g.b1[2 * n]);
     }
-    project<T, NMAX>(ws + degree_of(lm) * NMAX * NMAX, D1, v);
-#pragma unroll
-    for (int kk = 0; kk < NMAX; ++kk)
-      if (kk < K) rows[r * g.stride + lm * K + kk] = v[kk];
+    const T* wl = ws + degree_of(lm) * NMAX * NMAX;
+    for (int kk = 0; kk < K; ++kk) rows[r * g.stride + lm * K + kk] = project<T, NMAX>(wl + kk * NMAX, D1);
   }
   __syncthreads();
   typedef T vec __attribute__((ext_vector_type(16 / sizeof(T))));
@@ -642,6 +710,8 @@ struct SymPlan {
 // float32 at (10, 4), products + end in us by shares 1/2/4/8: 8 tiles 165/92/59/47, 63 tiles
 // 164/100/73/73, 125 tiles 171/107/95/143, 255 tiles 176/147/210/264, 375 tiles 226/230/257/378,
 // 938 tiles 459/529/632/957; sixteen shares were no better than eight at 1 tile and worse beyond.
+// In float64: 32 tiles 86/55/40/40, 125 tiles 87/64/57/71, 250 tiles 90/83/96/118, 500 tiles
+// 132/148/166/215.
 template <class T>
 SymPlan<T> sym_plan(const apx_ace_model* m, int n_act) {
   constexpr int TA = sym_tile<T>();
@@ -724,5 +794,8 @@ apx_status sym_products(apx_ctx* ctx, const apx_ace_model* m, T* A, int n_act, c
 template size_t sym_scratch<float>(const apx_ace_model*, int);
 template apx_status sym_products<float>(apx_ctx*, const apx_ace_model*, float*, int, const double*, const int*,
                                         double*, void*);
+template size_t sym_scratch<double>(const apx_ace_model*, int);
+template apx_status sym_products<double>(apx_ctx*, const apx_ace_model*, double*, int, const double*, const int*,
+                                         double*, void*);
 
 }  // namespace apx
