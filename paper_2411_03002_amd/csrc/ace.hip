@@ -7,13 +7,7 @@
 //                    and real solid harmonics, A'[k][lm] = sum_j g_k S_lm, then the radial
 //                    mixing A[n][lm] = sum_k Wp[l][n][k] A'[k][lm] (Wp folds W, N_l, 1/s_a).
 //  2. ace_sym.hip    energies and the adjoint projected back on the radial functions;
-//     k_ace_products the same with coefficient gradients: lane = atom, the tile held in LDS,
-//                    the coupling list dealt round-robin.  For a label pair (p1, p2) the coupled
-//                    product P_LM = sum G(l1 l2 L; m1 m2 M) A_p1m1 A_p2m2 is formed once and
-//                    every third block p3 >= p2 of degree L contributes B = sum_M P_LM A_p3M.
-//                    The adjoint pass reuses the same structure with
-//                    d = c1 + F_eps'(phi2) c2: Abar_p3 += d P, Pbar += d A_p3, then Pbar
-//                    is pushed back through the coupling into Abar_p1, Abar_p2.
+//     ace_grad.hip   coefficient gradients.
 //  3. k_ace_force    one wave per active atom: per neighbour the gradient of sum Abar'' g_k
 //                    S_lm, scattered as F_j -= w_i dE_i/dr_ij, F_i += w_i dE_i/dr_ij (float64
 //                    atomics).
@@ -21,7 +15,6 @@
 #include <cmath>
 #include <type_traits>
 
-#include "ace_coupling_gen.h"
 #include "ace_model.h"
 #include "ace_sym.h"
 #include "device_util.h"
@@ -36,8 +29,8 @@ struct AnchorDev {
 template <class T>
 struct AceScratch {
   T* A;             // [n_act][stride] atomic base
+  const T* B;       // [n_act][stride] projected adjoint B'[lm][k] = sum_n Wp[l][n][k] Abar[n][lm]
   int stride;
-  T* Ab;            // [n_act][na] adjoint, or null: A then holds the projected adjoint B'[lm][k]
   double* e_anch;   // [n_act]
   double* fp_anch;  // [n_act]
 };
@@ -303,321 +296,6 @@ __global__ void __launch_bounds__(64) k_ace_basis(const double* __restrict__ pos
 }
 
 // ------------------------------------------------------------------ kernel 2
-template <class T>
-struct Acc {
-  T s1, s2, e1, e2;  // running sums and compensation terms
-};
-
-template <class T, bool COMP>
-__device__ __forceinline__ void acc_add(T& s, T& e, T c, T B) {
-  if constexpr (COMP) {
-    // TwoProduct (via fma) and TwoSum: the dot-product compensation of Ogita, Rump and
-    // Oishi (2005), accumulating the rounding errors separately
-    const T p = c * B;
-    const T pe = fma(c, B, -p);
-    const T sn = s + p;
-    const T bp = sn - s;
-    const T se = (s - (sn - bp)) + (p - bp);
-    s = sn;
-    e += se + pe;
-  } else {
-    s = fma(c, B, s);
-  }
-}
-
-template <class T, int TILE>
-__device__ __forceinline__ void lds_add(T* p, T v, bool on) {
-  if (on) atomicAdd(p, v);
-}
-
-template <class T, int LMAX, int TILE, bool COMP, int L1, int L2>
-__device__ __forceinline__ void pair_fwd(const T* __restrict__ As, const int* rec, const AceTables<T>& tb, int t,
-                                         Acc<T>& acc) {
-  using C = Couple<LMAX, L1, L2>;
-  constexpr int P2 = (LMAX + 1) * (LMAX + 1);
-  constexpr int ST = TILE + 1;
-  const int o1 = rec[0], o2 = rec[1];
-  T a[2 * L1 + 1], bb[2 * L2 + 1], P[P2];
-#pragma unroll
-  for (int m = 0; m < 2 * L1 + 1; ++m) a[m] = As[(o1 + m) * ST + t];
-#pragma unroll
-  for (int m = 0; m < 2 * L2 + 1; ++m) bb[m] = As[(o2 + m) * ST + t];
-#pragma unroll
-  for (int m = 0; m < P2; ++m) P[m] = T(0);
-  C::template fwd<T>(a, bb, P);
-#pragma unroll
-  for (int L = 0; L <= LMAX; ++L) {
-    if ((C::kMask >> L) & 1) {
-      const int q0 = rec[4 + L], q1 = rec[5 + L];
-      const int o3b = rec[10 + L];
-#pragma unroll 2
-      for (int q = q0; q < q1; ++q) {
-        const int o3 = o3b + (q - q0) * P2;
-        const Coef2<T> c = tb.tc[q];
-        T B = T(0);
-#pragma unroll
-        for (int mm = 0; mm < 2 * L + 1; ++mm) B = fma(P[L * L + mm], As[(o3 + mm) * ST + t], B);
-        acc_add<T, COMP>(acc.s1, acc.e1, c.c1, B);
-        acc_add<T, COMP>(acc.s2, acc.e2, c.c2, B);
-      }
-    }
-  }
-}
-
-template <class T, int LMAX, int TILE, bool DC, int L1, int L2>
-__device__ __forceinline__ void pair_bwd(const T* __restrict__ As, T* __restrict__ Ab, const int* rec,
-                                         const AceTables<T>& tb, int t, bool own, T fp, double wdc, double wfp,
-                                         double* dc1, double* dc2) {
-  using C = Couple<LMAX, L1, L2>;
-  constexpr int P2 = (LMAX + 1) * (LMAX + 1);
-  constexpr int ST = TILE + 1;
-  const int o1 = rec[0], o2 = rec[1];
-  T a[2 * L1 + 1], bb[2 * L2 + 1], P[P2], Pb[P2];
-#pragma unroll
-  for (int m = 0; m < 2 * L1 + 1; ++m) a[m] = As[(o1 + m) * ST + t];
-#pragma unroll
-  for (int m = 0; m < 2 * L2 + 1; ++m) bb[m] = As[(o2 + m) * ST + t];
-#pragma unroll
-  for (int m = 0; m < P2; ++m) {
-    P[m] = T(0);
-    Pb[m] = T(0);
-  }
-  C::template fwd<T>(a, bb, P);
-#pragma unroll
-  for (int L = 0; L <= LMAX; ++L) {
-    if ((C::kMask >> L) & 1) {
-      const int q0 = rec[4 + L], q1 = rec[5 + L];
-      const int o3b = rec[10 + L];
-#pragma unroll 2
-      for (int q = q0; q < q1; ++q) {
-        const int o3 = o3b + (q - q0) * P2;
-        const Coef2<T> c = tb.tc[q];
-        const T d = fma(fp, c.c2, c.c1);
-        T B = T(0);
-#pragma unroll
-        for (int mm = 0; mm < 2 * L + 1; ++mm) {
-          const T a3 = As[(o3 + mm) * ST + t];
-          Pb[L * L + mm] = fma(d, a3, Pb[L * L + mm]);
-          lds_add<T, TILE>(&Ab[(o3 + mm) * ST + t], d * P[L * L + mm], own);
-          if constexpr (DC) B = fma(P[L * L + mm], a3, B);
-        }
-        if constexpr (DC) {
-          double g1 = own ? wdc * (double)B : 0.0;
-          double g2 = own ? wfp * (double)B : 0.0;
-          g1 = wave_sum(g1);
-          g2 = wave_sum(g2);
-          if ((threadIdx.x & 63) == 0) {
-            atomicAdd(&dc1[tb.t_v[q]], g1);
-            atomicAdd(&dc2[tb.t_v[q]], g2);
-          }
-        }
-      }
-    }
-  }
-  T ga[2 * L1 + 1], gb[2 * L2 + 1];
-#pragma unroll
-  for (int m = 0; m < 2 * L1 + 1; ++m) ga[m] = T(0);
-#pragma unroll
-  for (int m = 0; m < 2 * L2 + 1; ++m) gb[m] = T(0);
-  C::template bwd<T>(a, bb, Pb, ga, gb);
-#pragma unroll
-  for (int m = 0; m < 2 * L1 + 1; ++m) lds_add<T, TILE>(&Ab[(o1 + m) * ST + t], ga[m], own);
-#pragma unroll
-  for (int m = 0; m < 2 * L2 + 1; ++m) lds_add<T, TILE>(&Ab[(o2 + m) * ST + t], gb[m], own);
-}
-
-#define APX_PAIR_CASES_3(X) \
-  X(0, 0) X(0, 1) X(0, 2) X(0, 3) X(1, 0) X(1, 1) X(1, 2) X(1, 3) X(2, 0) X(2, 1) X(2, 2) X(2, 3) X(3, 0) X(3, 1) X(3, 2) X(3, 3)
-#define APX_PAIR_CASES_4(X)                                                                                  \
-  X(0, 0) X(0, 1) X(0, 2) X(0, 3) X(0, 4) X(1, 0) X(1, 1) X(1, 2) X(1, 3) X(1, 4) X(2, 0) X(2, 1) X(2, 2) X(2, 3) \
-  X(2, 4) X(3, 0) X(3, 1) X(3, 2) X(3, 3) X(3, 4) X(4, 0) X(4, 1) X(4, 2) X(4, 3) X(4, 4)
-
-
-// B1 and B2 contributions (wave 0 of each block), energy and adjoint.
-template <class T, int TILE, bool COMP>
-__device__ __forceinline__ void low_order_fwd(const T* __restrict__ As, const AceTables<T>& tb, int nb1, int nb2,
-                                              int t, Acc<T>& acc) {
-  constexpr int ST = TILE + 1;
-  for (int e = 0; e < nb1; ++e) {
-    const T a = As[tb.b1_off[e] * ST + t];
-    acc_add<T, COMP>(acc.s1, acc.e1, tb.b1_c1[e], a);
-    acc_add<T, COMP>(acc.s2, acc.e2, tb.b1_c2[e], a);
-  }
-  for (int e = 0; e < nb2; ++e) {
-    const int o1 = tb.b2_off[3 * e], o2 = tb.b2_off[3 * e + 1], l = tb.b2_off[3 * e + 2];
-    T B = T(0);
-    for (int m = 0; m < 2 * l + 1; ++m) B = fma(As[(o1 + m) * ST + t], As[(o2 + m) * ST + t], B);
-    acc_add<T, COMP>(acc.s1, acc.e1, tb.b2_c1[e], B);
-    acc_add<T, COMP>(acc.s2, acc.e2, tb.b2_c2[e], B);
-  }
-}
-
-template <class T, int TILE, bool DC>
-__device__ __forceinline__ void low_order_bwd(const T* __restrict__ As, T* __restrict__ Ab, const AceTables<T>& tb,
-                                              int nb1, int nb2, int t, bool own, T fp, double wdc, double wfp,
-                                              double* dc1, double* dc2) {
-  constexpr int ST = TILE + 1;
-  for (int e = 0; e < nb1; ++e) {
-    const int o = tb.b1_off[e];
-    const T d = fma(fp, tb.b1_c2[e], tb.b1_c1[e]);
-    lds_add<T, TILE>(&Ab[o * ST + t], d, own);
-    if constexpr (DC) {
-      const double B = (double)As[o * ST + t];
-      double g1 = own ? wdc * B : 0.0, g2 = own ? wfp * B : 0.0;
-      g1 = wave_sum(g1);
-      g2 = wave_sum(g2);
-      if ((threadIdx.x & 63) == 0) {
-        atomicAdd(&dc1[tb.b1_v[e]], g1);
-        atomicAdd(&dc2[tb.b1_v[e]], g2);
-      }
-    }
-  }
-  for (int e = 0; e < nb2; ++e) {
-    const int o1 = tb.b2_off[3 * e], o2 = tb.b2_off[3 * e + 1], l = tb.b2_off[3 * e + 2];
-    const T d = fma(fp, tb.b2_c2[e], tb.b2_c1[e]);
-    T B = T(0);
-    for (int m = 0; m < 2 * l + 1; ++m) {
-      const T x1 = As[(o1 + m) * ST + t], x2 = As[(o2 + m) * ST + t];
-      lds_add<T, TILE>(&Ab[(o1 + m) * ST + t], d * x2, own);
-      lds_add<T, TILE>(&Ab[(o2 + m) * ST + t], d * x1, own);
-      if constexpr (DC) B = fma(x1, x2, B);
-    }
-    if constexpr (DC) {
-      double g1 = own ? wdc * (double)B : 0.0, g2 = own ? wfp * (double)B : 0.0;
-      g1 = wave_sum(g1);
-      g2 = wave_sum(g2);
-      if ((threadIdx.x & 63) == 0) {
-        atomicAdd(&dc1[tb.b2_v[e]], g1);
-        atomicAdd(&dc2[tb.b2_v[e]], g2);
-      }
-    }
-  }
-}
-
-template <class T>
-__device__ __forceinline__ T feps(T x, T eps, T& dfdx) {
-  const T ax = x < T(0) ? -x : x;
-  const T s = sqrt(ax + eps * eps);
-  dfdx = T(0.5) / s;
-  const T v = s - eps;
-  return x < T(0) ? -v : v;
-}
-
-template <class T, int LMAX, int TILE, int NW, bool COMP, bool DC>
-__global__ void __launch_bounds__(NW * 64) k_ace_products(const T* __restrict__ Ag, T* __restrict__ Abg, int n_act,
-                                                                 int na, AceTables<T> tb, int nb1, int nb2, T eps,
-                                                                 const double* __restrict__ e_anch,
-                                                                 const int* __restrict__ active,
-                                                                 const double* __restrict__ w,
-                                                                 double* __restrict__ e_site,
-                                                                 double* __restrict__ dc1, double* __restrict__ dc2) {
-  constexpr int ST = TILE + 1;
-  extern __shared__ double smem_raw[];
-  T* As = reinterpret_cast<T*>(smem_raw);
-  T* Ab = As + (size_t)na * ST;
-  T* red = Ab + (size_t)na * ST;  // [NW][4][TILE]
-  T* fps = red + NW * 4 * TILE;   // [TILE]
-  const int tid = threadIdx.x;
-  const int nthr = NW * 64;
-  const int npairs = tb.npairs;
-  const int q0 = blockIdx.x * TILE;
-  for (int e = tid; e < TILE * na; e += nthr) {
-    const int t = e / na, a = e - t * na;
-    const int q = q0 + t;
-    As[a * ST + t] = q < n_act ? Ag[(size_t)q * na + a] : T(0);
-    Ab[a * ST + t] = T(0);
-  }
-  __syncthreads();
-  const int lane = tid & 63;
-  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);  // uniform across the wave
-  const int t = lane % TILE;
-  const bool own = lane < TILE;
-  // pairs are sorted by coupling type and dealt round-robin, so all waves of a block run
-  // the same specialised code at about the same time
-  const int pb = __builtin_amdgcn_readfirstlane(wv);
-  // ------------------------------------------------------------ energy pass
-  Acc<T> acc{T(0), T(0), T(0), T(0)};
-  // lane k < kPairRec holds word k of the wave's next pair record (one vector load a pair
-  // ahead, waited for only when the next pair reads it out)
-  int rv = 0;
-  if (pb < npairs && lane < kPairRec) rv = tb.pairs[pb * kPairRec + lane];
-  if (wv == 0) low_order_fwd<T, TILE, COMP>(As, tb, nb1, nb2, t, acc);
-  for (int pi = pb; pi < npairs; pi += NW) {
-    int rec[kPairRec];
-#pragma unroll
-    for (int k = 0; k < kPairRec; ++k) rec[k] = __builtin_amdgcn_readlane(rv, k);
-    if (pi + NW < npairs && lane < kPairRec) rv = tb.pairs[(pi + NW) * kPairRec + lane];
-    const int type = rec[2];
-#define APX_FWD(A_, B_) \
-  case A_ * (LMAX + 1) + B_: pair_fwd<T, LMAX, TILE, COMP, A_, B_>(As, rec, tb, t, acc); break;
-    if constexpr (LMAX == 3) {
-      switch (type) { APX_PAIR_CASES_3(APX_FWD) default: break; }
-    } else {
-      switch (type) { APX_PAIR_CASES_4(APX_FWD) default: break; }
-    }
-#undef APX_FWD
-  }
-  if (own) {
-    red[(wv * 4 + 0) * TILE + t] = acc.s1;
-    red[(wv * 4 + 1) * TILE + t] = acc.e1;
-    red[(wv * 4 + 2) * TILE + t] = acc.s2;
-    red[(wv * 4 + 3) * TILE + t] = acc.e2;
-  }
-  __syncthreads();
-  if (wv == 0 && own) {
-    T s1 = T(0), e1 = T(0), s2 = T(0), e2 = T(0);
-    for (int v = 0; v < NW; ++v) {
-      acc_add<T, COMP>(s1, e1, T(1), red[(v * 4 + 0) * TILE + t]);
-      e1 += red[(v * 4 + 1) * TILE + t];
-      acc_add<T, COMP>(s2, e2, T(1), red[(v * 4 + 2) * TILE + t]);
-      e2 += red[(v * 4 + 3) * TILE + t];
-    }
-    const T phi1 = s1 + e1, phi2 = s2 + e2;
-    T dfdx;
-    const T f2 = feps<T>(phi2, eps, dfdx);
-    fps[t] = dfdx;
-    const int q = q0 + t;
-    if (q < n_act) e_site[active[q]] = (double)phi1 + (double)f2 + e_anch[q];
-  }
-  __syncthreads();
-  // ----------------------------------------------------------- adjoint pass
-  const T fp = fps[t];
-  double wdc = 0.0, wfp = 0.0;
-  if constexpr (DC) {
-    const int q = q0 + t;
-    if (q < n_act && own) {
-      wdc = w ? w[active[q]] : 1.0;
-      wfp = wdc * (double)fp;
-    }
-  }
-  if (pb < npairs && lane < kPairRec) rv = tb.pairs[pb * kPairRec + lane];
-  if (wv == 0) low_order_bwd<T, TILE, DC>(As, Ab, tb, nb1, nb2, t, own, fp, wdc, wfp, dc1, dc2);
-  for (int pi = pb; pi < npairs; pi += NW) {
-    int rec[kPairRec];
-#pragma unroll
-    for (int k = 0; k < kPairRec; ++k) rec[k] = __builtin_amdgcn_readlane(rv, k);
-    if (pi + NW < npairs && lane < kPairRec) rv = tb.pairs[(pi + NW) * kPairRec + lane];
-    const int type = rec[2];
-#define APX_BWD(A_, B_)                                                                                   \
-  case A_ * (LMAX + 1) + B_:                                                                              \
-    pair_bwd<T, LMAX, TILE, DC, A_, B_>(As, Ab, rec, tb, t, own, fp, wdc, wfp, dc1, dc2);                 \
-    break;
-    if constexpr (LMAX == 3) {
-      switch (type) { APX_PAIR_CASES_3(APX_BWD) default: break; }
-    } else {
-      switch (type) { APX_PAIR_CASES_4(APX_BWD) default: break; }
-    }
-#undef APX_BWD
-  }
-  __syncthreads();
-  for (int e = tid; e < TILE * na; e += nthr) {
-    const int tt = e / na, a = e - tt * na;
-    const int q = q0 + tt;
-    if (q < n_act) Abg[(size_t)q * na + a] = Ab[a * ST + tt];
-  }
-}
-
-// ------------------------------------------------------------------ kernel 3
 // Ā' of one atom in LDS: lm-major rows of KP radial values (K rounded up to whole 16-byte
 // groups, the padding zero), so that a row is read by a few wide broadcast loads.
 template <class T, int NMAX>
@@ -631,7 +309,7 @@ template <class T, int LMAX, int NMAX>
 __global__ void __launch_bounds__(64, sizeof(T) == 4 ? 4 : 1) k_ace_force(const double* __restrict__ pos, int n, BoxDev b,
                                                   const int* __restrict__ count, const int* __restrict__ idx,
                                                   int max_nb, const int* __restrict__ active, int n_act, int K,
-                                                  T rc, T inv_h, double rc2, const T* __restrict__ Wp, AnchorDev an,
+                                                  T rc, T inv_h, double rc2, AnchorDev an,
                                                   AceScratch<T> sc, const double* __restrict__ w,
                                                   double* __restrict__ f, const double* __restrict__ w2,
                                                   double* __restrict__ f2) {
@@ -650,33 +328,12 @@ __global__ void __launch_bounds__(64, sizeof(T) == 4 ? 4 : 1) k_ace_force(const 
   // second weight set (the integrator's weight difference): scattered only where non-zero
   const double w2i = f2 ? w2[i] : 0.0;
   const int na = K * LM;
-  // the projected adjoint B'[lm][k] = sum_n Wp[l][n][k] Abar[n][lm], as the product kernels left
-  // it, or from the adjoint
   for (int o = lane; o < LM * KP; o += 64) Ab2[o] = T(0);
   __syncthreads();
-  if (!sc.Ab) {
-    const T* B = sc.A + (size_t)q * sc.stride;
-    for (int o = lane; o < na; o += 64) {
-      const int lm = o / K;
-      Ab2[lm * KP + o - lm * K] = B[o];
-    }
-  }
-  const T* Abr = sc.Ab + (size_t)q * na;
-  for (int o = lane; o < na && sc.Ab; o += 64) {
-    const int kk = o / LM, lm = o - kk * LM;
-    int l = 0;
-    while ((l + 1) * (l + 1) <= lm) ++l;
-    // the K loads of an output are issued together (unrolled to the largest K)
-    T wv_[kMaxK], av_[kMaxK];
-#pragma unroll
-    for (int nn = 0; nn < kMaxK; ++nn) {
-      wv_[nn] = nn < K ? Wp[((size_t)l * K + nn) * K + kk] : T(0);
-      av_[nn] = nn < K ? Abr[nn * LM + lm] : T(0);
-    }
-    T v = T(0);
-#pragma unroll
-    for (int nn = 0; nn < kMaxK; ++nn) v += wv_[nn] * av_[nn];
-    Ab2[lm * KP + kk] = v;
+  const T* B = sc.B + (size_t)q * sc.stride;
+  for (int o = lane; o < na; o += 64) {
+    const int lm = o / K;
+    Ab2[lm * KP + o - lm * K] = B[o];
   }
   __syncthreads();
   const double fpa = an.on ? sc.fp_anch[q] : 0.0;
@@ -822,47 +479,37 @@ __global__ void k_fill_zero(double* __restrict__ p, long long m) {
   if (i < m) p[i] = 0.0;
 }
 
-// hipFuncSetAttribute once per kernel (the dynamic LDS size is the same for every call
-// with a given model shape; the largest seen is kept)
-static apx_status ensure_lds(apx_ctx* ctx, const void* kern, size_t bytes) {
-  static std::vector<std::pair<const void*, size_t>> done;
-  for (auto& d : done)
-    if (d.first == kern && d.second >= bytes) return APX_OK;
-  APX_HIP(ctx, hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes));
-  for (auto& d : done)
-    if (d.first == kern) {
-      d.second = bytes;
-      return APX_OK;
-    }
-  done.push_back({kern, bytes});
-  return APX_OK;
-}
-
 template <class T, int LMAX>
 apx_status ace_run(apx_ctx* ctx, const apx_atoms* atoms, const apx_nlist* nl, const apx_ace_model* m,
-                   const AceTables<T>& tb, const double* w, const int* active, int n_act, double* e_site,
+                   const double* w, const int* active, int n_act, double* e_site,
                    double* f, double* dc1, double* dc2, apx::DevBuf& buf, const double* w2 = nullptr,
                    double* f2 = nullptr) {
-  constexpr int TILE = sizeof(T) == 4 ? 64 : 32;
   constexpr int LM = (LMAX + 1) * (LMAX + 1);
   const int n = (int)atoms->n;
-  const int na = m->na;
-  // without coefficient gradients: the symmetric product kernels
-  const bool sym = dc1 == nullptr;
-  const long long n_pad = (long long)((n_act + TILE - 1) / TILE) * TILE;
-  static_assert(TILE % sym_tile<T>() == 0, "whole tiles of either kind");
+  const SymTables<T>& tb = sym_tables<T>(m);
   AceScratch<T> sc;
-  sc.stride = sym ? sym_stride(na) : na;
-  const size_t bytes_A = sizeof(T) * (size_t)n_pad * sc.stride;
-  const size_t bytes_anch = sizeof(double) * 2 * (((size_t)n_act + 31) / 32 * 32);
-  const size_t bytes_more = sym ? sym_scratch<T>(m, n_act) : bytes_A;
-  APX_ALLOC(ctx, buf, bytes_A + bytes_anch + bytes_more);
-  char* base = static_cast<char*>(buf.p);
-  void* more = base + bytes_A + bytes_anch;
-  sc.A = reinterpret_cast<T*>(base);
-  sc.Ab = sym ? nullptr : static_cast<T*>(more);
-  sc.e_anch = reinterpret_cast<double*>(base + bytes_A);
+  sc.stride = sym_stride(m->na);
+  // the projected adjoint overwrites the atomic base, which only the coefficient gradients need
+  // afterwards (with the embedding's slopes)
+  auto whole = [](size_t b) { return (b + 255) / 256 * 256; };
+  const size_t bytes_A = whole(sizeof(T) * (size_t)n_act * sc.stride);
+  const size_t bytes_anch = whole(sizeof(double) * 2 * (size_t)n_act);
+  const size_t bytes_slope = dc1 ? whole(sizeof(T) * (size_t)n_act) : 0;
+  const size_t bytes_more = std::max(sym_scratch<T>(m, n_act), dc1 ? ace_grad_scratch(m, n_act) : 0);
+  APX_ALLOC(ctx, buf, (dc1 ? 2 : 1) * bytes_A + bytes_anch + bytes_slope + bytes_more);
+  char* p = static_cast<char*>(buf.p);
+  auto take = [&](size_t b) {
+    char* at = p;
+    p += b;
+    return at;
+  };
+  sc.A = reinterpret_cast<T*>(take(bytes_A));
+  T* B = dc1 ? reinterpret_cast<T*>(take(bytes_A)) : sc.A;
+  sc.B = B;
+  sc.e_anch = reinterpret_cast<double*>(take(bytes_anch));
   sc.fp_anch = sc.e_anch + n_act;
+  T* slope = dc1 ? reinterpret_cast<T*>(take(bytes_slope)) : nullptr;
+  void* more = p;
   BoxDev b = make_box(atoms);
   AnchorDev an{};
   an.on = m->anchored;
@@ -884,46 +531,16 @@ apx_status ace_run(apx_ctx* ctx, const apx_atoms* atoms, const apx_nlist* nl, co
                                                          n_act, m->n_max, rc, inv_h, rc2, tb.Wp, an, sc);
   APX_LAUNCH_CHECK(ctx);
   }
-  int lds_max = 0;
-  APX_HIP(ctx, hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, ctx->device));
-  if (sym) {
-    const apx_status s = sym_products<T>(ctx, m, sc.A, n_act, sc.e_anch, active, e_site, more);
-    if (s != APX_OK) return s;
-  }
-  if (!sym) {
-    // the LDS version (with coefficient gradients) stages the tile's
-    // A and its adjoint; for large bases the tile is halved so that both fit
-    constexpr int NW = sizeof(T) == 4 ? kAceWaves32 : kAceWaves64;
-    auto lds_for = [&](int tl) { return sizeof(T) * ((size_t)2 * na * (tl + 1) + NW * 4 * tl + tl); };
-    auto products = [&](auto tile_c) -> apx_status {
-      constexpr int TL = decltype(tile_c)::value;
-      const size_t lds2 = lds_for(TL);
-      const unsigned nblk = (unsigned)((n_act + TL - 1) / TL);
-      ProfScope ps(ctx, "ace.products");
-      auto kern = k_ace_products<T, LMAX, TL, NW, sizeof(T) == 4, true>;
-      if (ensure_lds(ctx, (const void*)kern, lds2) != APX_OK) return APX_EDEVICE;
-      kern<<<nblk, NW * 64, lds2, ctx->stream>>>(sc.A, sc.Ab, n_act, na, tb, m->nb1, m->nb2, (T)m->eps, sc.e_anch,
-                                                 active, w, e_site, dc1, dc2);
-      APX_LAUNCH_CHECK(ctx);
-      return APX_OK;
-    };
-    apx_status s;
-    if (lds_for(TILE) <= (size_t)lds_max)
-      s = products(std::integral_constant<int, TILE>{});
-    else if (lds_for(TILE / 2) <= (size_t)lds_max)
-      s = products(std::integral_constant<int, TILE / 2>{});
-    else
-      return fail(ctx, APX_EINVAL, "ACE tile needs %zu bytes of LDS, the device allows %d (reduce n_max)",
-                  lds_for(TILE / 2), lds_max);
-    if (s != APX_OK) return s;
-  }
+  apx_status s = sym_products<T>(ctx, m, sc.A, B, slope, n_act, sc.e_anch, active, e_site, more);
+  if (s == APX_OK && dc1) s = ace_grad<T>(ctx, m, sc.A, slope, w, active, n_act, dc1, dc2, more);
+  if (s != APX_OK) return s;
   ProfScope ps(ctx, "ace.force");
   auto force = [&](auto nmax_c) {
     constexpr int NM = decltype(nmax_c)::value;
     const size_t lds3 = sizeof(T) * (size_t)ForceLds<T, NM>::KP * LM;
     k_ace_force<T, LMAX, NM><<<n_act, 64, lds3, ctx->stream>>>(atoms->pos, n, b, nl->count, nl->idx, nl->max_nb,
-                                                               active, n_act, m->n_max, rc, inv_h, rc2, tb.Wp, an,
-                                                               sc, w, f, w2, f2);
+                                                               active, n_act, m->n_max, rc, inv_h, rc2, an, sc, w,
+                                                               f, w2, f2);
   };
   if (m->n_max <= 8) force(std::integral_constant<int, 8>{});
   else if (m->n_max <= 10) force(std::integral_constant<int, 10>{});
@@ -973,15 +590,15 @@ apx_status ace_impl(apx_ctx* ctx, const apx_atoms* atoms, const apx_nlist* nl, c
   const int na_ = (int)n_active;
   if (precision == APX_FP64) {
     if (m->l_max == 3)
-      return ace_run<double, 3>(ctx, atoms, nl, m, m->t64, w, active, na_, e_site, f, dE_dc1, dE_dc2, ace_buffer(ctx),
+      return ace_run<double, 3>(ctx, atoms, nl, m, w, active, na_, e_site, f, dE_dc1, dE_dc2, ace_buffer(ctx),
                                 w2, f2);
-    return ace_run<double, 4>(ctx, atoms, nl, m, m->t64, w, active, na_, e_site, f, dE_dc1, dE_dc2, ace_buffer(ctx),
+    return ace_run<double, 4>(ctx, atoms, nl, m, w, active, na_, e_site, f, dE_dc1, dE_dc2, ace_buffer(ctx),
                               w2, f2);
   }
   if (m->l_max == 3)
-    return ace_run<float, 3>(ctx, atoms, nl, m, m->t32, w, active, na_, e_site, f, dE_dc1, dE_dc2, ace_buffer(ctx),
+    return ace_run<float, 3>(ctx, atoms, nl, m, w, active, na_, e_site, f, dE_dc1, dE_dc2, ace_buffer(ctx),
                              w2, f2);
-  return ace_run<float, 4>(ctx, atoms, nl, m, m->t32, w, active, na_, e_site, f, dE_dc1, dE_dc2, ace_buffer(ctx),
+  return ace_run<float, 4>(ctx, atoms, nl, m, w, active, na_, e_site, f, dE_dc1, dE_dc2, ace_buffer(ctx),
                            w2, f2);
 }
 }  // namespace

@@ -1,6835 +1,1933 @@
-// Generated by gen_coupling.py -- do not edit.  Real Gaunt coupling of two
-// spherical-harmonic blocks, unrolled for each (l_max, l1, l2).
+// Generated by gen_coupling.py -- do not edit.  Real Gaunt coupling of two harmonic blocks
+// (degrees l1 <= l2), one component M at a time, scaled by 1 / kSymScale[l1][l2][L].
 #pragma once
 #include <hip/hip_runtime.h>
 namespace apx {
-template <int LMAX, int L1, int L2> struct Couple;
-template <> struct Couple<3, 0, 0> {
-  static constexpr int kMask = 1;
-  static constexpr int kTerms = 1;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[0] += T(0.28209479177387803) * (a[0] * b[0]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(0.28209479177387803) * Pb[0]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-  }
-};
-template <> struct Couple<3, 0, 1> {
-  static constexpr int kMask = 2;
-  static constexpr int kTerms = 3;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[1] += T(0.28209479177387808) * (a[0] * b[0]);
-    P[2] += T(0.28209479177387808) * (a[0] * b[1]);
-    P[3] += T(0.28209479177387808) * (a[0] * b[2]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(0.28209479177387808) * Pb[1]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.28209479177387808) * Pb[2]; ga[0] += t * b[1]; gb[1] += t * a[0]; }
-    { const T t = T(0.28209479177387808) * Pb[3]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-  }
-};
-template <> struct Couple<3, 0, 2> {
-  static constexpr int kMask = 4;
-  static constexpr int kTerms = 5;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[4] += T(0.2820947917738782) * (a[0] * b[0]);
-    P[5] += T(0.28209479177387831) * (a[0] * b[1]);
-    P[6] += T(0.28209479177387831) * (a[0] * b[2]);
-    P[7] += T(0.28209479177387831) * (a[0] * b[3]);
-    P[8] += T(0.28209479177387831) * (a[0] * b[4]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(0.2820947917738782) * Pb[4]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.28209479177387831) * Pb[5]; ga[0] += t * b[1]; gb[1] += t * a[0]; }
-    { const T t = T(0.28209479177387831) * Pb[6]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(0.28209479177387831) * Pb[7]; ga[0] += t * b[3]; gb[3] += t * a[0]; }
-    { const T t = T(0.28209479177387831) * Pb[8]; ga[0] += t * b[4]; gb[4] += t * a[0]; }
-  }
-};
-template <> struct Couple<3, 0, 3> {
-  static constexpr int kMask = 8;
-  static constexpr int kTerms = 7;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[9] += T(0.2820947917738782) * (a[0] * b[0]);
-    P[10] += T(0.2820947917738782) * (a[0] * b[1]);
-    P[11] += T(0.28209479177387825) * (a[0] * b[2]);
-    P[12] += T(0.28209479177387814) * (a[0] * b[3]);
-    P[13] += T(0.28209479177387825) * (a[0] * b[4]);
-    P[14] += T(0.28209479177387825) * (a[0] * b[5]);
-    P[15] += T(0.2820947917738782) * (a[0] * b[6]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(0.2820947917738782) * Pb[9]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.2820947917738782) * Pb[10]; ga[0] += t * b[1]; gb[1] += t * a[0]; }
-    { const T t = T(0.28209479177387825) * Pb[11]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(0.28209479177387814) * Pb[12]; ga[0] += t * b[3]; gb[3] += t * a[0]; }
-    { const T t = T(0.28209479177387825) * Pb[13]; ga[0] += t * b[4]; gb[4] += t * a[0]; }
-    { const T t = T(0.28209479177387825) * Pb[14]; ga[0] += t * b[5]; gb[5] += t * a[0]; }
-    { const T t = T(0.2820947917738782) * Pb[15]; ga[0] += t * b[6]; gb[6] += t * a[0]; }
-  }
-};
-template <> struct Couple<3, 1, 0> {
-  static constexpr int kMask = 2;
-  static constexpr int kTerms = 3;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[1] += T(0.28209479177387808) * (a[0] * b[0]);
-    P[2] += T(0.28209479177387808) * (a[1] * b[0]);
-    P[3] += T(0.28209479177387808) * (a[2] * b[0]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(0.28209479177387808) * Pb[1]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.28209479177387808) * Pb[2]; ga[1] += t * b[0]; gb[0] += t * a[1]; }
-    { const T t = T(0.28209479177387808) * Pb[3]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-  }
-};
-template <> struct Couple<3, 1, 1> {
-  static constexpr int kMask = 5;
-  static constexpr int kTerms = 14;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[0] += T(0.28209479177387803) * (a[0] * b[0]);
-    P[0] += T(0.28209479177387803) * (a[1] * b[1]);
-    P[0] += T(0.28209479177387803) * (a[2] * b[2]);
-    P[4] += T(0.21850968611841587) * (a[0] * b[2]);
-    P[4] += T(0.21850968611841587) * (a[2] * b[0]);
-    P[5] += T(0.21850968611841587) * (a[0] * b[1]);
-    P[5] += T(0.21850968611841587) * (a[1] * b[0]);
-    P[6] += T(-0.12615662610100806) * (a[0] * b[0]);
-    P[6] += T(0.252313252202016) * (a[1] * b[1]);
-    P[6] += T(-0.12615662610100806) * (a[2] * b[2]);
-    P[7] += T(0.21850968611841587) * (a[1] * b[2]);
-    P[7] += T(0.21850968611841587) * (a[2] * b[1]);
-    P[8] += T(-0.2185096861184159) * (a[0] * b[0]);
-    P[8] += T(0.2185096861184159) * (a[2] * b[2]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(0.28209479177387803) * Pb[0]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.28209479177387803) * Pb[0]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(0.28209479177387803) * Pb[0]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(0.21850968611841587) * Pb[4]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(0.21850968611841587) * Pb[4]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(0.21850968611841587) * Pb[5]; ga[0] += t * b[1]; gb[1] += t * a[0]; }
-    { const T t = T(0.21850968611841587) * Pb[5]; ga[1] += t * b[0]; gb[0] += t * a[1]; }
-    { const T t = T(-0.12615662610100806) * Pb[6]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.252313252202016) * Pb[6]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(-0.12615662610100806) * Pb[6]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(0.21850968611841587) * Pb[7]; ga[1] += t * b[2]; gb[2] += t * a[1]; }
-    { const T t = T(0.21850968611841587) * Pb[7]; ga[2] += t * b[1]; gb[1] += t * a[2]; }
-    { const T t = T(-0.2185096861184159) * Pb[8]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.2185096861184159) * Pb[8]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-  }
-};
-template <> struct Couple<3, 1, 2> {
-  static constexpr int kMask = 10;
-  static constexpr int kTerms = 32;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[1] += T(-0.12615662610100806) * (a[0] * b[2]);
-    P[1] += T(-0.2185096861184159) * (a[0] * b[4]);
-    P[1] += T(0.21850968611841587) * (a[1] * b[1]);
-    P[1] += T(0.21850968611841587) * (a[2] * b[0]);
-    P[2] += T(0.21850968611841587) * (a[0] * b[1]);
-    P[2] += T(0.252313252202016) * (a[1] * b[2]);
-    P[2] += T(0.21850968611841587) * (a[2] * b[3]);
-    P[3] += T(0.21850968611841587) * (a[0] * b[0]);
-    P[3] += T(0.21850968611841587) * (a[1] * b[3]);
-    P[3] += T(-0.12615662610100806) * (a[2] * b[2]);
-    P[3] += T(0.2185096861184159) * (a[2] * b[4]);
-    P[9] += T(0.22617901315954023) * (a[0] * b[4]);
-    P[9] += T(0.22617901315954039) * (a[2] * b[0]);
-    P[10] += T(0.18467439092237189) * (a[0] * b[3]);
-    P[10] += T(0.18467439092237187) * (a[1] * b[0]);
-    P[10] += T(0.18467439092237189) * (a[2] * b[1]);
-    P[11] += T(0.20230065940342065) * (a[0] * b[2]);
-    P[11] += T(0.058399170081901729) * (a[0] * b[4]);
-    P[11] += T(0.23359668032760758) * (a[1] * b[1]);
-    P[11] += T(-0.058399170081901861) * (a[2] * b[0]);
-    P[12] += T(-0.1430481681026689) * (a[0] * b[1]);
-    P[12] += T(0.24776669508347599) * (a[1] * b[2]);
-    P[12] += T(-0.1430481681026689) * (a[2] * b[3]);
-    P[13] += T(-0.058399170081901861) * (a[0] * b[0]);
-    P[13] += T(0.23359668032760758) * (a[1] * b[3]);
-    P[13] += T(0.20230065940342065) * (a[2] * b[2]);
-    P[13] += T(-0.058399170081901729) * (a[2] * b[4]);
-    P[14] += T(-0.18467439092237189) * (a[0] * b[1]);
-    P[14] += T(0.18467439092237187) * (a[1] * b[4]);
-    P[14] += T(0.18467439092237189) * (a[2] * b[3]);
-    P[15] += T(-0.22617901315954039) * (a[0] * b[0]);
-    P[15] += T(0.22617901315954023) * (a[2] * b[4]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(-0.12615662610100806) * Pb[1]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(-0.2185096861184159) * Pb[1]; ga[0] += t * b[4]; gb[4] += t * a[0]; }
-    { const T t = T(0.21850968611841587) * Pb[1]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(0.21850968611841587) * Pb[1]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(0.21850968611841587) * Pb[2]; ga[0] += t * b[1]; gb[1] += t * a[0]; }
-    { const T t = T(0.252313252202016) * Pb[2]; ga[1] += t * b[2]; gb[2] += t * a[1]; }
-    { const T t = T(0.21850968611841587) * Pb[2]; ga[2] += t * b[3]; gb[3] += t * a[2]; }
-    { const T t = T(0.21850968611841587) * Pb[3]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.21850968611841587) * Pb[3]; ga[1] += t * b[3]; gb[3] += t * a[1]; }
-    { const T t = T(-0.12615662610100806) * Pb[3]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(0.2185096861184159) * Pb[3]; ga[2] += t * b[4]; gb[4] += t * a[2]; }
-    { const T t = T(0.22617901315954023) * Pb[9]; ga[0] += t * b[4]; gb[4] += t * a[0]; }
-    { const T t = T(0.22617901315954039) * Pb[9]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(0.18467439092237189) * Pb[10]; ga[0] += t * b[3]; gb[3] += t * a[0]; }
-    { const T t = T(0.18467439092237187) * Pb[10]; ga[1] += t * b[0]; gb[0] += t * a[1]; }
-    { const T t = T(0.18467439092237189) * Pb[10]; ga[2] += t * b[1]; gb[1] += t * a[2]; }
-    { const T t = T(0.20230065940342065) * Pb[11]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(0.058399170081901729) * Pb[11]; ga[0] += t * b[4]; gb[4] += t * a[0]; }
-    { const T t = T(0.23359668032760758) * Pb[11]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(-0.058399170081901861) * Pb[11]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(-0.1430481681026689) * Pb[12]; ga[0] += t * b[1]; gb[1] += t * a[0]; }
-    { const T t = T(0.24776669508347599) * Pb[12]; ga[1] += t * b[2]; gb[2] += t * a[1]; }
-    { const T t = T(-0.1430481681026689) * Pb[12]; ga[2] += t * b[3]; gb[3] += t * a[2]; }
-    { const T t = T(-0.058399170081901861) * Pb[13]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.23359668032760758) * Pb[13]; ga[1] += t * b[3]; gb[3] += t * a[1]; }
-    { const T t = T(0.20230065940342065) * Pb[13]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(-0.058399170081901729) * Pb[13]; ga[2] += t * b[4]; gb[4] += t * a[2]; }
-    { const T t = T(-0.18467439092237189) * Pb[14]; ga[0] += t * b[1]; gb[1] += t * a[0]; }
-    { const T t = T(0.18467439092237187) * Pb[14]; ga[1] += t * b[4]; gb[4] += t * a[1]; }
-    { const T t = T(0.18467439092237189) * Pb[14]; ga[2] += t * b[3]; gb[3] += t * a[2]; }
-    { const T t = T(-0.22617901315954039) * Pb[15]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.22617901315954023) * Pb[15]; ga[2] += t * b[4]; gb[4] += t * a[2]; }
-  }
-};
-template <> struct Couple<3, 1, 3> {
-  static constexpr int kMask = 4;
-  static constexpr int kTerms = 21;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[4] += T(-0.058399170081901867) * (a[0] * b[4]);
-    P[4] += T(-0.22617901315954042) * (a[0] * b[6]);
-    P[4] += T(0.18467439092237187) * (a[1] * b[1]);
-    P[4] += T(0.22617901315954042) * (a[2] * b[0]);
-    P[4] += T(-0.058399170081901867) * (a[2] * b[2]);
-    P[5] += T(-0.1430481681026689) * (a[0] * b[3]);
-    P[5] += T(-0.18467439092237192) * (a[0] * b[5]);
-    P[5] += T(0.23359668032760761) * (a[1] * b[2]);
-    P[5] += T(0.18467439092237189) * (a[2] * b[1]);
-    P[6] += T(0.20230065940342068) * (a[0] * b[2]);
-    P[6] += T(0.24776669508347601) * (a[1] * b[3]);
-    P[6] += T(0.20230065940342068) * (a[2] * b[4]);
-    P[7] += T(0.18467439092237189) * (a[0] * b[1]);
-    P[7] += T(0.23359668032760761) * (a[1] * b[4]);
-    P[7] += T(-0.1430481681026689) * (a[2] * b[3]);
-    P[7] += T(0.18467439092237192) * (a[2] * b[5]);
-    P[8] += T(0.22617901315954025) * (a[0] * b[0]);
-    P[8] += T(0.058399170081901736) * (a[0] * b[2]);
-    P[8] += T(0.18467439092237187) * (a[1] * b[5]);
-    P[8] += T(-0.058399170081901736) * (a[2] * b[4]);
-    P[8] += T(0.22617901315954025) * (a[2] * b[6]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(-0.058399170081901867) * Pb[4]; ga[0] += t * b[4]; gb[4] += t * a[0]; }
-    { const T t = T(-0.22617901315954042) * Pb[4]; ga[0] += t * b[6]; gb[6] += t * a[0]; }
-    { const T t = T(0.18467439092237187) * Pb[4]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(0.22617901315954042) * Pb[4]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(-0.058399170081901867) * Pb[4]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(-0.1430481681026689) * Pb[5]; ga[0] += t * b[3]; gb[3] += t * a[0]; }
-    { const T t = T(-0.18467439092237192) * Pb[5]; ga[0] += t * b[5]; gb[5] += t * a[0]; }
-    { const T t = T(0.23359668032760761) * Pb[5]; ga[1] += t * b[2]; gb[2] += t * a[1]; }
-    { const T t = T(0.18467439092237189) * Pb[5]; ga[2] += t * b[1]; gb[1] += t * a[2]; }
-    { const T t = T(0.20230065940342068) * Pb[6]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(0.24776669508347601) * Pb[6]; ga[1] += t * b[3]; gb[3] += t * a[1]; }
-    { const T t = T(0.20230065940342068) * Pb[6]; ga[2] += t * b[4]; gb[4] += t * a[2]; }
-    { const T t = T(0.18467439092237189) * Pb[7]; ga[0] += t * b[1]; gb[1] += t * a[0]; }
-    { const T t = T(0.23359668032760761) * Pb[7]; ga[1] += t * b[4]; gb[4] += t * a[1]; }
-    { const T t = T(-0.1430481681026689) * Pb[7]; ga[2] += t * b[3]; gb[3] += t * a[2]; }
-    { const T t = T(0.18467439092237192) * Pb[7]; ga[2] += t * b[5]; gb[5] += t * a[2]; }
-    { const T t = T(0.22617901315954025) * Pb[8]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.058399170081901736) * Pb[8]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(0.18467439092237187) * Pb[8]; ga[1] += t * b[5]; gb[5] += t * a[1]; }
-    { const T t = T(-0.058399170081901736) * Pb[8]; ga[2] += t * b[4]; gb[4] += t * a[2]; }
-    { const T t = T(0.22617901315954025) * Pb[8]; ga[2] += t * b[6]; gb[6] += t * a[2]; }
-  }
-};
-template <> struct Couple<3, 2, 0> {
-  static constexpr int kMask = 4;
-  static constexpr int kTerms = 5;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[4] += T(0.2820947917738782) * (a[0] * b[0]);
-    P[5] += T(0.28209479177387831) * (a[1] * b[0]);
-    P[6] += T(0.28209479177387831) * (a[2] * b[0]);
-    P[7] += T(0.28209479177387831) * (a[3] * b[0]);
-    P[8] += T(0.28209479177387831) * (a[4] * b[0]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(0.2820947917738782) * Pb[4]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.28209479177387831) * Pb[5]; ga[1] += t * b[0]; gb[0] += t * a[1]; }
-    { const T t = T(0.28209479177387831) * Pb[6]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(0.28209479177387831) * Pb[7]; ga[3] += t * b[0]; gb[0] += t * a[3]; }
-    { const T t = T(0.28209479177387831) * Pb[8]; ga[4] += t * b[0]; gb[0] += t * a[4]; }
-  }
-};
-template <> struct Couple<3, 2, 1> {
-  static constexpr int kMask = 10;
-  static constexpr int kTerms = 32;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[1] += T(0.21850968611841587) * (a[0] * b[2]);
-    P[1] += T(0.21850968611841587) * (a[1] * b[1]);
-    P[1] += T(-0.12615662610100806) * (a[2] * b[0]);
-    P[1] += T(-0.2185096861184159) * (a[4] * b[0]);
-    P[2] += T(0.21850968611841587) * (a[1] * b[0]);
-    P[2] += T(0.252313252202016) * (a[2] * b[1]);
-    P[2] += T(0.21850968611841587) * (a[3] * b[2]);
-    P[3] += T(0.21850968611841587) * (a[0] * b[0]);
-    P[3] += T(-0.12615662610100806) * (a[2] * b[2]);
-    P[3] += T(0.21850968611841587) * (a[3] * b[1]);
-    P[3] += T(0.2185096861184159) * (a[4] * b[2]);
-    P[9] += T(0.22617901315954039) * (a[0] * b[2]);
-    P[9] += T(0.22617901315954023) * (a[4] * b[0]);
-    P[10] += T(0.18467439092237187) * (a[0] * b[1]);
-    P[10] += T(0.18467439092237189) * (a[1] * b[2]);
-    P[10] += T(0.18467439092237189) * (a[3] * b[0]);
-    P[11] += T(-0.058399170081901861) * (a[0] * b[2]);
-    P[11] += T(0.23359668032760758) * (a[1] * b[1]);
-    P[11] += T(0.20230065940342065) * (a[2] * b[0]);
-    P[11] += T(0.058399170081901729) * (a[4] * b[0]);
-    P[12] += T(-0.1430481681026689) * (a[1] * b[0]);
-    P[12] += T(0.24776669508347599) * (a[2] * b[1]);
-    P[12] += T(-0.1430481681026689) * (a[3] * b[2]);
-    P[13] += T(-0.058399170081901861) * (a[0] * b[0]);
-    P[13] += T(0.20230065940342065) * (a[2] * b[2]);
-    P[13] += T(0.23359668032760758) * (a[3] * b[1]);
-    P[13] += T(-0.058399170081901729) * (a[4] * b[2]);
-    P[14] += T(-0.18467439092237189) * (a[1] * b[0]);
-    P[14] += T(0.18467439092237189) * (a[3] * b[2]);
-    P[14] += T(0.18467439092237187) * (a[4] * b[1]);
-    P[15] += T(-0.22617901315954039) * (a[0] * b[0]);
-    P[15] += T(0.22617901315954023) * (a[4] * b[2]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(0.21850968611841587) * Pb[1]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(0.21850968611841587) * Pb[1]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(-0.12615662610100806) * Pb[1]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(-0.2185096861184159) * Pb[1]; ga[4] += t * b[0]; gb[0] += t * a[4]; }
-    { const T t = T(0.21850968611841587) * Pb[2]; ga[1] += t * b[0]; gb[0] += t * a[1]; }
-    { const T t = T(0.252313252202016) * Pb[2]; ga[2] += t * b[1]; gb[1] += t * a[2]; }
-    { const T t = T(0.21850968611841587) * Pb[2]; ga[3] += t * b[2]; gb[2] += t * a[3]; }
-    { const T t = T(0.21850968611841587) * Pb[3]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(-0.12615662610100806) * Pb[3]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(0.21850968611841587) * Pb[3]; ga[3] += t * b[1]; gb[1] += t * a[3]; }
-    { const T t = T(0.2185096861184159) * Pb[3]; ga[4] += t * b[2]; gb[2] += t * a[4]; }
-    { const T t = T(0.22617901315954039) * Pb[9]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(0.22617901315954023) * Pb[9]; ga[4] += t * b[0]; gb[0] += t * a[4]; }
-    { const T t = T(0.18467439092237187) * Pb[10]; ga[0] += t * b[1]; gb[1] += t * a[0]; }
-    { const T t = T(0.18467439092237189) * Pb[10]; ga[1] += t * b[2]; gb[2] += t * a[1]; }
-    { const T t = T(0.18467439092237189) * Pb[10]; ga[3] += t * b[0]; gb[0] += t * a[3]; }
-    { const T t = T(-0.058399170081901861) * Pb[11]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(0.23359668032760758) * Pb[11]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(0.20230065940342065) * Pb[11]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(0.058399170081901729) * Pb[11]; ga[4] += t * b[0]; gb[0] += t * a[4]; }
-    { const T t = T(-0.1430481681026689) * Pb[12]; ga[1] += t * b[0]; gb[0] += t * a[1]; }
-    { const T t = T(0.24776669508347599) * Pb[12]; ga[2] += t * b[1]; gb[1] += t * a[2]; }
-    { const T t = T(-0.1430481681026689) * Pb[12]; ga[3] += t * b[2]; gb[2] += t * a[3]; }
-    { const T t = T(-0.058399170081901861) * Pb[13]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.20230065940342065) * Pb[13]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(0.23359668032760758) * Pb[13]; ga[3] += t * b[1]; gb[1] += t * a[3]; }
-    { const T t = T(-0.058399170081901729) * Pb[13]; ga[4] += t * b[2]; gb[2] += t * a[4]; }
-    { const T t = T(-0.18467439092237189) * Pb[14]; ga[1] += t * b[0]; gb[0] += t * a[1]; }
-    { const T t = T(0.18467439092237189) * Pb[14]; ga[3] += t * b[2]; gb[2] += t * a[3]; }
-    { const T t = T(0.18467439092237187) * Pb[14]; ga[4] += t * b[1]; gb[1] += t * a[4]; }
-    { const T t = T(-0.22617901315954039) * Pb[15]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.22617901315954023) * Pb[15]; ga[4] += t * b[2]; gb[2] += t * a[4]; }
-  }
-};
-template <> struct Couple<3, 2, 2> {
-  static constexpr int kMask = 5;
-  static constexpr int kTerms = 30;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[0] += T(0.2820947917738782) * (a[0] * b[0]);
-    P[0] += T(0.28209479177387831) * (a[1] * b[1]);
-    P[0] += T(0.28209479177387831) * (a[2] * b[2]);
-    P[0] += T(0.28209479177387831) * (a[3] * b[3]);
-    P[0] += T(0.28209479177387831) * (a[4] * b[4]);
-    P[4] += T(-0.18022375157286874) * (a[0] * b[2]);
-    P[4] += T(0.15607834722743999) * (a[1] * b[3]);
-    P[4] += T(-0.18022375157286874) * (a[2] * b[0]);
-    P[4] += T(0.15607834722743999) * (a[3] * b[1]);
-    P[5] += T(0.15607834722743999) * (a[0] * b[3]);
-    P[5] += T(0.090111875786434384) * (a[1] * b[2]);
-    P[5] += T(-0.15607834722744002) * (a[1] * b[4]);
-    P[5] += T(0.090111875786434384) * (a[2] * b[1]);
-    P[5] += T(0.15607834722743999) * (a[3] * b[0]);
-    P[5] += T(-0.15607834722744002) * (a[4] * b[1]);
-    P[6] += T(-0.18022375157286874) * (a[0] * b[0]);
-    P[6] += T(0.090111875786434384) * (a[1] * b[1]);
-    P[6] += T(0.18022375157286855) * (a[2] * b[2]);
-    P[6] += T(0.090111875786434384) * (a[3] * b[3]);
-    P[6] += T(-0.18022375157286849) * (a[4] * b[4]);
-    P[7] += T(0.15607834722743999) * (a[0] * b[1]);
-    P[7] += T(0.15607834722743999) * (a[1] * b[0]);
-    P[7] += T(0.090111875786434384) * (a[2] * b[3]);
-    P[7] += T(0.090111875786434384) * (a[3] * b[2]);
-    P[7] += T(0.15607834722744002) * (a[3] * b[4]);
-    P[7] += T(0.15607834722744002) * (a[4] * b[3]);
-    P[8] += T(-0.15607834722744002) * (a[1] * b[1]);
-    P[8] += T(-0.18022375157286849) * (a[2] * b[4]);
-    P[8] += T(0.15607834722744002) * (a[3] * b[3]);
-    P[8] += T(-0.18022375157286849) * (a[4] * b[2]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(0.2820947917738782) * Pb[0]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.28209479177387831) * Pb[0]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(0.28209479177387831) * Pb[0]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(0.28209479177387831) * Pb[0]; ga[3] += t * b[3]; gb[3] += t * a[3]; }
-    { const T t = T(0.28209479177387831) * Pb[0]; ga[4] += t * b[4]; gb[4] += t * a[4]; }
-    { const T t = T(-0.18022375157286874) * Pb[4]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(0.15607834722743999) * Pb[4]; ga[1] += t * b[3]; gb[3] += t * a[1]; }
-    { const T t = T(-0.18022375157286874) * Pb[4]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(0.15607834722743999) * Pb[4]; ga[3] += t * b[1]; gb[1] += t * a[3]; }
-    { const T t = T(0.15607834722743999) * Pb[5]; ga[0] += t * b[3]; gb[3] += t * a[0]; }
-    { const T t = T(0.090111875786434384) * Pb[5]; ga[1] += t * b[2]; gb[2] += t * a[1]; }
-    { const T t = T(-0.15607834722744002) * Pb[5]; ga[1] += t * b[4]; gb[4] += t * a[1]; }
-    { const T t = T(0.090111875786434384) * Pb[5]; ga[2] += t * b[1]; gb[1] += t * a[2]; }
-    { const T t = T(0.15607834722743999) * Pb[5]; ga[3] += t * b[0]; gb[0] += t * a[3]; }
-    { const T t = T(-0.15607834722744002) * Pb[5]; ga[4] += t * b[1]; gb[1] += t * a[4]; }
-    { const T t = T(-0.18022375157286874) * Pb[6]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.090111875786434384) * Pb[6]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(0.18022375157286855) * Pb[6]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(0.090111875786434384) * Pb[6]; ga[3] += t * b[3]; gb[3] += t * a[3]; }
-    { const T t = T(-0.18022375157286849) * Pb[6]; ga[4] += t * b[4]; gb[4] += t * a[4]; }
-    { const T t = T(0.15607834722743999) * Pb[7]; ga[0] += t * b[1]; gb[1] += t * a[0]; }
-    { const T t = T(0.15607834722743999) * Pb[7]; ga[1] += t * b[0]; gb[0] += t * a[1]; }
-    { const T t = T(0.090111875786434384) * Pb[7]; ga[2] += t * b[3]; gb[3] += t * a[2]; }
-    { const T t = T(0.090111875786434384) * Pb[7]; ga[3] += t * b[2]; gb[2] += t * a[3]; }
-    { const T t = T(0.15607834722744002) * Pb[7]; ga[3] += t * b[4]; gb[4] += t * a[3]; }
-    { const T t = T(0.15607834722744002) * Pb[7]; ga[4] += t * b[3]; gb[3] += t * a[4]; }
-    { const T t = T(-0.15607834722744002) * Pb[8]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(-0.18022375157286849) * Pb[8]; ga[2] += t * b[4]; gb[4] += t * a[2]; }
-    { const T t = T(0.15607834722744002) * Pb[8]; ga[3] += t * b[3]; gb[3] += t * a[3]; }
-    { const T t = T(-0.18022375157286849) * Pb[8]; ga[4] += t * b[2]; gb[2] += t * a[4]; }
-  }
-};
-template <> struct Couple<3, 2, 3> {
-  static constexpr int kMask = 10;
-  static constexpr int kTerms = 62;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[1] += T(-0.058399170081901867) * (a[0] * b[4]);
-    P[1] += T(-0.22617901315954042) * (a[0] * b[6]);
-    P[1] += T(-0.1430481681026689) * (a[1] * b[3]);
-    P[1] += T(-0.18467439092237192) * (a[1] * b[5]);
-    P[1] += T(0.20230065940342068) * (a[2] * b[2]);
-    P[1] += T(0.18467439092237189) * (a[3] * b[1]);
-    P[1] += T(0.22617901315954025) * (a[4] * b[0]);
-    P[1] += T(0.058399170081901736) * (a[4] * b[2]);
-    P[2] += T(0.18467439092237187) * (a[0] * b[1]);
-    P[2] += T(0.23359668032760761) * (a[1] * b[2]);
-    P[2] += T(0.24776669508347601) * (a[2] * b[3]);
-    P[2] += T(0.23359668032760761) * (a[3] * b[4]);
-    P[2] += T(0.18467439092237187) * (a[4] * b[5]);
-    P[3] += T(0.22617901315954042) * (a[0] * b[0]);
-    P[3] += T(-0.058399170081901867) * (a[0] * b[2]);
-    P[3] += T(0.18467439092237189) * (a[1] * b[1]);
-    P[3] += T(0.20230065940342068) * (a[2] * b[4]);
-    P[3] += T(-0.1430481681026689) * (a[3] * b[3]);
-    P[3] += T(0.18467439092237192) * (a[3] * b[5]);
-    P[3] += T(-0.058399170081901736) * (a[4] * b[4]);
-    P[3] += T(0.22617901315954025) * (a[4] * b[6]);
-    P[9] += T(-0.094031597257959357) * (a[0] * b[4]);
-    P[9] += T(0.14867700967939756) * (a[1] * b[5]);
-    P[9] += T(-0.21026104350168001) * (a[2] * b[0]);
-    P[9] += T(0.14867700967939765) * (a[3] * b[1]);
-    P[9] += T(-0.094031597257959315) * (a[4] * b[2]);
-    P[10] += T(-0.1880631945159188) * (a[0] * b[3]);
-    P[10] += T(0.11516471649044524) * (a[1] * b[4]);
-    P[10] += T(-0.14867700967939765) * (a[1] * b[6]);
-    P[10] += T(0.14867700967939765) * (a[3] * b[0]);
-    P[10] += T(0.11516471649044524) * (a[3] * b[2]);
-    P[11] += T(0.14567312407894392) * (a[0] * b[4]);
-    P[11] += T(0.094031597257959329) * (a[0] * b[6]);
-    P[11] += T(0.059470803871758834) * (a[1] * b[3]);
-    P[11] += T(-0.1151647164904453) * (a[1] * b[5]);
-    P[11] += T(0.12615662610100786) * (a[2] * b[2]);
-    P[11] += T(0.11516471649044524) * (a[3] * b[1]);
-    P[11] += T(-0.094031597257959357) * (a[4] * b[0]);
-    P[11] += T(-0.14567312407894395) * (a[4] * b[2]);
-    P[12] += T(-0.1880631945159188) * (a[0] * b[1]);
-    P[12] += T(0.059470803871758834) * (a[1] * b[2]);
-    P[12] += T(0.16820883480134416) * (a[2] * b[3]);
-    P[12] += T(0.059470803871758827) * (a[3] * b[4]);
-    P[12] += T(-0.18806319451591863) * (a[4] * b[5]);
-    P[13] += T(-0.094031597257959315) * (a[0] * b[0]);
-    P[13] += T(0.14567312407894392) * (a[0] * b[2]);
-    P[13] += T(0.11516471649044524) * (a[1] * b[1]);
-    P[13] += T(0.12615662610100786) * (a[2] * b[4]);
-    P[13] += T(0.059470803871758827) * (a[3] * b[3]);
-    P[13] += T(0.11516471649044534) * (a[3] * b[5]);
-    P[13] += T(0.14567312407894398) * (a[4] * b[4]);
-    P[13] += T(-0.094031597257959357) * (a[4] * b[6]);
-    P[14] += T(0.14867700967939756) * (a[1] * b[0]);
-    P[14] += T(-0.1151647164904453) * (a[1] * b[2]);
-    P[14] += T(0.1151647164904453) * (a[3] * b[4]);
-    P[14] += T(0.14867700967939756) * (a[3] * b[6]);
-    P[14] += T(-0.18806319451591863) * (a[4] * b[3]);
-    P[15] += T(0.094031597257959357) * (a[0] * b[2]);
-    P[15] += T(-0.14867700967939765) * (a[1] * b[1]);
-    P[15] += T(-0.21026104350168001) * (a[2] * b[6]);
-    P[15] += T(0.14867700967939756) * (a[3] * b[5]);
-    P[15] += T(-0.094031597257959315) * (a[4] * b[4]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(-0.058399170081901867) * Pb[1]; ga[0] += t * b[4]; gb[4] += t * a[0]; }
-    { const T t = T(-0.22617901315954042) * Pb[1]; ga[0] += t * b[6]; gb[6] += t * a[0]; }
-    { const T t = T(-0.1430481681026689) * Pb[1]; ga[1] += t * b[3]; gb[3] += t * a[1]; }
-    { const T t = T(-0.18467439092237192) * Pb[1]; ga[1] += t * b[5]; gb[5] += t * a[1]; }
-    { const T t = T(0.20230065940342068) * Pb[1]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(0.18467439092237189) * Pb[1]; ga[3] += t * b[1]; gb[1] += t * a[3]; }
-    { const T t = T(0.22617901315954025) * Pb[1]; ga[4] += t * b[0]; gb[0] += t * a[4]; }
-    { const T t = T(0.058399170081901736) * Pb[1]; ga[4] += t * b[2]; gb[2] += t * a[4]; }
-    { const T t = T(0.18467439092237187) * Pb[2]; ga[0] += t * b[1]; gb[1] += t * a[0]; }
-    { const T t = T(0.23359668032760761) * Pb[2]; ga[1] += t * b[2]; gb[2] += t * a[1]; }
-    { const T t = T(0.24776669508347601) * Pb[2]; ga[2] += t * b[3]; gb[3] += t * a[2]; }
-    { const T t = T(0.23359668032760761) * Pb[2]; ga[3] += t * b[4]; gb[4] += t * a[3]; }
-    { const T t = T(0.18467439092237187) * Pb[2]; ga[4] += t * b[5]; gb[5] += t * a[4]; }
-    { const T t = T(0.22617901315954042) * Pb[3]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(-0.058399170081901867) * Pb[3]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(0.18467439092237189) * Pb[3]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(0.20230065940342068) * Pb[3]; ga[2] += t * b[4]; gb[4] += t * a[2]; }
-    { const T t = T(-0.1430481681026689) * Pb[3]; ga[3] += t * b[3]; gb[3] += t * a[3]; }
-    { const T t = T(0.18467439092237192) * Pb[3]; ga[3] += t * b[5]; gb[5] += t * a[3]; }
-    { const T t = T(-0.058399170081901736) * Pb[3]; ga[4] += t * b[4]; gb[4] += t * a[4]; }
-    { const T t = T(0.22617901315954025) * Pb[3]; ga[4] += t * b[6]; gb[6] += t * a[4]; }
-    { const T t = T(-0.094031597257959357) * Pb[9]; ga[0] += t * b[4]; gb[4] += t * a[0]; }
-    { const T t = T(0.14867700967939756) * Pb[9]; ga[1] += t * b[5]; gb[5] += t * a[1]; }
-    { const T t = T(-0.21026104350168001) * Pb[9]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(0.14867700967939765) * Pb[9]; ga[3] += t * b[1]; gb[1] += t * a[3]; }
-    { const T t = T(-0.094031597257959315) * Pb[9]; ga[4] += t * b[2]; gb[2] += t * a[4]; }
-    { const T t = T(-0.1880631945159188) * Pb[10]; ga[0] += t * b[3]; gb[3] += t * a[0]; }
-    { const T t = T(0.11516471649044524) * Pb[10]; ga[1] += t * b[4]; gb[4] += t * a[1]; }
-    { const T t = T(-0.14867700967939765) * Pb[10]; ga[1] += t * b[6]; gb[6] += t * a[1]; }
-    { const T t = T(0.14867700967939765) * Pb[10]; ga[3] += t * b[0]; gb[0] += t * a[3]; }
-    { const T t = T(0.11516471649044524) * Pb[10]; ga[3] += t * b[2]; gb[2] += t * a[3]; }
-    { const T t = T(0.14567312407894392) * Pb[11]; ga[0] += t * b[4]; gb[4] += t * a[0]; }
-    { const T t = T(0.094031597257959329) * Pb[11]; ga[0] += t * b[6]; gb[6] += t * a[0]; }
-    { const T t = T(0.059470803871758834) * Pb[11]; ga[1] += t * b[3]; gb[3] += t * a[1]; }
-    { const T t = T(-0.1151647164904453) * Pb[11]; ga[1] += t * b[5]; gb[5] += t * a[1]; }
-    { const T t = T(0.12615662610100786) * Pb[11]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(0.11516471649044524) * Pb[11]; ga[3] += t * b[1]; gb[1] += t * a[3]; }
-    { const T t = T(-0.094031597257959357) * Pb[11]; ga[4] += t * b[0]; gb[0] += t * a[4]; }
-    { const T t = T(-0.14567312407894395) * Pb[11]; ga[4] += t * b[2]; gb[2] += t * a[4]; }
-    { const T t = T(-0.1880631945159188) * Pb[12]; ga[0] += t * b[1]; gb[1] += t * a[0]; }
-    { const T t = T(0.059470803871758834) * Pb[12]; ga[1] += t * b[2]; gb[2] += t * a[1]; }
-    { const T t = T(0.16820883480134416) * Pb[12]; ga[2] += t * b[3]; gb[3] += t * a[2]; }
-    { const T t = T(0.059470803871758827) * Pb[12]; ga[3] += t * b[4]; gb[4] += t * a[3]; }
-    { const T t = T(-0.18806319451591863) * Pb[12]; ga[4] += t * b[5]; gb[5] += t * a[4]; }
-    { const T t = T(-0.094031597257959315) * Pb[13]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.14567312407894392) * Pb[13]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(0.11516471649044524) * Pb[13]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(0.12615662610100786) * Pb[13]; ga[2] += t * b[4]; gb[4] += t * a[2]; }
-    { const T t = T(0.059470803871758827) * Pb[13]; ga[3] += t * b[3]; gb[3] += t * a[3]; }
-    { const T t = T(0.11516471649044534) * Pb[13]; ga[3] += t * b[5]; gb[5] += t * a[3]; }
-    { const T t = T(0.14567312407894398) * Pb[13]; ga[4] += t * b[4]; gb[4] += t * a[4]; }
-    { const T t = T(-0.094031597257959357) * Pb[13]; ga[4] += t * b[6]; gb[6] += t * a[4]; }
-    { const T t = T(0.14867700967939756) * Pb[14]; ga[1] += t * b[0]; gb[0] += t * a[1]; }
-    { const T t = T(-0.1151647164904453) * Pb[14]; ga[1] += t * b[2]; gb[2] += t * a[1]; }
-    { const T t = T(0.1151647164904453) * Pb[14]; ga[3] += t * b[4]; gb[4] += t * a[3]; }
-    { const T t = T(0.14867700967939756) * Pb[14]; ga[3] += t * b[6]; gb[6] += t * a[3]; }
-    { const T t = T(-0.18806319451591863) * Pb[14]; ga[4] += t * b[3]; gb[3] += t * a[4]; }
-    { const T t = T(0.094031597257959357) * Pb[15]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(-0.14867700967939765) * Pb[15]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(-0.21026104350168001) * Pb[15]; ga[2] += t * b[6]; gb[6] += t * a[2]; }
-    { const T t = T(0.14867700967939756) * Pb[15]; ga[3] += t * b[5]; gb[5] += t * a[3]; }
-    { const T t = T(-0.094031597257959315) * Pb[15]; ga[4] += t * b[4]; gb[4] += t * a[4]; }
-  }
-};
-template <> struct Couple<3, 3, 0> {
-  static constexpr int kMask = 8;
-  static constexpr int kTerms = 7;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[9] += T(0.2820947917738782) * (a[0] * b[0]);
-    P[10] += T(0.2820947917738782) * (a[1] * b[0]);
-    P[11] += T(0.28209479177387825) * (a[2] * b[0]);
-    P[12] += T(0.28209479177387814) * (a[3] * b[0]);
-    P[13] += T(0.28209479177387825) * (a[4] * b[0]);
-    P[14] += T(0.28209479177387825) * (a[5] * b[0]);
-    P[15] += T(0.2820947917738782) * (a[6] * b[0]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(0.2820947917738782) * Pb[9]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.2820947917738782) * Pb[10]; ga[1] += t * b[0]; gb[0] += t * a[1]; }
-    { const T t = T(0.28209479177387825) * Pb[11]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(0.28209479177387814) * Pb[12]; ga[3] += t * b[0]; gb[0] += t * a[3]; }
-    { const T t = T(0.28209479177387825) * Pb[13]; ga[4] += t * b[0]; gb[0] += t * a[4]; }
-    { const T t = T(0.28209479177387825) * Pb[14]; ga[5] += t * b[0]; gb[0] += t * a[5]; }
-    { const T t = T(0.2820947917738782) * Pb[15]; ga[6] += t * b[0]; gb[0] += t * a[6]; }
-  }
-};
-template <> struct Couple<3, 3, 1> {
-  static constexpr int kMask = 4;
-  static constexpr int kTerms = 21;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[4] += T(0.22617901315954042) * (a[0] * b[2]);
-    P[4] += T(0.18467439092237187) * (a[1] * b[1]);
-    P[4] += T(-0.058399170081901867) * (a[2] * b[2]);
-    P[4] += T(-0.058399170081901867) * (a[4] * b[0]);
-    P[4] += T(-0.22617901315954042) * (a[6] * b[0]);
-    P[5] += T(0.18467439092237189) * (a[1] * b[2]);
-    P[5] += T(0.23359668032760761) * (a[2] * b[1]);
-    P[5] += T(-0.1430481681026689) * (a[3] * b[0]);
-    P[5] += T(-0.18467439092237192) * (a[5] * b[0]);
-    P[6] += T(0.20230065940342068) * (a[2] * b[0]);
-    P[6] += T(0.24776669508347601) * (a[3] * b[1]);
-    P[6] += T(0.20230065940342068) * (a[4] * b[2]);
-    P[7] += T(0.18467439092237189) * (a[1] * b[0]);
-    P[7] += T(-0.1430481681026689) * (a[3] * b[2]);
-    P[7] += T(0.23359668032760761) * (a[4] * b[1]);
-    P[7] += T(0.18467439092237192) * (a[5] * b[2]);
-    P[8] += T(0.22617901315954025) * (a[0] * b[0]);
-    P[8] += T(0.058399170081901736) * (a[2] * b[0]);
-    P[8] += T(-0.058399170081901736) * (a[4] * b[2]);
-    P[8] += T(0.18467439092237187) * (a[5] * b[1]);
-    P[8] += T(0.22617901315954025) * (a[6] * b[2]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(0.22617901315954042) * Pb[4]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(0.18467439092237187) * Pb[4]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(-0.058399170081901867) * Pb[4]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(-0.058399170081901867) * Pb[4]; ga[4] += t * b[0]; gb[0] += t * a[4]; }
-    { const T t = T(-0.22617901315954042) * Pb[4]; ga[6] += t * b[0]; gb[0] += t * a[6]; }
-    { const T t = T(0.18467439092237189) * Pb[5]; ga[1] += t * b[2]; gb[2] += t * a[1]; }
-    { const T t = T(0.23359668032760761) * Pb[5]; ga[2] += t * b[1]; gb[1] += t * a[2]; }
-    { const T t = T(-0.1430481681026689) * Pb[5]; ga[3] += t * b[0]; gb[0] += t * a[3]; }
-    { const T t = T(-0.18467439092237192) * Pb[5]; ga[5] += t * b[0]; gb[0] += t * a[5]; }
-    { const T t = T(0.20230065940342068) * Pb[6]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(0.24776669508347601) * Pb[6]; ga[3] += t * b[1]; gb[1] += t * a[3]; }
-    { const T t = T(0.20230065940342068) * Pb[6]; ga[4] += t * b[2]; gb[2] += t * a[4]; }
-    { const T t = T(0.18467439092237189) * Pb[7]; ga[1] += t * b[0]; gb[0] += t * a[1]; }
-    { const T t = T(-0.1430481681026689) * Pb[7]; ga[3] += t * b[2]; gb[2] += t * a[3]; }
-    { const T t = T(0.23359668032760761) * Pb[7]; ga[4] += t * b[1]; gb[1] += t * a[4]; }
-    { const T t = T(0.18467439092237192) * Pb[7]; ga[5] += t * b[2]; gb[2] += t * a[5]; }
-    { const T t = T(0.22617901315954025) * Pb[8]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.058399170081901736) * Pb[8]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(-0.058399170081901736) * Pb[8]; ga[4] += t * b[2]; gb[2] += t * a[4]; }
-    { const T t = T(0.18467439092237187) * Pb[8]; ga[5] += t * b[1]; gb[1] += t * a[5]; }
-    { const T t = T(0.22617901315954025) * Pb[8]; ga[6] += t * b[2]; gb[2] += t * a[6]; }
-  }
-};
-template <> struct Couple<3, 3, 2> {
-  static constexpr int kMask = 10;
-  static constexpr int kTerms = 62;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[1] += T(0.22617901315954025) * (a[0] * b[4]);
-    P[1] += T(0.18467439092237189) * (a[1] * b[3]);
-    P[1] += T(0.20230065940342068) * (a[2] * b[2]);
-    P[1] += T(0.058399170081901736) * (a[2] * b[4]);
-    P[1] += T(-0.1430481681026689) * (a[3] * b[1]);
-    P[1] += T(-0.058399170081901867) * (a[4] * b[0]);
-    P[1] += T(-0.18467439092237192) * (a[5] * b[1]);
-    P[1] += T(-0.22617901315954042) * (a[6] * b[0]);
-    P[2] += T(0.18467439092237187) * (a[1] * b[0]);
-    P[2] += T(0.23359668032760761) * (a[2] * b[1]);
-    P[2] += T(0.24776669508347601) * (a[3] * b[2]);
-    P[2] += T(0.23359668032760761) * (a[4] * b[3]);
-    P[2] += T(0.18467439092237187) * (a[5] * b[4]);
-    P[3] += T(0.22617901315954042) * (a[0] * b[0]);
-    P[3] += T(0.18467439092237189) * (a[1] * b[1]);
-    P[3] += T(-0.058399170081901867) * (a[2] * b[0]);
-    P[3] += T(-0.1430481681026689) * (a[3] * b[3]);
-    P[3] += T(0.20230065940342068) * (a[4] * b[2]);
-    P[3] += T(-0.058399170081901736) * (a[4] * b[4]);
-    P[3] += T(0.18467439092237192) * (a[5] * b[3]);
-    P[3] += T(0.22617901315954025) * (a[6] * b[4]);
-    P[9] += T(-0.21026104350168001) * (a[0] * b[2]);
-    P[9] += T(0.14867700967939765) * (a[1] * b[3]);
-    P[9] += T(-0.094031597257959315) * (a[2] * b[4]);
-    P[9] += T(-0.094031597257959357) * (a[4] * b[0]);
-    P[9] += T(0.14867700967939756) * (a[5] * b[1]);
-    P[10] += T(0.14867700967939765) * (a[0] * b[3]);
-    P[10] += T(0.11516471649044524) * (a[2] * b[3]);
-    P[10] += T(-0.1880631945159188) * (a[3] * b[0]);
-    P[10] += T(0.11516471649044524) * (a[4] * b[1]);
-    P[10] += T(-0.14867700967939765) * (a[6] * b[1]);
-    P[11] += T(-0.094031597257959357) * (a[0] * b[4]);
-    P[11] += T(0.11516471649044524) * (a[1] * b[3]);
-    P[11] += T(0.12615662610100786) * (a[2] * b[2]);
-    P[11] += T(-0.14567312407894395) * (a[2] * b[4]);
-    P[11] += T(0.059470803871758834) * (a[3] * b[1]);
-    P[11] += T(0.14567312407894392) * (a[4] * b[0]);
-    P[11] += T(-0.1151647164904453) * (a[5] * b[1]);
-    P[11] += T(0.094031597257959329) * (a[6] * b[0]);
-    P[12] += T(-0.1880631945159188) * (a[1] * b[0]);
-    P[12] += T(0.059470803871758834) * (a[2] * b[1]);
-    P[12] += T(0.16820883480134416) * (a[3] * b[2]);
-    P[12] += T(0.059470803871758827) * (a[4] * b[3]);
-    P[12] += T(-0.18806319451591863) * (a[5] * b[4]);
-    P[13] += T(-0.094031597257959315) * (a[0] * b[0]);
-    P[13] += T(0.11516471649044524) * (a[1] * b[1]);
-    P[13] += T(0.14567312407894392) * (a[2] * b[0]);
-    P[13] += T(0.059470803871758827) * (a[3] * b[3]);
-    P[13] += T(0.12615662610100786) * (a[4] * b[2]);
-    P[13] += T(0.14567312407894398) * (a[4] * b[4]);
-    P[13] += T(0.11516471649044534) * (a[5] * b[3]);
-    P[13] += T(-0.094031597257959357) * (a[6] * b[4]);
-    P[14] += T(0.14867700967939756) * (a[0] * b[1]);
-    P[14] += T(-0.1151647164904453) * (a[2] * b[1]);
-    P[14] += T(-0.18806319451591863) * (a[3] * b[4]);
-    P[14] += T(0.1151647164904453) * (a[4] * b[3]);
-    P[14] += T(0.14867700967939756) * (a[6] * b[3]);
-    P[15] += T(-0.14867700967939765) * (a[1] * b[1]);
-    P[15] += T(0.094031597257959357) * (a[2] * b[0]);
-    P[15] += T(-0.094031597257959315) * (a[4] * b[4]);
-    P[15] += T(0.14867700967939756) * (a[5] * b[3]);
-    P[15] += T(-0.21026104350168001) * (a[6] * b[2]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(0.22617901315954025) * Pb[1]; ga[0] += t * b[4]; gb[4] += t * a[0]; }
-    { const T t = T(0.18467439092237189) * Pb[1]; ga[1] += t * b[3]; gb[3] += t * a[1]; }
-    { const T t = T(0.20230065940342068) * Pb[1]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(0.058399170081901736) * Pb[1]; ga[2] += t * b[4]; gb[4] += t * a[2]; }
-    { const T t = T(-0.1430481681026689) * Pb[1]; ga[3] += t * b[1]; gb[1] += t * a[3]; }
-    { const T t = T(-0.058399170081901867) * Pb[1]; ga[4] += t * b[0]; gb[0] += t * a[4]; }
-    { const T t = T(-0.18467439092237192) * Pb[1]; ga[5] += t * b[1]; gb[1] += t * a[5]; }
-    { const T t = T(-0.22617901315954042) * Pb[1]; ga[6] += t * b[0]; gb[0] += t * a[6]; }
-    { const T t = T(0.18467439092237187) * Pb[2]; ga[1] += t * b[0]; gb[0] += t * a[1]; }
-    { const T t = T(0.23359668032760761) * Pb[2]; ga[2] += t * b[1]; gb[1] += t * a[2]; }
-    { const T t = T(0.24776669508347601) * Pb[2]; ga[3] += t * b[2]; gb[2] += t * a[3]; }
-    { const T t = T(0.23359668032760761) * Pb[2]; ga[4] += t * b[3]; gb[3] += t * a[4]; }
-    { const T t = T(0.18467439092237187) * Pb[2]; ga[5] += t * b[4]; gb[4] += t * a[5]; }
-    { const T t = T(0.22617901315954042) * Pb[3]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.18467439092237189) * Pb[3]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(-0.058399170081901867) * Pb[3]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(-0.1430481681026689) * Pb[3]; ga[3] += t * b[3]; gb[3] += t * a[3]; }
-    { const T t = T(0.20230065940342068) * Pb[3]; ga[4] += t * b[2]; gb[2] += t * a[4]; }
-    { const T t = T(-0.058399170081901736) * Pb[3]; ga[4] += t * b[4]; gb[4] += t * a[4]; }
-    { const T t = T(0.18467439092237192) * Pb[3]; ga[5] += t * b[3]; gb[3] += t * a[5]; }
-    { const T t = T(0.22617901315954025) * Pb[3]; ga[6] += t * b[4]; gb[4] += t * a[6]; }
-    { const T t = T(-0.21026104350168001) * Pb[9]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(0.14867700967939765) * Pb[9]; ga[1] += t * b[3]; gb[3] += t * a[1]; }
-    { const T t = T(-0.094031597257959315) * Pb[9]; ga[2] += t * b[4]; gb[4] += t * a[2]; }
-    { const T t = T(-0.094031597257959357) * Pb[9]; ga[4] += t * b[0]; gb[0] += t * a[4]; }
-    { const T t = T(0.14867700967939756) * Pb[9]; ga[5] += t * b[1]; gb[1] += t * a[5]; }
-    { const T t = T(0.14867700967939765) * Pb[10]; ga[0] += t * b[3]; gb[3] += t * a[0]; }
-    { const T t = T(0.11516471649044524) * Pb[10]; ga[2] += t * b[3]; gb[3] += t * a[2]; }
-    { const T t = T(-0.1880631945159188) * Pb[10]; ga[3] += t * b[0]; gb[0] += t * a[3]; }
-    { const T t = T(0.11516471649044524) * Pb[10]; ga[4] += t * b[1]; gb[1] += t * a[4]; }
-    { const T t = T(-0.14867700967939765) * Pb[10]; ga[6] += t * b[1]; gb[1] += t * a[6]; }
-    { const T t = T(-0.094031597257959357) * Pb[11]; ga[0] += t * b[4]; gb[4] += t * a[0]; }
-    { const T t = T(0.11516471649044524) * Pb[11]; ga[1] += t * b[3]; gb[3] += t * a[1]; }
-    { const T t = T(0.12615662610100786) * Pb[11]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(-0.14567312407894395) * Pb[11]; ga[2] += t * b[4]; gb[4] += t * a[2]; }
-    { const T t = T(0.059470803871758834) * Pb[11]; ga[3] += t * b[1]; gb[1] += t * a[3]; }
-    { const T t = T(0.14567312407894392) * Pb[11]; ga[4] += t * b[0]; gb[0] += t * a[4]; }
-    { const T t = T(-0.1151647164904453) * Pb[11]; ga[5] += t * b[1]; gb[1] += t * a[5]; }
-    { const T t = T(0.094031597257959329) * Pb[11]; ga[6] += t * b[0]; gb[0] += t * a[6]; }
-    { const T t = T(-0.1880631945159188) * Pb[12]; ga[1] += t * b[0]; gb[0] += t * a[1]; }
-    { const T t = T(0.059470803871758834) * Pb[12]; ga[2] += t * b[1]; gb[1] += t * a[2]; }
-    { const T t = T(0.16820883480134416) * Pb[12]; ga[3] += t * b[2]; gb[2] += t * a[3]; }
-    { const T t = T(0.059470803871758827) * Pb[12]; ga[4] += t * b[3]; gb[3] += t * a[4]; }
-    { const T t = T(-0.18806319451591863) * Pb[12]; ga[5] += t * b[4]; gb[4] += t * a[5]; }
-    { const T t = T(-0.094031597257959315) * Pb[13]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.11516471649044524) * Pb[13]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(0.14567312407894392) * Pb[13]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(0.059470803871758827) * Pb[13]; ga[3] += t * b[3]; gb[3] += t * a[3]; }
-    { const T t = T(0.12615662610100786) * Pb[13]; ga[4] += t * b[2]; gb[2] += t * a[4]; }
-    { const T t = T(0.14567312407894398) * Pb[13]; ga[4] += t * b[4]; gb[4] += t * a[4]; }
-    { const T t = T(0.11516471649044534) * Pb[13]; ga[5] += t * b[3]; gb[3] += t * a[5]; }
-    { const T t = T(-0.094031597257959357) * Pb[13]; ga[6] += t * b[4]; gb[4] += t * a[6]; }
-    { const T t = T(0.14867700967939756) * Pb[14]; ga[0] += t * b[1]; gb[1] += t * a[0]; }
-    { const T t = T(-0.1151647164904453) * Pb[14]; ga[2] += t * b[1]; gb[1] += t * a[2]; }
-    { const T t = T(-0.18806319451591863) * Pb[14]; ga[3] += t * b[4]; gb[4] += t * a[3]; }
-    { const T t = T(0.1151647164904453) * Pb[14]; ga[4] += t * b[3]; gb[3] += t * a[4]; }
-    { const T t = T(0.14867700967939756) * Pb[14]; ga[6] += t * b[3]; gb[3] += t * a[6]; }
-    { const T t = T(-0.14867700967939765) * Pb[15]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(0.094031597257959357) * Pb[15]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(-0.094031597257959315) * Pb[15]; ga[4] += t * b[4]; gb[4] += t * a[4]; }
-    { const T t = T(0.14867700967939756) * Pb[15]; ga[5] += t * b[3]; gb[3] += t * a[5]; }
-    { const T t = T(-0.21026104350168001) * Pb[15]; ga[6] += t * b[2]; gb[2] += t * a[6]; }
-  }
-};
-template <> struct Couple<3, 3, 3> {
-  static constexpr int kMask = 5;
-  static constexpr int kTerms = 48;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[0] += T(0.2820947917738782) * (a[0] * b[0]);
-    P[0] += T(0.2820947917738782) * (a[1] * b[1]);
-    P[0] += T(0.28209479177387825) * (a[2] * b[2]);
-    P[0] += T(0.28209479177387814) * (a[3] * b[3]);
-    P[0] += T(0.28209479177387825) * (a[4] * b[4]);
-    P[0] += T(0.28209479177387825) * (a[5] * b[5]);
-    P[0] += T(0.2820947917738782) * (a[6] * b[6]);
-    P[4] += T(-0.094031597257959357) * (a[0] * b[4]);
-    P[4] += T(-0.1880631945159188) * (a[1] * b[3]);
-    P[4] += T(0.14567312407894387) * (a[2] * b[4]);
-    P[4] += T(0.094031597257959357) * (a[2] * b[6]);
-    P[4] += T(-0.1880631945159188) * (a[3] * b[1]);
-    P[4] += T(-0.094031597257959357) * (a[4] * b[0]);
-    P[4] += T(0.14567312407894387) * (a[4] * b[2]);
-    P[4] += T(0.094031597257959357) * (a[6] * b[2]);
-    P[5] += T(0.14867700967939754) * (a[0] * b[5]);
-    P[5] += T(0.11516471649044524) * (a[1] * b[4]);
-    P[5] += T(-0.14867700967939765) * (a[1] * b[6]);
-    P[5] += T(0.0594708038717588) * (a[2] * b[3]);
-    P[5] += T(-0.1151647164904453) * (a[2] * b[5]);
-    P[5] += T(0.0594708038717588) * (a[3] * b[2]);
-    P[5] += T(0.11516471649044524) * (a[4] * b[1]);
-    P[5] += T(0.14867700967939754) * (a[5] * b[0]);
-    P[5] += T(-0.1151647164904453) * (a[5] * b[2]);
-    P[5] += T(-0.14867700967939765) * (a[6] * b[1]);
-    P[6] += T(-0.21026104350168001) * (a[0] * b[0]);
-    P[6] += T(0.12615662610100786) * (a[2] * b[2]);
-    P[6] += T(0.16820883480134416) * (a[3] * b[3]);
-    P[6] += T(0.12615662610100786) * (a[4] * b[4]);
-    P[6] += T(-0.21026104350168001) * (a[6] * b[6]);
-    P[7] += T(0.14867700967939765) * (a[0] * b[1]);
-    P[7] += T(0.14867700967939765) * (a[1] * b[0]);
-    P[7] += T(0.11516471649044524) * (a[1] * b[2]);
-    P[7] += T(0.11516471649044524) * (a[2] * b[1]);
-    P[7] += T(0.059470803871758765) * (a[3] * b[4]);
-    P[7] += T(0.059470803871758765) * (a[4] * b[3]);
-    P[7] += T(0.1151647164904453) * (a[4] * b[5]);
-    P[7] += T(0.11516471649044534) * (a[5] * b[4]);
-    P[7] += T(0.14867700967939754) * (a[5] * b[6]);
-    P[7] += T(0.14867700967939754) * (a[6] * b[5]);
-    P[8] += T(-0.094031597257959357) * (a[0] * b[2]);
-    P[8] += T(-0.094031597257959357) * (a[2] * b[0]);
-    P[8] += T(-0.14567312407894392) * (a[2] * b[2]);
-    P[8] += T(-0.18806319451591855) * (a[3] * b[5]);
-    P[8] += T(0.14567312407894392) * (a[4] * b[4]);
-    P[8] += T(-0.094031597257959371) * (a[4] * b[6]);
-    P[8] += T(-0.1880631945159186) * (a[5] * b[3]);
-    P[8] += T(-0.094031597257959357) * (a[6] * b[4]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(0.2820947917738782) * Pb[0]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.2820947917738782) * Pb[0]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(0.28209479177387825) * Pb[0]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(0.28209479177387814) * Pb[0]; ga[3] += t * b[3]; gb[3] += t * a[3]; }
-    { const T t = T(0.28209479177387825) * Pb[0]; ga[4] += t * b[4]; gb[4] += t * a[4]; }
-    { const T t = T(0.28209479177387825) * Pb[0]; ga[5] += t * b[5]; gb[5] += t * a[5]; }
-    { const T t = T(0.2820947917738782) * Pb[0]; ga[6] += t * b[6]; gb[6] += t * a[6]; }
-    { const T t = T(-0.094031597257959357) * Pb[4]; ga[0] += t * b[4]; gb[4] += t * a[0]; }
-    { const T t = T(-0.1880631945159188) * Pb[4]; ga[1] += t * b[3]; gb[3] += t * a[1]; }
-    { const T t = T(0.14567312407894387) * Pb[4]; ga[2] += t * b[4]; gb[4] += t * a[2]; }
-    { const T t = T(0.094031597257959357) * Pb[4]; ga[2] += t * b[6]; gb[6] += t * a[2]; }
-    { const T t = T(-0.1880631945159188) * Pb[4]; ga[3] += t * b[1]; gb[1] += t * a[3]; }
-    { const T t = T(-0.094031597257959357) * Pb[4]; ga[4] += t * b[0]; gb[0] += t * a[4]; }
-    { const T t = T(0.14567312407894387) * Pb[4]; ga[4] += t * b[2]; gb[2] += t * a[4]; }
-    { const T t = T(0.094031597257959357) * Pb[4]; ga[6] += t * b[2]; gb[2] += t * a[6]; }
-    { const T t = T(0.14867700967939754) * Pb[5]; ga[0] += t * b[5]; gb[5] += t * a[0]; }
-    { const T t = T(0.11516471649044524) * Pb[5]; ga[1] += t * b[4]; gb[4] += t * a[1]; }
-    { const T t = T(-0.14867700967939765) * Pb[5]; ga[1] += t * b[6]; gb[6] += t * a[1]; }
-    { const T t = T(0.0594708038717588) * Pb[5]; ga[2] += t * b[3]; gb[3] += t * a[2]; }
-    { const T t = T(-0.1151647164904453) * Pb[5]; ga[2] += t * b[5]; gb[5] += t * a[2]; }
-    { const T t = T(0.0594708038717588) * Pb[5]; ga[3] += t * b[2]; gb[2] += t * a[3]; }
-    { const T t = T(0.11516471649044524) * Pb[5]; ga[4] += t * b[1]; gb[1] += t * a[4]; }
-    { const T t = T(0.14867700967939754) * Pb[5]; ga[5] += t * b[0]; gb[0] += t * a[5]; }
-    { const T t = T(-0.1151647164904453) * Pb[5]; ga[5] += t * b[2]; gb[2] += t * a[5]; }
-    { const T t = T(-0.14867700967939765) * Pb[5]; ga[6] += t * b[1]; gb[1] += t * a[6]; }
-    { const T t = T(-0.21026104350168001) * Pb[6]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.12615662610100786) * Pb[6]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(0.16820883480134416) * Pb[6]; ga[3] += t * b[3]; gb[3] += t * a[3]; }
-    { const T t = T(0.12615662610100786) * Pb[6]; ga[4] += t * b[4]; gb[4] += t * a[4]; }
-    { const T t = T(-0.21026104350168001) * Pb[6]; ga[6] += t * b[6]; gb[6] += t * a[6]; }
-    { const T t = T(0.14867700967939765) * Pb[7]; ga[0] += t * b[1]; gb[1] += t * a[0]; }
-    { const T t = T(0.14867700967939765) * Pb[7]; ga[1] += t * b[0]; gb[0] += t * a[1]; }
-    { const T t = T(0.11516471649044524) * Pb[7]; ga[1] += t * b[2]; gb[2] += t * a[1]; }
-    { const T t = T(0.11516471649044524) * Pb[7]; ga[2] += t * b[1]; gb[1] += t * a[2]; }
-    { const T t = T(0.059470803871758765) * Pb[7]; ga[3] += t * b[4]; gb[4] += t * a[3]; }
-    { const T t = T(0.059470803871758765) * Pb[7]; ga[4] += t * b[3]; gb[3] += t * a[4]; }
-    { const T t = T(0.1151647164904453) * Pb[7]; ga[4] += t * b[5]; gb[5] += t * a[4]; }
-    { const T t = T(0.11516471649044534) * Pb[7]; ga[5] += t * b[4]; gb[4] += t * a[5]; }
-    { const T t = T(0.14867700967939754) * Pb[7]; ga[5] += t * b[6]; gb[6] += t * a[5]; }
-    { const T t = T(0.14867700967939754) * Pb[7]; ga[6] += t * b[5]; gb[5] += t * a[6]; }
-    { const T t = T(-0.094031597257959357) * Pb[8]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(-0.094031597257959357) * Pb[8]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(-0.14567312407894392) * Pb[8]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(-0.18806319451591855) * Pb[8]; ga[3] += t * b[5]; gb[5] += t * a[3]; }
-    { const T t = T(0.14567312407894392) * Pb[8]; ga[4] += t * b[4]; gb[4] += t * a[4]; }
-    { const T t = T(-0.094031597257959371) * Pb[8]; ga[4] += t * b[6]; gb[6] += t * a[4]; }
-    { const T t = T(-0.1880631945159186) * Pb[8]; ga[5] += t * b[3]; gb[3] += t * a[5]; }
-    { const T t = T(-0.094031597257959357) * Pb[8]; ga[6] += t * b[4]; gb[4] += t * a[6]; }
-  }
-};
-template <> struct Couple<4, 0, 0> {
-  static constexpr int kMask = 1;
-  static constexpr int kTerms = 1;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[0] += T(0.28209479177387803) * (a[0] * b[0]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(0.28209479177387803) * Pb[0]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-  }
-};
-template <> struct Couple<4, 0, 1> {
-  static constexpr int kMask = 2;
-  static constexpr int kTerms = 3;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[1] += T(0.28209479177387808) * (a[0] * b[0]);
-    P[2] += T(0.28209479177387808) * (a[0] * b[1]);
-    P[3] += T(0.28209479177387808) * (a[0] * b[2]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(0.28209479177387808) * Pb[1]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.28209479177387808) * Pb[2]; ga[0] += t * b[1]; gb[1] += t * a[0]; }
-    { const T t = T(0.28209479177387808) * Pb[3]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-  }
-};
-template <> struct Couple<4, 0, 2> {
-  static constexpr int kMask = 4;
-  static constexpr int kTerms = 5;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[4] += T(0.2820947917738782) * (a[0] * b[0]);
-    P[5] += T(0.28209479177387831) * (a[0] * b[1]);
-    P[6] += T(0.28209479177387831) * (a[0] * b[2]);
-    P[7] += T(0.28209479177387831) * (a[0] * b[3]);
-    P[8] += T(0.28209479177387831) * (a[0] * b[4]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(0.2820947917738782) * Pb[4]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.28209479177387831) * Pb[5]; ga[0] += t * b[1]; gb[1] += t * a[0]; }
-    { const T t = T(0.28209479177387831) * Pb[6]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(0.28209479177387831) * Pb[7]; ga[0] += t * b[3]; gb[3] += t * a[0]; }
-    { const T t = T(0.28209479177387831) * Pb[8]; ga[0] += t * b[4]; gb[4] += t * a[0]; }
-  }
-};
-template <> struct Couple<4, 0, 3> {
-  static constexpr int kMask = 8;
-  static constexpr int kTerms = 7;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[9] += T(0.2820947917738782) * (a[0] * b[0]);
-    P[10] += T(0.2820947917738782) * (a[0] * b[1]);
-    P[11] += T(0.28209479177387825) * (a[0] * b[2]);
-    P[12] += T(0.28209479177387814) * (a[0] * b[3]);
-    P[13] += T(0.28209479177387825) * (a[0] * b[4]);
-    P[14] += T(0.28209479177387825) * (a[0] * b[5]);
-    P[15] += T(0.2820947917738782) * (a[0] * b[6]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(0.2820947917738782) * Pb[9]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.2820947917738782) * Pb[10]; ga[0] += t * b[1]; gb[1] += t * a[0]; }
-    { const T t = T(0.28209479177387825) * Pb[11]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(0.28209479177387814) * Pb[12]; ga[0] += t * b[3]; gb[3] += t * a[0]; }
-    { const T t = T(0.28209479177387825) * Pb[13]; ga[0] += t * b[4]; gb[4] += t * a[0]; }
-    { const T t = T(0.28209479177387825) * Pb[14]; ga[0] += t * b[5]; gb[5] += t * a[0]; }
-    { const T t = T(0.2820947917738782) * Pb[15]; ga[0] += t * b[6]; gb[6] += t * a[0]; }
-  }
-};
-template <> struct Couple<4, 0, 4> {
-  static constexpr int kMask = 16;
-  static constexpr int kTerms = 9;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[16] += T(0.28209479177387781) * (a[0] * b[0]);
-    P[17] += T(0.28209479177387808) * (a[0] * b[1]);
-    P[18] += T(0.2820947917738782) * (a[0] * b[2]);
-    P[19] += T(0.28209479177387786) * (a[0] * b[3]);
-    P[20] += T(0.28209479177387836) * (a[0] * b[4]);
-    P[21] += T(0.28209479177387781) * (a[0] * b[5]);
-    P[22] += T(0.2820947917738782) * (a[0] * b[6]);
-    P[23] += T(0.28209479177387808) * (a[0] * b[7]);
-    P[24] += T(0.28209479177387825) * (a[0] * b[8]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(0.28209479177387781) * Pb[16]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.28209479177387808) * Pb[17]; ga[0] += t * b[1]; gb[1] += t * a[0]; }
-    { const T t = T(0.2820947917738782) * Pb[18]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(0.28209479177387786) * Pb[19]; ga[0] += t * b[3]; gb[3] += t * a[0]; }
-    { const T t = T(0.28209479177387836) * Pb[20]; ga[0] += t * b[4]; gb[4] += t * a[0]; }
-    { const T t = T(0.28209479177387781) * Pb[21]; ga[0] += t * b[5]; gb[5] += t * a[0]; }
-    { const T t = T(0.2820947917738782) * Pb[22]; ga[0] += t * b[6]; gb[6] += t * a[0]; }
-    { const T t = T(0.28209479177387808) * Pb[23]; ga[0] += t * b[7]; gb[7] += t * a[0]; }
-    { const T t = T(0.28209479177387825) * Pb[24]; ga[0] += t * b[8]; gb[8] += t * a[0]; }
-  }
-};
-template <> struct Couple<4, 1, 0> {
-  static constexpr int kMask = 2;
-  static constexpr int kTerms = 3;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[1] += T(0.28209479177387808) * (a[0] * b[0]);
-    P[2] += T(0.28209479177387808) * (a[1] * b[0]);
-    P[3] += T(0.28209479177387808) * (a[2] * b[0]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(0.28209479177387808) * Pb[1]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.28209479177387808) * Pb[2]; ga[1] += t * b[0]; gb[0] += t * a[1]; }
-    { const T t = T(0.28209479177387808) * Pb[3]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-  }
-};
-template <> struct Couple<4, 1, 1> {
-  static constexpr int kMask = 5;
-  static constexpr int kTerms = 14;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[0] += T(0.28209479177387803) * (a[0] * b[0]);
-    P[0] += T(0.28209479177387803) * (a[1] * b[1]);
-    P[0] += T(0.28209479177387803) * (a[2] * b[2]);
-    P[4] += T(0.21850968611841587) * (a[0] * b[2]);
-    P[4] += T(0.21850968611841587) * (a[2] * b[0]);
-    P[5] += T(0.21850968611841587) * (a[0] * b[1]);
-    P[5] += T(0.21850968611841587) * (a[1] * b[0]);
-    P[6] += T(-0.12615662610100806) * (a[0] * b[0]);
-    P[6] += T(0.252313252202016) * (a[1] * b[1]);
-    P[6] += T(-0.12615662610100806) * (a[2] * b[2]);
-    P[7] += T(0.21850968611841587) * (a[1] * b[2]);
-    P[7] += T(0.21850968611841587) * (a[2] * b[1]);
-    P[8] += T(-0.2185096861184159) * (a[0] * b[0]);
-    P[8] += T(0.2185096861184159) * (a[2] * b[2]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(0.28209479177387803) * Pb[0]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.28209479177387803) * Pb[0]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(0.28209479177387803) * Pb[0]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(0.21850968611841587) * Pb[4]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(0.21850968611841587) * Pb[4]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(0.21850968611841587) * Pb[5]; ga[0] += t * b[1]; gb[1] += t * a[0]; }
-    { const T t = T(0.21850968611841587) * Pb[5]; ga[1] += t * b[0]; gb[0] += t * a[1]; }
-    { const T t = T(-0.12615662610100806) * Pb[6]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.252313252202016) * Pb[6]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(-0.12615662610100806) * Pb[6]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(0.21850968611841587) * Pb[7]; ga[1] += t * b[2]; gb[2] += t * a[1]; }
-    { const T t = T(0.21850968611841587) * Pb[7]; ga[2] += t * b[1]; gb[1] += t * a[2]; }
-    { const T t = T(-0.2185096861184159) * Pb[8]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.2185096861184159) * Pb[8]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-  }
-};
-template <> struct Couple<4, 1, 2> {
-  static constexpr int kMask = 10;
-  static constexpr int kTerms = 32;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[1] += T(-0.12615662610100806) * (a[0] * b[2]);
-    P[1] += T(-0.2185096861184159) * (a[0] * b[4]);
-    P[1] += T(0.21850968611841587) * (a[1] * b[1]);
-    P[1] += T(0.21850968611841587) * (a[2] * b[0]);
-    P[2] += T(0.21850968611841587) * (a[0] * b[1]);
-    P[2] += T(0.252313252202016) * (a[1] * b[2]);
-    P[2] += T(0.21850968611841587) * (a[2] * b[3]);
-    P[3] += T(0.21850968611841587) * (a[0] * b[0]);
-    P[3] += T(0.21850968611841587) * (a[1] * b[3]);
-    P[3] += T(-0.12615662610100806) * (a[2] * b[2]);
-    P[3] += T(0.2185096861184159) * (a[2] * b[4]);
-    P[9] += T(0.22617901315954023) * (a[0] * b[4]);
-    P[9] += T(0.22617901315954039) * (a[2] * b[0]);
-    P[10] += T(0.18467439092237189) * (a[0] * b[3]);
-    P[10] += T(0.18467439092237187) * (a[1] * b[0]);
-    P[10] += T(0.18467439092237189) * (a[2] * b[1]);
-    P[11] += T(0.20230065940342065) * (a[0] * b[2]);
-    P[11] += T(0.058399170081901729) * (a[0] * b[4]);
-    P[11] += T(0.23359668032760758) * (a[1] * b[1]);
-    P[11] += T(-0.058399170081901861) * (a[2] * b[0]);
-    P[12] += T(-0.1430481681026689) * (a[0] * b[1]);
-    P[12] += T(0.24776669508347599) * (a[1] * b[2]);
-    P[12] += T(-0.1430481681026689) * (a[2] * b[3]);
-    P[13] += T(-0.058399170081901861) * (a[0] * b[0]);
-    P[13] += T(0.23359668032760758) * (a[1] * b[3]);
-    P[13] += T(0.20230065940342065) * (a[2] * b[2]);
-    P[13] += T(-0.058399170081901729) * (a[2] * b[4]);
-    P[14] += T(-0.18467439092237189) * (a[0] * b[1]);
-    P[14] += T(0.18467439092237187) * (a[1] * b[4]);
-    P[14] += T(0.18467439092237189) * (a[2] * b[3]);
-    P[15] += T(-0.22617901315954039) * (a[0] * b[0]);
-    P[15] += T(0.22617901315954023) * (a[2] * b[4]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(-0.12615662610100806) * Pb[1]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(-0.2185096861184159) * Pb[1]; ga[0] += t * b[4]; gb[4] += t * a[0]; }
-    { const T t = T(0.21850968611841587) * Pb[1]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(0.21850968611841587) * Pb[1]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(0.21850968611841587) * Pb[2]; ga[0] += t * b[1]; gb[1] += t * a[0]; }
-    { const T t = T(0.252313252202016) * Pb[2]; ga[1] += t * b[2]; gb[2] += t * a[1]; }
-    { const T t = T(0.21850968611841587) * Pb[2]; ga[2] += t * b[3]; gb[3] += t * a[2]; }
-    { const T t = T(0.21850968611841587) * Pb[3]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.21850968611841587) * Pb[3]; ga[1] += t * b[3]; gb[3] += t * a[1]; }
-    { const T t = T(-0.12615662610100806) * Pb[3]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(0.2185096861184159) * Pb[3]; ga[2] += t * b[4]; gb[4] += t * a[2]; }
-    { const T t = T(0.22617901315954023) * Pb[9]; ga[0] += t * b[4]; gb[4] += t * a[0]; }
-    { const T t = T(0.22617901315954039) * Pb[9]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(0.18467439092237189) * Pb[10]; ga[0] += t * b[3]; gb[3] += t * a[0]; }
-    { const T t = T(0.18467439092237187) * Pb[10]; ga[1] += t * b[0]; gb[0] += t * a[1]; }
-    { const T t = T(0.18467439092237189) * Pb[10]; ga[2] += t * b[1]; gb[1] += t * a[2]; }
-    { const T t = T(0.20230065940342065) * Pb[11]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(0.058399170081901729) * Pb[11]; ga[0] += t * b[4]; gb[4] += t * a[0]; }
-    { const T t = T(0.23359668032760758) * Pb[11]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(-0.058399170081901861) * Pb[11]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(-0.1430481681026689) * Pb[12]; ga[0] += t * b[1]; gb[1] += t * a[0]; }
-    { const T t = T(0.24776669508347599) * Pb[12]; ga[1] += t * b[2]; gb[2] += t * a[1]; }
-    { const T t = T(-0.1430481681026689) * Pb[12]; ga[2] += t * b[3]; gb[3] += t * a[2]; }
-    { const T t = T(-0.058399170081901861) * Pb[13]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.23359668032760758) * Pb[13]; ga[1] += t * b[3]; gb[3] += t * a[1]; }
-    { const T t = T(0.20230065940342065) * Pb[13]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(-0.058399170081901729) * Pb[13]; ga[2] += t * b[4]; gb[4] += t * a[2]; }
-    { const T t = T(-0.18467439092237189) * Pb[14]; ga[0] += t * b[1]; gb[1] += t * a[0]; }
-    { const T t = T(0.18467439092237187) * Pb[14]; ga[1] += t * b[4]; gb[4] += t * a[1]; }
-    { const T t = T(0.18467439092237189) * Pb[14]; ga[2] += t * b[3]; gb[3] += t * a[2]; }
-    { const T t = T(-0.22617901315954039) * Pb[15]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.22617901315954023) * Pb[15]; ga[2] += t * b[4]; gb[4] += t * a[2]; }
-  }
-};
-template <> struct Couple<4, 1, 3> {
-  static constexpr int kMask = 20;
-  static constexpr int kTerms = 52;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[4] += T(-0.058399170081901867) * (a[0] * b[4]);
-    P[4] += T(-0.22617901315954042) * (a[0] * b[6]);
-    P[4] += T(0.18467439092237187) * (a[1] * b[1]);
-    P[4] += T(0.22617901315954042) * (a[2] * b[0]);
-    P[4] += T(-0.058399170081901867) * (a[2] * b[2]);
-    P[5] += T(-0.1430481681026689) * (a[0] * b[3]);
-    P[5] += T(-0.18467439092237192) * (a[0] * b[5]);
-    P[5] += T(0.23359668032760761) * (a[1] * b[2]);
-    P[5] += T(0.18467439092237189) * (a[2] * b[1]);
-    P[6] += T(0.20230065940342068) * (a[0] * b[2]);
-    P[6] += T(0.24776669508347601) * (a[1] * b[3]);
-    P[6] += T(0.20230065940342068) * (a[2] * b[4]);
-    P[7] += T(0.18467439092237189) * (a[0] * b[1]);
-    P[7] += T(0.23359668032760761) * (a[1] * b[4]);
-    P[7] += T(-0.1430481681026689) * (a[2] * b[3]);
-    P[7] += T(0.18467439092237192) * (a[2] * b[5]);
-    P[8] += T(0.22617901315954025) * (a[0] * b[0]);
-    P[8] += T(0.058399170081901736) * (a[0] * b[2]);
-    P[8] += T(0.18467439092237187) * (a[1] * b[5]);
-    P[8] += T(-0.058399170081901736) * (a[2] * b[4]);
-    P[8] += T(0.22617901315954025) * (a[2] * b[6]);
-    P[16] += T(0.2303294329808902) * (a[0] * b[6]);
-    P[16] += T(0.2303294329808902) * (a[2] * b[0]);
-    P[17] += T(0.19947114020071624) * (a[0] * b[5]);
-    P[17] += T(0.16286750396763999) * (a[1] * b[0]);
-    P[17] += T(0.19947114020071635) * (a[2] * b[1]);
-    P[18] += T(0.16858388283618392) * (a[0] * b[4]);
-    P[18] += T(0.043528171377568134) * (a[0] * b[6]);
-    P[18] += T(0.21324361862292318) * (a[1] * b[1]);
-    P[18] += T(-0.043528171377568134) * (a[2] * b[0]);
-    P[18] += T(0.16858388283618392) * (a[2] * b[2]);
-    P[19] += T(0.19466390027300595) * (a[0] * b[3]);
-    P[19] += T(0.075393004386513349) * (a[0] * b[5]);
-    P[19] += T(0.23841361350444787) * (a[1] * b[2]);
-    P[19] += T(-0.075393004386513446) * (a[2] * b[1]);
-    P[20] += T(-0.150786008773027) * (a[0] * b[2]);
-    P[20] += T(0.24623252122982925) * (a[1] * b[3]);
-    P[20] += T(-0.150786008773027) * (a[2] * b[4]);
-    P[21] += T(-0.075393004386513446) * (a[0] * b[1]);
-    P[21] += T(0.23841361350444781) * (a[1] * b[4]);
-    P[21] += T(0.19466390027300595) * (a[2] * b[3]);
-    P[21] += T(-0.075393004386513335) * (a[2] * b[5]);
-    P[22] += T(-0.043528171377568189) * (a[0] * b[0]);
-    P[22] += T(-0.16858388283618395) * (a[0] * b[2]);
-    P[22] += T(0.21324361862292318) * (a[1] * b[5]);
-    P[22] += T(0.16858388283618395) * (a[2] * b[4]);
-    P[22] += T(-0.043528171377568182) * (a[2] * b[6]);
-    P[23] += T(-0.19947114020071635) * (a[0] * b[1]);
-    P[23] += T(0.16286750396763999) * (a[1] * b[6]);
-    P[23] += T(0.19947114020071624) * (a[2] * b[5]);
-    P[24] += T(-0.23032943298089051) * (a[0] * b[0]);
-    P[24] += T(0.23032943298089054) * (a[2] * b[6]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(-0.058399170081901867) * Pb[4]; ga[0] += t * b[4]; gb[4] += t * a[0]; }
-    { const T t = T(-0.22617901315954042) * Pb[4]; ga[0] += t * b[6]; gb[6] += t * a[0]; }
-    { const T t = T(0.18467439092237187) * Pb[4]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(0.22617901315954042) * Pb[4]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(-0.058399170081901867) * Pb[4]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(-0.1430481681026689) * Pb[5]; ga[0] += t * b[3]; gb[3] += t * a[0]; }
-    { const T t = T(-0.18467439092237192) * Pb[5]; ga[0] += t * b[5]; gb[5] += t * a[0]; }
-    { const T t = T(0.23359668032760761) * Pb[5]; ga[1] += t * b[2]; gb[2] += t * a[1]; }
-    { const T t = T(0.18467439092237189) * Pb[5]; ga[2] += t * b[1]; gb[1] += t * a[2]; }
-    { const T t = T(0.20230065940342068) * Pb[6]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(0.24776669508347601) * Pb[6]; ga[1] += t * b[3]; gb[3] += t * a[1]; }
-    { const T t = T(0.20230065940342068) * Pb[6]; ga[2] += t * b[4]; gb[4] += t * a[2]; }
-    { const T t = T(0.18467439092237189) * Pb[7]; ga[0] += t * b[1]; gb[1] += t * a[0]; }
-    { const T t = T(0.23359668032760761) * Pb[7]; ga[1] += t * b[4]; gb[4] += t * a[1]; }
-    { const T t = T(-0.1430481681026689) * Pb[7]; ga[2] += t * b[3]; gb[3] += t * a[2]; }
-    { const T t = T(0.18467439092237192) * Pb[7]; ga[2] += t * b[5]; gb[5] += t * a[2]; }
-    { const T t = T(0.22617901315954025) * Pb[8]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.058399170081901736) * Pb[8]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(0.18467439092237187) * Pb[8]; ga[1] += t * b[5]; gb[5] += t * a[1]; }
-    { const T t = T(-0.058399170081901736) * Pb[8]; ga[2] += t * b[4]; gb[4] += t * a[2]; }
-    { const T t = T(0.22617901315954025) * Pb[8]; ga[2] += t * b[6]; gb[6] += t * a[2]; }
-    { const T t = T(0.2303294329808902) * Pb[16]; ga[0] += t * b[6]; gb[6] += t * a[0]; }
-    { const T t = T(0.2303294329808902) * Pb[16]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(0.19947114020071624) * Pb[17]; ga[0] += t * b[5]; gb[5] += t * a[0]; }
-    { const T t = T(0.16286750396763999) * Pb[17]; ga[1] += t * b[0]; gb[0] += t * a[1]; }
-    { const T t = T(0.19947114020071635) * Pb[17]; ga[2] += t * b[1]; gb[1] += t * a[2]; }
-    { const T t = T(0.16858388283618392) * Pb[18]; ga[0] += t * b[4]; gb[4] += t * a[0]; }
-    { const T t = T(0.043528171377568134) * Pb[18]; ga[0] += t * b[6]; gb[6] += t * a[0]; }
-    { const T t = T(0.21324361862292318) * Pb[18]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(-0.043528171377568134) * Pb[18]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(0.16858388283618392) * Pb[18]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(0.19466390027300595) * Pb[19]; ga[0] += t * b[3]; gb[3] += t * a[0]; }
-    { const T t = T(0.075393004386513349) * Pb[19]; ga[0] += t * b[5]; gb[5] += t * a[0]; }
-    { const T t = T(0.23841361350444787) * Pb[19]; ga[1] += t * b[2]; gb[2] += t * a[1]; }
-    { const T t = T(-0.075393004386513446) * Pb[19]; ga[2] += t * b[1]; gb[1] += t * a[2]; }
-    { const T t = T(-0.150786008773027) * Pb[20]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(0.24623252122982925) * Pb[20]; ga[1] += t * b[3]; gb[3] += t * a[1]; }
-    { const T t = T(-0.150786008773027) * Pb[20]; ga[2] += t * b[4]; gb[4] += t * a[2]; }
-    { const T t = T(-0.075393004386513446) * Pb[21]; ga[0] += t * b[1]; gb[1] += t * a[0]; }
-    { const T t = T(0.23841361350444781) * Pb[21]; ga[1] += t * b[4]; gb[4] += t * a[1]; }
-    { const T t = T(0.19466390027300595) * Pb[21]; ga[2] += t * b[3]; gb[3] += t * a[2]; }
-    { const T t = T(-0.075393004386513335) * Pb[21]; ga[2] += t * b[5]; gb[5] += t * a[2]; }
-    { const T t = T(-0.043528171377568189) * Pb[22]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(-0.16858388283618395) * Pb[22]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(0.21324361862292318) * Pb[22]; ga[1] += t * b[5]; gb[5] += t * a[1]; }
-    { const T t = T(0.16858388283618395) * Pb[22]; ga[2] += t * b[4]; gb[4] += t * a[2]; }
-    { const T t = T(-0.043528171377568182) * Pb[22]; ga[2] += t * b[6]; gb[6] += t * a[2]; }
-    { const T t = T(-0.19947114020071635) * Pb[23]; ga[0] += t * b[1]; gb[1] += t * a[0]; }
-    { const T t = T(0.16286750396763999) * Pb[23]; ga[1] += t * b[6]; gb[6] += t * a[1]; }
-    { const T t = T(0.19947114020071624) * Pb[23]; ga[2] += t * b[5]; gb[5] += t * a[2]; }
-    { const T t = T(-0.23032943298089051) * Pb[24]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.23032943298089054) * Pb[24]; ga[2] += t * b[6]; gb[6] += t * a[2]; }
-  }
-};
-template <> struct Couple<4, 1, 4> {
-  static constexpr int kMask = 8;
-  static constexpr int kTerms = 31;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[9] += T(-0.043528171377568169) * (a[0] * b[6]);
-    P[9] += T(-0.23032943298089051) * (a[0] * b[8]);
-    P[9] += T(0.16286750396763999) * (a[1] * b[1]);
-    P[9] += T(0.2303294329808902) * (a[2] * b[0]);
-    P[9] += T(-0.043528171377568134) * (a[2] * b[2]);
-    P[10] += T(-0.075393004386513446) * (a[0] * b[5]);
-    P[10] += T(-0.19947114020071635) * (a[0] * b[7]);
-    P[10] += T(0.21324361862292318) * (a[1] * b[2]);
-    P[10] += T(0.19947114020071635) * (a[2] * b[1]);
-    P[10] += T(-0.075393004386513446) * (a[2] * b[3]);
-    P[11] += T(-0.150786008773027) * (a[0] * b[4]);
-    P[11] += T(-0.16858388283618395) * (a[0] * b[6]);
-    P[11] += T(0.23841361350444787) * (a[1] * b[3]);
-    P[11] += T(0.16858388283618392) * (a[2] * b[2]);
-    P[12] += T(0.19466390027300595) * (a[0] * b[3]);
-    P[12] += T(0.24623252122982925) * (a[1] * b[4]);
-    P[12] += T(0.19466390027300595) * (a[2] * b[5]);
-    P[13] += T(0.16858388283618392) * (a[0] * b[2]);
-    P[13] += T(0.23841361350444781) * (a[1] * b[5]);
-    P[13] += T(-0.150786008773027) * (a[2] * b[4]);
-    P[13] += T(0.16858388283618397) * (a[2] * b[6]);
-    P[14] += T(0.19947114020071624) * (a[0] * b[1]);
-    P[14] += T(0.075393004386513349) * (a[0] * b[3]);
-    P[14] += T(0.21324361862292313) * (a[1] * b[6]);
-    P[14] += T(-0.075393004386513335) * (a[2] * b[5]);
-    P[14] += T(0.19947114020071624) * (a[2] * b[7]);
-    P[15] += T(0.2303294329808902) * (a[0] * b[0]);
-    P[15] += T(0.043528171377568155) * (a[0] * b[2]);
-    P[15] += T(0.16286750396763999) * (a[1] * b[7]);
-    P[15] += T(-0.043528171377568182) * (a[2] * b[6]);
-    P[15] += T(0.23032943298089054) * (a[2] * b[8]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(-0.043528171377568169) * Pb[9]; ga[0] += t * b[6]; gb[6] += t * a[0]; }
-    { const T t = T(-0.23032943298089051) * Pb[9]; ga[0] += t * b[8]; gb[8] += t * a[0]; }
-    { const T t = T(0.16286750396763999) * Pb[9]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(0.2303294329808902) * Pb[9]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(-0.043528171377568134) * Pb[9]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(-0.075393004386513446) * Pb[10]; ga[0] += t * b[5]; gb[5] += t * a[0]; }
-    { const T t = T(-0.19947114020071635) * Pb[10]; ga[0] += t * b[7]; gb[7] += t * a[0]; }
-    { const T t = T(0.21324361862292318) * Pb[10]; ga[1] += t * b[2]; gb[2] += t * a[1]; }
-    { const T t = T(0.19947114020071635) * Pb[10]; ga[2] += t * b[1]; gb[1] += t * a[2]; }
-    { const T t = T(-0.075393004386513446) * Pb[10]; ga[2] += t * b[3]; gb[3] += t * a[2]; }
-    { const T t = T(-0.150786008773027) * Pb[11]; ga[0] += t * b[4]; gb[4] += t * a[0]; }
-    { const T t = T(-0.16858388283618395) * Pb[11]; ga[0] += t * b[6]; gb[6] += t * a[0]; }
-    { const T t = T(0.23841361350444787) * Pb[11]; ga[1] += t * b[3]; gb[3] += t * a[1]; }
-    { const T t = T(0.16858388283618392) * Pb[11]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(0.19466390027300595) * Pb[12]; ga[0] += t * b[3]; gb[3] += t * a[0]; }
-    { const T t = T(0.24623252122982925) * Pb[12]; ga[1] += t * b[4]; gb[4] += t * a[1]; }
-    { const T t = T(0.19466390027300595) * Pb[12]; ga[2] += t * b[5]; gb[5] += t * a[2]; }
-    { const T t = T(0.16858388283618392) * Pb[13]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(0.23841361350444781) * Pb[13]; ga[1] += t * b[5]; gb[5] += t * a[1]; }
-    { const T t = T(-0.150786008773027) * Pb[13]; ga[2] += t * b[4]; gb[4] += t * a[2]; }
-    { const T t = T(0.16858388283618397) * Pb[13]; ga[2] += t * b[6]; gb[6] += t * a[2]; }
-    { const T t = T(0.19947114020071624) * Pb[14]; ga[0] += t * b[1]; gb[1] += t * a[0]; }
-    { const T t = T(0.075393004386513349) * Pb[14]; ga[0] += t * b[3]; gb[3] += t * a[0]; }
-    { const T t = T(0.21324361862292313) * Pb[14]; ga[1] += t * b[6]; gb[6] += t * a[1]; }
-    { const T t = T(-0.075393004386513335) * Pb[14]; ga[2] += t * b[5]; gb[5] += t * a[2]; }
-    { const T t = T(0.19947114020071624) * Pb[14]; ga[2] += t * b[7]; gb[7] += t * a[2]; }
-    { const T t = T(0.2303294329808902) * Pb[15]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.043528171377568155) * Pb[15]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(0.16286750396763999) * Pb[15]; ga[1] += t * b[7]; gb[7] += t * a[1]; }
-    { const T t = T(-0.043528171377568182) * Pb[15]; ga[2] += t * b[6]; gb[6] += t * a[2]; }
-    { const T t = T(0.23032943298089054) * Pb[15]; ga[2] += t * b[8]; gb[8] += t * a[2]; }
-  }
-};
-template <> struct Couple<4, 2, 0> {
-  static constexpr int kMask = 4;
-  static constexpr int kTerms = 5;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[4] += T(0.2820947917738782) * (a[0] * b[0]);
-    P[5] += T(0.28209479177387831) * (a[1] * b[0]);
-    P[6] += T(0.28209479177387831) * (a[2] * b[0]);
-    P[7] += T(0.28209479177387831) * (a[3] * b[0]);
-    P[8] += T(0.28209479177387831) * (a[4] * b[0]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(0.2820947917738782) * Pb[4]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.28209479177387831) * Pb[5]; ga[1] += t * b[0]; gb[0] += t * a[1]; }
-    { const T t = T(0.28209479177387831) * Pb[6]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(0.28209479177387831) * Pb[7]; ga[3] += t * b[0]; gb[0] += t * a[3]; }
-    { const T t = T(0.28209479177387831) * Pb[8]; ga[4] += t * b[0]; gb[0] += t * a[4]; }
-  }
-};
-template <> struct Couple<4, 2, 1> {
-  static constexpr int kMask = 10;
-  static constexpr int kTerms = 32;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[1] += T(0.21850968611841587) * (a[0] * b[2]);
-    P[1] += T(0.21850968611841587) * (a[1] * b[1]);
-    P[1] += T(-0.12615662610100806) * (a[2] * b[0]);
-    P[1] += T(-0.2185096861184159) * (a[4] * b[0]);
-    P[2] += T(0.21850968611841587) * (a[1] * b[0]);
-    P[2] += T(0.252313252202016) * (a[2] * b[1]);
-    P[2] += T(0.21850968611841587) * (a[3] * b[2]);
-    P[3] += T(0.21850968611841587) * (a[0] * b[0]);
-    P[3] += T(-0.12615662610100806) * (a[2] * b[2]);
-    P[3] += T(0.21850968611841587) * (a[3] * b[1]);
-    P[3] += T(0.2185096861184159) * (a[4] * b[2]);
-    P[9] += T(0.22617901315954039) * (a[0] * b[2]);
-    P[9] += T(0.22617901315954023) * (a[4] * b[0]);
-    P[10] += T(0.18467439092237187) * (a[0] * b[1]);
-    P[10] += T(0.18467439092237189) * (a[1] * b[2]);
-    P[10] += T(0.18467439092237189) * (a[3] * b[0]);
-    P[11] += T(-0.058399170081901861) * (a[0] * b[2]);
-    P[11] += T(0.23359668032760758) * (a[1] * b[1]);
-    P[11] += T(0.20230065940342065) * (a[2] * b[0]);
-    P[11] += T(0.058399170081901729) * (a[4] * b[0]);
-    P[12] += T(-0.1430481681026689) * (a[1] * b[0]);
-    P[12] += T(0.24776669508347599) * (a[2] * b[1]);
-    P[12] += T(-0.1430481681026689) * (a[3] * b[2]);
-    P[13] += T(-0.058399170081901861) * (a[0] * b[0]);
-    P[13] += T(0.20230065940342065) * (a[2] * b[2]);
-    P[13] += T(0.23359668032760758) * (a[3] * b[1]);
-    P[13] += T(-0.058399170081901729) * (a[4] * b[2]);
-    P[14] += T(-0.18467439092237189) * (a[1] * b[0]);
-    P[14] += T(0.18467439092237189) * (a[3] * b[2]);
-    P[14] += T(0.18467439092237187) * (a[4] * b[1]);
-    P[15] += T(-0.22617901315954039) * (a[0] * b[0]);
-    P[15] += T(0.22617901315954023) * (a[4] * b[2]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(0.21850968611841587) * Pb[1]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(0.21850968611841587) * Pb[1]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(-0.12615662610100806) * Pb[1]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(-0.2185096861184159) * Pb[1]; ga[4] += t * b[0]; gb[0] += t * a[4]; }
-    { const T t = T(0.21850968611841587) * Pb[2]; ga[1] += t * b[0]; gb[0] += t * a[1]; }
-    { const T t = T(0.252313252202016) * Pb[2]; ga[2] += t * b[1]; gb[1] += t * a[2]; }
-    { const T t = T(0.21850968611841587) * Pb[2]; ga[3] += t * b[2]; gb[2] += t * a[3]; }
-    { const T t = T(0.21850968611841587) * Pb[3]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(-0.12615662610100806) * Pb[3]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(0.21850968611841587) * Pb[3]; ga[3] += t * b[1]; gb[1] += t * a[3]; }
-    { const T t = T(0.2185096861184159) * Pb[3]; ga[4] += t * b[2]; gb[2] += t * a[4]; }
-    { const T t = T(0.22617901315954039) * Pb[9]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(0.22617901315954023) * Pb[9]; ga[4] += t * b[0]; gb[0] += t * a[4]; }
-    { const T t = T(0.18467439092237187) * Pb[10]; ga[0] += t * b[1]; gb[1] += t * a[0]; }
-    { const T t = T(0.18467439092237189) * Pb[10]; ga[1] += t * b[2]; gb[2] += t * a[1]; }
-    { const T t = T(0.18467439092237189) * Pb[10]; ga[3] += t * b[0]; gb[0] += t * a[3]; }
-    { const T t = T(-0.058399170081901861) * Pb[11]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(0.23359668032760758) * Pb[11]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(0.20230065940342065) * Pb[11]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(0.058399170081901729) * Pb[11]; ga[4] += t * b[0]; gb[0] += t * a[4]; }
-    { const T t = T(-0.1430481681026689) * Pb[12]; ga[1] += t * b[0]; gb[0] += t * a[1]; }
-    { const T t = T(0.24776669508347599) * Pb[12]; ga[2] += t * b[1]; gb[1] += t * a[2]; }
-    { const T t = T(-0.1430481681026689) * Pb[12]; ga[3] += t * b[2]; gb[2] += t * a[3]; }
-    { const T t = T(-0.058399170081901861) * Pb[13]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.20230065940342065) * Pb[13]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(0.23359668032760758) * Pb[13]; ga[3] += t * b[1]; gb[1] += t * a[3]; }
-    { const T t = T(-0.058399170081901729) * Pb[13]; ga[4] += t * b[2]; gb[2] += t * a[4]; }
-    { const T t = T(-0.18467439092237189) * Pb[14]; ga[1] += t * b[0]; gb[0] += t * a[1]; }
-    { const T t = T(0.18467439092237189) * Pb[14]; ga[3] += t * b[2]; gb[2] += t * a[3]; }
-    { const T t = T(0.18467439092237187) * Pb[14]; ga[4] += t * b[1]; gb[1] += t * a[4]; }
-    { const T t = T(-0.22617901315954039) * Pb[15]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.22617901315954023) * Pb[15]; ga[4] += t * b[2]; gb[2] += t * a[4]; }
-  }
-};
-template <> struct Couple<4, 2, 2> {
-  static constexpr int kMask = 21;
-  static constexpr int kTerms = 67;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[0] += T(0.2820947917738782) * (a[0] * b[0]);
-    P[0] += T(0.28209479177387831) * (a[1] * b[1]);
-    P[0] += T(0.28209479177387831) * (a[2] * b[2]);
-    P[0] += T(0.28209479177387831) * (a[3] * b[3]);
-    P[0] += T(0.28209479177387831) * (a[4] * b[4]);
-    P[4] += T(-0.18022375157286874) * (a[0] * b[2]);
-    P[4] += T(0.15607834722743999) * (a[1] * b[3]);
-    P[4] += T(-0.18022375157286874) * (a[2] * b[0]);
-    P[4] += T(0.15607834722743999) * (a[3] * b[1]);
-    P[5] += T(0.15607834722743999) * (a[0] * b[3]);
-    P[5] += T(0.090111875786434384) * (a[1] * b[2]);
-    P[5] += T(-0.15607834722744002) * (a[1] * b[4]);
-    P[5] += T(0.090111875786434384) * (a[2] * b[1]);
-    P[5] += T(0.15607834722743999) * (a[3] * b[0]);
-    P[5] += T(-0.15607834722744002) * (a[4] * b[1]);
-    P[6] += T(-0.18022375157286874) * (a[0] * b[0]);
-    P[6] += T(0.090111875786434384) * (a[1] * b[1]);
-    P[6] += T(0.18022375157286855) * (a[2] * b[2]);
-    P[6] += T(0.090111875786434384) * (a[3] * b[3]);
-    P[6] += T(-0.18022375157286849) * (a[4] * b[4]);
-    P[7] += T(0.15607834722743999) * (a[0] * b[1]);
-    P[7] += T(0.15607834722743999) * (a[1] * b[0]);
-    P[7] += T(0.090111875786434384) * (a[2] * b[3]);
-    P[7] += T(0.090111875786434384) * (a[3] * b[2]);
-    P[7] += T(0.15607834722744002) * (a[3] * b[4]);
-    P[7] += T(0.15607834722744002) * (a[4] * b[3]);
-    P[8] += T(-0.15607834722744002) * (a[1] * b[1]);
-    P[8] += T(-0.18022375157286849) * (a[2] * b[4]);
-    P[8] += T(0.15607834722744002) * (a[3] * b[3]);
-    P[8] += T(-0.18022375157286849) * (a[4] * b[2]);
-    P[16] += T(0.23841361350444781) * (a[0] * b[4]);
-    P[16] += T(0.23841361350444781) * (a[4] * b[0]);
-    P[17] += T(0.16858388283618392) * (a[0] * b[3]);
-    P[17] += T(0.16858388283618383) * (a[1] * b[4]);
-    P[17] += T(0.16858388283618392) * (a[3] * b[0]);
-    P[17] += T(0.16858388283618383) * (a[4] * b[1]);
-    P[18] += T(0.15607834722743993) * (a[0] * b[2]);
-    P[18] += T(0.18022375157286868) * (a[1] * b[3]);
-    P[18] += T(0.15607834722743993) * (a[2] * b[0]);
-    P[18] += T(0.18022375157286868) * (a[3] * b[1]);
-    P[19] += T(-0.063718718434027544) * (a[0] * b[3]);
-    P[19] += T(0.22072811544182241) * (a[1] * b[2]);
-    P[19] += T(0.063718718434027433) * (a[1] * b[4]);
-    P[19] += T(0.22072811544182241) * (a[2] * b[1]);
-    P[19] += T(-0.063718718434027544) * (a[3] * b[0]);
-    P[19] += T(0.063718718434027433) * (a[4] * b[1]);
-    P[20] += T(0.040299255967696845) * (a[0] * b[0]);
-    P[20] += T(-0.16119702387078788) * (a[1] * b[1]);
-    P[20] += T(0.24179553580618143) * (a[2] * b[2]);
-    P[20] += T(-0.16119702387078788) * (a[3] * b[3]);
-    P[20] += T(0.040299255967696873) * (a[4] * b[4]);
-    P[21] += T(-0.063718718434027544) * (a[0] * b[1]);
-    P[21] += T(-0.063718718434027544) * (a[1] * b[0]);
-    P[21] += T(0.22072811544182241) * (a[2] * b[3]);
-    P[21] += T(0.22072811544182241) * (a[3] * b[2]);
-    P[21] += T(-0.063718718434027433) * (a[3] * b[4]);
-    P[21] += T(-0.063718718434027433) * (a[4] * b[3]);
-    P[22] += T(-0.18022375157286877) * (a[1] * b[1]);
-    P[22] += T(0.15607834722743996) * (a[2] * b[4]);
-    P[22] += T(0.18022375157286874) * (a[3] * b[3]);
-    P[22] += T(0.15607834722743996) * (a[4] * b[2]);
-    P[23] += T(-0.16858388283618392) * (a[0] * b[1]);
-    P[23] += T(-0.16858388283618392) * (a[1] * b[0]);
-    P[23] += T(0.16858388283618383) * (a[3] * b[4]);
-    P[23] += T(0.16858388283618383) * (a[4] * b[3]);
-    P[24] += T(-0.23841361350444834) * (a[0] * b[0]);
-    P[24] += T(0.23841361350444815) * (a[4] * b[4]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(0.2820947917738782) * Pb[0]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.28209479177387831) * Pb[0]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(0.28209479177387831) * Pb[0]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(0.28209479177387831) * Pb[0]; ga[3] += t * b[3]; gb[3] += t * a[3]; }
-    { const T t = T(0.28209479177387831) * Pb[0]; ga[4] += t * b[4]; gb[4] += t * a[4]; }
-    { const T t = T(-0.18022375157286874) * Pb[4]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(0.15607834722743999) * Pb[4]; ga[1] += t * b[3]; gb[3] += t * a[1]; }
-    { const T t = T(-0.18022375157286874) * Pb[4]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(0.15607834722743999) * Pb[4]; ga[3] += t * b[1]; gb[1] += t * a[3]; }
-    { const T t = T(0.15607834722743999) * Pb[5]; ga[0] += t * b[3]; gb[3] += t * a[0]; }
-    { const T t = T(0.090111875786434384) * Pb[5]; ga[1] += t * b[2]; gb[2] += t * a[1]; }
-    { const T t = T(-0.15607834722744002) * Pb[5]; ga[1] += t * b[4]; gb[4] += t * a[1]; }
-    { const T t = T(0.090111875786434384) * Pb[5]; ga[2] += t * b[1]; gb[1] += t * a[2]; }
-    { const T t = T(0.15607834722743999) * Pb[5]; ga[3] += t * b[0]; gb[0] += t * a[3]; }
-    { const T t = T(-0.15607834722744002) * Pb[5]; ga[4] += t * b[1]; gb[1] += t * a[4]; }
-    { const T t = T(-0.18022375157286874) * Pb[6]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.090111875786434384) * Pb[6]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(0.18022375157286855) * Pb[6]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(0.090111875786434384) * Pb[6]; ga[3] += t * b[3]; gb[3] += t * a[3]; }
-    { const T t = T(-0.18022375157286849) * Pb[6]; ga[4] += t * b[4]; gb[4] += t * a[4]; }
-    { const T t = T(0.15607834722743999) * Pb[7]; ga[0] += t * b[1]; gb[1] += t * a[0]; }
-    { const T t = T(0.15607834722743999) * Pb[7]; ga[1] += t * b[0]; gb[0] += t * a[1]; }
-    { const T t = T(0.090111875786434384) * Pb[7]; ga[2] += t * b[3]; gb[3] += t * a[2]; }
-    { const T t = T(0.090111875786434384) * Pb[7]; ga[3] += t * b[2]; gb[2] += t * a[3]; }
-    { const T t = T(0.15607834722744002) * Pb[7]; ga[3] += t * b[4]; gb[4] += t * a[3]; }
-    { const T t = T(0.15607834722744002) * Pb[7]; ga[4] += t * b[3]; gb[3] += t * a[4]; }
-    { const T t = T(-0.15607834722744002) * Pb[8]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(-0.18022375157286849) * Pb[8]; ga[2] += t * b[4]; gb[4] += t * a[2]; }
-    { const T t = T(0.15607834722744002) * Pb[8]; ga[3] += t * b[3]; gb[3] += t * a[3]; }
-    { const T t = T(-0.18022375157286849) * Pb[8]; ga[4] += t * b[2]; gb[2] += t * a[4]; }
-    { const T t = T(0.23841361350444781) * Pb[16]; ga[0] += t * b[4]; gb[4] += t * a[0]; }
-    { const T t = T(0.23841361350444781) * Pb[16]; ga[4] += t * b[0]; gb[0] += t * a[4]; }
-    { const T t = T(0.16858388283618392) * Pb[17]; ga[0] += t * b[3]; gb[3] += t * a[0]; }
-    { const T t = T(0.16858388283618383) * Pb[17]; ga[1] += t * b[4]; gb[4] += t * a[1]; }
-    { const T t = T(0.16858388283618392) * Pb[17]; ga[3] += t * b[0]; gb[0] += t * a[3]; }
-    { const T t = T(0.16858388283618383) * Pb[17]; ga[4] += t * b[1]; gb[1] += t * a[4]; }
-    { const T t = T(0.15607834722743993) * Pb[18]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(0.18022375157286868) * Pb[18]; ga[1] += t * b[3]; gb[3] += t * a[1]; }
-    { const T t = T(0.15607834722743993) * Pb[18]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(0.18022375157286868) * Pb[18]; ga[3] += t * b[1]; gb[1] += t * a[3]; }
-    { const T t = T(-0.063718718434027544) * Pb[19]; ga[0] += t * b[3]; gb[3] += t * a[0]; }
-    { const T t = T(0.22072811544182241) * Pb[19]; ga[1] += t * b[2]; gb[2] += t * a[1]; }
-    { const T t = T(0.063718718434027433) * Pb[19]; ga[1] += t * b[4]; gb[4] += t * a[1]; }
-    { const T t = T(0.22072811544182241) * Pb[19]; ga[2] += t * b[1]; gb[1] += t * a[2]; }
-    { const T t = T(-0.063718718434027544) * Pb[19]; ga[3] += t * b[0]; gb[0] += t * a[3]; }
-    { const T t = T(0.063718718434027433) * Pb[19]; ga[4] += t * b[1]; gb[1] += t * a[4]; }
-    { const T t = T(0.040299255967696845) * Pb[20]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(-0.16119702387078788) * Pb[20]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(0.24179553580618143) * Pb[20]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(-0.16119702387078788) * Pb[20]; ga[3] += t * b[3]; gb[3] += t * a[3]; }
-    { const T t = T(0.040299255967696873) * Pb[20]; ga[4] += t * b[4]; gb[4] += t * a[4]; }
-    { const T t = T(-0.063718718434027544) * Pb[21]; ga[0] += t * b[1]; gb[1] += t * a[0]; }
-    { const T t = T(-0.063718718434027544) * Pb[21]; ga[1] += t * b[0]; gb[0] += t * a[1]; }
-    { const T t = T(0.22072811544182241) * Pb[21]; ga[2] += t * b[3]; gb[3] += t * a[2]; }
-    { const T t = T(0.22072811544182241) * Pb[21]; ga[3] += t * b[2]; gb[2] += t * a[3]; }
-    { const T t = T(-0.063718718434027433) * Pb[21]; ga[3] += t * b[4]; gb[4] += t * a[3]; }
-    { const T t = T(-0.063718718434027433) * Pb[21]; ga[4] += t * b[3]; gb[3] += t * a[4]; }
-    { const T t = T(-0.18022375157286877) * Pb[22]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(0.15607834722743996) * Pb[22]; ga[2] += t * b[4]; gb[4] += t * a[2]; }
-    { const T t = T(0.18022375157286874) * Pb[22]; ga[3] += t * b[3]; gb[3] += t * a[3]; }
-    { const T t = T(0.15607834722743996) * Pb[22]; ga[4] += t * b[2]; gb[2] += t * a[4]; }
-    { const T t = T(-0.16858388283618392) * Pb[23]; ga[0] += t * b[1]; gb[1] += t * a[0]; }
-    { const T t = T(-0.16858388283618392) * Pb[23]; ga[1] += t * b[0]; gb[0] += t * a[1]; }
-    { const T t = T(0.16858388283618383) * Pb[23]; ga[3] += t * b[4]; gb[4] += t * a[3]; }
-    { const T t = T(0.16858388283618383) * Pb[23]; ga[4] += t * b[3]; gb[3] += t * a[4]; }
-    { const T t = T(-0.23841361350444834) * Pb[24]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.23841361350444815) * Pb[24]; ga[4] += t * b[4]; gb[4] += t * a[4]; }
-  }
-};
-template <> struct Couple<4, 2, 3> {
-  static constexpr int kMask = 10;
-  static constexpr int kTerms = 62;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[1] += T(-0.058399170081901867) * (a[0] * b[4]);
-    P[1] += T(-0.22617901315954042) * (a[0] * b[6]);
-    P[1] += T(-0.1430481681026689) * (a[1] * b[3]);
-    P[1] += T(-0.18467439092237192) * (a[1] * b[5]);
-    P[1] += T(0.20230065940342068) * (a[2] * b[2]);
-    P[1] += T(0.18467439092237189) * (a[3] * b[1]);
-    P[1] += T(0.22617901315954025) * (a[4] * b[0]);
-    P[1] += T(0.058399170081901736) * (a[4] * b[2]);
-    P[2] += T(0.18467439092237187) * (a[0] * b[1]);
-    P[2] += T(0.23359668032760761) * (a[1] * b[2]);
-    P[2] += T(0.24776669508347601) * (a[2] * b[3]);
-    P[2] += T(0.23359668032760761) * (a[3] * b[4]);
-    P[2] += T(0.18467439092237187) * (a[4] * b[5]);
-    P[3] += T(0.22617901315954042) * (a[0] * b[0]);
-    P[3] += T(-0.058399170081901867) * (a[0] * b[2]);
-    P[3] += T(0.18467439092237189) * (a[1] * b[1]);
-    P[3] += T(0.20230065940342068) * (a[2] * b[4]);
-    P[3] += T(-0.1430481681026689) * (a[3] * b[3]);
-    P[3] += T(0.18467439092237192) * (a[3] * b[5]);
-    P[3] += T(-0.058399170081901736) * (a[4] * b[4]);
-    P[3] += T(0.22617901315954025) * (a[4] * b[6]);
-    P[9] += T(-0.094031597257959357) * (a[0] * b[4]);
-    P[9] += T(0.14867700967939756) * (a[1] * b[5]);
-    P[9] += T(-0.21026104350168001) * (a[2] * b[0]);
-    P[9] += T(0.14867700967939765) * (a[3] * b[1]);
-    P[9] += T(-0.094031597257959315) * (a[4] * b[2]);
-    P[10] += T(-0.1880631945159188) * (a[0] * b[3]);
-    P[10] += T(0.11516471649044524) * (a[1] * b[4]);
-    P[10] += T(-0.14867700967939765) * (a[1] * b[6]);
-    P[10] += T(0.14867700967939765) * (a[3] * b[0]);
-    P[10] += T(0.11516471649044524) * (a[3] * b[2]);
-    P[11] += T(0.14567312407894392) * (a[0] * b[4]);
-    P[11] += T(0.094031597257959329) * (a[0] * b[6]);
-    P[11] += T(0.059470803871758834) * (a[1] * b[3]);
-    P[11] += T(-0.1151647164904453) * (a[1] * b[5]);
-    P[11] += T(0.12615662610100786) * (a[2] * b[2]);
-    P[11] += T(0.11516471649044524) * (a[3] * b[1]);
-    P[11] += T(-0.094031597257959357) * (a[4] * b[0]);
-    P[11] += T(-0.14567312407894395) * (a[4] * b[2]);
-    P[12] += T(-0.1880631945159188) * (a[0] * b[1]);
-    P[12] += T(0.059470803871758834) * (a[1] * b[2]);
-    P[12] += T(0.16820883480134416) * (a[2] * b[3]);
-    P[12] += T(0.059470803871758827) * (a[3] * b[4]);
-    P[12] += T(-0.18806319451591863) * (a[4] * b[5]);
-    P[13] += T(-0.094031597257959315) * (a[0] * b[0]);
-    P[13] += T(0.14567312407894392) * (a[0] * b[2]);
-    P[13] += T(0.11516471649044524) * (a[1] * b[1]);
-    P[13] += T(0.12615662610100786) * (a[2] * b[4]);
-    P[13] += T(0.059470803871758827) * (a[3] * b[3]);
-    P[13] += T(0.11516471649044534) * (a[3] * b[5]);
-    P[13] += T(0.14567312407894398) * (a[4] * b[4]);
-    P[13] += T(-0.094031597257959357) * (a[4] * b[6]);
-    P[14] += T(0.14867700967939756) * (a[1] * b[0]);
-    P[14] += T(-0.1151647164904453) * (a[1] * b[2]);
-    P[14] += T(0.1151647164904453) * (a[3] * b[4]);
-    P[14] += T(0.14867700967939756) * (a[3] * b[6]);
-    P[14] += T(-0.18806319451591863) * (a[4] * b[3]);
-    P[15] += T(0.094031597257959357) * (a[0] * b[2]);
-    P[15] += T(-0.14867700967939765) * (a[1] * b[1]);
-    P[15] += T(-0.21026104350168001) * (a[2] * b[6]);
-    P[15] += T(0.14867700967939756) * (a[3] * b[5]);
-    P[15] += T(-0.094031597257959315) * (a[4] * b[4]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(-0.058399170081901867) * Pb[1]; ga[0] += t * b[4]; gb[4] += t * a[0]; }
-    { const T t = T(-0.22617901315954042) * Pb[1]; ga[0] += t * b[6]; gb[6] += t * a[0]; }
-    { const T t = T(-0.1430481681026689) * Pb[1]; ga[1] += t * b[3]; gb[3] += t * a[1]; }
-    { const T t = T(-0.18467439092237192) * Pb[1]; ga[1] += t * b[5]; gb[5] += t * a[1]; }
-    { const T t = T(0.20230065940342068) * Pb[1]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(0.18467439092237189) * Pb[1]; ga[3] += t * b[1]; gb[1] += t * a[3]; }
-    { const T t = T(0.22617901315954025) * Pb[1]; ga[4] += t * b[0]; gb[0] += t * a[4]; }
-    { const T t = T(0.058399170081901736) * Pb[1]; ga[4] += t * b[2]; gb[2] += t * a[4]; }
-    { const T t = T(0.18467439092237187) * Pb[2]; ga[0] += t * b[1]; gb[1] += t * a[0]; }
-    { const T t = T(0.23359668032760761) * Pb[2]; ga[1] += t * b[2]; gb[2] += t * a[1]; }
-    { const T t = T(0.24776669508347601) * Pb[2]; ga[2] += t * b[3]; gb[3] += t * a[2]; }
-    { const T t = T(0.23359668032760761) * Pb[2]; ga[3] += t * b[4]; gb[4] += t * a[3]; }
-    { const T t = T(0.18467439092237187) * Pb[2]; ga[4] += t * b[5]; gb[5] += t * a[4]; }
-    { const T t = T(0.22617901315954042) * Pb[3]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(-0.058399170081901867) * Pb[3]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(0.18467439092237189) * Pb[3]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(0.20230065940342068) * Pb[3]; ga[2] += t * b[4]; gb[4] += t * a[2]; }
-    { const T t = T(-0.1430481681026689) * Pb[3]; ga[3] += t * b[3]; gb[3] += t * a[3]; }
-    { const T t = T(0.18467439092237192) * Pb[3]; ga[3] += t * b[5]; gb[5] += t * a[3]; }
-    { const T t = T(-0.058399170081901736) * Pb[3]; ga[4] += t * b[4]; gb[4] += t * a[4]; }
-    { const T t = T(0.22617901315954025) * Pb[3]; ga[4] += t * b[6]; gb[6] += t * a[4]; }
-    { const T t = T(-0.094031597257959357) * Pb[9]; ga[0] += t * b[4]; gb[4] += t * a[0]; }
-    { const T t = T(0.14867700967939756) * Pb[9]; ga[1] += t * b[5]; gb[5] += t * a[1]; }
-    { const T t = T(-0.21026104350168001) * Pb[9]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(0.14867700967939765) * Pb[9]; ga[3] += t * b[1]; gb[1] += t * a[3]; }
-    { const T t = T(-0.094031597257959315) * Pb[9]; ga[4] += t * b[2]; gb[2] += t * a[4]; }
-    { const T t = T(-0.1880631945159188) * Pb[10]; ga[0] += t * b[3]; gb[3] += t * a[0]; }
-    { const T t = T(0.11516471649044524) * Pb[10]; ga[1] += t * b[4]; gb[4] += t * a[1]; }
-    { const T t = T(-0.14867700967939765) * Pb[10]; ga[1] += t * b[6]; gb[6] += t * a[1]; }
-    { const T t = T(0.14867700967939765) * Pb[10]; ga[3] += t * b[0]; gb[0] += t * a[3]; }
-    { const T t = T(0.11516471649044524) * Pb[10]; ga[3] += t * b[2]; gb[2] += t * a[3]; }
-    { const T t = T(0.14567312407894392) * Pb[11]; ga[0] += t * b[4]; gb[4] += t * a[0]; }
-    { const T t = T(0.094031597257959329) * Pb[11]; ga[0] += t * b[6]; gb[6] += t * a[0]; }
-    { const T t = T(0.059470803871758834) * Pb[11]; ga[1] += t * b[3]; gb[3] += t * a[1]; }
-    { const T t = T(-0.1151647164904453) * Pb[11]; ga[1] += t * b[5]; gb[5] += t * a[1]; }
-    { const T t = T(0.12615662610100786) * Pb[11]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(0.11516471649044524) * Pb[11]; ga[3] += t * b[1]; gb[1] += t * a[3]; }
-    { const T t = T(-0.094031597257959357) * Pb[11]; ga[4] += t * b[0]; gb[0] += t * a[4]; }
-    { const T t = T(-0.14567312407894395) * Pb[11]; ga[4] += t * b[2]; gb[2] += t * a[4]; }
-    { const T t = T(-0.1880631945159188) * Pb[12]; ga[0] += t * b[1]; gb[1] += t * a[0]; }
-    { const T t = T(0.059470803871758834) * Pb[12]; ga[1] += t * b[2]; gb[2] += t * a[1]; }
-    { const T t = T(0.16820883480134416) * Pb[12]; ga[2] += t * b[3]; gb[3] += t * a[2]; }
-    { const T t = T(0.059470803871758827) * Pb[12]; ga[3] += t * b[4]; gb[4] += t * a[3]; }
-    { const T t = T(-0.18806319451591863) * Pb[12]; ga[4] += t * b[5]; gb[5] += t * a[4]; }
-    { const T t = T(-0.094031597257959315) * Pb[13]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.14567312407894392) * Pb[13]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(0.11516471649044524) * Pb[13]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(0.12615662610100786) * Pb[13]; ga[2] += t * b[4]; gb[4] += t * a[2]; }
-    { const T t = T(0.059470803871758827) * Pb[13]; ga[3] += t * b[3]; gb[3] += t * a[3]; }
-    { const T t = T(0.11516471649044534) * Pb[13]; ga[3] += t * b[5]; gb[5] += t * a[3]; }
-    { const T t = T(0.14567312407894398) * Pb[13]; ga[4] += t * b[4]; gb[4] += t * a[4]; }
-    { const T t = T(-0.094031597257959357) * Pb[13]; ga[4] += t * b[6]; gb[6] += t * a[4]; }
-    { const T t = T(0.14867700967939756) * Pb[14]; ga[1] += t * b[0]; gb[0] += t * a[1]; }
-    { const T t = T(-0.1151647164904453) * Pb[14]; ga[1] += t * b[2]; gb[2] += t * a[1]; }
-    { const T t = T(0.1151647164904453) * Pb[14]; ga[3] += t * b[4]; gb[4] += t * a[3]; }
-    { const T t = T(0.14867700967939756) * Pb[14]; ga[3] += t * b[6]; gb[6] += t * a[3]; }
-    { const T t = T(-0.18806319451591863) * Pb[14]; ga[4] += t * b[3]; gb[3] += t * a[4]; }
-    { const T t = T(0.094031597257959357) * Pb[15]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(-0.14867700967939765) * Pb[15]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(-0.21026104350168001) * Pb[15]; ga[2] += t * b[6]; gb[6] += t * a[2]; }
-    { const T t = T(0.14867700967939756) * Pb[15]; ga[3] += t * b[5]; gb[5] += t * a[3]; }
-    { const T t = T(-0.094031597257959315) * Pb[15]; ga[4] += t * b[4]; gb[4] += t * a[4]; }
-  }
-};
-template <> struct Couple<4, 2, 4> {
-  static constexpr int kMask = 20;
-  static constexpr int kTerms = 98;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[4] += T(0.040299255967696811) * (a[0] * b[4]);
-    P[4] += T(-0.23841361350444829) * (a[0] * b[8]);
-    P[4] += T(-0.063718718434027571) * (a[1] * b[5]);
-    P[4] += T(-0.16858388283618389) * (a[1] * b[7]);
-    P[4] += T(0.15607834722743988) * (a[2] * b[2]);
-    P[4] += T(0.16858388283618389) * (a[3] * b[1]);
-    P[4] += T(-0.063718718434027571) * (a[3] * b[3]);
-    P[4] += T(0.23841361350444776) * (a[4] * b[0]);
-    P[5] += T(-0.063718718434027558) * (a[0] * b[5]);
-    P[5] += T(-0.16858388283618389) * (a[0] * b[7]);
-    P[5] += T(-0.1611970238707878) * (a[1] * b[4]);
-    P[5] += T(-0.18022375157286874) * (a[1] * b[6]);
-    P[5] += T(0.22072811544182247) * (a[2] * b[3]);
-    P[5] += T(0.18022375157286866) * (a[3] * b[2]);
-    P[5] += T(0.16858388283618381) * (a[4] * b[1]);
-    P[5] += T(0.06371871843402746) * (a[4] * b[3]);
-    P[6] += T(0.15607834722743991) * (a[0] * b[2]);
-    P[6] += T(0.22072811544182239) * (a[1] * b[3]);
-    P[6] += T(0.24179553580618141) * (a[2] * b[4]);
-    P[6] += T(0.22072811544182239) * (a[3] * b[5]);
-    P[6] += T(0.15607834722743993) * (a[4] * b[6]);
-    P[7] += T(0.16858388283618389) * (a[0] * b[1]);
-    P[7] += T(-0.063718718434027558) * (a[0] * b[3]);
-    P[7] += T(0.18022375157286866) * (a[1] * b[2]);
-    P[7] += T(0.22072811544182241) * (a[2] * b[5]);
-    P[7] += T(-0.16119702387078777) * (a[3] * b[4]);
-    P[7] += T(0.18022375157286868) * (a[3] * b[6]);
-    P[7] += T(-0.06371871843402746) * (a[4] * b[5]);
-    P[7] += T(0.16858388283618381) * (a[4] * b[7]);
-    P[8] += T(0.23841361350444776) * (a[0] * b[0]);
-    P[8] += T(0.16858388283618381) * (a[1] * b[1]);
-    P[8] += T(0.063718718434027433) * (a[1] * b[3]);
-    P[8] += T(0.15607834722743988) * (a[2] * b[6]);
-    P[8] += T(-0.063718718434027447) * (a[3] * b[5]);
-    P[8] += T(0.16858388283618381) * (a[3] * b[7]);
-    P[8] += T(0.040299255967696929) * (a[4] * b[4]);
-    P[8] += T(0.23841361350444812) * (a[4] * b[8]);
-    P[16] += T(-0.075080816691962482) * (a[0] * b[6]);
-    P[16] += T(0.14046334619025069) * (a[1] * b[7]);
-    P[16] += T(-0.22937568382001464) * (a[2] * b[0]);
-    P[16] += T(0.14046334619025069) * (a[3] * b[1]);
-    P[16] += T(-0.075080816691962496) * (a[4] * b[2]);
-    P[17] += T(-0.11262122503794367) * (a[0] * b[5]);
-    P[17] += T(0.13272538654977695) * (a[1] * b[6]);
-    P[17] += T(-0.1404633461902508) * (a[1] * b[8]);
-    P[17] += T(-0.057343920955003555) * (a[2] * b[1]);
-    P[17] += T(0.14046334619025072) * (a[3] * b[0]);
-    P[17] += T(0.13272538654977706) * (a[3] * b[2]);
-    P[17] += T(-0.11262122503794365) * (a[4] * b[3]);
-    P[18] += T(-0.19036461502711174) * (a[0] * b[4]);
-    P[18] += T(0.075080816691962302) * (a[0] * b[8]);
-    P[18] += T(0.090297865408018235) * (a[1] * b[5]);
-    P[18] += T(-0.132725386549777) * (a[1] * b[7]);
-    P[18] += T(0.06553590966286113) * (a[2] * b[2]);
-    P[18] += T(0.132725386549777) * (a[3] * b[1]);
-    P[18] += T(0.090297865408018235) * (a[3] * b[3]);
-    P[18] += T(-0.075080816691962496) * (a[4] * b[0]);
-    P[19] += T(0.14188940657039981) * (a[0] * b[5]);
-    P[19] += T(0.11262122503794365) * (a[0] * b[7]);
-    P[19] += T(0.044869370061212506) * (a[1] * b[4]);
-    P[19] += T(-0.090297865408018402) * (a[1] * b[6]);
-    P[19] += T(0.13926380803358024) * (a[2] * b[3]);
-    P[19] += T(0.090297865408018194) * (a[3] * b[2]);
-    P[19] += T(-0.11262122503794361) * (a[4] * b[1]);
-    P[19] += T(-0.14188940657039986) * (a[4] * b[3]);
-    P[20] += T(-0.19036461502711174) * (a[0] * b[2]);
-    P[20] += T(0.044869370061212464) * (a[1] * b[3]);
-    P[20] += T(0.16383977415715348) * (a[2] * b[4]);
-    P[20] += T(0.044869370061212464) * (a[3] * b[5]);
-    P[20] += T(-0.1903646150271118) * (a[4] * b[6]);
-    P[21] += T(-0.11262122503794367) * (a[0] * b[1]);
-    P[21] += T(0.14188940657039981) * (a[0] * b[3]);
-    P[21] += T(0.090297865408018194) * (a[1] * b[2]);
-    P[21] += T(0.13926380803358016) * (a[2] * b[5]);
-    P[21] += T(0.044869370061212478) * (a[3] * b[4]);
-    P[21] += T(0.090297865408018402) * (a[3] * b[6]);
-    P[21] += T(0.14188940657039986) * (a[4] * b[5]);
-    P[21] += T(-0.11262122503794363) * (a[4] * b[7]);
-    P[22] += T(-0.075080816691962496) * (a[0] * b[0]);
-    P[22] += T(0.13272538654977695) * (a[1] * b[1]);
-    P[22] += T(-0.09029786540801843) * (a[1] * b[3]);
-    P[22] += T(0.065535909662861241) * (a[2] * b[6]);
-    P[22] += T(0.090297865408018416) * (a[3] * b[5]);
-    P[22] += T(0.13272538654977692) * (a[3] * b[7]);
-    P[22] += T(-0.1903646150271118) * (a[4] * b[4]);
-    P[22] += T(-0.075080816691962482) * (a[4] * b[8]);
-    P[23] += T(0.11262122503794368) * (a[0] * b[3]);
-    P[23] += T(0.14046334619025072) * (a[1] * b[0]);
-    P[23] += T(-0.13272538654977706) * (a[1] * b[2]);
-    P[23] += T(-0.057343920955003555) * (a[2] * b[7]);
-    P[23] += T(0.13272538654977692) * (a[3] * b[6]);
-    P[23] += T(0.1404633461902508) * (a[3] * b[8]);
-    P[23] += T(-0.11262122503794364) * (a[4] * b[5]);
-    P[24] += T(0.075080816691962357) * (a[0] * b[2]);
-    P[24] += T(-0.14046334619025078) * (a[1] * b[1]);
-    P[24] += T(-0.22937568382001453) * (a[2] * b[8]);
-    P[24] += T(0.14046334619025078) * (a[3] * b[7]);
-    P[24] += T(-0.075080816691962482) * (a[4] * b[6]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(0.040299255967696811) * Pb[4]; ga[0] += t * b[4]; gb[4] += t * a[0]; }
-    { const T t = T(-0.23841361350444829) * Pb[4]; ga[0] += t * b[8]; gb[8] += t * a[0]; }
-    { const T t = T(-0.063718718434027571) * Pb[4]; ga[1] += t * b[5]; gb[5] += t * a[1]; }
-    { const T t = T(-0.16858388283618389) * Pb[4]; ga[1] += t * b[7]; gb[7] += t * a[1]; }
-    { const T t = T(0.15607834722743988) * Pb[4]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(0.16858388283618389) * Pb[4]; ga[3] += t * b[1]; gb[1] += t * a[3]; }
-    { const T t = T(-0.063718718434027571) * Pb[4]; ga[3] += t * b[3]; gb[3] += t * a[3]; }
-    { const T t = T(0.23841361350444776) * Pb[4]; ga[4] += t * b[0]; gb[0] += t * a[4]; }
-    { const T t = T(-0.063718718434027558) * Pb[5]; ga[0] += t * b[5]; gb[5] += t * a[0]; }
-    { const T t = T(-0.16858388283618389) * Pb[5]; ga[0] += t * b[7]; gb[7] += t * a[0]; }
-    { const T t = T(-0.1611970238707878) * Pb[5]; ga[1] += t * b[4]; gb[4] += t * a[1]; }
-    { const T t = T(-0.18022375157286874) * Pb[5]; ga[1] += t * b[6]; gb[6] += t * a[1]; }
-    { const T t = T(0.22072811544182247) * Pb[5]; ga[2] += t * b[3]; gb[3] += t * a[2]; }
-    { const T t = T(0.18022375157286866) * Pb[5]; ga[3] += t * b[2]; gb[2] += t * a[3]; }
-    { const T t = T(0.16858388283618381) * Pb[5]; ga[4] += t * b[1]; gb[1] += t * a[4]; }
-    { const T t = T(0.06371871843402746) * Pb[5]; ga[4] += t * b[3]; gb[3] += t * a[4]; }
-    { const T t = T(0.15607834722743991) * Pb[6]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(0.22072811544182239) * Pb[6]; ga[1] += t * b[3]; gb[3] += t * a[1]; }
-    { const T t = T(0.24179553580618141) * Pb[6]; ga[2] += t * b[4]; gb[4] += t * a[2]; }
-    { const T t = T(0.22072811544182239) * Pb[6]; ga[3] += t * b[5]; gb[5] += t * a[3]; }
-    { const T t = T(0.15607834722743993) * Pb[6]; ga[4] += t * b[6]; gb[6] += t * a[4]; }
-    { const T t = T(0.16858388283618389) * Pb[7]; ga[0] += t * b[1]; gb[1] += t * a[0]; }
-    { const T t = T(-0.063718718434027558) * Pb[7]; ga[0] += t * b[3]; gb[3] += t * a[0]; }
-    { const T t = T(0.18022375157286866) * Pb[7]; ga[1] += t * b[2]; gb[2] += t * a[1]; }
-    { const T t = T(0.22072811544182241) * Pb[7]; ga[2] += t * b[5]; gb[5] += t * a[2]; }
-    { const T t = T(-0.16119702387078777) * Pb[7]; ga[3] += t * b[4]; gb[4] += t * a[3]; }
-    { const T t = T(0.18022375157286868) * Pb[7]; ga[3] += t * b[6]; gb[6] += t * a[3]; }
-    { const T t = T(-0.06371871843402746) * Pb[7]; ga[4] += t * b[5]; gb[5] += t * a[4]; }
-    { const T t = T(0.16858388283618381) * Pb[7]; ga[4] += t * b[7]; gb[7] += t * a[4]; }
-    { const T t = T(0.23841361350444776) * Pb[8]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.16858388283618381) * Pb[8]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(0.063718718434027433) * Pb[8]; ga[1] += t * b[3]; gb[3] += t * a[1]; }
-    { const T t = T(0.15607834722743988) * Pb[8]; ga[2] += t * b[6]; gb[6] += t * a[2]; }
-    { const T t = T(-0.063718718434027447) * Pb[8]; ga[3] += t * b[5]; gb[5] += t * a[3]; }
-    { const T t = T(0.16858388283618381) * Pb[8]; ga[3] += t * b[7]; gb[7] += t * a[3]; }
-    { const T t = T(0.040299255967696929) * Pb[8]; ga[4] += t * b[4]; gb[4] += t * a[4]; }
-    { const T t = T(0.23841361350444812) * Pb[8]; ga[4] += t * b[8]; gb[8] += t * a[4]; }
-    { const T t = T(-0.075080816691962482) * Pb[16]; ga[0] += t * b[6]; gb[6] += t * a[0]; }
-    { const T t = T(0.14046334619025069) * Pb[16]; ga[1] += t * b[7]; gb[7] += t * a[1]; }
-    { const T t = T(-0.22937568382001464) * Pb[16]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(0.14046334619025069) * Pb[16]; ga[3] += t * b[1]; gb[1] += t * a[3]; }
-    { const T t = T(-0.075080816691962496) * Pb[16]; ga[4] += t * b[2]; gb[2] += t * a[4]; }
-    { const T t = T(-0.11262122503794367) * Pb[17]; ga[0] += t * b[5]; gb[5] += t * a[0]; }
-    { const T t = T(0.13272538654977695) * Pb[17]; ga[1] += t * b[6]; gb[6] += t * a[1]; }
-    { const T t = T(-0.1404633461902508) * Pb[17]; ga[1] += t * b[8]; gb[8] += t * a[1]; }
-    { const T t = T(-0.057343920955003555) * Pb[17]; ga[2] += t * b[1]; gb[1] += t * a[2]; }
-    { const T t = T(0.14046334619025072) * Pb[17]; ga[3] += t * b[0]; gb[0] += t * a[3]; }
-    { const T t = T(0.13272538654977706) * Pb[17]; ga[3] += t * b[2]; gb[2] += t * a[3]; }
-    { const T t = T(-0.11262122503794365) * Pb[17]; ga[4] += t * b[3]; gb[3] += t * a[4]; }
-    { const T t = T(-0.19036461502711174) * Pb[18]; ga[0] += t * b[4]; gb[4] += t * a[0]; }
-    { const T t = T(0.075080816691962302) * Pb[18]; ga[0] += t * b[8]; gb[8] += t * a[0]; }
-    { const T t = T(0.090297865408018235) * Pb[18]; ga[1] += t * b[5]; gb[5] += t * a[1]; }
-    { const T t = T(-0.132725386549777) * Pb[18]; ga[1] += t * b[7]; gb[7] += t * a[1]; }
-    { const T t = T(0.06553590966286113) * Pb[18]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(0.132725386549777) * Pb[18]; ga[3] += t * b[1]; gb[1] += t * a[3]; }
-    { const T t = T(0.090297865408018235) * Pb[18]; ga[3] += t * b[3]; gb[3] += t * a[3]; }
-    { const T t = T(-0.075080816691962496) * Pb[18]; ga[4] += t * b[0]; gb[0] += t * a[4]; }
-    { const T t = T(0.14188940657039981) * Pb[19]; ga[0] += t * b[5]; gb[5] += t * a[0]; }
-    { const T t = T(0.11262122503794365) * Pb[19]; ga[0] += t * b[7]; gb[7] += t * a[0]; }
-    { const T t = T(0.044869370061212506) * Pb[19]; ga[1] += t * b[4]; gb[4] += t * a[1]; }
-    { const T t = T(-0.090297865408018402) * Pb[19]; ga[1] += t * b[6]; gb[6] += t * a[1]; }
-    { const T t = T(0.13926380803358024) * Pb[19]; ga[2] += t * b[3]; gb[3] += t * a[2]; }
-    { const T t = T(0.090297865408018194) * Pb[19]; ga[3] += t * b[2]; gb[2] += t * a[3]; }
-    { const T t = T(-0.11262122503794361) * Pb[19]; ga[4] += t * b[1]; gb[1] += t * a[4]; }
-    { const T t = T(-0.14188940657039986) * Pb[19]; ga[4] += t * b[3]; gb[3] += t * a[4]; }
-    { const T t = T(-0.19036461502711174) * Pb[20]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(0.044869370061212464) * Pb[20]; ga[1] += t * b[3]; gb[3] += t * a[1]; }
-    { const T t = T(0.16383977415715348) * Pb[20]; ga[2] += t * b[4]; gb[4] += t * a[2]; }
-    { const T t = T(0.044869370061212464) * Pb[20]; ga[3] += t * b[5]; gb[5] += t * a[3]; }
-    { const T t = T(-0.1903646150271118) * Pb[20]; ga[4] += t * b[6]; gb[6] += t * a[4]; }
-    { const T t = T(-0.11262122503794367) * Pb[21]; ga[0] += t * b[1]; gb[1] += t * a[0]; }
-    { const T t = T(0.14188940657039981) * Pb[21]; ga[0] += t * b[3]; gb[3] += t * a[0]; }
-    { const T t = T(0.090297865408018194) * Pb[21]; ga[1] += t * b[2]; gb[2] += t * a[1]; }
-    { const T t = T(0.13926380803358016) * Pb[21]; ga[2] += t * b[5]; gb[5] += t * a[2]; }
-    { const T t = T(0.044869370061212478) * Pb[21]; ga[3] += t * b[4]; gb[4] += t * a[3]; }
-    { const T t = T(0.090297865408018402) * Pb[21]; ga[3] += t * b[6]; gb[6] += t * a[3]; }
-    { const T t = T(0.14188940657039986) * Pb[21]; ga[4] += t * b[5]; gb[5] += t * a[4]; }
-    { const T t = T(-0.11262122503794363) * Pb[21]; ga[4] += t * b[7]; gb[7] += t * a[4]; }
-    { const T t = T(-0.075080816691962496) * Pb[22]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.13272538654977695) * Pb[22]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(-0.09029786540801843) * Pb[22]; ga[1] += t * b[3]; gb[3] += t * a[1]; }
-    { const T t = T(0.065535909662861241) * Pb[22]; ga[2] += t * b[6]; gb[6] += t * a[2]; }
-    { const T t = T(0.090297865408018416) * Pb[22]; ga[3] += t * b[5]; gb[5] += t * a[3]; }
-    { const T t = T(0.13272538654977692) * Pb[22]; ga[3] += t * b[7]; gb[7] += t * a[3]; }
-    { const T t = T(-0.1903646150271118) * Pb[22]; ga[4] += t * b[4]; gb[4] += t * a[4]; }
-    { const T t = T(-0.075080816691962482) * Pb[22]; ga[4] += t * b[8]; gb[8] += t * a[4]; }
-    { const T t = T(0.11262122503794368) * Pb[23]; ga[0] += t * b[3]; gb[3] += t * a[0]; }
-    { const T t = T(0.14046334619025072) * Pb[23]; ga[1] += t * b[0]; gb[0] += t * a[1]; }
-    { const T t = T(-0.13272538654977706) * Pb[23]; ga[1] += t * b[2]; gb[2] += t * a[1]; }
-    { const T t = T(-0.057343920955003555) * Pb[23]; ga[2] += t * b[7]; gb[7] += t * a[2]; }
-    { const T t = T(0.13272538654977692) * Pb[23]; ga[3] += t * b[6]; gb[6] += t * a[3]; }
-    { const T t = T(0.1404633461902508) * Pb[23]; ga[3] += t * b[8]; gb[8] += t * a[3]; }
-    { const T t = T(-0.11262122503794364) * Pb[23]; ga[4] += t * b[5]; gb[5] += t * a[4]; }
-    { const T t = T(0.075080816691962357) * Pb[24]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(-0.14046334619025078) * Pb[24]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(-0.22937568382001453) * Pb[24]; ga[2] += t * b[8]; gb[8] += t * a[2]; }
-    { const T t = T(0.14046334619025078) * Pb[24]; ga[3] += t * b[7]; gb[7] += t * a[3]; }
-    { const T t = T(-0.075080816691962482) * Pb[24]; ga[4] += t * b[6]; gb[6] += t * a[4]; }
-  }
-};
-template <> struct Couple<4, 3, 0> {
-  static constexpr int kMask = 8;
-  static constexpr int kTerms = 7;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[9] += T(0.2820947917738782) * (a[0] * b[0]);
-    P[10] += T(0.2820947917738782) * (a[1] * b[0]);
-    P[11] += T(0.28209479177387825) * (a[2] * b[0]);
-    P[12] += T(0.28209479177387814) * (a[3] * b[0]);
-    P[13] += T(0.28209479177387825) * (a[4] * b[0]);
-    P[14] += T(0.28209479177387825) * (a[5] * b[0]);
-    P[15] += T(0.2820947917738782) * (a[6] * b[0]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(0.2820947917738782) * Pb[9]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.2820947917738782) * Pb[10]; ga[1] += t * b[0]; gb[0] += t * a[1]; }
-    { const T t = T(0.28209479177387825) * Pb[11]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(0.28209479177387814) * Pb[12]; ga[3] += t * b[0]; gb[0] += t * a[3]; }
-    { const T t = T(0.28209479177387825) * Pb[13]; ga[4] += t * b[0]; gb[0] += t * a[4]; }
-    { const T t = T(0.28209479177387825) * Pb[14]; ga[5] += t * b[0]; gb[0] += t * a[5]; }
-    { const T t = T(0.2820947917738782) * Pb[15]; ga[6] += t * b[0]; gb[0] += t * a[6]; }
-  }
-};
-template <> struct Couple<4, 3, 1> {
-  static constexpr int kMask = 20;
-  static constexpr int kTerms = 52;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[4] += T(0.22617901315954042) * (a[0] * b[2]);
-    P[4] += T(0.18467439092237187) * (a[1] * b[1]);
-    P[4] += T(-0.058399170081901867) * (a[2] * b[2]);
-    P[4] += T(-0.058399170081901867) * (a[4] * b[0]);
-    P[4] += T(-0.22617901315954042) * (a[6] * b[0]);
-    P[5] += T(0.18467439092237189) * (a[1] * b[2]);
-    P[5] += T(0.23359668032760761) * (a[2] * b[1]);
-    P[5] += T(-0.1430481681026689) * (a[3] * b[0]);
-    P[5] += T(-0.18467439092237192) * (a[5] * b[0]);
-    P[6] += T(0.20230065940342068) * (a[2] * b[0]);
-    P[6] += T(0.24776669508347601) * (a[3] * b[1]);
-    P[6] += T(0.20230065940342068) * (a[4] * b[2]);
-    P[7] += T(0.18467439092237189) * (a[1] * b[0]);
-    P[7] += T(-0.1430481681026689) * (a[3] * b[2]);
-    P[7] += T(0.23359668032760761) * (a[4] * b[1]);
-    P[7] += T(0.18467439092237192) * (a[5] * b[2]);
-    P[8] += T(0.22617901315954025) * (a[0] * b[0]);
-    P[8] += T(0.058399170081901736) * (a[2] * b[0]);
-    P[8] += T(-0.058399170081901736) * (a[4] * b[2]);
-    P[8] += T(0.18467439092237187) * (a[5] * b[1]);
-    P[8] += T(0.22617901315954025) * (a[6] * b[2]);
-    P[16] += T(0.2303294329808902) * (a[0] * b[2]);
-    P[16] += T(0.2303294329808902) * (a[6] * b[0]);
-    P[17] += T(0.16286750396763999) * (a[0] * b[1]);
-    P[17] += T(0.19947114020071635) * (a[1] * b[2]);
-    P[17] += T(0.19947114020071624) * (a[5] * b[0]);
-    P[18] += T(-0.043528171377568134) * (a[0] * b[2]);
-    P[18] += T(0.21324361862292318) * (a[1] * b[1]);
-    P[18] += T(0.16858388283618392) * (a[2] * b[2]);
-    P[18] += T(0.16858388283618392) * (a[4] * b[0]);
-    P[18] += T(0.043528171377568134) * (a[6] * b[0]);
-    P[19] += T(-0.075393004386513446) * (a[1] * b[2]);
-    P[19] += T(0.23841361350444787) * (a[2] * b[1]);
-    P[19] += T(0.19466390027300595) * (a[3] * b[0]);
-    P[19] += T(0.075393004386513349) * (a[5] * b[0]);
-    P[20] += T(-0.150786008773027) * (a[2] * b[0]);
-    P[20] += T(0.24623252122982925) * (a[3] * b[1]);
-    P[20] += T(-0.150786008773027) * (a[4] * b[2]);
-    P[21] += T(-0.075393004386513446) * (a[1] * b[0]);
-    P[21] += T(0.19466390027300595) * (a[3] * b[2]);
-    P[21] += T(0.23841361350444781) * (a[4] * b[1]);
-    P[21] += T(-0.075393004386513335) * (a[5] * b[2]);
-    P[22] += T(-0.043528171377568189) * (a[0] * b[0]);
-    P[22] += T(-0.16858388283618395) * (a[2] * b[0]);
-    P[22] += T(0.16858388283618395) * (a[4] * b[2]);
-    P[22] += T(0.21324361862292318) * (a[5] * b[1]);
-    P[22] += T(-0.043528171377568182) * (a[6] * b[2]);
-    P[23] += T(-0.19947114020071635) * (a[1] * b[0]);
-    P[23] += T(0.19947114020071624) * (a[5] * b[2]);
-    P[23] += T(0.16286750396763999) * (a[6] * b[1]);
-    P[24] += T(-0.23032943298089051) * (a[0] * b[0]);
-    P[24] += T(0.23032943298089054) * (a[6] * b[2]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(0.22617901315954042) * Pb[4]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(0.18467439092237187) * Pb[4]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(-0.058399170081901867) * Pb[4]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(-0.058399170081901867) * Pb[4]; ga[4] += t * b[0]; gb[0] += t * a[4]; }
-    { const T t = T(-0.22617901315954042) * Pb[4]; ga[6] += t * b[0]; gb[0] += t * a[6]; }
-    { const T t = T(0.18467439092237189) * Pb[5]; ga[1] += t * b[2]; gb[2] += t * a[1]; }
-    { const T t = T(0.23359668032760761) * Pb[5]; ga[2] += t * b[1]; gb[1] += t * a[2]; }
-    { const T t = T(-0.1430481681026689) * Pb[5]; ga[3] += t * b[0]; gb[0] += t * a[3]; }
-    { const T t = T(-0.18467439092237192) * Pb[5]; ga[5] += t * b[0]; gb[0] += t * a[5]; }
-    { const T t = T(0.20230065940342068) * Pb[6]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(0.24776669508347601) * Pb[6]; ga[3] += t * b[1]; gb[1] += t * a[3]; }
-    { const T t = T(0.20230065940342068) * Pb[6]; ga[4] += t * b[2]; gb[2] += t * a[4]; }
-    { const T t = T(0.18467439092237189) * Pb[7]; ga[1] += t * b[0]; gb[0] += t * a[1]; }
-    { const T t = T(-0.1430481681026689) * Pb[7]; ga[3] += t * b[2]; gb[2] += t * a[3]; }
-    { const T t = T(0.23359668032760761) * Pb[7]; ga[4] += t * b[1]; gb[1] += t * a[4]; }
-    { const T t = T(0.18467439092237192) * Pb[7]; ga[5] += t * b[2]; gb[2] += t * a[5]; }
-    { const T t = T(0.22617901315954025) * Pb[8]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.058399170081901736) * Pb[8]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(-0.058399170081901736) * Pb[8]; ga[4] += t * b[2]; gb[2] += t * a[4]; }
-    { const T t = T(0.18467439092237187) * Pb[8]; ga[5] += t * b[1]; gb[1] += t * a[5]; }
-    { const T t = T(0.22617901315954025) * Pb[8]; ga[6] += t * b[2]; gb[2] += t * a[6]; }
-    { const T t = T(0.2303294329808902) * Pb[16]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(0.2303294329808902) * Pb[16]; ga[6] += t * b[0]; gb[0] += t * a[6]; }
-    { const T t = T(0.16286750396763999) * Pb[17]; ga[0] += t * b[1]; gb[1] += t * a[0]; }
-    { const T t = T(0.19947114020071635) * Pb[17]; ga[1] += t * b[2]; gb[2] += t * a[1]; }
-    { const T t = T(0.19947114020071624) * Pb[17]; ga[5] += t * b[0]; gb[0] += t * a[5]; }
-    { const T t = T(-0.043528171377568134) * Pb[18]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(0.21324361862292318) * Pb[18]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(0.16858388283618392) * Pb[18]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(0.16858388283618392) * Pb[18]; ga[4] += t * b[0]; gb[0] += t * a[4]; }
-    { const T t = T(0.043528171377568134) * Pb[18]; ga[6] += t * b[0]; gb[0] += t * a[6]; }
-    { const T t = T(-0.075393004386513446) * Pb[19]; ga[1] += t * b[2]; gb[2] += t * a[1]; }
-    { const T t = T(0.23841361350444787) * Pb[19]; ga[2] += t * b[1]; gb[1] += t * a[2]; }
-    { const T t = T(0.19466390027300595) * Pb[19]; ga[3] += t * b[0]; gb[0] += t * a[3]; }
-    { const T t = T(0.075393004386513349) * Pb[19]; ga[5] += t * b[0]; gb[0] += t * a[5]; }
-    { const T t = T(-0.150786008773027) * Pb[20]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(0.24623252122982925) * Pb[20]; ga[3] += t * b[1]; gb[1] += t * a[3]; }
-    { const T t = T(-0.150786008773027) * Pb[20]; ga[4] += t * b[2]; gb[2] += t * a[4]; }
-    { const T t = T(-0.075393004386513446) * Pb[21]; ga[1] += t * b[0]; gb[0] += t * a[1]; }
-    { const T t = T(0.19466390027300595) * Pb[21]; ga[3] += t * b[2]; gb[2] += t * a[3]; }
-    { const T t = T(0.23841361350444781) * Pb[21]; ga[4] += t * b[1]; gb[1] += t * a[4]; }
-    { const T t = T(-0.075393004386513335) * Pb[21]; ga[5] += t * b[2]; gb[2] += t * a[5]; }
-    { const T t = T(-0.043528171377568189) * Pb[22]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(-0.16858388283618395) * Pb[22]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(0.16858388283618395) * Pb[22]; ga[4] += t * b[2]; gb[2] += t * a[4]; }
-    { const T t = T(0.21324361862292318) * Pb[22]; ga[5] += t * b[1]; gb[1] += t * a[5]; }
-    { const T t = T(-0.043528171377568182) * Pb[22]; ga[6] += t * b[2]; gb[2] += t * a[6]; }
-    { const T t = T(-0.19947114020071635) * Pb[23]; ga[1] += t * b[0]; gb[0] += t * a[1]; }
-    { const T t = T(0.19947114020071624) * Pb[23]; ga[5] += t * b[2]; gb[2] += t * a[5]; }
-    { const T t = T(0.16286750396763999) * Pb[23]; ga[6] += t * b[1]; gb[1] += t * a[6]; }
-    { const T t = T(-0.23032943298089051) * Pb[24]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.23032943298089054) * Pb[24]; ga[6] += t * b[2]; gb[2] += t * a[6]; }
-  }
-};
-template <> struct Couple<4, 3, 2> {
-  static constexpr int kMask = 10;
-  static constexpr int kTerms = 62;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[1] += T(0.22617901315954025) * (a[0] * b[4]);
-    P[1] += T(0.18467439092237189) * (a[1] * b[3]);
-    P[1] += T(0.20230065940342068) * (a[2] * b[2]);
-    P[1] += T(0.058399170081901736) * (a[2] * b[4]);
-    P[1] += T(-0.1430481681026689) * (a[3] * b[1]);
-    P[1] += T(-0.058399170081901867) * (a[4] * b[0]);
-    P[1] += T(-0.18467439092237192) * (a[5] * b[1]);
-    P[1] += T(-0.22617901315954042) * (a[6] * b[0]);
-    P[2] += T(0.18467439092237187) * (a[1] * b[0]);
-    P[2] += T(0.23359668032760761) * (a[2] * b[1]);
-    P[2] += T(0.24776669508347601) * (a[3] * b[2]);
-    P[2] += T(0.23359668032760761) * (a[4] * b[3]);
-    P[2] += T(0.18467439092237187) * (a[5] * b[4]);
-    P[3] += T(0.22617901315954042) * (a[0] * b[0]);
-    P[3] += T(0.18467439092237189) * (a[1] * b[1]);
-    P[3] += T(-0.058399170081901867) * (a[2] * b[0]);
-    P[3] += T(-0.1430481681026689) * (a[3] * b[3]);
-    P[3] += T(0.20230065940342068) * (a[4] * b[2]);
-    P[3] += T(-0.058399170081901736) * (a[4] * b[4]);
-    P[3] += T(0.18467439092237192) * (a[5] * b[3]);
-    P[3] += T(0.22617901315954025) * (a[6] * b[4]);
-    P[9] += T(-0.21026104350168001) * (a[0] * b[2]);
-    P[9] += T(0.14867700967939765) * (a[1] * b[3]);
-    P[9] += T(-0.094031597257959315) * (a[2] * b[4]);
-    P[9] += T(-0.094031597257959357) * (a[4] * b[0]);
-    P[9] += T(0.14867700967939756) * (a[5] * b[1]);
-    P[10] += T(0.14867700967939765) * (a[0] * b[3]);
-    P[10] += T(0.11516471649044524) * (a[2] * b[3]);
-    P[10] += T(-0.1880631945159188) * (a[3] * b[0]);
-    P[10] += T(0.11516471649044524) * (a[4] * b[1]);
-    P[10] += T(-0.14867700967939765) * (a[6] * b[1]);
-    P[11] += T(-0.094031597257959357) * (a[0] * b[4]);
-    P[11] += T(0.11516471649044524) * (a[1] * b[3]);
-    P[11] += T(0.12615662610100786) * (a[2] * b[2]);
-    P[11] += T(-0.14567312407894395) * (a[2] * b[4]);
-    P[11] += T(0.059470803871758834) * (a[3] * b[1]);
-    P[11] += T(0.14567312407894392) * (a[4] * b[0]);
-    P[11] += T(-0.1151647164904453) * (a[5] * b[1]);
-    P[11] += T(0.094031597257959329) * (a[6] * b[0]);
-    P[12] += T(-0.1880631945159188) * (a[1] * b[0]);
-    P[12] += T(0.059470803871758834) * (a[2] * b[1]);
-    P[12] += T(0.16820883480134416) * (a[3] * b[2]);
-    P[12] += T(0.059470803871758827) * (a[4] * b[3]);
-    P[12] += T(-0.18806319451591863) * (a[5] * b[4]);
-    P[13] += T(-0.094031597257959315) * (a[0] * b[0]);
-    P[13] += T(0.11516471649044524) * (a[1] * b[1]);
-    P[13] += T(0.14567312407894392) * (a[2] * b[0]);
-    P[13] += T(0.059470803871758827) * (a[3] * b[3]);
-    P[13] += T(0.12615662610100786) * (a[4] * b[2]);
-    P[13] += T(0.14567312407894398) * (a[4] * b[4]);
-    P[13] += T(0.11516471649044534) * (a[5] * b[3]);
-    P[13] += T(-0.094031597257959357) * (a[6] * b[4]);
-    P[14] += T(0.14867700967939756) * (a[0] * b[1]);
-    P[14] += T(-0.1151647164904453) * (a[2] * b[1]);
-    P[14] += T(-0.18806319451591863) * (a[3] * b[4]);
-    P[14] += T(0.1151647164904453) * (a[4] * b[3]);
-    P[14] += T(0.14867700967939756) * (a[6] * b[3]);
-    P[15] += T(-0.14867700967939765) * (a[1] * b[1]);
-    P[15] += T(0.094031597257959357) * (a[2] * b[0]);
-    P[15] += T(-0.094031597257959315) * (a[4] * b[4]);
-    P[15] += T(0.14867700967939756) * (a[5] * b[3]);
-    P[15] += T(-0.21026104350168001) * (a[6] * b[2]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(0.22617901315954025) * Pb[1]; ga[0] += t * b[4]; gb[4] += t * a[0]; }
-    { const T t = T(0.18467439092237189) * Pb[1]; ga[1] += t * b[3]; gb[3] += t * a[1]; }
-    { const T t = T(0.20230065940342068) * Pb[1]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(0.058399170081901736) * Pb[1]; ga[2] += t * b[4]; gb[4] += t * a[2]; }
-    { const T t = T(-0.1430481681026689) * Pb[1]; ga[3] += t * b[1]; gb[1] += t * a[3]; }
-    { const T t = T(-0.058399170081901867) * Pb[1]; ga[4] += t * b[0]; gb[0] += t * a[4]; }
-    { const T t = T(-0.18467439092237192) * Pb[1]; ga[5] += t * b[1]; gb[1] += t * a[5]; }
-    { const T t = T(-0.22617901315954042) * Pb[1]; ga[6] += t * b[0]; gb[0] += t * a[6]; }
-    { const T t = T(0.18467439092237187) * Pb[2]; ga[1] += t * b[0]; gb[0] += t * a[1]; }
-    { const T t = T(0.23359668032760761) * Pb[2]; ga[2] += t * b[1]; gb[1] += t * a[2]; }
-    { const T t = T(0.24776669508347601) * Pb[2]; ga[3] += t * b[2]; gb[2] += t * a[3]; }
-    { const T t = T(0.23359668032760761) * Pb[2]; ga[4] += t * b[3]; gb[3] += t * a[4]; }
-    { const T t = T(0.18467439092237187) * Pb[2]; ga[5] += t * b[4]; gb[4] += t * a[5]; }
-    { const T t = T(0.22617901315954042) * Pb[3]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.18467439092237189) * Pb[3]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(-0.058399170081901867) * Pb[3]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(-0.1430481681026689) * Pb[3]; ga[3] += t * b[3]; gb[3] += t * a[3]; }
-    { const T t = T(0.20230065940342068) * Pb[3]; ga[4] += t * b[2]; gb[2] += t * a[4]; }
-    { const T t = T(-0.058399170081901736) * Pb[3]; ga[4] += t * b[4]; gb[4] += t * a[4]; }
-    { const T t = T(0.18467439092237192) * Pb[3]; ga[5] += t * b[3]; gb[3] += t * a[5]; }
-    { const T t = T(0.22617901315954025) * Pb[3]; ga[6] += t * b[4]; gb[4] += t * a[6]; }
-    { const T t = T(-0.21026104350168001) * Pb[9]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(0.14867700967939765) * Pb[9]; ga[1] += t * b[3]; gb[3] += t * a[1]; }
-    { const T t = T(-0.094031597257959315) * Pb[9]; ga[2] += t * b[4]; gb[4] += t * a[2]; }
-    { const T t = T(-0.094031597257959357) * Pb[9]; ga[4] += t * b[0]; gb[0] += t * a[4]; }
-    { const T t = T(0.14867700967939756) * Pb[9]; ga[5] += t * b[1]; gb[1] += t * a[5]; }
-    { const T t = T(0.14867700967939765) * Pb[10]; ga[0] += t * b[3]; gb[3] += t * a[0]; }
-    { const T t = T(0.11516471649044524) * Pb[10]; ga[2] += t * b[3]; gb[3] += t * a[2]; }
-    { const T t = T(-0.1880631945159188) * Pb[10]; ga[3] += t * b[0]; gb[0] += t * a[3]; }
-    { const T t = T(0.11516471649044524) * Pb[10]; ga[4] += t * b[1]; gb[1] += t * a[4]; }
-    { const T t = T(-0.14867700967939765) * Pb[10]; ga[6] += t * b[1]; gb[1] += t * a[6]; }
-    { const T t = T(-0.094031597257959357) * Pb[11]; ga[0] += t * b[4]; gb[4] += t * a[0]; }
-    { const T t = T(0.11516471649044524) * Pb[11]; ga[1] += t * b[3]; gb[3] += t * a[1]; }
-    { const T t = T(0.12615662610100786) * Pb[11]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(-0.14567312407894395) * Pb[11]; ga[2] += t * b[4]; gb[4] += t * a[2]; }
-    { const T t = T(0.059470803871758834) * Pb[11]; ga[3] += t * b[1]; gb[1] += t * a[3]; }
-    { const T t = T(0.14567312407894392) * Pb[11]; ga[4] += t * b[0]; gb[0] += t * a[4]; }
-    { const T t = T(-0.1151647164904453) * Pb[11]; ga[5] += t * b[1]; gb[1] += t * a[5]; }
-    { const T t = T(0.094031597257959329) * Pb[11]; ga[6] += t * b[0]; gb[0] += t * a[6]; }
-    { const T t = T(-0.1880631945159188) * Pb[12]; ga[1] += t * b[0]; gb[0] += t * a[1]; }
-    { const T t = T(0.059470803871758834) * Pb[12]; ga[2] += t * b[1]; gb[1] += t * a[2]; }
-    { const T t = T(0.16820883480134416) * Pb[12]; ga[3] += t * b[2]; gb[2] += t * a[3]; }
-    { const T t = T(0.059470803871758827) * Pb[12]; ga[4] += t * b[3]; gb[3] += t * a[4]; }
-    { const T t = T(-0.18806319451591863) * Pb[12]; ga[5] += t * b[4]; gb[4] += t * a[5]; }
-    { const T t = T(-0.094031597257959315) * Pb[13]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.11516471649044524) * Pb[13]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(0.14567312407894392) * Pb[13]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(0.059470803871758827) * Pb[13]; ga[3] += t * b[3]; gb[3] += t * a[3]; }
-    { const T t = T(0.12615662610100786) * Pb[13]; ga[4] += t * b[2]; gb[2] += t * a[4]; }
-    { const T t = T(0.14567312407894398) * Pb[13]; ga[4] += t * b[4]; gb[4] += t * a[4]; }
-    { const T t = T(0.11516471649044534) * Pb[13]; ga[5] += t * b[3]; gb[3] += t * a[5]; }
-    { const T t = T(-0.094031597257959357) * Pb[13]; ga[6] += t * b[4]; gb[4] += t * a[6]; }
-    { const T t = T(0.14867700967939756) * Pb[14]; ga[0] += t * b[1]; gb[1] += t * a[0]; }
-    { const T t = T(-0.1151647164904453) * Pb[14]; ga[2] += t * b[1]; gb[1] += t * a[2]; }
-    { const T t = T(-0.18806319451591863) * Pb[14]; ga[3] += t * b[4]; gb[4] += t * a[3]; }
-    { const T t = T(0.1151647164904453) * Pb[14]; ga[4] += t * b[3]; gb[3] += t * a[4]; }
-    { const T t = T(0.14867700967939756) * Pb[14]; ga[6] += t * b[3]; gb[3] += t * a[6]; }
-    { const T t = T(-0.14867700967939765) * Pb[15]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(0.094031597257959357) * Pb[15]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(-0.094031597257959315) * Pb[15]; ga[4] += t * b[4]; gb[4] += t * a[4]; }
-    { const T t = T(0.14867700967939756) * Pb[15]; ga[5] += t * b[3]; gb[3] += t * a[5]; }
-    { const T t = T(-0.21026104350168001) * Pb[15]; ga[6] += t * b[2]; gb[2] += t * a[6]; }
-  }
-};
-template <> struct Couple<4, 3, 3> {
-  static constexpr int kMask = 21;
-  static constexpr int kTerms = 115;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[0] += T(0.2820947917738782) * (a[0] * b[0]);
-    P[0] += T(0.2820947917738782) * (a[1] * b[1]);
-    P[0] += T(0.28209479177387825) * (a[2] * b[2]);
-    P[0] += T(0.28209479177387814) * (a[3] * b[3]);
-    P[0] += T(0.28209479177387825) * (a[4] * b[4]);
-    P[0] += T(0.28209479177387825) * (a[5] * b[5]);
-    P[0] += T(0.2820947917738782) * (a[6] * b[6]);
-    P[4] += T(-0.094031597257959357) * (a[0] * b[4]);
-    P[4] += T(-0.1880631945159188) * (a[1] * b[3]);
-    P[4] += T(0.14567312407894387) * (a[2] * b[4]);
-    P[4] += T(0.094031597257959357) * (a[2] * b[6]);
-    P[4] += T(-0.1880631945159188) * (a[3] * b[1]);
-    P[4] += T(-0.094031597257959357) * (a[4] * b[0]);
-    P[4] += T(0.14567312407894387) * (a[4] * b[2]);
-    P[4] += T(0.094031597257959357) * (a[6] * b[2]);
-    P[5] += T(0.14867700967939754) * (a[0] * b[5]);
-    P[5] += T(0.11516471649044524) * (a[1] * b[4]);
-    P[5] += T(-0.14867700967939765) * (a[1] * b[6]);
-    P[5] += T(0.0594708038717588) * (a[2] * b[3]);
-    P[5] += T(-0.1151647164904453) * (a[2] * b[5]);
-    P[5] += T(0.0594708038717588) * (a[3] * b[2]);
-    P[5] += T(0.11516471649044524) * (a[4] * b[1]);
-    P[5] += T(0.14867700967939754) * (a[5] * b[0]);
-    P[5] += T(-0.1151647164904453) * (a[5] * b[2]);
-    P[5] += T(-0.14867700967939765) * (a[6] * b[1]);
-    P[6] += T(-0.21026104350168001) * (a[0] * b[0]);
-    P[6] += T(0.12615662610100786) * (a[2] * b[2]);
-    P[6] += T(0.16820883480134416) * (a[3] * b[3]);
-    P[6] += T(0.12615662610100786) * (a[4] * b[4]);
-    P[6] += T(-0.21026104350168001) * (a[6] * b[6]);
-    P[7] += T(0.14867700967939765) * (a[0] * b[1]);
-    P[7] += T(0.14867700967939765) * (a[1] * b[0]);
-    P[7] += T(0.11516471649044524) * (a[1] * b[2]);
-    P[7] += T(0.11516471649044524) * (a[2] * b[1]);
-    P[7] += T(0.059470803871758765) * (a[3] * b[4]);
-    P[7] += T(0.059470803871758765) * (a[4] * b[3]);
-    P[7] += T(0.1151647164904453) * (a[4] * b[5]);
-    P[7] += T(0.11516471649044534) * (a[5] * b[4]);
-    P[7] += T(0.14867700967939754) * (a[5] * b[6]);
-    P[7] += T(0.14867700967939754) * (a[6] * b[5]);
-    P[8] += T(-0.094031597257959357) * (a[0] * b[2]);
-    P[8] += T(-0.094031597257959357) * (a[2] * b[0]);
-    P[8] += T(-0.14567312407894392) * (a[2] * b[2]);
-    P[8] += T(-0.18806319451591855) * (a[3] * b[5]);
-    P[8] += T(0.14567312407894392) * (a[4] * b[4]);
-    P[8] += T(-0.094031597257959371) * (a[4] * b[6]);
-    P[8] += T(-0.1880631945159186) * (a[5] * b[3]);
-    P[8] += T(-0.094031597257959357) * (a[6] * b[4]);
-    P[16] += T(-0.11752006695060026) * (a[0] * b[4]);
-    P[16] += T(0.151717754048285) * (a[1] * b[5]);
-    P[16] += T(-0.11752006695060026) * (a[2] * b[6]);
-    P[16] += T(-0.11752006695060026) * (a[4] * b[0]);
-    P[16] += T(0.151717754048285) * (a[5] * b[1]);
-    P[16] += T(-0.11752006695060023) * (a[6] * b[2]);
-    P[17] += T(-0.20355072686733564) * (a[0] * b[3]);
-    P[17] += T(0.067850242289111948) * (a[1] * b[4]);
-    P[17] += T(0.067850242289111934) * (a[2] * b[5]);
-    P[17] += T(-0.20355072686733564) * (a[3] * b[0]);
-    P[17] += T(0.067850242289111948) * (a[4] * b[1]);
-    P[17] += T(0.067850242289111934) * (a[5] * b[2]);
-    P[18] += T(0.13325523051897822) * (a[0] * b[4]);
-    P[18] += T(-0.044418410172992757) * (a[1] * b[3]);
-    P[18] += T(0.11468784191000729) * (a[2] * b[4]);
-    P[18] += T(-0.1332552305189782) * (a[2] * b[6]);
-    P[18] += T(-0.044418410172992757) * (a[3] * b[1]);
-    P[18] += T(0.1332552305189782) * (a[4] * b[0]);
-    P[18] += T(0.11468784191000729) * (a[4] * b[2]);
-    P[18] += T(-0.1332552305189782) * (a[6] * b[2]);
-    P[19] += T(-0.099322584599279867) * (a[0] * b[5]);
-    P[19] += T(0.10257992428141016) * (a[1] * b[4]);
-    P[19] += T(0.099322584599279881) * (a[1] * b[6]);
-    P[19] += T(0.099322584599279909) * (a[2] * b[3]);
-    P[19] += T(-0.10257992428141016) * (a[2] * b[5]);
-    P[19] += T(0.099322584599279909) * (a[3] * b[2]);
-    P[19] += T(0.10257992428141016) * (a[4] * b[1]);
-    P[19] += T(-0.099322584599279867) * (a[5] * b[0]);
-    P[19] += T(-0.10257992428141022) * (a[5] * b[2]);
-    P[19] += T(0.099322584599279881) * (a[6] * b[1]);
-    P[20] += T(0.076934943211057691) * (a[0] * b[0]);
-    P[20] += T(-0.17951486749246795) * (a[1] * b[1]);
-    P[20] += T(0.025644981070352291) * (a[2] * b[2]);
-    P[20] += T(0.15386988642211546) * (a[3] * b[3]);
-    P[20] += T(0.025644981070352325) * (a[4] * b[4]);
-    P[20] += T(-0.17951486749246778) * (a[5] * b[5]);
-    P[20] += T(0.076934943211057705) * (a[6] * b[6]);
-    P[21] += T(-0.099322584599279881) * (a[0] * b[1]);
-    P[21] += T(-0.099322584599279881) * (a[1] * b[0]);
-    P[21] += T(0.10257992428141016) * (a[1] * b[2]);
-    P[21] += T(0.10257992428141016) * (a[2] * b[1]);
-    P[21] += T(0.099322584599279881) * (a[3] * b[4]);
-    P[21] += T(0.099322584599279881) * (a[4] * b[3]);
-    P[21] += T(0.10257992428141022) * (a[4] * b[5]);
-    P[21] += T(0.10257992428141022) * (a[5] * b[4]);
-    P[21] += T(-0.099322584599279867) * (a[5] * b[6]);
-    P[21] += T(-0.099322584599279867) * (a[6] * b[5]);
-    P[22] += T(0.1332552305189782) * (a[0] * b[2]);
-    P[22] += T(0.1332552305189782) * (a[2] * b[0]);
-    P[22] += T(-0.11468784191000719) * (a[2] * b[2]);
-    P[22] += T(-0.044418410172992556) * (a[3] * b[5]);
-    P[22] += T(0.11468784191000722) * (a[4] * b[4]);
-    P[22] += T(0.13325523051897817) * (a[4] * b[6]);
-    P[22] += T(-0.044418410172992556) * (a[5] * b[3]);
-    P[22] += T(0.1332552305189782) * (a[6] * b[4]);
-    P[23] += T(-0.067850242289111962) * (a[1] * b[2]);
-    P[23] += T(-0.067850242289111962) * (a[2] * b[1]);
-    P[23] += T(-0.20355072686733564) * (a[3] * b[6]);
-    P[23] += T(0.067850242289111934) * (a[4] * b[5]);
-    P[23] += T(0.067850242289111934) * (a[5] * b[4]);
-    P[23] += T(-0.20355072686733564) * (a[6] * b[3]);
-    P[24] += T(0.1175200669506001) * (a[0] * b[2]);
-    P[24] += T(-0.15171775404828516) * (a[1] * b[1]);
-    P[24] += T(0.1175200669506001) * (a[2] * b[0]);
-    P[24] += T(-0.11752006695060009) * (a[4] * b[6]);
-    P[24] += T(0.15171775404828503) * (a[5] * b[5]);
-    P[24] += T(-0.11752006695060012) * (a[6] * b[4]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(0.2820947917738782) * Pb[0]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.2820947917738782) * Pb[0]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(0.28209479177387825) * Pb[0]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(0.28209479177387814) * Pb[0]; ga[3] += t * b[3]; gb[3] += t * a[3]; }
-    { const T t = T(0.28209479177387825) * Pb[0]; ga[4] += t * b[4]; gb[4] += t * a[4]; }
-    { const T t = T(0.28209479177387825) * Pb[0]; ga[5] += t * b[5]; gb[5] += t * a[5]; }
-    { const T t = T(0.2820947917738782) * Pb[0]; ga[6] += t * b[6]; gb[6] += t * a[6]; }
-    { const T t = T(-0.094031597257959357) * Pb[4]; ga[0] += t * b[4]; gb[4] += t * a[0]; }
-    { const T t = T(-0.1880631945159188) * Pb[4]; ga[1] += t * b[3]; gb[3] += t * a[1]; }
-    { const T t = T(0.14567312407894387) * Pb[4]; ga[2] += t * b[4]; gb[4] += t * a[2]; }
-    { const T t = T(0.094031597257959357) * Pb[4]; ga[2] += t * b[6]; gb[6] += t * a[2]; }
-    { const T t = T(-0.1880631945159188) * Pb[4]; ga[3] += t * b[1]; gb[1] += t * a[3]; }
-    { const T t = T(-0.094031597257959357) * Pb[4]; ga[4] += t * b[0]; gb[0] += t * a[4]; }
-    { const T t = T(0.14567312407894387) * Pb[4]; ga[4] += t * b[2]; gb[2] += t * a[4]; }
-    { const T t = T(0.094031597257959357) * Pb[4]; ga[6] += t * b[2]; gb[2] += t * a[6]; }
-    { const T t = T(0.14867700967939754) * Pb[5]; ga[0] += t * b[5]; gb[5] += t * a[0]; }
-    { const T t = T(0.11516471649044524) * Pb[5]; ga[1] += t * b[4]; gb[4] += t * a[1]; }
-    { const T t = T(-0.14867700967939765) * Pb[5]; ga[1] += t * b[6]; gb[6] += t * a[1]; }
-    { const T t = T(0.0594708038717588) * Pb[5]; ga[2] += t * b[3]; gb[3] += t * a[2]; }
-    { const T t = T(-0.1151647164904453) * Pb[5]; ga[2] += t * b[5]; gb[5] += t * a[2]; }
-    { const T t = T(0.0594708038717588) * Pb[5]; ga[3] += t * b[2]; gb[2] += t * a[3]; }
-    { const T t = T(0.11516471649044524) * Pb[5]; ga[4] += t * b[1]; gb[1] += t * a[4]; }
-    { const T t = T(0.14867700967939754) * Pb[5]; ga[5] += t * b[0]; gb[0] += t * a[5]; }
-    { const T t = T(-0.1151647164904453) * Pb[5]; ga[5] += t * b[2]; gb[2] += t * a[5]; }
-    { const T t = T(-0.14867700967939765) * Pb[5]; ga[6] += t * b[1]; gb[1] += t * a[6]; }
-    { const T t = T(-0.21026104350168001) * Pb[6]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.12615662610100786) * Pb[6]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(0.16820883480134416) * Pb[6]; ga[3] += t * b[3]; gb[3] += t * a[3]; }
-    { const T t = T(0.12615662610100786) * Pb[6]; ga[4] += t * b[4]; gb[4] += t * a[4]; }
-    { const T t = T(-0.21026104350168001) * Pb[6]; ga[6] += t * b[6]; gb[6] += t * a[6]; }
-    { const T t = T(0.14867700967939765) * Pb[7]; ga[0] += t * b[1]; gb[1] += t * a[0]; }
-    { const T t = T(0.14867700967939765) * Pb[7]; ga[1] += t * b[0]; gb[0] += t * a[1]; }
-    { const T t = T(0.11516471649044524) * Pb[7]; ga[1] += t * b[2]; gb[2] += t * a[1]; }
-    { const T t = T(0.11516471649044524) * Pb[7]; ga[2] += t * b[1]; gb[1] += t * a[2]; }
-    { const T t = T(0.059470803871758765) * Pb[7]; ga[3] += t * b[4]; gb[4] += t * a[3]; }
-    { const T t = T(0.059470803871758765) * Pb[7]; ga[4] += t * b[3]; gb[3] += t * a[4]; }
-    { const T t = T(0.1151647164904453) * Pb[7]; ga[4] += t * b[5]; gb[5] += t * a[4]; }
-    { const T t = T(0.11516471649044534) * Pb[7]; ga[5] += t * b[4]; gb[4] += t * a[5]; }
-    { const T t = T(0.14867700967939754) * Pb[7]; ga[5] += t * b[6]; gb[6] += t * a[5]; }
-    { const T t = T(0.14867700967939754) * Pb[7]; ga[6] += t * b[5]; gb[5] += t * a[6]; }
-    { const T t = T(-0.094031597257959357) * Pb[8]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(-0.094031597257959357) * Pb[8]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(-0.14567312407894392) * Pb[8]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(-0.18806319451591855) * Pb[8]; ga[3] += t * b[5]; gb[5] += t * a[3]; }
-    { const T t = T(0.14567312407894392) * Pb[8]; ga[4] += t * b[4]; gb[4] += t * a[4]; }
-    { const T t = T(-0.094031597257959371) * Pb[8]; ga[4] += t * b[6]; gb[6] += t * a[4]; }
-    { const T t = T(-0.1880631945159186) * Pb[8]; ga[5] += t * b[3]; gb[3] += t * a[5]; }
-    { const T t = T(-0.094031597257959357) * Pb[8]; ga[6] += t * b[4]; gb[4] += t * a[6]; }
-    { const T t = T(-0.11752006695060026) * Pb[16]; ga[0] += t * b[4]; gb[4] += t * a[0]; }
-    { const T t = T(0.151717754048285) * Pb[16]; ga[1] += t * b[5]; gb[5] += t * a[1]; }
-    { const T t = T(-0.11752006695060026) * Pb[16]; ga[2] += t * b[6]; gb[6] += t * a[2]; }
-    { const T t = T(-0.11752006695060026) * Pb[16]; ga[4] += t * b[0]; gb[0] += t * a[4]; }
-    { const T t = T(0.151717754048285) * Pb[16]; ga[5] += t * b[1]; gb[1] += t * a[5]; }
-    { const T t = T(-0.11752006695060023) * Pb[16]; ga[6] += t * b[2]; gb[2] += t * a[6]; }
-    { const T t = T(-0.20355072686733564) * Pb[17]; ga[0] += t * b[3]; gb[3] += t * a[0]; }
-    { const T t = T(0.067850242289111948) * Pb[17]; ga[1] += t * b[4]; gb[4] += t * a[1]; }
-    { const T t = T(0.067850242289111934) * Pb[17]; ga[2] += t * b[5]; gb[5] += t * a[2]; }
-    { const T t = T(-0.20355072686733564) * Pb[17]; ga[3] += t * b[0]; gb[0] += t * a[3]; }
-    { const T t = T(0.067850242289111948) * Pb[17]; ga[4] += t * b[1]; gb[1] += t * a[4]; }
-    { const T t = T(0.067850242289111934) * Pb[17]; ga[5] += t * b[2]; gb[2] += t * a[5]; }
-    { const T t = T(0.13325523051897822) * Pb[18]; ga[0] += t * b[4]; gb[4] += t * a[0]; }
-    { const T t = T(-0.044418410172992757) * Pb[18]; ga[1] += t * b[3]; gb[3] += t * a[1]; }
-    { const T t = T(0.11468784191000729) * Pb[18]; ga[2] += t * b[4]; gb[4] += t * a[2]; }
-    { const T t = T(-0.1332552305189782) * Pb[18]; ga[2] += t * b[6]; gb[6] += t * a[2]; }
-    { const T t = T(-0.044418410172992757) * Pb[18]; ga[3] += t * b[1]; gb[1] += t * a[3]; }
-    { const T t = T(0.1332552305189782) * Pb[18]; ga[4] += t * b[0]; gb[0] += t * a[4]; }
-    { const T t = T(0.11468784191000729) * Pb[18]; ga[4] += t * b[2]; gb[2] += t * a[4]; }
-    { const T t = T(-0.1332552305189782) * Pb[18]; ga[6] += t * b[2]; gb[2] += t * a[6]; }
-    { const T t = T(-0.099322584599279867) * Pb[19]; ga[0] += t * b[5]; gb[5] += t * a[0]; }
-    { const T t = T(0.10257992428141016) * Pb[19]; ga[1] += t * b[4]; gb[4] += t * a[1]; }
-    { const T t = T(0.099322584599279881) * Pb[19]; ga[1] += t * b[6]; gb[6] += t * a[1]; }
-    { const T t = T(0.099322584599279909) * Pb[19]; ga[2] += t * b[3]; gb[3] += t * a[2]; }
-    { const T t = T(-0.10257992428141016) * Pb[19]; ga[2] += t * b[5]; gb[5] += t * a[2]; }
-    { const T t = T(0.099322584599279909) * Pb[19]; ga[3] += t * b[2]; gb[2] += t * a[3]; }
-    { const T t = T(0.10257992428141016) * Pb[19]; ga[4] += t * b[1]; gb[1] += t * a[4]; }
-    { const T t = T(-0.099322584599279867) * Pb[19]; ga[5] += t * b[0]; gb[0] += t * a[5]; }
-    { const T t = T(-0.10257992428141022) * Pb[19]; ga[5] += t * b[2]; gb[2] += t * a[5]; }
-    { const T t = T(0.099322584599279881) * Pb[19]; ga[6] += t * b[1]; gb[1] += t * a[6]; }
-    { const T t = T(0.076934943211057691) * Pb[20]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(-0.17951486749246795) * Pb[20]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(0.025644981070352291) * Pb[20]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(0.15386988642211546) * Pb[20]; ga[3] += t * b[3]; gb[3] += t * a[3]; }
-    { const T t = T(0.025644981070352325) * Pb[20]; ga[4] += t * b[4]; gb[4] += t * a[4]; }
-    { const T t = T(-0.17951486749246778) * Pb[20]; ga[5] += t * b[5]; gb[5] += t * a[5]; }
-    { const T t = T(0.076934943211057705) * Pb[20]; ga[6] += t * b[6]; gb[6] += t * a[6]; }
-    { const T t = T(-0.099322584599279881) * Pb[21]; ga[0] += t * b[1]; gb[1] += t * a[0]; }
-    { const T t = T(-0.099322584599279881) * Pb[21]; ga[1] += t * b[0]; gb[0] += t * a[1]; }
-    { const T t = T(0.10257992428141016) * Pb[21]; ga[1] += t * b[2]; gb[2] += t * a[1]; }
-    { const T t = T(0.10257992428141016) * Pb[21]; ga[2] += t * b[1]; gb[1] += t * a[2]; }
-    { const T t = T(0.099322584599279881) * Pb[21]; ga[3] += t * b[4]; gb[4] += t * a[3]; }
-    { const T t = T(0.099322584599279881) * Pb[21]; ga[4] += t * b[3]; gb[3] += t * a[4]; }
-    { const T t = T(0.10257992428141022) * Pb[21]; ga[4] += t * b[5]; gb[5] += t * a[4]; }
-    { const T t = T(0.10257992428141022) * Pb[21]; ga[5] += t * b[4]; gb[4] += t * a[5]; }
-    { const T t = T(-0.099322584599279867) * Pb[21]; ga[5] += t * b[6]; gb[6] += t * a[5]; }
-    { const T t = T(-0.099322584599279867) * Pb[21]; ga[6] += t * b[5]; gb[5] += t * a[6]; }
-    { const T t = T(0.1332552305189782) * Pb[22]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(0.1332552305189782) * Pb[22]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(-0.11468784191000719) * Pb[22]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(-0.044418410172992556) * Pb[22]; ga[3] += t * b[5]; gb[5] += t * a[3]; }
-    { const T t = T(0.11468784191000722) * Pb[22]; ga[4] += t * b[4]; gb[4] += t * a[4]; }
-    { const T t = T(0.13325523051897817) * Pb[22]; ga[4] += t * b[6]; gb[6] += t * a[4]; }
-    { const T t = T(-0.044418410172992556) * Pb[22]; ga[5] += t * b[3]; gb[3] += t * a[5]; }
-    { const T t = T(0.1332552305189782) * Pb[22]; ga[6] += t * b[4]; gb[4] += t * a[6]; }
-    { const T t = T(-0.067850242289111962) * Pb[23]; ga[1] += t * b[2]; gb[2] += t * a[1]; }
-    { const T t = T(-0.067850242289111962) * Pb[23]; ga[2] += t * b[1]; gb[1] += t * a[2]; }
-    { const T t = T(-0.20355072686733564) * Pb[23]; ga[3] += t * b[6]; gb[6] += t * a[3]; }
-    { const T t = T(0.067850242289111934) * Pb[23]; ga[4] += t * b[5]; gb[5] += t * a[4]; }
-    { const T t = T(0.067850242289111934) * Pb[23]; ga[5] += t * b[4]; gb[4] += t * a[5]; }
-    { const T t = T(-0.20355072686733564) * Pb[23]; ga[6] += t * b[3]; gb[3] += t * a[6]; }
-    { const T t = T(0.1175200669506001) * Pb[24]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(-0.15171775404828516) * Pb[24]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(0.1175200669506001) * Pb[24]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(-0.11752006695060009) * Pb[24]; ga[4] += t * b[6]; gb[6] += t * a[4]; }
-    { const T t = T(0.15171775404828503) * Pb[24]; ga[5] += t * b[5]; gb[5] += t * a[5]; }
-    { const T t = T(-0.11752006695060012) * Pb[24]; ga[6] += t * b[4]; gb[4] += t * a[6]; }
-  }
-};
-template <> struct Couple<4, 3, 4> {
-  static constexpr int kMask = 10;
-  static constexpr int kTerms = 98;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[1] += T(-0.043528171377568182) * (a[0] * b[6]);
-    P[1] += T(-0.23032943298089045) * (a[0] * b[8]);
-    P[1] += T(-0.075393004386513432) * (a[1] * b[5]);
-    P[1] += T(-0.1994711402007163) * (a[1] * b[7]);
-    P[1] += T(-0.15078600877302697) * (a[2] * b[4]);
-    P[1] += T(-0.16858388283618392) * (a[2] * b[6]);
-    P[1] += T(0.19466390027300592) * (a[3] * b[3]);
-    P[1] += T(0.16858388283618389) * (a[4] * b[2]);
-    P[1] += T(0.19947114020071621) * (a[5] * b[1]);
-    P[1] += T(0.075393004386513335) * (a[5] * b[3]);
-    P[1] += T(0.23032943298089015) * (a[6] * b[0]);
-    P[1] += T(0.043528171377568127) * (a[6] * b[2]);
-    P[2] += T(0.16286750396763996) * (a[0] * b[1]);
-    P[2] += T(0.21324361862292315) * (a[1] * b[2]);
-    P[2] += T(0.23841361350444784) * (a[2] * b[3]);
-    P[2] += T(0.24623252122982922) * (a[3] * b[4]);
-    P[2] += T(0.23841361350444776) * (a[4] * b[5]);
-    P[2] += T(0.21324361862292315) * (a[5] * b[6]);
-    P[2] += T(0.16286750396763996) * (a[6] * b[7]);
-    P[3] += T(0.23032943298089015) * (a[0] * b[0]);
-    P[3] += T(-0.043528171377568127) * (a[0] * b[2]);
-    P[3] += T(0.1994711402007163) * (a[1] * b[1]);
-    P[3] += T(-0.075393004386513432) * (a[1] * b[3]);
-    P[3] += T(0.16858388283618389) * (a[2] * b[2]);
-    P[3] += T(0.19466390027300592) * (a[3] * b[5]);
-    P[3] += T(-0.15078600877302697) * (a[4] * b[4]);
-    P[3] += T(0.16858388283618392) * (a[4] * b[6]);
-    P[3] += T(-0.075393004386513321) * (a[5] * b[5]);
-    P[3] += T(0.19947114020071621) * (a[5] * b[7]);
-    P[3] += T(-0.043528171377568176) * (a[6] * b[6]);
-    P[3] += T(0.23032943298089048) * (a[6] * b[8]);
-    P[9] += T(0.076934943211057705) * (a[0] * b[4]);
-    P[9] += T(-0.099322584599279867) * (a[1] * b[5]);
-    P[9] += T(0.13325523051897822) * (a[2] * b[6]);
-    P[9] += T(0.11752006695060022) * (a[2] * b[8]);
-    P[9] += T(-0.20355072686733561) * (a[3] * b[1]);
-    P[9] += T(-0.11752006695060026) * (a[4] * b[0]);
-    P[9] += T(0.13325523051897814) * (a[4] * b[2]);
-    P[9] += T(-0.099322584599279881) * (a[5] * b[3]);
-    P[10] += T(-0.099322584599279881) * (a[0] * b[5]);
-    P[10] += T(-0.17951486749246792) * (a[1] * b[4]);
-    P[10] += T(-0.15171775404828525) * (a[1] * b[8]);
-    P[10] += T(0.10257992428141011) * (a[2] * b[5]);
-    P[10] += T(-0.067850242289111934) * (a[2] * b[7]);
-    P[10] += T(-0.044418410172992751) * (a[3] * b[2]);
-    P[10] += T(0.067850242289111906) * (a[4] * b[1]);
-    P[10] += T(0.10257992428141011) * (a[4] * b[3]);
-    P[10] += T(0.15171775404828494) * (a[5] * b[0]);
-    P[10] += T(0.099322584599279881) * (a[6] * b[3]);
-    P[11] += T(0.1332552305189782) * (a[0] * b[6]);
-    P[11] += T(0.11752006695060019) * (a[0] * b[8]);
-    P[11] += T(0.10257992428141011) * (a[1] * b[5]);
-    P[11] += T(-0.067850242289111934) * (a[1] * b[7]);
-    P[11] += T(0.025644981070352315) * (a[2] * b[4]);
-    P[11] += T(-0.11468784191000718) * (a[2] * b[6]);
-    P[11] += T(0.099322584599279895) * (a[3] * b[3]);
-    P[11] += T(0.11468784191000722) * (a[4] * b[2]);
-    P[11] += T(0.067850242289111934) * (a[5] * b[1]);
-    P[11] += T(-0.10257992428141018) * (a[5] * b[3]);
-    P[11] += T(-0.11752006695060027) * (a[6] * b[0]);
-    P[11] += T(-0.13325523051897814) * (a[6] * b[2]);
-    P[12] += T(-0.20355072686733566) * (a[0] * b[1]);
-    P[12] += T(-0.044418410172992751) * (a[1] * b[2]);
-    P[12] += T(0.099322584599279895) * (a[2] * b[3]);
-    P[12] += T(0.15386988642211544) * (a[3] * b[4]);
-    P[12] += T(0.099322584599279881) * (a[4] * b[5]);
-    P[12] += T(-0.044418410172992549) * (a[5] * b[6]);
-    P[12] += T(-0.20355072686733566) * (a[6] * b[7]);
-    P[13] += T(-0.11752006695060027) * (a[0] * b[0]);
-    P[13] += T(0.13325523051897814) * (a[0] * b[2]);
-    P[13] += T(0.067850242289111906) * (a[1] * b[1]);
-    P[13] += T(0.10257992428141011) * (a[1] * b[3]);
-    P[13] += T(0.11468784191000722) * (a[2] * b[2]);
-    P[13] += T(0.099322584599279881) * (a[3] * b[5]);
-    P[13] += T(0.02564498107035235) * (a[4] * b[4]);
-    P[13] += T(0.11468784191000721) * (a[4] * b[6]);
-    P[13] += T(0.1025799242814102) * (a[5] * b[5]);
-    P[13] += T(0.06785024228911192) * (a[5] * b[7]);
-    P[13] += T(0.1332552305189782) * (a[6] * b[6]);
-    P[13] += T(-0.11752006695060019) * (a[6] * b[8]);
-    P[14] += T(-0.099322584599279853) * (a[0] * b[3]);
-    P[14] += T(0.15171775404828494) * (a[1] * b[0]);
-    P[14] += T(0.067850242289111948) * (a[2] * b[1]);
-    P[14] += T(-0.10257992428141025) * (a[2] * b[3]);
-    P[14] += T(-0.044418410172992549) * (a[3] * b[6]);
-    P[14] += T(0.1025799242814102) * (a[4] * b[5]);
-    P[14] += T(0.067850242289111962) * (a[4] * b[7]);
-    P[14] += T(-0.17951486749246778) * (a[5] * b[4]);
-    P[14] += T(0.151717754048285) * (a[5] * b[8]);
-    P[14] += T(-0.099322584599279881) * (a[6] * b[5]);
-    P[15] += T(0.099322584599279853) * (a[1] * b[3]);
-    P[15] += T(-0.11752006695060024) * (a[2] * b[0]);
-    P[15] += T(-0.13325523051897817) * (a[2] * b[2]);
-    P[15] += T(-0.20355072686733561) * (a[3] * b[7]);
-    P[15] += T(0.1332552305189782) * (a[4] * b[6]);
-    P[15] += T(-0.11752006695060023) * (a[4] * b[8]);
-    P[15] += T(-0.099322584599279881) * (a[5] * b[5]);
-    P[15] += T(0.076934943211057705) * (a[6] * b[4]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(-0.043528171377568182) * Pb[1]; ga[0] += t * b[6]; gb[6] += t * a[0]; }
-    { const T t = T(-0.23032943298089045) * Pb[1]; ga[0] += t * b[8]; gb[8] += t * a[0]; }
-    { const T t = T(-0.075393004386513432) * Pb[1]; ga[1] += t * b[5]; gb[5] += t * a[1]; }
-    { const T t = T(-0.1994711402007163) * Pb[1]; ga[1] += t * b[7]; gb[7] += t * a[1]; }
-    { const T t = T(-0.15078600877302697) * Pb[1]; ga[2] += t * b[4]; gb[4] += t * a[2]; }
-    { const T t = T(-0.16858388283618392) * Pb[1]; ga[2] += t * b[6]; gb[6] += t * a[2]; }
-    { const T t = T(0.19466390027300592) * Pb[1]; ga[3] += t * b[3]; gb[3] += t * a[3]; }
-    { const T t = T(0.16858388283618389) * Pb[1]; ga[4] += t * b[2]; gb[2] += t * a[4]; }
-    { const T t = T(0.19947114020071621) * Pb[1]; ga[5] += t * b[1]; gb[1] += t * a[5]; }
-    { const T t = T(0.075393004386513335) * Pb[1]; ga[5] += t * b[3]; gb[3] += t * a[5]; }
-    { const T t = T(0.23032943298089015) * Pb[1]; ga[6] += t * b[0]; gb[0] += t * a[6]; }
-    { const T t = T(0.043528171377568127) * Pb[1]; ga[6] += t * b[2]; gb[2] += t * a[6]; }
-    { const T t = T(0.16286750396763996) * Pb[2]; ga[0] += t * b[1]; gb[1] += t * a[0]; }
-    { const T t = T(0.21324361862292315) * Pb[2]; ga[1] += t * b[2]; gb[2] += t * a[1]; }
-    { const T t = T(0.23841361350444784) * Pb[2]; ga[2] += t * b[3]; gb[3] += t * a[2]; }
-    { const T t = T(0.24623252122982922) * Pb[2]; ga[3] += t * b[4]; gb[4] += t * a[3]; }
-    { const T t = T(0.23841361350444776) * Pb[2]; ga[4] += t * b[5]; gb[5] += t * a[4]; }
-    { const T t = T(0.21324361862292315) * Pb[2]; ga[5] += t * b[6]; gb[6] += t * a[5]; }
-    { const T t = T(0.16286750396763996) * Pb[2]; ga[6] += t * b[7]; gb[7] += t * a[6]; }
-    { const T t = T(0.23032943298089015) * Pb[3]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(-0.043528171377568127) * Pb[3]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(0.1994711402007163) * Pb[3]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(-0.075393004386513432) * Pb[3]; ga[1] += t * b[3]; gb[3] += t * a[1]; }
-    { const T t = T(0.16858388283618389) * Pb[3]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(0.19466390027300592) * Pb[3]; ga[3] += t * b[5]; gb[5] += t * a[3]; }
-    { const T t = T(-0.15078600877302697) * Pb[3]; ga[4] += t * b[4]; gb[4] += t * a[4]; }
-    { const T t = T(0.16858388283618392) * Pb[3]; ga[4] += t * b[6]; gb[6] += t * a[4]; }
-    { const T t = T(-0.075393004386513321) * Pb[3]; ga[5] += t * b[5]; gb[5] += t * a[5]; }
-    { const T t = T(0.19947114020071621) * Pb[3]; ga[5] += t * b[7]; gb[7] += t * a[5]; }
-    { const T t = T(-0.043528171377568176) * Pb[3]; ga[6] += t * b[6]; gb[6] += t * a[6]; }
-    { const T t = T(0.23032943298089048) * Pb[3]; ga[6] += t * b[8]; gb[8] += t * a[6]; }
-    { const T t = T(0.076934943211057705) * Pb[9]; ga[0] += t * b[4]; gb[4] += t * a[0]; }
-    { const T t = T(-0.099322584599279867) * Pb[9]; ga[1] += t * b[5]; gb[5] += t * a[1]; }
-    { const T t = T(0.13325523051897822) * Pb[9]; ga[2] += t * b[6]; gb[6] += t * a[2]; }
-    { const T t = T(0.11752006695060022) * Pb[9]; ga[2] += t * b[8]; gb[8] += t * a[2]; }
-    { const T t = T(-0.20355072686733561) * Pb[9]; ga[3] += t * b[1]; gb[1] += t * a[3]; }
-    { const T t = T(-0.11752006695060026) * Pb[9]; ga[4] += t * b[0]; gb[0] += t * a[4]; }
-    { const T t = T(0.13325523051897814) * Pb[9]; ga[4] += t * b[2]; gb[2] += t * a[4]; }
-    { const T t = T(-0.099322584599279881) * Pb[9]; ga[5] += t * b[3]; gb[3] += t * a[5]; }
-    { const T t = T(-0.099322584599279881) * Pb[10]; ga[0] += t * b[5]; gb[5] += t * a[0]; }
-    { const T t = T(-0.17951486749246792) * Pb[10]; ga[1] += t * b[4]; gb[4] += t * a[1]; }
-    { const T t = T(-0.15171775404828525) * Pb[10]; ga[1] += t * b[8]; gb[8] += t * a[1]; }
-    { const T t = T(0.10257992428141011) * Pb[10]; ga[2] += t * b[5]; gb[5] += t * a[2]; }
-    { const T t = T(-0.067850242289111934) * Pb[10]; ga[2] += t * b[7]; gb[7] += t * a[2]; }
-    { const T t = T(-0.044418410172992751) * Pb[10]; ga[3] += t * b[2]; gb[2] += t * a[3]; }
-    { const T t = T(0.067850242289111906) * Pb[10]; ga[4] += t * b[1]; gb[1] += t * a[4]; }
-    { const T t = T(0.10257992428141011) * Pb[10]; ga[4] += t * b[3]; gb[3] += t * a[4]; }
-    { const T t = T(0.15171775404828494) * Pb[10]; ga[5] += t * b[0]; gb[0] += t * a[5]; }
-    { const T t = T(0.099322584599279881) * Pb[10]; ga[6] += t * b[3]; gb[3] += t * a[6]; }
-    { const T t = T(0.1332552305189782) * Pb[11]; ga[0] += t * b[6]; gb[6] += t * a[0]; }
-    { const T t = T(0.11752006695060019) * Pb[11]; ga[0] += t * b[8]; gb[8] += t * a[0]; }
-    { const T t = T(0.10257992428141011) * Pb[11]; ga[1] += t * b[5]; gb[5] += t * a[1]; }
-    { const T t = T(-0.067850242289111934) * Pb[11]; ga[1] += t * b[7]; gb[7] += t * a[1]; }
-    { const T t = T(0.025644981070352315) * Pb[11]; ga[2] += t * b[4]; gb[4] += t * a[2]; }
-    { const T t = T(-0.11468784191000718) * Pb[11]; ga[2] += t * b[6]; gb[6] += t * a[2]; }
-    { const T t = T(0.099322584599279895) * Pb[11]; ga[3] += t * b[3]; gb[3] += t * a[3]; }
-    { const T t = T(0.11468784191000722) * Pb[11]; ga[4] += t * b[2]; gb[2] += t * a[4]; }
-    { const T t = T(0.067850242289111934) * Pb[11]; ga[5] += t * b[1]; gb[1] += t * a[5]; }
-    { const T t = T(-0.10257992428141018) * Pb[11]; ga[5] += t * b[3]; gb[3] += t * a[5]; }
-    { const T t = T(-0.11752006695060027) * Pb[11]; ga[6] += t * b[0]; gb[0] += t * a[6]; }
-    { const T t = T(-0.13325523051897814) * Pb[11]; ga[6] += t * b[2]; gb[2] += t * a[6]; }
-    { const T t = T(-0.20355072686733566) * Pb[12]; ga[0] += t * b[1]; gb[1] += t * a[0]; }
-    { const T t = T(-0.044418410172992751) * Pb[12]; ga[1] += t * b[2]; gb[2] += t * a[1]; }
-    { const T t = T(0.099322584599279895) * Pb[12]; ga[2] += t * b[3]; gb[3] += t * a[2]; }
-    { const T t = T(0.15386988642211544) * Pb[12]; ga[3] += t * b[4]; gb[4] += t * a[3]; }
-    { const T t = T(0.099322584599279881) * Pb[12]; ga[4] += t * b[5]; gb[5] += t * a[4]; }
-    { const T t = T(-0.044418410172992549) * Pb[12]; ga[5] += t * b[6]; gb[6] += t * a[5]; }
-    { const T t = T(-0.20355072686733566) * Pb[12]; ga[6] += t * b[7]; gb[7] += t * a[6]; }
-    { const T t = T(-0.11752006695060027) * Pb[13]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.13325523051897814) * Pb[13]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(0.067850242289111906) * Pb[13]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(0.10257992428141011) * Pb[13]; ga[1] += t * b[3]; gb[3] += t * a[1]; }
-    { const T t = T(0.11468784191000722) * Pb[13]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(0.099322584599279881) * Pb[13]; ga[3] += t * b[5]; gb[5] += t * a[3]; }
-    { const T t = T(0.02564498107035235) * Pb[13]; ga[4] += t * b[4]; gb[4] += t * a[4]; }
-    { const T t = T(0.11468784191000721) * Pb[13]; ga[4] += t * b[6]; gb[6] += t * a[4]; }
-    { const T t = T(0.1025799242814102) * Pb[13]; ga[5] += t * b[5]; gb[5] += t * a[5]; }
-    { const T t = T(0.06785024228911192) * Pb[13]; ga[5] += t * b[7]; gb[7] += t * a[5]; }
-    { const T t = T(0.1332552305189782) * Pb[13]; ga[6] += t * b[6]; gb[6] += t * a[6]; }
-    { const T t = T(-0.11752006695060019) * Pb[13]; ga[6] += t * b[8]; gb[8] += t * a[6]; }
-    { const T t = T(-0.099322584599279853) * Pb[14]; ga[0] += t * b[3]; gb[3] += t * a[0]; }
-    { const T t = T(0.15171775404828494) * Pb[14]; ga[1] += t * b[0]; gb[0] += t * a[1]; }
-    { const T t = T(0.067850242289111948) * Pb[14]; ga[2] += t * b[1]; gb[1] += t * a[2]; }
-    { const T t = T(-0.10257992428141025) * Pb[14]; ga[2] += t * b[3]; gb[3] += t * a[2]; }
-    { const T t = T(-0.044418410172992549) * Pb[14]; ga[3] += t * b[6]; gb[6] += t * a[3]; }
-    { const T t = T(0.1025799242814102) * Pb[14]; ga[4] += t * b[5]; gb[5] += t * a[4]; }
-    { const T t = T(0.067850242289111962) * Pb[14]; ga[4] += t * b[7]; gb[7] += t * a[4]; }
-    { const T t = T(-0.17951486749246778) * Pb[14]; ga[5] += t * b[4]; gb[4] += t * a[5]; }
-    { const T t = T(0.151717754048285) * Pb[14]; ga[5] += t * b[8]; gb[8] += t * a[5]; }
-    { const T t = T(-0.099322584599279881) * Pb[14]; ga[6] += t * b[5]; gb[5] += t * a[6]; }
-    { const T t = T(0.099322584599279853) * Pb[15]; ga[1] += t * b[3]; gb[3] += t * a[1]; }
-    { const T t = T(-0.11752006695060024) * Pb[15]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(-0.13325523051897817) * Pb[15]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(-0.20355072686733561) * Pb[15]; ga[3] += t * b[7]; gb[7] += t * a[3]; }
-    { const T t = T(0.1332552305189782) * Pb[15]; ga[4] += t * b[6]; gb[6] += t * a[4]; }
-    { const T t = T(-0.11752006695060023) * Pb[15]; ga[4] += t * b[8]; gb[8] += t * a[4]; }
-    { const T t = T(-0.099322584599279881) * Pb[15]; ga[5] += t * b[5]; gb[5] += t * a[5]; }
-    { const T t = T(0.076934943211057705) * Pb[15]; ga[6] += t * b[4]; gb[4] += t * a[6]; }
-  }
-};
-template <> struct Couple<4, 4, 0> {
-  static constexpr int kMask = 16;
-  static constexpr int kTerms = 9;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[16] += T(0.28209479177387781) * (a[0] * b[0]);
-    P[17] += T(0.28209479177387808) * (a[1] * b[0]);
-    P[18] += T(0.2820947917738782) * (a[2] * b[0]);
-    P[19] += T(0.28209479177387786) * (a[3] * b[0]);
-    P[20] += T(0.28209479177387836) * (a[4] * b[0]);
-    P[21] += T(0.28209479177387781) * (a[5] * b[0]);
-    P[22] += T(0.2820947917738782) * (a[6] * b[0]);
-    P[23] += T(0.28209479177387808) * (a[7] * b[0]);
-    P[24] += T(0.28209479177387825) * (a[8] * b[0]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(0.28209479177387781) * Pb[16]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.28209479177387808) * Pb[17]; ga[1] += t * b[0]; gb[0] += t * a[1]; }
-    { const T t = T(0.2820947917738782) * Pb[18]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(0.28209479177387786) * Pb[19]; ga[3] += t * b[0]; gb[0] += t * a[3]; }
-    { const T t = T(0.28209479177387836) * Pb[20]; ga[4] += t * b[0]; gb[0] += t * a[4]; }
-    { const T t = T(0.28209479177387781) * Pb[21]; ga[5] += t * b[0]; gb[0] += t * a[5]; }
-    { const T t = T(0.2820947917738782) * Pb[22]; ga[6] += t * b[0]; gb[0] += t * a[6]; }
-    { const T t = T(0.28209479177387808) * Pb[23]; ga[7] += t * b[0]; gb[0] += t * a[7]; }
-    { const T t = T(0.28209479177387825) * Pb[24]; ga[8] += t * b[0]; gb[0] += t * a[8]; }
-  }
-};
-template <> struct Couple<4, 4, 1> {
-  static constexpr int kMask = 8;
-  static constexpr int kTerms = 31;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[9] += T(0.2303294329808902) * (a[0] * b[2]);
-    P[9] += T(0.16286750396763999) * (a[1] * b[1]);
-    P[9] += T(-0.043528171377568134) * (a[2] * b[2]);
-    P[9] += T(-0.043528171377568169) * (a[6] * b[0]);
-    P[9] += T(-0.23032943298089051) * (a[8] * b[0]);
-    P[10] += T(0.19947114020071635) * (a[1] * b[2]);
-    P[10] += T(0.21324361862292318) * (a[2] * b[1]);
-    P[10] += T(-0.075393004386513446) * (a[3] * b[2]);
-    P[10] += T(-0.075393004386513446) * (a[5] * b[0]);
-    P[10] += T(-0.19947114020071635) * (a[7] * b[0]);
-    P[11] += T(0.16858388283618392) * (a[2] * b[2]);
-    P[11] += T(0.23841361350444787) * (a[3] * b[1]);
-    P[11] += T(-0.150786008773027) * (a[4] * b[0]);
-    P[11] += T(-0.16858388283618395) * (a[6] * b[0]);
-    P[12] += T(0.19466390027300595) * (a[3] * b[0]);
-    P[12] += T(0.24623252122982925) * (a[4] * b[1]);
-    P[12] += T(0.19466390027300595) * (a[5] * b[2]);
-    P[13] += T(0.16858388283618392) * (a[2] * b[0]);
-    P[13] += T(-0.150786008773027) * (a[4] * b[2]);
-    P[13] += T(0.23841361350444781) * (a[5] * b[1]);
-    P[13] += T(0.16858388283618397) * (a[6] * b[2]);
-    P[14] += T(0.19947114020071624) * (a[1] * b[0]);
-    P[14] += T(0.075393004386513349) * (a[3] * b[0]);
-    P[14] += T(-0.075393004386513335) * (a[5] * b[2]);
-    P[14] += T(0.21324361862292313) * (a[6] * b[1]);
-    P[14] += T(0.19947114020071624) * (a[7] * b[2]);
-    P[15] += T(0.2303294329808902) * (a[0] * b[0]);
-    P[15] += T(0.043528171377568155) * (a[2] * b[0]);
-    P[15] += T(-0.043528171377568182) * (a[6] * b[2]);
-    P[15] += T(0.16286750396763999) * (a[7] * b[1]);
-    P[15] += T(0.23032943298089054) * (a[8] * b[2]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(0.2303294329808902) * Pb[9]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(0.16286750396763999) * Pb[9]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(-0.043528171377568134) * Pb[9]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(-0.043528171377568169) * Pb[9]; ga[6] += t * b[0]; gb[0] += t * a[6]; }
-    { const T t = T(-0.23032943298089051) * Pb[9]; ga[8] += t * b[0]; gb[0] += t * a[8]; }
-    { const T t = T(0.19947114020071635) * Pb[10]; ga[1] += t * b[2]; gb[2] += t * a[1]; }
-    { const T t = T(0.21324361862292318) * Pb[10]; ga[2] += t * b[1]; gb[1] += t * a[2]; }
-    { const T t = T(-0.075393004386513446) * Pb[10]; ga[3] += t * b[2]; gb[2] += t * a[3]; }
-    { const T t = T(-0.075393004386513446) * Pb[10]; ga[5] += t * b[0]; gb[0] += t * a[5]; }
-    { const T t = T(-0.19947114020071635) * Pb[10]; ga[7] += t * b[0]; gb[0] += t * a[7]; }
-    { const T t = T(0.16858388283618392) * Pb[11]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(0.23841361350444787) * Pb[11]; ga[3] += t * b[1]; gb[1] += t * a[3]; }
-    { const T t = T(-0.150786008773027) * Pb[11]; ga[4] += t * b[0]; gb[0] += t * a[4]; }
-    { const T t = T(-0.16858388283618395) * Pb[11]; ga[6] += t * b[0]; gb[0] += t * a[6]; }
-    { const T t = T(0.19466390027300595) * Pb[12]; ga[3] += t * b[0]; gb[0] += t * a[3]; }
-    { const T t = T(0.24623252122982925) * Pb[12]; ga[4] += t * b[1]; gb[1] += t * a[4]; }
-    { const T t = T(0.19466390027300595) * Pb[12]; ga[5] += t * b[2]; gb[2] += t * a[5]; }
-    { const T t = T(0.16858388283618392) * Pb[13]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(-0.150786008773027) * Pb[13]; ga[4] += t * b[2]; gb[2] += t * a[4]; }
-    { const T t = T(0.23841361350444781) * Pb[13]; ga[5] += t * b[1]; gb[1] += t * a[5]; }
-    { const T t = T(0.16858388283618397) * Pb[13]; ga[6] += t * b[2]; gb[2] += t * a[6]; }
-    { const T t = T(0.19947114020071624) * Pb[14]; ga[1] += t * b[0]; gb[0] += t * a[1]; }
-    { const T t = T(0.075393004386513349) * Pb[14]; ga[3] += t * b[0]; gb[0] += t * a[3]; }
-    { const T t = T(-0.075393004386513335) * Pb[14]; ga[5] += t * b[2]; gb[2] += t * a[5]; }
-    { const T t = T(0.21324361862292313) * Pb[14]; ga[6] += t * b[1]; gb[1] += t * a[6]; }
-    { const T t = T(0.19947114020071624) * Pb[14]; ga[7] += t * b[2]; gb[2] += t * a[7]; }
-    { const T t = T(0.2303294329808902) * Pb[15]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.043528171377568155) * Pb[15]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(-0.043528171377568182) * Pb[15]; ga[6] += t * b[2]; gb[2] += t * a[6]; }
-    { const T t = T(0.16286750396763999) * Pb[15]; ga[7] += t * b[1]; gb[1] += t * a[7]; }
-    { const T t = T(0.23032943298089054) * Pb[15]; ga[8] += t * b[2]; gb[2] += t * a[8]; }
-  }
-};
-template <> struct Couple<4, 4, 2> {
-  static constexpr int kMask = 20;
-  static constexpr int kTerms = 98;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[4] += T(0.23841361350444776) * (a[0] * b[4]);
-    P[4] += T(0.16858388283618389) * (a[1] * b[3]);
-    P[4] += T(0.15607834722743988) * (a[2] * b[2]);
-    P[4] += T(-0.063718718434027571) * (a[3] * b[3]);
-    P[4] += T(0.040299255967696811) * (a[4] * b[0]);
-    P[4] += T(-0.063718718434027571) * (a[5] * b[1]);
-    P[4] += T(-0.16858388283618389) * (a[7] * b[1]);
-    P[4] += T(-0.23841361350444829) * (a[8] * b[0]);
-    P[5] += T(0.16858388283618381) * (a[1] * b[4]);
-    P[5] += T(0.18022375157286866) * (a[2] * b[3]);
-    P[5] += T(0.22072811544182247) * (a[3] * b[2]);
-    P[5] += T(0.06371871843402746) * (a[3] * b[4]);
-    P[5] += T(-0.1611970238707878) * (a[4] * b[1]);
-    P[5] += T(-0.063718718434027558) * (a[5] * b[0]);
-    P[5] += T(-0.18022375157286874) * (a[6] * b[1]);
-    P[5] += T(-0.16858388283618389) * (a[7] * b[0]);
-    P[6] += T(0.15607834722743991) * (a[2] * b[0]);
-    P[6] += T(0.22072811544182239) * (a[3] * b[1]);
-    P[6] += T(0.24179553580618141) * (a[4] * b[2]);
-    P[6] += T(0.22072811544182239) * (a[5] * b[3]);
-    P[6] += T(0.15607834722743993) * (a[6] * b[4]);
-    P[7] += T(0.16858388283618389) * (a[1] * b[0]);
-    P[7] += T(0.18022375157286866) * (a[2] * b[1]);
-    P[7] += T(-0.063718718434027558) * (a[3] * b[0]);
-    P[7] += T(-0.16119702387078777) * (a[4] * b[3]);
-    P[7] += T(0.22072811544182241) * (a[5] * b[2]);
-    P[7] += T(-0.06371871843402746) * (a[5] * b[4]);
-    P[7] += T(0.18022375157286868) * (a[6] * b[3]);
-    P[7] += T(0.16858388283618381) * (a[7] * b[4]);
-    P[8] += T(0.23841361350444776) * (a[0] * b[0]);
-    P[8] += T(0.16858388283618381) * (a[1] * b[1]);
-    P[8] += T(0.063718718434027433) * (a[3] * b[1]);
-    P[8] += T(0.040299255967696908) * (a[4] * b[4]);
-    P[8] += T(-0.063718718434027447) * (a[5] * b[3]);
-    P[8] += T(0.15607834722743988) * (a[6] * b[2]);
-    P[8] += T(0.16858388283618381) * (a[7] * b[3]);
-    P[8] += T(0.23841361350444812) * (a[8] * b[4]);
-    P[16] += T(-0.22937568382001464) * (a[0] * b[2]);
-    P[16] += T(0.14046334619025069) * (a[1] * b[3]);
-    P[16] += T(-0.075080816691962482) * (a[2] * b[4]);
-    P[16] += T(-0.075080816691962482) * (a[6] * b[0]);
-    P[16] += T(0.14046334619025069) * (a[7] * b[1]);
-    P[17] += T(0.14046334619025072) * (a[0] * b[3]);
-    P[17] += T(-0.057343920955003555) * (a[1] * b[2]);
-    P[17] += T(0.13272538654977706) * (a[2] * b[3]);
-    P[17] += T(-0.11262122503794364) * (a[3] * b[4]);
-    P[17] += T(-0.11262122503794367) * (a[5] * b[0]);
-    P[17] += T(0.13272538654977695) * (a[6] * b[1]);
-    P[17] += T(-0.1404633461902508) * (a[8] * b[1]);
-    P[18] += T(-0.075080816691962496) * (a[0] * b[4]);
-    P[18] += T(0.132725386549777) * (a[1] * b[3]);
-    P[18] += T(0.06553590966286113) * (a[2] * b[2]);
-    P[18] += T(0.090297865408018235) * (a[3] * b[3]);
-    P[18] += T(-0.19036461502711174) * (a[4] * b[0]);
-    P[18] += T(0.090297865408018235) * (a[5] * b[1]);
-    P[18] += T(-0.132725386549777) * (a[7] * b[1]);
-    P[18] += T(0.075080816691962302) * (a[8] * b[0]);
-    P[19] += T(-0.11262122503794361) * (a[1] * b[4]);
-    P[19] += T(0.090297865408018194) * (a[2] * b[3]);
-    P[19] += T(0.13926380803358024) * (a[3] * b[2]);
-    P[19] += T(-0.14188940657039986) * (a[3] * b[4]);
-    P[19] += T(0.044869370061212506) * (a[4] * b[1]);
-    P[19] += T(0.14188940657039981) * (a[5] * b[0]);
-    P[19] += T(-0.090297865408018402) * (a[6] * b[1]);
-    P[19] += T(0.11262122503794365) * (a[7] * b[0]);
-    P[20] += T(-0.19036461502711174) * (a[2] * b[0]);
-    P[20] += T(0.044869370061212464) * (a[3] * b[1]);
-    P[20] += T(0.16383977415715348) * (a[4] * b[2]);
-    P[20] += T(0.044869370061212464) * (a[5] * b[3]);
-    P[20] += T(-0.19036461502711177) * (a[6] * b[4]);
-    P[21] += T(-0.11262122503794367) * (a[1] * b[0]);
-    P[21] += T(0.090297865408018194) * (a[2] * b[1]);
-    P[21] += T(0.14188940657039981) * (a[3] * b[0]);
-    P[21] += T(0.044869370061212478) * (a[4] * b[3]);
-    P[21] += T(0.13926380803358016) * (a[5] * b[2]);
-    P[21] += T(0.14188940657039986) * (a[5] * b[4]);
-    P[21] += T(0.090297865408018402) * (a[6] * b[3]);
-    P[21] += T(-0.11262122503794363) * (a[7] * b[4]);
-    P[22] += T(-0.075080816691962496) * (a[0] * b[0]);
-    P[22] += T(0.13272538654977695) * (a[1] * b[1]);
-    P[22] += T(-0.09029786540801843) * (a[3] * b[1]);
-    P[22] += T(-0.19036461502711183) * (a[4] * b[4]);
-    P[22] += T(0.090297865408018416) * (a[5] * b[3]);
-    P[22] += T(0.065535909662861283) * (a[6] * b[2]);
-    P[22] += T(0.13272538654977692) * (a[7] * b[3]);
-    P[22] += T(-0.075080816691962482) * (a[8] * b[4]);
-    P[23] += T(0.14046334619025072) * (a[0] * b[1]);
-    P[23] += T(-0.13272538654977706) * (a[2] * b[1]);
-    P[23] += T(0.11262122503794368) * (a[3] * b[0]);
-    P[23] += T(-0.11262122503794365) * (a[5] * b[4]);
-    P[23] += T(0.13272538654977692) * (a[6] * b[3]);
-    P[23] += T(-0.057343920955003555) * (a[7] * b[2]);
-    P[23] += T(0.1404633461902508) * (a[8] * b[3]);
-    P[24] += T(-0.14046334619025078) * (a[1] * b[1]);
-    P[24] += T(0.075080816691962357) * (a[2] * b[0]);
-    P[24] += T(-0.075080816691962468) * (a[6] * b[4]);
-    P[24] += T(0.14046334619025078) * (a[7] * b[3]);
-    P[24] += T(-0.22937568382001453) * (a[8] * b[2]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(0.23841361350444776) * Pb[4]; ga[0] += t * b[4]; gb[4] += t * a[0]; }
-    { const T t = T(0.16858388283618389) * Pb[4]; ga[1] += t * b[3]; gb[3] += t * a[1]; }
-    { const T t = T(0.15607834722743988) * Pb[4]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(-0.063718718434027571) * Pb[4]; ga[3] += t * b[3]; gb[3] += t * a[3]; }
-    { const T t = T(0.040299255967696811) * Pb[4]; ga[4] += t * b[0]; gb[0] += t * a[4]; }
-    { const T t = T(-0.063718718434027571) * Pb[4]; ga[5] += t * b[1]; gb[1] += t * a[5]; }
-    { const T t = T(-0.16858388283618389) * Pb[4]; ga[7] += t * b[1]; gb[1] += t * a[7]; }
-    { const T t = T(-0.23841361350444829) * Pb[4]; ga[8] += t * b[0]; gb[0] += t * a[8]; }
-    { const T t = T(0.16858388283618381) * Pb[5]; ga[1] += t * b[4]; gb[4] += t * a[1]; }
-    { const T t = T(0.18022375157286866) * Pb[5]; ga[2] += t * b[3]; gb[3] += t * a[2]; }
-    { const T t = T(0.22072811544182247) * Pb[5]; ga[3] += t * b[2]; gb[2] += t * a[3]; }
-    { const T t = T(0.06371871843402746) * Pb[5]; ga[3] += t * b[4]; gb[4] += t * a[3]; }
-    { const T t = T(-0.1611970238707878) * Pb[5]; ga[4] += t * b[1]; gb[1] += t * a[4]; }
-    { const T t = T(-0.063718718434027558) * Pb[5]; ga[5] += t * b[0]; gb[0] += t * a[5]; }
-    { const T t = T(-0.18022375157286874) * Pb[5]; ga[6] += t * b[1]; gb[1] += t * a[6]; }
-    { const T t = T(-0.16858388283618389) * Pb[5]; ga[7] += t * b[0]; gb[0] += t * a[7]; }
-    { const T t = T(0.15607834722743991) * Pb[6]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(0.22072811544182239) * Pb[6]; ga[3] += t * b[1]; gb[1] += t * a[3]; }
-    { const T t = T(0.24179553580618141) * Pb[6]; ga[4] += t * b[2]; gb[2] += t * a[4]; }
-    { const T t = T(0.22072811544182239) * Pb[6]; ga[5] += t * b[3]; gb[3] += t * a[5]; }
-    { const T t = T(0.15607834722743993) * Pb[6]; ga[6] += t * b[4]; gb[4] += t * a[6]; }
-    { const T t = T(0.16858388283618389) * Pb[7]; ga[1] += t * b[0]; gb[0] += t * a[1]; }
-    { const T t = T(0.18022375157286866) * Pb[7]; ga[2] += t * b[1]; gb[1] += t * a[2]; }
-    { const T t = T(-0.063718718434027558) * Pb[7]; ga[3] += t * b[0]; gb[0] += t * a[3]; }
-    { const T t = T(-0.16119702387078777) * Pb[7]; ga[4] += t * b[3]; gb[3] += t * a[4]; }
-    { const T t = T(0.22072811544182241) * Pb[7]; ga[5] += t * b[2]; gb[2] += t * a[5]; }
-    { const T t = T(-0.06371871843402746) * Pb[7]; ga[5] += t * b[4]; gb[4] += t * a[5]; }
-    { const T t = T(0.18022375157286868) * Pb[7]; ga[6] += t * b[3]; gb[3] += t * a[6]; }
-    { const T t = T(0.16858388283618381) * Pb[7]; ga[7] += t * b[4]; gb[4] += t * a[7]; }
-    { const T t = T(0.23841361350444776) * Pb[8]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.16858388283618381) * Pb[8]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(0.063718718434027433) * Pb[8]; ga[3] += t * b[1]; gb[1] += t * a[3]; }
-    { const T t = T(0.040299255967696908) * Pb[8]; ga[4] += t * b[4]; gb[4] += t * a[4]; }
-    { const T t = T(-0.063718718434027447) * Pb[8]; ga[5] += t * b[3]; gb[3] += t * a[5]; }
-    { const T t = T(0.15607834722743988) * Pb[8]; ga[6] += t * b[2]; gb[2] += t * a[6]; }
-    { const T t = T(0.16858388283618381) * Pb[8]; ga[7] += t * b[3]; gb[3] += t * a[7]; }
-    { const T t = T(0.23841361350444812) * Pb[8]; ga[8] += t * b[4]; gb[4] += t * a[8]; }
-    { const T t = T(-0.22937568382001464) * Pb[16]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(0.14046334619025069) * Pb[16]; ga[1] += t * b[3]; gb[3] += t * a[1]; }
-    { const T t = T(-0.075080816691962482) * Pb[16]; ga[2] += t * b[4]; gb[4] += t * a[2]; }
-    { const T t = T(-0.075080816691962482) * Pb[16]; ga[6] += t * b[0]; gb[0] += t * a[6]; }
-    { const T t = T(0.14046334619025069) * Pb[16]; ga[7] += t * b[1]; gb[1] += t * a[7]; }
-    { const T t = T(0.14046334619025072) * Pb[17]; ga[0] += t * b[3]; gb[3] += t * a[0]; }
-    { const T t = T(-0.057343920955003555) * Pb[17]; ga[1] += t * b[2]; gb[2] += t * a[1]; }
-    { const T t = T(0.13272538654977706) * Pb[17]; ga[2] += t * b[3]; gb[3] += t * a[2]; }
-    { const T t = T(-0.11262122503794364) * Pb[17]; ga[3] += t * b[4]; gb[4] += t * a[3]; }
-    { const T t = T(-0.11262122503794367) * Pb[17]; ga[5] += t * b[0]; gb[0] += t * a[5]; }
-    { const T t = T(0.13272538654977695) * Pb[17]; ga[6] += t * b[1]; gb[1] += t * a[6]; }
-    { const T t = T(-0.1404633461902508) * Pb[17]; ga[8] += t * b[1]; gb[1] += t * a[8]; }
-    { const T t = T(-0.075080816691962496) * Pb[18]; ga[0] += t * b[4]; gb[4] += t * a[0]; }
-    { const T t = T(0.132725386549777) * Pb[18]; ga[1] += t * b[3]; gb[3] += t * a[1]; }
-    { const T t = T(0.06553590966286113) * Pb[18]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(0.090297865408018235) * Pb[18]; ga[3] += t * b[3]; gb[3] += t * a[3]; }
-    { const T t = T(-0.19036461502711174) * Pb[18]; ga[4] += t * b[0]; gb[0] += t * a[4]; }
-    { const T t = T(0.090297865408018235) * Pb[18]; ga[5] += t * b[1]; gb[1] += t * a[5]; }
-    { const T t = T(-0.132725386549777) * Pb[18]; ga[7] += t * b[1]; gb[1] += t * a[7]; }
-    { const T t = T(0.075080816691962302) * Pb[18]; ga[8] += t * b[0]; gb[0] += t * a[8]; }
-    { const T t = T(-0.11262122503794361) * Pb[19]; ga[1] += t * b[4]; gb[4] += t * a[1]; }
-    { const T t = T(0.090297865408018194) * Pb[19]; ga[2] += t * b[3]; gb[3] += t * a[2]; }
-    { const T t = T(0.13926380803358024) * Pb[19]; ga[3] += t * b[2]; gb[2] += t * a[3]; }
-    { const T t = T(-0.14188940657039986) * Pb[19]; ga[3] += t * b[4]; gb[4] += t * a[3]; }
-    { const T t = T(0.044869370061212506) * Pb[19]; ga[4] += t * b[1]; gb[1] += t * a[4]; }
-    { const T t = T(0.14188940657039981) * Pb[19]; ga[5] += t * b[0]; gb[0] += t * a[5]; }
-    { const T t = T(-0.090297865408018402) * Pb[19]; ga[6] += t * b[1]; gb[1] += t * a[6]; }
-    { const T t = T(0.11262122503794365) * Pb[19]; ga[7] += t * b[0]; gb[0] += t * a[7]; }
-    { const T t = T(-0.19036461502711174) * Pb[20]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(0.044869370061212464) * Pb[20]; ga[3] += t * b[1]; gb[1] += t * a[3]; }
-    { const T t = T(0.16383977415715348) * Pb[20]; ga[4] += t * b[2]; gb[2] += t * a[4]; }
-    { const T t = T(0.044869370061212464) * Pb[20]; ga[5] += t * b[3]; gb[3] += t * a[5]; }
-    { const T t = T(-0.19036461502711177) * Pb[20]; ga[6] += t * b[4]; gb[4] += t * a[6]; }
-    { const T t = T(-0.11262122503794367) * Pb[21]; ga[1] += t * b[0]; gb[0] += t * a[1]; }
-    { const T t = T(0.090297865408018194) * Pb[21]; ga[2] += t * b[1]; gb[1] += t * a[2]; }
-    { const T t = T(0.14188940657039981) * Pb[21]; ga[3] += t * b[0]; gb[0] += t * a[3]; }
-    { const T t = T(0.044869370061212478) * Pb[21]; ga[4] += t * b[3]; gb[3] += t * a[4]; }
-    { const T t = T(0.13926380803358016) * Pb[21]; ga[5] += t * b[2]; gb[2] += t * a[5]; }
-    { const T t = T(0.14188940657039986) * Pb[21]; ga[5] += t * b[4]; gb[4] += t * a[5]; }
-    { const T t = T(0.090297865408018402) * Pb[21]; ga[6] += t * b[3]; gb[3] += t * a[6]; }
-    { const T t = T(-0.11262122503794363) * Pb[21]; ga[7] += t * b[4]; gb[4] += t * a[7]; }
-    { const T t = T(-0.075080816691962496) * Pb[22]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.13272538654977695) * Pb[22]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(-0.09029786540801843) * Pb[22]; ga[3] += t * b[1]; gb[1] += t * a[3]; }
-    { const T t = T(-0.19036461502711183) * Pb[22]; ga[4] += t * b[4]; gb[4] += t * a[4]; }
-    { const T t = T(0.090297865408018416) * Pb[22]; ga[5] += t * b[3]; gb[3] += t * a[5]; }
-    { const T t = T(0.065535909662861283) * Pb[22]; ga[6] += t * b[2]; gb[2] += t * a[6]; }
-    { const T t = T(0.13272538654977692) * Pb[22]; ga[7] += t * b[3]; gb[3] += t * a[7]; }
-    { const T t = T(-0.075080816691962482) * Pb[22]; ga[8] += t * b[4]; gb[4] += t * a[8]; }
-    { const T t = T(0.14046334619025072) * Pb[23]; ga[0] += t * b[1]; gb[1] += t * a[0]; }
-    { const T t = T(-0.13272538654977706) * Pb[23]; ga[2] += t * b[1]; gb[1] += t * a[2]; }
-    { const T t = T(0.11262122503794368) * Pb[23]; ga[3] += t * b[0]; gb[0] += t * a[3]; }
-    { const T t = T(-0.11262122503794365) * Pb[23]; ga[5] += t * b[4]; gb[4] += t * a[5]; }
-    { const T t = T(0.13272538654977692) * Pb[23]; ga[6] += t * b[3]; gb[3] += t * a[6]; }
-    { const T t = T(-0.057343920955003555) * Pb[23]; ga[7] += t * b[2]; gb[2] += t * a[7]; }
-    { const T t = T(0.1404633461902508) * Pb[23]; ga[8] += t * b[3]; gb[3] += t * a[8]; }
-    { const T t = T(-0.14046334619025078) * Pb[24]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(0.075080816691962357) * Pb[24]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(-0.075080816691962468) * Pb[24]; ga[6] += t * b[4]; gb[4] += t * a[6]; }
-    { const T t = T(0.14046334619025078) * Pb[24]; ga[7] += t * b[3]; gb[3] += t * a[7]; }
-    { const T t = T(-0.22937568382001453) * Pb[24]; ga[8] += t * b[2]; gb[2] += t * a[8]; }
-  }
-};
-template <> struct Couple<4, 4, 3> {
-  static constexpr int kMask = 10;
-  static constexpr int kTerms = 98;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[1] += T(0.23032943298089015) * (a[0] * b[6]);
-    P[1] += T(0.19947114020071621) * (a[1] * b[5]);
-    P[1] += T(0.16858388283618389) * (a[2] * b[4]);
-    P[1] += T(0.043528171377568148) * (a[2] * b[6]);
-    P[1] += T(0.19466390027300592) * (a[3] * b[3]);
-    P[1] += T(0.075393004386513335) * (a[3] * b[5]);
-    P[1] += T(-0.15078600877302697) * (a[4] * b[2]);
-    P[1] += T(-0.075393004386513432) * (a[5] * b[1]);
-    P[1] += T(-0.043528171377568162) * (a[6] * b[0]);
-    P[1] += T(-0.16858388283618392) * (a[6] * b[2]);
-    P[1] += T(-0.1994711402007163) * (a[7] * b[1]);
-    P[1] += T(-0.23032943298089045) * (a[8] * b[0]);
-    P[2] += T(0.16286750396763996) * (a[1] * b[0]);
-    P[2] += T(0.21324361862292315) * (a[2] * b[1]);
-    P[2] += T(0.23841361350444784) * (a[3] * b[2]);
-    P[2] += T(0.24623252122982922) * (a[4] * b[3]);
-    P[2] += T(0.23841361350444776) * (a[5] * b[4]);
-    P[2] += T(0.2132436186229231) * (a[6] * b[5]);
-    P[2] += T(0.16286750396763996) * (a[7] * b[6]);
-    P[3] += T(0.23032943298089015) * (a[0] * b[0]);
-    P[3] += T(0.1994711402007163) * (a[1] * b[1]);
-    P[3] += T(-0.043528171377568127) * (a[2] * b[0]);
-    P[3] += T(0.16858388283618389) * (a[2] * b[2]);
-    P[3] += T(-0.075393004386513432) * (a[3] * b[1]);
-    P[3] += T(-0.15078600877302697) * (a[4] * b[4]);
-    P[3] += T(0.19466390027300592) * (a[5] * b[3]);
-    P[3] += T(-0.075393004386513321) * (a[5] * b[5]);
-    P[3] += T(0.16858388283618395) * (a[6] * b[4]);
-    P[3] += T(-0.043528171377568176) * (a[6] * b[6]);
-    P[3] += T(0.19947114020071621) * (a[7] * b[5]);
-    P[3] += T(0.23032943298089048) * (a[8] * b[6]);
-    P[9] += T(-0.11752006695060026) * (a[0] * b[4]);
-    P[9] += T(-0.20355072686733561) * (a[1] * b[3]);
-    P[9] += T(0.13325523051897814) * (a[2] * b[4]);
-    P[9] += T(-0.099322584599279881) * (a[3] * b[5]);
-    P[9] += T(0.076934943211057677) * (a[4] * b[0]);
-    P[9] += T(-0.099322584599279867) * (a[5] * b[1]);
-    P[9] += T(0.13325523051897822) * (a[6] * b[2]);
-    P[9] += T(0.11752006695060023) * (a[8] * b[2]);
-    P[10] += T(0.15171775404828494) * (a[0] * b[5]);
-    P[10] += T(0.067850242289111906) * (a[1] * b[4]);
-    P[10] += T(-0.044418410172992751) * (a[2] * b[3]);
-    P[10] += T(0.10257992428141011) * (a[3] * b[4]);
-    P[10] += T(0.099322584599279881) * (a[3] * b[6]);
-    P[10] += T(-0.17951486749246792) * (a[4] * b[1]);
-    P[10] += T(-0.099322584599279881) * (a[5] * b[0]);
-    P[10] += T(0.10257992428141011) * (a[5] * b[2]);
-    P[10] += T(-0.067850242289111934) * (a[7] * b[2]);
-    P[10] += T(-0.15171775404828525) * (a[8] * b[1]);
-    P[11] += T(-0.11752006695060027) * (a[0] * b[6]);
-    P[11] += T(0.067850242289111934) * (a[1] * b[5]);
-    P[11] += T(0.11468784191000722) * (a[2] * b[4]);
-    P[11] += T(-0.13325523051897814) * (a[2] * b[6]);
-    P[11] += T(0.099322584599279895) * (a[3] * b[3]);
-    P[11] += T(-0.10257992428141019) * (a[3] * b[5]);
-    P[11] += T(0.025644981070352315) * (a[4] * b[2]);
-    P[11] += T(0.10257992428141011) * (a[5] * b[1]);
-    P[11] += T(0.1332552305189782) * (a[6] * b[0]);
-    P[11] += T(-0.11468784191000718) * (a[6] * b[2]);
-    P[11] += T(-0.067850242289111934) * (a[7] * b[1]);
-    P[11] += T(0.11752006695060019) * (a[8] * b[0]);
-    P[12] += T(-0.20355072686733566) * (a[1] * b[0]);
-    P[12] += T(-0.044418410172992751) * (a[2] * b[1]);
-    P[12] += T(0.099322584599279895) * (a[3] * b[2]);
-    P[12] += T(0.15386988642211544) * (a[4] * b[3]);
-    P[12] += T(0.099322584599279881) * (a[5] * b[4]);
-    P[12] += T(-0.044418410172992549) * (a[6] * b[5]);
-    P[12] += T(-0.20355072686733566) * (a[7] * b[6]);
-    P[13] += T(-0.11752006695060027) * (a[0] * b[0]);
-    P[13] += T(0.067850242289111906) * (a[1] * b[1]);
-    P[13] += T(0.13325523051897814) * (a[2] * b[0]);
-    P[13] += T(0.11468784191000722) * (a[2] * b[2]);
-    P[13] += T(0.10257992428141011) * (a[3] * b[1]);
-    P[13] += T(0.02564498107035235) * (a[4] * b[4]);
-    P[13] += T(0.099322584599279881) * (a[5] * b[3]);
-    P[13] += T(0.10257992428141015) * (a[5] * b[5]);
-    P[13] += T(0.11468784191000721) * (a[6] * b[4]);
-    P[13] += T(0.1332552305189782) * (a[6] * b[6]);
-    P[13] += T(0.06785024228911192) * (a[7] * b[5]);
-    P[13] += T(-0.11752006695060019) * (a[8] * b[6]);
-    P[14] += T(0.15171775404828494) * (a[0] * b[1]);
-    P[14] += T(0.067850242289111948) * (a[1] * b[2]);
-    P[14] += T(-0.099322584599279853) * (a[3] * b[0]);
-    P[14] += T(-0.10257992428141025) * (a[3] * b[2]);
-    P[14] += T(-0.17951486749246778) * (a[4] * b[5]);
-    P[14] += T(0.1025799242814102) * (a[5] * b[4]);
-    P[14] += T(-0.099322584599279881) * (a[5] * b[6]);
-    P[14] += T(-0.044418410172992549) * (a[6] * b[3]);
-    P[14] += T(0.067850242289111934) * (a[7] * b[4]);
-    P[14] += T(0.151717754048285) * (a[8] * b[5]);
-    P[15] += T(-0.11752006695060024) * (a[0] * b[2]);
-    P[15] += T(-0.13325523051897817) * (a[2] * b[2]);
-    P[15] += T(0.099322584599279853) * (a[3] * b[1]);
-    P[15] += T(0.076934943211057691) * (a[4] * b[6]);
-    P[15] += T(-0.099322584599279881) * (a[5] * b[5]);
-    P[15] += T(0.13325523051897822) * (a[6] * b[4]);
-    P[15] += T(-0.20355072686733561) * (a[7] * b[3]);
-    P[15] += T(-0.11752006695060019) * (a[8] * b[4]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(0.23032943298089015) * Pb[1]; ga[0] += t * b[6]; gb[6] += t * a[0]; }
-    { const T t = T(0.19947114020071621) * Pb[1]; ga[1] += t * b[5]; gb[5] += t * a[1]; }
-    { const T t = T(0.16858388283618389) * Pb[1]; ga[2] += t * b[4]; gb[4] += t * a[2]; }
-    { const T t = T(0.043528171377568148) * Pb[1]; ga[2] += t * b[6]; gb[6] += t * a[2]; }
-    { const T t = T(0.19466390027300592) * Pb[1]; ga[3] += t * b[3]; gb[3] += t * a[3]; }
-    { const T t = T(0.075393004386513335) * Pb[1]; ga[3] += t * b[5]; gb[5] += t * a[3]; }
-    { const T t = T(-0.15078600877302697) * Pb[1]; ga[4] += t * b[2]; gb[2] += t * a[4]; }
-    { const T t = T(-0.075393004386513432) * Pb[1]; ga[5] += t * b[1]; gb[1] += t * a[5]; }
-    { const T t = T(-0.043528171377568162) * Pb[1]; ga[6] += t * b[0]; gb[0] += t * a[6]; }
-    { const T t = T(-0.16858388283618392) * Pb[1]; ga[6] += t * b[2]; gb[2] += t * a[6]; }
-    { const T t = T(-0.1994711402007163) * Pb[1]; ga[7] += t * b[1]; gb[1] += t * a[7]; }
-    { const T t = T(-0.23032943298089045) * Pb[1]; ga[8] += t * b[0]; gb[0] += t * a[8]; }
-    { const T t = T(0.16286750396763996) * Pb[2]; ga[1] += t * b[0]; gb[0] += t * a[1]; }
-    { const T t = T(0.21324361862292315) * Pb[2]; ga[2] += t * b[1]; gb[1] += t * a[2]; }
-    { const T t = T(0.23841361350444784) * Pb[2]; ga[3] += t * b[2]; gb[2] += t * a[3]; }
-    { const T t = T(0.24623252122982922) * Pb[2]; ga[4] += t * b[3]; gb[3] += t * a[4]; }
-    { const T t = T(0.23841361350444776) * Pb[2]; ga[5] += t * b[4]; gb[4] += t * a[5]; }
-    { const T t = T(0.2132436186229231) * Pb[2]; ga[6] += t * b[5]; gb[5] += t * a[6]; }
-    { const T t = T(0.16286750396763996) * Pb[2]; ga[7] += t * b[6]; gb[6] += t * a[7]; }
-    { const T t = T(0.23032943298089015) * Pb[3]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.1994711402007163) * Pb[3]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(-0.043528171377568127) * Pb[3]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(0.16858388283618389) * Pb[3]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(-0.075393004386513432) * Pb[3]; ga[3] += t * b[1]; gb[1] += t * a[3]; }
-    { const T t = T(-0.15078600877302697) * Pb[3]; ga[4] += t * b[4]; gb[4] += t * a[4]; }
-    { const T t = T(0.19466390027300592) * Pb[3]; ga[5] += t * b[3]; gb[3] += t * a[5]; }
-    { const T t = T(-0.075393004386513321) * Pb[3]; ga[5] += t * b[5]; gb[5] += t * a[5]; }
-    { const T t = T(0.16858388283618395) * Pb[3]; ga[6] += t * b[4]; gb[4] += t * a[6]; }
-    { const T t = T(-0.043528171377568176) * Pb[3]; ga[6] += t * b[6]; gb[6] += t * a[6]; }
-    { const T t = T(0.19947114020071621) * Pb[3]; ga[7] += t * b[5]; gb[5] += t * a[7]; }
-    { const T t = T(0.23032943298089048) * Pb[3]; ga[8] += t * b[6]; gb[6] += t * a[8]; }
-    { const T t = T(-0.11752006695060026) * Pb[9]; ga[0] += t * b[4]; gb[4] += t * a[0]; }
-    { const T t = T(-0.20355072686733561) * Pb[9]; ga[1] += t * b[3]; gb[3] += t * a[1]; }
-    { const T t = T(0.13325523051897814) * Pb[9]; ga[2] += t * b[4]; gb[4] += t * a[2]; }
-    { const T t = T(-0.099322584599279881) * Pb[9]; ga[3] += t * b[5]; gb[5] += t * a[3]; }
-    { const T t = T(0.076934943211057677) * Pb[9]; ga[4] += t * b[0]; gb[0] += t * a[4]; }
-    { const T t = T(-0.099322584599279867) * Pb[9]; ga[5] += t * b[1]; gb[1] += t * a[5]; }
-    { const T t = T(0.13325523051897822) * Pb[9]; ga[6] += t * b[2]; gb[2] += t * a[6]; }
-    { const T t = T(0.11752006695060023) * Pb[9]; ga[8] += t * b[2]; gb[2] += t * a[8]; }
-    { const T t = T(0.15171775404828494) * Pb[10]; ga[0] += t * b[5]; gb[5] += t * a[0]; }
-    { const T t = T(0.067850242289111906) * Pb[10]; ga[1] += t * b[4]; gb[4] += t * a[1]; }
-    { const T t = T(-0.044418410172992751) * Pb[10]; ga[2] += t * b[3]; gb[3] += t * a[2]; }
-    { const T t = T(0.10257992428141011) * Pb[10]; ga[3] += t * b[4]; gb[4] += t * a[3]; }
-    { const T t = T(0.099322584599279881) * Pb[10]; ga[3] += t * b[6]; gb[6] += t * a[3]; }
-    { const T t = T(-0.17951486749246792) * Pb[10]; ga[4] += t * b[1]; gb[1] += t * a[4]; }
-    { const T t = T(-0.099322584599279881) * Pb[10]; ga[5] += t * b[0]; gb[0] += t * a[5]; }
-    { const T t = T(0.10257992428141011) * Pb[10]; ga[5] += t * b[2]; gb[2] += t * a[5]; }
-    { const T t = T(-0.067850242289111934) * Pb[10]; ga[7] += t * b[2]; gb[2] += t * a[7]; }
-    { const T t = T(-0.15171775404828525) * Pb[10]; ga[8] += t * b[1]; gb[1] += t * a[8]; }
-    { const T t = T(-0.11752006695060027) * Pb[11]; ga[0] += t * b[6]; gb[6] += t * a[0]; }
-    { const T t = T(0.067850242289111934) * Pb[11]; ga[1] += t * b[5]; gb[5] += t * a[1]; }
-    { const T t = T(0.11468784191000722) * Pb[11]; ga[2] += t * b[4]; gb[4] += t * a[2]; }
-    { const T t = T(-0.13325523051897814) * Pb[11]; ga[2] += t * b[6]; gb[6] += t * a[2]; }
-    { const T t = T(0.099322584599279895) * Pb[11]; ga[3] += t * b[3]; gb[3] += t * a[3]; }
-    { const T t = T(-0.10257992428141019) * Pb[11]; ga[3] += t * b[5]; gb[5] += t * a[3]; }
-    { const T t = T(0.025644981070352315) * Pb[11]; ga[4] += t * b[2]; gb[2] += t * a[4]; }
-    { const T t = T(0.10257992428141011) * Pb[11]; ga[5] += t * b[1]; gb[1] += t * a[5]; }
-    { const T t = T(0.1332552305189782) * Pb[11]; ga[6] += t * b[0]; gb[0] += t * a[6]; }
-    { const T t = T(-0.11468784191000718) * Pb[11]; ga[6] += t * b[2]; gb[2] += t * a[6]; }
-    { const T t = T(-0.067850242289111934) * Pb[11]; ga[7] += t * b[1]; gb[1] += t * a[7]; }
-    { const T t = T(0.11752006695060019) * Pb[11]; ga[8] += t * b[0]; gb[0] += t * a[8]; }
-    { const T t = T(-0.20355072686733566) * Pb[12]; ga[1] += t * b[0]; gb[0] += t * a[1]; }
-    { const T t = T(-0.044418410172992751) * Pb[12]; ga[2] += t * b[1]; gb[1] += t * a[2]; }
-    { const T t = T(0.099322584599279895) * Pb[12]; ga[3] += t * b[2]; gb[2] += t * a[3]; }
-    { const T t = T(0.15386988642211544) * Pb[12]; ga[4] += t * b[3]; gb[3] += t * a[4]; }
-    { const T t = T(0.099322584599279881) * Pb[12]; ga[5] += t * b[4]; gb[4] += t * a[5]; }
-    { const T t = T(-0.044418410172992549) * Pb[12]; ga[6] += t * b[5]; gb[5] += t * a[6]; }
-    { const T t = T(-0.20355072686733566) * Pb[12]; ga[7] += t * b[6]; gb[6] += t * a[7]; }
-    { const T t = T(-0.11752006695060027) * Pb[13]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.067850242289111906) * Pb[13]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(0.13325523051897814) * Pb[13]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(0.11468784191000722) * Pb[13]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(0.10257992428141011) * Pb[13]; ga[3] += t * b[1]; gb[1] += t * a[3]; }
-    { const T t = T(0.02564498107035235) * Pb[13]; ga[4] += t * b[4]; gb[4] += t * a[4]; }
-    { const T t = T(0.099322584599279881) * Pb[13]; ga[5] += t * b[3]; gb[3] += t * a[5]; }
-    { const T t = T(0.10257992428141015) * Pb[13]; ga[5] += t * b[5]; gb[5] += t * a[5]; }
-    { const T t = T(0.11468784191000721) * Pb[13]; ga[6] += t * b[4]; gb[4] += t * a[6]; }
-    { const T t = T(0.1332552305189782) * Pb[13]; ga[6] += t * b[6]; gb[6] += t * a[6]; }
-    { const T t = T(0.06785024228911192) * Pb[13]; ga[7] += t * b[5]; gb[5] += t * a[7]; }
-    { const T t = T(-0.11752006695060019) * Pb[13]; ga[8] += t * b[6]; gb[6] += t * a[8]; }
-    { const T t = T(0.15171775404828494) * Pb[14]; ga[0] += t * b[1]; gb[1] += t * a[0]; }
-    { const T t = T(0.067850242289111948) * Pb[14]; ga[1] += t * b[2]; gb[2] += t * a[1]; }
-    { const T t = T(-0.099322584599279853) * Pb[14]; ga[3] += t * b[0]; gb[0] += t * a[3]; }
-    { const T t = T(-0.10257992428141025) * Pb[14]; ga[3] += t * b[2]; gb[2] += t * a[3]; }
-    { const T t = T(-0.17951486749246778) * Pb[14]; ga[4] += t * b[5]; gb[5] += t * a[4]; }
-    { const T t = T(0.1025799242814102) * Pb[14]; ga[5] += t * b[4]; gb[4] += t * a[5]; }
-    { const T t = T(-0.099322584599279881) * Pb[14]; ga[5] += t * b[6]; gb[6] += t * a[5]; }
-    { const T t = T(-0.044418410172992549) * Pb[14]; ga[6] += t * b[3]; gb[3] += t * a[6]; }
-    { const T t = T(0.067850242289111934) * Pb[14]; ga[7] += t * b[4]; gb[4] += t * a[7]; }
-    { const T t = T(0.151717754048285) * Pb[14]; ga[8] += t * b[5]; gb[5] += t * a[8]; }
-    { const T t = T(-0.11752006695060024) * Pb[15]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(-0.13325523051897817) * Pb[15]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(0.099322584599279853) * Pb[15]; ga[3] += t * b[1]; gb[1] += t * a[3]; }
-    { const T t = T(0.076934943211057691) * Pb[15]; ga[4] += t * b[6]; gb[6] += t * a[4]; }
-    { const T t = T(-0.099322584599279881) * Pb[15]; ga[5] += t * b[5]; gb[5] += t * a[5]; }
-    { const T t = T(0.13325523051897822) * Pb[15]; ga[6] += t * b[4]; gb[4] += t * a[6]; }
-    { const T t = T(-0.20355072686733561) * Pb[15]; ga[7] += t * b[3]; gb[3] += t * a[7]; }
-    { const T t = T(-0.11752006695060019) * Pb[15]; ga[8] += t * b[4]; gb[4] += t * a[8]; }
-  }
-};
-template <> struct Couple<4, 4, 4> {
-  static constexpr int kMask = 21;
-  static constexpr int kTerms = 167;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[0] += T(0.28209479177387786) * (a[0] * b[0]);
-    P[0] += T(0.28209479177387814) * (a[1] * b[1]);
-    P[0] += T(0.2820947917738782) * (a[2] * b[2]);
-    P[0] += T(0.28209479177387792) * (a[3] * b[3]);
-    P[0] += T(0.28209479177387842) * (a[4] * b[4]);
-    P[0] += T(0.28209479177387786) * (a[5] * b[5]);
-    P[0] += T(0.28209479177387825) * (a[6] * b[6]);
-    P[0] += T(0.28209479177387814) * (a[7] * b[7]);
-    P[0] += T(0.28209479177387831) * (a[8] * b[8]);
-    P[4] += T(-0.075080816691962496) * (a[0] * b[6]);
-    P[4] += T(-0.11262122503794365) * (a[1] * b[5]);
-    P[4] += T(-0.19036461502711166) * (a[2] * b[4]);
-    P[4] += T(0.075080816691962315) * (a[2] * b[8]);
-    P[4] += T(0.14188940657039983) * (a[3] * b[5]);
-    P[4] += T(0.11262122503794365) * (a[3] * b[7]);
-    P[4] += T(-0.19036461502711166) * (a[4] * b[2]);
-    P[4] += T(-0.11262122503794365) * (a[5] * b[1]);
-    P[4] += T(0.14188940657039983) * (a[5] * b[3]);
-    P[4] += T(-0.075080816691962496) * (a[6] * b[0]);
-    P[4] += T(0.11262122503794365) * (a[7] * b[3]);
-    P[4] += T(0.075080816691962315) * (a[8] * b[2]);
-    P[5] += T(0.14046334619025075) * (a[0] * b[7]);
-    P[5] += T(0.13272538654977697) * (a[1] * b[6]);
-    P[5] += T(-0.1404633461902508) * (a[1] * b[8]);
-    P[5] += T(0.090297865408018207) * (a[2] * b[5]);
-    P[5] += T(-0.13272538654977709) * (a[2] * b[7]);
-    P[5] += T(0.044869370061212312) * (a[3] * b[4]);
-    P[5] += T(-0.090297865408018402) * (a[3] * b[6]);
-    P[5] += T(0.044869370061212312) * (a[4] * b[3]);
-    P[5] += T(0.090297865408018207) * (a[5] * b[2]);
-    P[5] += T(0.13272538654977697) * (a[6] * b[1]);
-    P[5] += T(-0.090297865408018402) * (a[6] * b[3]);
-    P[5] += T(0.14046334619025075) * (a[7] * b[0]);
-    P[5] += T(-0.13272538654977703) * (a[7] * b[2]);
-    P[5] += T(-0.1404633461902508) * (a[8] * b[1]);
-    P[6] += T(-0.22937568382001466) * (a[0] * b[0]);
-    P[6] += T(-0.057343920955003562) * (a[1] * b[1]);
-    P[6] += T(0.065535909662861144) * (a[2] * b[2]);
-    P[6] += T(0.13926380803358027) * (a[3] * b[3]);
-    P[6] += T(0.16383977415715351) * (a[4] * b[4]);
-    P[6] += T(0.13926380803358016) * (a[5] * b[5]);
-    P[6] += T(0.065535909662861297) * (a[6] * b[6]);
-    P[6] += T(-0.057343920955003562) * (a[7] * b[7]);
-    P[6] += T(-0.22937568382001455) * (a[8] * b[8]);
-    P[7] += T(0.14046334619025075) * (a[0] * b[1]);
-    P[7] += T(0.14046334619025075) * (a[1] * b[0]);
-    P[7] += T(0.13272538654977703) * (a[1] * b[2]);
-    P[7] += T(0.13272538654977706) * (a[2] * b[1]);
-    P[7] += T(0.090297865408018207) * (a[2] * b[3]);
-    P[7] += T(0.090297865408018207) * (a[3] * b[2]);
-    P[7] += T(0.044869370061212284) * (a[4] * b[5]);
-    P[7] += T(0.044869370061212284) * (a[5] * b[4]);
-    P[7] += T(0.090297865408018388) * (a[5] * b[6]);
-    P[7] += T(0.090297865408018402) * (a[6] * b[5]);
-    P[7] += T(0.13272538654977695) * (a[6] * b[7]);
-    P[7] += T(0.13272538654977695) * (a[7] * b[6]);
-    P[7] += T(0.1404633461902508) * (a[7] * b[8]);
-    P[7] += T(0.1404633461902508) * (a[8] * b[7]);
-    P[8] += T(-0.075080816691962496) * (a[0] * b[2]);
-    P[8] += T(-0.11262122503794363) * (a[1] * b[3]);
-    P[8] += T(-0.075080816691962496) * (a[2] * b[0]);
-    P[8] += T(-0.11262122503794363) * (a[3] * b[1]);
-    P[8] += T(-0.14188940657039986) * (a[3] * b[3]);
-    P[8] += T(-0.19036461502711177) * (a[4] * b[6]);
-    P[8] += T(0.14188940657039986) * (a[5] * b[5]);
-    P[8] += T(-0.11262122503794363) * (a[5] * b[7]);
-    P[8] += T(-0.19036461502711172) * (a[6] * b[4]);
-    P[8] += T(-0.075080816691962496) * (a[6] * b[8]);
-    P[8] += T(-0.11262122503794363) * (a[7] * b[5]);
-    P[8] += T(-0.07508081669196251) * (a[8] * b[6]);
-    P[16] += T(0.1065253059845416) * (a[0] * b[4]);
-    P[16] += T(-0.11909891275269989) * (a[1] * b[5]);
-    P[16] += T(0.13504547338363843) * (a[2] * b[6]);
-    P[16] += T(-0.1190989127526999) * (a[3] * b[7]);
-    P[16] += T(0.10652530598454157) * (a[4] * b[0]);
-    P[16] += T(-0.11909891275269992) * (a[5] * b[1]);
-    P[16] += T(0.13504547338363843) * (a[6] * b[2]);
-    P[16] += T(-0.1190989127526999) * (a[7] * b[3]);
-    P[17] += T(-0.11909891275269989) * (a[0] * b[5]);
-    P[17] += T(-0.15978795897681217) * (a[1] * b[4]);
-    P[17] += T(0.045015157794546165) * (a[2] * b[5]);
-    P[17] += T(0.045015157794546068) * (a[3] * b[6]);
-    P[17] += T(0.11909891275269992) * (a[3] * b[8]);
-    P[17] += T(-0.15978795897681219) * (a[4] * b[1]);
-    P[17] += T(-0.11909891275269992) * (a[5] * b[0]);
-    P[17] += T(0.045015157794546165) * (a[5] * b[2]);
-    P[17] += T(0.045015157794546068) * (a[6] * b[3]);
-    P[17] += T(0.11909891275269993) * (a[8] * b[3]);
-    P[18] += T(0.13504547338363845) * (a[0] * b[6]);
-    P[18] += T(0.045015157794546096) * (a[1] * b[5]);
-    P[18] += T(-0.083698454702139574) * (a[2] * b[4]);
-    P[18] += T(-0.13504547338363845) * (a[2] * b[8]);
-    P[18] += T(0.10208478235945705) * (a[3] * b[5]);
-    P[18] += T(-0.045015157794546054) * (a[3] * b[7]);
-    P[18] += T(-0.083698454702139574) * (a[4] * b[2]);
-    P[18] += T(0.045015157794546096) * (a[5] * b[1]);
-    P[18] += T(0.10208478235945705) * (a[5] * b[3]);
-    P[18] += T(0.13504547338363843) * (a[6] * b[0]);
-    P[18] += T(-0.045015157794546082) * (a[7] * b[3]);
-    P[18] += T(-0.13504547338363843) * (a[8] * b[2]);
-    P[19] += T(-0.1190989127526999) * (a[0] * b[7]);
-    P[19] += T(0.04501515779454613) * (a[1] * b[6]);
-    P[19] += T(0.11909891275269988) * (a[1] * b[8]);
-    P[19] += T(0.10208478235945705) * (a[2] * b[5]);
-    P[19] += T(-0.045015157794546096) * (a[2] * b[7]);
-    P[19] += T(0.068480553847204917) * (a[3] * b[4]);
-    P[19] += T(-0.10208478235945732) * (a[3] * b[6]);
-    P[19] += T(0.068480553847204917) * (a[4] * b[3]);
-    P[19] += T(0.10208478235945705) * (a[5] * b[2]);
-    P[19] += T(0.045015157794546116) * (a[6] * b[1]);
-    P[19] += T(-0.10208478235945732) * (a[6] * b[3]);
-    P[19] += T(-0.1190989127526999) * (a[7] * b[0]);
-    P[19] += T(-0.045015157794546116) * (a[7] * b[2]);
-    P[19] += T(0.11909891275269988) * (a[8] * b[1]);
-    P[20] += T(0.10652530598454149) * (a[0] * b[0]);
-    P[20] += T(-0.15978795897681211) * (a[1] * b[1]);
-    P[20] += T(-0.083698454702139477) * (a[2] * b[2]);
-    P[20] += T(0.068480553847205056) * (a[3] * b[3]);
-    P[20] += T(0.13696110769441061) * (a[4] * b[4]);
-    P[20] += T(0.068480553847205028) * (a[5] * b[5]);
-    P[20] += T(-0.083698454702139269) * (a[6] * b[6]);
-    P[20] += T(-0.15978795897681206) * (a[7] * b[7]);
-    P[20] += T(0.10652530598454124) * (a[8] * b[8]);
-    P[21] += T(-0.1190989127526999) * (a[0] * b[1]);
-    P[21] += T(-0.1190989127526999) * (a[1] * b[0]);
-    P[21] += T(0.045015157794546116) * (a[1] * b[2]);
-    P[21] += T(0.045015157794546082) * (a[2] * b[1]);
-    P[21] += T(0.10208478235945705) * (a[2] * b[3]);
-    P[21] += T(0.10208478235945705) * (a[3] * b[2]);
-    P[21] += T(0.068480553847204889) * (a[4] * b[5]);
-    P[21] += T(0.068480553847204889) * (a[5] * b[4]);
-    P[21] += T(0.10208478235945721) * (a[5] * b[6]);
-    P[21] += T(0.10208478235945721) * (a[6] * b[5]);
-    P[21] += T(0.045015157794546096) * (a[6] * b[7]);
-    P[21] += T(0.04501515779454611) * (a[7] * b[6]);
-    P[21] += T(-0.1190989127526999) * (a[7] * b[8]);
-    P[21] += T(-0.1190989127526999) * (a[8] * b[7]);
-    P[22] += T(0.13504547338363843) * (a[0] * b[2]);
-    P[22] += T(0.045015157794546096) * (a[1] * b[3]);
-    P[22] += T(0.13504547338363843) * (a[2] * b[0]);
-    P[22] += T(0.045015157794546096) * (a[3] * b[1]);
-    P[22] += T(-0.10208478235945732) * (a[3] * b[3]);
-    P[22] += T(-0.083698454702139408) * (a[4] * b[6]);
-    P[22] += T(0.10208478235945721) * (a[5] * b[5]);
-    P[22] += T(0.045015157794546075) * (a[5] * b[7]);
-    P[22] += T(-0.083698454702139408) * (a[6] * b[4]);
-    P[22] += T(0.13504547338363834) * (a[6] * b[8]);
-    P[22] += T(0.045015157794546075) * (a[7] * b[5]);
-    P[22] += T(0.13504547338363837) * (a[8] * b[6]);
-    P[23] += T(-0.1190989127526999) * (a[0] * b[3]);
-    P[23] += T(-0.045015157794546123) * (a[2] * b[3]);
-    P[23] += T(-0.1190989127526999) * (a[3] * b[0]);
-    P[23] += T(-0.045015157794546123) * (a[3] * b[2]);
-    P[23] += T(-0.15978795897681219) * (a[4] * b[7]);
-    P[23] += T(0.045015157794546089) * (a[5] * b[6]);
-    P[23] += T(-0.11909891275269992) * (a[5] * b[8]);
-    P[23] += T(0.045015157794546089) * (a[6] * b[5]);
-    P[23] += T(-0.15978795897681214) * (a[7] * b[4]);
-    P[23] += T(-0.11909891275269992) * (a[8] * b[5]);
-    P[24] += T(0.1190989127526999) * (a[1] * b[3]);
-    P[24] += T(-0.13504547338363845) * (a[2] * b[2]);
-    P[24] += T(0.1190989127526999) * (a[3] * b[1]);
-    P[24] += T(0.10652530598454124) * (a[4] * b[8]);
-    P[24] += T(-0.11909891275269992) * (a[5] * b[7]);
-    P[24] += T(0.13504547338363837) * (a[6] * b[6]);
-    P[24] += T(-0.11909891275269989) * (a[7] * b[5]);
-    P[24] += T(0.10652530598454124) * (a[8] * b[4]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(0.28209479177387786) * Pb[0]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.28209479177387814) * Pb[0]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(0.2820947917738782) * Pb[0]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(0.28209479177387792) * Pb[0]; ga[3] += t * b[3]; gb[3] += t * a[3]; }
-    { const T t = T(0.28209479177387842) * Pb[0]; ga[4] += t * b[4]; gb[4] += t * a[4]; }
-    { const T t = T(0.28209479177387786) * Pb[0]; ga[5] += t * b[5]; gb[5] += t * a[5]; }
-    { const T t = T(0.28209479177387825) * Pb[0]; ga[6] += t * b[6]; gb[6] += t * a[6]; }
-    { const T t = T(0.28209479177387814) * Pb[0]; ga[7] += t * b[7]; gb[7] += t * a[7]; }
-    { const T t = T(0.28209479177387831) * Pb[0]; ga[8] += t * b[8]; gb[8] += t * a[8]; }
-    { const T t = T(-0.075080816691962496) * Pb[4]; ga[0] += t * b[6]; gb[6] += t * a[0]; }
-    { const T t = T(-0.11262122503794365) * Pb[4]; ga[1] += t * b[5]; gb[5] += t * a[1]; }
-    { const T t = T(-0.19036461502711166) * Pb[4]; ga[2] += t * b[4]; gb[4] += t * a[2]; }
-    { const T t = T(0.075080816691962315) * Pb[4]; ga[2] += t * b[8]; gb[8] += t * a[2]; }
-    { const T t = T(0.14188940657039983) * Pb[4]; ga[3] += t * b[5]; gb[5] += t * a[3]; }
-    { const T t = T(0.11262122503794365) * Pb[4]; ga[3] += t * b[7]; gb[7] += t * a[3]; }
-    { const T t = T(-0.19036461502711166) * Pb[4]; ga[4] += t * b[2]; gb[2] += t * a[4]; }
-    { const T t = T(-0.11262122503794365) * Pb[4]; ga[5] += t * b[1]; gb[1] += t * a[5]; }
-    { const T t = T(0.14188940657039983) * Pb[4]; ga[5] += t * b[3]; gb[3] += t * a[5]; }
-    { const T t = T(-0.075080816691962496) * Pb[4]; ga[6] += t * b[0]; gb[0] += t * a[6]; }
-    { const T t = T(0.11262122503794365) * Pb[4]; ga[7] += t * b[3]; gb[3] += t * a[7]; }
-    { const T t = T(0.075080816691962315) * Pb[4]; ga[8] += t * b[2]; gb[2] += t * a[8]; }
-    { const T t = T(0.14046334619025075) * Pb[5]; ga[0] += t * b[7]; gb[7] += t * a[0]; }
-    { const T t = T(0.13272538654977697) * Pb[5]; ga[1] += t * b[6]; gb[6] += t * a[1]; }
-    { const T t = T(-0.1404633461902508) * Pb[5]; ga[1] += t * b[8]; gb[8] += t * a[1]; }
-    { const T t = T(0.090297865408018207) * Pb[5]; ga[2] += t * b[5]; gb[5] += t * a[2]; }
-    { const T t = T(-0.13272538654977709) * Pb[5]; ga[2] += t * b[7]; gb[7] += t * a[2]; }
-    { const T t = T(0.044869370061212312) * Pb[5]; ga[3] += t * b[4]; gb[4] += t * a[3]; }
-    { const T t = T(-0.090297865408018402) * Pb[5]; ga[3] += t * b[6]; gb[6] += t * a[3]; }
-    { const T t = T(0.044869370061212312) * Pb[5]; ga[4] += t * b[3]; gb[3] += t * a[4]; }
-    { const T t = T(0.090297865408018207) * Pb[5]; ga[5] += t * b[2]; gb[2] += t * a[5]; }
-    { const T t = T(0.13272538654977697) * Pb[5]; ga[6] += t * b[1]; gb[1] += t * a[6]; }
-    { const T t = T(-0.090297865408018402) * Pb[5]; ga[6] += t * b[3]; gb[3] += t * a[6]; }
-    { const T t = T(0.14046334619025075) * Pb[5]; ga[7] += t * b[0]; gb[0] += t * a[7]; }
-    { const T t = T(-0.13272538654977703) * Pb[5]; ga[7] += t * b[2]; gb[2] += t * a[7]; }
-    { const T t = T(-0.1404633461902508) * Pb[5]; ga[8] += t * b[1]; gb[1] += t * a[8]; }
-    { const T t = T(-0.22937568382001466) * Pb[6]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(-0.057343920955003562) * Pb[6]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(0.065535909662861144) * Pb[6]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(0.13926380803358027) * Pb[6]; ga[3] += t * b[3]; gb[3] += t * a[3]; }
-    { const T t = T(0.16383977415715351) * Pb[6]; ga[4] += t * b[4]; gb[4] += t * a[4]; }
-    { const T t = T(0.13926380803358016) * Pb[6]; ga[5] += t * b[5]; gb[5] += t * a[5]; }
-    { const T t = T(0.065535909662861297) * Pb[6]; ga[6] += t * b[6]; gb[6] += t * a[6]; }
-    { const T t = T(-0.057343920955003562) * Pb[6]; ga[7] += t * b[7]; gb[7] += t * a[7]; }
-    { const T t = T(-0.22937568382001455) * Pb[6]; ga[8] += t * b[8]; gb[8] += t * a[8]; }
-    { const T t = T(0.14046334619025075) * Pb[7]; ga[0] += t * b[1]; gb[1] += t * a[0]; }
-    { const T t = T(0.14046334619025075) * Pb[7]; ga[1] += t * b[0]; gb[0] += t * a[1]; }
-    { const T t = T(0.13272538654977703) * Pb[7]; ga[1] += t * b[2]; gb[2] += t * a[1]; }
-    { const T t = T(0.13272538654977706) * Pb[7]; ga[2] += t * b[1]; gb[1] += t * a[2]; }
-    { const T t = T(0.090297865408018207) * Pb[7]; ga[2] += t * b[3]; gb[3] += t * a[2]; }
-    { const T t = T(0.090297865408018207) * Pb[7]; ga[3] += t * b[2]; gb[2] += t * a[3]; }
-    { const T t = T(0.044869370061212284) * Pb[7]; ga[4] += t * b[5]; gb[5] += t * a[4]; }
-    { const T t = T(0.044869370061212284) * Pb[7]; ga[5] += t * b[4]; gb[4] += t * a[5]; }
-    { const T t = T(0.090297865408018388) * Pb[7]; ga[5] += t * b[6]; gb[6] += t * a[5]; }
-    { const T t = T(0.090297865408018402) * Pb[7]; ga[6] += t * b[5]; gb[5] += t * a[6]; }
-    { const T t = T(0.13272538654977695) * Pb[7]; ga[6] += t * b[7]; gb[7] += t * a[6]; }
-    { const T t = T(0.13272538654977695) * Pb[7]; ga[7] += t * b[6]; gb[6] += t * a[7]; }
-    { const T t = T(0.1404633461902508) * Pb[7]; ga[7] += t * b[8]; gb[8] += t * a[7]; }
-    { const T t = T(0.1404633461902508) * Pb[7]; ga[8] += t * b[7]; gb[7] += t * a[8]; }
-    { const T t = T(-0.075080816691962496) * Pb[8]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(-0.11262122503794363) * Pb[8]; ga[1] += t * b[3]; gb[3] += t * a[1]; }
-    { const T t = T(-0.075080816691962496) * Pb[8]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(-0.11262122503794363) * Pb[8]; ga[3] += t * b[1]; gb[1] += t * a[3]; }
-    { const T t = T(-0.14188940657039986) * Pb[8]; ga[3] += t * b[3]; gb[3] += t * a[3]; }
-    { const T t = T(-0.19036461502711177) * Pb[8]; ga[4] += t * b[6]; gb[6] += t * a[4]; }
-    { const T t = T(0.14188940657039986) * Pb[8]; ga[5] += t * b[5]; gb[5] += t * a[5]; }
-    { const T t = T(-0.11262122503794363) * Pb[8]; ga[5] += t * b[7]; gb[7] += t * a[5]; }
-    { const T t = T(-0.19036461502711172) * Pb[8]; ga[6] += t * b[4]; gb[4] += t * a[6]; }
-    { const T t = T(-0.075080816691962496) * Pb[8]; ga[6] += t * b[8]; gb[8] += t * a[6]; }
-    { const T t = T(-0.11262122503794363) * Pb[8]; ga[7] += t * b[5]; gb[5] += t * a[7]; }
-    { const T t = T(-0.07508081669196251) * Pb[8]; ga[8] += t * b[6]; gb[6] += t * a[8]; }
-    { const T t = T(0.1065253059845416) * Pb[16]; ga[0] += t * b[4]; gb[4] += t * a[0]; }
-    { const T t = T(-0.11909891275269989) * Pb[16]; ga[1] += t * b[5]; gb[5] += t * a[1]; }
-    { const T t = T(0.13504547338363843) * Pb[16]; ga[2] += t * b[6]; gb[6] += t * a[2]; }
-    { const T t = T(-0.1190989127526999) * Pb[16]; ga[3] += t * b[7]; gb[7] += t * a[3]; }
-    { const T t = T(0.10652530598454157) * Pb[16]; ga[4] += t * b[0]; gb[0] += t * a[4]; }
-    { const T t = T(-0.11909891275269992) * Pb[16]; ga[5] += t * b[1]; gb[1] += t * a[5]; }
-    { const T t = T(0.13504547338363843) * Pb[16]; ga[6] += t * b[2]; gb[2] += t * a[6]; }
-    { const T t = T(-0.1190989127526999) * Pb[16]; ga[7] += t * b[3]; gb[3] += t * a[7]; }
-    { const T t = T(-0.11909891275269989) * Pb[17]; ga[0] += t * b[5]; gb[5] += t * a[0]; }
-    { const T t = T(-0.15978795897681217) * Pb[17]; ga[1] += t * b[4]; gb[4] += t * a[1]; }
-    { const T t = T(0.045015157794546165) * Pb[17]; ga[2] += t * b[5]; gb[5] += t * a[2]; }
-    { const T t = T(0.045015157794546068) * Pb[17]; ga[3] += t * b[6]; gb[6] += t * a[3]; }
-    { const T t = T(0.11909891275269992) * Pb[17]; ga[3] += t * b[8]; gb[8] += t * a[3]; }
-    { const T t = T(-0.15978795897681219) * Pb[17]; ga[4] += t * b[1]; gb[1] += t * a[4]; }
-    { const T t = T(-0.11909891275269992) * Pb[17]; ga[5] += t * b[0]; gb[0] += t * a[5]; }
-    { const T t = T(0.045015157794546165) * Pb[17]; ga[5] += t * b[2]; gb[2] += t * a[5]; }
-    { const T t = T(0.045015157794546068) * Pb[17]; ga[6] += t * b[3]; gb[3] += t * a[6]; }
-    { const T t = T(0.11909891275269993) * Pb[17]; ga[8] += t * b[3]; gb[3] += t * a[8]; }
-    { const T t = T(0.13504547338363845) * Pb[18]; ga[0] += t * b[6]; gb[6] += t * a[0]; }
-    { const T t = T(0.045015157794546096) * Pb[18]; ga[1] += t * b[5]; gb[5] += t * a[1]; }
-    { const T t = T(-0.083698454702139574) * Pb[18]; ga[2] += t * b[4]; gb[4] += t * a[2]; }
-    { const T t = T(-0.13504547338363845) * Pb[18]; ga[2] += t * b[8]; gb[8] += t * a[2]; }
-    { const T t = T(0.10208478235945705) * Pb[18]; ga[3] += t * b[5]; gb[5] += t * a[3]; }
-    { const T t = T(-0.045015157794546054) * Pb[18]; ga[3] += t * b[7]; gb[7] += t * a[3]; }
-    { const T t = T(-0.083698454702139574) * Pb[18]; ga[4] += t * b[2]; gb[2] += t * a[4]; }
-    { const T t = T(0.045015157794546096) * Pb[18]; ga[5] += t * b[1]; gb[1] += t * a[5]; }
-    { const T t = T(0.10208478235945705) * Pb[18]; ga[5] += t * b[3]; gb[3] += t * a[5]; }
-    { const T t = T(0.13504547338363843) * Pb[18]; ga[6] += t * b[0]; gb[0] += t * a[6]; }
-    { const T t = T(-0.045015157794546082) * Pb[18]; ga[7] += t * b[3]; gb[3] += t * a[7]; }
-    { const T t = T(-0.13504547338363843) * Pb[18]; ga[8] += t * b[2]; gb[2] += t * a[8]; }
-    { const T t = T(-0.1190989127526999) * Pb[19]; ga[0] += t * b[7]; gb[7] += t * a[0]; }
-    { const T t = T(0.04501515779454613) * Pb[19]; ga[1] += t * b[6]; gb[6] += t * a[1]; }
-    { const T t = T(0.11909891275269988) * Pb[19]; ga[1] += t * b[8]; gb[8] += t * a[1]; }
-    { const T t = T(0.10208478235945705) * Pb[19]; ga[2] += t * b[5]; gb[5] += t * a[2]; }
-    { const T t = T(-0.045015157794546096) * Pb[19]; ga[2] += t * b[7]; gb[7] += t * a[2]; }
-    { const T t = T(0.068480553847204917) * Pb[19]; ga[3] += t * b[4]; gb[4] += t * a[3]; }
-    { const T t = T(-0.10208478235945732) * Pb[19]; ga[3] += t * b[6]; gb[6] += t * a[3]; }
-    { const T t = T(0.068480553847204917) * Pb[19]; ga[4] += t * b[3]; gb[3] += t * a[4]; }
-    { const T t = T(0.10208478235945705) * Pb[19]; ga[5] += t * b[2]; gb[2] += t * a[5]; }
-    { const T t = T(0.045015157794546116) * Pb[19]; ga[6] += t * b[1]; gb[1] += t * a[6]; }
-    { const T t = T(-0.10208478235945732) * Pb[19]; ga[6] += t * b[3]; gb[3] += t * a[6]; }
-    { const T t = T(-0.1190989127526999) * Pb[19]; ga[7] += t * b[0]; gb[0] += t * a[7]; }
-    { const T t = T(-0.045015157794546116) * Pb[19]; ga[7] += t * b[2]; gb[2] += t * a[7]; }
-    { const T t = T(0.11909891275269988) * Pb[19]; ga[8] += t * b[1]; gb[1] += t * a[8]; }
-    { const T t = T(0.10652530598454149) * Pb[20]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(-0.15978795897681211) * Pb[20]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(-0.083698454702139477) * Pb[20]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(0.068480553847205056) * Pb[20]; ga[3] += t * b[3]; gb[3] += t * a[3]; }
-    { const T t = T(0.13696110769441061) * Pb[20]; ga[4] += t * b[4]; gb[4] += t * a[4]; }
-    { const T t = T(0.068480553847205028) * Pb[20]; ga[5] += t * b[5]; gb[5] += t * a[5]; }
-    { const T t = T(-0.083698454702139269) * Pb[20]; ga[6] += t * b[6]; gb[6] += t * a[6]; }
-    { const T t = T(-0.15978795897681206) * Pb[20]; ga[7] += t * b[7]; gb[7] += t * a[7]; }
-    { const T t = T(0.10652530598454124) * Pb[20]; ga[8] += t * b[8]; gb[8] += t * a[8]; }
-    { const T t = T(-0.1190989127526999) * Pb[21]; ga[0] += t * b[1]; gb[1] += t * a[0]; }
-    { const T t = T(-0.1190989127526999) * Pb[21]; ga[1] += t * b[0]; gb[0] += t * a[1]; }
-    { const T t = T(0.045015157794546116) * Pb[21]; ga[1] += t * b[2]; gb[2] += t * a[1]; }
-    { const T t = T(0.045015157794546082) * Pb[21]; ga[2] += t * b[1]; gb[1] += t * a[2]; }
-    { const T t = T(0.10208478235945705) * Pb[21]; ga[2] += t * b[3]; gb[3] += t * a[2]; }
-    { const T t = T(0.10208478235945705) * Pb[21]; ga[3] += t * b[2]; gb[2] += t * a[3]; }
-    { const T t = T(0.068480553847204889) * Pb[21]; ga[4] += t * b[5]; gb[5] += t * a[4]; }
-    { const T t = T(0.068480553847204889) * Pb[21]; ga[5] += t * b[4]; gb[4] += t * a[5]; }
-    { const T t = T(0.10208478235945721) * Pb[21]; ga[5] += t * b[6]; gb[6] += t * a[5]; }
-    { const T t = T(0.10208478235945721) * Pb[21]; ga[6] += t * b[5]; gb[5] += t * a[6]; }
-    { const T t = T(0.045015157794546096) * Pb[21]; ga[6] += t * b[7]; gb[7] += t * a[6]; }
-    { const T t = T(0.04501515779454611) * Pb[21]; ga[7] += t * b[6]; gb[6] += t * a[7]; }
-    { const T t = T(-0.1190989127526999) * Pb[21]; ga[7] += t * b[8]; gb[8] += t * a[7]; }
-    { const T t = T(-0.1190989127526999) * Pb[21]; ga[8] += t * b[7]; gb[7] += t * a[8]; }
-    { const T t = T(0.13504547338363843) * Pb[22]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(0.045015157794546096) * Pb[22]; ga[1] += t * b[3]; gb[3] += t * a[1]; }
-    { const T t = T(0.13504547338363843) * Pb[22]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(0.045015157794546096) * Pb[22]; ga[3] += t * b[1]; gb[1] += t * a[3]; }
-    { const T t = T(-0.10208478235945732) * Pb[22]; ga[3] += t * b[3]; gb[3] += t * a[3]; }
-    { const T t = T(-0.083698454702139408) * Pb[22]; ga[4] += t * b[6]; gb[6] += t * a[4]; }
-    { const T t = T(0.10208478235945721) * Pb[22]; ga[5] += t * b[5]; gb[5] += t * a[5]; }
-    { const T t = T(0.045015157794546075) * Pb[22]; ga[5] += t * b[7]; gb[7] += t * a[5]; }
-    { const T t = T(-0.083698454702139408) * Pb[22]; ga[6] += t * b[4]; gb[4] += t * a[6]; }
-    { const T t = T(0.13504547338363834) * Pb[22]; ga[6] += t * b[8]; gb[8] += t * a[6]; }
-    { const T t = T(0.045015157794546075) * Pb[22]; ga[7] += t * b[5]; gb[5] += t * a[7]; }
-    { const T t = T(0.13504547338363837) * Pb[22]; ga[8] += t * b[6]; gb[6] += t * a[8]; }
-    { const T t = T(-0.1190989127526999) * Pb[23]; ga[0] += t * b[3]; gb[3] += t * a[0]; }
-    { const T t = T(-0.045015157794546123) * Pb[23]; ga[2] += t * b[3]; gb[3] += t * a[2]; }
-    { const T t = T(-0.1190989127526999) * Pb[23]; ga[3] += t * b[0]; gb[0] += t * a[3]; }
-    { const T t = T(-0.045015157794546123) * Pb[23]; ga[3] += t * b[2]; gb[2] += t * a[3]; }
-    { const T t = T(-0.15978795897681219) * Pb[23]; ga[4] += t * b[7]; gb[7] += t * a[4]; }
-    { const T t = T(0.045015157794546089) * Pb[23]; ga[5] += t * b[6]; gb[6] += t * a[5]; }
-    { const T t = T(-0.11909891275269992) * Pb[23]; ga[5] += t * b[8]; gb[8] += t * a[5]; }
-    { const T t = T(0.045015157794546089) * Pb[23]; ga[6] += t * b[5]; gb[5] += t * a[6]; }
-    { const T t = T(-0.15978795897681214) * Pb[23]; ga[7] += t * b[4]; gb[4] += t * a[7]; }
-    { const T t = T(-0.11909891275269992) * Pb[23]; ga[8] += t * b[5]; gb[5] += t * a[8]; }
-    { const T t = T(0.1190989127526999) * Pb[24]; ga[1] += t * b[3]; gb[3] += t * a[1]; }
-    { const T t = T(-0.13504547338363845) * Pb[24]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(0.1190989127526999) * Pb[24]; ga[3] += t * b[1]; gb[1] += t * a[3]; }
-    { const T t = T(0.10652530598454124) * Pb[24]; ga[4] += t * b[8]; gb[8] += t * a[4]; }
-    { const T t = T(-0.11909891275269992) * Pb[24]; ga[5] += t * b[7]; gb[7] += t * a[5]; }
-    { const T t = T(0.13504547338363837) * Pb[24]; ga[6] += t * b[6]; gb[6] += t * a[6]; }
-    { const T t = T(-0.11909891275269989) * Pb[24]; ga[7] += t * b[5]; gb[5] += t * a[7]; }
-    { const T t = T(0.10652530598454124) * Pb[24]; ga[8] += t * b[4]; gb[4] += t * a[8]; }
-  }
-};
-template <int LMAX, int L1, int L2, int L> struct Couple3;
-template <> struct Couple3<3, 0, 0, 0> {
-  static constexpr int kTerms = 1;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[0] += T(0.28209479177387803) * (a[0] * b[0]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(0.28209479177387803) * Pb[0]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-  }
-};
-template <> struct Couple3<3, 0, 1, 1> {
-  static constexpr int kTerms = 3;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[0] += T(0.28209479177387808) * (a[0] * b[0]);
-    P[1] += T(0.28209479177387808) * (a[0] * b[1]);
-    P[2] += T(0.28209479177387808) * (a[0] * b[2]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(0.28209479177387808) * Pb[0]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.28209479177387808) * Pb[1]; ga[0] += t * b[1]; gb[1] += t * a[0]; }
-    { const T t = T(0.28209479177387808) * Pb[2]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-  }
-};
-template <> struct Couple3<3, 0, 2, 2> {
-  static constexpr int kTerms = 5;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[0] += T(0.2820947917738782) * (a[0] * b[0]);
-    P[1] += T(0.28209479177387831) * (a[0] * b[1]);
-    P[2] += T(0.28209479177387831) * (a[0] * b[2]);
-    P[3] += T(0.28209479177387831) * (a[0] * b[3]);
-    P[4] += T(0.28209479177387831) * (a[0] * b[4]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(0.2820947917738782) * Pb[0]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.28209479177387831) * Pb[1]; ga[0] += t * b[1]; gb[1] += t * a[0]; }
-    { const T t = T(0.28209479177387831) * Pb[2]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(0.28209479177387831) * Pb[3]; ga[0] += t * b[3]; gb[3] += t * a[0]; }
-    { const T t = T(0.28209479177387831) * Pb[4]; ga[0] += t * b[4]; gb[4] += t * a[0]; }
-  }
-};
-template <> struct Couple3<3, 0, 3, 3> {
-  static constexpr int kTerms = 7;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[0] += T(0.2820947917738782) * (a[0] * b[0]);
-    P[1] += T(0.2820947917738782) * (a[0] * b[1]);
-    P[2] += T(0.28209479177387825) * (a[0] * b[2]);
-    P[3] += T(0.28209479177387814) * (a[0] * b[3]);
-    P[4] += T(0.28209479177387825) * (a[0] * b[4]);
-    P[5] += T(0.28209479177387825) * (a[0] * b[5]);
-    P[6] += T(0.2820947917738782) * (a[0] * b[6]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(0.2820947917738782) * Pb[0]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.2820947917738782) * Pb[1]; ga[0] += t * b[1]; gb[1] += t * a[0]; }
-    { const T t = T(0.28209479177387825) * Pb[2]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(0.28209479177387814) * Pb[3]; ga[0] += t * b[3]; gb[3] += t * a[0]; }
-    { const T t = T(0.28209479177387825) * Pb[4]; ga[0] += t * b[4]; gb[4] += t * a[0]; }
-    { const T t = T(0.28209479177387825) * Pb[5]; ga[0] += t * b[5]; gb[5] += t * a[0]; }
-    { const T t = T(0.2820947917738782) * Pb[6]; ga[0] += t * b[6]; gb[6] += t * a[0]; }
-  }
-};
-template <> struct Couple3<3, 1, 0, 1> {
-  static constexpr int kTerms = 3;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[0] += T(0.28209479177387808) * (a[0] * b[0]);
-    P[1] += T(0.28209479177387808) * (a[1] * b[0]);
-    P[2] += T(0.28209479177387808) * (a[2] * b[0]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(0.28209479177387808) * Pb[0]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.28209479177387808) * Pb[1]; ga[1] += t * b[0]; gb[0] += t * a[1]; }
-    { const T t = T(0.28209479177387808) * Pb[2]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-  }
-};
-template <> struct Couple3<3, 1, 1, 0> {
-  static constexpr int kTerms = 3;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[0] += T(0.28209479177387803) * (a[0] * b[0]);
-    P[0] += T(0.28209479177387803) * (a[1] * b[1]);
-    P[0] += T(0.28209479177387803) * (a[2] * b[2]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(0.28209479177387803) * Pb[0]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.28209479177387803) * Pb[0]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(0.28209479177387803) * Pb[0]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-  }
-};
-template <> struct Couple3<3, 1, 1, 2> {
-  static constexpr int kTerms = 11;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[0] += T(0.21850968611841587) * (a[0] * b[2]);
-    P[0] += T(0.21850968611841587) * (a[2] * b[0]);
-    P[1] += T(0.21850968611841587) * (a[0] * b[1]);
-    P[1] += T(0.21850968611841587) * (a[1] * b[0]);
-    P[2] += T(-0.12615662610100806) * (a[0] * b[0]);
-    P[2] += T(0.252313252202016) * (a[1] * b[1]);
-    P[2] += T(-0.12615662610100806) * (a[2] * b[2]);
-    P[3] += T(0.21850968611841587) * (a[1] * b[2]);
-    P[3] += T(0.21850968611841587) * (a[2] * b[1]);
-    P[4] += T(-0.2185096861184159) * (a[0] * b[0]);
-    P[4] += T(0.2185096861184159) * (a[2] * b[2]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(0.21850968611841587) * Pb[0]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(0.21850968611841587) * Pb[0]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(0.21850968611841587) * Pb[1]; ga[0] += t * b[1]; gb[1] += t * a[0]; }
-    { const T t = T(0.21850968611841587) * Pb[1]; ga[1] += t * b[0]; gb[0] += t * a[1]; }
-    { const T t = T(-0.12615662610100806) * Pb[2]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.252313252202016) * Pb[2]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(-0.12615662610100806) * Pb[2]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(0.21850968611841587) * Pb[3]; ga[1] += t * b[2]; gb[2] += t * a[1]; }
-    { const T t = T(0.21850968611841587) * Pb[3]; ga[2] += t * b[1]; gb[1] += t * a[2]; }
-    { const T t = T(-0.2185096861184159) * Pb[4]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.2185096861184159) * Pb[4]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-  }
-};
-template <> struct Couple3<3, 1, 2, 1> {
-  static constexpr int kTerms = 11;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[0] += T(-0.12615662610100806) * (a[0] * b[2]);
-    P[0] += T(-0.2185096861184159) * (a[0] * b[4]);
-    P[0] += T(0.21850968611841587) * (a[1] * b[1]);
-    P[0] += T(0.21850968611841587) * (a[2] * b[0]);
-    P[1] += T(0.21850968611841587) * (a[0] * b[1]);
-    P[1] += T(0.252313252202016) * (a[1] * b[2]);
-    P[1] += T(0.21850968611841587) * (a[2] * b[3]);
-    P[2] += T(0.21850968611841587) * (a[0] * b[0]);
-    P[2] += T(0.21850968611841587) * (a[1] * b[3]);
-    P[2] += T(-0.12615662610100806) * (a[2] * b[2]);
-    P[2] += T(0.2185096861184159) * (a[2] * b[4]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(-0.12615662610100806) * Pb[0]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(-0.2185096861184159) * Pb[0]; ga[0] += t * b[4]; gb[4] += t * a[0]; }
-    { const T t = T(0.21850968611841587) * Pb[0]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(0.21850968611841587) * Pb[0]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(0.21850968611841587) * Pb[1]; ga[0] += t * b[1]; gb[1] += t * a[0]; }
-    { const T t = T(0.252313252202016) * Pb[1]; ga[1] += t * b[2]; gb[2] += t * a[1]; }
-    { const T t = T(0.21850968611841587) * Pb[1]; ga[2] += t * b[3]; gb[3] += t * a[2]; }
-    { const T t = T(0.21850968611841587) * Pb[2]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.21850968611841587) * Pb[2]; ga[1] += t * b[3]; gb[3] += t * a[1]; }
-    { const T t = T(-0.12615662610100806) * Pb[2]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(0.2185096861184159) * Pb[2]; ga[2] += t * b[4]; gb[4] += t * a[2]; }
-  }
-};
-template <> struct Couple3<3, 1, 2, 3> {
-  static constexpr int kTerms = 21;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[0] += T(0.22617901315954023) * (a[0] * b[4]);
-    P[0] += T(0.22617901315954039) * (a[2] * b[0]);
-    P[1] += T(0.18467439092237189) * (a[0] * b[3]);
-    P[1] += T(0.18467439092237187) * (a[1] * b[0]);
-    P[1] += T(0.18467439092237189) * (a[2] * b[1]);
-    P[2] += T(0.20230065940342065) * (a[0] * b[2]);
-    P[2] += T(0.058399170081901729) * (a[0] * b[4]);
-    P[2] += T(0.23359668032760758) * (a[1] * b[1]);
-    P[2] += T(-0.058399170081901861) * (a[2] * b[0]);
-    P[3] += T(-0.1430481681026689) * (a[0] * b[1]);
-    P[3] += T(0.24776669508347599) * (a[1] * b[2]);
-    P[3] += T(-0.1430481681026689) * (a[2] * b[3]);
-    P[4] += T(-0.058399170081901861) * (a[0] * b[0]);
-    P[4] += T(0.23359668032760758) * (a[1] * b[3]);
-    P[4] += T(0.20230065940342065) * (a[2] * b[2]);
-    P[4] += T(-0.058399170081901729) * (a[2] * b[4]);
-    P[5] += T(-0.18467439092237189) * (a[0] * b[1]);
-    P[5] += T(0.18467439092237187) * (a[1] * b[4]);
-    P[5] += T(0.18467439092237189) * (a[2] * b[3]);
-    P[6] += T(-0.22617901315954039) * (a[0] * b[0]);
-    P[6] += T(0.22617901315954023) * (a[2] * b[4]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(0.22617901315954023) * Pb[0]; ga[0] += t * b[4]; gb[4] += t * a[0]; }
-    { const T t = T(0.22617901315954039) * Pb[0]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(0.18467439092237189) * Pb[1]; ga[0] += t * b[3]; gb[3] += t * a[0]; }
-    { const T t = T(0.18467439092237187) * Pb[1]; ga[1] += t * b[0]; gb[0] += t * a[1]; }
-    { const T t = T(0.18467439092237189) * Pb[1]; ga[2] += t * b[1]; gb[1] += t * a[2]; }
-    { const T t = T(0.20230065940342065) * Pb[2]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(0.058399170081901729) * Pb[2]; ga[0] += t * b[4]; gb[4] += t * a[0]; }
-    { const T t = T(0.23359668032760758) * Pb[2]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(-0.058399170081901861) * Pb[2]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(-0.1430481681026689) * Pb[3]; ga[0] += t * b[1]; gb[1] += t * a[0]; }
-    { const T t = T(0.24776669508347599) * Pb[3]; ga[1] += t * b[2]; gb[2] += t * a[1]; }
-    { const T t = T(-0.1430481681026689) * Pb[3]; ga[2] += t * b[3]; gb[3] += t * a[2]; }
-    { const T t = T(-0.058399170081901861) * Pb[4]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.23359668032760758) * Pb[4]; ga[1] += t * b[3]; gb[3] += t * a[1]; }
-    { const T t = T(0.20230065940342065) * Pb[4]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(-0.058399170081901729) * Pb[4]; ga[2] += t * b[4]; gb[4] += t * a[2]; }
-    { const T t = T(-0.18467439092237189) * Pb[5]; ga[0] += t * b[1]; gb[1] += t * a[0]; }
-    { const T t = T(0.18467439092237187) * Pb[5]; ga[1] += t * b[4]; gb[4] += t * a[1]; }
-    { const T t = T(0.18467439092237189) * Pb[5]; ga[2] += t * b[3]; gb[3] += t * a[2]; }
-    { const T t = T(-0.22617901315954039) * Pb[6]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.22617901315954023) * Pb[6]; ga[2] += t * b[4]; gb[4] += t * a[2]; }
-  }
-};
-template <> struct Couple3<3, 1, 3, 2> {
-  static constexpr int kTerms = 21;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[0] += T(-0.058399170081901867) * (a[0] * b[4]);
-    P[0] += T(-0.22617901315954042) * (a[0] * b[6]);
-    P[0] += T(0.18467439092237187) * (a[1] * b[1]);
-    P[0] += T(0.22617901315954042) * (a[2] * b[0]);
-    P[0] += T(-0.058399170081901867) * (a[2] * b[2]);
-    P[1] += T(-0.1430481681026689) * (a[0] * b[3]);
-    P[1] += T(-0.18467439092237192) * (a[0] * b[5]);
-    P[1] += T(0.23359668032760761) * (a[1] * b[2]);
-    P[1] += T(0.18467439092237189) * (a[2] * b[1]);
-    P[2] += T(0.20230065940342068) * (a[0] * b[2]);
-    P[2] += T(0.24776669508347601) * (a[1] * b[3]);
-    P[2] += T(0.20230065940342068) * (a[2] * b[4]);
-    P[3] += T(0.18467439092237189) * (a[0] * b[1]);
-    P[3] += T(0.23359668032760761) * (a[1] * b[4]);
-    P[3] += T(-0.1430481681026689) * (a[2] * b[3]);
-    P[3] += T(0.18467439092237192) * (a[2] * b[5]);
-    P[4] += T(0.22617901315954025) * (a[0] * b[0]);
-    P[4] += T(0.058399170081901736) * (a[0] * b[2]);
-    P[4] += T(0.18467439092237187) * (a[1] * b[5]);
-    P[4] += T(-0.058399170081901736) * (a[2] * b[4]);
-    P[4] += T(0.22617901315954025) * (a[2] * b[6]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(-0.058399170081901867) * Pb[0]; ga[0] += t * b[4]; gb[4] += t * a[0]; }
-    { const T t = T(-0.22617901315954042) * Pb[0]; ga[0] += t * b[6]; gb[6] += t * a[0]; }
-    { const T t = T(0.18467439092237187) * Pb[0]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(0.22617901315954042) * Pb[0]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(-0.058399170081901867) * Pb[0]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(-0.1430481681026689) * Pb[1]; ga[0] += t * b[3]; gb[3] += t * a[0]; }
-    { const T t = T(-0.18467439092237192) * Pb[1]; ga[0] += t * b[5]; gb[5] += t * a[0]; }
-    { const T t = T(0.23359668032760761) * Pb[1]; ga[1] += t * b[2]; gb[2] += t * a[1]; }
-    { const T t = T(0.18467439092237189) * Pb[1]; ga[2] += t * b[1]; gb[1] += t * a[2]; }
-    { const T t = T(0.20230065940342068) * Pb[2]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(0.24776669508347601) * Pb[2]; ga[1] += t * b[3]; gb[3] += t * a[1]; }
-    { const T t = T(0.20230065940342068) * Pb[2]; ga[2] += t * b[4]; gb[4] += t * a[2]; }
-    { const T t = T(0.18467439092237189) * Pb[3]; ga[0] += t * b[1]; gb[1] += t * a[0]; }
-    { const T t = T(0.23359668032760761) * Pb[3]; ga[1] += t * b[4]; gb[4] += t * a[1]; }
-    { const T t = T(-0.1430481681026689) * Pb[3]; ga[2] += t * b[3]; gb[3] += t * a[2]; }
-    { const T t = T(0.18467439092237192) * Pb[3]; ga[2] += t * b[5]; gb[5] += t * a[2]; }
-    { const T t = T(0.22617901315954025) * Pb[4]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.058399170081901736) * Pb[4]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(0.18467439092237187) * Pb[4]; ga[1] += t * b[5]; gb[5] += t * a[1]; }
-    { const T t = T(-0.058399170081901736) * Pb[4]; ga[2] += t * b[4]; gb[4] += t * a[2]; }
-    { const T t = T(0.22617901315954025) * Pb[4]; ga[2] += t * b[6]; gb[6] += t * a[2]; }
-  }
-};
-template <> struct Couple3<3, 2, 0, 2> {
-  static constexpr int kTerms = 5;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[0] += T(0.2820947917738782) * (a[0] * b[0]);
-    P[1] += T(0.28209479177387831) * (a[1] * b[0]);
-    P[2] += T(0.28209479177387831) * (a[2] * b[0]);
-    P[3] += T(0.28209479177387831) * (a[3] * b[0]);
-    P[4] += T(0.28209479177387831) * (a[4] * b[0]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(0.2820947917738782) * Pb[0]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.28209479177387831) * Pb[1]; ga[1] += t * b[0]; gb[0] += t * a[1]; }
-    { const T t = T(0.28209479177387831) * Pb[2]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(0.28209479177387831) * Pb[3]; ga[3] += t * b[0]; gb[0] += t * a[3]; }
-    { const T t = T(0.28209479177387831) * Pb[4]; ga[4] += t * b[0]; gb[0] += t * a[4]; }
-  }
-};
-template <> struct Couple3<3, 2, 1, 1> {
-  static constexpr int kTerms = 11;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[0] += T(0.21850968611841587) * (a[0] * b[2]);
-    P[0] += T(0.21850968611841587) * (a[1] * b[1]);
-    P[0] += T(-0.12615662610100806) * (a[2] * b[0]);
-    P[0] += T(-0.2185096861184159) * (a[4] * b[0]);
-    P[1] += T(0.21850968611841587) * (a[1] * b[0]);
-    P[1] += T(0.252313252202016) * (a[2] * b[1]);
-    P[1] += T(0.21850968611841587) * (a[3] * b[2]);
-    P[2] += T(0.21850968611841587) * (a[0] * b[0]);
-    P[2] += T(-0.12615662610100806) * (a[2] * b[2]);
-    P[2] += T(0.21850968611841587) * (a[3] * b[1]);
-    P[2] += T(0.2185096861184159) * (a[4] * b[2]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(0.21850968611841587) * Pb[0]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(0.21850968611841587) * Pb[0]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(-0.12615662610100806) * Pb[0]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(-0.2185096861184159) * Pb[0]; ga[4] += t * b[0]; gb[0] += t * a[4]; }
-    { const T t = T(0.21850968611841587) * Pb[1]; ga[1] += t * b[0]; gb[0] += t * a[1]; }
-    { const T t = T(0.252313252202016) * Pb[1]; ga[2] += t * b[1]; gb[1] += t * a[2]; }
-    { const T t = T(0.21850968611841587) * Pb[1]; ga[3] += t * b[2]; gb[2] += t * a[3]; }
-    { const T t = T(0.21850968611841587) * Pb[2]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(-0.12615662610100806) * Pb[2]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(0.21850968611841587) * Pb[2]; ga[3] += t * b[1]; gb[1] += t * a[3]; }
-    { const T t = T(0.2185096861184159) * Pb[2]; ga[4] += t * b[2]; gb[2] += t * a[4]; }
-  }
-};
-template <> struct Couple3<3, 2, 1, 3> {
-  static constexpr int kTerms = 21;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[0] += T(0.22617901315954039) * (a[0] * b[2]);
-    P[0] += T(0.22617901315954023) * (a[4] * b[0]);
-    P[1] += T(0.18467439092237187) * (a[0] * b[1]);
-    P[1] += T(0.18467439092237189) * (a[1] * b[2]);
-    P[1] += T(0.18467439092237189) * (a[3] * b[0]);
-    P[2] += T(-0.058399170081901861) * (a[0] * b[2]);
-    P[2] += T(0.23359668032760758) * (a[1] * b[1]);
-    P[2] += T(0.20230065940342065) * (a[2] * b[0]);
-    P[2] += T(0.058399170081901729) * (a[4] * b[0]);
-    P[3] += T(-0.1430481681026689) * (a[1] * b[0]);
-    P[3] += T(0.24776669508347599) * (a[2] * b[1]);
-    P[3] += T(-0.1430481681026689) * (a[3] * b[2]);
-    P[4] += T(-0.058399170081901861) * (a[0] * b[0]);
-    P[4] += T(0.20230065940342065) * (a[2] * b[2]);
-    P[4] += T(0.23359668032760758) * (a[3] * b[1]);
-    P[4] += T(-0.058399170081901729) * (a[4] * b[2]);
-    P[5] += T(-0.18467439092237189) * (a[1] * b[0]);
-    P[5] += T(0.18467439092237189) * (a[3] * b[2]);
-    P[5] += T(0.18467439092237187) * (a[4] * b[1]);
-    P[6] += T(-0.22617901315954039) * (a[0] * b[0]);
-    P[6] += T(0.22617901315954023) * (a[4] * b[2]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(0.22617901315954039) * Pb[0]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(0.22617901315954023) * Pb[0]; ga[4] += t * b[0]; gb[0] += t * a[4]; }
-    { const T t = T(0.18467439092237187) * Pb[1]; ga[0] += t * b[1]; gb[1] += t * a[0]; }
-    { const T t = T(0.18467439092237189) * Pb[1]; ga[1] += t * b[2]; gb[2] += t * a[1]; }
-    { const T t = T(0.18467439092237189) * Pb[1]; ga[3] += t * b[0]; gb[0] += t * a[3]; }
-    { const T t = T(-0.058399170081901861) * Pb[2]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(0.23359668032760758) * Pb[2]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(0.20230065940342065) * Pb[2]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(0.058399170081901729) * Pb[2]; ga[4] += t * b[0]; gb[0] += t * a[4]; }
-    { const T t = T(-0.1430481681026689) * Pb[3]; ga[1] += t * b[0]; gb[0] += t * a[1]; }
-    { const T t = T(0.24776669508347599) * Pb[3]; ga[2] += t * b[1]; gb[1] += t * a[2]; }
-    { const T t = T(-0.1430481681026689) * Pb[3]; ga[3] += t * b[2]; gb[2] += t * a[3]; }
-    { const T t = T(-0.058399170081901861) * Pb[4]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.20230065940342065) * Pb[4]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(0.23359668032760758) * Pb[4]; ga[3] += t * b[1]; gb[1] += t * a[3]; }
-    { const T t = T(-0.058399170081901729) * Pb[4]; ga[4] += t * b[2]; gb[2] += t * a[4]; }
-    { const T t = T(-0.18467439092237189) * Pb[5]; ga[1] += t * b[0]; gb[0] += t * a[1]; }
-    { const T t = T(0.18467439092237189) * Pb[5]; ga[3] += t * b[2]; gb[2] += t * a[3]; }
-    { const T t = T(0.18467439092237187) * Pb[5]; ga[4] += t * b[1]; gb[1] += t * a[4]; }
-    { const T t = T(-0.22617901315954039) * Pb[6]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.22617901315954023) * Pb[6]; ga[4] += t * b[2]; gb[2] += t * a[4]; }
-  }
-};
-template <> struct Couple3<3, 2, 2, 0> {
-  static constexpr int kTerms = 5;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[0] += T(0.2820947917738782) * (a[0] * b[0]);
-    P[0] += T(0.28209479177387831) * (a[1] * b[1]);
-    P[0] += T(0.28209479177387831) * (a[2] * b[2]);
-    P[0] += T(0.28209479177387831) * (a[3] * b[3]);
-    P[0] += T(0.28209479177387831) * (a[4] * b[4]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(0.2820947917738782) * Pb[0]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.28209479177387831) * Pb[0]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(0.28209479177387831) * Pb[0]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(0.28209479177387831) * Pb[0]; ga[3] += t * b[3]; gb[3] += t * a[3]; }
-    { const T t = T(0.28209479177387831) * Pb[0]; ga[4] += t * b[4]; gb[4] += t * a[4]; }
-  }
-};
-template <> struct Couple3<3, 2, 2, 2> {
-  static constexpr int kTerms = 25;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[0] += T(-0.18022375157286874) * (a[0] * b[2]);
-    P[0] += T(0.15607834722743999) * (a[1] * b[3]);
-    P[0] += T(-0.18022375157286874) * (a[2] * b[0]);
-    P[0] += T(0.15607834722743999) * (a[3] * b[1]);
-    P[1] += T(0.15607834722743999) * (a[0] * b[3]);
-    P[1] += T(0.090111875786434384) * (a[1] * b[2]);
-    P[1] += T(-0.15607834722744002) * (a[1] * b[4]);
-    P[1] += T(0.090111875786434384) * (a[2] * b[1]);
-    P[1] += T(0.15607834722743999) * (a[3] * b[0]);
-    P[1] += T(-0.15607834722744002) * (a[4] * b[1]);
-    P[2] += T(-0.18022375157286874) * (a[0] * b[0]);
-    P[2] += T(0.090111875786434384) * (a[1] * b[1]);
-    P[2] += T(0.18022375157286855) * (a[2] * b[2]);
-    P[2] += T(0.090111875786434384) * (a[3] * b[3]);
-    P[2] += T(-0.18022375157286849) * (a[4] * b[4]);
-    P[3] += T(0.15607834722743999) * (a[0] * b[1]);
-    P[3] += T(0.15607834722743999) * (a[1] * b[0]);
-    P[3] += T(0.090111875786434384) * (a[2] * b[3]);
-    P[3] += T(0.090111875786434384) * (a[3] * b[2]);
-    P[3] += T(0.15607834722744002) * (a[3] * b[4]);
-    P[3] += T(0.15607834722744002) * (a[4] * b[3]);
-    P[4] += T(-0.15607834722744002) * (a[1] * b[1]);
-    P[4] += T(-0.18022375157286849) * (a[2] * b[4]);
-    P[4] += T(0.15607834722744002) * (a[3] * b[3]);
-    P[4] += T(-0.18022375157286849) * (a[4] * b[2]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(-0.18022375157286874) * Pb[0]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(0.15607834722743999) * Pb[0]; ga[1] += t * b[3]; gb[3] += t * a[1]; }
-    { const T t = T(-0.18022375157286874) * Pb[0]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(0.15607834722743999) * Pb[0]; ga[3] += t * b[1]; gb[1] += t * a[3]; }
-    { const T t = T(0.15607834722743999) * Pb[1]; ga[0] += t * b[3]; gb[3] += t * a[0]; }
-    { const T t = T(0.090111875786434384) * Pb[1]; ga[1] += t * b[2]; gb[2] += t * a[1]; }
-    { const T t = T(-0.15607834722744002) * Pb[1]; ga[1] += t * b[4]; gb[4] += t * a[1]; }
-    { const T t = T(0.090111875786434384) * Pb[1]; ga[2] += t * b[1]; gb[1] += t * a[2]; }
-    { const T t = T(0.15607834722743999) * Pb[1]; ga[3] += t * b[0]; gb[0] += t * a[3]; }
-    { const T t = T(-0.15607834722744002) * Pb[1]; ga[4] += t * b[1]; gb[1] += t * a[4]; }
-    { const T t = T(-0.18022375157286874) * Pb[2]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.090111875786434384) * Pb[2]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(0.18022375157286855) * Pb[2]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(0.090111875786434384) * Pb[2]; ga[3] += t * b[3]; gb[3] += t * a[3]; }
-    { const T t = T(-0.18022375157286849) * Pb[2]; ga[4] += t * b[4]; gb[4] += t * a[4]; }
-    { const T t = T(0.15607834722743999) * Pb[3]; ga[0] += t * b[1]; gb[1] += t * a[0]; }
-    { const T t = T(0.15607834722743999) * Pb[3]; ga[1] += t * b[0]; gb[0] += t * a[1]; }
-    { const T t = T(0.090111875786434384) * Pb[3]; ga[2] += t * b[3]; gb[3] += t * a[2]; }
-    { const T t = T(0.090111875786434384) * Pb[3]; ga[3] += t * b[2]; gb[2] += t * a[3]; }
-    { const T t = T(0.15607834722744002) * Pb[3]; ga[3] += t * b[4]; gb[4] += t * a[3]; }
-    { const T t = T(0.15607834722744002) * Pb[3]; ga[4] += t * b[3]; gb[3] += t * a[4]; }
-    { const T t = T(-0.15607834722744002) * Pb[4]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(-0.18022375157286849) * Pb[4]; ga[2] += t * b[4]; gb[4] += t * a[2]; }
-    { const T t = T(0.15607834722744002) * Pb[4]; ga[3] += t * b[3]; gb[3] += t * a[3]; }
-    { const T t = T(-0.18022375157286849) * Pb[4]; ga[4] += t * b[2]; gb[2] += t * a[4]; }
-  }
-};
-template <> struct Couple3<3, 2, 3, 1> {
-  static constexpr int kTerms = 21;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[0] += T(-0.058399170081901867) * (a[0] * b[4]);
-    P[0] += T(-0.22617901315954042) * (a[0] * b[6]);
-    P[0] += T(-0.1430481681026689) * (a[1] * b[3]);
-    P[0] += T(-0.18467439092237192) * (a[1] * b[5]);
-    P[0] += T(0.20230065940342068) * (a[2] * b[2]);
-    P[0] += T(0.18467439092237189) * (a[3] * b[1]);
-    P[0] += T(0.22617901315954025) * (a[4] * b[0]);
-    P[0] += T(0.058399170081901736) * (a[4] * b[2]);
-    P[1] += T(0.18467439092237187) * (a[0] * b[1]);
-    P[1] += T(0.23359668032760761) * (a[1] * b[2]);
-    P[1] += T(0.24776669508347601) * (a[2] * b[3]);
-    P[1] += T(0.23359668032760761) * (a[3] * b[4]);
-    P[1] += T(0.18467439092237187) * (a[4] * b[5]);
-    P[2] += T(0.22617901315954042) * (a[0] * b[0]);
-    P[2] += T(-0.058399170081901867) * (a[0] * b[2]);
-    P[2] += T(0.18467439092237189) * (a[1] * b[1]);
-    P[2] += T(0.20230065940342068) * (a[2] * b[4]);
-    P[2] += T(-0.1430481681026689) * (a[3] * b[3]);
-    P[2] += T(0.18467439092237192) * (a[3] * b[5]);
-    P[2] += T(-0.058399170081901736) * (a[4] * b[4]);
-    P[2] += T(0.22617901315954025) * (a[4] * b[6]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(-0.058399170081901867) * Pb[0]; ga[0] += t * b[4]; gb[4] += t * a[0]; }
-    { const T t = T(-0.22617901315954042) * Pb[0]; ga[0] += t * b[6]; gb[6] += t * a[0]; }
-    { const T t = T(-0.1430481681026689) * Pb[0]; ga[1] += t * b[3]; gb[3] += t * a[1]; }
-    { const T t = T(-0.18467439092237192) * Pb[0]; ga[1] += t * b[5]; gb[5] += t * a[1]; }
-    { const T t = T(0.20230065940342068) * Pb[0]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(0.18467439092237189) * Pb[0]; ga[3] += t * b[1]; gb[1] += t * a[3]; }
-    { const T t = T(0.22617901315954025) * Pb[0]; ga[4] += t * b[0]; gb[0] += t * a[4]; }
-    { const T t = T(0.058399170081901736) * Pb[0]; ga[4] += t * b[2]; gb[2] += t * a[4]; }
-    { const T t = T(0.18467439092237187) * Pb[1]; ga[0] += t * b[1]; gb[1] += t * a[0]; }
-    { const T t = T(0.23359668032760761) * Pb[1]; ga[1] += t * b[2]; gb[2] += t * a[1]; }
-    { const T t = T(0.24776669508347601) * Pb[1]; ga[2] += t * b[3]; gb[3] += t * a[2]; }
-    { const T t = T(0.23359668032760761) * Pb[1]; ga[3] += t * b[4]; gb[4] += t * a[3]; }
-    { const T t = T(0.18467439092237187) * Pb[1]; ga[4] += t * b[5]; gb[5] += t * a[4]; }
-    { const T t = T(0.22617901315954042) * Pb[2]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(-0.058399170081901867) * Pb[2]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(0.18467439092237189) * Pb[2]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(0.20230065940342068) * Pb[2]; ga[2] += t * b[4]; gb[4] += t * a[2]; }
-    { const T t = T(-0.1430481681026689) * Pb[2]; ga[3] += t * b[3]; gb[3] += t * a[3]; }
-    { const T t = T(0.18467439092237192) * Pb[2]; ga[3] += t * b[5]; gb[5] += t * a[3]; }
-    { const T t = T(-0.058399170081901736) * Pb[2]; ga[4] += t * b[4]; gb[4] += t * a[4]; }
-    { const T t = T(0.22617901315954025) * Pb[2]; ga[4] += t * b[6]; gb[6] += t * a[4]; }
-  }
-};
-template <> struct Couple3<3, 2, 3, 3> {
-  static constexpr int kTerms = 41;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[0] += T(-0.094031597257959357) * (a[0] * b[4]);
-    P[0] += T(0.14867700967939756) * (a[1] * b[5]);
-    P[0] += T(-0.21026104350168001) * (a[2] * b[0]);
-    P[0] += T(0.14867700967939765) * (a[3] * b[1]);
-    P[0] += T(-0.094031597257959315) * (a[4] * b[2]);
-    P[1] += T(-0.1880631945159188) * (a[0] * b[3]);
-    P[1] += T(0.11516471649044524) * (a[1] * b[4]);
-    P[1] += T(-0.14867700967939765) * (a[1] * b[6]);
-    P[1] += T(0.14867700967939765) * (a[3] * b[0]);
-    P[1] += T(0.11516471649044524) * (a[3] * b[2]);
-    P[2] += T(0.14567312407894392) * (a[0] * b[4]);
-    P[2] += T(0.094031597257959329) * (a[0] * b[6]);
-    P[2] += T(0.059470803871758834) * (a[1] * b[3]);
-    P[2] += T(-0.1151647164904453) * (a[1] * b[5]);
-    P[2] += T(0.12615662610100786) * (a[2] * b[2]);
-    P[2] += T(0.11516471649044524) * (a[3] * b[1]);
-    P[2] += T(-0.094031597257959357) * (a[4] * b[0]);
-    P[2] += T(-0.14567312407894395) * (a[4] * b[2]);
-    P[3] += T(-0.1880631945159188) * (a[0] * b[1]);
-    P[3] += T(0.059470803871758834) * (a[1] * b[2]);
-    P[3] += T(0.16820883480134416) * (a[2] * b[3]);
-    P[3] += T(0.059470803871758827) * (a[3] * b[4]);
-    P[3] += T(-0.18806319451591863) * (a[4] * b[5]);
-    P[4] += T(-0.094031597257959315) * (a[0] * b[0]);
-    P[4] += T(0.14567312407894392) * (a[0] * b[2]);
-    P[4] += T(0.11516471649044524) * (a[1] * b[1]);
-    P[4] += T(0.12615662610100786) * (a[2] * b[4]);
-    P[4] += T(0.059470803871758827) * (a[3] * b[3]);
-    P[4] += T(0.11516471649044534) * (a[3] * b[5]);
-    P[4] += T(0.14567312407894398) * (a[4] * b[4]);
-    P[4] += T(-0.094031597257959357) * (a[4] * b[6]);
-    P[5] += T(0.14867700967939756) * (a[1] * b[0]);
-    P[5] += T(-0.1151647164904453) * (a[1] * b[2]);
-    P[5] += T(0.1151647164904453) * (a[3] * b[4]);
-    P[5] += T(0.14867700967939756) * (a[3] * b[6]);
-    P[5] += T(-0.18806319451591863) * (a[4] * b[3]);
-    P[6] += T(0.094031597257959357) * (a[0] * b[2]);
-    P[6] += T(-0.14867700967939765) * (a[1] * b[1]);
-    P[6] += T(-0.21026104350168001) * (a[2] * b[6]);
-    P[6] += T(0.14867700967939756) * (a[3] * b[5]);
-    P[6] += T(-0.094031597257959315) * (a[4] * b[4]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(-0.094031597257959357) * Pb[0]; ga[0] += t * b[4]; gb[4] += t * a[0]; }
-    { const T t = T(0.14867700967939756) * Pb[0]; ga[1] += t * b[5]; gb[5] += t * a[1]; }
-    { const T t = T(-0.21026104350168001) * Pb[0]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(0.14867700967939765) * Pb[0]; ga[3] += t * b[1]; gb[1] += t * a[3]; }
-    { const T t = T(-0.094031597257959315) * Pb[0]; ga[4] += t * b[2]; gb[2] += t * a[4]; }
-    { const T t = T(-0.1880631945159188) * Pb[1]; ga[0] += t * b[3]; gb[3] += t * a[0]; }
-    { const T t = T(0.11516471649044524) * Pb[1]; ga[1] += t * b[4]; gb[4] += t * a[1]; }
-    { const T t = T(-0.14867700967939765) * Pb[1]; ga[1] += t * b[6]; gb[6] += t * a[1]; }
-    { const T t = T(0.14867700967939765) * Pb[1]; ga[3] += t * b[0]; gb[0] += t * a[3]; }
-    { const T t = T(0.11516471649044524) * Pb[1]; ga[3] += t * b[2]; gb[2] += t * a[3]; }
-    { const T t = T(0.14567312407894392) * Pb[2]; ga[0] += t * b[4]; gb[4] += t * a[0]; }
-    { const T t = T(0.094031597257959329) * Pb[2]; ga[0] += t * b[6]; gb[6] += t * a[0]; }
-    { const T t = T(0.059470803871758834) * Pb[2]; ga[1] += t * b[3]; gb[3] += t * a[1]; }
-    { const T t = T(-0.1151647164904453) * Pb[2]; ga[1] += t * b[5]; gb[5] += t * a[1]; }
-    { const T t = T(0.12615662610100786) * Pb[2]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(0.11516471649044524) * Pb[2]; ga[3] += t * b[1]; gb[1] += t * a[3]; }
-    { const T t = T(-0.094031597257959357) * Pb[2]; ga[4] += t * b[0]; gb[0] += t * a[4]; }
-    { const T t = T(-0.14567312407894395) * Pb[2]; ga[4] += t * b[2]; gb[2] += t * a[4]; }
-    { const T t = T(-0.1880631945159188) * Pb[3]; ga[0] += t * b[1]; gb[1] += t * a[0]; }
-    { const T t = T(0.059470803871758834) * Pb[3]; ga[1] += t * b[2]; gb[2] += t * a[1]; }
-    { const T t = T(0.16820883480134416) * Pb[3]; ga[2] += t * b[3]; gb[3] += t * a[2]; }
-    { const T t = T(0.059470803871758827) * Pb[3]; ga[3] += t * b[4]; gb[4] += t * a[3]; }
-    { const T t = T(-0.18806319451591863) * Pb[3]; ga[4] += t * b[5]; gb[5] += t * a[4]; }
-    { const T t = T(-0.094031597257959315) * Pb[4]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.14567312407894392) * Pb[4]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(0.11516471649044524) * Pb[4]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(0.12615662610100786) * Pb[4]; ga[2] += t * b[4]; gb[4] += t * a[2]; }
-    { const T t = T(0.059470803871758827) * Pb[4]; ga[3] += t * b[3]; gb[3] += t * a[3]; }
-    { const T t = T(0.11516471649044534) * Pb[4]; ga[3] += t * b[5]; gb[5] += t * a[3]; }
-    { const T t = T(0.14567312407894398) * Pb[4]; ga[4] += t * b[4]; gb[4] += t * a[4]; }
-    { const T t = T(-0.094031597257959357) * Pb[4]; ga[4] += t * b[6]; gb[6] += t * a[4]; }
-    { const T t = T(0.14867700967939756) * Pb[5]; ga[1] += t * b[0]; gb[0] += t * a[1]; }
-    { const T t = T(-0.1151647164904453) * Pb[5]; ga[1] += t * b[2]; gb[2] += t * a[1]; }
-    { const T t = T(0.1151647164904453) * Pb[5]; ga[3] += t * b[4]; gb[4] += t * a[3]; }
-    { const T t = T(0.14867700967939756) * Pb[5]; ga[3] += t * b[6]; gb[6] += t * a[3]; }
-    { const T t = T(-0.18806319451591863) * Pb[5]; ga[4] += t * b[3]; gb[3] += t * a[4]; }
-    { const T t = T(0.094031597257959357) * Pb[6]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(-0.14867700967939765) * Pb[6]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(-0.21026104350168001) * Pb[6]; ga[2] += t * b[6]; gb[6] += t * a[2]; }
-    { const T t = T(0.14867700967939756) * Pb[6]; ga[3] += t * b[5]; gb[5] += t * a[3]; }
-    { const T t = T(-0.094031597257959315) * Pb[6]; ga[4] += t * b[4]; gb[4] += t * a[4]; }
-  }
-};
-template <> struct Couple3<3, 3, 0, 3> {
-  static constexpr int kTerms = 7;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[0] += T(0.2820947917738782) * (a[0] * b[0]);
-    P[1] += T(0.2820947917738782) * (a[1] * b[0]);
-    P[2] += T(0.28209479177387825) * (a[2] * b[0]);
-    P[3] += T(0.28209479177387814) * (a[3] * b[0]);
-    P[4] += T(0.28209479177387825) * (a[4] * b[0]);
-    P[5] += T(0.28209479177387825) * (a[5] * b[0]);
-    P[6] += T(0.2820947917738782) * (a[6] * b[0]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(0.2820947917738782) * Pb[0]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.2820947917738782) * Pb[1]; ga[1] += t * b[0]; gb[0] += t * a[1]; }
-    { const T t = T(0.28209479177387825) * Pb[2]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(0.28209479177387814) * Pb[3]; ga[3] += t * b[0]; gb[0] += t * a[3]; }
-    { const T t = T(0.28209479177387825) * Pb[4]; ga[4] += t * b[0]; gb[0] += t * a[4]; }
-    { const T t = T(0.28209479177387825) * Pb[5]; ga[5] += t * b[0]; gb[0] += t * a[5]; }
-    { const T t = T(0.2820947917738782) * Pb[6]; ga[6] += t * b[0]; gb[0] += t * a[6]; }
-  }
-};
-template <> struct Couple3<3, 3, 1, 2> {
-  static constexpr int kTerms = 21;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[0] += T(0.22617901315954042) * (a[0] * b[2]);
-    P[0] += T(0.18467439092237187) * (a[1] * b[1]);
-    P[0] += T(-0.058399170081901867) * (a[2] * b[2]);
-    P[0] += T(-0.058399170081901867) * (a[4] * b[0]);
-    P[0] += T(-0.22617901315954042) * (a[6] * b[0]);
-    P[1] += T(0.18467439092237189) * (a[1] * b[2]);
-    P[1] += T(0.23359668032760761) * (a[2] * b[1]);
-    P[1] += T(-0.1430481681026689) * (a[3] * b[0]);
-    P[1] += T(-0.18467439092237192) * (a[5] * b[0]);
-    P[2] += T(0.20230065940342068) * (a[2] * b[0]);
-    P[2] += T(0.24776669508347601) * (a[3] * b[1]);
-    P[2] += T(0.20230065940342068) * (a[4] * b[2]);
-    P[3] += T(0.18467439092237189) * (a[1] * b[0]);
-    P[3] += T(-0.1430481681026689) * (a[3] * b[2]);
-    P[3] += T(0.23359668032760761) * (a[4] * b[1]);
-    P[3] += T(0.18467439092237192) * (a[5] * b[2]);
-    P[4] += T(0.22617901315954025) * (a[0] * b[0]);
-    P[4] += T(0.058399170081901736) * (a[2] * b[0]);
-    P[4] += T(-0.058399170081901736) * (a[4] * b[2]);
-    P[4] += T(0.18467439092237187) * (a[5] * b[1]);
-    P[4] += T(0.22617901315954025) * (a[6] * b[2]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(0.22617901315954042) * Pb[0]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(0.18467439092237187) * Pb[0]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(-0.058399170081901867) * Pb[0]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(-0.058399170081901867) * Pb[0]; ga[4] += t * b[0]; gb[0] += t * a[4]; }
-    { const T t = T(-0.22617901315954042) * Pb[0]; ga[6] += t * b[0]; gb[0] += t * a[6]; }
-    { const T t = T(0.18467439092237189) * Pb[1]; ga[1] += t * b[2]; gb[2] += t * a[1]; }
-    { const T t = T(0.23359668032760761) * Pb[1]; ga[2] += t * b[1]; gb[1] += t * a[2]; }
-    { const T t = T(-0.1430481681026689) * Pb[1]; ga[3] += t * b[0]; gb[0] += t * a[3]; }
-    { const T t = T(-0.18467439092237192) * Pb[1]; ga[5] += t * b[0]; gb[0] += t * a[5]; }
-    { const T t = T(0.20230065940342068) * Pb[2]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(0.24776669508347601) * Pb[2]; ga[3] += t * b[1]; gb[1] += t * a[3]; }
-    { const T t = T(0.20230065940342068) * Pb[2]; ga[4] += t * b[2]; gb[2] += t * a[4]; }
-    { const T t = T(0.18467439092237189) * Pb[3]; ga[1] += t * b[0]; gb[0] += t * a[1]; }
-    { const T t = T(-0.1430481681026689) * Pb[3]; ga[3] += t * b[2]; gb[2] += t * a[3]; }
-    { const T t = T(0.23359668032760761) * Pb[3]; ga[4] += t * b[1]; gb[1] += t * a[4]; }
-    { const T t = T(0.18467439092237192) * Pb[3]; ga[5] += t * b[2]; gb[2] += t * a[5]; }
-    { const T t = T(0.22617901315954025) * Pb[4]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.058399170081901736) * Pb[4]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(-0.058399170081901736) * Pb[4]; ga[4] += t * b[2]; gb[2] += t * a[4]; }
-    { const T t = T(0.18467439092237187) * Pb[4]; ga[5] += t * b[1]; gb[1] += t * a[5]; }
-    { const T t = T(0.22617901315954025) * Pb[4]; ga[6] += t * b[2]; gb[2] += t * a[6]; }
-  }
-};
-template <> struct Couple3<3, 3, 2, 1> {
-  static constexpr int kTerms = 21;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[0] += T(0.22617901315954025) * (a[0] * b[4]);
-    P[0] += T(0.18467439092237189) * (a[1] * b[3]);
-    P[0] += T(0.20230065940342068) * (a[2] * b[2]);
-    P[0] += T(0.058399170081901736) * (a[2] * b[4]);
-    P[0] += T(-0.1430481681026689) * (a[3] * b[1]);
-    P[0] += T(-0.058399170081901867) * (a[4] * b[0]);
-    P[0] += T(-0.18467439092237192) * (a[5] * b[1]);
-    P[0] += T(-0.22617901315954042) * (a[6] * b[0]);
-    P[1] += T(0.18467439092237187) * (a[1] * b[0]);
-    P[1] += T(0.23359668032760761) * (a[2] * b[1]);
-    P[1] += T(0.24776669508347601) * (a[3] * b[2]);
-    P[1] += T(0.23359668032760761) * (a[4] * b[3]);
-    P[1] += T(0.18467439092237187) * (a[5] * b[4]);
-    P[2] += T(0.22617901315954042) * (a[0] * b[0]);
-    P[2] += T(0.18467439092237189) * (a[1] * b[1]);
-    P[2] += T(-0.058399170081901867) * (a[2] * b[0]);
-    P[2] += T(-0.1430481681026689) * (a[3] * b[3]);
-    P[2] += T(0.20230065940342068) * (a[4] * b[2]);
-    P[2] += T(-0.058399170081901736) * (a[4] * b[4]);
-    P[2] += T(0.18467439092237192) * (a[5] * b[3]);
-    P[2] += T(0.22617901315954025) * (a[6] * b[4]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(0.22617901315954025) * Pb[0]; ga[0] += t * b[4]; gb[4] += t * a[0]; }
-    { const T t = T(0.18467439092237189) * Pb[0]; ga[1] += t * b[3]; gb[3] += t * a[1]; }
-    { const T t = T(0.20230065940342068) * Pb[0]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(0.058399170081901736) * Pb[0]; ga[2] += t * b[4]; gb[4] += t * a[2]; }
-    { const T t = T(-0.1430481681026689) * Pb[0]; ga[3] += t * b[1]; gb[1] += t * a[3]; }
-    { const T t = T(-0.058399170081901867) * Pb[0]; ga[4] += t * b[0]; gb[0] += t * a[4]; }
-    { const T t = T(-0.18467439092237192) * Pb[0]; ga[5] += t * b[1]; gb[1] += t * a[5]; }
-    { const T t = T(-0.22617901315954042) * Pb[0]; ga[6] += t * b[0]; gb[0] += t * a[6]; }
-    { const T t = T(0.18467439092237187) * Pb[1]; ga[1] += t * b[0]; gb[0] += t * a[1]; }
-    { const T t = T(0.23359668032760761) * Pb[1]; ga[2] += t * b[1]; gb[1] += t * a[2]; }
-    { const T t = T(0.24776669508347601) * Pb[1]; ga[3] += t * b[2]; gb[2] += t * a[3]; }
-    { const T t = T(0.23359668032760761) * Pb[1]; ga[4] += t * b[3]; gb[3] += t * a[4]; }
-    { const T t = T(0.18467439092237187) * Pb[1]; ga[5] += t * b[4]; gb[4] += t * a[5]; }
-    { const T t = T(0.22617901315954042) * Pb[2]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.18467439092237189) * Pb[2]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(-0.058399170081901867) * Pb[2]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(-0.1430481681026689) * Pb[2]; ga[3] += t * b[3]; gb[3] += t * a[3]; }
-    { const T t = T(0.20230065940342068) * Pb[2]; ga[4] += t * b[2]; gb[2] += t * a[4]; }
-    { const T t = T(-0.058399170081901736) * Pb[2]; ga[4] += t * b[4]; gb[4] += t * a[4]; }
-    { const T t = T(0.18467439092237192) * Pb[2]; ga[5] += t * b[3]; gb[3] += t * a[5]; }
-    { const T t = T(0.22617901315954025) * Pb[2]; ga[6] += t * b[4]; gb[4] += t * a[6]; }
-  }
-};
-template <> struct Couple3<3, 3, 2, 3> {
-  static constexpr int kTerms = 41;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[0] += T(-0.21026104350168001) * (a[0] * b[2]);
-    P[0] += T(0.14867700967939765) * (a[1] * b[3]);
-    P[0] += T(-0.094031597257959315) * (a[2] * b[4]);
-    P[0] += T(-0.094031597257959357) * (a[4] * b[0]);
-    P[0] += T(0.14867700967939756) * (a[5] * b[1]);
-    P[1] += T(0.14867700967939765) * (a[0] * b[3]);
-    P[1] += T(0.11516471649044524) * (a[2] * b[3]);
-    P[1] += T(-0.1880631945159188) * (a[3] * b[0]);
-    P[1] += T(0.11516471649044524) * (a[4] * b[1]);
-    P[1] += T(-0.14867700967939765) * (a[6] * b[1]);
-    P[2] += T(-0.094031597257959357) * (a[0] * b[4]);
-    P[2] += T(0.11516471649044524) * (a[1] * b[3]);
-    P[2] += T(0.12615662610100786) * (a[2] * b[2]);
-    P[2] += T(-0.14567312407894395) * (a[2] * b[4]);
-    P[2] += T(0.059470803871758834) * (a[3] * b[1]);
-    P[2] += T(0.14567312407894392) * (a[4] * b[0]);
-    P[2] += T(-0.1151647164904453) * (a[5] * b[1]);
-    P[2] += T(0.094031597257959329) * (a[6] * b[0]);
-    P[3] += T(-0.1880631945159188) * (a[1] * b[0]);
-    P[3] += T(0.059470803871758834) * (a[2] * b[1]);
-    P[3] += T(0.16820883480134416) * (a[3] * b[2]);
-    P[3] += T(0.059470803871758827) * (a[4] * b[3]);
-    P[3] += T(-0.18806319451591863) * (a[5] * b[4]);
-    P[4] += T(-0.094031597257959315) * (a[0] * b[0]);
-    P[4] += T(0.11516471649044524) * (a[1] * b[1]);
-    P[4] += T(0.14567312407894392) * (a[2] * b[0]);
-    P[4] += T(0.059470803871758827) * (a[3] * b[3]);
-    P[4] += T(0.12615662610100786) * (a[4] * b[2]);
-    P[4] += T(0.14567312407894398) * (a[4] * b[4]);
-    P[4] += T(0.11516471649044534) * (a[5] * b[3]);
-    P[4] += T(-0.094031597257959357) * (a[6] * b[4]);
-    P[5] += T(0.14867700967939756) * (a[0] * b[1]);
-    P[5] += T(-0.1151647164904453) * (a[2] * b[1]);
-    P[5] += T(-0.18806319451591863) * (a[3] * b[4]);
-    P[5] += T(0.1151647164904453) * (a[4] * b[3]);
-    P[5] += T(0.14867700967939756) * (a[6] * b[3]);
-    P[6] += T(-0.14867700967939765) * (a[1] * b[1]);
-    P[6] += T(0.094031597257959357) * (a[2] * b[0]);
-    P[6] += T(-0.094031597257959315) * (a[4] * b[4]);
-    P[6] += T(0.14867700967939756) * (a[5] * b[3]);
-    P[6] += T(-0.21026104350168001) * (a[6] * b[2]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(-0.21026104350168001) * Pb[0]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(0.14867700967939765) * Pb[0]; ga[1] += t * b[3]; gb[3] += t * a[1]; }
-    { const T t = T(-0.094031597257959315) * Pb[0]; ga[2] += t * b[4]; gb[4] += t * a[2]; }
-    { const T t = T(-0.094031597257959357) * Pb[0]; ga[4] += t * b[0]; gb[0] += t * a[4]; }
-    { const T t = T(0.14867700967939756) * Pb[0]; ga[5] += t * b[1]; gb[1] += t * a[5]; }
-    { const T t = T(0.14867700967939765) * Pb[1]; ga[0] += t * b[3]; gb[3] += t * a[0]; }
-    { const T t = T(0.11516471649044524) * Pb[1]; ga[2] += t * b[3]; gb[3] += t * a[2]; }
-    { const T t = T(-0.1880631945159188) * Pb[1]; ga[3] += t * b[0]; gb[0] += t * a[3]; }
-    { const T t = T(0.11516471649044524) * Pb[1]; ga[4] += t * b[1]; gb[1] += t * a[4]; }
-    { const T t = T(-0.14867700967939765) * Pb[1]; ga[6] += t * b[1]; gb[1] += t * a[6]; }
-    { const T t = T(-0.094031597257959357) * Pb[2]; ga[0] += t * b[4]; gb[4] += t * a[0]; }
-    { const T t = T(0.11516471649044524) * Pb[2]; ga[1] += t * b[3]; gb[3] += t * a[1]; }
-    { const T t = T(0.12615662610100786) * Pb[2]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(-0.14567312407894395) * Pb[2]; ga[2] += t * b[4]; gb[4] += t * a[2]; }
-    { const T t = T(0.059470803871758834) * Pb[2]; ga[3] += t * b[1]; gb[1] += t * a[3]; }
-    { const T t = T(0.14567312407894392) * Pb[2]; ga[4] += t * b[0]; gb[0] += t * a[4]; }
-    { const T t = T(-0.1151647164904453) * Pb[2]; ga[5] += t * b[1]; gb[1] += t * a[5]; }
-    { const T t = T(0.094031597257959329) * Pb[2]; ga[6] += t * b[0]; gb[0] += t * a[6]; }
-    { const T t = T(-0.1880631945159188) * Pb[3]; ga[1] += t * b[0]; gb[0] += t * a[1]; }
-    { const T t = T(0.059470803871758834) * Pb[3]; ga[2] += t * b[1]; gb[1] += t * a[2]; }
-    { const T t = T(0.16820883480134416) * Pb[3]; ga[3] += t * b[2]; gb[2] += t * a[3]; }
-    { const T t = T(0.059470803871758827) * Pb[3]; ga[4] += t * b[3]; gb[3] += t * a[4]; }
-    { const T t = T(-0.18806319451591863) * Pb[3]; ga[5] += t * b[4]; gb[4] += t * a[5]; }
-    { const T t = T(-0.094031597257959315) * Pb[4]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.11516471649044524) * Pb[4]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(0.14567312407894392) * Pb[4]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(0.059470803871758827) * Pb[4]; ga[3] += t * b[3]; gb[3] += t * a[3]; }
-    { const T t = T(0.12615662610100786) * Pb[4]; ga[4] += t * b[2]; gb[2] += t * a[4]; }
-    { const T t = T(0.14567312407894398) * Pb[4]; ga[4] += t * b[4]; gb[4] += t * a[4]; }
-    { const T t = T(0.11516471649044534) * Pb[4]; ga[5] += t * b[3]; gb[3] += t * a[5]; }
-    { const T t = T(-0.094031597257959357) * Pb[4]; ga[6] += t * b[4]; gb[4] += t * a[6]; }
-    { const T t = T(0.14867700967939756) * Pb[5]; ga[0] += t * b[1]; gb[1] += t * a[0]; }
-    { const T t = T(-0.1151647164904453) * Pb[5]; ga[2] += t * b[1]; gb[1] += t * a[2]; }
-    { const T t = T(-0.18806319451591863) * Pb[5]; ga[3] += t * b[4]; gb[4] += t * a[3]; }
-    { const T t = T(0.1151647164904453) * Pb[5]; ga[4] += t * b[3]; gb[3] += t * a[4]; }
-    { const T t = T(0.14867700967939756) * Pb[5]; ga[6] += t * b[3]; gb[3] += t * a[6]; }
-    { const T t = T(-0.14867700967939765) * Pb[6]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(0.094031597257959357) * Pb[6]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(-0.094031597257959315) * Pb[6]; ga[4] += t * b[4]; gb[4] += t * a[4]; }
-    { const T t = T(0.14867700967939756) * Pb[6]; ga[5] += t * b[3]; gb[3] += t * a[5]; }
-    { const T t = T(-0.21026104350168001) * Pb[6]; ga[6] += t * b[2]; gb[2] += t * a[6]; }
-  }
-};
-template <> struct Couple3<3, 3, 3, 0> {
-  static constexpr int kTerms = 7;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[0] += T(0.2820947917738782) * (a[0] * b[0]);
-    P[0] += T(0.2820947917738782) * (a[1] * b[1]);
-    P[0] += T(0.28209479177387825) * (a[2] * b[2]);
-    P[0] += T(0.28209479177387814) * (a[3] * b[3]);
-    P[0] += T(0.28209479177387825) * (a[4] * b[4]);
-    P[0] += T(0.28209479177387825) * (a[5] * b[5]);
-    P[0] += T(0.2820947917738782) * (a[6] * b[6]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(0.2820947917738782) * Pb[0]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.2820947917738782) * Pb[0]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(0.28209479177387825) * Pb[0]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(0.28209479177387814) * Pb[0]; ga[3] += t * b[3]; gb[3] += t * a[3]; }
-    { const T t = T(0.28209479177387825) * Pb[0]; ga[4] += t * b[4]; gb[4] += t * a[4]; }
-    { const T t = T(0.28209479177387825) * Pb[0]; ga[5] += t * b[5]; gb[5] += t * a[5]; }
-    { const T t = T(0.2820947917738782) * Pb[0]; ga[6] += t * b[6]; gb[6] += t * a[6]; }
-  }
-};
-template <> struct Couple3<3, 3, 3, 2> {
-  static constexpr int kTerms = 41;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[0] += T(-0.094031597257959357) * (a[0] * b[4]);
-    P[0] += T(-0.1880631945159188) * (a[1] * b[3]);
-    P[0] += T(0.14567312407894387) * (a[2] * b[4]);
-    P[0] += T(0.094031597257959357) * (a[2] * b[6]);
-    P[0] += T(-0.1880631945159188) * (a[3] * b[1]);
-    P[0] += T(-0.094031597257959357) * (a[4] * b[0]);
-    P[0] += T(0.14567312407894387) * (a[4] * b[2]);
-    P[0] += T(0.094031597257959357) * (a[6] * b[2]);
-    P[1] += T(0.14867700967939754) * (a[0] * b[5]);
-    P[1] += T(0.11516471649044524) * (a[1] * b[4]);
-    P[1] += T(-0.14867700967939765) * (a[1] * b[6]);
-    P[1] += T(0.0594708038717588) * (a[2] * b[3]);
-    P[1] += T(-0.1151647164904453) * (a[2] * b[5]);
-    P[1] += T(0.0594708038717588) * (a[3] * b[2]);
-    P[1] += T(0.11516471649044524) * (a[4] * b[1]);
-    P[1] += T(0.14867700967939754) * (a[5] * b[0]);
-    P[1] += T(-0.1151647164904453) * (a[5] * b[2]);
-    P[1] += T(-0.14867700967939765) * (a[6] * b[1]);
-    P[2] += T(-0.21026104350168001) * (a[0] * b[0]);
-    P[2] += T(0.12615662610100786) * (a[2] * b[2]);
-    P[2] += T(0.16820883480134416) * (a[3] * b[3]);
-    P[2] += T(0.12615662610100786) * (a[4] * b[4]);
-    P[2] += T(-0.21026104350168001) * (a[6] * b[6]);
-    P[3] += T(0.14867700967939765) * (a[0] * b[1]);
-    P[3] += T(0.14867700967939765) * (a[1] * b[0]);
-    P[3] += T(0.11516471649044524) * (a[1] * b[2]);
-    P[3] += T(0.11516471649044524) * (a[2] * b[1]);
-    P[3] += T(0.059470803871758765) * (a[3] * b[4]);
-    P[3] += T(0.059470803871758765) * (a[4] * b[3]);
-    P[3] += T(0.1151647164904453) * (a[4] * b[5]);
-    P[3] += T(0.11516471649044534) * (a[5] * b[4]);
-    P[3] += T(0.14867700967939754) * (a[5] * b[6]);
-    P[3] += T(0.14867700967939754) * (a[6] * b[5]);
-    P[4] += T(-0.094031597257959357) * (a[0] * b[2]);
-    P[4] += T(-0.094031597257959357) * (a[2] * b[0]);
-    P[4] += T(-0.14567312407894392) * (a[2] * b[2]);
-    P[4] += T(-0.18806319451591855) * (a[3] * b[5]);
-    P[4] += T(0.14567312407894392) * (a[4] * b[4]);
-    P[4] += T(-0.094031597257959371) * (a[4] * b[6]);
-    P[4] += T(-0.1880631945159186) * (a[5] * b[3]);
-    P[4] += T(-0.094031597257959357) * (a[6] * b[4]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(-0.094031597257959357) * Pb[0]; ga[0] += t * b[4]; gb[4] += t * a[0]; }
-    { const T t = T(-0.1880631945159188) * Pb[0]; ga[1] += t * b[3]; gb[3] += t * a[1]; }
-    { const T t = T(0.14567312407894387) * Pb[0]; ga[2] += t * b[4]; gb[4] += t * a[2]; }
-    { const T t = T(0.094031597257959357) * Pb[0]; ga[2] += t * b[6]; gb[6] += t * a[2]; }
-    { const T t = T(-0.1880631945159188) * Pb[0]; ga[3] += t * b[1]; gb[1] += t * a[3]; }
-    { const T t = T(-0.094031597257959357) * Pb[0]; ga[4] += t * b[0]; gb[0] += t * a[4]; }
-    { const T t = T(0.14567312407894387) * Pb[0]; ga[4] += t * b[2]; gb[2] += t * a[4]; }
-    { const T t = T(0.094031597257959357) * Pb[0]; ga[6] += t * b[2]; gb[2] += t * a[6]; }
-    { const T t = T(0.14867700967939754) * Pb[1]; ga[0] += t * b[5]; gb[5] += t * a[0]; }
-    { const T t = T(0.11516471649044524) * Pb[1]; ga[1] += t * b[4]; gb[4] += t * a[1]; }
-    { const T t = T(-0.14867700967939765) * Pb[1]; ga[1] += t * b[6]; gb[6] += t * a[1]; }
-    { const T t = T(0.0594708038717588) * Pb[1]; ga[2] += t * b[3]; gb[3] += t * a[2]; }
-    { const T t = T(-0.1151647164904453) * Pb[1]; ga[2] += t * b[5]; gb[5] += t * a[2]; }
-    { const T t = T(0.0594708038717588) * Pb[1]; ga[3] += t * b[2]; gb[2] += t * a[3]; }
-    { const T t = T(0.11516471649044524) * Pb[1]; ga[4] += t * b[1]; gb[1] += t * a[4]; }
-    { const T t = T(0.14867700967939754) * Pb[1]; ga[5] += t * b[0]; gb[0] += t * a[5]; }
-    { const T t = T(-0.1151647164904453) * Pb[1]; ga[5] += t * b[2]; gb[2] += t * a[5]; }
-    { const T t = T(-0.14867700967939765) * Pb[1]; ga[6] += t * b[1]; gb[1] += t * a[6]; }
-    { const T t = T(-0.21026104350168001) * Pb[2]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.12615662610100786) * Pb[2]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(0.16820883480134416) * Pb[2]; ga[3] += t * b[3]; gb[3] += t * a[3]; }
-    { const T t = T(0.12615662610100786) * Pb[2]; ga[4] += t * b[4]; gb[4] += t * a[4]; }
-    { const T t = T(-0.21026104350168001) * Pb[2]; ga[6] += t * b[6]; gb[6] += t * a[6]; }
-    { const T t = T(0.14867700967939765) * Pb[3]; ga[0] += t * b[1]; gb[1] += t * a[0]; }
-    { const T t = T(0.14867700967939765) * Pb[3]; ga[1] += t * b[0]; gb[0] += t * a[1]; }
-    { const T t = T(0.11516471649044524) * Pb[3]; ga[1] += t * b[2]; gb[2] += t * a[1]; }
-    { const T t = T(0.11516471649044524) * Pb[3]; ga[2] += t * b[1]; gb[1] += t * a[2]; }
-    { const T t = T(0.059470803871758765) * Pb[3]; ga[3] += t * b[4]; gb[4] += t * a[3]; }
-    { const T t = T(0.059470803871758765) * Pb[3]; ga[4] += t * b[3]; gb[3] += t * a[4]; }
-    { const T t = T(0.1151647164904453) * Pb[3]; ga[4] += t * b[5]; gb[5] += t * a[4]; }
-    { const T t = T(0.11516471649044534) * Pb[3]; ga[5] += t * b[4]; gb[4] += t * a[5]; }
-    { const T t = T(0.14867700967939754) * Pb[3]; ga[5] += t * b[6]; gb[6] += t * a[5]; }
-    { const T t = T(0.14867700967939754) * Pb[3]; ga[6] += t * b[5]; gb[5] += t * a[6]; }
-    { const T t = T(-0.094031597257959357) * Pb[4]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(-0.094031597257959357) * Pb[4]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(-0.14567312407894392) * Pb[4]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(-0.18806319451591855) * Pb[4]; ga[3] += t * b[5]; gb[5] += t * a[3]; }
-    { const T t = T(0.14567312407894392) * Pb[4]; ga[4] += t * b[4]; gb[4] += t * a[4]; }
-    { const T t = T(-0.094031597257959371) * Pb[4]; ga[4] += t * b[6]; gb[6] += t * a[4]; }
-    { const T t = T(-0.1880631945159186) * Pb[4]; ga[5] += t * b[3]; gb[3] += t * a[5]; }
-    { const T t = T(-0.094031597257959357) * Pb[4]; ga[6] += t * b[4]; gb[4] += t * a[6]; }
-  }
-};
-template <> struct Couple3<4, 0, 0, 0> {
-  static constexpr int kTerms = 1;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[0] += T(0.28209479177387803) * (a[0] * b[0]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(0.28209479177387803) * Pb[0]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-  }
-};
-template <> struct Couple3<4, 0, 1, 1> {
-  static constexpr int kTerms = 3;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[0] += T(0.28209479177387808) * (a[0] * b[0]);
-    P[1] += T(0.28209479177387808) * (a[0] * b[1]);
-    P[2] += T(0.28209479177387808) * (a[0] * b[2]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(0.28209479177387808) * Pb[0]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.28209479177387808) * Pb[1]; ga[0] += t * b[1]; gb[1] += t * a[0]; }
-    { const T t = T(0.28209479177387808) * Pb[2]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-  }
-};
-template <> struct Couple3<4, 0, 2, 2> {
-  static constexpr int kTerms = 5;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[0] += T(0.2820947917738782) * (a[0] * b[0]);
-    P[1] += T(0.28209479177387831) * (a[0] * b[1]);
-    P[2] += T(0.28209479177387831) * (a[0] * b[2]);
-    P[3] += T(0.28209479177387831) * (a[0] * b[3]);
-    P[4] += T(0.28209479177387831) * (a[0] * b[4]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(0.2820947917738782) * Pb[0]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.28209479177387831) * Pb[1]; ga[0] += t * b[1]; gb[1] += t * a[0]; }
-    { const T t = T(0.28209479177387831) * Pb[2]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(0.28209479177387831) * Pb[3]; ga[0] += t * b[3]; gb[3] += t * a[0]; }
-    { const T t = T(0.28209479177387831) * Pb[4]; ga[0] += t * b[4]; gb[4] += t * a[0]; }
-  }
-};
-template <> struct Couple3<4, 0, 3, 3> {
-  static constexpr int kTerms = 7;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[0] += T(0.2820947917738782) * (a[0] * b[0]);
-    P[1] += T(0.2820947917738782) * (a[0] * b[1]);
-    P[2] += T(0.28209479177387825) * (a[0] * b[2]);
-    P[3] += T(0.28209479177387814) * (a[0] * b[3]);
-    P[4] += T(0.28209479177387825) * (a[0] * b[4]);
-    P[5] += T(0.28209479177387825) * (a[0] * b[5]);
-    P[6] += T(0.2820947917738782) * (a[0] * b[6]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(0.2820947917738782) * Pb[0]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.2820947917738782) * Pb[1]; ga[0] += t * b[1]; gb[1] += t * a[0]; }
-    { const T t = T(0.28209479177387825) * Pb[2]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(0.28209479177387814) * Pb[3]; ga[0] += t * b[3]; gb[3] += t * a[0]; }
-    { const T t = T(0.28209479177387825) * Pb[4]; ga[0] += t * b[4]; gb[4] += t * a[0]; }
-    { const T t = T(0.28209479177387825) * Pb[5]; ga[0] += t * b[5]; gb[5] += t * a[0]; }
-    { const T t = T(0.2820947917738782) * Pb[6]; ga[0] += t * b[6]; gb[6] += t * a[0]; }
-  }
-};
-template <> struct Couple3<4, 0, 4, 4> {
-  static constexpr int kTerms = 9;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[0] += T(0.28209479177387781) * (a[0] * b[0]);
-    P[1] += T(0.28209479177387808) * (a[0] * b[1]);
-    P[2] += T(0.2820947917738782) * (a[0] * b[2]);
-    P[3] += T(0.28209479177387786) * (a[0] * b[3]);
-    P[4] += T(0.28209479177387836) * (a[0] * b[4]);
-    P[5] += T(0.28209479177387781) * (a[0] * b[5]);
-    P[6] += T(0.2820947917738782) * (a[0] * b[6]);
-    P[7] += T(0.28209479177387808) * (a[0] * b[7]);
-    P[8] += T(0.28209479177387825) * (a[0] * b[8]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(0.28209479177387781) * Pb[0]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.28209479177387808) * Pb[1]; ga[0] += t * b[1]; gb[1] += t * a[0]; }
-    { const T t = T(0.2820947917738782) * Pb[2]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(0.28209479177387786) * Pb[3]; ga[0] += t * b[3]; gb[3] += t * a[0]; }
-    { const T t = T(0.28209479177387836) * Pb[4]; ga[0] += t * b[4]; gb[4] += t * a[0]; }
-    { const T t = T(0.28209479177387781) * Pb[5]; ga[0] += t * b[5]; gb[5] += t * a[0]; }
-    { const T t = T(0.2820947917738782) * Pb[6]; ga[0] += t * b[6]; gb[6] += t * a[0]; }
-    { const T t = T(0.28209479177387808) * Pb[7]; ga[0] += t * b[7]; gb[7] += t * a[0]; }
-    { const T t = T(0.28209479177387825) * Pb[8]; ga[0] += t * b[8]; gb[8] += t * a[0]; }
-  }
-};
-template <> struct Couple3<4, 1, 0, 1> {
-  static constexpr int kTerms = 3;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[0] += T(0.28209479177387808) * (a[0] * b[0]);
-    P[1] += T(0.28209479177387808) * (a[1] * b[0]);
-    P[2] += T(0.28209479177387808) * (a[2] * b[0]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(0.28209479177387808) * Pb[0]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.28209479177387808) * Pb[1]; ga[1] += t * b[0]; gb[0] += t * a[1]; }
-    { const T t = T(0.28209479177387808) * Pb[2]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-  }
-};
-template <> struct Couple3<4, 1, 1, 0> {
-  static constexpr int kTerms = 3;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[0] += T(0.28209479177387803) * (a[0] * b[0]);
-    P[0] += T(0.28209479177387803) * (a[1] * b[1]);
-    P[0] += T(0.28209479177387803) * (a[2] * b[2]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(0.28209479177387803) * Pb[0]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.28209479177387803) * Pb[0]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(0.28209479177387803) * Pb[0]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-  }
-};
-template <> struct Couple3<4, 1, 1, 2> {
-  static constexpr int kTerms = 11;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[0] += T(0.21850968611841587) * (a[0] * b[2]);
-    P[0] += T(0.21850968611841587) * (a[2] * b[0]);
-    P[1] += T(0.21850968611841587) * (a[0] * b[1]);
-    P[1] += T(0.21850968611841587) * (a[1] * b[0]);
-    P[2] += T(-0.12615662610100806) * (a[0] * b[0]);
-    P[2] += T(0.252313252202016) * (a[1] * b[1]);
-    P[2] += T(-0.12615662610100806) * (a[2] * b[2]);
-    P[3] += T(0.21850968611841587) * (a[1] * b[2]);
-    P[3] += T(0.21850968611841587) * (a[2] * b[1]);
-    P[4] += T(-0.2185096861184159) * (a[0] * b[0]);
-    P[4] += T(0.2185096861184159) * (a[2] * b[2]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(0.21850968611841587) * Pb[0]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(0.21850968611841587) * Pb[0]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(0.21850968611841587) * Pb[1]; ga[0] += t * b[1]; gb[1] += t * a[0]; }
-    { const T t = T(0.21850968611841587) * Pb[1]; ga[1] += t * b[0]; gb[0] += t * a[1]; }
-    { const T t = T(-0.12615662610100806) * Pb[2]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.252313252202016) * Pb[2]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(-0.12615662610100806) * Pb[2]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(0.21850968611841587) * Pb[3]; ga[1] += t * b[2]; gb[2] += t * a[1]; }
-    { const T t = T(0.21850968611841587) * Pb[3]; ga[2] += t * b[1]; gb[1] += t * a[2]; }
-    { const T t = T(-0.2185096861184159) * Pb[4]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.2185096861184159) * Pb[4]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-  }
-};
-template <> struct Couple3<4, 1, 2, 1> {
-  static constexpr int kTerms = 11;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[0] += T(-0.12615662610100806) * (a[0] * b[2]);
-    P[0] += T(-0.2185096861184159) * (a[0] * b[4]);
-    P[0] += T(0.21850968611841587) * (a[1] * b[1]);
-    P[0] += T(0.21850968611841587) * (a[2] * b[0]);
-    P[1] += T(0.21850968611841587) * (a[0] * b[1]);
-    P[1] += T(0.252313252202016) * (a[1] * b[2]);
-    P[1] += T(0.21850968611841587) * (a[2] * b[3]);
-    P[2] += T(0.21850968611841587) * (a[0] * b[0]);
-    P[2] += T(0.21850968611841587) * (a[1] * b[3]);
-    P[2] += T(-0.12615662610100806) * (a[2] * b[2]);
-    P[2] += T(0.2185096861184159) * (a[2] * b[4]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(-0.12615662610100806) * Pb[0]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(-0.2185096861184159) * Pb[0]; ga[0] += t * b[4]; gb[4] += t * a[0]; }
-    { const T t = T(0.21850968611841587) * Pb[0]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(0.21850968611841587) * Pb[0]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(0.21850968611841587) * Pb[1]; ga[0] += t * b[1]; gb[1] += t * a[0]; }
-    { const T t = T(0.252313252202016) * Pb[1]; ga[1] += t * b[2]; gb[2] += t * a[1]; }
-    { const T t = T(0.21850968611841587) * Pb[1]; ga[2] += t * b[3]; gb[3] += t * a[2]; }
-    { const T t = T(0.21850968611841587) * Pb[2]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.21850968611841587) * Pb[2]; ga[1] += t * b[3]; gb[3] += t * a[1]; }
-    { const T t = T(-0.12615662610100806) * Pb[2]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(0.2185096861184159) * Pb[2]; ga[2] += t * b[4]; gb[4] += t * a[2]; }
-  }
-};
-template <> struct Couple3<4, 1, 2, 3> {
-  static constexpr int kTerms = 21;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[0] += T(0.22617901315954023) * (a[0] * b[4]);
-    P[0] += T(0.22617901315954039) * (a[2] * b[0]);
-    P[1] += T(0.18467439092237189) * (a[0] * b[3]);
-    P[1] += T(0.18467439092237187) * (a[1] * b[0]);
-    P[1] += T(0.18467439092237189) * (a[2] * b[1]);
-    P[2] += T(0.20230065940342065) * (a[0] * b[2]);
-    P[2] += T(0.058399170081901729) * (a[0] * b[4]);
-    P[2] += T(0.23359668032760758) * (a[1] * b[1]);
-    P[2] += T(-0.058399170081901861) * (a[2] * b[0]);
-    P[3] += T(-0.1430481681026689) * (a[0] * b[1]);
-    P[3] += T(0.24776669508347599) * (a[1] * b[2]);
-    P[3] += T(-0.1430481681026689) * (a[2] * b[3]);
-    P[4] += T(-0.058399170081901861) * (a[0] * b[0]);
-    P[4] += T(0.23359668032760758) * (a[1] * b[3]);
-    P[4] += T(0.20230065940342065) * (a[2] * b[2]);
-    P[4] += T(-0.058399170081901729) * (a[2] * b[4]);
-    P[5] += T(-0.18467439092237189) * (a[0] * b[1]);
-    P[5] += T(0.18467439092237187) * (a[1] * b[4]);
-    P[5] += T(0.18467439092237189) * (a[2] * b[3]);
-    P[6] += T(-0.22617901315954039) * (a[0] * b[0]);
-    P[6] += T(0.22617901315954023) * (a[2] * b[4]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(0.22617901315954023) * Pb[0]; ga[0] += t * b[4]; gb[4] += t * a[0]; }
-    { const T t = T(0.22617901315954039) * Pb[0]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(0.18467439092237189) * Pb[1]; ga[0] += t * b[3]; gb[3] += t * a[0]; }
-    { const T t = T(0.18467439092237187) * Pb[1]; ga[1] += t * b[0]; gb[0] += t * a[1]; }
-    { const T t = T(0.18467439092237189) * Pb[1]; ga[2] += t * b[1]; gb[1] += t * a[2]; }
-    { const T t = T(0.20230065940342065) * Pb[2]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(0.058399170081901729) * Pb[2]; ga[0] += t * b[4]; gb[4] += t * a[0]; }
-    { const T t = T(0.23359668032760758) * Pb[2]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(-0.058399170081901861) * Pb[2]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(-0.1430481681026689) * Pb[3]; ga[0] += t * b[1]; gb[1] += t * a[0]; }
-    { const T t = T(0.24776669508347599) * Pb[3]; ga[1] += t * b[2]; gb[2] += t * a[1]; }
-    { const T t = T(-0.1430481681026689) * Pb[3]; ga[2] += t * b[3]; gb[3] += t * a[2]; }
-    { const T t = T(-0.058399170081901861) * Pb[4]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.23359668032760758) * Pb[4]; ga[1] += t * b[3]; gb[3] += t * a[1]; }
-    { const T t = T(0.20230065940342065) * Pb[4]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(-0.058399170081901729) * Pb[4]; ga[2] += t * b[4]; gb[4] += t * a[2]; }
-    { const T t = T(-0.18467439092237189) * Pb[5]; ga[0] += t * b[1]; gb[1] += t * a[0]; }
-    { const T t = T(0.18467439092237187) * Pb[5]; ga[1] += t * b[4]; gb[4] += t * a[1]; }
-    { const T t = T(0.18467439092237189) * Pb[5]; ga[2] += t * b[3]; gb[3] += t * a[2]; }
-    { const T t = T(-0.22617901315954039) * Pb[6]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.22617901315954023) * Pb[6]; ga[2] += t * b[4]; gb[4] += t * a[2]; }
-  }
-};
-template <> struct Couple3<4, 1, 3, 2> {
-  static constexpr int kTerms = 21;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[0] += T(-0.058399170081901867) * (a[0] * b[4]);
-    P[0] += T(-0.22617901315954042) * (a[0] * b[6]);
-    P[0] += T(0.18467439092237187) * (a[1] * b[1]);
-    P[0] += T(0.22617901315954042) * (a[2] * b[0]);
-    P[0] += T(-0.058399170081901867) * (a[2] * b[2]);
-    P[1] += T(-0.1430481681026689) * (a[0] * b[3]);
-    P[1] += T(-0.18467439092237192) * (a[0] * b[5]);
-    P[1] += T(0.23359668032760761) * (a[1] * b[2]);
-    P[1] += T(0.18467439092237189) * (a[2] * b[1]);
-    P[2] += T(0.20230065940342068) * (a[0] * b[2]);
-    P[2] += T(0.24776669508347601) * (a[1] * b[3]);
-    P[2] += T(0.20230065940342068) * (a[2] * b[4]);
-    P[3] += T(0.18467439092237189) * (a[0] * b[1]);
-    P[3] += T(0.23359668032760761) * (a[1] * b[4]);
-    P[3] += T(-0.1430481681026689) * (a[2] * b[3]);
-    P[3] += T(0.18467439092237192) * (a[2] * b[5]);
-    P[4] += T(0.22617901315954025) * (a[0] * b[0]);
-    P[4] += T(0.058399170081901736) * (a[0] * b[2]);
-    P[4] += T(0.18467439092237187) * (a[1] * b[5]);
-    P[4] += T(-0.058399170081901736) * (a[2] * b[4]);
-    P[4] += T(0.22617901315954025) * (a[2] * b[6]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(-0.058399170081901867) * Pb[0]; ga[0] += t * b[4]; gb[4] += t * a[0]; }
-    { const T t = T(-0.22617901315954042) * Pb[0]; ga[0] += t * b[6]; gb[6] += t * a[0]; }
-    { const T t = T(0.18467439092237187) * Pb[0]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(0.22617901315954042) * Pb[0]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(-0.058399170081901867) * Pb[0]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(-0.1430481681026689) * Pb[1]; ga[0] += t * b[3]; gb[3] += t * a[0]; }
-    { const T t = T(-0.18467439092237192) * Pb[1]; ga[0] += t * b[5]; gb[5] += t * a[0]; }
-    { const T t = T(0.23359668032760761) * Pb[1]; ga[1] += t * b[2]; gb[2] += t * a[1]; }
-    { const T t = T(0.18467439092237189) * Pb[1]; ga[2] += t * b[1]; gb[1] += t * a[2]; }
-    { const T t = T(0.20230065940342068) * Pb[2]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(0.24776669508347601) * Pb[2]; ga[1] += t * b[3]; gb[3] += t * a[1]; }
-    { const T t = T(0.20230065940342068) * Pb[2]; ga[2] += t * b[4]; gb[4] += t * a[2]; }
-    { const T t = T(0.18467439092237189) * Pb[3]; ga[0] += t * b[1]; gb[1] += t * a[0]; }
-    { const T t = T(0.23359668032760761) * Pb[3]; ga[1] += t * b[4]; gb[4] += t * a[1]; }
-    { const T t = T(-0.1430481681026689) * Pb[3]; ga[2] += t * b[3]; gb[3] += t * a[2]; }
-    { const T t = T(0.18467439092237192) * Pb[3]; ga[2] += t * b[5]; gb[5] += t * a[2]; }
-    { const T t = T(0.22617901315954025) * Pb[4]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.058399170081901736) * Pb[4]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(0.18467439092237187) * Pb[4]; ga[1] += t * b[5]; gb[5] += t * a[1]; }
-    { const T t = T(-0.058399170081901736) * Pb[4]; ga[2] += t * b[4]; gb[4] += t * a[2]; }
-    { const T t = T(0.22617901315954025) * Pb[4]; ga[2] += t * b[6]; gb[6] += t * a[2]; }
-  }
-};
-template <> struct Couple3<4, 1, 3, 4> {
-  static constexpr int kTerms = 31;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[0] += T(0.2303294329808902) * (a[0] * b[6]);
-    P[0] += T(0.2303294329808902) * (a[2] * b[0]);
-    P[1] += T(0.19947114020071624) * (a[0] * b[5]);
-    P[1] += T(0.16286750396763999) * (a[1] * b[0]);
-    P[1] += T(0.19947114020071635) * (a[2] * b[1]);
-    P[2] += T(0.16858388283618392) * (a[0] * b[4]);
-    P[2] += T(0.043528171377568134) * (a[0] * b[6]);
-    P[2] += T(0.21324361862292318) * (a[1] * b[1]);
-    P[2] += T(-0.043528171377568134) * (a[2] * b[0]);
-    P[2] += T(0.16858388283618392) * (a[2] * b[2]);
-    P[3] += T(0.19466390027300595) * (a[0] * b[3]);
-    P[3] += T(0.075393004386513349) * (a[0] * b[5]);
-    P[3] += T(0.23841361350444787) * (a[1] * b[2]);
-    P[3] += T(-0.075393004386513446) * (a[2] * b[1]);
-    P[4] += T(-0.150786008773027) * (a[0] * b[2]);
-    P[4] += T(0.24623252122982925) * (a[1] * b[3]);
-    P[4] += T(-0.150786008773027) * (a[2] * b[4]);
-    P[5] += T(-0.075393004386513446) * (a[0] * b[1]);
-    P[5] += T(0.23841361350444781) * (a[1] * b[4]);
-    P[5] += T(0.19466390027300595) * (a[2] * b[3]);
-    P[5] += T(-0.075393004386513335) * (a[2] * b[5]);
-    P[6] += T(-0.043528171377568189) * (a[0] * b[0]);
-    P[6] += T(-0.16858388283618395) * (a[0] * b[2]);
-    P[6] += T(0.21324361862292318) * (a[1] * b[5]);
-    P[6] += T(0.16858388283618395) * (a[2] * b[4]);
-    P[6] += T(-0.043528171377568182) * (a[2] * b[6]);
-    P[7] += T(-0.19947114020071635) * (a[0] * b[1]);
-    P[7] += T(0.16286750396763999) * (a[1] * b[6]);
-    P[7] += T(0.19947114020071624) * (a[2] * b[5]);
-    P[8] += T(-0.23032943298089051) * (a[0] * b[0]);
-    P[8] += T(0.23032943298089054) * (a[2] * b[6]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(0.2303294329808902) * Pb[0]; ga[0] += t * b[6]; gb[6] += t * a[0]; }
-    { const T t = T(0.2303294329808902) * Pb[0]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(0.19947114020071624) * Pb[1]; ga[0] += t * b[5]; gb[5] += t * a[0]; }
-    { const T t = T(0.16286750396763999) * Pb[1]; ga[1] += t * b[0]; gb[0] += t * a[1]; }
-    { const T t = T(0.19947114020071635) * Pb[1]; ga[2] += t * b[1]; gb[1] += t * a[2]; }
-    { const T t = T(0.16858388283618392) * Pb[2]; ga[0] += t * b[4]; gb[4] += t * a[0]; }
-    { const T t = T(0.043528171377568134) * Pb[2]; ga[0] += t * b[6]; gb[6] += t * a[0]; }
-    { const T t = T(0.21324361862292318) * Pb[2]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(-0.043528171377568134) * Pb[2]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(0.16858388283618392) * Pb[2]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(0.19466390027300595) * Pb[3]; ga[0] += t * b[3]; gb[3] += t * a[0]; }
-    { const T t = T(0.075393004386513349) * Pb[3]; ga[0] += t * b[5]; gb[5] += t * a[0]; }
-    { const T t = T(0.23841361350444787) * Pb[3]; ga[1] += t * b[2]; gb[2] += t * a[1]; }
-    { const T t = T(-0.075393004386513446) * Pb[3]; ga[2] += t * b[1]; gb[1] += t * a[2]; }
-    { const T t = T(-0.150786008773027) * Pb[4]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(0.24623252122982925) * Pb[4]; ga[1] += t * b[3]; gb[3] += t * a[1]; }
-    { const T t = T(-0.150786008773027) * Pb[4]; ga[2] += t * b[4]; gb[4] += t * a[2]; }
-    { const T t = T(-0.075393004386513446) * Pb[5]; ga[0] += t * b[1]; gb[1] += t * a[0]; }
-    { const T t = T(0.23841361350444781) * Pb[5]; ga[1] += t * b[4]; gb[4] += t * a[1]; }
-    { const T t = T(0.19466390027300595) * Pb[5]; ga[2] += t * b[3]; gb[3] += t * a[2]; }
-    { const T t = T(-0.075393004386513335) * Pb[5]; ga[2] += t * b[5]; gb[5] += t * a[2]; }
-    { const T t = T(-0.043528171377568189) * Pb[6]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(-0.16858388283618395) * Pb[6]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(0.21324361862292318) * Pb[6]; ga[1] += t * b[5]; gb[5] += t * a[1]; }
-    { const T t = T(0.16858388283618395) * Pb[6]; ga[2] += t * b[4]; gb[4] += t * a[2]; }
-    { const T t = T(-0.043528171377568182) * Pb[6]; ga[2] += t * b[6]; gb[6] += t * a[2]; }
-    { const T t = T(-0.19947114020071635) * Pb[7]; ga[0] += t * b[1]; gb[1] += t * a[0]; }
-    { const T t = T(0.16286750396763999) * Pb[7]; ga[1] += t * b[6]; gb[6] += t * a[1]; }
-    { const T t = T(0.19947114020071624) * Pb[7]; ga[2] += t * b[5]; gb[5] += t * a[2]; }
-    { const T t = T(-0.23032943298089051) * Pb[8]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.23032943298089054) * Pb[8]; ga[2] += t * b[6]; gb[6] += t * a[2]; }
-  }
-};
-template <> struct Couple3<4, 1, 4, 3> {
-  static constexpr int kTerms = 31;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[0] += T(-0.043528171377568169) * (a[0] * b[6]);
-    P[0] += T(-0.23032943298089051) * (a[0] * b[8]);
-    P[0] += T(0.16286750396763999) * (a[1] * b[1]);
-    P[0] += T(0.2303294329808902) * (a[2] * b[0]);
-    P[0] += T(-0.043528171377568134) * (a[2] * b[2]);
-    P[1] += T(-0.075393004386513446) * (a[0] * b[5]);
-    P[1] += T(-0.19947114020071635) * (a[0] * b[7]);
-    P[1] += T(0.21324361862292318) * (a[1] * b[2]);
-    P[1] += T(0.19947114020071635) * (a[2] * b[1]);
-    P[1] += T(-0.075393004386513446) * (a[2] * b[3]);
-    P[2] += T(-0.150786008773027) * (a[0] * b[4]);
-    P[2] += T(-0.16858388283618395) * (a[0] * b[6]);
-    P[2] += T(0.23841361350444787) * (a[1] * b[3]);
-    P[2] += T(0.16858388283618392) * (a[2] * b[2]);
-    P[3] += T(0.19466390027300595) * (a[0] * b[3]);
-    P[3] += T(0.24623252122982925) * (a[1] * b[4]);
-    P[3] += T(0.19466390027300595) * (a[2] * b[5]);
-    P[4] += T(0.16858388283618392) * (a[0] * b[2]);
-    P[4] += T(0.23841361350444781) * (a[1] * b[5]);
-    P[4] += T(-0.150786008773027) * (a[2] * b[4]);
-    P[4] += T(0.16858388283618397) * (a[2] * b[6]);
-    P[5] += T(0.19947114020071624) * (a[0] * b[1]);
-    P[5] += T(0.075393004386513349) * (a[0] * b[3]);
-    P[5] += T(0.21324361862292313) * (a[1] * b[6]);
-    P[5] += T(-0.075393004386513335) * (a[2] * b[5]);
-    P[5] += T(0.19947114020071624) * (a[2] * b[7]);
-    P[6] += T(0.2303294329808902) * (a[0] * b[0]);
-    P[6] += T(0.043528171377568155) * (a[0] * b[2]);
-    P[6] += T(0.16286750396763999) * (a[1] * b[7]);
-    P[6] += T(-0.043528171377568182) * (a[2] * b[6]);
-    P[6] += T(0.23032943298089054) * (a[2] * b[8]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(-0.043528171377568169) * Pb[0]; ga[0] += t * b[6]; gb[6] += t * a[0]; }
-    { const T t = T(-0.23032943298089051) * Pb[0]; ga[0] += t * b[8]; gb[8] += t * a[0]; }
-    { const T t = T(0.16286750396763999) * Pb[0]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(0.2303294329808902) * Pb[0]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(-0.043528171377568134) * Pb[0]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(-0.075393004386513446) * Pb[1]; ga[0] += t * b[5]; gb[5] += t * a[0]; }
-    { const T t = T(-0.19947114020071635) * Pb[1]; ga[0] += t * b[7]; gb[7] += t * a[0]; }
-    { const T t = T(0.21324361862292318) * Pb[1]; ga[1] += t * b[2]; gb[2] += t * a[1]; }
-    { const T t = T(0.19947114020071635) * Pb[1]; ga[2] += t * b[1]; gb[1] += t * a[2]; }
-    { const T t = T(-0.075393004386513446) * Pb[1]; ga[2] += t * b[3]; gb[3] += t * a[2]; }
-    { const T t = T(-0.150786008773027) * Pb[2]; ga[0] += t * b[4]; gb[4] += t * a[0]; }
-    { const T t = T(-0.16858388283618395) * Pb[2]; ga[0] += t * b[6]; gb[6] += t * a[0]; }
-    { const T t = T(0.23841361350444787) * Pb[2]; ga[1] += t * b[3]; gb[3] += t * a[1]; }
-    { const T t = T(0.16858388283618392) * Pb[2]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(0.19466390027300595) * Pb[3]; ga[0] += t * b[3]; gb[3] += t * a[0]; }
-    { const T t = T(0.24623252122982925) * Pb[3]; ga[1] += t * b[4]; gb[4] += t * a[1]; }
-    { const T t = T(0.19466390027300595) * Pb[3]; ga[2] += t * b[5]; gb[5] += t * a[2]; }
-    { const T t = T(0.16858388283618392) * Pb[4]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(0.23841361350444781) * Pb[4]; ga[1] += t * b[5]; gb[5] += t * a[1]; }
-    { const T t = T(-0.150786008773027) * Pb[4]; ga[2] += t * b[4]; gb[4] += t * a[2]; }
-    { const T t = T(0.16858388283618397) * Pb[4]; ga[2] += t * b[6]; gb[6] += t * a[2]; }
-    { const T t = T(0.19947114020071624) * Pb[5]; ga[0] += t * b[1]; gb[1] += t * a[0]; }
-    { const T t = T(0.075393004386513349) * Pb[5]; ga[0] += t * b[3]; gb[3] += t * a[0]; }
-    { const T t = T(0.21324361862292313) * Pb[5]; ga[1] += t * b[6]; gb[6] += t * a[1]; }
-    { const T t = T(-0.075393004386513335) * Pb[5]; ga[2] += t * b[5]; gb[5] += t * a[2]; }
-    { const T t = T(0.19947114020071624) * Pb[5]; ga[2] += t * b[7]; gb[7] += t * a[2]; }
-    { const T t = T(0.2303294329808902) * Pb[6]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.043528171377568155) * Pb[6]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(0.16286750396763999) * Pb[6]; ga[1] += t * b[7]; gb[7] += t * a[1]; }
-    { const T t = T(-0.043528171377568182) * Pb[6]; ga[2] += t * b[6]; gb[6] += t * a[2]; }
-    { const T t = T(0.23032943298089054) * Pb[6]; ga[2] += t * b[8]; gb[8] += t * a[2]; }
-  }
-};
-template <> struct Couple3<4, 2, 0, 2> {
-  static constexpr int kTerms = 5;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[0] += T(0.2820947917738782) * (a[0] * b[0]);
-    P[1] += T(0.28209479177387831) * (a[1] * b[0]);
-    P[2] += T(0.28209479177387831) * (a[2] * b[0]);
-    P[3] += T(0.28209479177387831) * (a[3] * b[0]);
-    P[4] += T(0.28209479177387831) * (a[4] * b[0]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(0.2820947917738782) * Pb[0]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.28209479177387831) * Pb[1]; ga[1] += t * b[0]; gb[0] += t * a[1]; }
-    { const T t = T(0.28209479177387831) * Pb[2]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(0.28209479177387831) * Pb[3]; ga[3] += t * b[0]; gb[0] += t * a[3]; }
-    { const T t = T(0.28209479177387831) * Pb[4]; ga[4] += t * b[0]; gb[0] += t * a[4]; }
-  }
-};
-template <> struct Couple3<4, 2, 1, 1> {
-  static constexpr int kTerms = 11;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[0] += T(0.21850968611841587) * (a[0] * b[2]);
-    P[0] += T(0.21850968611841587) * (a[1] * b[1]);
-    P[0] += T(-0.12615662610100806) * (a[2] * b[0]);
-    P[0] += T(-0.2185096861184159) * (a[4] * b[0]);
-    P[1] += T(0.21850968611841587) * (a[1] * b[0]);
-    P[1] += T(0.252313252202016) * (a[2] * b[1]);
-    P[1] += T(0.21850968611841587) * (a[3] * b[2]);
-    P[2] += T(0.21850968611841587) * (a[0] * b[0]);
-    P[2] += T(-0.12615662610100806) * (a[2] * b[2]);
-    P[2] += T(0.21850968611841587) * (a[3] * b[1]);
-    P[2] += T(0.2185096861184159) * (a[4] * b[2]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(0.21850968611841587) * Pb[0]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(0.21850968611841587) * Pb[0]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(-0.12615662610100806) * Pb[0]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(-0.2185096861184159) * Pb[0]; ga[4] += t * b[0]; gb[0] += t * a[4]; }
-    { const T t = T(0.21850968611841587) * Pb[1]; ga[1] += t * b[0]; gb[0] += t * a[1]; }
-    { const T t = T(0.252313252202016) * Pb[1]; ga[2] += t * b[1]; gb[1] += t * a[2]; }
-    { const T t = T(0.21850968611841587) * Pb[1]; ga[3] += t * b[2]; gb[2] += t * a[3]; }
-    { const T t = T(0.21850968611841587) * Pb[2]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(-0.12615662610100806) * Pb[2]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(0.21850968611841587) * Pb[2]; ga[3] += t * b[1]; gb[1] += t * a[3]; }
-    { const T t = T(0.2185096861184159) * Pb[2]; ga[4] += t * b[2]; gb[2] += t * a[4]; }
-  }
-};
-template <> struct Couple3<4, 2, 1, 3> {
-  static constexpr int kTerms = 21;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[0] += T(0.22617901315954039) * (a[0] * b[2]);
-    P[0] += T(0.22617901315954023) * (a[4] * b[0]);
-    P[1] += T(0.18467439092237187) * (a[0] * b[1]);
-    P[1] += T(0.18467439092237189) * (a[1] * b[2]);
-    P[1] += T(0.18467439092237189) * (a[3] * b[0]);
-    P[2] += T(-0.058399170081901861) * (a[0] * b[2]);
-    P[2] += T(0.23359668032760758) * (a[1] * b[1]);
-    P[2] += T(0.20230065940342065) * (a[2] * b[0]);
-    P[2] += T(0.058399170081901729) * (a[4] * b[0]);
-    P[3] += T(-0.1430481681026689) * (a[1] * b[0]);
-    P[3] += T(0.24776669508347599) * (a[2] * b[1]);
-    P[3] += T(-0.1430481681026689) * (a[3] * b[2]);
-    P[4] += T(-0.058399170081901861) * (a[0] * b[0]);
-    P[4] += T(0.20230065940342065) * (a[2] * b[2]);
-    P[4] += T(0.23359668032760758) * (a[3] * b[1]);
-    P[4] += T(-0.058399170081901729) * (a[4] * b[2]);
-    P[5] += T(-0.18467439092237189) * (a[1] * b[0]);
-    P[5] += T(0.18467439092237189) * (a[3] * b[2]);
-    P[5] += T(0.18467439092237187) * (a[4] * b[1]);
-    P[6] += T(-0.22617901315954039) * (a[0] * b[0]);
-    P[6] += T(0.22617901315954023) * (a[4] * b[2]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(0.22617901315954039) * Pb[0]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(0.22617901315954023) * Pb[0]; ga[4] += t * b[0]; gb[0] += t * a[4]; }
-    { const T t = T(0.18467439092237187) * Pb[1]; ga[0] += t * b[1]; gb[1] += t * a[0]; }
-    { const T t = T(0.18467439092237189) * Pb[1]; ga[1] += t * b[2]; gb[2] += t * a[1]; }
-    { const T t = T(0.18467439092237189) * Pb[1]; ga[3] += t * b[0]; gb[0] += t * a[3]; }
-    { const T t = T(-0.058399170081901861) * Pb[2]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(0.23359668032760758) * Pb[2]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(0.20230065940342065) * Pb[2]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(0.058399170081901729) * Pb[2]; ga[4] += t * b[0]; gb[0] += t * a[4]; }
-    { const T t = T(-0.1430481681026689) * Pb[3]; ga[1] += t * b[0]; gb[0] += t * a[1]; }
-    { const T t = T(0.24776669508347599) * Pb[3]; ga[2] += t * b[1]; gb[1] += t * a[2]; }
-    { const T t = T(-0.1430481681026689) * Pb[3]; ga[3] += t * b[2]; gb[2] += t * a[3]; }
-    { const T t = T(-0.058399170081901861) * Pb[4]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.20230065940342065) * Pb[4]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(0.23359668032760758) * Pb[4]; ga[3] += t * b[1]; gb[1] += t * a[3]; }
-    { const T t = T(-0.058399170081901729) * Pb[4]; ga[4] += t * b[2]; gb[2] += t * a[4]; }
-    { const T t = T(-0.18467439092237189) * Pb[5]; ga[1] += t * b[0]; gb[0] += t * a[1]; }
-    { const T t = T(0.18467439092237189) * Pb[5]; ga[3] += t * b[2]; gb[2] += t * a[3]; }
-    { const T t = T(0.18467439092237187) * Pb[5]; ga[4] += t * b[1]; gb[1] += t * a[4]; }
-    { const T t = T(-0.22617901315954039) * Pb[6]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.22617901315954023) * Pb[6]; ga[4] += t * b[2]; gb[2] += t * a[4]; }
-  }
-};
-template <> struct Couple3<4, 2, 2, 0> {
-  static constexpr int kTerms = 5;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[0] += T(0.2820947917738782) * (a[0] * b[0]);
-    P[0] += T(0.28209479177387831) * (a[1] * b[1]);
-    P[0] += T(0.28209479177387831) * (a[2] * b[2]);
-    P[0] += T(0.28209479177387831) * (a[3] * b[3]);
-    P[0] += T(0.28209479177387831) * (a[4] * b[4]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(0.2820947917738782) * Pb[0]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.28209479177387831) * Pb[0]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(0.28209479177387831) * Pb[0]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(0.28209479177387831) * Pb[0]; ga[3] += t * b[3]; gb[3] += t * a[3]; }
-    { const T t = T(0.28209479177387831) * Pb[0]; ga[4] += t * b[4]; gb[4] += t * a[4]; }
-  }
-};
-template <> struct Couple3<4, 2, 2, 2> {
-  static constexpr int kTerms = 25;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[0] += T(-0.18022375157286874) * (a[0] * b[2]);
-    P[0] += T(0.15607834722743999) * (a[1] * b[3]);
-    P[0] += T(-0.18022375157286874) * (a[2] * b[0]);
-    P[0] += T(0.15607834722743999) * (a[3] * b[1]);
-    P[1] += T(0.15607834722743999) * (a[0] * b[3]);
-    P[1] += T(0.090111875786434384) * (a[1] * b[2]);
-    P[1] += T(-0.15607834722744002) * (a[1] * b[4]);
-    P[1] += T(0.090111875786434384) * (a[2] * b[1]);
-    P[1] += T(0.15607834722743999) * (a[3] * b[0]);
-    P[1] += T(-0.15607834722744002) * (a[4] * b[1]);
-    P[2] += T(-0.18022375157286874) * (a[0] * b[0]);
-    P[2] += T(0.090111875786434384) * (a[1] * b[1]);
-    P[2] += T(0.18022375157286855) * (a[2] * b[2]);
-    P[2] += T(0.090111875786434384) * (a[3] * b[3]);
-    P[2] += T(-0.18022375157286849) * (a[4] * b[4]);
-    P[3] += T(0.15607834722743999) * (a[0] * b[1]);
-    P[3] += T(0.15607834722743999) * (a[1] * b[0]);
-    P[3] += T(0.090111875786434384) * (a[2] * b[3]);
-    P[3] += T(0.090111875786434384) * (a[3] * b[2]);
-    P[3] += T(0.15607834722744002) * (a[3] * b[4]);
-    P[3] += T(0.15607834722744002) * (a[4] * b[3]);
-    P[4] += T(-0.15607834722744002) * (a[1] * b[1]);
-    P[4] += T(-0.18022375157286849) * (a[2] * b[4]);
-    P[4] += T(0.15607834722744002) * (a[3] * b[3]);
-    P[4] += T(-0.18022375157286849) * (a[4] * b[2]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(-0.18022375157286874) * Pb[0]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(0.15607834722743999) * Pb[0]; ga[1] += t * b[3]; gb[3] += t * a[1]; }
-    { const T t = T(-0.18022375157286874) * Pb[0]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(0.15607834722743999) * Pb[0]; ga[3] += t * b[1]; gb[1] += t * a[3]; }
-    { const T t = T(0.15607834722743999) * Pb[1]; ga[0] += t * b[3]; gb[3] += t * a[0]; }
-    { const T t = T(0.090111875786434384) * Pb[1]; ga[1] += t * b[2]; gb[2] += t * a[1]; }
-    { const T t = T(-0.15607834722744002) * Pb[1]; ga[1] += t * b[4]; gb[4] += t * a[1]; }
-    { const T t = T(0.090111875786434384) * Pb[1]; ga[2] += t * b[1]; gb[1] += t * a[2]; }
-    { const T t = T(0.15607834722743999) * Pb[1]; ga[3] += t * b[0]; gb[0] += t * a[3]; }
-    { const T t = T(-0.15607834722744002) * Pb[1]; ga[4] += t * b[1]; gb[1] += t * a[4]; }
-    { const T t = T(-0.18022375157286874) * Pb[2]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.090111875786434384) * Pb[2]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(0.18022375157286855) * Pb[2]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(0.090111875786434384) * Pb[2]; ga[3] += t * b[3]; gb[3] += t * a[3]; }
-    { const T t = T(-0.18022375157286849) * Pb[2]; ga[4] += t * b[4]; gb[4] += t * a[4]; }
-    { const T t = T(0.15607834722743999) * Pb[3]; ga[0] += t * b[1]; gb[1] += t * a[0]; }
-    { const T t = T(0.15607834722743999) * Pb[3]; ga[1] += t * b[0]; gb[0] += t * a[1]; }
-    { const T t = T(0.090111875786434384) * Pb[3]; ga[2] += t * b[3]; gb[3] += t * a[2]; }
-    { const T t = T(0.090111875786434384) * Pb[3]; ga[3] += t * b[2]; gb[2] += t * a[3]; }
-    { const T t = T(0.15607834722744002) * Pb[3]; ga[3] += t * b[4]; gb[4] += t * a[3]; }
-    { const T t = T(0.15607834722744002) * Pb[3]; ga[4] += t * b[3]; gb[3] += t * a[4]; }
-    { const T t = T(-0.15607834722744002) * Pb[4]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(-0.18022375157286849) * Pb[4]; ga[2] += t * b[4]; gb[4] += t * a[2]; }
-    { const T t = T(0.15607834722744002) * Pb[4]; ga[3] += t * b[3]; gb[3] += t * a[3]; }
-    { const T t = T(-0.18022375157286849) * Pb[4]; ga[4] += t * b[2]; gb[2] += t * a[4]; }
-  }
-};
-template <> struct Couple3<4, 2, 2, 4> {
-  static constexpr int kTerms = 37;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[0] += T(0.23841361350444781) * (a[0] * b[4]);
-    P[0] += T(0.23841361350444781) * (a[4] * b[0]);
-    P[1] += T(0.16858388283618392) * (a[0] * b[3]);
-    P[1] += T(0.16858388283618383) * (a[1] * b[4]);
-    P[1] += T(0.16858388283618392) * (a[3] * b[0]);
-    P[1] += T(0.16858388283618383) * (a[4] * b[1]);
-    P[2] += T(0.15607834722743993) * (a[0] * b[2]);
-    P[2] += T(0.18022375157286868) * (a[1] * b[3]);
-    P[2] += T(0.15607834722743993) * (a[2] * b[0]);
-    P[2] += T(0.18022375157286868) * (a[3] * b[1]);
-    P[3] += T(-0.063718718434027544) * (a[0] * b[3]);
-    P[3] += T(0.22072811544182241) * (a[1] * b[2]);
-    P[3] += T(0.063718718434027433) * (a[1] * b[4]);
-    P[3] += T(0.22072811544182241) * (a[2] * b[1]);
-    P[3] += T(-0.063718718434027544) * (a[3] * b[0]);
-    P[3] += T(0.063718718434027433) * (a[4] * b[1]);
-    P[4] += T(0.040299255967696845) * (a[0] * b[0]);
-    P[4] += T(-0.16119702387078788) * (a[1] * b[1]);
-    P[4] += T(0.24179553580618143) * (a[2] * b[2]);
-    P[4] += T(-0.16119702387078788) * (a[3] * b[3]);
-    P[4] += T(0.040299255967696873) * (a[4] * b[4]);
-    P[5] += T(-0.063718718434027544) * (a[0] * b[1]);
-    P[5] += T(-0.063718718434027544) * (a[1] * b[0]);
-    P[5] += T(0.22072811544182241) * (a[2] * b[3]);
-    P[5] += T(0.22072811544182241) * (a[3] * b[2]);
-    P[5] += T(-0.063718718434027433) * (a[3] * b[4]);
-    P[5] += T(-0.063718718434027433) * (a[4] * b[3]);
-    P[6] += T(-0.18022375157286877) * (a[1] * b[1]);
-    P[6] += T(0.15607834722743996) * (a[2] * b[4]);
-    P[6] += T(0.18022375157286874) * (a[3] * b[3]);
-    P[6] += T(0.15607834722743996) * (a[4] * b[2]);
-    P[7] += T(-0.16858388283618392) * (a[0] * b[1]);
-    P[7] += T(-0.16858388283618392) * (a[1] * b[0]);
-    P[7] += T(0.16858388283618383) * (a[3] * b[4]);
-    P[7] += T(0.16858388283618383) * (a[4] * b[3]);
-    P[8] += T(-0.23841361350444834) * (a[0] * b[0]);
-    P[8] += T(0.23841361350444815) * (a[4] * b[4]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(0.23841361350444781) * Pb[0]; ga[0] += t * b[4]; gb[4] += t * a[0]; }
-    { const T t = T(0.23841361350444781) * Pb[0]; ga[4] += t * b[0]; gb[0] += t * a[4]; }
-    { const T t = T(0.16858388283618392) * Pb[1]; ga[0] += t * b[3]; gb[3] += t * a[0]; }
-    { const T t = T(0.16858388283618383) * Pb[1]; ga[1] += t * b[4]; gb[4] += t * a[1]; }
-    { const T t = T(0.16858388283618392) * Pb[1]; ga[3] += t * b[0]; gb[0] += t * a[3]; }
-    { const T t = T(0.16858388283618383) * Pb[1]; ga[4] += t * b[1]; gb[1] += t * a[4]; }
-    { const T t = T(0.15607834722743993) * Pb[2]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(0.18022375157286868) * Pb[2]; ga[1] += t * b[3]; gb[3] += t * a[1]; }
-    { const T t = T(0.15607834722743993) * Pb[2]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(0.18022375157286868) * Pb[2]; ga[3] += t * b[1]; gb[1] += t * a[3]; }
-    { const T t = T(-0.063718718434027544) * Pb[3]; ga[0] += t * b[3]; gb[3] += t * a[0]; }
-    { const T t = T(0.22072811544182241) * Pb[3]; ga[1] += t * b[2]; gb[2] += t * a[1]; }
-    { const T t = T(0.063718718434027433) * Pb[3]; ga[1] += t * b[4]; gb[4] += t * a[1]; }
-    { const T t = T(0.22072811544182241) * Pb[3]; ga[2] += t * b[1]; gb[1] += t * a[2]; }
-    { const T t = T(-0.063718718434027544) * Pb[3]; ga[3] += t * b[0]; gb[0] += t * a[3]; }
-    { const T t = T(0.063718718434027433) * Pb[3]; ga[4] += t * b[1]; gb[1] += t * a[4]; }
-    { const T t = T(0.040299255967696845) * Pb[4]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(-0.16119702387078788) * Pb[4]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(0.24179553580618143) * Pb[4]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(-0.16119702387078788) * Pb[4]; ga[3] += t * b[3]; gb[3] += t * a[3]; }
-    { const T t = T(0.040299255967696873) * Pb[4]; ga[4] += t * b[4]; gb[4] += t * a[4]; }
-    { const T t = T(-0.063718718434027544) * Pb[5]; ga[0] += t * b[1]; gb[1] += t * a[0]; }
-    { const T t = T(-0.063718718434027544) * Pb[5]; ga[1] += t * b[0]; gb[0] += t * a[1]; }
-    { const T t = T(0.22072811544182241) * Pb[5]; ga[2] += t * b[3]; gb[3] += t * a[2]; }
-    { const T t = T(0.22072811544182241) * Pb[5]; ga[3] += t * b[2]; gb[2] += t * a[3]; }
-    { const T t = T(-0.063718718434027433) * Pb[5]; ga[3] += t * b[4]; gb[4] += t * a[3]; }
-    { const T t = T(-0.063718718434027433) * Pb[5]; ga[4] += t * b[3]; gb[3] += t * a[4]; }
-    { const T t = T(-0.18022375157286877) * Pb[6]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(0.15607834722743996) * Pb[6]; ga[2] += t * b[4]; gb[4] += t * a[2]; }
-    { const T t = T(0.18022375157286874) * Pb[6]; ga[3] += t * b[3]; gb[3] += t * a[3]; }
-    { const T t = T(0.15607834722743996) * Pb[6]; ga[4] += t * b[2]; gb[2] += t * a[4]; }
-    { const T t = T(-0.16858388283618392) * Pb[7]; ga[0] += t * b[1]; gb[1] += t * a[0]; }
-    { const T t = T(-0.16858388283618392) * Pb[7]; ga[1] += t * b[0]; gb[0] += t * a[1]; }
-    { const T t = T(0.16858388283618383) * Pb[7]; ga[3] += t * b[4]; gb[4] += t * a[3]; }
-    { const T t = T(0.16858388283618383) * Pb[7]; ga[4] += t * b[3]; gb[3] += t * a[4]; }
-    { const T t = T(-0.23841361350444834) * Pb[8]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.23841361350444815) * Pb[8]; ga[4] += t * b[4]; gb[4] += t * a[4]; }
-  }
-};
-template <> struct Couple3<4, 2, 3, 1> {
-  static constexpr int kTerms = 21;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[0] += T(-0.058399170081901867) * (a[0] * b[4]);
-    P[0] += T(-0.22617901315954042) * (a[0] * b[6]);
-    P[0] += T(-0.1430481681026689) * (a[1] * b[3]);
-    P[0] += T(-0.18467439092237192) * (a[1] * b[5]);
-    P[0] += T(0.20230065940342068) * (a[2] * b[2]);
-    P[0] += T(0.18467439092237189) * (a[3] * b[1]);
-    P[0] += T(0.22617901315954025) * (a[4] * b[0]);
-    P[0] += T(0.058399170081901736) * (a[4] * b[2]);
-    P[1] += T(0.18467439092237187) * (a[0] * b[1]);
-    P[1] += T(0.23359668032760761) * (a[1] * b[2]);
-    P[1] += T(0.24776669508347601) * (a[2] * b[3]);
-    P[1] += T(0.23359668032760761) * (a[3] * b[4]);
-    P[1] += T(0.18467439092237187) * (a[4] * b[5]);
-    P[2] += T(0.22617901315954042) * (a[0] * b[0]);
-    P[2] += T(-0.058399170081901867) * (a[0] * b[2]);
-    P[2] += T(0.18467439092237189) * (a[1] * b[1]);
-    P[2] += T(0.20230065940342068) * (a[2] * b[4]);
-    P[2] += T(-0.1430481681026689) * (a[3] * b[3]);
-    P[2] += T(0.18467439092237192) * (a[3] * b[5]);
-    P[2] += T(-0.058399170081901736) * (a[4] * b[4]);
-    P[2] += T(0.22617901315954025) * (a[4] * b[6]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(-0.058399170081901867) * Pb[0]; ga[0] += t * b[4]; gb[4] += t * a[0]; }
-    { const T t = T(-0.22617901315954042) * Pb[0]; ga[0] += t * b[6]; gb[6] += t * a[0]; }
-    { const T t = T(-0.1430481681026689) * Pb[0]; ga[1] += t * b[3]; gb[3] += t * a[1]; }
-    { const T t = T(-0.18467439092237192) * Pb[0]; ga[1] += t * b[5]; gb[5] += t * a[1]; }
-    { const T t = T(0.20230065940342068) * Pb[0]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(0.18467439092237189) * Pb[0]; ga[3] += t * b[1]; gb[1] += t * a[3]; }
-    { const T t = T(0.22617901315954025) * Pb[0]; ga[4] += t * b[0]; gb[0] += t * a[4]; }
-    { const T t = T(0.058399170081901736) * Pb[0]; ga[4] += t * b[2]; gb[2] += t * a[4]; }
-    { const T t = T(0.18467439092237187) * Pb[1]; ga[0] += t * b[1]; gb[1] += t * a[0]; }
-    { const T t = T(0.23359668032760761) * Pb[1]; ga[1] += t * b[2]; gb[2] += t * a[1]; }
-    { const T t = T(0.24776669508347601) * Pb[1]; ga[2] += t * b[3]; gb[3] += t * a[2]; }
-    { const T t = T(0.23359668032760761) * Pb[1]; ga[3] += t * b[4]; gb[4] += t * a[3]; }
-    { const T t = T(0.18467439092237187) * Pb[1]; ga[4] += t * b[5]; gb[5] += t * a[4]; }
-    { const T t = T(0.22617901315954042) * Pb[2]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(-0.058399170081901867) * Pb[2]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(0.18467439092237189) * Pb[2]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(0.20230065940342068) * Pb[2]; ga[2] += t * b[4]; gb[4] += t * a[2]; }
-    { const T t = T(-0.1430481681026689) * Pb[2]; ga[3] += t * b[3]; gb[3] += t * a[3]; }
-    { const T t = T(0.18467439092237192) * Pb[2]; ga[3] += t * b[5]; gb[5] += t * a[3]; }
-    { const T t = T(-0.058399170081901736) * Pb[2]; ga[4] += t * b[4]; gb[4] += t * a[4]; }
-    { const T t = T(0.22617901315954025) * Pb[2]; ga[4] += t * b[6]; gb[6] += t * a[4]; }
-  }
-};
-template <> struct Couple3<4, 2, 3, 3> {
-  static constexpr int kTerms = 41;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[0] += T(-0.094031597257959357) * (a[0] * b[4]);
-    P[0] += T(0.14867700967939756) * (a[1] * b[5]);
-    P[0] += T(-0.21026104350168001) * (a[2] * b[0]);
-    P[0] += T(0.14867700967939765) * (a[3] * b[1]);
-    P[0] += T(-0.094031597257959315) * (a[4] * b[2]);
-    P[1] += T(-0.1880631945159188) * (a[0] * b[3]);
-    P[1] += T(0.11516471649044524) * (a[1] * b[4]);
-    P[1] += T(-0.14867700967939765) * (a[1] * b[6]);
-    P[1] += T(0.14867700967939765) * (a[3] * b[0]);
-    P[1] += T(0.11516471649044524) * (a[3] * b[2]);
-    P[2] += T(0.14567312407894392) * (a[0] * b[4]);
-    P[2] += T(0.094031597257959329) * (a[0] * b[6]);
-    P[2] += T(0.059470803871758834) * (a[1] * b[3]);
-    P[2] += T(-0.1151647164904453) * (a[1] * b[5]);
-    P[2] += T(0.12615662610100786) * (a[2] * b[2]);
-    P[2] += T(0.11516471649044524) * (a[3] * b[1]);
-    P[2] += T(-0.094031597257959357) * (a[4] * b[0]);
-    P[2] += T(-0.14567312407894395) * (a[4] * b[2]);
-    P[3] += T(-0.1880631945159188) * (a[0] * b[1]);
-    P[3] += T(0.059470803871758834) * (a[1] * b[2]);
-    P[3] += T(0.16820883480134416) * (a[2] * b[3]);
-    P[3] += T(0.059470803871758827) * (a[3] * b[4]);
-    P[3] += T(-0.18806319451591863) * (a[4] * b[5]);
-    P[4] += T(-0.094031597257959315) * (a[0] * b[0]);
-    P[4] += T(0.14567312407894392) * (a[0] * b[2]);
-    P[4] += T(0.11516471649044524) * (a[1] * b[1]);
-    P[4] += T(0.12615662610100786) * (a[2] * b[4]);
-    P[4] += T(0.059470803871758827) * (a[3] * b[3]);
-    P[4] += T(0.11516471649044534) * (a[3] * b[5]);
-    P[4] += T(0.14567312407894398) * (a[4] * b[4]);
-    P[4] += T(-0.094031597257959357) * (a[4] * b[6]);
-    P[5] += T(0.14867700967939756) * (a[1] * b[0]);
-    P[5] += T(-0.1151647164904453) * (a[1] * b[2]);
-    P[5] += T(0.1151647164904453) * (a[3] * b[4]);
-    P[5] += T(0.14867700967939756) * (a[3] * b[6]);
-    P[5] += T(-0.18806319451591863) * (a[4] * b[3]);
-    P[6] += T(0.094031597257959357) * (a[0] * b[2]);
-    P[6] += T(-0.14867700967939765) * (a[1] * b[1]);
-    P[6] += T(-0.21026104350168001) * (a[2] * b[6]);
-    P[6] += T(0.14867700967939756) * (a[3] * b[5]);
-    P[6] += T(-0.094031597257959315) * (a[4] * b[4]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(-0.094031597257959357) * Pb[0]; ga[0] += t * b[4]; gb[4] += t * a[0]; }
-    { const T t = T(0.14867700967939756) * Pb[0]; ga[1] += t * b[5]; gb[5] += t * a[1]; }
-    { const T t = T(-0.21026104350168001) * Pb[0]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(0.14867700967939765) * Pb[0]; ga[3] += t * b[1]; gb[1] += t * a[3]; }
-    { const T t = T(-0.094031597257959315) * Pb[0]; ga[4] += t * b[2]; gb[2] += t * a[4]; }
-    { const T t = T(-0.1880631945159188) * Pb[1]; ga[0] += t * b[3]; gb[3] += t * a[0]; }
-    { const T t = T(0.11516471649044524) * Pb[1]; ga[1] += t * b[4]; gb[4] += t * a[1]; }
-    { const T t = T(-0.14867700967939765) * Pb[1]; ga[1] += t * b[6]; gb[6] += t * a[1]; }
-    { const T t = T(0.14867700967939765) * Pb[1]; ga[3] += t * b[0]; gb[0] += t * a[3]; }
-    { const T t = T(0.11516471649044524) * Pb[1]; ga[3] += t * b[2]; gb[2] += t * a[3]; }
-    { const T t = T(0.14567312407894392) * Pb[2]; ga[0] += t * b[4]; gb[4] += t * a[0]; }
-    { const T t = T(0.094031597257959329) * Pb[2]; ga[0] += t * b[6]; gb[6] += t * a[0]; }
-    { const T t = T(0.059470803871758834) * Pb[2]; ga[1] += t * b[3]; gb[3] += t * a[1]; }
-    { const T t = T(-0.1151647164904453) * Pb[2]; ga[1] += t * b[5]; gb[5] += t * a[1]; }
-    { const T t = T(0.12615662610100786) * Pb[2]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(0.11516471649044524) * Pb[2]; ga[3] += t * b[1]; gb[1] += t * a[3]; }
-    { const T t = T(-0.094031597257959357) * Pb[2]; ga[4] += t * b[0]; gb[0] += t * a[4]; }
-    { const T t = T(-0.14567312407894395) * Pb[2]; ga[4] += t * b[2]; gb[2] += t * a[4]; }
-    { const T t = T(-0.1880631945159188) * Pb[3]; ga[0] += t * b[1]; gb[1] += t * a[0]; }
-    { const T t = T(0.059470803871758834) * Pb[3]; ga[1] += t * b[2]; gb[2] += t * a[1]; }
-    { const T t = T(0.16820883480134416) * Pb[3]; ga[2] += t * b[3]; gb[3] += t * a[2]; }
-    { const T t = T(0.059470803871758827) * Pb[3]; ga[3] += t * b[4]; gb[4] += t * a[3]; }
-    { const T t = T(-0.18806319451591863) * Pb[3]; ga[4] += t * b[5]; gb[5] += t * a[4]; }
-    { const T t = T(-0.094031597257959315) * Pb[4]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.14567312407894392) * Pb[4]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(0.11516471649044524) * Pb[4]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(0.12615662610100786) * Pb[4]; ga[2] += t * b[4]; gb[4] += t * a[2]; }
-    { const T t = T(0.059470803871758827) * Pb[4]; ga[3] += t * b[3]; gb[3] += t * a[3]; }
-    { const T t = T(0.11516471649044534) * Pb[4]; ga[3] += t * b[5]; gb[5] += t * a[3]; }
-    { const T t = T(0.14567312407894398) * Pb[4]; ga[4] += t * b[4]; gb[4] += t * a[4]; }
-    { const T t = T(-0.094031597257959357) * Pb[4]; ga[4] += t * b[6]; gb[6] += t * a[4]; }
-    { const T t = T(0.14867700967939756) * Pb[5]; ga[1] += t * b[0]; gb[0] += t * a[1]; }
-    { const T t = T(-0.1151647164904453) * Pb[5]; ga[1] += t * b[2]; gb[2] += t * a[1]; }
-    { const T t = T(0.1151647164904453) * Pb[5]; ga[3] += t * b[4]; gb[4] += t * a[3]; }
-    { const T t = T(0.14867700967939756) * Pb[5]; ga[3] += t * b[6]; gb[6] += t * a[3]; }
-    { const T t = T(-0.18806319451591863) * Pb[5]; ga[4] += t * b[3]; gb[3] += t * a[4]; }
-    { const T t = T(0.094031597257959357) * Pb[6]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(-0.14867700967939765) * Pb[6]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(-0.21026104350168001) * Pb[6]; ga[2] += t * b[6]; gb[6] += t * a[2]; }
-    { const T t = T(0.14867700967939756) * Pb[6]; ga[3] += t * b[5]; gb[5] += t * a[3]; }
-    { const T t = T(-0.094031597257959315) * Pb[6]; ga[4] += t * b[4]; gb[4] += t * a[4]; }
-  }
-};
-template <> struct Couple3<4, 2, 4, 2> {
-  static constexpr int kTerms = 37;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[0] += T(0.040299255967696811) * (a[0] * b[4]);
-    P[0] += T(-0.23841361350444829) * (a[0] * b[8]);
-    P[0] += T(-0.063718718434027571) * (a[1] * b[5]);
-    P[0] += T(-0.16858388283618389) * (a[1] * b[7]);
-    P[0] += T(0.15607834722743988) * (a[2] * b[2]);
-    P[0] += T(0.16858388283618389) * (a[3] * b[1]);
-    P[0] += T(-0.063718718434027571) * (a[3] * b[3]);
-    P[0] += T(0.23841361350444776) * (a[4] * b[0]);
-    P[1] += T(-0.063718718434027558) * (a[0] * b[5]);
-    P[1] += T(-0.16858388283618389) * (a[0] * b[7]);
-    P[1] += T(-0.1611970238707878) * (a[1] * b[4]);
-    P[1] += T(-0.18022375157286874) * (a[1] * b[6]);
-    P[1] += T(0.22072811544182247) * (a[2] * b[3]);
-    P[1] += T(0.18022375157286866) * (a[3] * b[2]);
-    P[1] += T(0.16858388283618381) * (a[4] * b[1]);
-    P[1] += T(0.06371871843402746) * (a[4] * b[3]);
-    P[2] += T(0.15607834722743991) * (a[0] * b[2]);
-    P[2] += T(0.22072811544182239) * (a[1] * b[3]);
-    P[2] += T(0.24179553580618141) * (a[2] * b[4]);
-    P[2] += T(0.22072811544182239) * (a[3] * b[5]);
-    P[2] += T(0.15607834722743993) * (a[4] * b[6]);
-    P[3] += T(0.16858388283618389) * (a[0] * b[1]);
-    P[3] += T(-0.063718718434027558) * (a[0] * b[3]);
-    P[3] += T(0.18022375157286866) * (a[1] * b[2]);
-    P[3] += T(0.22072811544182241) * (a[2] * b[5]);
-    P[3] += T(-0.16119702387078777) * (a[3] * b[4]);
-    P[3] += T(0.18022375157286868) * (a[3] * b[6]);
-    P[3] += T(-0.06371871843402746) * (a[4] * b[5]);
-    P[3] += T(0.16858388283618381) * (a[4] * b[7]);
-    P[4] += T(0.23841361350444776) * (a[0] * b[0]);
-    P[4] += T(0.16858388283618381) * (a[1] * b[1]);
-    P[4] += T(0.063718718434027433) * (a[1] * b[3]);
-    P[4] += T(0.15607834722743988) * (a[2] * b[6]);
-    P[4] += T(-0.063718718434027447) * (a[3] * b[5]);
-    P[4] += T(0.16858388283618381) * (a[3] * b[7]);
-    P[4] += T(0.040299255967696929) * (a[4] * b[4]);
-    P[4] += T(0.23841361350444812) * (a[4] * b[8]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(0.040299255967696811) * Pb[0]; ga[0] += t * b[4]; gb[4] += t * a[0]; }
-    { const T t = T(-0.23841361350444829) * Pb[0]; ga[0] += t * b[8]; gb[8] += t * a[0]; }
-    { const T t = T(-0.063718718434027571) * Pb[0]; ga[1] += t * b[5]; gb[5] += t * a[1]; }
-    { const T t = T(-0.16858388283618389) * Pb[0]; ga[1] += t * b[7]; gb[7] += t * a[1]; }
-    { const T t = T(0.15607834722743988) * Pb[0]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(0.16858388283618389) * Pb[0]; ga[3] += t * b[1]; gb[1] += t * a[3]; }
-    { const T t = T(-0.063718718434027571) * Pb[0]; ga[3] += t * b[3]; gb[3] += t * a[3]; }
-    { const T t = T(0.23841361350444776) * Pb[0]; ga[4] += t * b[0]; gb[0] += t * a[4]; }
-    { const T t = T(-0.063718718434027558) * Pb[1]; ga[0] += t * b[5]; gb[5] += t * a[0]; }
-    { const T t = T(-0.16858388283618389) * Pb[1]; ga[0] += t * b[7]; gb[7] += t * a[0]; }
-    { const T t = T(-0.1611970238707878) * Pb[1]; ga[1] += t * b[4]; gb[4] += t * a[1]; }
-    { const T t = T(-0.18022375157286874) * Pb[1]; ga[1] += t * b[6]; gb[6] += t * a[1]; }
-    { const T t = T(0.22072811544182247) * Pb[1]; ga[2] += t * b[3]; gb[3] += t * a[2]; }
-    { const T t = T(0.18022375157286866) * Pb[1]; ga[3] += t * b[2]; gb[2] += t * a[3]; }
-    { const T t = T(0.16858388283618381) * Pb[1]; ga[4] += t * b[1]; gb[1] += t * a[4]; }
-    { const T t = T(0.06371871843402746) * Pb[1]; ga[4] += t * b[3]; gb[3] += t * a[4]; }
-    { const T t = T(0.15607834722743991) * Pb[2]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(0.22072811544182239) * Pb[2]; ga[1] += t * b[3]; gb[3] += t * a[1]; }
-    { const T t = T(0.24179553580618141) * Pb[2]; ga[2] += t * b[4]; gb[4] += t * a[2]; }
-    { const T t = T(0.22072811544182239) * Pb[2]; ga[3] += t * b[5]; gb[5] += t * a[3]; }
-    { const T t = T(0.15607834722743993) * Pb[2]; ga[4] += t * b[6]; gb[6] += t * a[4]; }
-    { const T t = T(0.16858388283618389) * Pb[3]; ga[0] += t * b[1]; gb[1] += t * a[0]; }
-    { const T t = T(-0.063718718434027558) * Pb[3]; ga[0] += t * b[3]; gb[3] += t * a[0]; }
-    { const T t = T(0.18022375157286866) * Pb[3]; ga[1] += t * b[2]; gb[2] += t * a[1]; }
-    { const T t = T(0.22072811544182241) * Pb[3]; ga[2] += t * b[5]; gb[5] += t * a[2]; }
-    { const T t = T(-0.16119702387078777) * Pb[3]; ga[3] += t * b[4]; gb[4] += t * a[3]; }
-    { const T t = T(0.18022375157286868) * Pb[3]; ga[3] += t * b[6]; gb[6] += t * a[3]; }
-    { const T t = T(-0.06371871843402746) * Pb[3]; ga[4] += t * b[5]; gb[5] += t * a[4]; }
-    { const T t = T(0.16858388283618381) * Pb[3]; ga[4] += t * b[7]; gb[7] += t * a[4]; }
-    { const T t = T(0.23841361350444776) * Pb[4]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.16858388283618381) * Pb[4]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(0.063718718434027433) * Pb[4]; ga[1] += t * b[3]; gb[3] += t * a[1]; }
-    { const T t = T(0.15607834722743988) * Pb[4]; ga[2] += t * b[6]; gb[6] += t * a[2]; }
-    { const T t = T(-0.063718718434027447) * Pb[4]; ga[3] += t * b[5]; gb[5] += t * a[3]; }
-    { const T t = T(0.16858388283618381) * Pb[4]; ga[3] += t * b[7]; gb[7] += t * a[3]; }
-    { const T t = T(0.040299255967696929) * Pb[4]; ga[4] += t * b[4]; gb[4] += t * a[4]; }
-    { const T t = T(0.23841361350444812) * Pb[4]; ga[4] += t * b[8]; gb[8] += t * a[4]; }
-  }
-};
-template <> struct Couple3<4, 2, 4, 4> {
-  static constexpr int kTerms = 61;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[0] += T(-0.075080816691962482) * (a[0] * b[6]);
-    P[0] += T(0.14046334619025069) * (a[1] * b[7]);
-    P[0] += T(-0.22937568382001464) * (a[2] * b[0]);
-    P[0] += T(0.14046334619025069) * (a[3] * b[1]);
-    P[0] += T(-0.075080816691962496) * (a[4] * b[2]);
-    P[1] += T(-0.11262122503794367) * (a[0] * b[5]);
-    P[1] += T(0.13272538654977695) * (a[1] * b[6]);
-    P[1] += T(-0.1404633461902508) * (a[1] * b[8]);
-    P[1] += T(-0.057343920955003555) * (a[2] * b[1]);
-    P[1] += T(0.14046334619025072) * (a[3] * b[0]);
-    P[1] += T(0.13272538654977706) * (a[3] * b[2]);
-    P[1] += T(-0.11262122503794365) * (a[4] * b[3]);
-    P[2] += T(-0.19036461502711174) * (a[0] * b[4]);
-    P[2] += T(0.075080816691962302) * (a[0] * b[8]);
-    P[2] += T(0.090297865408018235) * (a[1] * b[5]);
-    P[2] += T(-0.132725386549777) * (a[1] * b[7]);
-    P[2] += T(0.06553590966286113) * (a[2] * b[2]);
-    P[2] += T(0.132725386549777) * (a[3] * b[1]);
-    P[2] += T(0.090297865408018235) * (a[3] * b[3]);
-    P[2] += T(-0.075080816691962496) * (a[4] * b[0]);
-    P[3] += T(0.14188940657039981) * (a[0] * b[5]);
-    P[3] += T(0.11262122503794365) * (a[0] * b[7]);
-    P[3] += T(0.044869370061212506) * (a[1] * b[4]);
-    P[3] += T(-0.090297865408018402) * (a[1] * b[6]);
-    P[3] += T(0.13926380803358024) * (a[2] * b[3]);
-    P[3] += T(0.090297865408018194) * (a[3] * b[2]);
-    P[3] += T(-0.11262122503794361) * (a[4] * b[1]);
-    P[3] += T(-0.14188940657039986) * (a[4] * b[3]);
-    P[4] += T(-0.19036461502711174) * (a[0] * b[2]);
-    P[4] += T(0.044869370061212464) * (a[1] * b[3]);
-    P[4] += T(0.16383977415715348) * (a[2] * b[4]);
-    P[4] += T(0.044869370061212464) * (a[3] * b[5]);
-    P[4] += T(-0.1903646150271118) * (a[4] * b[6]);
-    P[5] += T(-0.11262122503794367) * (a[0] * b[1]);
-    P[5] += T(0.14188940657039981) * (a[0] * b[3]);
-    P[5] += T(0.090297865408018194) * (a[1] * b[2]);
-    P[5] += T(0.13926380803358016) * (a[2] * b[5]);
-    P[5] += T(0.044869370061212478) * (a[3] * b[4]);
-    P[5] += T(0.090297865408018402) * (a[3] * b[6]);
-    P[5] += T(0.14188940657039986) * (a[4] * b[5]);
-    P[5] += T(-0.11262122503794363) * (a[4] * b[7]);
-    P[6] += T(-0.075080816691962496) * (a[0] * b[0]);
-    P[6] += T(0.13272538654977695) * (a[1] * b[1]);
-    P[6] += T(-0.09029786540801843) * (a[1] * b[3]);
-    P[6] += T(0.065535909662861241) * (a[2] * b[6]);
-    P[6] += T(0.090297865408018416) * (a[3] * b[5]);
-    P[6] += T(0.13272538654977692) * (a[3] * b[7]);
-    P[6] += T(-0.1903646150271118) * (a[4] * b[4]);
-    P[6] += T(-0.075080816691962482) * (a[4] * b[8]);
-    P[7] += T(0.11262122503794368) * (a[0] * b[3]);
-    P[7] += T(0.14046334619025072) * (a[1] * b[0]);
-    P[7] += T(-0.13272538654977706) * (a[1] * b[2]);
-    P[7] += T(-0.057343920955003555) * (a[2] * b[7]);
-    P[7] += T(0.13272538654977692) * (a[3] * b[6]);
-    P[7] += T(0.1404633461902508) * (a[3] * b[8]);
-    P[7] += T(-0.11262122503794364) * (a[4] * b[5]);
-    P[8] += T(0.075080816691962357) * (a[0] * b[2]);
-    P[8] += T(-0.14046334619025078) * (a[1] * b[1]);
-    P[8] += T(-0.22937568382001453) * (a[2] * b[8]);
-    P[8] += T(0.14046334619025078) * (a[3] * b[7]);
-    P[8] += T(-0.075080816691962482) * (a[4] * b[6]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(-0.075080816691962482) * Pb[0]; ga[0] += t * b[6]; gb[6] += t * a[0]; }
-    { const T t = T(0.14046334619025069) * Pb[0]; ga[1] += t * b[7]; gb[7] += t * a[1]; }
-    { const T t = T(-0.22937568382001464) * Pb[0]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(0.14046334619025069) * Pb[0]; ga[3] += t * b[1]; gb[1] += t * a[3]; }
-    { const T t = T(-0.075080816691962496) * Pb[0]; ga[4] += t * b[2]; gb[2] += t * a[4]; }
-    { const T t = T(-0.11262122503794367) * Pb[1]; ga[0] += t * b[5]; gb[5] += t * a[0]; }
-    { const T t = T(0.13272538654977695) * Pb[1]; ga[1] += t * b[6]; gb[6] += t * a[1]; }
-    { const T t = T(-0.1404633461902508) * Pb[1]; ga[1] += t * b[8]; gb[8] += t * a[1]; }
-    { const T t = T(-0.057343920955003555) * Pb[1]; ga[2] += t * b[1]; gb[1] += t * a[2]; }
-    { const T t = T(0.14046334619025072) * Pb[1]; ga[3] += t * b[0]; gb[0] += t * a[3]; }
-    { const T t = T(0.13272538654977706) * Pb[1]; ga[3] += t * b[2]; gb[2] += t * a[3]; }
-    { const T t = T(-0.11262122503794365) * Pb[1]; ga[4] += t * b[3]; gb[3] += t * a[4]; }
-    { const T t = T(-0.19036461502711174) * Pb[2]; ga[0] += t * b[4]; gb[4] += t * a[0]; }
-    { const T t = T(0.075080816691962302) * Pb[2]; ga[0] += t * b[8]; gb[8] += t * a[0]; }
-    { const T t = T(0.090297865408018235) * Pb[2]; ga[1] += t * b[5]; gb[5] += t * a[1]; }
-    { const T t = T(-0.132725386549777) * Pb[2]; ga[1] += t * b[7]; gb[7] += t * a[1]; }
-    { const T t = T(0.06553590966286113) * Pb[2]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(0.132725386549777) * Pb[2]; ga[3] += t * b[1]; gb[1] += t * a[3]; }
-    { const T t = T(0.090297865408018235) * Pb[2]; ga[3] += t * b[3]; gb[3] += t * a[3]; }
-    { const T t = T(-0.075080816691962496) * Pb[2]; ga[4] += t * b[0]; gb[0] += t * a[4]; }
-    { const T t = T(0.14188940657039981) * Pb[3]; ga[0] += t * b[5]; gb[5] += t * a[0]; }
-    { const T t = T(0.11262122503794365) * Pb[3]; ga[0] += t * b[7]; gb[7] += t * a[0]; }
-    { const T t = T(0.044869370061212506) * Pb[3]; ga[1] += t * b[4]; gb[4] += t * a[1]; }
-    { const T t = T(-0.090297865408018402) * Pb[3]; ga[1] += t * b[6]; gb[6] += t * a[1]; }
-    { const T t = T(0.13926380803358024) * Pb[3]; ga[2] += t * b[3]; gb[3] += t * a[2]; }
-    { const T t = T(0.090297865408018194) * Pb[3]; ga[3] += t * b[2]; gb[2] += t * a[3]; }
-    { const T t = T(-0.11262122503794361) * Pb[3]; ga[4] += t * b[1]; gb[1] += t * a[4]; }
-    { const T t = T(-0.14188940657039986) * Pb[3]; ga[4] += t * b[3]; gb[3] += t * a[4]; }
-    { const T t = T(-0.19036461502711174) * Pb[4]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(0.044869370061212464) * Pb[4]; ga[1] += t * b[3]; gb[3] += t * a[1]; }
-    { const T t = T(0.16383977415715348) * Pb[4]; ga[2] += t * b[4]; gb[4] += t * a[2]; }
-    { const T t = T(0.044869370061212464) * Pb[4]; ga[3] += t * b[5]; gb[5] += t * a[3]; }
-    { const T t = T(-0.1903646150271118) * Pb[4]; ga[4] += t * b[6]; gb[6] += t * a[4]; }
-    { const T t = T(-0.11262122503794367) * Pb[5]; ga[0] += t * b[1]; gb[1] += t * a[0]; }
-    { const T t = T(0.14188940657039981) * Pb[5]; ga[0] += t * b[3]; gb[3] += t * a[0]; }
-    { const T t = T(0.090297865408018194) * Pb[5]; ga[1] += t * b[2]; gb[2] += t * a[1]; }
-    { const T t = T(0.13926380803358016) * Pb[5]; ga[2] += t * b[5]; gb[5] += t * a[2]; }
-    { const T t = T(0.044869370061212478) * Pb[5]; ga[3] += t * b[4]; gb[4] += t * a[3]; }
-    { const T t = T(0.090297865408018402) * Pb[5]; ga[3] += t * b[6]; gb[6] += t * a[3]; }
-    { const T t = T(0.14188940657039986) * Pb[5]; ga[4] += t * b[5]; gb[5] += t * a[4]; }
-    { const T t = T(-0.11262122503794363) * Pb[5]; ga[4] += t * b[7]; gb[7] += t * a[4]; }
-    { const T t = T(-0.075080816691962496) * Pb[6]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.13272538654977695) * Pb[6]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(-0.09029786540801843) * Pb[6]; ga[1] += t * b[3]; gb[3] += t * a[1]; }
-    { const T t = T(0.065535909662861241) * Pb[6]; ga[2] += t * b[6]; gb[6] += t * a[2]; }
-    { const T t = T(0.090297865408018416) * Pb[6]; ga[3] += t * b[5]; gb[5] += t * a[3]; }
-    { const T t = T(0.13272538654977692) * Pb[6]; ga[3] += t * b[7]; gb[7] += t * a[3]; }
-    { const T t = T(-0.1903646150271118) * Pb[6]; ga[4] += t * b[4]; gb[4] += t * a[4]; }
-    { const T t = T(-0.075080816691962482) * Pb[6]; ga[4] += t * b[8]; gb[8] += t * a[4]; }
-    { const T t = T(0.11262122503794368) * Pb[7]; ga[0] += t * b[3]; gb[3] += t * a[0]; }
-    { const T t = T(0.14046334619025072) * Pb[7]; ga[1] += t * b[0]; gb[0] += t * a[1]; }
-    { const T t = T(-0.13272538654977706) * Pb[7]; ga[1] += t * b[2]; gb[2] += t * a[1]; }
-    { const T t = T(-0.057343920955003555) * Pb[7]; ga[2] += t * b[7]; gb[7] += t * a[2]; }
-    { const T t = T(0.13272538654977692) * Pb[7]; ga[3] += t * b[6]; gb[6] += t * a[3]; }
-    { const T t = T(0.1404633461902508) * Pb[7]; ga[3] += t * b[8]; gb[8] += t * a[3]; }
-    { const T t = T(-0.11262122503794364) * Pb[7]; ga[4] += t * b[5]; gb[5] += t * a[4]; }
-    { const T t = T(0.075080816691962357) * Pb[8]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(-0.14046334619025078) * Pb[8]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(-0.22937568382001453) * Pb[8]; ga[2] += t * b[8]; gb[8] += t * a[2]; }
-    { const T t = T(0.14046334619025078) * Pb[8]; ga[3] += t * b[7]; gb[7] += t * a[3]; }
-    { const T t = T(-0.075080816691962482) * Pb[8]; ga[4] += t * b[6]; gb[6] += t * a[4]; }
-  }
-};
-template <> struct Couple3<4, 3, 0, 3> {
-  static constexpr int kTerms = 7;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[0] += T(0.2820947917738782) * (a[0] * b[0]);
-    P[1] += T(0.2820947917738782) * (a[1] * b[0]);
-    P[2] += T(0.28209479177387825) * (a[2] * b[0]);
-    P[3] += T(0.28209479177387814) * (a[3] * b[0]);
-    P[4] += T(0.28209479177387825) * (a[4] * b[0]);
-    P[5] += T(0.28209479177387825) * (a[5] * b[0]);
-    P[6] += T(0.2820947917738782) * (a[6] * b[0]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(0.2820947917738782) * Pb[0]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.2820947917738782) * Pb[1]; ga[1] += t * b[0]; gb[0] += t * a[1]; }
-    { const T t = T(0.28209479177387825) * Pb[2]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(0.28209479177387814) * Pb[3]; ga[3] += t * b[0]; gb[0] += t * a[3]; }
-    { const T t = T(0.28209479177387825) * Pb[4]; ga[4] += t * b[0]; gb[0] += t * a[4]; }
-    { const T t = T(0.28209479177387825) * Pb[5]; ga[5] += t * b[0]; gb[0] += t * a[5]; }
-    { const T t = T(0.2820947917738782) * Pb[6]; ga[6] += t * b[0]; gb[0] += t * a[6]; }
-  }
-};
-template <> struct Couple3<4, 3, 1, 2> {
-  static constexpr int kTerms = 21;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[0] += T(0.22617901315954042) * (a[0] * b[2]);
-    P[0] += T(0.18467439092237187) * (a[1] * b[1]);
-    P[0] += T(-0.058399170081901867) * (a[2] * b[2]);
-    P[0] += T(-0.058399170081901867) * (a[4] * b[0]);
-    P[0] += T(-0.22617901315954042) * (a[6] * b[0]);
-    P[1] += T(0.18467439092237189) * (a[1] * b[2]);
-    P[1] += T(0.23359668032760761) * (a[2] * b[1]);
-    P[1] += T(-0.1430481681026689) * (a[3] * b[0]);
-    P[1] += T(-0.18467439092237192) * (a[5] * b[0]);
-    P[2] += T(0.20230065940342068) * (a[2] * b[0]);
-    P[2] += T(0.24776669508347601) * (a[3] * b[1]);
-    P[2] += T(0.20230065940342068) * (a[4] * b[2]);
-    P[3] += T(0.18467439092237189) * (a[1] * b[0]);
-    P[3] += T(-0.1430481681026689) * (a[3] * b[2]);
-    P[3] += T(0.23359668032760761) * (a[4] * b[1]);
-    P[3] += T(0.18467439092237192) * (a[5] * b[2]);
-    P[4] += T(0.22617901315954025) * (a[0] * b[0]);
-    P[4] += T(0.058399170081901736) * (a[2] * b[0]);
-    P[4] += T(-0.058399170081901736) * (a[4] * b[2]);
-    P[4] += T(0.18467439092237187) * (a[5] * b[1]);
-    P[4] += T(0.22617901315954025) * (a[6] * b[2]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(0.22617901315954042) * Pb[0]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(0.18467439092237187) * Pb[0]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(-0.058399170081901867) * Pb[0]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(-0.058399170081901867) * Pb[0]; ga[4] += t * b[0]; gb[0] += t * a[4]; }
-    { const T t = T(-0.22617901315954042) * Pb[0]; ga[6] += t * b[0]; gb[0] += t * a[6]; }
-    { const T t = T(0.18467439092237189) * Pb[1]; ga[1] += t * b[2]; gb[2] += t * a[1]; }
-    { const T t = T(0.23359668032760761) * Pb[1]; ga[2] += t * b[1]; gb[1] += t * a[2]; }
-    { const T t = T(-0.1430481681026689) * Pb[1]; ga[3] += t * b[0]; gb[0] += t * a[3]; }
-    { const T t = T(-0.18467439092237192) * Pb[1]; ga[5] += t * b[0]; gb[0] += t * a[5]; }
-    { const T t = T(0.20230065940342068) * Pb[2]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(0.24776669508347601) * Pb[2]; ga[3] += t * b[1]; gb[1] += t * a[3]; }
-    { const T t = T(0.20230065940342068) * Pb[2]; ga[4] += t * b[2]; gb[2] += t * a[4]; }
-    { const T t = T(0.18467439092237189) * Pb[3]; ga[1] += t * b[0]; gb[0] += t * a[1]; }
-    { const T t = T(-0.1430481681026689) * Pb[3]; ga[3] += t * b[2]; gb[2] += t * a[3]; }
-    { const T t = T(0.23359668032760761) * Pb[3]; ga[4] += t * b[1]; gb[1] += t * a[4]; }
-    { const T t = T(0.18467439092237192) * Pb[3]; ga[5] += t * b[2]; gb[2] += t * a[5]; }
-    { const T t = T(0.22617901315954025) * Pb[4]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.058399170081901736) * Pb[4]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(-0.058399170081901736) * Pb[4]; ga[4] += t * b[2]; gb[2] += t * a[4]; }
-    { const T t = T(0.18467439092237187) * Pb[4]; ga[5] += t * b[1]; gb[1] += t * a[5]; }
-    { const T t = T(0.22617901315954025) * Pb[4]; ga[6] += t * b[2]; gb[2] += t * a[6]; }
-  }
-};
-template <> struct Couple3<4, 3, 1, 4> {
-  static constexpr int kTerms = 31;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[0] += T(0.2303294329808902) * (a[0] * b[2]);
-    P[0] += T(0.2303294329808902) * (a[6] * b[0]);
-    P[1] += T(0.16286750396763999) * (a[0] * b[1]);
-    P[1] += T(0.19947114020071635) * (a[1] * b[2]);
-    P[1] += T(0.19947114020071624) * (a[5] * b[0]);
-    P[2] += T(-0.043528171377568134) * (a[0] * b[2]);
-    P[2] += T(0.21324361862292318) * (a[1] * b[1]);
-    P[2] += T(0.16858388283618392) * (a[2] * b[2]);
-    P[2] += T(0.16858388283618392) * (a[4] * b[0]);
-    P[2] += T(0.043528171377568134) * (a[6] * b[0]);
-    P[3] += T(-0.075393004386513446) * (a[1] * b[2]);
-    P[3] += T(0.23841361350444787) * (a[2] * b[1]);
-    P[3] += T(0.19466390027300595) * (a[3] * b[0]);
-    P[3] += T(0.075393004386513349) * (a[5] * b[0]);
-    P[4] += T(-0.150786008773027) * (a[2] * b[0]);
-    P[4] += T(0.24623252122982925) * (a[3] * b[1]);
-    P[4] += T(-0.150786008773027) * (a[4] * b[2]);
-    P[5] += T(-0.075393004386513446) * (a[1] * b[0]);
-    P[5] += T(0.19466390027300595) * (a[3] * b[2]);
-    P[5] += T(0.23841361350444781) * (a[4] * b[1]);
-    P[5] += T(-0.075393004386513335) * (a[5] * b[2]);
-    P[6] += T(-0.043528171377568189) * (a[0] * b[0]);
-    P[6] += T(-0.16858388283618395) * (a[2] * b[0]);
-    P[6] += T(0.16858388283618395) * (a[4] * b[2]);
-    P[6] += T(0.21324361862292318) * (a[5] * b[1]);
-    P[6] += T(-0.043528171377568182) * (a[6] * b[2]);
-    P[7] += T(-0.19947114020071635) * (a[1] * b[0]);
-    P[7] += T(0.19947114020071624) * (a[5] * b[2]);
-    P[7] += T(0.16286750396763999) * (a[6] * b[1]);
-    P[8] += T(-0.23032943298089051) * (a[0] * b[0]);
-    P[8] += T(0.23032943298089054) * (a[6] * b[2]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(0.2303294329808902) * Pb[0]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(0.2303294329808902) * Pb[0]; ga[6] += t * b[0]; gb[0] += t * a[6]; }
-    { const T t = T(0.16286750396763999) * Pb[1]; ga[0] += t * b[1]; gb[1] += t * a[0]; }
-    { const T t = T(0.19947114020071635) * Pb[1]; ga[1] += t * b[2]; gb[2] += t * a[1]; }
-    { const T t = T(0.19947114020071624) * Pb[1]; ga[5] += t * b[0]; gb[0] += t * a[5]; }
-    { const T t = T(-0.043528171377568134) * Pb[2]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(0.21324361862292318) * Pb[2]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(0.16858388283618392) * Pb[2]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(0.16858388283618392) * Pb[2]; ga[4] += t * b[0]; gb[0] += t * a[4]; }
-    { const T t = T(0.043528171377568134) * Pb[2]; ga[6] += t * b[0]; gb[0] += t * a[6]; }
-    { const T t = T(-0.075393004386513446) * Pb[3]; ga[1] += t * b[2]; gb[2] += t * a[1]; }
-    { const T t = T(0.23841361350444787) * Pb[3]; ga[2] += t * b[1]; gb[1] += t * a[2]; }
-    { const T t = T(0.19466390027300595) * Pb[3]; ga[3] += t * b[0]; gb[0] += t * a[3]; }
-    { const T t = T(0.075393004386513349) * Pb[3]; ga[5] += t * b[0]; gb[0] += t * a[5]; }
-    { const T t = T(-0.150786008773027) * Pb[4]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(0.24623252122982925) * Pb[4]; ga[3] += t * b[1]; gb[1] += t * a[3]; }
-    { const T t = T(-0.150786008773027) * Pb[4]; ga[4] += t * b[2]; gb[2] += t * a[4]; }
-    { const T t = T(-0.075393004386513446) * Pb[5]; ga[1] += t * b[0]; gb[0] += t * a[1]; }
-    { const T t = T(0.19466390027300595) * Pb[5]; ga[3] += t * b[2]; gb[2] += t * a[3]; }
-    { const T t = T(0.23841361350444781) * Pb[5]; ga[4] += t * b[1]; gb[1] += t * a[4]; }
-    { const T t = T(-0.075393004386513335) * Pb[5]; ga[5] += t * b[2]; gb[2] += t * a[5]; }
-    { const T t = T(-0.043528171377568189) * Pb[6]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(-0.16858388283618395) * Pb[6]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(0.16858388283618395) * Pb[6]; ga[4] += t * b[2]; gb[2] += t * a[4]; }
-    { const T t = T(0.21324361862292318) * Pb[6]; ga[5] += t * b[1]; gb[1] += t * a[5]; }
-    { const T t = T(-0.043528171377568182) * Pb[6]; ga[6] += t * b[2]; gb[2] += t * a[6]; }
-    { const T t = T(-0.19947114020071635) * Pb[7]; ga[1] += t * b[0]; gb[0] += t * a[1]; }
-    { const T t = T(0.19947114020071624) * Pb[7]; ga[5] += t * b[2]; gb[2] += t * a[5]; }
-    { const T t = T(0.16286750396763999) * Pb[7]; ga[6] += t * b[1]; gb[1] += t * a[6]; }
-    { const T t = T(-0.23032943298089051) * Pb[8]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.23032943298089054) * Pb[8]; ga[6] += t * b[2]; gb[2] += t * a[6]; }
-  }
-};
-template <> struct Couple3<4, 3, 2, 1> {
-  static constexpr int kTerms = 21;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[0] += T(0.22617901315954025) * (a[0] * b[4]);
-    P[0] += T(0.18467439092237189) * (a[1] * b[3]);
-    P[0] += T(0.20230065940342068) * (a[2] * b[2]);
-    P[0] += T(0.058399170081901736) * (a[2] * b[4]);
-    P[0] += T(-0.1430481681026689) * (a[3] * b[1]);
-    P[0] += T(-0.058399170081901867) * (a[4] * b[0]);
-    P[0] += T(-0.18467439092237192) * (a[5] * b[1]);
-    P[0] += T(-0.22617901315954042) * (a[6] * b[0]);
-    P[1] += T(0.18467439092237187) * (a[1] * b[0]);
-    P[1] += T(0.23359668032760761) * (a[2] * b[1]);
-    P[1] += T(0.24776669508347601) * (a[3] * b[2]);
-    P[1] += T(0.23359668032760761) * (a[4] * b[3]);
-    P[1] += T(0.18467439092237187) * (a[5] * b[4]);
-    P[2] += T(0.22617901315954042) * (a[0] * b[0]);
-    P[2] += T(0.18467439092237189) * (a[1] * b[1]);
-    P[2] += T(-0.058399170081901867) * (a[2] * b[0]);
-    P[2] += T(-0.1430481681026689) * (a[3] * b[3]);
-    P[2] += T(0.20230065940342068) * (a[4] * b[2]);
-    P[2] += T(-0.058399170081901736) * (a[4] * b[4]);
-    P[2] += T(0.18467439092237192) * (a[5] * b[3]);
-    P[2] += T(0.22617901315954025) * (a[6] * b[4]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(0.22617901315954025) * Pb[0]; ga[0] += t * b[4]; gb[4] += t * a[0]; }
-    { const T t = T(0.18467439092237189) * Pb[0]; ga[1] += t * b[3]; gb[3] += t * a[1]; }
-    { const T t = T(0.20230065940342068) * Pb[0]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(0.058399170081901736) * Pb[0]; ga[2] += t * b[4]; gb[4] += t * a[2]; }
-    { const T t = T(-0.1430481681026689) * Pb[0]; ga[3] += t * b[1]; gb[1] += t * a[3]; }
-    { const T t = T(-0.058399170081901867) * Pb[0]; ga[4] += t * b[0]; gb[0] += t * a[4]; }
-    { const T t = T(-0.18467439092237192) * Pb[0]; ga[5] += t * b[1]; gb[1] += t * a[5]; }
-    { const T t = T(-0.22617901315954042) * Pb[0]; ga[6] += t * b[0]; gb[0] += t * a[6]; }
-    { const T t = T(0.18467439092237187) * Pb[1]; ga[1] += t * b[0]; gb[0] += t * a[1]; }
-    { const T t = T(0.23359668032760761) * Pb[1]; ga[2] += t * b[1]; gb[1] += t * a[2]; }
-    { const T t = T(0.24776669508347601) * Pb[1]; ga[3] += t * b[2]; gb[2] += t * a[3]; }
-    { const T t = T(0.23359668032760761) * Pb[1]; ga[4] += t * b[3]; gb[3] += t * a[4]; }
-    { const T t = T(0.18467439092237187) * Pb[1]; ga[5] += t * b[4]; gb[4] += t * a[5]; }
-    { const T t = T(0.22617901315954042) * Pb[2]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.18467439092237189) * Pb[2]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(-0.058399170081901867) * Pb[2]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(-0.1430481681026689) * Pb[2]; ga[3] += t * b[3]; gb[3] += t * a[3]; }
-    { const T t = T(0.20230065940342068) * Pb[2]; ga[4] += t * b[2]; gb[2] += t * a[4]; }
-    { const T t = T(-0.058399170081901736) * Pb[2]; ga[4] += t * b[4]; gb[4] += t * a[4]; }
-    { const T t = T(0.18467439092237192) * Pb[2]; ga[5] += t * b[3]; gb[3] += t * a[5]; }
-    { const T t = T(0.22617901315954025) * Pb[2]; ga[6] += t * b[4]; gb[4] += t * a[6]; }
-  }
-};
-template <> struct Couple3<4, 3, 2, 3> {
-  static constexpr int kTerms = 41;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[0] += T(-0.21026104350168001) * (a[0] * b[2]);
-    P[0] += T(0.14867700967939765) * (a[1] * b[3]);
-    P[0] += T(-0.094031597257959315) * (a[2] * b[4]);
-    P[0] += T(-0.094031597257959357) * (a[4] * b[0]);
-    P[0] += T(0.14867700967939756) * (a[5] * b[1]);
-    P[1] += T(0.14867700967939765) * (a[0] * b[3]);
-    P[1] += T(0.11516471649044524) * (a[2] * b[3]);
-    P[1] += T(-0.1880631945159188) * (a[3] * b[0]);
-    P[1] += T(0.11516471649044524) * (a[4] * b[1]);
-    P[1] += T(-0.14867700967939765) * (a[6] * b[1]);
-    P[2] += T(-0.094031597257959357) * (a[0] * b[4]);
-    P[2] += T(0.11516471649044524) * (a[1] * b[3]);
-    P[2] += T(0.12615662610100786) * (a[2] * b[2]);
-    P[2] += T(-0.14567312407894395) * (a[2] * b[4]);
-    P[2] += T(0.059470803871758834) * (a[3] * b[1]);
-    P[2] += T(0.14567312407894392) * (a[4] * b[0]);
-    P[2] += T(-0.1151647164904453) * (a[5] * b[1]);
-    P[2] += T(0.094031597257959329) * (a[6] * b[0]);
-    P[3] += T(-0.1880631945159188) * (a[1] * b[0]);
-    P[3] += T(0.059470803871758834) * (a[2] * b[1]);
-    P[3] += T(0.16820883480134416) * (a[3] * b[2]);
-    P[3] += T(0.059470803871758827) * (a[4] * b[3]);
-    P[3] += T(-0.18806319451591863) * (a[5] * b[4]);
-    P[4] += T(-0.094031597257959315) * (a[0] * b[0]);
-    P[4] += T(0.11516471649044524) * (a[1] * b[1]);
-    P[4] += T(0.14567312407894392) * (a[2] * b[0]);
-    P[4] += T(0.059470803871758827) * (a[3] * b[3]);
-    P[4] += T(0.12615662610100786) * (a[4] * b[2]);
-    P[4] += T(0.14567312407894398) * (a[4] * b[4]);
-    P[4] += T(0.11516471649044534) * (a[5] * b[3]);
-    P[4] += T(-0.094031597257959357) * (a[6] * b[4]);
-    P[5] += T(0.14867700967939756) * (a[0] * b[1]);
-    P[5] += T(-0.1151647164904453) * (a[2] * b[1]);
-    P[5] += T(-0.18806319451591863) * (a[3] * b[4]);
-    P[5] += T(0.1151647164904453) * (a[4] * b[3]);
-    P[5] += T(0.14867700967939756) * (a[6] * b[3]);
-    P[6] += T(-0.14867700967939765) * (a[1] * b[1]);
-    P[6] += T(0.094031597257959357) * (a[2] * b[0]);
-    P[6] += T(-0.094031597257959315) * (a[4] * b[4]);
-    P[6] += T(0.14867700967939756) * (a[5] * b[3]);
-    P[6] += T(-0.21026104350168001) * (a[6] * b[2]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(-0.21026104350168001) * Pb[0]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(0.14867700967939765) * Pb[0]; ga[1] += t * b[3]; gb[3] += t * a[1]; }
-    { const T t = T(-0.094031597257959315) * Pb[0]; ga[2] += t * b[4]; gb[4] += t * a[2]; }
-    { const T t = T(-0.094031597257959357) * Pb[0]; ga[4] += t * b[0]; gb[0] += t * a[4]; }
-    { const T t = T(0.14867700967939756) * Pb[0]; ga[5] += t * b[1]; gb[1] += t * a[5]; }
-    { const T t = T(0.14867700967939765) * Pb[1]; ga[0] += t * b[3]; gb[3] += t * a[0]; }
-    { const T t = T(0.11516471649044524) * Pb[1]; ga[2] += t * b[3]; gb[3] += t * a[2]; }
-    { const T t = T(-0.1880631945159188) * Pb[1]; ga[3] += t * b[0]; gb[0] += t * a[3]; }
-    { const T t = T(0.11516471649044524) * Pb[1]; ga[4] += t * b[1]; gb[1] += t * a[4]; }
-    { const T t = T(-0.14867700967939765) * Pb[1]; ga[6] += t * b[1]; gb[1] += t * a[6]; }
-    { const T t = T(-0.094031597257959357) * Pb[2]; ga[0] += t * b[4]; gb[4] += t * a[0]; }
-    { const T t = T(0.11516471649044524) * Pb[2]; ga[1] += t * b[3]; gb[3] += t * a[1]; }
-    { const T t = T(0.12615662610100786) * Pb[2]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(-0.14567312407894395) * Pb[2]; ga[2] += t * b[4]; gb[4] += t * a[2]; }
-    { const T t = T(0.059470803871758834) * Pb[2]; ga[3] += t * b[1]; gb[1] += t * a[3]; }
-    { const T t = T(0.14567312407894392) * Pb[2]; ga[4] += t * b[0]; gb[0] += t * a[4]; }
-    { const T t = T(-0.1151647164904453) * Pb[2]; ga[5] += t * b[1]; gb[1] += t * a[5]; }
-    { const T t = T(0.094031597257959329) * Pb[2]; ga[6] += t * b[0]; gb[0] += t * a[6]; }
-    { const T t = T(-0.1880631945159188) * Pb[3]; ga[1] += t * b[0]; gb[0] += t * a[1]; }
-    { const T t = T(0.059470803871758834) * Pb[3]; ga[2] += t * b[1]; gb[1] += t * a[2]; }
-    { const T t = T(0.16820883480134416) * Pb[3]; ga[3] += t * b[2]; gb[2] += t * a[3]; }
-    { const T t = T(0.059470803871758827) * Pb[3]; ga[4] += t * b[3]; gb[3] += t * a[4]; }
-    { const T t = T(-0.18806319451591863) * Pb[3]; ga[5] += t * b[4]; gb[4] += t * a[5]; }
-    { const T t = T(-0.094031597257959315) * Pb[4]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.11516471649044524) * Pb[4]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(0.14567312407894392) * Pb[4]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(0.059470803871758827) * Pb[4]; ga[3] += t * b[3]; gb[3] += t * a[3]; }
-    { const T t = T(0.12615662610100786) * Pb[4]; ga[4] += t * b[2]; gb[2] += t * a[4]; }
-    { const T t = T(0.14567312407894398) * Pb[4]; ga[4] += t * b[4]; gb[4] += t * a[4]; }
-    { const T t = T(0.11516471649044534) * Pb[4]; ga[5] += t * b[3]; gb[3] += t * a[5]; }
-    { const T t = T(-0.094031597257959357) * Pb[4]; ga[6] += t * b[4]; gb[4] += t * a[6]; }
-    { const T t = T(0.14867700967939756) * Pb[5]; ga[0] += t * b[1]; gb[1] += t * a[0]; }
-    { const T t = T(-0.1151647164904453) * Pb[5]; ga[2] += t * b[1]; gb[1] += t * a[2]; }
-    { const T t = T(-0.18806319451591863) * Pb[5]; ga[3] += t * b[4]; gb[4] += t * a[3]; }
-    { const T t = T(0.1151647164904453) * Pb[5]; ga[4] += t * b[3]; gb[3] += t * a[4]; }
-    { const T t = T(0.14867700967939756) * Pb[5]; ga[6] += t * b[3]; gb[3] += t * a[6]; }
-    { const T t = T(-0.14867700967939765) * Pb[6]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(0.094031597257959357) * Pb[6]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(-0.094031597257959315) * Pb[6]; ga[4] += t * b[4]; gb[4] += t * a[4]; }
-    { const T t = T(0.14867700967939756) * Pb[6]; ga[5] += t * b[3]; gb[3] += t * a[5]; }
-    { const T t = T(-0.21026104350168001) * Pb[6]; ga[6] += t * b[2]; gb[2] += t * a[6]; }
-  }
-};
-template <> struct Couple3<4, 3, 3, 0> {
-  static constexpr int kTerms = 7;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[0] += T(0.2820947917738782) * (a[0] * b[0]);
-    P[0] += T(0.2820947917738782) * (a[1] * b[1]);
-    P[0] += T(0.28209479177387825) * (a[2] * b[2]);
-    P[0] += T(0.28209479177387814) * (a[3] * b[3]);
-    P[0] += T(0.28209479177387825) * (a[4] * b[4]);
-    P[0] += T(0.28209479177387825) * (a[5] * b[5]);
-    P[0] += T(0.2820947917738782) * (a[6] * b[6]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(0.2820947917738782) * Pb[0]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.2820947917738782) * Pb[0]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(0.28209479177387825) * Pb[0]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(0.28209479177387814) * Pb[0]; ga[3] += t * b[3]; gb[3] += t * a[3]; }
-    { const T t = T(0.28209479177387825) * Pb[0]; ga[4] += t * b[4]; gb[4] += t * a[4]; }
-    { const T t = T(0.28209479177387825) * Pb[0]; ga[5] += t * b[5]; gb[5] += t * a[5]; }
-    { const T t = T(0.2820947917738782) * Pb[0]; ga[6] += t * b[6]; gb[6] += t * a[6]; }
-  }
-};
-template <> struct Couple3<4, 3, 3, 2> {
-  static constexpr int kTerms = 41;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[0] += T(-0.094031597257959357) * (a[0] * b[4]);
-    P[0] += T(-0.1880631945159188) * (a[1] * b[3]);
-    P[0] += T(0.14567312407894387) * (a[2] * b[4]);
-    P[0] += T(0.094031597257959357) * (a[2] * b[6]);
-    P[0] += T(-0.1880631945159188) * (a[3] * b[1]);
-    P[0] += T(-0.094031597257959357) * (a[4] * b[0]);
-    P[0] += T(0.14567312407894387) * (a[4] * b[2]);
-    P[0] += T(0.094031597257959357) * (a[6] * b[2]);
-    P[1] += T(0.14867700967939754) * (a[0] * b[5]);
-    P[1] += T(0.11516471649044524) * (a[1] * b[4]);
-    P[1] += T(-0.14867700967939765) * (a[1] * b[6]);
-    P[1] += T(0.0594708038717588) * (a[2] * b[3]);
-    P[1] += T(-0.1151647164904453) * (a[2] * b[5]);
-    P[1] += T(0.0594708038717588) * (a[3] * b[2]);
-    P[1] += T(0.11516471649044524) * (a[4] * b[1]);
-    P[1] += T(0.14867700967939754) * (a[5] * b[0]);
-    P[1] += T(-0.1151647164904453) * (a[5] * b[2]);
-    P[1] += T(-0.14867700967939765) * (a[6] * b[1]);
-    P[2] += T(-0.21026104350168001) * (a[0] * b[0]);
-    P[2] += T(0.12615662610100786) * (a[2] * b[2]);
-    P[2] += T(0.16820883480134416) * (a[3] * b[3]);
-    P[2] += T(0.12615662610100786) * (a[4] * b[4]);
-    P[2] += T(-0.21026104350168001) * (a[6] * b[6]);
-    P[3] += T(0.14867700967939765) * (a[0] * b[1]);
-    P[3] += T(0.14867700967939765) * (a[1] * b[0]);
-    P[3] += T(0.11516471649044524) * (a[1] * b[2]);
-    P[3] += T(0.11516471649044524) * (a[2] * b[1]);
-    P[3] += T(0.059470803871758765) * (a[3] * b[4]);
-    P[3] += T(0.059470803871758765) * (a[4] * b[3]);
-    P[3] += T(0.1151647164904453) * (a[4] * b[5]);
-    P[3] += T(0.11516471649044534) * (a[5] * b[4]);
-    P[3] += T(0.14867700967939754) * (a[5] * b[6]);
-    P[3] += T(0.14867700967939754) * (a[6] * b[5]);
-    P[4] += T(-0.094031597257959357) * (a[0] * b[2]);
-    P[4] += T(-0.094031597257959357) * (a[2] * b[0]);
-    P[4] += T(-0.14567312407894392) * (a[2] * b[2]);
-    P[4] += T(-0.18806319451591855) * (a[3] * b[5]);
-    P[4] += T(0.14567312407894392) * (a[4] * b[4]);
-    P[4] += T(-0.094031597257959371) * (a[4] * b[6]);
-    P[4] += T(-0.1880631945159186) * (a[5] * b[3]);
-    P[4] += T(-0.094031597257959357) * (a[6] * b[4]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(-0.094031597257959357) * Pb[0]; ga[0] += t * b[4]; gb[4] += t * a[0]; }
-    { const T t = T(-0.1880631945159188) * Pb[0]; ga[1] += t * b[3]; gb[3] += t * a[1]; }
-    { const T t = T(0.14567312407894387) * Pb[0]; ga[2] += t * b[4]; gb[4] += t * a[2]; }
-    { const T t = T(0.094031597257959357) * Pb[0]; ga[2] += t * b[6]; gb[6] += t * a[2]; }
-    { const T t = T(-0.1880631945159188) * Pb[0]; ga[3] += t * b[1]; gb[1] += t * a[3]; }
-    { const T t = T(-0.094031597257959357) * Pb[0]; ga[4] += t * b[0]; gb[0] += t * a[4]; }
-    { const T t = T(0.14567312407894387) * Pb[0]; ga[4] += t * b[2]; gb[2] += t * a[4]; }
-    { const T t = T(0.094031597257959357) * Pb[0]; ga[6] += t * b[2]; gb[2] += t * a[6]; }
-    { const T t = T(0.14867700967939754) * Pb[1]; ga[0] += t * b[5]; gb[5] += t * a[0]; }
-    { const T t = T(0.11516471649044524) * Pb[1]; ga[1] += t * b[4]; gb[4] += t * a[1]; }
-    { const T t = T(-0.14867700967939765) * Pb[1]; ga[1] += t * b[6]; gb[6] += t * a[1]; }
-    { const T t = T(0.0594708038717588) * Pb[1]; ga[2] += t * b[3]; gb[3] += t * a[2]; }
-    { const T t = T(-0.1151647164904453) * Pb[1]; ga[2] += t * b[5]; gb[5] += t * a[2]; }
-    { const T t = T(0.0594708038717588) * Pb[1]; ga[3] += t * b[2]; gb[2] += t * a[3]; }
-    { const T t = T(0.11516471649044524) * Pb[1]; ga[4] += t * b[1]; gb[1] += t * a[4]; }
-    { const T t = T(0.14867700967939754) * Pb[1]; ga[5] += t * b[0]; gb[0] += t * a[5]; }
-    { const T t = T(-0.1151647164904453) * Pb[1]; ga[5] += t * b[2]; gb[2] += t * a[5]; }
-    { const T t = T(-0.14867700967939765) * Pb[1]; ga[6] += t * b[1]; gb[1] += t * a[6]; }
-    { const T t = T(-0.21026104350168001) * Pb[2]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.12615662610100786) * Pb[2]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(0.16820883480134416) * Pb[2]; ga[3] += t * b[3]; gb[3] += t * a[3]; }
-    { const T t = T(0.12615662610100786) * Pb[2]; ga[4] += t * b[4]; gb[4] += t * a[4]; }
-    { const T t = T(-0.21026104350168001) * Pb[2]; ga[6] += t * b[6]; gb[6] += t * a[6]; }
-    { const T t = T(0.14867700967939765) * Pb[3]; ga[0] += t * b[1]; gb[1] += t * a[0]; }
-    { const T t = T(0.14867700967939765) * Pb[3]; ga[1] += t * b[0]; gb[0] += t * a[1]; }
-    { const T t = T(0.11516471649044524) * Pb[3]; ga[1] += t * b[2]; gb[2] += t * a[1]; }
-    { const T t = T(0.11516471649044524) * Pb[3]; ga[2] += t * b[1]; gb[1] += t * a[2]; }
-    { const T t = T(0.059470803871758765) * Pb[3]; ga[3] += t * b[4]; gb[4] += t * a[3]; }
-    { const T t = T(0.059470803871758765) * Pb[3]; ga[4] += t * b[3]; gb[3] += t * a[4]; }
-    { const T t = T(0.1151647164904453) * Pb[3]; ga[4] += t * b[5]; gb[5] += t * a[4]; }
-    { const T t = T(0.11516471649044534) * Pb[3]; ga[5] += t * b[4]; gb[4] += t * a[5]; }
-    { const T t = T(0.14867700967939754) * Pb[3]; ga[5] += t * b[6]; gb[6] += t * a[5]; }
-    { const T t = T(0.14867700967939754) * Pb[3]; ga[6] += t * b[5]; gb[5] += t * a[6]; }
-    { const T t = T(-0.094031597257959357) * Pb[4]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(-0.094031597257959357) * Pb[4]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(-0.14567312407894392) * Pb[4]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(-0.18806319451591855) * Pb[4]; ga[3] += t * b[5]; gb[5] += t * a[3]; }
-    { const T t = T(0.14567312407894392) * Pb[4]; ga[4] += t * b[4]; gb[4] += t * a[4]; }
-    { const T t = T(-0.094031597257959371) * Pb[4]; ga[4] += t * b[6]; gb[6] += t * a[4]; }
-    { const T t = T(-0.1880631945159186) * Pb[4]; ga[5] += t * b[3]; gb[3] += t * a[5]; }
-    { const T t = T(-0.094031597257959357) * Pb[4]; ga[6] += t * b[4]; gb[4] += t * a[6]; }
-  }
-};
-template <> struct Couple3<4, 3, 3, 4> {
-  static constexpr int kTerms = 67;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[0] += T(-0.11752006695060026) * (a[0] * b[4]);
-    P[0] += T(0.151717754048285) * (a[1] * b[5]);
-    P[0] += T(-0.11752006695060026) * (a[2] * b[6]);
-    P[0] += T(-0.11752006695060026) * (a[4] * b[0]);
-    P[0] += T(0.151717754048285) * (a[5] * b[1]);
-    P[0] += T(-0.11752006695060023) * (a[6] * b[2]);
-    P[1] += T(-0.20355072686733564) * (a[0] * b[3]);
-    P[1] += T(0.067850242289111948) * (a[1] * b[4]);
-    P[1] += T(0.067850242289111934) * (a[2] * b[5]);
-    P[1] += T(-0.20355072686733564) * (a[3] * b[0]);
-    P[1] += T(0.067850242289111948) * (a[4] * b[1]);
-    P[1] += T(0.067850242289111934) * (a[5] * b[2]);
-    P[2] += T(0.13325523051897822) * (a[0] * b[4]);
-    P[2] += T(-0.044418410172992757) * (a[1] * b[3]);
-    P[2] += T(0.11468784191000729) * (a[2] * b[4]);
-    P[2] += T(-0.1332552305189782) * (a[2] * b[6]);
-    P[2] += T(-0.044418410172992757) * (a[3] * b[1]);
-    P[2] += T(0.1332552305189782) * (a[4] * b[0]);
-    P[2] += T(0.11468784191000729) * (a[4] * b[2]);
-    P[2] += T(-0.1332552305189782) * (a[6] * b[2]);
-    P[3] += T(-0.099322584599279867) * (a[0] * b[5]);
-    P[3] += T(0.10257992428141016) * (a[1] * b[4]);
-    P[3] += T(0.099322584599279881) * (a[1] * b[6]);
-    P[3] += T(0.099322584599279909) * (a[2] * b[3]);
-    P[3] += T(-0.10257992428141016) * (a[2] * b[5]);
-    P[3] += T(0.099322584599279909) * (a[3] * b[2]);
-    P[3] += T(0.10257992428141016) * (a[4] * b[1]);
-    P[3] += T(-0.099322584599279867) * (a[5] * b[0]);
-    P[3] += T(-0.10257992428141022) * (a[5] * b[2]);
-    P[3] += T(0.099322584599279881) * (a[6] * b[1]);
-    P[4] += T(0.076934943211057691) * (a[0] * b[0]);
-    P[4] += T(-0.17951486749246795) * (a[1] * b[1]);
-    P[4] += T(0.025644981070352291) * (a[2] * b[2]);
-    P[4] += T(0.15386988642211546) * (a[3] * b[3]);
-    P[4] += T(0.025644981070352325) * (a[4] * b[4]);
-    P[4] += T(-0.17951486749246778) * (a[5] * b[5]);
-    P[4] += T(0.076934943211057705) * (a[6] * b[6]);
-    P[5] += T(-0.099322584599279881) * (a[0] * b[1]);
-    P[5] += T(-0.099322584599279881) * (a[1] * b[0]);
-    P[5] += T(0.10257992428141016) * (a[1] * b[2]);
-    P[5] += T(0.10257992428141016) * (a[2] * b[1]);
-    P[5] += T(0.099322584599279881) * (a[3] * b[4]);
-    P[5] += T(0.099322584599279881) * (a[4] * b[3]);
-    P[5] += T(0.10257992428141022) * (a[4] * b[5]);
-    P[5] += T(0.10257992428141022) * (a[5] * b[4]);
-    P[5] += T(-0.099322584599279867) * (a[5] * b[6]);
-    P[5] += T(-0.099322584599279867) * (a[6] * b[5]);
-    P[6] += T(0.1332552305189782) * (a[0] * b[2]);
-    P[6] += T(0.1332552305189782) * (a[2] * b[0]);
-    P[6] += T(-0.11468784191000719) * (a[2] * b[2]);
-    P[6] += T(-0.044418410172992556) * (a[3] * b[5]);
-    P[6] += T(0.11468784191000722) * (a[4] * b[4]);
-    P[6] += T(0.13325523051897817) * (a[4] * b[6]);
-    P[6] += T(-0.044418410172992556) * (a[5] * b[3]);
-    P[6] += T(0.1332552305189782) * (a[6] * b[4]);
-    P[7] += T(-0.067850242289111962) * (a[1] * b[2]);
-    P[7] += T(-0.067850242289111962) * (a[2] * b[1]);
-    P[7] += T(-0.20355072686733564) * (a[3] * b[6]);
-    P[7] += T(0.067850242289111934) * (a[4] * b[5]);
-    P[7] += T(0.067850242289111934) * (a[5] * b[4]);
-    P[7] += T(-0.20355072686733564) * (a[6] * b[3]);
-    P[8] += T(0.1175200669506001) * (a[0] * b[2]);
-    P[8] += T(-0.15171775404828516) * (a[1] * b[1]);
-    P[8] += T(0.1175200669506001) * (a[2] * b[0]);
-    P[8] += T(-0.11752006695060009) * (a[4] * b[6]);
-    P[8] += T(0.15171775404828503) * (a[5] * b[5]);
-    P[8] += T(-0.11752006695060012) * (a[6] * b[4]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(-0.11752006695060026) * Pb[0]; ga[0] += t * b[4]; gb[4] += t * a[0]; }
-    { const T t = T(0.151717754048285) * Pb[0]; ga[1] += t * b[5]; gb[5] += t * a[1]; }
-    { const T t = T(-0.11752006695060026) * Pb[0]; ga[2] += t * b[6]; gb[6] += t * a[2]; }
-    { const T t = T(-0.11752006695060026) * Pb[0]; ga[4] += t * b[0]; gb[0] += t * a[4]; }
-    { const T t = T(0.151717754048285) * Pb[0]; ga[5] += t * b[1]; gb[1] += t * a[5]; }
-    { const T t = T(-0.11752006695060023) * Pb[0]; ga[6] += t * b[2]; gb[2] += t * a[6]; }
-    { const T t = T(-0.20355072686733564) * Pb[1]; ga[0] += t * b[3]; gb[3] += t * a[0]; }
-    { const T t = T(0.067850242289111948) * Pb[1]; ga[1] += t * b[4]; gb[4] += t * a[1]; }
-    { const T t = T(0.067850242289111934) * Pb[1]; ga[2] += t * b[5]; gb[5] += t * a[2]; }
-    { const T t = T(-0.20355072686733564) * Pb[1]; ga[3] += t * b[0]; gb[0] += t * a[3]; }
-    { const T t = T(0.067850242289111948) * Pb[1]; ga[4] += t * b[1]; gb[1] += t * a[4]; }
-    { const T t = T(0.067850242289111934) * Pb[1]; ga[5] += t * b[2]; gb[2] += t * a[5]; }
-    { const T t = T(0.13325523051897822) * Pb[2]; ga[0] += t * b[4]; gb[4] += t * a[0]; }
-    { const T t = T(-0.044418410172992757) * Pb[2]; ga[1] += t * b[3]; gb[3] += t * a[1]; }
-    { const T t = T(0.11468784191000729) * Pb[2]; ga[2] += t * b[4]; gb[4] += t * a[2]; }
-    { const T t = T(-0.1332552305189782) * Pb[2]; ga[2] += t * b[6]; gb[6] += t * a[2]; }
-    { const T t = T(-0.044418410172992757) * Pb[2]; ga[3] += t * b[1]; gb[1] += t * a[3]; }
-    { const T t = T(0.1332552305189782) * Pb[2]; ga[4] += t * b[0]; gb[0] += t * a[4]; }
-    { const T t = T(0.11468784191000729) * Pb[2]; ga[4] += t * b[2]; gb[2] += t * a[4]; }
-    { const T t = T(-0.1332552305189782) * Pb[2]; ga[6] += t * b[2]; gb[2] += t * a[6]; }
-    { const T t = T(-0.099322584599279867) * Pb[3]; ga[0] += t * b[5]; gb[5] += t * a[0]; }
-    { const T t = T(0.10257992428141016) * Pb[3]; ga[1] += t * b[4]; gb[4] += t * a[1]; }
-    { const T t = T(0.099322584599279881) * Pb[3]; ga[1] += t * b[6]; gb[6] += t * a[1]; }
-    { const T t = T(0.099322584599279909) * Pb[3]; ga[2] += t * b[3]; gb[3] += t * a[2]; }
-    { const T t = T(-0.10257992428141016) * Pb[3]; ga[2] += t * b[5]; gb[5] += t * a[2]; }
-    { const T t = T(0.099322584599279909) * Pb[3]; ga[3] += t * b[2]; gb[2] += t * a[3]; }
-    { const T t = T(0.10257992428141016) * Pb[3]; ga[4] += t * b[1]; gb[1] += t * a[4]; }
-    { const T t = T(-0.099322584599279867) * Pb[3]; ga[5] += t * b[0]; gb[0] += t * a[5]; }
-    { const T t = T(-0.10257992428141022) * Pb[3]; ga[5] += t * b[2]; gb[2] += t * a[5]; }
-    { const T t = T(0.099322584599279881) * Pb[3]; ga[6] += t * b[1]; gb[1] += t * a[6]; }
-    { const T t = T(0.076934943211057691) * Pb[4]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(-0.17951486749246795) * Pb[4]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(0.025644981070352291) * Pb[4]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(0.15386988642211546) * Pb[4]; ga[3] += t * b[3]; gb[3] += t * a[3]; }
-    { const T t = T(0.025644981070352325) * Pb[4]; ga[4] += t * b[4]; gb[4] += t * a[4]; }
-    { const T t = T(-0.17951486749246778) * Pb[4]; ga[5] += t * b[5]; gb[5] += t * a[5]; }
-    { const T t = T(0.076934943211057705) * Pb[4]; ga[6] += t * b[6]; gb[6] += t * a[6]; }
-    { const T t = T(-0.099322584599279881) * Pb[5]; ga[0] += t * b[1]; gb[1] += t * a[0]; }
-    { const T t = T(-0.099322584599279881) * Pb[5]; ga[1] += t * b[0]; gb[0] += t * a[1]; }
-    { const T t = T(0.10257992428141016) * Pb[5]; ga[1] += t * b[2]; gb[2] += t * a[1]; }
-    { const T t = T(0.10257992428141016) * Pb[5]; ga[2] += t * b[1]; gb[1] += t * a[2]; }
-    { const T t = T(0.099322584599279881) * Pb[5]; ga[3] += t * b[4]; gb[4] += t * a[3]; }
-    { const T t = T(0.099322584599279881) * Pb[5]; ga[4] += t * b[3]; gb[3] += t * a[4]; }
-    { const T t = T(0.10257992428141022) * Pb[5]; ga[4] += t * b[5]; gb[5] += t * a[4]; }
-    { const T t = T(0.10257992428141022) * Pb[5]; ga[5] += t * b[4]; gb[4] += t * a[5]; }
-    { const T t = T(-0.099322584599279867) * Pb[5]; ga[5] += t * b[6]; gb[6] += t * a[5]; }
-    { const T t = T(-0.099322584599279867) * Pb[5]; ga[6] += t * b[5]; gb[5] += t * a[6]; }
-    { const T t = T(0.1332552305189782) * Pb[6]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(0.1332552305189782) * Pb[6]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(-0.11468784191000719) * Pb[6]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(-0.044418410172992556) * Pb[6]; ga[3] += t * b[5]; gb[5] += t * a[3]; }
-    { const T t = T(0.11468784191000722) * Pb[6]; ga[4] += t * b[4]; gb[4] += t * a[4]; }
-    { const T t = T(0.13325523051897817) * Pb[6]; ga[4] += t * b[6]; gb[6] += t * a[4]; }
-    { const T t = T(-0.044418410172992556) * Pb[6]; ga[5] += t * b[3]; gb[3] += t * a[5]; }
-    { const T t = T(0.1332552305189782) * Pb[6]; ga[6] += t * b[4]; gb[4] += t * a[6]; }
-    { const T t = T(-0.067850242289111962) * Pb[7]; ga[1] += t * b[2]; gb[2] += t * a[1]; }
-    { const T t = T(-0.067850242289111962) * Pb[7]; ga[2] += t * b[1]; gb[1] += t * a[2]; }
-    { const T t = T(-0.20355072686733564) * Pb[7]; ga[3] += t * b[6]; gb[6] += t * a[3]; }
-    { const T t = T(0.067850242289111934) * Pb[7]; ga[4] += t * b[5]; gb[5] += t * a[4]; }
-    { const T t = T(0.067850242289111934) * Pb[7]; ga[5] += t * b[4]; gb[4] += t * a[5]; }
-    { const T t = T(-0.20355072686733564) * Pb[7]; ga[6] += t * b[3]; gb[3] += t * a[6]; }
-    { const T t = T(0.1175200669506001) * Pb[8]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(-0.15171775404828516) * Pb[8]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(0.1175200669506001) * Pb[8]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(-0.11752006695060009) * Pb[8]; ga[4] += t * b[6]; gb[6] += t * a[4]; }
-    { const T t = T(0.15171775404828503) * Pb[8]; ga[5] += t * b[5]; gb[5] += t * a[5]; }
-    { const T t = T(-0.11752006695060012) * Pb[8]; ga[6] += t * b[4]; gb[4] += t * a[6]; }
-  }
-};
-template <> struct Couple3<4, 3, 4, 1> {
-  static constexpr int kTerms = 31;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[0] += T(-0.043528171377568182) * (a[0] * b[6]);
-    P[0] += T(-0.23032943298089045) * (a[0] * b[8]);
-    P[0] += T(-0.075393004386513432) * (a[1] * b[5]);
-    P[0] += T(-0.1994711402007163) * (a[1] * b[7]);
-    P[0] += T(-0.15078600877302697) * (a[2] * b[4]);
-    P[0] += T(-0.16858388283618392) * (a[2] * b[6]);
-    P[0] += T(0.19466390027300592) * (a[3] * b[3]);
-    P[0] += T(0.16858388283618389) * (a[4] * b[2]);
-    P[0] += T(0.19947114020071621) * (a[5] * b[1]);
-    P[0] += T(0.075393004386513335) * (a[5] * b[3]);
-    P[0] += T(0.23032943298089015) * (a[6] * b[0]);
-    P[0] += T(0.043528171377568127) * (a[6] * b[2]);
-    P[1] += T(0.16286750396763996) * (a[0] * b[1]);
-    P[1] += T(0.21324361862292315) * (a[1] * b[2]);
-    P[1] += T(0.23841361350444784) * (a[2] * b[3]);
-    P[1] += T(0.24623252122982922) * (a[3] * b[4]);
-    P[1] += T(0.23841361350444776) * (a[4] * b[5]);
-    P[1] += T(0.21324361862292315) * (a[5] * b[6]);
-    P[1] += T(0.16286750396763996) * (a[6] * b[7]);
-    P[2] += T(0.23032943298089015) * (a[0] * b[0]);
-    P[2] += T(-0.043528171377568127) * (a[0] * b[2]);
-    P[2] += T(0.1994711402007163) * (a[1] * b[1]);
-    P[2] += T(-0.075393004386513432) * (a[1] * b[3]);
-    P[2] += T(0.16858388283618389) * (a[2] * b[2]);
-    P[2] += T(0.19466390027300592) * (a[3] * b[5]);
-    P[2] += T(-0.15078600877302697) * (a[4] * b[4]);
-    P[2] += T(0.16858388283618392) * (a[4] * b[6]);
-    P[2] += T(-0.075393004386513321) * (a[5] * b[5]);
-    P[2] += T(0.19947114020071621) * (a[5] * b[7]);
-    P[2] += T(-0.043528171377568176) * (a[6] * b[6]);
-    P[2] += T(0.23032943298089048) * (a[6] * b[8]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(-0.043528171377568182) * Pb[0]; ga[0] += t * b[6]; gb[6] += t * a[0]; }
-    { const T t = T(-0.23032943298089045) * Pb[0]; ga[0] += t * b[8]; gb[8] += t * a[0]; }
-    { const T t = T(-0.075393004386513432) * Pb[0]; ga[1] += t * b[5]; gb[5] += t * a[1]; }
-    { const T t = T(-0.1994711402007163) * Pb[0]; ga[1] += t * b[7]; gb[7] += t * a[1]; }
-    { const T t = T(-0.15078600877302697) * Pb[0]; ga[2] += t * b[4]; gb[4] += t * a[2]; }
-    { const T t = T(-0.16858388283618392) * Pb[0]; ga[2] += t * b[6]; gb[6] += t * a[2]; }
-    { const T t = T(0.19466390027300592) * Pb[0]; ga[3] += t * b[3]; gb[3] += t * a[3]; }
-    { const T t = T(0.16858388283618389) * Pb[0]; ga[4] += t * b[2]; gb[2] += t * a[4]; }
-    { const T t = T(0.19947114020071621) * Pb[0]; ga[5] += t * b[1]; gb[1] += t * a[5]; }
-    { const T t = T(0.075393004386513335) * Pb[0]; ga[5] += t * b[3]; gb[3] += t * a[5]; }
-    { const T t = T(0.23032943298089015) * Pb[0]; ga[6] += t * b[0]; gb[0] += t * a[6]; }
-    { const T t = T(0.043528171377568127) * Pb[0]; ga[6] += t * b[2]; gb[2] += t * a[6]; }
-    { const T t = T(0.16286750396763996) * Pb[1]; ga[0] += t * b[1]; gb[1] += t * a[0]; }
-    { const T t = T(0.21324361862292315) * Pb[1]; ga[1] += t * b[2]; gb[2] += t * a[1]; }
-    { const T t = T(0.23841361350444784) * Pb[1]; ga[2] += t * b[3]; gb[3] += t * a[2]; }
-    { const T t = T(0.24623252122982922) * Pb[1]; ga[3] += t * b[4]; gb[4] += t * a[3]; }
-    { const T t = T(0.23841361350444776) * Pb[1]; ga[4] += t * b[5]; gb[5] += t * a[4]; }
-    { const T t = T(0.21324361862292315) * Pb[1]; ga[5] += t * b[6]; gb[6] += t * a[5]; }
-    { const T t = T(0.16286750396763996) * Pb[1]; ga[6] += t * b[7]; gb[7] += t * a[6]; }
-    { const T t = T(0.23032943298089015) * Pb[2]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(-0.043528171377568127) * Pb[2]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(0.1994711402007163) * Pb[2]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(-0.075393004386513432) * Pb[2]; ga[1] += t * b[3]; gb[3] += t * a[1]; }
-    { const T t = T(0.16858388283618389) * Pb[2]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(0.19466390027300592) * Pb[2]; ga[3] += t * b[5]; gb[5] += t * a[3]; }
-    { const T t = T(-0.15078600877302697) * Pb[2]; ga[4] += t * b[4]; gb[4] += t * a[4]; }
-    { const T t = T(0.16858388283618392) * Pb[2]; ga[4] += t * b[6]; gb[6] += t * a[4]; }
-    { const T t = T(-0.075393004386513321) * Pb[2]; ga[5] += t * b[5]; gb[5] += t * a[5]; }
-    { const T t = T(0.19947114020071621) * Pb[2]; ga[5] += t * b[7]; gb[7] += t * a[5]; }
-    { const T t = T(-0.043528171377568176) * Pb[2]; ga[6] += t * b[6]; gb[6] += t * a[6]; }
-    { const T t = T(0.23032943298089048) * Pb[2]; ga[6] += t * b[8]; gb[8] += t * a[6]; }
-  }
-};
-template <> struct Couple3<4, 3, 4, 3> {
-  static constexpr int kTerms = 67;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[0] += T(0.076934943211057705) * (a[0] * b[4]);
-    P[0] += T(-0.099322584599279867) * (a[1] * b[5]);
-    P[0] += T(0.13325523051897822) * (a[2] * b[6]);
-    P[0] += T(0.11752006695060022) * (a[2] * b[8]);
-    P[0] += T(-0.20355072686733561) * (a[3] * b[1]);
-    P[0] += T(-0.11752006695060026) * (a[4] * b[0]);
-    P[0] += T(0.13325523051897814) * (a[4] * b[2]);
-    P[0] += T(-0.099322584599279881) * (a[5] * b[3]);
-    P[1] += T(-0.099322584599279881) * (a[0] * b[5]);
-    P[1] += T(-0.17951486749246792) * (a[1] * b[4]);
-    P[1] += T(-0.15171775404828525) * (a[1] * b[8]);
-    P[1] += T(0.10257992428141011) * (a[2] * b[5]);
-    P[1] += T(-0.067850242289111934) * (a[2] * b[7]);
-    P[1] += T(-0.044418410172992751) * (a[3] * b[2]);
-    P[1] += T(0.067850242289111906) * (a[4] * b[1]);
-    P[1] += T(0.10257992428141011) * (a[4] * b[3]);
-    P[1] += T(0.15171775404828494) * (a[5] * b[0]);
-    P[1] += T(0.099322584599279881) * (a[6] * b[3]);
-    P[2] += T(0.1332552305189782) * (a[0] * b[6]);
-    P[2] += T(0.11752006695060019) * (a[0] * b[8]);
-    P[2] += T(0.10257992428141011) * (a[1] * b[5]);
-    P[2] += T(-0.067850242289111934) * (a[1] * b[7]);
-    P[2] += T(0.025644981070352315) * (a[2] * b[4]);
-    P[2] += T(-0.11468784191000718) * (a[2] * b[6]);
-    P[2] += T(0.099322584599279895) * (a[3] * b[3]);
-    P[2] += T(0.11468784191000722) * (a[4] * b[2]);
-    P[2] += T(0.067850242289111934) * (a[5] * b[1]);
-    P[2] += T(-0.10257992428141018) * (a[5] * b[3]);
-    P[2] += T(-0.11752006695060027) * (a[6] * b[0]);
-    P[2] += T(-0.13325523051897814) * (a[6] * b[2]);
-    P[3] += T(-0.20355072686733566) * (a[0] * b[1]);
-    P[3] += T(-0.044418410172992751) * (a[1] * b[2]);
-    P[3] += T(0.099322584599279895) * (a[2] * b[3]);
-    P[3] += T(0.15386988642211544) * (a[3] * b[4]);
-    P[3] += T(0.099322584599279881) * (a[4] * b[5]);
-    P[3] += T(-0.044418410172992549) * (a[5] * b[6]);
-    P[3] += T(-0.20355072686733566) * (a[6] * b[7]);
-    P[4] += T(-0.11752006695060027) * (a[0] * b[0]);
-    P[4] += T(0.13325523051897814) * (a[0] * b[2]);
-    P[4] += T(0.067850242289111906) * (a[1] * b[1]);
-    P[4] += T(0.10257992428141011) * (a[1] * b[3]);
-    P[4] += T(0.11468784191000722) * (a[2] * b[2]);
-    P[4] += T(0.099322584599279881) * (a[3] * b[5]);
-    P[4] += T(0.02564498107035235) * (a[4] * b[4]);
-    P[4] += T(0.11468784191000721) * (a[4] * b[6]);
-    P[4] += T(0.1025799242814102) * (a[5] * b[5]);
-    P[4] += T(0.06785024228911192) * (a[5] * b[7]);
-    P[4] += T(0.1332552305189782) * (a[6] * b[6]);
-    P[4] += T(-0.11752006695060019) * (a[6] * b[8]);
-    P[5] += T(-0.099322584599279853) * (a[0] * b[3]);
-    P[5] += T(0.15171775404828494) * (a[1] * b[0]);
-    P[5] += T(0.067850242289111948) * (a[2] * b[1]);
-    P[5] += T(-0.10257992428141025) * (a[2] * b[3]);
-    P[5] += T(-0.044418410172992549) * (a[3] * b[6]);
-    P[5] += T(0.1025799242814102) * (a[4] * b[5]);
-    P[5] += T(0.067850242289111962) * (a[4] * b[7]);
-    P[5] += T(-0.17951486749246778) * (a[5] * b[4]);
-    P[5] += T(0.151717754048285) * (a[5] * b[8]);
-    P[5] += T(-0.099322584599279881) * (a[6] * b[5]);
-    P[6] += T(0.099322584599279853) * (a[1] * b[3]);
-    P[6] += T(-0.11752006695060024) * (a[2] * b[0]);
-    P[6] += T(-0.13325523051897817) * (a[2] * b[2]);
-    P[6] += T(-0.20355072686733561) * (a[3] * b[7]);
-    P[6] += T(0.1332552305189782) * (a[4] * b[6]);
-    P[6] += T(-0.11752006695060023) * (a[4] * b[8]);
-    P[6] += T(-0.099322584599279881) * (a[5] * b[5]);
-    P[6] += T(0.076934943211057705) * (a[6] * b[4]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(0.076934943211057705) * Pb[0]; ga[0] += t * b[4]; gb[4] += t * a[0]; }
-    { const T t = T(-0.099322584599279867) * Pb[0]; ga[1] += t * b[5]; gb[5] += t * a[1]; }
-    { const T t = T(0.13325523051897822) * Pb[0]; ga[2] += t * b[6]; gb[6] += t * a[2]; }
-    { const T t = T(0.11752006695060022) * Pb[0]; ga[2] += t * b[8]; gb[8] += t * a[2]; }
-    { const T t = T(-0.20355072686733561) * Pb[0]; ga[3] += t * b[1]; gb[1] += t * a[3]; }
-    { const T t = T(-0.11752006695060026) * Pb[0]; ga[4] += t * b[0]; gb[0] += t * a[4]; }
-    { const T t = T(0.13325523051897814) * Pb[0]; ga[4] += t * b[2]; gb[2] += t * a[4]; }
-    { const T t = T(-0.099322584599279881) * Pb[0]; ga[5] += t * b[3]; gb[3] += t * a[5]; }
-    { const T t = T(-0.099322584599279881) * Pb[1]; ga[0] += t * b[5]; gb[5] += t * a[0]; }
-    { const T t = T(-0.17951486749246792) * Pb[1]; ga[1] += t * b[4]; gb[4] += t * a[1]; }
-    { const T t = T(-0.15171775404828525) * Pb[1]; ga[1] += t * b[8]; gb[8] += t * a[1]; }
-    { const T t = T(0.10257992428141011) * Pb[1]; ga[2] += t * b[5]; gb[5] += t * a[2]; }
-    { const T t = T(-0.067850242289111934) * Pb[1]; ga[2] += t * b[7]; gb[7] += t * a[2]; }
-    { const T t = T(-0.044418410172992751) * Pb[1]; ga[3] += t * b[2]; gb[2] += t * a[3]; }
-    { const T t = T(0.067850242289111906) * Pb[1]; ga[4] += t * b[1]; gb[1] += t * a[4]; }
-    { const T t = T(0.10257992428141011) * Pb[1]; ga[4] += t * b[3]; gb[3] += t * a[4]; }
-    { const T t = T(0.15171775404828494) * Pb[1]; ga[5] += t * b[0]; gb[0] += t * a[5]; }
-    { const T t = T(0.099322584599279881) * Pb[1]; ga[6] += t * b[3]; gb[3] += t * a[6]; }
-    { const T t = T(0.1332552305189782) * Pb[2]; ga[0] += t * b[6]; gb[6] += t * a[0]; }
-    { const T t = T(0.11752006695060019) * Pb[2]; ga[0] += t * b[8]; gb[8] += t * a[0]; }
-    { const T t = T(0.10257992428141011) * Pb[2]; ga[1] += t * b[5]; gb[5] += t * a[1]; }
-    { const T t = T(-0.067850242289111934) * Pb[2]; ga[1] += t * b[7]; gb[7] += t * a[1]; }
-    { const T t = T(0.025644981070352315) * Pb[2]; ga[2] += t * b[4]; gb[4] += t * a[2]; }
-    { const T t = T(-0.11468784191000718) * Pb[2]; ga[2] += t * b[6]; gb[6] += t * a[2]; }
-    { const T t = T(0.099322584599279895) * Pb[2]; ga[3] += t * b[3]; gb[3] += t * a[3]; }
-    { const T t = T(0.11468784191000722) * Pb[2]; ga[4] += t * b[2]; gb[2] += t * a[4]; }
-    { const T t = T(0.067850242289111934) * Pb[2]; ga[5] += t * b[1]; gb[1] += t * a[5]; }
-    { const T t = T(-0.10257992428141018) * Pb[2]; ga[5] += t * b[3]; gb[3] += t * a[5]; }
-    { const T t = T(-0.11752006695060027) * Pb[2]; ga[6] += t * b[0]; gb[0] += t * a[6]; }
-    { const T t = T(-0.13325523051897814) * Pb[2]; ga[6] += t * b[2]; gb[2] += t * a[6]; }
-    { const T t = T(-0.20355072686733566) * Pb[3]; ga[0] += t * b[1]; gb[1] += t * a[0]; }
-    { const T t = T(-0.044418410172992751) * Pb[3]; ga[1] += t * b[2]; gb[2] += t * a[1]; }
-    { const T t = T(0.099322584599279895) * Pb[3]; ga[2] += t * b[3]; gb[3] += t * a[2]; }
-    { const T t = T(0.15386988642211544) * Pb[3]; ga[3] += t * b[4]; gb[4] += t * a[3]; }
-    { const T t = T(0.099322584599279881) * Pb[3]; ga[4] += t * b[5]; gb[5] += t * a[4]; }
-    { const T t = T(-0.044418410172992549) * Pb[3]; ga[5] += t * b[6]; gb[6] += t * a[5]; }
-    { const T t = T(-0.20355072686733566) * Pb[3]; ga[6] += t * b[7]; gb[7] += t * a[6]; }
-    { const T t = T(-0.11752006695060027) * Pb[4]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.13325523051897814) * Pb[4]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(0.067850242289111906) * Pb[4]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(0.10257992428141011) * Pb[4]; ga[1] += t * b[3]; gb[3] += t * a[1]; }
-    { const T t = T(0.11468784191000722) * Pb[4]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(0.099322584599279881) * Pb[4]; ga[3] += t * b[5]; gb[5] += t * a[3]; }
-    { const T t = T(0.02564498107035235) * Pb[4]; ga[4] += t * b[4]; gb[4] += t * a[4]; }
-    { const T t = T(0.11468784191000721) * Pb[4]; ga[4] += t * b[6]; gb[6] += t * a[4]; }
-    { const T t = T(0.1025799242814102) * Pb[4]; ga[5] += t * b[5]; gb[5] += t * a[5]; }
-    { const T t = T(0.06785024228911192) * Pb[4]; ga[5] += t * b[7]; gb[7] += t * a[5]; }
-    { const T t = T(0.1332552305189782) * Pb[4]; ga[6] += t * b[6]; gb[6] += t * a[6]; }
-    { const T t = T(-0.11752006695060019) * Pb[4]; ga[6] += t * b[8]; gb[8] += t * a[6]; }
-    { const T t = T(-0.099322584599279853) * Pb[5]; ga[0] += t * b[3]; gb[3] += t * a[0]; }
-    { const T t = T(0.15171775404828494) * Pb[5]; ga[1] += t * b[0]; gb[0] += t * a[1]; }
-    { const T t = T(0.067850242289111948) * Pb[5]; ga[2] += t * b[1]; gb[1] += t * a[2]; }
-    { const T t = T(-0.10257992428141025) * Pb[5]; ga[2] += t * b[3]; gb[3] += t * a[2]; }
-    { const T t = T(-0.044418410172992549) * Pb[5]; ga[3] += t * b[6]; gb[6] += t * a[3]; }
-    { const T t = T(0.1025799242814102) * Pb[5]; ga[4] += t * b[5]; gb[5] += t * a[4]; }
-    { const T t = T(0.067850242289111962) * Pb[5]; ga[4] += t * b[7]; gb[7] += t * a[4]; }
-    { const T t = T(-0.17951486749246778) * Pb[5]; ga[5] += t * b[4]; gb[4] += t * a[5]; }
-    { const T t = T(0.151717754048285) * Pb[5]; ga[5] += t * b[8]; gb[8] += t * a[5]; }
-    { const T t = T(-0.099322584599279881) * Pb[5]; ga[6] += t * b[5]; gb[5] += t * a[6]; }
-    { const T t = T(0.099322584599279853) * Pb[6]; ga[1] += t * b[3]; gb[3] += t * a[1]; }
-    { const T t = T(-0.11752006695060024) * Pb[6]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(-0.13325523051897817) * Pb[6]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(-0.20355072686733561) * Pb[6]; ga[3] += t * b[7]; gb[7] += t * a[3]; }
-    { const T t = T(0.1332552305189782) * Pb[6]; ga[4] += t * b[6]; gb[6] += t * a[4]; }
-    { const T t = T(-0.11752006695060023) * Pb[6]; ga[4] += t * b[8]; gb[8] += t * a[4]; }
-    { const T t = T(-0.099322584599279881) * Pb[6]; ga[5] += t * b[5]; gb[5] += t * a[5]; }
-    { const T t = T(0.076934943211057705) * Pb[6]; ga[6] += t * b[4]; gb[4] += t * a[6]; }
-  }
-};
-template <> struct Couple3<4, 4, 0, 4> {
-  static constexpr int kTerms = 9;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[0] += T(0.28209479177387781) * (a[0] * b[0]);
-    P[1] += T(0.28209479177387808) * (a[1] * b[0]);
-    P[2] += T(0.2820947917738782) * (a[2] * b[0]);
-    P[3] += T(0.28209479177387786) * (a[3] * b[0]);
-    P[4] += T(0.28209479177387836) * (a[4] * b[0]);
-    P[5] += T(0.28209479177387781) * (a[5] * b[0]);
-    P[6] += T(0.2820947917738782) * (a[6] * b[0]);
-    P[7] += T(0.28209479177387808) * (a[7] * b[0]);
-    P[8] += T(0.28209479177387825) * (a[8] * b[0]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(0.28209479177387781) * Pb[0]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.28209479177387808) * Pb[1]; ga[1] += t * b[0]; gb[0] += t * a[1]; }
-    { const T t = T(0.2820947917738782) * Pb[2]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(0.28209479177387786) * Pb[3]; ga[3] += t * b[0]; gb[0] += t * a[3]; }
-    { const T t = T(0.28209479177387836) * Pb[4]; ga[4] += t * b[0]; gb[0] += t * a[4]; }
-    { const T t = T(0.28209479177387781) * Pb[5]; ga[5] += t * b[0]; gb[0] += t * a[5]; }
-    { const T t = T(0.2820947917738782) * Pb[6]; ga[6] += t * b[0]; gb[0] += t * a[6]; }
-    { const T t = T(0.28209479177387808) * Pb[7]; ga[7] += t * b[0]; gb[0] += t * a[7]; }
-    { const T t = T(0.28209479177387825) * Pb[8]; ga[8] += t * b[0]; gb[0] += t * a[8]; }
-  }
-};
-template <> struct Couple3<4, 4, 1, 3> {
-  static constexpr int kTerms = 31;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[0] += T(0.2303294329808902) * (a[0] * b[2]);
-    P[0] += T(0.16286750396763999) * (a[1] * b[1]);
-    P[0] += T(-0.043528171377568134) * (a[2] * b[2]);
-    P[0] += T(-0.043528171377568169) * (a[6] * b[0]);
-    P[0] += T(-0.23032943298089051) * (a[8] * b[0]);
-    P[1] += T(0.19947114020071635) * (a[1] * b[2]);
-    P[1] += T(0.21324361862292318) * (a[2] * b[1]);
-    P[1] += T(-0.075393004386513446) * (a[3] * b[2]);
-    P[1] += T(-0.075393004386513446) * (a[5] * b[0]);
-    P[1] += T(-0.19947114020071635) * (a[7] * b[0]);
-    P[2] += T(0.16858388283618392) * (a[2] * b[2]);
-    P[2] += T(0.23841361350444787) * (a[3] * b[1]);
-    P[2] += T(-0.150786008773027) * (a[4] * b[0]);
-    P[2] += T(-0.16858388283618395) * (a[6] * b[0]);
-    P[3] += T(0.19466390027300595) * (a[3] * b[0]);
-    P[3] += T(0.24623252122982925) * (a[4] * b[1]);
-    P[3] += T(0.19466390027300595) * (a[5] * b[2]);
-    P[4] += T(0.16858388283618392) * (a[2] * b[0]);
-    P[4] += T(-0.150786008773027) * (a[4] * b[2]);
-    P[4] += T(0.23841361350444781) * (a[5] * b[1]);
-    P[4] += T(0.16858388283618397) * (a[6] * b[2]);
-    P[5] += T(0.19947114020071624) * (a[1] * b[0]);
-    P[5] += T(0.075393004386513349) * (a[3] * b[0]);
-    P[5] += T(-0.075393004386513335) * (a[5] * b[2]);
-    P[5] += T(0.21324361862292313) * (a[6] * b[1]);
-    P[5] += T(0.19947114020071624) * (a[7] * b[2]);
-    P[6] += T(0.2303294329808902) * (a[0] * b[0]);
-    P[6] += T(0.043528171377568155) * (a[2] * b[0]);
-    P[6] += T(-0.043528171377568182) * (a[6] * b[2]);
-    P[6] += T(0.16286750396763999) * (a[7] * b[1]);
-    P[6] += T(0.23032943298089054) * (a[8] * b[2]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(0.2303294329808902) * Pb[0]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(0.16286750396763999) * Pb[0]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(-0.043528171377568134) * Pb[0]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(-0.043528171377568169) * Pb[0]; ga[6] += t * b[0]; gb[0] += t * a[6]; }
-    { const T t = T(-0.23032943298089051) * Pb[0]; ga[8] += t * b[0]; gb[0] += t * a[8]; }
-    { const T t = T(0.19947114020071635) * Pb[1]; ga[1] += t * b[2]; gb[2] += t * a[1]; }
-    { const T t = T(0.21324361862292318) * Pb[1]; ga[2] += t * b[1]; gb[1] += t * a[2]; }
-    { const T t = T(-0.075393004386513446) * Pb[1]; ga[3] += t * b[2]; gb[2] += t * a[3]; }
-    { const T t = T(-0.075393004386513446) * Pb[1]; ga[5] += t * b[0]; gb[0] += t * a[5]; }
-    { const T t = T(-0.19947114020071635) * Pb[1]; ga[7] += t * b[0]; gb[0] += t * a[7]; }
-    { const T t = T(0.16858388283618392) * Pb[2]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(0.23841361350444787) * Pb[2]; ga[3] += t * b[1]; gb[1] += t * a[3]; }
-    { const T t = T(-0.150786008773027) * Pb[2]; ga[4] += t * b[0]; gb[0] += t * a[4]; }
-    { const T t = T(-0.16858388283618395) * Pb[2]; ga[6] += t * b[0]; gb[0] += t * a[6]; }
-    { const T t = T(0.19466390027300595) * Pb[3]; ga[3] += t * b[0]; gb[0] += t * a[3]; }
-    { const T t = T(0.24623252122982925) * Pb[3]; ga[4] += t * b[1]; gb[1] += t * a[4]; }
-    { const T t = T(0.19466390027300595) * Pb[3]; ga[5] += t * b[2]; gb[2] += t * a[5]; }
-    { const T t = T(0.16858388283618392) * Pb[4]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(-0.150786008773027) * Pb[4]; ga[4] += t * b[2]; gb[2] += t * a[4]; }
-    { const T t = T(0.23841361350444781) * Pb[4]; ga[5] += t * b[1]; gb[1] += t * a[5]; }
-    { const T t = T(0.16858388283618397) * Pb[4]; ga[6] += t * b[2]; gb[2] += t * a[6]; }
-    { const T t = T(0.19947114020071624) * Pb[5]; ga[1] += t * b[0]; gb[0] += t * a[1]; }
-    { const T t = T(0.075393004386513349) * Pb[5]; ga[3] += t * b[0]; gb[0] += t * a[3]; }
-    { const T t = T(-0.075393004386513335) * Pb[5]; ga[5] += t * b[2]; gb[2] += t * a[5]; }
-    { const T t = T(0.21324361862292313) * Pb[5]; ga[6] += t * b[1]; gb[1] += t * a[6]; }
-    { const T t = T(0.19947114020071624) * Pb[5]; ga[7] += t * b[2]; gb[2] += t * a[7]; }
-    { const T t = T(0.2303294329808902) * Pb[6]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.043528171377568155) * Pb[6]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(-0.043528171377568182) * Pb[6]; ga[6] += t * b[2]; gb[2] += t * a[6]; }
-    { const T t = T(0.16286750396763999) * Pb[6]; ga[7] += t * b[1]; gb[1] += t * a[7]; }
-    { const T t = T(0.23032943298089054) * Pb[6]; ga[8] += t * b[2]; gb[2] += t * a[8]; }
-  }
-};
-template <> struct Couple3<4, 4, 2, 2> {
-  static constexpr int kTerms = 37;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[0] += T(0.23841361350444776) * (a[0] * b[4]);
-    P[0] += T(0.16858388283618389) * (a[1] * b[3]);
-    P[0] += T(0.15607834722743988) * (a[2] * b[2]);
-    P[0] += T(-0.063718718434027571) * (a[3] * b[3]);
-    P[0] += T(0.040299255967696811) * (a[4] * b[0]);
-    P[0] += T(-0.063718718434027571) * (a[5] * b[1]);
-    P[0] += T(-0.16858388283618389) * (a[7] * b[1]);
-    P[0] += T(-0.23841361350444829) * (a[8] * b[0]);
-    P[1] += T(0.16858388283618381) * (a[1] * b[4]);
-    P[1] += T(0.18022375157286866) * (a[2] * b[3]);
-    P[1] += T(0.22072811544182247) * (a[3] * b[2]);
-    P[1] += T(0.06371871843402746) * (a[3] * b[4]);
-    P[1] += T(-0.1611970238707878) * (a[4] * b[1]);
-    P[1] += T(-0.063718718434027558) * (a[5] * b[0]);
-    P[1] += T(-0.18022375157286874) * (a[6] * b[1]);
-    P[1] += T(-0.16858388283618389) * (a[7] * b[0]);
-    P[2] += T(0.15607834722743991) * (a[2] * b[0]);
-    P[2] += T(0.22072811544182239) * (a[3] * b[1]);
-    P[2] += T(0.24179553580618141) * (a[4] * b[2]);
-    P[2] += T(0.22072811544182239) * (a[5] * b[3]);
-    P[2] += T(0.15607834722743993) * (a[6] * b[4]);
-    P[3] += T(0.16858388283618389) * (a[1] * b[0]);
-    P[3] += T(0.18022375157286866) * (a[2] * b[1]);
-    P[3] += T(-0.063718718434027558) * (a[3] * b[0]);
-    P[3] += T(-0.16119702387078777) * (a[4] * b[3]);
-    P[3] += T(0.22072811544182241) * (a[5] * b[2]);
-    P[3] += T(-0.06371871843402746) * (a[5] * b[4]);
-    P[3] += T(0.18022375157286868) * (a[6] * b[3]);
-    P[3] += T(0.16858388283618381) * (a[7] * b[4]);
-    P[4] += T(0.23841361350444776) * (a[0] * b[0]);
-    P[4] += T(0.16858388283618381) * (a[1] * b[1]);
-    P[4] += T(0.063718718434027433) * (a[3] * b[1]);
-    P[4] += T(0.040299255967696908) * (a[4] * b[4]);
-    P[4] += T(-0.063718718434027447) * (a[5] * b[3]);
-    P[4] += T(0.15607834722743988) * (a[6] * b[2]);
-    P[4] += T(0.16858388283618381) * (a[7] * b[3]);
-    P[4] += T(0.23841361350444812) * (a[8] * b[4]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(0.23841361350444776) * Pb[0]; ga[0] += t * b[4]; gb[4] += t * a[0]; }
-    { const T t = T(0.16858388283618389) * Pb[0]; ga[1] += t * b[3]; gb[3] += t * a[1]; }
-    { const T t = T(0.15607834722743988) * Pb[0]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(-0.063718718434027571) * Pb[0]; ga[3] += t * b[3]; gb[3] += t * a[3]; }
-    { const T t = T(0.040299255967696811) * Pb[0]; ga[4] += t * b[0]; gb[0] += t * a[4]; }
-    { const T t = T(-0.063718718434027571) * Pb[0]; ga[5] += t * b[1]; gb[1] += t * a[5]; }
-    { const T t = T(-0.16858388283618389) * Pb[0]; ga[7] += t * b[1]; gb[1] += t * a[7]; }
-    { const T t = T(-0.23841361350444829) * Pb[0]; ga[8] += t * b[0]; gb[0] += t * a[8]; }
-    { const T t = T(0.16858388283618381) * Pb[1]; ga[1] += t * b[4]; gb[4] += t * a[1]; }
-    { const T t = T(0.18022375157286866) * Pb[1]; ga[2] += t * b[3]; gb[3] += t * a[2]; }
-    { const T t = T(0.22072811544182247) * Pb[1]; ga[3] += t * b[2]; gb[2] += t * a[3]; }
-    { const T t = T(0.06371871843402746) * Pb[1]; ga[3] += t * b[4]; gb[4] += t * a[3]; }
-    { const T t = T(-0.1611970238707878) * Pb[1]; ga[4] += t * b[1]; gb[1] += t * a[4]; }
-    { const T t = T(-0.063718718434027558) * Pb[1]; ga[5] += t * b[0]; gb[0] += t * a[5]; }
-    { const T t = T(-0.18022375157286874) * Pb[1]; ga[6] += t * b[1]; gb[1] += t * a[6]; }
-    { const T t = T(-0.16858388283618389) * Pb[1]; ga[7] += t * b[0]; gb[0] += t * a[7]; }
-    { const T t = T(0.15607834722743991) * Pb[2]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(0.22072811544182239) * Pb[2]; ga[3] += t * b[1]; gb[1] += t * a[3]; }
-    { const T t = T(0.24179553580618141) * Pb[2]; ga[4] += t * b[2]; gb[2] += t * a[4]; }
-    { const T t = T(0.22072811544182239) * Pb[2]; ga[5] += t * b[3]; gb[3] += t * a[5]; }
-    { const T t = T(0.15607834722743993) * Pb[2]; ga[6] += t * b[4]; gb[4] += t * a[6]; }
-    { const T t = T(0.16858388283618389) * Pb[3]; ga[1] += t * b[0]; gb[0] += t * a[1]; }
-    { const T t = T(0.18022375157286866) * Pb[3]; ga[2] += t * b[1]; gb[1] += t * a[2]; }
-    { const T t = T(-0.063718718434027558) * Pb[3]; ga[3] += t * b[0]; gb[0] += t * a[3]; }
-    { const T t = T(-0.16119702387078777) * Pb[3]; ga[4] += t * b[3]; gb[3] += t * a[4]; }
-    { const T t = T(0.22072811544182241) * Pb[3]; ga[5] += t * b[2]; gb[2] += t * a[5]; }
-    { const T t = T(-0.06371871843402746) * Pb[3]; ga[5] += t * b[4]; gb[4] += t * a[5]; }
-    { const T t = T(0.18022375157286868) * Pb[3]; ga[6] += t * b[3]; gb[3] += t * a[6]; }
-    { const T t = T(0.16858388283618381) * Pb[3]; ga[7] += t * b[4]; gb[4] += t * a[7]; }
-    { const T t = T(0.23841361350444776) * Pb[4]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.16858388283618381) * Pb[4]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(0.063718718434027433) * Pb[4]; ga[3] += t * b[1]; gb[1] += t * a[3]; }
-    { const T t = T(0.040299255967696908) * Pb[4]; ga[4] += t * b[4]; gb[4] += t * a[4]; }
-    { const T t = T(-0.063718718434027447) * Pb[4]; ga[5] += t * b[3]; gb[3] += t * a[5]; }
-    { const T t = T(0.15607834722743988) * Pb[4]; ga[6] += t * b[2]; gb[2] += t * a[6]; }
-    { const T t = T(0.16858388283618381) * Pb[4]; ga[7] += t * b[3]; gb[3] += t * a[7]; }
-    { const T t = T(0.23841361350444812) * Pb[4]; ga[8] += t * b[4]; gb[4] += t * a[8]; }
-  }
-};
-template <> struct Couple3<4, 4, 2, 4> {
-  static constexpr int kTerms = 61;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[0] += T(-0.22937568382001464) * (a[0] * b[2]);
-    P[0] += T(0.14046334619025069) * (a[1] * b[3]);
-    P[0] += T(-0.075080816691962482) * (a[2] * b[4]);
-    P[0] += T(-0.075080816691962482) * (a[6] * b[0]);
-    P[0] += T(0.14046334619025069) * (a[7] * b[1]);
-    P[1] += T(0.14046334619025072) * (a[0] * b[3]);
-    P[1] += T(-0.057343920955003555) * (a[1] * b[2]);
-    P[1] += T(0.13272538654977706) * (a[2] * b[3]);
-    P[1] += T(-0.11262122503794364) * (a[3] * b[4]);
-    P[1] += T(-0.11262122503794367) * (a[5] * b[0]);
-    P[1] += T(0.13272538654977695) * (a[6] * b[1]);
-    P[1] += T(-0.1404633461902508) * (a[8] * b[1]);
-    P[2] += T(-0.075080816691962496) * (a[0] * b[4]);
-    P[2] += T(0.132725386549777) * (a[1] * b[3]);
-    P[2] += T(0.06553590966286113) * (a[2] * b[2]);
-    P[2] += T(0.090297865408018235) * (a[3] * b[3]);
-    P[2] += T(-0.19036461502711174) * (a[4] * b[0]);
-    P[2] += T(0.090297865408018235) * (a[5] * b[1]);
-    P[2] += T(-0.132725386549777) * (a[7] * b[1]);
-    P[2] += T(0.075080816691962302) * (a[8] * b[0]);
-    P[3] += T(-0.11262122503794361) * (a[1] * b[4]);
-    P[3] += T(0.090297865408018194) * (a[2] * b[3]);
-    P[3] += T(0.13926380803358024) * (a[3] * b[2]);
-    P[3] += T(-0.14188940657039986) * (a[3] * b[4]);
-    P[3] += T(0.044869370061212506) * (a[4] * b[1]);
-    P[3] += T(0.14188940657039981) * (a[5] * b[0]);
-    P[3] += T(-0.090297865408018402) * (a[6] * b[1]);
-    P[3] += T(0.11262122503794365) * (a[7] * b[0]);
-    P[4] += T(-0.19036461502711174) * (a[2] * b[0]);
-    P[4] += T(0.044869370061212464) * (a[3] * b[1]);
-    P[4] += T(0.16383977415715348) * (a[4] * b[2]);
-    P[4] += T(0.044869370061212464) * (a[5] * b[3]);
-    P[4] += T(-0.19036461502711177) * (a[6] * b[4]);
-    P[5] += T(-0.11262122503794367) * (a[1] * b[0]);
-    P[5] += T(0.090297865408018194) * (a[2] * b[1]);
-    P[5] += T(0.14188940657039981) * (a[3] * b[0]);
-    P[5] += T(0.044869370061212478) * (a[4] * b[3]);
-    P[5] += T(0.13926380803358016) * (a[5] * b[2]);
-    P[5] += T(0.14188940657039986) * (a[5] * b[4]);
-    P[5] += T(0.090297865408018402) * (a[6] * b[3]);
-    P[5] += T(-0.11262122503794363) * (a[7] * b[4]);
-    P[6] += T(-0.075080816691962496) * (a[0] * b[0]);
-    P[6] += T(0.13272538654977695) * (a[1] * b[1]);
-    P[6] += T(-0.09029786540801843) * (a[3] * b[1]);
-    P[6] += T(-0.19036461502711183) * (a[4] * b[4]);
-    P[6] += T(0.090297865408018416) * (a[5] * b[3]);
-    P[6] += T(0.065535909662861283) * (a[6] * b[2]);
-    P[6] += T(0.13272538654977692) * (a[7] * b[3]);
-    P[6] += T(-0.075080816691962482) * (a[8] * b[4]);
-    P[7] += T(0.14046334619025072) * (a[0] * b[1]);
-    P[7] += T(-0.13272538654977706) * (a[2] * b[1]);
-    P[7] += T(0.11262122503794368) * (a[3] * b[0]);
-    P[7] += T(-0.11262122503794365) * (a[5] * b[4]);
-    P[7] += T(0.13272538654977692) * (a[6] * b[3]);
-    P[7] += T(-0.057343920955003555) * (a[7] * b[2]);
-    P[7] += T(0.1404633461902508) * (a[8] * b[3]);
-    P[8] += T(-0.14046334619025078) * (a[1] * b[1]);
-    P[8] += T(0.075080816691962357) * (a[2] * b[0]);
-    P[8] += T(-0.075080816691962468) * (a[6] * b[4]);
-    P[8] += T(0.14046334619025078) * (a[7] * b[3]);
-    P[8] += T(-0.22937568382001453) * (a[8] * b[2]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(-0.22937568382001464) * Pb[0]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(0.14046334619025069) * Pb[0]; ga[1] += t * b[3]; gb[3] += t * a[1]; }
-    { const T t = T(-0.075080816691962482) * Pb[0]; ga[2] += t * b[4]; gb[4] += t * a[2]; }
-    { const T t = T(-0.075080816691962482) * Pb[0]; ga[6] += t * b[0]; gb[0] += t * a[6]; }
-    { const T t = T(0.14046334619025069) * Pb[0]; ga[7] += t * b[1]; gb[1] += t * a[7]; }
-    { const T t = T(0.14046334619025072) * Pb[1]; ga[0] += t * b[3]; gb[3] += t * a[0]; }
-    { const T t = T(-0.057343920955003555) * Pb[1]; ga[1] += t * b[2]; gb[2] += t * a[1]; }
-    { const T t = T(0.13272538654977706) * Pb[1]; ga[2] += t * b[3]; gb[3] += t * a[2]; }
-    { const T t = T(-0.11262122503794364) * Pb[1]; ga[3] += t * b[4]; gb[4] += t * a[3]; }
-    { const T t = T(-0.11262122503794367) * Pb[1]; ga[5] += t * b[0]; gb[0] += t * a[5]; }
-    { const T t = T(0.13272538654977695) * Pb[1]; ga[6] += t * b[1]; gb[1] += t * a[6]; }
-    { const T t = T(-0.1404633461902508) * Pb[1]; ga[8] += t * b[1]; gb[1] += t * a[8]; }
-    { const T t = T(-0.075080816691962496) * Pb[2]; ga[0] += t * b[4]; gb[4] += t * a[0]; }
-    { const T t = T(0.132725386549777) * Pb[2]; ga[1] += t * b[3]; gb[3] += t * a[1]; }
-    { const T t = T(0.06553590966286113) * Pb[2]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(0.090297865408018235) * Pb[2]; ga[3] += t * b[3]; gb[3] += t * a[3]; }
-    { const T t = T(-0.19036461502711174) * Pb[2]; ga[4] += t * b[0]; gb[0] += t * a[4]; }
-    { const T t = T(0.090297865408018235) * Pb[2]; ga[5] += t * b[1]; gb[1] += t * a[5]; }
-    { const T t = T(-0.132725386549777) * Pb[2]; ga[7] += t * b[1]; gb[1] += t * a[7]; }
-    { const T t = T(0.075080816691962302) * Pb[2]; ga[8] += t * b[0]; gb[0] += t * a[8]; }
-    { const T t = T(-0.11262122503794361) * Pb[3]; ga[1] += t * b[4]; gb[4] += t * a[1]; }
-    { const T t = T(0.090297865408018194) * Pb[3]; ga[2] += t * b[3]; gb[3] += t * a[2]; }
-    { const T t = T(0.13926380803358024) * Pb[3]; ga[3] += t * b[2]; gb[2] += t * a[3]; }
-    { const T t = T(-0.14188940657039986) * Pb[3]; ga[3] += t * b[4]; gb[4] += t * a[3]; }
-    { const T t = T(0.044869370061212506) * Pb[3]; ga[4] += t * b[1]; gb[1] += t * a[4]; }
-    { const T t = T(0.14188940657039981) * Pb[3]; ga[5] += t * b[0]; gb[0] += t * a[5]; }
-    { const T t = T(-0.090297865408018402) * Pb[3]; ga[6] += t * b[1]; gb[1] += t * a[6]; }
-    { const T t = T(0.11262122503794365) * Pb[3]; ga[7] += t * b[0]; gb[0] += t * a[7]; }
-    { const T t = T(-0.19036461502711174) * Pb[4]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(0.044869370061212464) * Pb[4]; ga[3] += t * b[1]; gb[1] += t * a[3]; }
-    { const T t = T(0.16383977415715348) * Pb[4]; ga[4] += t * b[2]; gb[2] += t * a[4]; }
-    { const T t = T(0.044869370061212464) * Pb[4]; ga[5] += t * b[3]; gb[3] += t * a[5]; }
-    { const T t = T(-0.19036461502711177) * Pb[4]; ga[6] += t * b[4]; gb[4] += t * a[6]; }
-    { const T t = T(-0.11262122503794367) * Pb[5]; ga[1] += t * b[0]; gb[0] += t * a[1]; }
-    { const T t = T(0.090297865408018194) * Pb[5]; ga[2] += t * b[1]; gb[1] += t * a[2]; }
-    { const T t = T(0.14188940657039981) * Pb[5]; ga[3] += t * b[0]; gb[0] += t * a[3]; }
-    { const T t = T(0.044869370061212478) * Pb[5]; ga[4] += t * b[3]; gb[3] += t * a[4]; }
-    { const T t = T(0.13926380803358016) * Pb[5]; ga[5] += t * b[2]; gb[2] += t * a[5]; }
-    { const T t = T(0.14188940657039986) * Pb[5]; ga[5] += t * b[4]; gb[4] += t * a[5]; }
-    { const T t = T(0.090297865408018402) * Pb[5]; ga[6] += t * b[3]; gb[3] += t * a[6]; }
-    { const T t = T(-0.11262122503794363) * Pb[5]; ga[7] += t * b[4]; gb[4] += t * a[7]; }
-    { const T t = T(-0.075080816691962496) * Pb[6]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.13272538654977695) * Pb[6]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(-0.09029786540801843) * Pb[6]; ga[3] += t * b[1]; gb[1] += t * a[3]; }
-    { const T t = T(-0.19036461502711183) * Pb[6]; ga[4] += t * b[4]; gb[4] += t * a[4]; }
-    { const T t = T(0.090297865408018416) * Pb[6]; ga[5] += t * b[3]; gb[3] += t * a[5]; }
-    { const T t = T(0.065535909662861283) * Pb[6]; ga[6] += t * b[2]; gb[2] += t * a[6]; }
-    { const T t = T(0.13272538654977692) * Pb[6]; ga[7] += t * b[3]; gb[3] += t * a[7]; }
-    { const T t = T(-0.075080816691962482) * Pb[6]; ga[8] += t * b[4]; gb[4] += t * a[8]; }
-    { const T t = T(0.14046334619025072) * Pb[7]; ga[0] += t * b[1]; gb[1] += t * a[0]; }
-    { const T t = T(-0.13272538654977706) * Pb[7]; ga[2] += t * b[1]; gb[1] += t * a[2]; }
-    { const T t = T(0.11262122503794368) * Pb[7]; ga[3] += t * b[0]; gb[0] += t * a[3]; }
-    { const T t = T(-0.11262122503794365) * Pb[7]; ga[5] += t * b[4]; gb[4] += t * a[5]; }
-    { const T t = T(0.13272538654977692) * Pb[7]; ga[6] += t * b[3]; gb[3] += t * a[6]; }
-    { const T t = T(-0.057343920955003555) * Pb[7]; ga[7] += t * b[2]; gb[2] += t * a[7]; }
-    { const T t = T(0.1404633461902508) * Pb[7]; ga[8] += t * b[3]; gb[3] += t * a[8]; }
-    { const T t = T(-0.14046334619025078) * Pb[8]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(0.075080816691962357) * Pb[8]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(-0.075080816691962468) * Pb[8]; ga[6] += t * b[4]; gb[4] += t * a[6]; }
-    { const T t = T(0.14046334619025078) * Pb[8]; ga[7] += t * b[3]; gb[3] += t * a[7]; }
-    { const T t = T(-0.22937568382001453) * Pb[8]; ga[8] += t * b[2]; gb[2] += t * a[8]; }
-  }
-};
-template <> struct Couple3<4, 4, 3, 1> {
-  static constexpr int kTerms = 31;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[0] += T(0.23032943298089015) * (a[0] * b[6]);
-    P[0] += T(0.19947114020071621) * (a[1] * b[5]);
-    P[0] += T(0.16858388283618389) * (a[2] * b[4]);
-    P[0] += T(0.043528171377568148) * (a[2] * b[6]);
-    P[0] += T(0.19466390027300592) * (a[3] * b[3]);
-    P[0] += T(0.075393004386513335) * (a[3] * b[5]);
-    P[0] += T(-0.15078600877302697) * (a[4] * b[2]);
-    P[0] += T(-0.075393004386513432) * (a[5] * b[1]);
-    P[0] += T(-0.043528171377568162) * (a[6] * b[0]);
-    P[0] += T(-0.16858388283618392) * (a[6] * b[2]);
-    P[0] += T(-0.1994711402007163) * (a[7] * b[1]);
-    P[0] += T(-0.23032943298089045) * (a[8] * b[0]);
-    P[1] += T(0.16286750396763996) * (a[1] * b[0]);
-    P[1] += T(0.21324361862292315) * (a[2] * b[1]);
-    P[1] += T(0.23841361350444784) * (a[3] * b[2]);
-    P[1] += T(0.24623252122982922) * (a[4] * b[3]);
-    P[1] += T(0.23841361350444776) * (a[5] * b[4]);
-    P[1] += T(0.2132436186229231) * (a[6] * b[5]);
-    P[1] += T(0.16286750396763996) * (a[7] * b[6]);
-    P[2] += T(0.23032943298089015) * (a[0] * b[0]);
-    P[2] += T(0.1994711402007163) * (a[1] * b[1]);
-    P[2] += T(-0.043528171377568127) * (a[2] * b[0]);
-    P[2] += T(0.16858388283618389) * (a[2] * b[2]);
-    P[2] += T(-0.075393004386513432) * (a[3] * b[1]);
-    P[2] += T(-0.15078600877302697) * (a[4] * b[4]);
-    P[2] += T(0.19466390027300592) * (a[5] * b[3]);
-    P[2] += T(-0.075393004386513321) * (a[5] * b[5]);
-    P[2] += T(0.16858388283618395) * (a[6] * b[4]);
-    P[2] += T(-0.043528171377568176) * (a[6] * b[6]);
-    P[2] += T(0.19947114020071621) * (a[7] * b[5]);
-    P[2] += T(0.23032943298089048) * (a[8] * b[6]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(0.23032943298089015) * Pb[0]; ga[0] += t * b[6]; gb[6] += t * a[0]; }
-    { const T t = T(0.19947114020071621) * Pb[0]; ga[1] += t * b[5]; gb[5] += t * a[1]; }
-    { const T t = T(0.16858388283618389) * Pb[0]; ga[2] += t * b[4]; gb[4] += t * a[2]; }
-    { const T t = T(0.043528171377568148) * Pb[0]; ga[2] += t * b[6]; gb[6] += t * a[2]; }
-    { const T t = T(0.19466390027300592) * Pb[0]; ga[3] += t * b[3]; gb[3] += t * a[3]; }
-    { const T t = T(0.075393004386513335) * Pb[0]; ga[3] += t * b[5]; gb[5] += t * a[3]; }
-    { const T t = T(-0.15078600877302697) * Pb[0]; ga[4] += t * b[2]; gb[2] += t * a[4]; }
-    { const T t = T(-0.075393004386513432) * Pb[0]; ga[5] += t * b[1]; gb[1] += t * a[5]; }
-    { const T t = T(-0.043528171377568162) * Pb[0]; ga[6] += t * b[0]; gb[0] += t * a[6]; }
-    { const T t = T(-0.16858388283618392) * Pb[0]; ga[6] += t * b[2]; gb[2] += t * a[6]; }
-    { const T t = T(-0.1994711402007163) * Pb[0]; ga[7] += t * b[1]; gb[1] += t * a[7]; }
-    { const T t = T(-0.23032943298089045) * Pb[0]; ga[8] += t * b[0]; gb[0] += t * a[8]; }
-    { const T t = T(0.16286750396763996) * Pb[1]; ga[1] += t * b[0]; gb[0] += t * a[1]; }
-    { const T t = T(0.21324361862292315) * Pb[1]; ga[2] += t * b[1]; gb[1] += t * a[2]; }
-    { const T t = T(0.23841361350444784) * Pb[1]; ga[3] += t * b[2]; gb[2] += t * a[3]; }
-    { const T t = T(0.24623252122982922) * Pb[1]; ga[4] += t * b[3]; gb[3] += t * a[4]; }
-    { const T t = T(0.23841361350444776) * Pb[1]; ga[5] += t * b[4]; gb[4] += t * a[5]; }
-    { const T t = T(0.2132436186229231) * Pb[1]; ga[6] += t * b[5]; gb[5] += t * a[6]; }
-    { const T t = T(0.16286750396763996) * Pb[1]; ga[7] += t * b[6]; gb[6] += t * a[7]; }
-    { const T t = T(0.23032943298089015) * Pb[2]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.1994711402007163) * Pb[2]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(-0.043528171377568127) * Pb[2]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(0.16858388283618389) * Pb[2]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(-0.075393004386513432) * Pb[2]; ga[3] += t * b[1]; gb[1] += t * a[3]; }
-    { const T t = T(-0.15078600877302697) * Pb[2]; ga[4] += t * b[4]; gb[4] += t * a[4]; }
-    { const T t = T(0.19466390027300592) * Pb[2]; ga[5] += t * b[3]; gb[3] += t * a[5]; }
-    { const T t = T(-0.075393004386513321) * Pb[2]; ga[5] += t * b[5]; gb[5] += t * a[5]; }
-    { const T t = T(0.16858388283618395) * Pb[2]; ga[6] += t * b[4]; gb[4] += t * a[6]; }
-    { const T t = T(-0.043528171377568176) * Pb[2]; ga[6] += t * b[6]; gb[6] += t * a[6]; }
-    { const T t = T(0.19947114020071621) * Pb[2]; ga[7] += t * b[5]; gb[5] += t * a[7]; }
-    { const T t = T(0.23032943298089048) * Pb[2]; ga[8] += t * b[6]; gb[6] += t * a[8]; }
-  }
-};
-template <> struct Couple3<4, 4, 3, 3> {
-  static constexpr int kTerms = 67;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[0] += T(-0.11752006695060026) * (a[0] * b[4]);
-    P[0] += T(-0.20355072686733561) * (a[1] * b[3]);
-    P[0] += T(0.13325523051897814) * (a[2] * b[4]);
-    P[0] += T(-0.099322584599279881) * (a[3] * b[5]);
-    P[0] += T(0.076934943211057677) * (a[4] * b[0]);
-    P[0] += T(-0.099322584599279867) * (a[5] * b[1]);
-    P[0] += T(0.13325523051897822) * (a[6] * b[2]);
-    P[0] += T(0.11752006695060023) * (a[8] * b[2]);
-    P[1] += T(0.15171775404828494) * (a[0] * b[5]);
-    P[1] += T(0.067850242289111906) * (a[1] * b[4]);
-    P[1] += T(-0.044418410172992751) * (a[2] * b[3]);
-    P[1] += T(0.10257992428141011) * (a[3] * b[4]);
-    P[1] += T(0.099322584599279881) * (a[3] * b[6]);
-    P[1] += T(-0.17951486749246792) * (a[4] * b[1]);
-    P[1] += T(-0.099322584599279881) * (a[5] * b[0]);
-    P[1] += T(0.10257992428141011) * (a[5] * b[2]);
-    P[1] += T(-0.067850242289111934) * (a[7] * b[2]);
-    P[1] += T(-0.15171775404828525) * (a[8] * b[1]);
-    P[2] += T(-0.11752006695060027) * (a[0] * b[6]);
-    P[2] += T(0.067850242289111934) * (a[1] * b[5]);
-    P[2] += T(0.11468784191000722) * (a[2] * b[4]);
-    P[2] += T(-0.13325523051897814) * (a[2] * b[6]);
-    P[2] += T(0.099322584599279895) * (a[3] * b[3]);
-    P[2] += T(-0.10257992428141019) * (a[3] * b[5]);
-    P[2] += T(0.025644981070352315) * (a[4] * b[2]);
-    P[2] += T(0.10257992428141011) * (a[5] * b[1]);
-    P[2] += T(0.1332552305189782) * (a[6] * b[0]);
-    P[2] += T(-0.11468784191000718) * (a[6] * b[2]);
-    P[2] += T(-0.067850242289111934) * (a[7] * b[1]);
-    P[2] += T(0.11752006695060019) * (a[8] * b[0]);
-    P[3] += T(-0.20355072686733566) * (a[1] * b[0]);
-    P[3] += T(-0.044418410172992751) * (a[2] * b[1]);
-    P[3] += T(0.099322584599279895) * (a[3] * b[2]);
-    P[3] += T(0.15386988642211544) * (a[4] * b[3]);
-    P[3] += T(0.099322584599279881) * (a[5] * b[4]);
-    P[3] += T(-0.044418410172992549) * (a[6] * b[5]);
-    P[3] += T(-0.20355072686733566) * (a[7] * b[6]);
-    P[4] += T(-0.11752006695060027) * (a[0] * b[0]);
-    P[4] += T(0.067850242289111906) * (a[1] * b[1]);
-    P[4] += T(0.13325523051897814) * (a[2] * b[0]);
-    P[4] += T(0.11468784191000722) * (a[2] * b[2]);
-    P[4] += T(0.10257992428141011) * (a[3] * b[1]);
-    P[4] += T(0.02564498107035235) * (a[4] * b[4]);
-    P[4] += T(0.099322584599279881) * (a[5] * b[3]);
-    P[4] += T(0.10257992428141015) * (a[5] * b[5]);
-    P[4] += T(0.11468784191000721) * (a[6] * b[4]);
-    P[4] += T(0.1332552305189782) * (a[6] * b[6]);
-    P[4] += T(0.06785024228911192) * (a[7] * b[5]);
-    P[4] += T(-0.11752006695060019) * (a[8] * b[6]);
-    P[5] += T(0.15171775404828494) * (a[0] * b[1]);
-    P[5] += T(0.067850242289111948) * (a[1] * b[2]);
-    P[5] += T(-0.099322584599279853) * (a[3] * b[0]);
-    P[5] += T(-0.10257992428141025) * (a[3] * b[2]);
-    P[5] += T(-0.17951486749246778) * (a[4] * b[5]);
-    P[5] += T(0.1025799242814102) * (a[5] * b[4]);
-    P[5] += T(-0.099322584599279881) * (a[5] * b[6]);
-    P[5] += T(-0.044418410172992549) * (a[6] * b[3]);
-    P[5] += T(0.067850242289111934) * (a[7] * b[4]);
-    P[5] += T(0.151717754048285) * (a[8] * b[5]);
-    P[6] += T(-0.11752006695060024) * (a[0] * b[2]);
-    P[6] += T(-0.13325523051897817) * (a[2] * b[2]);
-    P[6] += T(0.099322584599279853) * (a[3] * b[1]);
-    P[6] += T(0.076934943211057691) * (a[4] * b[6]);
-    P[6] += T(-0.099322584599279881) * (a[5] * b[5]);
-    P[6] += T(0.13325523051897822) * (a[6] * b[4]);
-    P[6] += T(-0.20355072686733561) * (a[7] * b[3]);
-    P[6] += T(-0.11752006695060019) * (a[8] * b[4]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(-0.11752006695060026) * Pb[0]; ga[0] += t * b[4]; gb[4] += t * a[0]; }
-    { const T t = T(-0.20355072686733561) * Pb[0]; ga[1] += t * b[3]; gb[3] += t * a[1]; }
-    { const T t = T(0.13325523051897814) * Pb[0]; ga[2] += t * b[4]; gb[4] += t * a[2]; }
-    { const T t = T(-0.099322584599279881) * Pb[0]; ga[3] += t * b[5]; gb[5] += t * a[3]; }
-    { const T t = T(0.076934943211057677) * Pb[0]; ga[4] += t * b[0]; gb[0] += t * a[4]; }
-    { const T t = T(-0.099322584599279867) * Pb[0]; ga[5] += t * b[1]; gb[1] += t * a[5]; }
-    { const T t = T(0.13325523051897822) * Pb[0]; ga[6] += t * b[2]; gb[2] += t * a[6]; }
-    { const T t = T(0.11752006695060023) * Pb[0]; ga[8] += t * b[2]; gb[2] += t * a[8]; }
-    { const T t = T(0.15171775404828494) * Pb[1]; ga[0] += t * b[5]; gb[5] += t * a[0]; }
-    { const T t = T(0.067850242289111906) * Pb[1]; ga[1] += t * b[4]; gb[4] += t * a[1]; }
-    { const T t = T(-0.044418410172992751) * Pb[1]; ga[2] += t * b[3]; gb[3] += t * a[2]; }
-    { const T t = T(0.10257992428141011) * Pb[1]; ga[3] += t * b[4]; gb[4] += t * a[3]; }
-    { const T t = T(0.099322584599279881) * Pb[1]; ga[3] += t * b[6]; gb[6] += t * a[3]; }
-    { const T t = T(-0.17951486749246792) * Pb[1]; ga[4] += t * b[1]; gb[1] += t * a[4]; }
-    { const T t = T(-0.099322584599279881) * Pb[1]; ga[5] += t * b[0]; gb[0] += t * a[5]; }
-    { const T t = T(0.10257992428141011) * Pb[1]; ga[5] += t * b[2]; gb[2] += t * a[5]; }
-    { const T t = T(-0.067850242289111934) * Pb[1]; ga[7] += t * b[2]; gb[2] += t * a[7]; }
-    { const T t = T(-0.15171775404828525) * Pb[1]; ga[8] += t * b[1]; gb[1] += t * a[8]; }
-    { const T t = T(-0.11752006695060027) * Pb[2]; ga[0] += t * b[6]; gb[6] += t * a[0]; }
-    { const T t = T(0.067850242289111934) * Pb[2]; ga[1] += t * b[5]; gb[5] += t * a[1]; }
-    { const T t = T(0.11468784191000722) * Pb[2]; ga[2] += t * b[4]; gb[4] += t * a[2]; }
-    { const T t = T(-0.13325523051897814) * Pb[2]; ga[2] += t * b[6]; gb[6] += t * a[2]; }
-    { const T t = T(0.099322584599279895) * Pb[2]; ga[3] += t * b[3]; gb[3] += t * a[3]; }
-    { const T t = T(-0.10257992428141019) * Pb[2]; ga[3] += t * b[5]; gb[5] += t * a[3]; }
-    { const T t = T(0.025644981070352315) * Pb[2]; ga[4] += t * b[2]; gb[2] += t * a[4]; }
-    { const T t = T(0.10257992428141011) * Pb[2]; ga[5] += t * b[1]; gb[1] += t * a[5]; }
-    { const T t = T(0.1332552305189782) * Pb[2]; ga[6] += t * b[0]; gb[0] += t * a[6]; }
-    { const T t = T(-0.11468784191000718) * Pb[2]; ga[6] += t * b[2]; gb[2] += t * a[6]; }
-    { const T t = T(-0.067850242289111934) * Pb[2]; ga[7] += t * b[1]; gb[1] += t * a[7]; }
-    { const T t = T(0.11752006695060019) * Pb[2]; ga[8] += t * b[0]; gb[0] += t * a[8]; }
-    { const T t = T(-0.20355072686733566) * Pb[3]; ga[1] += t * b[0]; gb[0] += t * a[1]; }
-    { const T t = T(-0.044418410172992751) * Pb[3]; ga[2] += t * b[1]; gb[1] += t * a[2]; }
-    { const T t = T(0.099322584599279895) * Pb[3]; ga[3] += t * b[2]; gb[2] += t * a[3]; }
-    { const T t = T(0.15386988642211544) * Pb[3]; ga[4] += t * b[3]; gb[3] += t * a[4]; }
-    { const T t = T(0.099322584599279881) * Pb[3]; ga[5] += t * b[4]; gb[4] += t * a[5]; }
-    { const T t = T(-0.044418410172992549) * Pb[3]; ga[6] += t * b[5]; gb[5] += t * a[6]; }
-    { const T t = T(-0.20355072686733566) * Pb[3]; ga[7] += t * b[6]; gb[6] += t * a[7]; }
-    { const T t = T(-0.11752006695060027) * Pb[4]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.067850242289111906) * Pb[4]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(0.13325523051897814) * Pb[4]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(0.11468784191000722) * Pb[4]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(0.10257992428141011) * Pb[4]; ga[3] += t * b[1]; gb[1] += t * a[3]; }
-    { const T t = T(0.02564498107035235) * Pb[4]; ga[4] += t * b[4]; gb[4] += t * a[4]; }
-    { const T t = T(0.099322584599279881) * Pb[4]; ga[5] += t * b[3]; gb[3] += t * a[5]; }
-    { const T t = T(0.10257992428141015) * Pb[4]; ga[5] += t * b[5]; gb[5] += t * a[5]; }
-    { const T t = T(0.11468784191000721) * Pb[4]; ga[6] += t * b[4]; gb[4] += t * a[6]; }
-    { const T t = T(0.1332552305189782) * Pb[4]; ga[6] += t * b[6]; gb[6] += t * a[6]; }
-    { const T t = T(0.06785024228911192) * Pb[4]; ga[7] += t * b[5]; gb[5] += t * a[7]; }
-    { const T t = T(-0.11752006695060019) * Pb[4]; ga[8] += t * b[6]; gb[6] += t * a[8]; }
-    { const T t = T(0.15171775404828494) * Pb[5]; ga[0] += t * b[1]; gb[1] += t * a[0]; }
-    { const T t = T(0.067850242289111948) * Pb[5]; ga[1] += t * b[2]; gb[2] += t * a[1]; }
-    { const T t = T(-0.099322584599279853) * Pb[5]; ga[3] += t * b[0]; gb[0] += t * a[3]; }
-    { const T t = T(-0.10257992428141025) * Pb[5]; ga[3] += t * b[2]; gb[2] += t * a[3]; }
-    { const T t = T(-0.17951486749246778) * Pb[5]; ga[4] += t * b[5]; gb[5] += t * a[4]; }
-    { const T t = T(0.1025799242814102) * Pb[5]; ga[5] += t * b[4]; gb[4] += t * a[5]; }
-    { const T t = T(-0.099322584599279881) * Pb[5]; ga[5] += t * b[6]; gb[6] += t * a[5]; }
-    { const T t = T(-0.044418410172992549) * Pb[5]; ga[6] += t * b[3]; gb[3] += t * a[6]; }
-    { const T t = T(0.067850242289111934) * Pb[5]; ga[7] += t * b[4]; gb[4] += t * a[7]; }
-    { const T t = T(0.151717754048285) * Pb[5]; ga[8] += t * b[5]; gb[5] += t * a[8]; }
-    { const T t = T(-0.11752006695060024) * Pb[6]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(-0.13325523051897817) * Pb[6]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(0.099322584599279853) * Pb[6]; ga[3] += t * b[1]; gb[1] += t * a[3]; }
-    { const T t = T(0.076934943211057691) * Pb[6]; ga[4] += t * b[6]; gb[6] += t * a[4]; }
-    { const T t = T(-0.099322584599279881) * Pb[6]; ga[5] += t * b[5]; gb[5] += t * a[5]; }
-    { const T t = T(0.13325523051897822) * Pb[6]; ga[6] += t * b[4]; gb[4] += t * a[6]; }
-    { const T t = T(-0.20355072686733561) * Pb[6]; ga[7] += t * b[3]; gb[3] += t * a[7]; }
-    { const T t = T(-0.11752006695060019) * Pb[6]; ga[8] += t * b[4]; gb[4] += t * a[8]; }
-  }
-};
-template <> struct Couple3<4, 4, 4, 0> {
-  static constexpr int kTerms = 9;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[0] += T(0.28209479177387786) * (a[0] * b[0]);
-    P[0] += T(0.28209479177387814) * (a[1] * b[1]);
-    P[0] += T(0.2820947917738782) * (a[2] * b[2]);
-    P[0] += T(0.28209479177387792) * (a[3] * b[3]);
-    P[0] += T(0.28209479177387842) * (a[4] * b[4]);
-    P[0] += T(0.28209479177387786) * (a[5] * b[5]);
-    P[0] += T(0.28209479177387825) * (a[6] * b[6]);
-    P[0] += T(0.28209479177387814) * (a[7] * b[7]);
-    P[0] += T(0.28209479177387831) * (a[8] * b[8]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(0.28209479177387786) * Pb[0]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(0.28209479177387814) * Pb[0]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(0.2820947917738782) * Pb[0]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(0.28209479177387792) * Pb[0]; ga[3] += t * b[3]; gb[3] += t * a[3]; }
-    { const T t = T(0.28209479177387842) * Pb[0]; ga[4] += t * b[4]; gb[4] += t * a[4]; }
-    { const T t = T(0.28209479177387786) * Pb[0]; ga[5] += t * b[5]; gb[5] += t * a[5]; }
-    { const T t = T(0.28209479177387825) * Pb[0]; ga[6] += t * b[6]; gb[6] += t * a[6]; }
-    { const T t = T(0.28209479177387814) * Pb[0]; ga[7] += t * b[7]; gb[7] += t * a[7]; }
-    { const T t = T(0.28209479177387831) * Pb[0]; ga[8] += t * b[8]; gb[8] += t * a[8]; }
-  }
-};
-template <> struct Couple3<4, 4, 4, 2> {
-  static constexpr int kTerms = 61;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[0] += T(-0.075080816691962496) * (a[0] * b[6]);
-    P[0] += T(-0.11262122503794365) * (a[1] * b[5]);
-    P[0] += T(-0.19036461502711166) * (a[2] * b[4]);
-    P[0] += T(0.075080816691962315) * (a[2] * b[8]);
-    P[0] += T(0.14188940657039983) * (a[3] * b[5]);
-    P[0] += T(0.11262122503794365) * (a[3] * b[7]);
-    P[0] += T(-0.19036461502711166) * (a[4] * b[2]);
-    P[0] += T(-0.11262122503794365) * (a[5] * b[1]);
-    P[0] += T(0.14188940657039983) * (a[5] * b[3]);
-    P[0] += T(-0.075080816691962496) * (a[6] * b[0]);
-    P[0] += T(0.11262122503794365) * (a[7] * b[3]);
-    P[0] += T(0.075080816691962315) * (a[8] * b[2]);
-    P[1] += T(0.14046334619025075) * (a[0] * b[7]);
-    P[1] += T(0.13272538654977697) * (a[1] * b[6]);
-    P[1] += T(-0.1404633461902508) * (a[1] * b[8]);
-    P[1] += T(0.090297865408018207) * (a[2] * b[5]);
-    P[1] += T(-0.13272538654977709) * (a[2] * b[7]);
-    P[1] += T(0.044869370061212312) * (a[3] * b[4]);
-    P[1] += T(-0.090297865408018402) * (a[3] * b[6]);
-    P[1] += T(0.044869370061212312) * (a[4] * b[3]);
-    P[1] += T(0.090297865408018207) * (a[5] * b[2]);
-    P[1] += T(0.13272538654977697) * (a[6] * b[1]);
-    P[1] += T(-0.090297865408018402) * (a[6] * b[3]);
-    P[1] += T(0.14046334619025075) * (a[7] * b[0]);
-    P[1] += T(-0.13272538654977703) * (a[7] * b[2]);
-    P[1] += T(-0.1404633461902508) * (a[8] * b[1]);
-    P[2] += T(-0.22937568382001466) * (a[0] * b[0]);
-    P[2] += T(-0.057343920955003562) * (a[1] * b[1]);
-    P[2] += T(0.065535909662861144) * (a[2] * b[2]);
-    P[2] += T(0.13926380803358027) * (a[3] * b[3]);
-    P[2] += T(0.16383977415715351) * (a[4] * b[4]);
-    P[2] += T(0.13926380803358016) * (a[5] * b[5]);
-    P[2] += T(0.065535909662861297) * (a[6] * b[6]);
-    P[2] += T(-0.057343920955003562) * (a[7] * b[7]);
-    P[2] += T(-0.22937568382001455) * (a[8] * b[8]);
-    P[3] += T(0.14046334619025075) * (a[0] * b[1]);
-    P[3] += T(0.14046334619025075) * (a[1] * b[0]);
-    P[3] += T(0.13272538654977703) * (a[1] * b[2]);
-    P[3] += T(0.13272538654977706) * (a[2] * b[1]);
-    P[3] += T(0.090297865408018207) * (a[2] * b[3]);
-    P[3] += T(0.090297865408018207) * (a[3] * b[2]);
-    P[3] += T(0.044869370061212284) * (a[4] * b[5]);
-    P[3] += T(0.044869370061212284) * (a[5] * b[4]);
-    P[3] += T(0.090297865408018388) * (a[5] * b[6]);
-    P[3] += T(0.090297865408018402) * (a[6] * b[5]);
-    P[3] += T(0.13272538654977695) * (a[6] * b[7]);
-    P[3] += T(0.13272538654977695) * (a[7] * b[6]);
-    P[3] += T(0.1404633461902508) * (a[7] * b[8]);
-    P[3] += T(0.1404633461902508) * (a[8] * b[7]);
-    P[4] += T(-0.075080816691962496) * (a[0] * b[2]);
-    P[4] += T(-0.11262122503794363) * (a[1] * b[3]);
-    P[4] += T(-0.075080816691962496) * (a[2] * b[0]);
-    P[4] += T(-0.11262122503794363) * (a[3] * b[1]);
-    P[4] += T(-0.14188940657039986) * (a[3] * b[3]);
-    P[4] += T(-0.19036461502711177) * (a[4] * b[6]);
-    P[4] += T(0.14188940657039986) * (a[5] * b[5]);
-    P[4] += T(-0.11262122503794363) * (a[5] * b[7]);
-    P[4] += T(-0.19036461502711172) * (a[6] * b[4]);
-    P[4] += T(-0.075080816691962496) * (a[6] * b[8]);
-    P[4] += T(-0.11262122503794363) * (a[7] * b[5]);
-    P[4] += T(-0.07508081669196251) * (a[8] * b[6]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(-0.075080816691962496) * Pb[0]; ga[0] += t * b[6]; gb[6] += t * a[0]; }
-    { const T t = T(-0.11262122503794365) * Pb[0]; ga[1] += t * b[5]; gb[5] += t * a[1]; }
-    { const T t = T(-0.19036461502711166) * Pb[0]; ga[2] += t * b[4]; gb[4] += t * a[2]; }
-    { const T t = T(0.075080816691962315) * Pb[0]; ga[2] += t * b[8]; gb[8] += t * a[2]; }
-    { const T t = T(0.14188940657039983) * Pb[0]; ga[3] += t * b[5]; gb[5] += t * a[3]; }
-    { const T t = T(0.11262122503794365) * Pb[0]; ga[3] += t * b[7]; gb[7] += t * a[3]; }
-    { const T t = T(-0.19036461502711166) * Pb[0]; ga[4] += t * b[2]; gb[2] += t * a[4]; }
-    { const T t = T(-0.11262122503794365) * Pb[0]; ga[5] += t * b[1]; gb[1] += t * a[5]; }
-    { const T t = T(0.14188940657039983) * Pb[0]; ga[5] += t * b[3]; gb[3] += t * a[5]; }
-    { const T t = T(-0.075080816691962496) * Pb[0]; ga[6] += t * b[0]; gb[0] += t * a[6]; }
-    { const T t = T(0.11262122503794365) * Pb[0]; ga[7] += t * b[3]; gb[3] += t * a[7]; }
-    { const T t = T(0.075080816691962315) * Pb[0]; ga[8] += t * b[2]; gb[2] += t * a[8]; }
-    { const T t = T(0.14046334619025075) * Pb[1]; ga[0] += t * b[7]; gb[7] += t * a[0]; }
-    { const T t = T(0.13272538654977697) * Pb[1]; ga[1] += t * b[6]; gb[6] += t * a[1]; }
-    { const T t = T(-0.1404633461902508) * Pb[1]; ga[1] += t * b[8]; gb[8] += t * a[1]; }
-    { const T t = T(0.090297865408018207) * Pb[1]; ga[2] += t * b[5]; gb[5] += t * a[2]; }
-    { const T t = T(-0.13272538654977709) * Pb[1]; ga[2] += t * b[7]; gb[7] += t * a[2]; }
-    { const T t = T(0.044869370061212312) * Pb[1]; ga[3] += t * b[4]; gb[4] += t * a[3]; }
-    { const T t = T(-0.090297865408018402) * Pb[1]; ga[3] += t * b[6]; gb[6] += t * a[3]; }
-    { const T t = T(0.044869370061212312) * Pb[1]; ga[4] += t * b[3]; gb[3] += t * a[4]; }
-    { const T t = T(0.090297865408018207) * Pb[1]; ga[5] += t * b[2]; gb[2] += t * a[5]; }
-    { const T t = T(0.13272538654977697) * Pb[1]; ga[6] += t * b[1]; gb[1] += t * a[6]; }
-    { const T t = T(-0.090297865408018402) * Pb[1]; ga[6] += t * b[3]; gb[3] += t * a[6]; }
-    { const T t = T(0.14046334619025075) * Pb[1]; ga[7] += t * b[0]; gb[0] += t * a[7]; }
-    { const T t = T(-0.13272538654977703) * Pb[1]; ga[7] += t * b[2]; gb[2] += t * a[7]; }
-    { const T t = T(-0.1404633461902508) * Pb[1]; ga[8] += t * b[1]; gb[1] += t * a[8]; }
-    { const T t = T(-0.22937568382001466) * Pb[2]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(-0.057343920955003562) * Pb[2]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(0.065535909662861144) * Pb[2]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(0.13926380803358027) * Pb[2]; ga[3] += t * b[3]; gb[3] += t * a[3]; }
-    { const T t = T(0.16383977415715351) * Pb[2]; ga[4] += t * b[4]; gb[4] += t * a[4]; }
-    { const T t = T(0.13926380803358016) * Pb[2]; ga[5] += t * b[5]; gb[5] += t * a[5]; }
-    { const T t = T(0.065535909662861297) * Pb[2]; ga[6] += t * b[6]; gb[6] += t * a[6]; }
-    { const T t = T(-0.057343920955003562) * Pb[2]; ga[7] += t * b[7]; gb[7] += t * a[7]; }
-    { const T t = T(-0.22937568382001455) * Pb[2]; ga[8] += t * b[8]; gb[8] += t * a[8]; }
-    { const T t = T(0.14046334619025075) * Pb[3]; ga[0] += t * b[1]; gb[1] += t * a[0]; }
-    { const T t = T(0.14046334619025075) * Pb[3]; ga[1] += t * b[0]; gb[0] += t * a[1]; }
-    { const T t = T(0.13272538654977703) * Pb[3]; ga[1] += t * b[2]; gb[2] += t * a[1]; }
-    { const T t = T(0.13272538654977706) * Pb[3]; ga[2] += t * b[1]; gb[1] += t * a[2]; }
-    { const T t = T(0.090297865408018207) * Pb[3]; ga[2] += t * b[3]; gb[3] += t * a[2]; }
-    { const T t = T(0.090297865408018207) * Pb[3]; ga[3] += t * b[2]; gb[2] += t * a[3]; }
-    { const T t = T(0.044869370061212284) * Pb[3]; ga[4] += t * b[5]; gb[5] += t * a[4]; }
-    { const T t = T(0.044869370061212284) * Pb[3]; ga[5] += t * b[4]; gb[4] += t * a[5]; }
-    { const T t = T(0.090297865408018388) * Pb[3]; ga[5] += t * b[6]; gb[6] += t * a[5]; }
-    { const T t = T(0.090297865408018402) * Pb[3]; ga[6] += t * b[5]; gb[5] += t * a[6]; }
-    { const T t = T(0.13272538654977695) * Pb[3]; ga[6] += t * b[7]; gb[7] += t * a[6]; }
-    { const T t = T(0.13272538654977695) * Pb[3]; ga[7] += t * b[6]; gb[6] += t * a[7]; }
-    { const T t = T(0.1404633461902508) * Pb[3]; ga[7] += t * b[8]; gb[8] += t * a[7]; }
-    { const T t = T(0.1404633461902508) * Pb[3]; ga[8] += t * b[7]; gb[7] += t * a[8]; }
-    { const T t = T(-0.075080816691962496) * Pb[4]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(-0.11262122503794363) * Pb[4]; ga[1] += t * b[3]; gb[3] += t * a[1]; }
-    { const T t = T(-0.075080816691962496) * Pb[4]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(-0.11262122503794363) * Pb[4]; ga[3] += t * b[1]; gb[1] += t * a[3]; }
-    { const T t = T(-0.14188940657039986) * Pb[4]; ga[3] += t * b[3]; gb[3] += t * a[3]; }
-    { const T t = T(-0.19036461502711177) * Pb[4]; ga[4] += t * b[6]; gb[6] += t * a[4]; }
-    { const T t = T(0.14188940657039986) * Pb[4]; ga[5] += t * b[5]; gb[5] += t * a[5]; }
-    { const T t = T(-0.11262122503794363) * Pb[4]; ga[5] += t * b[7]; gb[7] += t * a[5]; }
-    { const T t = T(-0.19036461502711172) * Pb[4]; ga[6] += t * b[4]; gb[4] += t * a[6]; }
-    { const T t = T(-0.075080816691962496) * Pb[4]; ga[6] += t * b[8]; gb[8] += t * a[6]; }
-    { const T t = T(-0.11262122503794363) * Pb[4]; ga[7] += t * b[5]; gb[5] += t * a[7]; }
-    { const T t = T(-0.07508081669196251) * Pb[4]; ga[8] += t * b[6]; gb[6] += t * a[8]; }
-  }
-};
-template <> struct Couple3<4, 4, 4, 4> {
-  static constexpr int kTerms = 97;
-  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {
-    P[0] += T(0.1065253059845416) * (a[0] * b[4]);
-    P[0] += T(-0.11909891275269989) * (a[1] * b[5]);
-    P[0] += T(0.13504547338363843) * (a[2] * b[6]);
-    P[0] += T(-0.1190989127526999) * (a[3] * b[7]);
-    P[0] += T(0.10652530598454157) * (a[4] * b[0]);
-    P[0] += T(-0.11909891275269992) * (a[5] * b[1]);
-    P[0] += T(0.13504547338363843) * (a[6] * b[2]);
-    P[0] += T(-0.1190989127526999) * (a[7] * b[3]);
-    P[1] += T(-0.11909891275269989) * (a[0] * b[5]);
-    P[1] += T(-0.15978795897681217) * (a[1] * b[4]);
-    P[1] += T(0.045015157794546165) * (a[2] * b[5]);
-    P[1] += T(0.045015157794546068) * (a[3] * b[6]);
-    P[1] += T(0.11909891275269992) * (a[3] * b[8]);
-    P[1] += T(-0.15978795897681219) * (a[4] * b[1]);
-    P[1] += T(-0.11909891275269992) * (a[5] * b[0]);
-    P[1] += T(0.045015157794546165) * (a[5] * b[2]);
-    P[1] += T(0.045015157794546068) * (a[6] * b[3]);
-    P[1] += T(0.11909891275269993) * (a[8] * b[3]);
-    P[2] += T(0.13504547338363845) * (a[0] * b[6]);
-    P[2] += T(0.045015157794546096) * (a[1] * b[5]);
-    P[2] += T(-0.083698454702139574) * (a[2] * b[4]);
-    P[2] += T(-0.13504547338363845) * (a[2] * b[8]);
-    P[2] += T(0.10208478235945705) * (a[3] * b[5]);
-    P[2] += T(-0.045015157794546054) * (a[3] * b[7]);
-    P[2] += T(-0.083698454702139574) * (a[4] * b[2]);
-    P[2] += T(0.045015157794546096) * (a[5] * b[1]);
-    P[2] += T(0.10208478235945705) * (a[5] * b[3]);
-    P[2] += T(0.13504547338363843) * (a[6] * b[0]);
-    P[2] += T(-0.045015157794546082) * (a[7] * b[3]);
-    P[2] += T(-0.13504547338363843) * (a[8] * b[2]);
-    P[3] += T(-0.1190989127526999) * (a[0] * b[7]);
-    P[3] += T(0.04501515779454613) * (a[1] * b[6]);
-    P[3] += T(0.11909891275269988) * (a[1] * b[8]);
-    P[3] += T(0.10208478235945705) * (a[2] * b[5]);
-    P[3] += T(-0.045015157794546096) * (a[2] * b[7]);
-    P[3] += T(0.068480553847204917) * (a[3] * b[4]);
-    P[3] += T(-0.10208478235945732) * (a[3] * b[6]);
-    P[3] += T(0.068480553847204917) * (a[4] * b[3]);
-    P[3] += T(0.10208478235945705) * (a[5] * b[2]);
-    P[3] += T(0.045015157794546116) * (a[6] * b[1]);
-    P[3] += T(-0.10208478235945732) * (a[6] * b[3]);
-    P[3] += T(-0.1190989127526999) * (a[7] * b[0]);
-    P[3] += T(-0.045015157794546116) * (a[7] * b[2]);
-    P[3] += T(0.11909891275269988) * (a[8] * b[1]);
-    P[4] += T(0.10652530598454149) * (a[0] * b[0]);
-    P[4] += T(-0.15978795897681211) * (a[1] * b[1]);
-    P[4] += T(-0.083698454702139477) * (a[2] * b[2]);
-    P[4] += T(0.068480553847205056) * (a[3] * b[3]);
-    P[4] += T(0.13696110769441061) * (a[4] * b[4]);
-    P[4] += T(0.068480553847205028) * (a[5] * b[5]);
-    P[4] += T(-0.083698454702139269) * (a[6] * b[6]);
-    P[4] += T(-0.15978795897681206) * (a[7] * b[7]);
-    P[4] += T(0.10652530598454124) * (a[8] * b[8]);
-    P[5] += T(-0.1190989127526999) * (a[0] * b[1]);
-    P[5] += T(-0.1190989127526999) * (a[1] * b[0]);
-    P[5] += T(0.045015157794546116) * (a[1] * b[2]);
-    P[5] += T(0.045015157794546082) * (a[2] * b[1]);
-    P[5] += T(0.10208478235945705) * (a[2] * b[3]);
-    P[5] += T(0.10208478235945705) * (a[3] * b[2]);
-    P[5] += T(0.068480553847204889) * (a[4] * b[5]);
-    P[5] += T(0.068480553847204889) * (a[5] * b[4]);
-    P[5] += T(0.10208478235945721) * (a[5] * b[6]);
-    P[5] += T(0.10208478235945721) * (a[6] * b[5]);
-    P[5] += T(0.045015157794546096) * (a[6] * b[7]);
-    P[5] += T(0.04501515779454611) * (a[7] * b[6]);
-    P[5] += T(-0.1190989127526999) * (a[7] * b[8]);
-    P[5] += T(-0.1190989127526999) * (a[8] * b[7]);
-    P[6] += T(0.13504547338363843) * (a[0] * b[2]);
-    P[6] += T(0.045015157794546096) * (a[1] * b[3]);
-    P[6] += T(0.13504547338363843) * (a[2] * b[0]);
-    P[6] += T(0.045015157794546096) * (a[3] * b[1]);
-    P[6] += T(-0.10208478235945732) * (a[3] * b[3]);
-    P[6] += T(-0.083698454702139408) * (a[4] * b[6]);
-    P[6] += T(0.10208478235945721) * (a[5] * b[5]);
-    P[6] += T(0.045015157794546075) * (a[5] * b[7]);
-    P[6] += T(-0.083698454702139408) * (a[6] * b[4]);
-    P[6] += T(0.13504547338363834) * (a[6] * b[8]);
-    P[6] += T(0.045015157794546075) * (a[7] * b[5]);
-    P[6] += T(0.13504547338363837) * (a[8] * b[6]);
-    P[7] += T(-0.1190989127526999) * (a[0] * b[3]);
-    P[7] += T(-0.045015157794546123) * (a[2] * b[3]);
-    P[7] += T(-0.1190989127526999) * (a[3] * b[0]);
-    P[7] += T(-0.045015157794546123) * (a[3] * b[2]);
-    P[7] += T(-0.15978795897681219) * (a[4] * b[7]);
-    P[7] += T(0.045015157794546089) * (a[5] * b[6]);
-    P[7] += T(-0.11909891275269992) * (a[5] * b[8]);
-    P[7] += T(0.045015157794546089) * (a[6] * b[5]);
-    P[7] += T(-0.15978795897681214) * (a[7] * b[4]);
-    P[7] += T(-0.11909891275269992) * (a[8] * b[5]);
-    P[8] += T(0.1190989127526999) * (a[1] * b[3]);
-    P[8] += T(-0.13504547338363845) * (a[2] * b[2]);
-    P[8] += T(0.1190989127526999) * (a[3] * b[1]);
-    P[8] += T(0.10652530598454124) * (a[4] * b[8]);
-    P[8] += T(-0.11909891275269992) * (a[5] * b[7]);
-    P[8] += T(0.13504547338363837) * (a[6] * b[6]);
-    P[8] += T(-0.11909891275269989) * (a[7] * b[5]);
-    P[8] += T(0.10652530598454124) * (a[8] * b[4]);
-  }
-  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {
-    { const T t = T(0.1065253059845416) * Pb[0]; ga[0] += t * b[4]; gb[4] += t * a[0]; }
-    { const T t = T(-0.11909891275269989) * Pb[0]; ga[1] += t * b[5]; gb[5] += t * a[1]; }
-    { const T t = T(0.13504547338363843) * Pb[0]; ga[2] += t * b[6]; gb[6] += t * a[2]; }
-    { const T t = T(-0.1190989127526999) * Pb[0]; ga[3] += t * b[7]; gb[7] += t * a[3]; }
-    { const T t = T(0.10652530598454157) * Pb[0]; ga[4] += t * b[0]; gb[0] += t * a[4]; }
-    { const T t = T(-0.11909891275269992) * Pb[0]; ga[5] += t * b[1]; gb[1] += t * a[5]; }
-    { const T t = T(0.13504547338363843) * Pb[0]; ga[6] += t * b[2]; gb[2] += t * a[6]; }
-    { const T t = T(-0.1190989127526999) * Pb[0]; ga[7] += t * b[3]; gb[3] += t * a[7]; }
-    { const T t = T(-0.11909891275269989) * Pb[1]; ga[0] += t * b[5]; gb[5] += t * a[0]; }
-    { const T t = T(-0.15978795897681217) * Pb[1]; ga[1] += t * b[4]; gb[4] += t * a[1]; }
-    { const T t = T(0.045015157794546165) * Pb[1]; ga[2] += t * b[5]; gb[5] += t * a[2]; }
-    { const T t = T(0.045015157794546068) * Pb[1]; ga[3] += t * b[6]; gb[6] += t * a[3]; }
-    { const T t = T(0.11909891275269992) * Pb[1]; ga[3] += t * b[8]; gb[8] += t * a[3]; }
-    { const T t = T(-0.15978795897681219) * Pb[1]; ga[4] += t * b[1]; gb[1] += t * a[4]; }
-    { const T t = T(-0.11909891275269992) * Pb[1]; ga[5] += t * b[0]; gb[0] += t * a[5]; }
-    { const T t = T(0.045015157794546165) * Pb[1]; ga[5] += t * b[2]; gb[2] += t * a[5]; }
-    { const T t = T(0.045015157794546068) * Pb[1]; ga[6] += t * b[3]; gb[3] += t * a[6]; }
-    { const T t = T(0.11909891275269993) * Pb[1]; ga[8] += t * b[3]; gb[3] += t * a[8]; }
-    { const T t = T(0.13504547338363845) * Pb[2]; ga[0] += t * b[6]; gb[6] += t * a[0]; }
-    { const T t = T(0.045015157794546096) * Pb[2]; ga[1] += t * b[5]; gb[5] += t * a[1]; }
-    { const T t = T(-0.083698454702139574) * Pb[2]; ga[2] += t * b[4]; gb[4] += t * a[2]; }
-    { const T t = T(-0.13504547338363845) * Pb[2]; ga[2] += t * b[8]; gb[8] += t * a[2]; }
-    { const T t = T(0.10208478235945705) * Pb[2]; ga[3] += t * b[5]; gb[5] += t * a[3]; }
-    { const T t = T(-0.045015157794546054) * Pb[2]; ga[3] += t * b[7]; gb[7] += t * a[3]; }
-    { const T t = T(-0.083698454702139574) * Pb[2]; ga[4] += t * b[2]; gb[2] += t * a[4]; }
-    { const T t = T(0.045015157794546096) * Pb[2]; ga[5] += t * b[1]; gb[1] += t * a[5]; }
-    { const T t = T(0.10208478235945705) * Pb[2]; ga[5] += t * b[3]; gb[3] += t * a[5]; }
-    { const T t = T(0.13504547338363843) * Pb[2]; ga[6] += t * b[0]; gb[0] += t * a[6]; }
-    { const T t = T(-0.045015157794546082) * Pb[2]; ga[7] += t * b[3]; gb[3] += t * a[7]; }
-    { const T t = T(-0.13504547338363843) * Pb[2]; ga[8] += t * b[2]; gb[2] += t * a[8]; }
-    { const T t = T(-0.1190989127526999) * Pb[3]; ga[0] += t * b[7]; gb[7] += t * a[0]; }
-    { const T t = T(0.04501515779454613) * Pb[3]; ga[1] += t * b[6]; gb[6] += t * a[1]; }
-    { const T t = T(0.11909891275269988) * Pb[3]; ga[1] += t * b[8]; gb[8] += t * a[1]; }
-    { const T t = T(0.10208478235945705) * Pb[3]; ga[2] += t * b[5]; gb[5] += t * a[2]; }
-    { const T t = T(-0.045015157794546096) * Pb[3]; ga[2] += t * b[7]; gb[7] += t * a[2]; }
-    { const T t = T(0.068480553847204917) * Pb[3]; ga[3] += t * b[4]; gb[4] += t * a[3]; }
-    { const T t = T(-0.10208478235945732) * Pb[3]; ga[3] += t * b[6]; gb[6] += t * a[3]; }
-    { const T t = T(0.068480553847204917) * Pb[3]; ga[4] += t * b[3]; gb[3] += t * a[4]; }
-    { const T t = T(0.10208478235945705) * Pb[3]; ga[5] += t * b[2]; gb[2] += t * a[5]; }
-    { const T t = T(0.045015157794546116) * Pb[3]; ga[6] += t * b[1]; gb[1] += t * a[6]; }
-    { const T t = T(-0.10208478235945732) * Pb[3]; ga[6] += t * b[3]; gb[3] += t * a[6]; }
-    { const T t = T(-0.1190989127526999) * Pb[3]; ga[7] += t * b[0]; gb[0] += t * a[7]; }
-    { const T t = T(-0.045015157794546116) * Pb[3]; ga[7] += t * b[2]; gb[2] += t * a[7]; }
-    { const T t = T(0.11909891275269988) * Pb[3]; ga[8] += t * b[1]; gb[1] += t * a[8]; }
-    { const T t = T(0.10652530598454149) * Pb[4]; ga[0] += t * b[0]; gb[0] += t * a[0]; }
-    { const T t = T(-0.15978795897681211) * Pb[4]; ga[1] += t * b[1]; gb[1] += t * a[1]; }
-    { const T t = T(-0.083698454702139477) * Pb[4]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(0.068480553847205056) * Pb[4]; ga[3] += t * b[3]; gb[3] += t * a[3]; }
-    { const T t = T(0.13696110769441061) * Pb[4]; ga[4] += t * b[4]; gb[4] += t * a[4]; }
-    { const T t = T(0.068480553847205028) * Pb[4]; ga[5] += t * b[5]; gb[5] += t * a[5]; }
-    { const T t = T(-0.083698454702139269) * Pb[4]; ga[6] += t * b[6]; gb[6] += t * a[6]; }
-    { const T t = T(-0.15978795897681206) * Pb[4]; ga[7] += t * b[7]; gb[7] += t * a[7]; }
-    { const T t = T(0.10652530598454124) * Pb[4]; ga[8] += t * b[8]; gb[8] += t * a[8]; }
-    { const T t = T(-0.1190989127526999) * Pb[5]; ga[0] += t * b[1]; gb[1] += t * a[0]; }
-    { const T t = T(-0.1190989127526999) * Pb[5]; ga[1] += t * b[0]; gb[0] += t * a[1]; }
-    { const T t = T(0.045015157794546116) * Pb[5]; ga[1] += t * b[2]; gb[2] += t * a[1]; }
-    { const T t = T(0.045015157794546082) * Pb[5]; ga[2] += t * b[1]; gb[1] += t * a[2]; }
-    { const T t = T(0.10208478235945705) * Pb[5]; ga[2] += t * b[3]; gb[3] += t * a[2]; }
-    { const T t = T(0.10208478235945705) * Pb[5]; ga[3] += t * b[2]; gb[2] += t * a[3]; }
-    { const T t = T(0.068480553847204889) * Pb[5]; ga[4] += t * b[5]; gb[5] += t * a[4]; }
-    { const T t = T(0.068480553847204889) * Pb[5]; ga[5] += t * b[4]; gb[4] += t * a[5]; }
-    { const T t = T(0.10208478235945721) * Pb[5]; ga[5] += t * b[6]; gb[6] += t * a[5]; }
-    { const T t = T(0.10208478235945721) * Pb[5]; ga[6] += t * b[5]; gb[5] += t * a[6]; }
-    { const T t = T(0.045015157794546096) * Pb[5]; ga[6] += t * b[7]; gb[7] += t * a[6]; }
-    { const T t = T(0.04501515779454611) * Pb[5]; ga[7] += t * b[6]; gb[6] += t * a[7]; }
-    { const T t = T(-0.1190989127526999) * Pb[5]; ga[7] += t * b[8]; gb[8] += t * a[7]; }
-    { const T t = T(-0.1190989127526999) * Pb[5]; ga[8] += t * b[7]; gb[7] += t * a[8]; }
-    { const T t = T(0.13504547338363843) * Pb[6]; ga[0] += t * b[2]; gb[2] += t * a[0]; }
-    { const T t = T(0.045015157794546096) * Pb[6]; ga[1] += t * b[3]; gb[3] += t * a[1]; }
-    { const T t = T(0.13504547338363843) * Pb[6]; ga[2] += t * b[0]; gb[0] += t * a[2]; }
-    { const T t = T(0.045015157794546096) * Pb[6]; ga[3] += t * b[1]; gb[1] += t * a[3]; }
-    { const T t = T(-0.10208478235945732) * Pb[6]; ga[3] += t * b[3]; gb[3] += t * a[3]; }
-    { const T t = T(-0.083698454702139408) * Pb[6]; ga[4] += t * b[6]; gb[6] += t * a[4]; }
-    { const T t = T(0.10208478235945721) * Pb[6]; ga[5] += t * b[5]; gb[5] += t * a[5]; }
-    { const T t = T(0.045015157794546075) * Pb[6]; ga[5] += t * b[7]; gb[7] += t * a[5]; }
-    { const T t = T(-0.083698454702139408) * Pb[6]; ga[6] += t * b[4]; gb[4] += t * a[6]; }
-    { const T t = T(0.13504547338363834) * Pb[6]; ga[6] += t * b[8]; gb[8] += t * a[6]; }
-    { const T t = T(0.045015157794546075) * Pb[6]; ga[7] += t * b[5]; gb[5] += t * a[7]; }
-    { const T t = T(0.13504547338363837) * Pb[6]; ga[8] += t * b[6]; gb[6] += t * a[8]; }
-    { const T t = T(-0.1190989127526999) * Pb[7]; ga[0] += t * b[3]; gb[3] += t * a[0]; }
-    { const T t = T(-0.045015157794546123) * Pb[7]; ga[2] += t * b[3]; gb[3] += t * a[2]; }
-    { const T t = T(-0.1190989127526999) * Pb[7]; ga[3] += t * b[0]; gb[0] += t * a[3]; }
-    { const T t = T(-0.045015157794546123) * Pb[7]; ga[3] += t * b[2]; gb[2] += t * a[3]; }
-    { const T t = T(-0.15978795897681219) * Pb[7]; ga[4] += t * b[7]; gb[7] += t * a[4]; }
-    { const T t = T(0.045015157794546089) * Pb[7]; ga[5] += t * b[6]; gb[6] += t * a[5]; }
-    { const T t = T(-0.11909891275269992) * Pb[7]; ga[5] += t * b[8]; gb[8] += t * a[5]; }
-    { const T t = T(0.045015157794546089) * Pb[7]; ga[6] += t * b[5]; gb[5] += t * a[6]; }
-    { const T t = T(-0.15978795897681214) * Pb[7]; ga[7] += t * b[4]; gb[4] += t * a[7]; }
-    { const T t = T(-0.11909891275269992) * Pb[7]; ga[8] += t * b[5]; gb[5] += t * a[8]; }
-    { const T t = T(0.1190989127526999) * Pb[8]; ga[1] += t * b[3]; gb[3] += t * a[1]; }
-    { const T t = T(-0.13504547338363845) * Pb[8]; ga[2] += t * b[2]; gb[2] += t * a[2]; }
-    { const T t = T(0.1190989127526999) * Pb[8]; ga[3] += t * b[1]; gb[1] += t * a[3]; }
-    { const T t = T(0.10652530598454124) * Pb[8]; ga[4] += t * b[8]; gb[8] += t * a[4]; }
-    { const T t = T(-0.11909891275269992) * Pb[8]; ga[5] += t * b[7]; gb[7] += t * a[5]; }
-    { const T t = T(0.13504547338363837) * Pb[8]; ga[6] += t * b[6]; gb[6] += t * a[6]; }
-    { const T t = T(-0.11909891275269989) * Pb[8]; ga[7] += t * b[5]; gb[5] += t * a[7]; }
-    { const T t = T(0.10652530598454124) * Pb[8]; ga[8] += t * b[4]; gb[4] += t * a[8]; }
+constexpr double kSymScale[5][5][5] = {
+    {{0.28209479177387803, 1, 1, 1, 1}, {1, 0.28209479177387808, 1, 1, 1}, {1, 1, 0.2820947917738782, 1, 1}, {1, 1, 1, 0.2820947917738782, 1}, {1, 1, 1, 1, 0.28209479177387781}},
+    {{1, 1, 1, 1, 1}, {0.28209479177387803, 1, 0.2185096861184159, 1, 1}, {1, 0.21850968611841587, 1, 0.23359668032760758, 1}, {1, 1, 0.18467439092237189, 1, 0.23841361350444787}, {1, 1, 1, 0.23841361350444787, 1}},
+    {{1, 1, 1, 1, 1}, {1, 1, 1, 1, 1}, {0.2820947917738782, 1, 0.18022375157286874, 1, 0.23841361350444834}, {1, 0.18467439092237187, 1, 0.14867700967939756, 1}, {1, 1, 0.16858388283618389, 1, 0.14046334619025072}},
+    {{1, 1, 1, 1, 1}, {1, 1, 1, 1, 1}, {1, 1, 1, 1, 1}, {0.2820947917738782, 1, 0.1880631945159188, 1, 0.099322584599279881}, {1, 0.23032943298089015, 1, 0.099322584599279853, 1}},
+    {{1, 1, 1, 1, 1}, {1, 1, 1, 1, 1}, {1, 1, 1, 1, 1}, {1, 1, 1, 1, 1}, {0.28209479177387786, 1, 0.19036461502711166, 1, 0.1190989127526999}},
+};
+constexpr int kGauntTerms[5][5][5] = {
+    {{1, 0, 0, 0, 0}, {0, 3, 0, 0, 0}, {0, 0, 5, 0, 0}, {0, 0, 0, 7, 0}, {0, 0, 0, 0, 9}},
+    {{0, 3, 0, 0, 0}, {3, 0, 11, 0, 0}, {0, 11, 0, 21, 0}, {0, 0, 21, 0, 31}, {0, 0, 0, 31, 0}},
+    {{0, 0, 5, 0, 0}, {0, 11, 0, 21, 0}, {5, 0, 25, 0, 37}, {0, 21, 0, 41, 0}, {0, 0, 37, 0, 61}},
+    {{0, 0, 0, 7, 0}, {0, 0, 21, 0, 31}, {0, 21, 0, 41, 0}, {7, 0, 41, 0, 67}, {0, 31, 0, 67, 0}},
+    {{0, 0, 0, 0, 9}, {0, 0, 0, 31, 0}, {0, 0, 37, 0, 61}, {0, 31, 0, 67, 0}, {9, 0, 61, 0, 97}},
+};
+template <int L1, int L2, int M> struct SymP;
+template <> struct SymP<0, 0, 0> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    {
+      T t = a[0] * b[0];
+      P[0] = t;
+    }
+  }
+};
+template <> struct SymP<0, 1, -1> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    {
+      T t = a[0] * b[0];
+      P[1] = t;
+    }
+  }
+};
+template <> struct SymP<0, 1, 0> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    {
+      T t = a[0] * b[1];
+      P[1] = t;
+    }
+  }
+};
+template <> struct SymP<0, 1, 1> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    {
+      T t = a[0] * b[2];
+      P[1] = t;
+    }
+  }
+};
+template <> struct SymP<0, 2, -2> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    {
+      T t = a[0] * b[0];
+      P[2] = t;
+    }
+  }
+};
+template <> struct SymP<0, 2, -1> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    {
+      T t = a[0] * b[1];
+      P[2] = t;
+    }
+  }
+};
+template <> struct SymP<0, 2, 0> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    {
+      T t = a[0] * b[2];
+      P[2] = t;
+    }
+  }
+};
+template <> struct SymP<0, 2, 1> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    {
+      T t = a[0] * b[3];
+      P[2] = t;
+    }
+  }
+};
+template <> struct SymP<0, 2, 2> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    {
+      T t = a[0] * b[4];
+      P[2] = t;
+    }
+  }
+};
+template <> struct SymP<0, 3, -3> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    {
+      T t = a[0] * b[0];
+      P[3] = t;
+    }
+  }
+};
+template <> struct SymP<0, 3, -2> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    {
+      T t = a[0] * b[1];
+      P[3] = t;
+    }
+  }
+};
+template <> struct SymP<0, 3, -1> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    {
+      T t = a[0] * b[2];
+      P[3] = t;
+    }
+  }
+};
+template <> struct SymP<0, 3, 0> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    {
+      T t = a[0] * b[3];
+      P[3] = t;
+    }
+  }
+};
+template <> struct SymP<0, 3, 1> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    {
+      T t = a[0] * b[4];
+      P[3] = t;
+    }
+  }
+};
+template <> struct SymP<0, 3, 2> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    {
+      T t = a[0] * b[5];
+      P[3] = t;
+    }
+  }
+};
+template <> struct SymP<0, 3, 3> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    {
+      T t = a[0] * b[6];
+      P[3] = t;
+    }
+  }
+};
+template <> struct SymP<0, 4, -4> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    if constexpr (LMAX >= 4) {
+      T t = a[0] * b[0];
+      P[4] = t;
+    }
+  }
+};
+template <> struct SymP<0, 4, -3> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    if constexpr (LMAX >= 4) {
+      T t = a[0] * b[1];
+      P[4] = t;
+    }
+  }
+};
+template <> struct SymP<0, 4, -2> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    if constexpr (LMAX >= 4) {
+      T t = a[0] * b[2];
+      P[4] = t;
+    }
+  }
+};
+template <> struct SymP<0, 4, -1> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    if constexpr (LMAX >= 4) {
+      T t = a[0] * b[3];
+      P[4] = t;
+    }
+  }
+};
+template <> struct SymP<0, 4, 0> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    if constexpr (LMAX >= 4) {
+      T t = a[0] * b[4];
+      P[4] = t;
+    }
+  }
+};
+template <> struct SymP<0, 4, 1> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    if constexpr (LMAX >= 4) {
+      T t = a[0] * b[5];
+      P[4] = t;
+    }
+  }
+};
+template <> struct SymP<0, 4, 2> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    if constexpr (LMAX >= 4) {
+      T t = a[0] * b[6];
+      P[4] = t;
+    }
+  }
+};
+template <> struct SymP<0, 4, 3> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    if constexpr (LMAX >= 4) {
+      T t = a[0] * b[7];
+      P[4] = t;
+    }
+  }
+};
+template <> struct SymP<0, 4, 4> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    if constexpr (LMAX >= 4) {
+      T t = a[0] * b[8];
+      P[4] = t;
+    }
+  }
+};
+template <> struct SymP<1, 1, -2> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    {
+      T t = a[0] * b[2];
+      t = fma(a[2], b[0], t);
+      P[2] = t;
+    }
+  }
+};
+template <> struct SymP<1, 1, -1> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    {
+      T t = a[0] * b[1];
+      t = fma(a[1], b[0], t);
+      P[2] = t;
+    }
+  }
+};
+template <> struct SymP<1, 1, 0> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    {
+      T t = a[0] * b[0];
+      t = fma(a[2], b[2], t);
+      P[0] = t;
+      P[2] = T(-0.57735026918962584) * t;
+    }
+    {
+      T t = a[1] * b[1];
+      P[0] = P[0] + t;
+      P[2] = fma(T(1.154700538379251), t, P[2]);
+    }
+  }
+};
+template <> struct SymP<1, 1, 1> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    {
+      T t = a[1] * b[2];
+      t = fma(a[2], b[1], t);
+      P[2] = t;
+    }
+  }
+};
+template <> struct SymP<1, 1, 2> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    {
+      T t = a[0] * b[0];
+      t = fma(-a[2], b[2], t);
+      P[2] = -t;
+    }
+  }
+};
+template <> struct SymP<1, 2, -3> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    {
+      T t = a[0] * b[4];
+      t = fma(a[2], b[0], t);
+      P[3] = T(0.96824583655185315) * t;
+    }
+  }
+};
+template <> struct SymP<1, 2, -2> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    {
+      T t = a[0] * b[3];
+      t = fma(a[1], b[0], t);
+      t = fma(a[2], b[1], t);
+      P[3] = T(0.79056941504209466) * t;
+    }
+  }
+};
+template <> struct SymP<1, 2, -1> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    {
+      T t = a[0] * b[2];
+      P[1] = T(-0.57735026918962584) * t;
+      P[3] = T(0.86602540378443804) * t;
+    }
+    {
+      T t = a[0] * b[4];
+      t = fma(-a[2], b[0], t);
+      P[1] = P[1] - t;
+      P[3] = fma(T(0.24999999999999928), t, P[3]);
+    }
+    {
+      T t = a[1] * b[1];
+      P[1] = P[1] + t;
+      P[3] = P[3] + t;
+    }
+  }
+};
+template <> struct SymP<1, 2, 0> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    {
+      T t = a[0] * b[1];
+      t = fma(a[2], b[3], t);
+      P[1] = t;
+      P[3] = T(-0.61237243569579436) * t;
+    }
+    {
+      T t = a[1] * b[2];
+      P[1] = fma(T(1.1547005383792512), t, P[1]);
+      P[3] = fma(T(1.0606601717798201), t, P[3]);
+    }
+  }
+};
+template <> struct SymP<1, 2, 1> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    {
+      T t = a[0] * b[0];
+      t = fma(a[2], b[4], t);
+      P[1] = t;
+      P[3] = T(-0.24999999999999986) * t;
+    }
+    {
+      T t = a[1] * b[3];
+      P[1] = P[1] + t;
+      P[3] = P[3] + t;
+    }
+    {
+      T t = a[2] * b[2];
+      P[1] = fma(T(-0.57735026918962584), t, P[1]);
+      P[3] = fma(T(0.86602540378443804), t, P[3]);
+    }
+  }
+};
+template <> struct SymP<1, 2, 2> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    {
+      T t = a[0] * b[1];
+      t = fma(-a[1], b[4], t);
+      t = fma(-a[2], b[3], t);
+      P[3] = T(-0.79056941504209466) * t;
+    }
+  }
+};
+template <> struct SymP<1, 2, 3> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    {
+      T t = a[0] * b[0];
+      t = fma(-a[2], b[4], t);
+      P[3] = T(-0.96824583655185392) * t;
+    }
+  }
+};
+template <> struct SymP<1, 3, -4> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    if constexpr (LMAX >= 4) {
+      T t = a[0] * b[6];
+      t = fma(a[2], b[0], t);
+      P[4] = T(0.96609178307929611) * t;
+    }
+  }
+};
+template <> struct SymP<1, 3, -3> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    if constexpr (LMAX >= 4) {
+      T t = a[0] * b[5];
+      t = fma(a[2], b[1], t);
+      P[4] = T(0.83666002653407578) * t;
+    }
+    if constexpr (LMAX >= 4) {
+      T t = a[1] * b[0];
+      P[4] = fma(T(0.68313005106397384), t, P[4]);
+    }
+  }
+};
+template <> struct SymP<1, 3, -2> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    {
+      T t = a[0] * b[4];
+      t = fma(a[2], b[2], t);
+      P[2] = T(-0.31622776601683789) * t;
+      if constexpr (LMAX >= 4) P[4] = T(0.70710678118654835) * t;
+    }
+    {
+      T t = a[0] * b[6];
+      t = fma(-a[2], b[0], t);
+      P[2] = fma(T(-1.2247448713915892), t, P[2]);
+      if constexpr (LMAX >= 4) P[4] = fma(T(0.18257418583505539), t, P[4]);
+    }
+    {
+      T t = a[1] * b[1];
+      P[2] = P[2] + t;
+      if constexpr (LMAX >= 4) P[4] = fma(T(0.89442719099991697), t, P[4]);
+    }
+  }
+};
+template <> struct SymP<1, 3, -1> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    {
+      T t = a[0] * b[3];
+      P[2] = T(-0.7745966692414834) * t;
+      if constexpr (LMAX >= 4) P[4] = T(0.81649658092772581) * t;
+    }
+    {
+      T t = a[0] * b[5];
+      t = fma(-a[2], b[1], t);
+      P[2] = P[2] - t;
+      if constexpr (LMAX >= 4) P[4] = fma(T(0.31622776601683783), t, P[4]);
+    }
+    {
+      T t = a[1] * b[2];
+      P[2] = fma(T(1.2649110640673522), t, P[2]);
+      if constexpr (LMAX >= 4) P[4] = P[4] + t;
+    }
+  }
+};
+template <> struct SymP<1, 3, 0> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    {
+      T t = a[0] * b[2];
+      t = fma(a[2], b[4], t);
+      P[2] = T(1.0954451150103319) * t;
+      if constexpr (LMAX >= 4) P[4] = T(-0.63245553203367699) * t;
+    }
+    {
+      T t = a[1] * b[3];
+      P[2] = fma(T(1.341640786499873), t, P[2]);
+      if constexpr (LMAX >= 4) P[4] = fma(T(1.0327955589886459), t, P[4]);
+    }
+  }
+};
+template <> struct SymP<1, 3, 1> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    {
+      T t = a[0] * b[1];
+      t = fma(a[2], b[5], t);
+      P[2] = t;
+      if constexpr (LMAX >= 4) P[4] = T(-0.31622776601683822) * t;
+    }
+    {
+      T t = a[1] * b[4];
+      P[2] = fma(T(1.2649110640673522), t, P[2]);
+      if constexpr (LMAX >= 4) P[4] = P[4] + t;
+    }
+    {
+      T t = a[2] * b[3];
+      P[2] = fma(T(-0.7745966692414834), t, P[2]);
+      if constexpr (LMAX >= 4) P[4] = fma(T(0.81649658092772581), t, P[4]);
+    }
+  }
+};
+template <> struct SymP<1, 3, 2> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    {
+      T t = a[0] * b[0];
+      t = fma(a[2], b[6], t);
+      P[2] = T(1.2247448713915883) * t;
+      if constexpr (LMAX >= 4) P[4] = T(-0.18257418583505561) * t;
+    }
+    {
+      T t = a[0] * b[2];
+      t = fma(-a[2], b[4], t);
+      P[2] = fma(T(0.31622776601683716), t, P[2]);
+      if constexpr (LMAX >= 4) P[4] = fma(T(-0.70710678118654846), t, P[4]);
+    }
+    {
+      T t = a[1] * b[5];
+      P[2] = P[2] + t;
+      if constexpr (LMAX >= 4) P[4] = fma(T(0.89442719099991697), t, P[4]);
+    }
+  }
+};
+template <> struct SymP<1, 3, 3> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    if constexpr (LMAX >= 4) {
+      T t = a[0] * b[1];
+      t = fma(-a[2], b[5], t);
+      P[4] = T(-0.83666002653407623) * t;
+    }
+    if constexpr (LMAX >= 4) {
+      T t = a[1] * b[6];
+      P[4] = fma(T(0.68313005106397384), t, P[4]);
+    }
+  }
+};
+template <> struct SymP<1, 3, 4> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    if constexpr (LMAX >= 4) {
+      T t = a[0] * b[0];
+      t = fma(-a[2], b[6], t);
+      P[4] = T(-0.96609178307929744) * t;
+    }
+  }
+};
+template <> struct SymP<1, 4, -3> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    {
+      T t = a[0] * b[6];
+      t = fma(a[2], b[2], t);
+      P[3] = T(-0.18257418583505552) * t;
+    }
+    {
+      T t = a[0] * b[8];
+      t = fma(-a[2], b[0], t);
+      P[3] = fma(T(-0.96609178307929744), t, P[3]);
+    }
+    {
+      T t = a[1] * b[1];
+      P[3] = fma(T(0.68313005106397384), t, P[3]);
+    }
+  }
+};
+template <> struct SymP<1, 4, -2> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    {
+      T t = a[0] * b[5];
+      t = fma(a[2], b[3], t);
+      P[3] = T(-0.31622776601683822) * t;
+    }
+    {
+      T t = a[0] * b[7];
+      t = fma(-a[2], b[1], t);
+      P[3] = fma(T(-0.83666002653407623), t, P[3]);
+    }
+    {
+      T t = a[1] * b[2];
+      P[3] = fma(T(0.89442719099991697), t, P[3]);
+    }
+  }
+};
+template <> struct SymP<1, 4, -1> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    {
+      T t = a[0] * b[4];
+      P[3] = T(-0.63245553203367699) * t;
+    }
+    {
+      T t = a[0] * b[6];
+      t = fma(-a[2], b[2], t);
+      P[3] = fma(T(-0.70710678118654846), t, P[3]);
+    }
+    {
+      T t = a[1] * b[3];
+      P[3] = P[3] + t;
+    }
+  }
+};
+template <> struct SymP<1, 4, 0> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    {
+      T t = a[0] * b[3];
+      t = fma(a[2], b[5], t);
+      P[3] = T(0.81649658092772581) * t;
+    }
+    {
+      T t = a[1] * b[4];
+      P[3] = fma(T(1.0327955589886459), t, P[3]);
+    }
+  }
+};
+template <> struct SymP<1, 4, 1> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    {
+      T t = a[0] * b[2];
+      t = fma(a[2], b[6], t);
+      P[3] = T(0.70710678118654835) * t;
+    }
+    {
+      T t = a[1] * b[5];
+      P[3] = P[3] + t;
+    }
+    {
+      T t = a[2] * b[4];
+      P[3] = fma(T(-0.63245553203367699), t, P[3]);
+    }
+  }
+};
+template <> struct SymP<1, 4, 2> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    {
+      T t = a[0] * b[1];
+      t = fma(a[2], b[7], t);
+      P[3] = T(0.83666002653407578) * t;
+    }
+    {
+      T t = a[0] * b[3];
+      t = fma(-a[2], b[5], t);
+      P[3] = fma(T(0.31622776601683783), t, P[3]);
+    }
+    {
+      T t = a[1] * b[6];
+      P[3] = fma(T(0.89442719099991674), t, P[3]);
+    }
+  }
+};
+template <> struct SymP<1, 4, 3> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    {
+      T t = a[0] * b[0];
+      t = fma(a[2], b[8], t);
+      P[3] = T(0.96609178307929611) * t;
+    }
+    {
+      T t = a[0] * b[2];
+      t = fma(-a[2], b[6], t);
+      P[3] = fma(T(0.18257418583505547), t, P[3]);
+    }
+    {
+      T t = a[1] * b[7];
+      P[3] = fma(T(0.68313005106397384), t, P[3]);
+    }
+  }
+};
+template <> struct SymP<2, 2, -4> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    if constexpr (LMAX >= 4) {
+      T t = a[0] * b[4];
+      t = fma(a[4], b[0], t);
+      P[4] = t;
+    }
+  }
+};
+template <> struct SymP<2, 2, -3> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    if constexpr (LMAX >= 4) {
+      T t = a[0] * b[3];
+      t = fma(a[1], b[4], t);
+      t = fma(a[3], b[0], t);
+      t = fma(a[4], b[1], t);
+      P[4] = T(0.70710678118654691) * t;
+    }
+  }
+};
+template <> struct SymP<2, 2, -2> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    {
+      T t = a[0] * b[2];
+      t = fma(a[2], b[0], t);
+      P[2] = -t;
+      if constexpr (LMAX >= 4) P[4] = T(0.65465367070797664) * t;
+    }
+    {
+      T t = a[1] * b[3];
+      t = fma(a[3], b[1], t);
+      P[2] = fma(T(0.86602540378443849), t, P[2]);
+      if constexpr (LMAX >= 4) P[4] = fma(T(0.75592894601845395), t, P[4]);
+    }
+  }
+};
+template <> struct SymP<2, 2, -1> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    {
+      T t = a[0] * b[3];
+      t = fma(-a[1], b[4], t);
+      t = fma(a[3], b[0], t);
+      t = fma(-a[4], b[1], t);
+      P[2] = T(0.86602540378443849) * t;
+      if constexpr (LMAX >= 4) P[4] = T(-0.26726124191242406) * t;
+    }
+    {
+      T t = a[1] * b[2];
+      t = fma(a[2], b[1], t);
+      P[2] = fma(T(0.50000000000000011), t, P[2]);
+      if constexpr (LMAX >= 4) P[4] = fma(T(0.92582009977254953), t, P[4]);
+    }
+  }
+};
+template <> struct SymP<2, 2, 0> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    {
+      T t = a[0] * b[0];
+      t = fma(a[4], b[4], t);
+      P[0] = t;
+      P[2] = -t;
+      if constexpr (LMAX >= 4) P[4] = T(0.16903085094570297) * t;
+    }
+    {
+      T t = a[1] * b[1];
+      t = fma(a[3], b[3], t);
+      P[0] = P[0] + t;
+      P[2] = fma(T(0.50000000000000011), t, P[2]);
+      if constexpr (LMAX >= 4) P[4] = fma(T(-0.67612340378281399), t, P[4]);
+    }
+    {
+      T t = a[2] * b[2];
+      P[0] = P[0] + t;
+      P[2] = P[2] + t;
+      if constexpr (LMAX >= 4) P[4] = fma(T(1.0141851056742193), t, P[4]);
+    }
+  }
+};
+template <> struct SymP<2, 2, 1> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    {
+      T t = a[0] * b[1];
+      t = fma(a[1], b[0], t);
+      t = fma(a[3], b[4], t);
+      t = fma(a[4], b[3], t);
+      P[2] = T(0.86602540378443849) * t;
+      if constexpr (LMAX >= 4) P[4] = T(-0.26726124191242406) * t;
+    }
+    {
+      T t = a[2] * b[3];
+      t = fma(a[3], b[2], t);
+      P[2] = fma(T(0.50000000000000011), t, P[2]);
+      if constexpr (LMAX >= 4) P[4] = fma(T(0.92582009977254953), t, P[4]);
+    }
+  }
+};
+template <> struct SymP<2, 2, 2> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    {
+      T t = a[1] * b[1];
+      t = fma(-a[3], b[3], t);
+      P[2] = T(-0.86602540378443871) * t;
+      if constexpr (LMAX >= 4) P[4] = T(-0.7559289460184544) * t;
+    }
+    {
+      T t = a[2] * b[4];
+      t = fma(a[4], b[2], t);
+      P[2] = P[2] - t;
+      if constexpr (LMAX >= 4) P[4] = fma(T(0.65465367070797675), t, P[4]);
+    }
+  }
+};
+template <> struct SymP<2, 2, 3> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    if constexpr (LMAX >= 4) {
+      T t = a[0] * b[1];
+      t = fma(a[1], b[0], t);
+      t = fma(-a[3], b[4], t);
+      t = fma(-a[4], b[3], t);
+      P[4] = T(-0.70710678118654691) * t;
+    }
+  }
+};
+template <> struct SymP<2, 2, 4> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    if constexpr (LMAX >= 4) {
+      T t = a[0] * b[0];
+      t = fma(-a[4], b[4], t);
+      P[4] = -t;
+    }
+  }
+};
+template <> struct SymP<2, 3, -3> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    {
+      T t = a[0] * b[4];
+      t = fma(a[4], b[2], t);
+      P[3] = T(-0.63245553203367577) * t;
+    }
+    {
+      T t = a[1] * b[5];
+      t = fma(a[3], b[1], t);
+      P[3] = P[3] + t;
+    }
+    {
+      T t = a[2] * b[0];
+      P[3] = fma(T(-1.4142135623730954), t, P[3]);
+    }
+  }
+};
+template <> struct SymP<2, 3, -2> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    {
+      T t = a[0] * b[3];
+      P[3] = T(-1.2649110640673522) * t;
+    }
+    {
+      T t = a[1] * b[4];
+      t = fma(a[3], b[2], t);
+      P[3] = fma(T(0.77459666924148407), t, P[3]);
+    }
+    {
+      T t = a[1] * b[6];
+      t = fma(-a[3], b[0], t);
+      P[3] = P[3] - t;
+    }
+  }
+};
+template <> struct SymP<2, 3, -1> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    {
+      T t = a[0] * b[4];
+      t = fma(-a[4], b[2], t);
+      P[1] = T(-0.31622776601683794) * t;
+      P[3] = T(0.97979589711327175) * t;
+    }
+    {
+      T t = a[0] * b[6];
+      t = fma(-a[4], b[0], t);
+      P[1] = fma(T(-1.2247448713915894), t, P[1]);
+      P[3] = fma(T(0.63245553203367566), t, P[3]);
+    }
+    {
+      T t = a[1] * b[3];
+      P[1] = fma(T(-0.77459666924148352), t, P[1]);
+      P[3] = fma(T(0.39999999999999869), t, P[3]);
+    }
+    {
+      T t = a[1] * b[5];
+      t = fma(-a[3], b[1], t);
+      P[1] = P[1] - t;
+      P[3] = fma(T(-0.7745966692414844), t, P[3]);
+    }
+    {
+      T t = a[2] * b[2];
+      P[1] = fma(T(1.0954451150103321), t, P[1]);
+      P[3] = fma(T(0.84852813742385624), t, P[3]);
+    }
+  }
+};
+template <> struct SymP<2, 3, 0> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    {
+      T t = a[0] * b[1];
+      t = fma(a[4], b[5], t);
+      P[1] = t;
+      P[3] = T(-1.2649110640673522) * t;
+    }
+    {
+      T t = a[1] * b[2];
+      t = fma(a[3], b[4], t);
+      P[1] = fma(T(1.2649110640673524), t, P[1]);
+      P[3] = fma(T(0.39999999999999869), t, P[3]);
+    }
+    {
+      T t = a[2] * b[3];
+      P[1] = fma(T(1.3416407864998732), t, P[1]);
+      P[3] = fma(T(1.1313708498984774), t, P[3]);
+    }
+  }
+};
+template <> struct SymP<2, 3, 1> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    {
+      T t = a[0] * b[0];
+      t = fma(a[4], b[6], t);
+      P[1] = T(1.2247448713915894) * t;
+      P[3] = T(-0.63245553203367555) * t;
+    }
+    {
+      T t = a[0] * b[2];
+      t = fma(a[4], b[4], t);
+      P[1] = fma(T(-0.31622776601683794), t, P[1]);
+      P[3] = fma(T(0.97979589711327175), t, P[3]);
+    }
+    {
+      T t = a[1] * b[1];
+      t = fma(a[3], b[5], t);
+      P[1] = P[1] + t;
+      P[3] = fma(T(0.77459666924148407), t, P[3]);
+    }
+    {
+      T t = a[2] * b[4];
+      P[1] = fma(T(1.0954451150103321), t, P[1]);
+      P[3] = fma(T(0.84852813742385624), t, P[3]);
+    }
+    {
+      T t = a[3] * b[3];
+      P[1] = fma(T(-0.77459666924148352), t, P[1]);
+      P[3] = fma(T(0.39999999999999869), t, P[3]);
+    }
+  }
+};
+template <> struct SymP<2, 3, 2> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    {
+      T t = a[1] * b[0];
+      t = fma(a[3], b[6], t);
+      P[3] = t;
+    }
+    {
+      T t = a[1] * b[2];
+      t = fma(-a[3], b[4], t);
+      P[3] = fma(T(-0.7745966692414844), t, P[3]);
+    }
+    {
+      T t = a[4] * b[3];
+      P[3] = fma(T(-1.2649110640673511), t, P[3]);
+    }
+  }
+};
+template <> struct SymP<2, 3, 3> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    {
+      T t = a[0] * b[2];
+      t = fma(-a[4], b[4], t);
+      P[3] = T(0.63245553203367577) * t;
+    }
+    {
+      T t = a[1] * b[1];
+      t = fma(-a[3], b[5], t);
+      P[3] = P[3] - t;
+    }
+    {
+      T t = a[2] * b[6];
+      P[3] = fma(T(-1.4142135623730954), t, P[3]);
+    }
+  }
+};
+template <> struct SymP<2, 4, -4> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    if constexpr (LMAX >= 4) {
+      T t = a[0] * b[6];
+      t = fma(a[4], b[2], t);
+      P[4] = T(-0.53452248382484924) * t;
+    }
+    if constexpr (LMAX >= 4) {
+      T t = a[1] * b[7];
+      t = fma(a[3], b[1], t);
+      P[4] = P[4] + t;
+    }
+    if constexpr (LMAX >= 4) {
+      T t = a[2] * b[0];
+      P[4] = fma(T(-1.6329931618554532), t, P[4]);
+    }
+  }
+};
+template <> struct SymP<2, 4, -3> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    if constexpr (LMAX >= 4) {
+      T t = a[0] * b[5];
+      t = fma(a[4], b[3], t);
+      P[4] = T(-0.80178372573727341) * t;
+    }
+    if constexpr (LMAX >= 4) {
+      T t = a[1] * b[6];
+      t = fma(a[3], b[2], t);
+      P[4] = fma(T(0.94491118252306838), t, P[4]);
+    }
+    if constexpr (LMAX >= 4) {
+      T t = a[1] * b[8];
+      t = fma(-a[3], b[0], t);
+      P[4] = P[4] - t;
+    }
+    if constexpr (LMAX >= 4) {
+      T t = a[2] * b[1];
+      P[4] = fma(T(-0.40824829046386252), t, P[4]);
+    }
+  }
+};
+template <> struct SymP<2, 4, -2> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    {
+      T t = a[0] * b[4];
+      P[2] = T(0.23904572186687828) * t;
+      if constexpr (LMAX >= 4) P[4] = T(-1.3552618543578778) * t;
+    }
+    {
+      T t = a[0] * b[8];
+      t = fma(-a[4], b[0], t);
+      P[2] = fma(T(-1.4142135623730963), t, P[2]);
+      if constexpr (LMAX >= 4) P[4] = fma(T(0.5345224838248479), t, P[4]);
+    }
+    {
+      T t = a[1] * b[5];
+      t = fma(a[3], b[3], t);
+      P[2] = fma(T(-0.37796447300922736), t, P[2]);
+      if constexpr (LMAX >= 4) P[4] = fma(T(0.64285714285714224), t, P[4]);
+    }
+    {
+      T t = a[1] * b[7];
+      t = fma(-a[3], b[1], t);
+      P[2] = P[2] - t;
+      if constexpr (LMAX >= 4) P[4] = fma(T(-0.94491118252306883), t, P[4]);
+    }
+    {
+      T t = a[2] * b[2];
+      P[2] = fma(T(0.92582009977255131), t, P[2]);
+      if constexpr (LMAX >= 4) P[4] = fma(T(0.46656947481584238), t, P[4]);
+    }
+  }
+};
+template <> struct SymP<2, 4, -1> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    {
+      T t = a[0] * b[5];
+      t = fma(-a[4], b[3], t);
+      P[2] = T(-0.37796447300922725) * t;
+      if constexpr (LMAX >= 4) P[4] = T(1.0101525445522106) * t;
+    }
+    {
+      T t = a[0] * b[7];
+      t = fma(-a[4], b[1], t);
+      P[2] = P[2] - t;
+      if constexpr (LMAX >= 4) P[4] = fma(T(0.8017837257372733), t, P[4]);
+    }
+    {
+      T t = a[1] * b[4];
+      P[2] = fma(T(-0.95618288746751645), t, P[2]);
+      if constexpr (LMAX >= 4) P[4] = fma(T(0.3194382824999708), t, P[4]);
+    }
+    {
+      T t = a[1] * b[6];
+      t = fma(-a[3], b[2], t);
+      P[2] = fma(T(-1.0690449676496983), t, P[2]);
+      if constexpr (LMAX >= 4) P[4] = fma(T(-0.64285714285714346), t, P[4]);
+    }
+    {
+      T t = a[2] * b[3];
+      P[2] = fma(T(1.3093073414159533), t, P[2]);
+      if constexpr (LMAX >= 4) P[4] = fma(T(0.99146013398366739), t, P[4]);
+    }
+  }
+};
+template <> struct SymP<2, 4, 0> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    {
+      T t = a[0] * b[2];
+      t = fma(a[4], b[6], t);
+      P[2] = T(0.92582009977255153) * t;
+      if constexpr (LMAX >= 4) P[4] = T(-1.3552618543578778) * t;
+    }
+    {
+      T t = a[1] * b[3];
+      t = fma(a[3], b[5], t);
+      P[2] = fma(T(1.3093073414159526), t, P[2]);
+      if constexpr (LMAX >= 4) P[4] = fma(T(0.31943828249997047), t, P[4]);
+    }
+    {
+      T t = a[2] * b[4];
+      P[2] = fma(T(1.4342743312012729), t, P[2]);
+      if constexpr (LMAX >= 4) P[4] = fma(T(1.1664236870396105), t, P[4]);
+    }
+  }
+};
+template <> struct SymP<2, 4, 1> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    {
+      T t = a[0] * b[1];
+      t = fma(a[4], b[7], t);
+      P[2] = t;
+      if constexpr (LMAX >= 4) P[4] = T(-0.80178372573727341) * t;
+    }
+    {
+      T t = a[0] * b[3];
+      t = fma(a[4], b[5], t);
+      P[2] = fma(T(-0.37796447300922725), t, P[2]);
+      if constexpr (LMAX >= 4) P[4] = fma(T(1.0101525445522106), t, P[4]);
+    }
+    {
+      T t = a[1] * b[2];
+      t = fma(a[3], b[6], t);
+      P[2] = fma(T(1.0690449676496978), t, P[2]);
+      if constexpr (LMAX >= 4) P[4] = fma(T(0.64285714285714191), t, P[4]);
+    }
+    {
+      T t = a[2] * b[5];
+      P[2] = fma(T(1.3093073414159528), t, P[2]);
+      if constexpr (LMAX >= 4) P[4] = fma(T(0.99146013398366684), t, P[4]);
+    }
+    {
+      T t = a[3] * b[4];
+      P[2] = fma(T(-0.95618288746751623), t, P[2]);
+      if constexpr (LMAX >= 4) P[4] = fma(T(0.31943828249997058), t, P[4]);
+    }
+  }
+};
+template <> struct SymP<2, 4, 2> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    {
+      T t = a[0] * b[0];
+      t = fma(a[4], b[8], t);
+      P[2] = T(1.4142135623730931) * t;
+      if constexpr (LMAX >= 4) P[4] = T(-0.53452248382484924) * t;
+    }
+    {
+      T t = a[1] * b[1];
+      t = fma(a[3], b[7], t);
+      P[2] = P[2] + t;
+      if constexpr (LMAX >= 4) P[4] = fma(T(0.94491118252306838), t, P[4]);
+    }
+    {
+      T t = a[1] * b[3];
+      t = fma(-a[3], b[5], t);
+      P[2] = fma(T(0.37796447300922653), t, P[2]);
+      if constexpr (LMAX >= 4) P[4] = fma(T(-0.64285714285714368), t, P[4]);
+    }
+    {
+      T t = a[2] * b[6];
+      P[2] = fma(T(0.92582009977255131), t, P[2]);
+      if constexpr (LMAX >= 4) P[4] = fma(T(0.46656947481584315), t, P[4]);
+    }
+    {
+      T t = a[4] * b[4];
+      P[2] = fma(T(0.23904572186687897), t, P[2]);
+      if constexpr (LMAX >= 4) P[4] = fma(T(-1.3552618543578783), t, P[4]);
+    }
+  }
+};
+template <> struct SymP<2, 4, 3> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    if constexpr (LMAX >= 4) {
+      T t = a[0] * b[3];
+      t = fma(-a[4], b[5], t);
+      P[4] = T(0.80178372573727352) * t;
+    }
+    if constexpr (LMAX >= 4) {
+      T t = a[1] * b[0];
+      t = fma(a[3], b[8], t);
+      P[4] = P[4] + t;
+    }
+    if constexpr (LMAX >= 4) {
+      T t = a[1] * b[2];
+      t = fma(-a[3], b[6], t);
+      P[4] = fma(T(-0.94491118252306927), t, P[4]);
+    }
+    if constexpr (LMAX >= 4) {
+      T t = a[2] * b[7];
+      P[4] = fma(T(-0.40824829046386252), t, P[4]);
+    }
+  }
+};
+template <> struct SymP<2, 4, 4> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    if constexpr (LMAX >= 4) {
+      T t = a[0] * b[2];
+      t = fma(-a[4], b[6], t);
+      P[4] = T(0.53452248382484835) * t;
+    }
+    if constexpr (LMAX >= 4) {
+      T t = a[1] * b[1];
+      t = fma(-a[3], b[7], t);
+      P[4] = P[4] - t;
+    }
+    if constexpr (LMAX >= 4) {
+      T t = a[2] * b[8];
+      P[4] = fma(T(-1.6329931618554523), t, P[4]);
+    }
+  }
+};
+template <> struct SymP<3, 3, -4> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    if constexpr (LMAX >= 4) {
+      T t = a[0] * b[4];
+      t = fma(a[2], b[6], t);
+      t = fma(a[4], b[0], t);
+      t = fma(a[6], b[2], t);
+      P[4] = T(-1.1832159566199238) * t;
+    }
+    if constexpr (LMAX >= 4) {
+      T t = a[1] * b[5];
+      t = fma(a[5], b[1], t);
+      P[4] = fma(T(1.5275252316519459), t, P[4]);
+    }
+  }
+};
+template <> struct SymP<3, 3, -3> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    if constexpr (LMAX >= 4) {
+      T t = a[0] * b[3];
+      t = fma(a[3], b[0], t);
+      P[4] = T(-2.0493901531919199) * t;
+    }
+    if constexpr (LMAX >= 4) {
+      T t = a[1] * b[4];
+      t = fma(a[2], b[5], t);
+      t = fma(a[4], b[1], t);
+      t = fma(a[5], b[2], t);
+      P[4] = fma(T(0.68313005106397406), t, P[4]);
+    }
+  }
+};
+template <> struct SymP<3, 3, -2> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    {
+      T t = a[0] * b[4];
+      t = fma(-a[2], b[6], t);
+      t = fma(a[4], b[0], t);
+      t = fma(-a[6], b[2], t);
+      P[2] = T(-0.49999999999999978) * t;
+      if constexpr (LMAX >= 4) P[4] = T(1.3416407864998749) * t;
+    }
+    {
+      T t = a[1] * b[3];
+      t = fma(a[3], b[1], t);
+      P[2] = P[2] - t;
+      if constexpr (LMAX >= 4) P[4] = fma(T(-0.44721359549995848), t, P[4]);
+    }
+    {
+      T t = a[2] * b[4];
+      t = fma(a[4], b[2], t);
+      P[2] = fma(T(0.77459666924148318), t, P[2]);
+      if constexpr (LMAX >= 4) P[4] = fma(T(1.1547005383792521), t, P[4]);
+    }
+  }
+};
+template <> struct SymP<3, 3, -1> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    {
+      T t = a[0] * b[5];
+      t = fma(-a[1], b[6], t);
+      t = fma(a[5], b[0], t);
+      t = fma(-a[6], b[1], t);
+      P[2] = T(0.79056941504209444) * t;
+      if constexpr (LMAX >= 4) P[4] = -t;
+    }
+    {
+      T t = a[1] * b[4];
+      t = fma(-a[2], b[5], t);
+      t = fma(a[4], b[1], t);
+      t = fma(-a[5], b[2], t);
+      P[2] = fma(T(0.6123724356957948), t, P[2]);
+      if constexpr (LMAX >= 4) P[4] = fma(T(1.0327955589886442), t, P[4]);
+    }
+    {
+      T t = a[2] * b[3];
+      t = fma(a[3], b[2], t);
+      P[2] = fma(T(0.31622776601683661), t, P[2]);
+      if constexpr (LMAX >= 4) P[4] = P[4] + t;
+    }
+  }
+};
+template <> struct SymP<3, 3, 0> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    {
+      T t = a[0] * b[0];
+      t = fma(a[6], b[6], t);
+      P[0] = t;
+      P[2] = T(-1.1180339887498947) * t;
+      if constexpr (LMAX >= 4) P[4] = T(0.77459666924148385) * t;
+    }
+    {
+      T t = a[1] * b[1];
+      t = fma(a[5], b[5], t);
+      P[0] = P[0] + t;
+      if constexpr (LMAX >= 4) P[4] = fma(T(-1.8073922282301289), t, P[4]);
+    }
+    {
+      T t = a[2] * b[2];
+      t = fma(a[4], b[4], t);
+      P[0] = P[0] + t;
+      P[2] = fma(T(0.67082039324993603), t, P[2]);
+      if constexpr (LMAX >= 4) P[4] = fma(T(0.25819888974715854), t, P[4]);
+    }
+    {
+      T t = a[3] * b[3];
+      P[0] = P[0] + t;
+      P[2] = fma(T(0.89442719099991652), t, P[2]);
+      if constexpr (LMAX >= 4) P[4] = fma(T(1.5491933384829684), t, P[4]);
+    }
+  }
+};
+template <> struct SymP<3, 3, 1> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    {
+      T t = a[0] * b[1];
+      t = fma(a[1], b[0], t);
+      t = fma(a[5], b[6], t);
+      t = fma(a[6], b[5], t);
+      P[2] = T(0.79056941504209499) * t;
+      if constexpr (LMAX >= 4) P[4] = -t;
+    }
+    {
+      T t = a[1] * b[2];
+      t = fma(a[2], b[1], t);
+      t = fma(a[4], b[5], t);
+      t = fma(a[5], b[4], t);
+      P[2] = fma(T(0.6123724356957948), t, P[2]);
+      if constexpr (LMAX >= 4) P[4] = fma(T(1.0327955589886442), t, P[4]);
+    }
+    {
+      T t = a[3] * b[4];
+      t = fma(a[4], b[3], t);
+      P[2] = fma(T(0.31622776601683644), t, P[2]);
+      if constexpr (LMAX >= 4) P[4] = P[4] + t;
+    }
+  }
+};
+template <> struct SymP<3, 3, 2> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    {
+      T t = a[0] * b[2];
+      t = fma(a[2], b[0], t);
+      t = fma(a[4], b[6], t);
+      t = fma(a[6], b[4], t);
+      P[2] = T(-0.49999999999999978) * t;
+      if constexpr (LMAX >= 4) P[4] = T(1.3416407864998747) * t;
+    }
+    {
+      T t = a[2] * b[2];
+      t = fma(-a[4], b[4], t);
+      P[2] = fma(T(-0.77459666924148352), t, P[2]);
+      if constexpr (LMAX >= 4) P[4] = fma(T(-1.154700538379251), t, P[4]);
+    }
+    {
+      T t = a[3] * b[5];
+      t = fma(a[5], b[3], t);
+      P[2] = P[2] - t;
+      if constexpr (LMAX >= 4) P[4] = fma(T(-0.44721359549995643), t, P[4]);
+    }
+  }
+};
+template <> struct SymP<3, 3, 3> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    if constexpr (LMAX >= 4) {
+      T t = a[1] * b[2];
+      t = fma(a[2], b[1], t);
+      t = fma(-a[4], b[5], t);
+      t = fma(-a[5], b[4], t);
+      P[4] = T(-0.68313005106397418) * t;
+    }
+    if constexpr (LMAX >= 4) {
+      T t = a[3] * b[6];
+      t = fma(a[6], b[3], t);
+      P[4] = fma(T(-2.0493901531919199), t, P[4]);
+    }
+  }
+};
+template <> struct SymP<3, 3, 4> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    if constexpr (LMAX >= 4) {
+      T t = a[0] * b[2];
+      t = fma(a[2], b[0], t);
+      t = fma(-a[4], b[6], t);
+      t = fma(-a[6], b[4], t);
+      P[4] = T(1.1832159566199223) * t;
+    }
+    if constexpr (LMAX >= 4) {
+      T t = a[1] * b[1];
+      t = fma(-a[5], b[5], t);
+      P[4] = fma(T(-1.5275252316519476), t, P[4]);
+    }
+  }
+};
+template <> struct SymP<3, 4, -3> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    {
+      T t = a[0] * b[4];
+      P[3] = T(0.77459666924148418) * t;
+    }
+    {
+      T t = a[1] * b[5];
+      t = fma(a[5], b[3], t);
+      P[3] = P[3] - t;
+    }
+    {
+      T t = a[2] * b[6];
+      t = fma(a[4], b[2], t);
+      P[3] = fma(T(1.3416407864998754), t, P[3]);
+    }
+    {
+      T t = a[2] * b[8];
+      t = fma(-a[4], b[0], t);
+      P[3] = fma(T(1.1832159566199236), t, P[3]);
+    }
+    {
+      T t = a[3] * b[1];
+      P[3] = fma(T(-2.0493901531919203), t, P[3]);
+    }
+  }
+};
+template <> struct SymP<3, 4, -2> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    {
+      T t = a[0] * b[5];
+      t = fma(-a[6], b[3], t);
+      P[3] = -t;
+    }
+    {
+      T t = a[1] * b[4];
+      P[3] = fma(T(-1.8073922282301291), t, P[3]);
+    }
+    {
+      T t = a[1] * b[8];
+      t = fma(-a[5], b[0], t);
+      P[3] = fma(T(-1.527525231651949), t, P[3]);
+    }
+    {
+      T t = a[2] * b[5];
+      t = fma(a[4], b[3], t);
+      P[3] = fma(T(1.0327955589886439), t, P[3]);
+    }
+    {
+      T t = a[2] * b[7];
+      t = fma(-a[4], b[1], t);
+      P[3] = fma(T(-0.68313005106397406), t, P[3]);
+    }
+    {
+      T t = a[3] * b[2];
+      P[3] = fma(T(-0.44721359549995854), t, P[3]);
+    }
+  }
+};
+template <> struct SymP<3, 4, -1> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    {
+      T t = a[0] * b[6];
+      t = fma(-a[6], b[2], t);
+      P[1] = T(-0.18898223650461382) * t;
+      P[3] = T(1.3416407864998749) * t;
+    }
+    {
+      T t = a[0] * b[8];
+      t = fma(-a[6], b[0], t);
+      P[1] = P[1] - t;
+      P[3] = fma(T(1.1832159566199234), t, P[3]);
+    }
+    {
+      T t = a[1] * b[5];
+      t = fma(-a[5], b[3], t);
+      P[1] = fma(T(-0.32732683535398882), t, P[1]);
+      P[3] = fma(T(1.0327955589886439), t, P[3]);
+    }
+    {
+      T t = a[1] * b[7];
+      t = fma(-a[5], b[1], t);
+      P[1] = fma(T(-0.86602540378443915), t, P[1]);
+      P[3] = fma(T(-0.68313005106397406), t, P[3]);
+    }
+    {
+      T t = a[2] * b[4];
+      P[1] = fma(T(-0.65465367070797809), t, P[1]);
+      P[3] = fma(T(0.25819888974715882), t, P[3]);
+    }
+    {
+      T t = a[2] * b[6];
+      t = fma(-a[4], b[2], t);
+      P[1] = fma(T(-0.73192505471140068), t, P[1]);
+      P[3] = fma(T(-1.1547005383792512), t, P[3]);
+    }
+    {
+      T t = a[3] * b[3];
+      P[1] = fma(T(0.84515425472851613), t, P[1]);
+      P[3] = P[3] + t;
+    }
+  }
+};
+template <> struct SymP<3, 4, 0> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    {
+      T t = a[0] * b[1];
+      t = fma(a[6], b[7], t);
+      P[1] = T(0.70710678118654802) * t;
+      P[3] = T(-2.0493901531919207) * t;
+    }
+    {
+      T t = a[1] * b[2];
+      t = fma(a[5], b[6], t);
+      P[1] = fma(T(0.92582009977255242), t, P[1]);
+      P[3] = fma(T(-0.44721359549995854), t, P[3]);
+    }
+    {
+      T t = a[2] * b[3];
+      t = fma(a[4], b[5], t);
+      P[1] = fma(T(1.0350983390135311), t, P[1]);
+      P[3] = P[3] + t;
+    }
+    {
+      T t = a[3] * b[4];
+      P[1] = fma(T(1.0690449676496989), t, P[1]);
+      P[3] = fma(T(1.5491933384829686), t, P[3]);
+    }
+  }
+};
+template <> struct SymP<3, 4, 1> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    {
+      T t = a[0] * b[0];
+      t = fma(a[6], b[8], t);
+      P[1] = t;
+      P[3] = T(-1.1832159566199243) * t;
+    }
+    {
+      T t = a[0] * b[2];
+      t = fma(a[6], b[6], t);
+      P[1] = fma(T(-0.1889822365046136), t, P[1]);
+      P[3] = fma(T(1.3416407864998745), t, P[3]);
+    }
+    {
+      T t = a[1] * b[1];
+      t = fma(a[5], b[7], t);
+      P[1] = fma(T(0.86602540378443915), t, P[1]);
+      P[3] = fma(T(0.68313005106397384), t, P[3]);
+    }
+    {
+      T t = a[1] * b[3];
+      t = fma(a[5], b[5], t);
+      P[1] = fma(T(-0.32732683535398882), t, P[1]);
+      P[3] = fma(T(1.0327955589886439), t, P[3]);
+    }
+    {
+      T t = a[2] * b[2];
+      t = fma(a[4], b[6], t);
+      P[1] = fma(T(0.73192505471140057), t, P[1]);
+      P[3] = fma(T(1.1547005383792517), t, P[3]);
+    }
+    {
+      T t = a[3] * b[5];
+      P[1] = fma(T(0.84515425472851613), t, P[1]);
+      P[3] = P[3] + t;
+    }
+    {
+      T t = a[4] * b[4];
+      P[1] = fma(T(-0.65465367070797809), t, P[1]);
+      P[3] = fma(T(0.25819888974715921), t, P[3]);
+    }
+  }
+};
+template <> struct SymP<3, 4, 2> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    {
+      T t = a[0] * b[3];
+      t = fma(a[6], b[5], t);
+      P[3] = -t;
+    }
+    {
+      T t = a[1] * b[0];
+      t = fma(a[5], b[8], t);
+      P[3] = fma(T(1.5275252316519459), t, P[3]);
+    }
+    {
+      T t = a[2] * b[1];
+      t = fma(a[4], b[7], t);
+      P[3] = fma(T(0.68313005106397429), t, P[3]);
+    }
+    {
+      T t = a[2] * b[3];
+      t = fma(-a[4], b[5], t);
+      P[3] = fma(T(-1.0327955589886453), t, P[3]);
+    }
+    {
+      T t = a[3] * b[6];
+      P[3] = fma(T(-0.44721359549995648), t, P[3]);
+    }
+    {
+      T t = a[5] * b[4];
+      P[3] = fma(T(-1.8073922282301278), t, P[3]);
+    }
+  }
+};
+template <> struct SymP<3, 4, 3> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    {
+      T t = a[1] * b[3];
+      t = fma(-a[5], b[5], t);
+      P[3] = t;
+    }
+    {
+      T t = a[2] * b[0];
+      t = fma(a[4], b[8], t);
+      P[3] = fma(T(-1.1832159566199241), t, P[3]);
+    }
+    {
+      T t = a[2] * b[2];
+      t = fma(-a[4], b[6], t);
+      P[3] = fma(T(-1.3416407864998747), t, P[3]);
+    }
+    {
+      T t = a[3] * b[7];
+      P[3] = fma(T(-2.0493901531919203), t, P[3]);
+    }
+    {
+      T t = a[6] * b[4];
+      P[3] = fma(T(0.77459666924148418), t, P[3]);
+    }
+  }
+};
+template <> struct SymP<4, 4, -4> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    if constexpr (LMAX >= 4) {
+      T t = a[0] * b[4];
+      t = fma(a[4], b[0], t);
+      P[4] = T(0.8944271909999173) * t;
+    }
+    if constexpr (LMAX >= 4) {
+      T t = a[1] * b[5];
+      t = fma(a[3], b[7], t);
+      t = fma(a[5], b[1], t);
+      t = fma(a[7], b[3], t);
+      P[4] = P[4] - t;
+    }
+    if constexpr (LMAX >= 4) {
+      T t = a[2] * b[6];
+      t = fma(a[6], b[2], t);
+      P[4] = fma(T(1.1338934190276815), t, P[4]);
+    }
+  }
+};
+template <> struct SymP<4, 4, -3> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    if constexpr (LMAX >= 4) {
+      T t = a[0] * b[5];
+      t = fma(-a[3], b[8], t);
+      t = fma(a[5], b[0], t);
+      t = fma(-a[8], b[3], t);
+      P[4] = -t;
+    }
+    if constexpr (LMAX >= 4) {
+      T t = a[1] * b[4];
+      t = fma(a[4], b[1], t);
+      P[4] = fma(T(-1.3416407864998741), t, P[4]);
+    }
+    if constexpr (LMAX >= 4) {
+      T t = a[2] * b[5];
+      t = fma(a[3], b[6], t);
+      t = fma(a[5], b[2], t);
+      t = fma(a[6], b[3], t);
+      P[4] = fma(T(0.37796447300922736), t, P[4]);
+    }
+  }
+};
+template <> struct SymP<4, 4, -2> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    {
+      T t = a[0] * b[6];
+      t = fma(-a[2], b[8], t);
+      t = fma(a[6], b[0], t);
+      t = fma(-a[8], b[2], t);
+      P[2] = T(-0.39440531887330799) * t;
+      if constexpr (LMAX >= 4) P[4] = T(1.1338934190276817) * t;
+    }
+    {
+      T t = a[1] * b[5];
+      t = fma(-a[3], b[7], t);
+      t = fma(a[5], b[1], t);
+      t = fma(-a[7], b[3], t);
+      P[2] = fma(T(-0.59160797830996159), t, P[2]);
+      if constexpr (LMAX >= 4) P[4] = fma(T(0.37796447300922675), t, P[4]);
+    }
+    {
+      T t = a[2] * b[4];
+      t = fma(a[4], b[2], t);
+      P[2] = P[2] - t;
+      if constexpr (LMAX >= 4) P[4] = fma(T(-0.7027642214999329), t, P[4]);
+    }
+    {
+      T t = a[3] * b[5];
+      t = fma(a[5], b[3], t);
+      P[2] = fma(T(0.74535599249992968), t, P[2]);
+      if constexpr (LMAX >= 4) P[4] = fma(T(0.85714285714285698), t, P[4]);
+    }
+  }
+};
+template <> struct SymP<4, 4, -1> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    {
+      T t = a[0] * b[7];
+      t = fma(-a[1], b[8], t);
+      t = fma(a[7], b[0], t);
+      t = fma(-a[8], b[1], t);
+      P[2] = T(0.73786478737262184) * t;
+      if constexpr (LMAX >= 4) P[4] = -t;
+    }
+    {
+      T t = a[1] * b[6];
+      t = fma(-a[2], b[7], t);
+      t = fma(a[6], b[1], t);
+      t = fma(-a[7], b[2], t);
+      P[2] = fma(T(0.69721668877839649), t, P[2]);
+      if constexpr (LMAX >= 4) P[4] = fma(T(0.37796447300922703), t, P[4]);
+    }
+    {
+      T t = a[2] * b[5];
+      t = fma(-a[3], b[6], t);
+      t = fma(a[5], b[2], t);
+      t = fma(-a[6], b[3], t);
+      P[2] = fma(T(0.47434164902525616), t, P[2]);
+      if constexpr (LMAX >= 4) P[4] = fma(T(0.85714285714285698), t, P[4]);
+    }
+    {
+      T t = a[3] * b[4];
+      t = fma(a[4], b[3], t);
+      P[2] = fma(T(0.23570226039551537), t, P[2]);
+      if constexpr (LMAX >= 4) P[4] = fma(T(0.57498890849994344), t, P[4]);
+    }
+  }
+};
+template <> struct SymP<4, 4, 0> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    {
+      T t = a[0] * b[0];
+      t = fma(a[8], b[8], t);
+      P[0] = t;
+      P[2] = T(-1.2049281521534192) * t;
+      if constexpr (LMAX >= 4) P[4] = T(0.89442719099991641) * t;
+    }
+    {
+      T t = a[1] * b[1];
+      t = fma(a[7], b[7], t);
+      P[0] = P[0] + t;
+      P[2] = fma(T(-0.30123203803835424), t, P[2]);
+      if constexpr (LMAX >= 4) P[4] = fma(T(-1.3416407864998734), t, P[4]);
+    }
+    {
+      T t = a[2] * b[2];
+      t = fma(a[6], b[6], t);
+      P[0] = P[0] + t;
+      P[2] = fma(T(0.34426518632954733), t, P[2]);
+      if constexpr (LMAX >= 4) P[4] = fma(T(-0.70276422149993201), t, P[4]);
+    }
+    {
+      T t = a[3] * b[3];
+      t = fma(a[5], b[5], t);
+      P[0] = P[0] + t;
+      P[2] = fma(T(0.73156352095028987), t, P[2]);
+      if constexpr (LMAX >= 4) P[4] = fma(T(0.57498890849994466), t, P[4]);
+    }
+    {
+      T t = a[4] * b[4];
+      P[0] = P[0] + t;
+      P[2] = fma(T(0.8606629658238717), t, P[2]);
+      if constexpr (LMAX >= 4) P[4] = fma(T(1.1499778169998935), t, P[4]);
+    }
+  }
+};
+template <> struct SymP<4, 4, 1> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    {
+      T t = a[0] * b[1];
+      t = fma(a[1], b[0], t);
+      t = fma(a[7], b[8], t);
+      t = fma(a[8], b[7], t);
+      P[2] = T(0.73786478737262184) * t;
+      if constexpr (LMAX >= 4) P[4] = -t;
+    }
+    {
+      T t = a[1] * b[2];
+      t = fma(a[2], b[1], t);
+      t = fma(a[6], b[7], t);
+      t = fma(a[7], b[6], t);
+      P[2] = fma(T(0.69721668877839682), t, P[2]);
+      if constexpr (LMAX >= 4) P[4] = fma(T(0.37796447300922692), t, P[4]);
+    }
+    {
+      T t = a[2] * b[3];
+      t = fma(a[3], b[2], t);
+      t = fma(a[5], b[6], t);
+      t = fma(a[6], b[5], t);
+      P[2] = fma(T(0.47434164902525616), t, P[2]);
+      if constexpr (LMAX >= 4) P[4] = fma(T(0.85714285714285698), t, P[4]);
+    }
+    {
+      T t = a[4] * b[5];
+      t = fma(a[5], b[4], t);
+      P[2] = fma(T(0.23570226039551523), t, P[2]);
+      if constexpr (LMAX >= 4) P[4] = fma(T(0.57498890849994322), t, P[4]);
+    }
+  }
+};
+template <> struct SymP<4, 4, 2> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    {
+      T t = a[0] * b[2];
+      t = fma(a[2], b[0], t);
+      t = fma(a[6], b[8], t);
+      t = fma(a[8], b[6], t);
+      P[2] = T(-0.39440531887330799) * t;
+      if constexpr (LMAX >= 4) P[4] = T(1.1338934190276815) * t;
+    }
+    {
+      T t = a[1] * b[3];
+      t = fma(a[3], b[1], t);
+      t = fma(a[5], b[7], t);
+      t = fma(a[7], b[5], t);
+      P[2] = fma(T(-0.59160797830996137), t, P[2]);
+      if constexpr (LMAX >= 4) P[4] = fma(T(0.37796447300922675), t, P[4]);
+    }
+    {
+      T t = a[3] * b[3];
+      t = fma(-a[5], b[5], t);
+      P[2] = fma(T(-0.74535599249992979), t, P[2]);
+      if constexpr (LMAX >= 4) P[4] = fma(T(-0.85714285714285932), t, P[4]);
+    }
+    {
+      T t = a[4] * b[6];
+      t = fma(a[6], b[4], t);
+      P[2] = P[2] - t;
+      if constexpr (LMAX >= 4) P[4] = fma(T(-0.70276422149993145), t, P[4]);
+    }
+  }
+};
+template <> struct SymP<4, 4, 3> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    if constexpr (LMAX >= 4) {
+      T t = a[0] * b[3];
+      t = fma(a[3], b[0], t);
+      t = fma(a[5], b[8], t);
+      t = fma(a[8], b[5], t);
+      P[4] = -t;
+    }
+    if constexpr (LMAX >= 4) {
+      T t = a[2] * b[3];
+      t = fma(a[3], b[2], t);
+      t = fma(-a[5], b[6], t);
+      t = fma(-a[6], b[5], t);
+      P[4] = fma(T(-0.37796447300922698), t, P[4]);
+    }
+    if constexpr (LMAX >= 4) {
+      T t = a[4] * b[7];
+      t = fma(a[7], b[4], t);
+      P[4] = fma(T(-1.3416407864998743), t, P[4]);
+    }
+  }
+};
+template <> struct SymP<4, 4, 4> {
+  template <int LMAX, class T>
+  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {
+    if constexpr (LMAX >= 4) {
+      T t = a[1] * b[3];
+      t = fma(a[3], b[1], t);
+      t = fma(-a[5], b[7], t);
+      t = fma(-a[7], b[5], t);
+      P[4] = t;
+    }
+    if constexpr (LMAX >= 4) {
+      T t = a[2] * b[2];
+      t = fma(-a[6], b[6], t);
+      P[4] = fma(T(-1.1338934190276817), t, P[4]);
+    }
+    if constexpr (LMAX >= 4) {
+      T t = a[4] * b[8];
+      t = fma(a[8], b[4], t);
+      P[4] = fma(T(0.8944271909999143), t, P[4]);
+    }
   }
 };
 }  // namespace apx

@@ -32,8 +32,8 @@
 #include <type_traits>
 #include <utility>
 
+#include "ace_coupling_gen.h"
 #include "ace_sym.h"
-#include "ace_sym_gen.h"
 #include "device_util.h"
 
 namespace apx {
@@ -47,7 +47,9 @@ constexpr int kSymMaxSplit = 8;             // blocks that share a tile's pairs
 
 template <class T>
 struct SymArgs {
-  T* A;            // [tile * TA + atom][stride]: atomic base in, projected adjoint out
+  const T* A;      // [tile * TA + atom][stride] atomic base
+  T* B;            // the same rows: projected adjoint (may be A: a tile is read before it is written)
+  T* slope;        // [atom] F_eps'(phi2), or null
   const T* Wp;
   const T* coef;   // rows of C, see SymTables
   const T* b1;     // [n_max][2]
@@ -494,6 +496,7 @@ struct SymProg {
         const int q = slab_tile * TA + lane;  // slab_tile: the tile itself
         const double root = sqrt(fabs(e1[1]) + g.eps * g.eps), f2 = root - g.eps;
         fps[lane] = T(0.5 / root);
+        if (g.slope && q < g.n_act) g.slope[q] = T(0.5 / root);
         if (q < g.n_act) g.e_site[g.active[q]] = e1[0] + (e1[1] < 0.0 ? -f2 : f2) + g.e_anch[q];
       } else {
 #pragma unroll
@@ -596,7 +599,7 @@ __global__ void __launch_bounds__(kSymWaves * 64, 4) k_ace_sym(SymArgs<T> g) {
   const int tile = g.tile0 + blockIdx.x;
   const int t = tid & (TA - 1), ch = tid / TA;
   const int q = tile * TA + t;
-  T* row = g.A + (size_t)q * g.stride;
+  const T* row = g.A + (size_t)q * g.stride;
   if constexpr (FUSED) stage_mixing<T, LMAX, NMAX>(g.Wp, K, ws);
   // 16 bytes of one atom's row per lane, lanes over atoms: the LDS stores are conflict-free,
   // and a row's cache lines are used up by the next loads
@@ -636,7 +639,7 @@ __global__ void __launch_bounds__(kSymWaves * 64, 4) k_ace_sym(SymArgs<T> g) {
         const int lm = (o + k) / K, kk = o + k - lm * K;
         v[k] = o + k < na ? As[(kk * LM + lm) * TA + t] : T(0);
       }
-      if (q < g.n_act) *reinterpret_cast<vec*>(row + o) = v;
+      if (q < g.n_act) *reinterpret_cast<vec*>(g.B + (size_t)q * g.stride + o) = v;
     }
   }
 }
@@ -677,6 +680,7 @@ __global__ void __launch_bounds__(kFinThreads) k_ace_sym_finish(SymArgs<T> g) {
   }
   const double root = sqrt(fabs(phi[1]) + g.eps * g.eps), f2 = root - g.eps;
   const T fp = T(0.5 / root);
+  if (lm == 0 && g.slope && q < g.n_act) g.slope[q] = fp;
   if (lm == 0 && q < g.n_act) g.e_site[g.active[q]] = phi[0] + (phi[1] < 0.0 ? -f2 : f2) + g.e_anch[q];
   __syncthreads();
   if (lm < LM) {
@@ -693,7 +697,7 @@ __global__ void __launch_bounds__(kFinThreads) k_ace_sym_finish(SymArgs<T> g) {
   constexpr int V = 16 / (int)sizeof(T);
   const int left = g.n_act - q0;
   const int total = (left < NA ? left : NA) * g.stride;
-  vec* out = reinterpret_cast<vec*>(g.A + (size_t)q0 * g.stride);
+  vec* out = reinterpret_cast<vec*>(g.B + (size_t)q0 * g.stride);
   for (int o = threadIdx.x; o * V < total; o += kFinThreads) out[o] = reinterpret_cast<const vec*>(rows)[o];
 }
 
@@ -725,14 +729,16 @@ SymPlan<T> sym_plan(const apx_ace_model* m, int n_act) {
 }
 
 template <class T, int LMAX, int NMAX>
-apx_status sym_launch(apx_ctx* ctx, const apx_ace_model* m, T* A, int n_act, const double* e_anch, const int* active,
-                      double* e_site, void* scratch) {
+apx_status sym_launch(apx_ctx* ctx, const apx_ace_model* m, const T* A, T* B, T* slope, int n_act,
+                      const double* e_anch, const int* active, double* e_site, void* scratch) {
   using Acc = SymAcc<T, NMAX>;
   constexpr int TA = Acc::TA;
   const SymTables<T>& tb = sym_tables<T>(m);
   const SymPlan<T> pl = sym_plan<T>(m, n_act);
   SymArgs<T> g;
   g.A = A;
+  g.B = B;
+  g.slope = slope;
   g.coef = tb.coef;
   g.b1 = tb.b1;
   g.pairs = tb.pairs;
@@ -776,11 +782,12 @@ size_t sym_scratch(const apx_ace_model* m, int n_act) {
 }
 
 template <class T>
-apx_status sym_products(apx_ctx* ctx, const apx_ace_model* m, T* A, int n_act, const double* e_anch,
-                        const int* active, double* e_site, void* scratch) {
+apx_status sym_products(apx_ctx* ctx, const apx_ace_model* m, const T* A, T* B, T* slope, int n_act,
+                        const double* e_anch, const int* active, double* e_site, void* scratch) {
   const int nm = sym_nmax(m->n_max);
 #define APX_SYM_CASE(LM_, NM_) \
-  if (m->l_max == LM_ && nm == NM_) return sym_launch<T, LM_, NM_>(ctx, m, A, n_act, e_anch, active, e_site, scratch);
+  if (m->l_max == LM_ && nm == NM_)                                                                      \
+    return sym_launch<T, LM_, NM_>(ctx, m, A, B, slope, n_act, e_anch, active, e_site, scratch);
   APX_SYM_CASE(3, 8)
   APX_SYM_CASE(3, 10)
   APX_SYM_CASE(3, 12)
@@ -792,10 +799,10 @@ apx_status sym_products(apx_ctx* ctx, const apx_ace_model* m, T* A, int n_act, c
 }
 
 template size_t sym_scratch<float>(const apx_ace_model*, int);
-template apx_status sym_products<float>(apx_ctx*, const apx_ace_model*, float*, int, const double*, const int*,
-                                        double*, void*);
 template size_t sym_scratch<double>(const apx_ace_model*, int);
-template apx_status sym_products<double>(apx_ctx*, const apx_ace_model*, double*, int, const double*, const int*,
-                                         double*, void*);
+template apx_status sym_products<float>(apx_ctx*, const apx_ace_model*, const float*, float*, float*, int,
+                                        const double*, const int*, double*, void*);
+template apx_status sym_products<double>(apx_ctx*, const apx_ace_model*, const double*, double*, double*, int,
+                                         const double*, const int*, double*, void*);
 
 }  // namespace apx

@@ -12,20 +12,22 @@ exactly by expanding the product into monomials and integrating each with
     integral x^a y^b z^c dOmega = 2 G((a+1)/2) G((b+1)/2) G((c+1)/2) / G((a+b+c+3)/2)
 for even a, b, c (zero otherwise), G the gamma function.
 
-For every l_max in {3, 4} and every ordered pair (l1, l2) the generator writes a
-struct with
-    fwd(a, b, P):          P[L*L+L+M] += sum G a[m1] b[m2]        (allowed L <= l_max)
-    bwd(a, b, Pb, ga, gb): ga[m1] += sum G Pb[LM] b[m2];  gb[m2] += sum G Pb[LM] a[m1]
-with m indices offset by l (index l + m), and for every coupled degree L the same two
-functions restricted to that L (Couple3, with P indexed by M + L).  Run: python gen_coupling.py  (writes the
-header next to this file).
+For degrees l1 <= l2 and a component M the generated function forms, for every coupled degree
+L <= l_max (l1 + l2 + L even, L >= |M|), the scaled product
+    P[L] = (1 / s(l1, l2, L)) sum_{m1 m2} G(l1 l2 L; m1 m2 M) a[m1] b[m2]
+(m indices offset by l).  Products whose coefficients agree up to a sign in every L are summed
+first (a product of real harmonics meets M = |m1 + m2| and M = |m1 - m2| in two or four such
+products), and each sum enters the degrees by one multiply-add.  The scale s(l1, l2, L), the
+coefficient most of these sums share, is folded into the tabulated expansion coefficients
+(kSymScale), which saves their multiplication.  kGauntTerms[l1][l2][L] counts the nonzero
+coefficients.  Run: python gen_coupling.py (writes the header next to this file).
 """
 
 from __future__ import annotations
 
 import math
 import os
-from collections import defaultdict
+from collections import Counter, defaultdict
 
 LMAX_ALL = 4
 
@@ -101,64 +103,106 @@ def gaunt_table(lmax):
     return G
 
 
-def emit(lmax_list=(3, 4)):
+def sums_of(G, l1, l2, M):
+    """[(signed products [(m1, m2, sign)], {L: coefficient})] of component M."""
+    vec = {}
+    for (a, m1, b, m2, L, MM), v in G.items():
+        if a == l1 and b == l2 and MM == M:
+            vec.setdefault((m1, m2), {})[L] = v
+    out = []
+    for (m1, m2), c in sorted(vec.items()):
+        for prods, c0 in out:
+            if c0.keys() != c.keys():
+                continue
+            for sg in (1, -1):
+                if all(abs(c[L] - sg * c0[L]) < 1e-13 for L in c):
+                    prods.append((m1, m2, sg))
+                    break
+            else:
+                continue
+            break
+        else:
+            out.append(([(m1, m2, 1)], c))
+    return out
+
+
+def emit():
     G = gaunt_table(LMAX_ALL)
+    n = LMAX_ALL + 1
+    scale = [[[1.0] * n for _ in range(n)] for _ in range(n)]
+    for l1 in range(n):
+        for l2 in range(l1, n):
+            votes = {}
+            for M in range(-LMAX_ALL, LMAX_ALL + 1):
+                for prods, c in sums_of(G, l1, l2, M):
+                    for L, v in c.items():
+                        votes.setdefault(L, Counter())[round(abs(v), 12)] += 1
+            for L, cnt in votes.items():
+                scale[l1][l2][L] = max(cnt.items(), key=lambda kv: (kv[1], kv[0]))[0]
+    # the exact value behind each rounded vote
+    for l1 in range(n):
+        for l2 in range(l1, n):
+            for L in range(n):
+                for (a, m1, b, m2, LL, M), v in G.items():
+                    if a == l1 and b == l2 and LL == L and abs(abs(v) - scale[l1][l2][L]) < 1e-11:
+                        scale[l1][l2][L] = abs(v)
+                        break
     lines = [
-        "// Generated by gen_coupling.py -- do not edit.  Real Gaunt coupling of two",
-        "// spherical-harmonic blocks, unrolled for each (l_max, l1, l2).",
+        "// Generated by gen_coupling.py -- do not edit.  Real Gaunt coupling of two harmonic blocks",
+        "// (degrees l1 <= l2), one component M at a time, scaled by 1 / kSymScale[l1][l2][L].",
         "#pragma once",
         "#include <hip/hip_runtime.h>",
         "namespace apx {",
-        "template <int LMAX, int L1, int L2> struct Couple;",
+        f"constexpr double kSymScale[{n}][{n}][{n}] = {{",
     ]
-    for lmax in lmax_list:
-        for l1 in range(lmax + 1):
-            for l2 in range(lmax + 1):
-                ent = [(k, v) for k, v in G.items() if k[0] == l1 and k[2] == l2 and k[4] <= lmax]
-                ent.sort(key=lambda kv: (kv[0][4], kv[0][5], kv[0][1], kv[0][3]))
-                mask = 0
-                for (a, m1, b, m2, L, M), v in ent:
-                    mask |= 1 << L
-                lines.append(f"template <> struct Couple<{lmax}, {l1}, {l2}> {{")
-                lines.append(f"  static constexpr int kMask = {mask};")
-                lines.append(f"  static constexpr int kTerms = {len(ent)};")
-                lines.append("  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {")
-                for (a_, m1, b_, m2, L, M), v in ent:
-                    lines.append(f"    P[{L * L + L + M}] += T({v:.17g}) * (a[{m1 + l1}] * b[{m2 + l2}]);")
-                lines.append("  }")
-                lines.append("  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {")
-                for (a_, m1, b_, m2, L, M), v in ent:
-                    k = L * L + L + M
-                    lines.append(f"    {{ const T t = T({v:.17g}) * Pb[{k}]; ga[{m1 + l1}] += t * b[{m2 + l2}]; gb[{m2 + l2}] += t * a[{m1 + l1}]; }}")
+    for l1 in range(n):
+        lines.append("    {" + ", ".join("{" + ", ".join(f"{x:.17g}" for x in scale[l1][l2]) + "}" for l2 in range(n)) + "},")
+    lines.append("};")
+    lines.append(f"constexpr int kGauntTerms[{n}][{n}][{n}] = {{")
+    for l1 in range(n):
+        cnt = [[sum(1 for k in G if k[0] == l1 and k[2] == l2 and k[4] == L) for L in range(n)] for l2 in range(n)]
+        lines.append("    {" + ", ".join("{" + ", ".join(str(x) for x in c) + "}" for c in cnt) + "},")
+    lines.append("};")
+    lines.append("template <int L1, int L2, int M> struct SymP;")
+    for l1 in range(n):
+        for l2 in range(l1, n):
+            for M in range(-LMAX_ALL, LMAX_ALL + 1):
+                sums = sums_of(G, l1, l2, M)
+                if not sums:
+                    continue
+                degs = sorted({L for _, c in sums for L in c})
+                lines.append(f"template <> struct SymP<{l1}, {l2}, {M}> {{")
+                lines.append("  template <int LMAX, class T>")
+                lines.append("  __device__ __forceinline__ static void p(const T* a, const T* b, T* P) {")
+                started = set()
+                for prods, c in sums:
+                    if min(c) > 3:
+                        lines.append("    if constexpr (LMAX >= 4) {")
+                        ind = "      "
+                    else:
+                        lines.append("    {")
+                        ind = "      "
+                    m1, m2, _ = prods[0]
+                    lines.append(f"{ind}T t = a[{m1 + l1}] * b[{m2 + l2}];")
+                    for m1, m2, sg in prods[1:]:
+                        lines.append(f"{ind}t = fma({'-' if sg < 0 else ''}a[{m1 + l1}], b[{m2 + l2}], t);")
+                    for L in sorted(c):
+                        g = c[L] / scale[l1][l2][L]
+                        unit = abs(abs(g) - 1.0) < 1e-12
+                        guard = f"if constexpr (LMAX >= {L}) " if L > 3 and min(c) <= 3 else ""
+                        if unit:
+                            s = "" if g > 0 else "-"
+                            rhs = f"{s}t" if L not in started else (f"P[{L}] {'+' if g > 0 else '-'} t")
+                        else:
+                            rhs = f"T({g:.17g}) * t" if L not in started else f"fma(T({g:.17g}), t, P[{L}])"
+                        lines.append(f"{ind}{guard}P[{L}] = {rhs};")
+                        started.add(L)
+                    lines.append("    }")
                 lines.append("  }")
                 lines.append("};")
-    # per-degree parts: Couple3<LMAX, L1, L2, L> with P[M] (index M + L) and its adjoint
-    lines.append("template <int LMAX, int L1, int L2, int L> struct Couple3;")
-    for lmax in lmax_list:
-        for l1 in range(lmax + 1):
-            for l2 in range(lmax + 1):
-                for L in range(lmax + 1):
-                    ent = [(k, v) for k, v in G.items() if k[0] == l1 and k[2] == l2 and k[4] == L]
-                    if not ent:
-                        continue
-                    ent.sort(key=lambda kv: (kv[0][5], kv[0][1], kv[0][3]))
-                    lines.append(f"template <> struct Couple3<{lmax}, {l1}, {l2}, {L}> {{")
-                    lines.append(f"  static constexpr int kTerms = {len(ent)};")
-                    lines.append("  template <class T> __device__ __forceinline__ static void fwd(const T* a, const T* b, T* P) {")
-                    for (a_, m1, b_, m2, L_, M), v in ent:
-                        lines.append(f"    P[{M + L}] += T({v:.17g}) * (a[{m1 + l1}] * b[{m2 + l2}]);")
-                    lines.append("  }")
-                    lines.append("  template <class T> __device__ __forceinline__ static void bwd(const T* a, const T* b, const T* Pb, T* ga, T* gb) {")
-                    for (a_, m1, b_, m2, L_, M), v in ent:
-                        lines.append(f"    {{ const T t = T({v:.17g}) * Pb[{M + L}]; ga[{m1 + l1}] += t * b[{m2 + l2}]; gb[{m2 + l2}] += t * a[{m1 + l1}]; }}")
-                    lines.append("  }")
-                    lines.append("};")
+                assert started == set(degs)
     lines.append("}  // namespace apx")
     return "\n".join(lines) + "\n"
-
-
-def gaunt_nnz(lmax):
-    return {k: v for k, v in gaunt_table(lmax).items()}
 
 
 if __name__ == "__main__":

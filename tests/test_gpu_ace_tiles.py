@@ -76,3 +76,44 @@ def test_many_tiles_equal_few(env, precision):
     tol = TOL[precision]
     assert (one["e_site"] - e).abs().max().item() < tol
     assert (one["f"] - f).abs().max().item() < tol
+
+
+@pytest.mark.parametrize("n_max,l_max,n_act", [(1, 3, 1), (2, 4, 31), (8, 3, 32), (9, 4, 33), (11, 3, 65), (12, 4, 97)])
+def test_gradient_edges(env, n_max, l_max, n_act):
+    """Coefficient gradients at the edges of their chunks of 32 atoms and groups of 16 pairs:
+    float64 within 1e-10, float32 within 1e-5 of the largest component."""
+    ops, ctx, s, atoms, nl, i, j = env
+    print(f"[case] gradient n_max {n_max} l_max {l_max} n_act {n_act}", flush=True)
+    prm = synth.ace_random(n_max, l_max, oace.num_basis(n_max, l_max), seed=5)
+    rng = np.random.default_rng(n_act)
+    sites = np.sort(rng.choice(s.n, n_act, replace=False))
+    w = rng.uniform(0.1, 1.0, s.n)
+    model = ops.AceModel(ctx, prm)
+    act, wt = torch.as_tensor(sites.astype(np.int32), device="cuda"), torch.as_tensor(w, device="cuda")
+    o64 = ops.ace_energy_forces(ctx, atoms, nl, model, act, wt, "fp64", want_dc=True)
+    o32 = ops.ace_energy_forces(ctx, atoms, nl, model, act, wt, "fp32", want_dc=True)
+    plain = ops.ace_energy_forces(ctx, atoms, nl, model, act, wt, "fp64")
+    c1 = torch.tensor(prm.c1, requires_grad=True)
+    c2 = torch.tensor(prm.c2, requires_grad=True)
+    e = oace.site_energies(torch.as_tensor(s.pos), s.box, s.periodic, i, j, prm, s.n, sites, c1, c2)
+    for key, g in zip(("dE_dc1", "dE_dc2"), torch.autograd.grad((torch.as_tensor(w) * e).sum(), (c1, c2))):
+        g = g.numpy()
+        assert np.abs(o64[key].cpu().numpy() - g).max() < 1e-10, key
+        assert np.abs(o32[key].cpu().numpy() - g).max() < 1e-5 * np.abs(g).max(), key
+    assert (o64["e_site"] - plain["e_site"]).abs().max().item() < 1e-10
+    assert (o64["f"] - plain["f"]).abs().max().item() < 1e-10
+
+
+def test_gradient_of_many_chunks(env):
+    """9,000 atoms (more chunks than blocks, each block adds to its own sum) against parts."""
+    ops, ctx = env[0], env[1]
+    s = configs.bulk(14, seed=4, sigma=0.08)
+    atoms = ops.device_atoms(s)
+    nl = ops.build_neighbors(ctx, atoms, 5.5)
+    model = ops.AceModel(ctx, synth.ace_random(8, 3, oace.num_basis(8, 3), seed=5))
+    every = torch.arange(9000, dtype=torch.int32, device="cuda")
+    one = ops.ace_energy_forces(ctx, atoms, nl, model, every, None, "fp64", want_dc=True)
+    for key in ("dE_dc1", "dE_dc2"):
+        parts = sum(ops.ace_energy_forces(ctx, atoms, nl, model, p, None, "fp64", want_dc=True)[key]
+                    for p in every.split(700))
+        assert (one[key] - parts).abs().max().item() < 1e-12 * one[key].abs().max().item()
