@@ -8,6 +8,7 @@
 // |F_EAM|] and w0_extra = 1 - f_cut((yhat - tau_lo)/(tau_hi - tau_lo)) with
 // yhat = exp(prediction) - 1e-3.  Atoms whose features lie outside the training range get
 // w0_extra = 0, i.e. only the centro-symmetry criterion (the fallback).
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 
@@ -27,7 +28,6 @@ constexpr int kOffB3 = 8576;
 constexpr int kOffW4 = 8640;           // [64]
 constexpr int kOffB4 = 8704;
 constexpr int kNParams = 8705;
-constexpr int kSamples = 64;           // samples per training block
 constexpr float kCoordR2 = 3.08f * 3.08f;
 
 struct Std4 {
@@ -38,11 +38,10 @@ struct Std4 {
 
 struct apx_mlp {
   int device = 0;
-  apx::DevBuf buf;    // params, m, v, grad, loss, bf16 weights
+  apx::DevBuf buf;    // params, m, v, loss, bf16 weights
   float* params = nullptr;
   float* m = nullptr;
   float* v = nullptr;
-  float* grad = nullptr;
   float* loss = nullptr;
   unsigned short* wb = nullptr;  // bf16: W1 padded [64][16], W2 [64][64], W3 [64][64], W4 [64]
   bool wb_valid = false;
@@ -83,168 +82,246 @@ __global__ void __launch_bounds__(256) k_features(const double* __restrict__ pos
 }
 
 // ------------------------------------------------- float32 forward / backward
-// One block of 256 threads processes 64 samples; weights and activations live in LDS.
-// With BWD the block adds its share of the gradient of the mean squared error
-// (mean over `total` samples) to `grad` and its squared residuals to `loss`.
+// Sixteen samples per tile, four waves, on the float32 matrix cores (16x16x4): wave w owns the
+// sixteen neurons 16 w .. 16 w + 15 of every hidden layer.  The weights a wave multiplies with
+// stay in its registers over the block's tiles (forward: column = own neuron; backward: column =
+// own neuron of the layer below), the activations pass through LDS, and an accumulator's rows are
+// samples, so that a wave meets its own activations again in the backward pass.  The weight
+// gradients are products delta^T H over the samples, accumulated in registers over the tiles;
+// every block writes its own sums (no atomics) and k_mlp_sum adds them in a fixed order.
+// Latency-bound (a chain of six small products a tile); at a batch of 4,096 the pass that read
+// both factors of every multiply-add from LDS took 59 us on 64 blocks and needed its outputs
+// cleared (9 us); this one 17 us on 256 blocks, the sum 4 us.
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+constexpr int kTile = 16;                 // samples
+constexpr int kActLd = kH + 4;            // activation rows in LDS: sixteen samples x four k on distinct banks
+constexpr int kPassBlocks = 256;          // blocks of a gradient pass
+constexpr int kSlabLd = kNParams + 7;     // a block's sums: the parameters, then the loss
+
+__device__ __forceinline__ f32x4 mma(float a, float b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+
+// sum over k of act[sample][k] * w[k][neuron], w as operands of sixteen steps
+__device__ __forceinline__ f32x4 layer(const float* act, const float (&w)[16], int lane) {
+  f32x4 c0 = {0.f, 0.f, 0.f, 0.f}, c1 = c0;
+  const float* a = act + (lane & 15) * kActLd + (lane >> 4);
+#pragma unroll
+  for (int st = 0; st < 16; st += 2) {
+    c0 = mma(a[4 * st], w[st], c0);
+    c1 = mma(a[4 * st + 4], w[st + 1], c1);
+  }
+  return c0 + c1;
+}
+
+// The wave's rows j of delta^T H: column tile kt holds k = 16 kt + lane % 16.
+__device__ __forceinline__ void outer(const float* delta, const float* act, int wv, int lane, f32x4 (&g)[4],
+                                      float& bias) {
+  const int r = lane >> 4, c = lane & 15;
+#pragma unroll
+  for (int st = 0; st < 4; ++st) {
+    const int s = 4 * st + r;
+    const float d = delta[s * kActLd + 16 * wv + c];
+    bias += d;
+#pragma unroll
+    for (int kt = 0; kt < 4; ++kt) g[kt] = mma(d, act[s * kActLd + 16 * kt + c], g[kt]);
+  }
+}
+
+// With BWD the block writes its share of the gradient of the mean squared error (mean over
+// `total` samples) and of the error to its row of `slab`; otherwise the outputs to `out`.
 template <bool BWD>
 __global__ void __launch_bounds__(256) k_mlp_pass(const float* __restrict__ feat, const float* __restrict__ target,
                                                   const int* __restrict__ sel, int nb, int total,
-                                                  const float* __restrict__ P, Std4 st, float* __restrict__ grad,
-                                                  float* __restrict__ loss, float* __restrict__ out) {
-  __shared__ float W[kNParams];
-  __shared__ float X[kSamples][kIn];
-  __shared__ float H1[kSamples][kH + 1], H2[kSamples][kH + 1], H3[kSamples][kH + 1];
-  __shared__ float dY[kSamples];
-  const int tid = threadIdx.x;
-  const int s0 = blockIdx.x * kSamples;
-  for (int e = tid; e < kNParams; e += 256) W[e] = P[e];
-  {
-    const int s = tid >> 2, c = tid & 3;
-    const int g = s0 + s;
-    float x = 0.f;
-    if (g < nb) {
-      const int id = sel ? sel[g] : g;
-      x = (feat[4 * (size_t)id + c] - st.mu[c]) / st.sd[c];
-    }
-    X[s][c] = x;
-  }
-  __syncthreads();
-  for (int o = tid; o < kSamples * kH; o += 256) {
-    const int s = o / kH, j = o % kH;
-    float z = W[kOffB1 + j];
+                                                  const float* __restrict__ P, Std4 st, float* __restrict__ slab,
+                                                  float* __restrict__ out) {
+  constexpr int NB = BWD ? 5 : 2;
+  __shared__ float X[kTile][8];
+  __shared__ float buf[NB][kTile * kActLd];  // H1, H2, delta3, delta2, delta1
+  __shared__ float ypart[4][kTile], dY[kTile];
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int r = lane >> 4, c = lane & 15, j = 16 * wv + c;
+  float *H1 = buf[0], *H2 = buf[1];
+  float w2[16], w3[16], v2[16], v3[16];  // forward and backward operands of layers 2 and 3
 #pragma unroll
-    for (int k = 0; k < kIn; ++k) z = fmaf(W[kOffW1 + j * kIn + k], X[s][k], z);
-    H1[s][j] = tanhf(z);
+  for (int q = 0; q < 16; ++q) {
+    const int k = 4 * q + r;
+    w2[q] = P[kOffW2 + j * kH + k];
+    w3[q] = P[kOffW3 + j * kH + k];
+    if constexpr (BWD) {
+      v2[q] = P[kOffW2 + k * kH + j];
+      v3[q] = P[kOffW3 + k * kH + j];
+    }
   }
-  __syncthreads();
-  for (int o = tid; o < kSamples * kH; o += 256) {
-    const int s = o / kH, j = o % kH;
-    float z = W[kOffB2 + j];
-    for (int k = 0; k < kH; ++k) z = fmaf(W[kOffW2 + j * kH + k], H1[s][k], z);
-    H2[s][j] = tanhf(z);
-  }
-  __syncthreads();
-  for (int o = tid; o < kSamples * kH; o += 256) {
-    const int s = o / kH, j = o % kH;
-    float z = W[kOffB3 + j];
-    for (int k = 0; k < kH; ++k) z = fmaf(W[kOffW3 + j * kH + k], H2[s][k], z);
-    H3[s][j] = tanhf(z);
-  }
-  __syncthreads();
-  if (tid < kSamples) {
-    const int g = s0 + tid;
-    float y = W[kOffB4];
-    for (int k = 0; k < kH; ++k) y = fmaf(W[kOffW4 + k], H3[tid][k], y);
-    float d = 0.f, r2 = 0.f;
-    if (g < nb) {
-      if (out) out[g] = y;
-      if (BWD) {
-        const int id = sel ? sel[g] : g;
-        const float r = y - target[id];
-        d = 2.f * r / (float)total;
-        r2 = r * r;
+  const float w1 = P[kOffW1 + j * kIn + r], w4 = P[kOffW4 + j];
+  const float b1 = P[kOffB1 + j], b2 = P[kOffB2 + j], b3 = P[kOffB3 + j], b4 = P[kOffB4];
+  f32x4 g2[4], g3[4], g1 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int kt = 0; kt < 4; ++kt) g2[kt] = g3[kt] = g1;
+  float gb1 = 0.f, gb2 = 0.f, gb3 = 0.f, g4 = 0.f, gb4 = 0.f, err = 0.f;
+  const unsigned n = (unsigned)nb;  // (a stride beyond the last sample stays below 2^32)
+  for (unsigned s0 = blockIdx.x * kTile; s0 < n; s0 += gridDim.x * kTile) {
+    float y_target = 0.f;
+    if (tid < kTile * kIn) {
+      const int s = tid >> 2;
+      const unsigned g = s0 + s;
+      float x = 0.f;
+      if (g < n) {
+        const unsigned id = sel ? (unsigned)sel[g] : g;
+        x = (feat[4 * (size_t)id + (tid & 3)] - st.mu[tid & 3]) / st.sd[tid & 3];
+      }
+      X[s][tid & 3] = x;
+    }
+    if (BWD && tid < kTile && s0 + tid < n) y_target = target[sel ? (unsigned)sel[s0 + tid] : s0 + tid];
+    __syncthreads();
+    // rows of the accumulators: sample 4 r + q
+    f32x4 z = mma(X[c][r], w1, f32x4{b1, b1, b1, b1}), h1, h2, h3;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      h1[q] = tanhf(z[q]);
+      H1[(4 * r + q) * kActLd + j] = h1[q];
+    }
+    __syncthreads();
+    z = layer(H1, w2, lane);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      h2[q] = tanhf(z[q] + b2);
+      H2[(4 * r + q) * kActLd + j] = h2[q];
+    }
+    __syncthreads();
+    z = layer(H2, w3, lane);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      h3[q] = tanhf(z[q] + b3);
+      float y = w4 * h3[q];  // summed over the wave's neurons
+#pragma unroll
+      for (int off = 8; off > 0; off >>= 1) y += __shfl_xor(y, off, kWave);
+      if (c == 0) ypart[wv][4 * r + q] = y;
+    }
+    __syncthreads();
+    if (tid < kTile) {
+      const float y = b4 + ((ypart[0][tid] + ypart[1][tid]) + (ypart[2][tid] + ypart[3][tid]));
+      float d = 0.f;
+      if (s0 + tid < n) {
+        if (out) out[s0 + tid] = y;
+        if (BWD) {
+          const float e = y - y_target;
+          d = 2.f * e / (float)total;
+          err = fmaf(e, e, err);
+        }
+      }
+      dY[tid] = d;
+    }
+    if constexpr (BWD) {
+      float *D3 = buf[NB - 3], *D2 = buf[NB - 2], *D1 = buf[NB - 1];
+      __syncthreads();
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const float d = dY[4 * r + q];
+        g4 = fmaf(d, h3[q], g4);
+        D3[(4 * r + q) * kActLd + j] = d * w4 * (1.f - h3[q] * h3[q]);
+      }
+      if (tid < kTile) gb4 += dY[tid];
+      __syncthreads();
+      z = layer(D3, v3, lane);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) D2[(4 * r + q) * kActLd + j] = z[q] * (1.f - h2[q] * h2[q]);
+      outer(D3, H2, wv, lane, g3, gb3);
+      __syncthreads();
+      z = layer(D2, v2, lane);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) D1[(4 * r + q) * kActLd + j] = z[q] * (1.f - h1[q] * h1[q]);
+      outer(D2, H1, wv, lane, g2, gb2);
+      __syncthreads();
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int s = 4 * q + r;
+        const float d = D1[s * kActLd + j];
+        gb1 += d;
+        g1 = mma(d, c < kIn ? X[s][c] : 0.f, g1);
       }
     }
-    dY[tid] = d;
-    if (BWD) {
-      r2 = wave_sum(r2);
-      if (tid == 0) atomicAdd(loss, r2 / (float)total);
+    __syncthreads();
+  }
+  if constexpr (BWD) {
+    float* S = slab + (size_t)blockIdx.x * kSlabLd;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int row = 16 * wv + 4 * r + q;
+#pragma unroll
+      for (int kt = 0; kt < 4; ++kt) {
+        S[kOffW2 + row * kH + 16 * kt + c] = g2[kt][q];
+        S[kOffW3 + row * kH + 16 * kt + c] = g3[kt][q];
+      }
+      if (c < kIn) S[kOffW1 + row * kIn + c] = g1[q];
+    }
+    auto over_rows = [](float v) {
+      v += __shfl_xor(v, 16, kWave);
+      return v + __shfl_xor(v, 32, kWave);
+    };
+    gb1 = over_rows(gb1);
+    gb2 = over_rows(gb2);
+    gb3 = over_rows(gb3);
+    g4 = over_rows(g4);
+    if (r == 0) {
+      S[kOffB1 + j] = gb1;
+      S[kOffB2 + j] = gb2;
+      S[kOffB3 + j] = gb3;
+      S[kOffW4 + j] = g4;
+    }
+    if (wv == 0) {
+      gb4 = wave_sum(gb4);
+      err = wave_sum(err);
+      if (lane == 0) {
+        S[kOffB4] = gb4;
+        S[kNParams] = err;
+      }
     }
   }
-  if (!BWD) return;
+}
+
+struct AdamArgs {
+  float *p, *m, *v;
+  float lr, b1, b2, eps, c1, c2;
+};
+
+__device__ __forceinline__ void adam(const AdamArgs& a, int i, float gi) {
+  const float mi = a.b1 * a.m[i] + (1.f - a.b1) * gi;
+  const float vi = a.b2 * a.v[i] + (1.f - a.b2) * gi * gi;
+  a.m[i] = mi;
+  a.v[i] = vi;
+  const float mh = mi / a.c1, vh = vi / a.c2;
+  a.p[i] = a.p[i] - a.lr * mh / (sqrtf(vh) + a.eps);
+}
+
+// Sums the blocks' gradients (and the mean squared error, entry kNParams): 32 entries by 8 shares
+// of the blocks per block.  ADAM: the parameters are updated with the sum instead of storing it.
+template <bool ADAM>
+__global__ void __launch_bounds__(256) k_mlp_sum(const float* __restrict__ slab, int nblk, int total,
+                                                 float* __restrict__ grad, float* __restrict__ loss, AdamArgs a) {
+  __shared__ float sh[8][33];
+  const int col = threadIdx.x & 31, part = threadIdx.x >> 5;
+  const int i = blockIdx.x * 32 + col;
+  float v = 0.f;
+  if (i <= kNParams) {
+#pragma unroll 8
+    for (int b = part; b < nblk; b += 8) v += slab[(size_t)b * kSlabLd + i];
+  }
+  sh[part][col] = v;
   __syncthreads();
-  // output layer
-  if (tid < kH) {
-    float g = 0.f;
-    for (int s = 0; s < kSamples; ++s) g = fmaf(dY[s], H3[s][tid], g);
-    atomicAdd(&grad[kOffW4 + tid], g);
-  }
-  if (tid == kH) {
-    float g = 0.f;
-    for (int s = 0; s < kSamples; ++s) g += dY[s];
-    atomicAdd(&grad[kOffB4], g);
-  }
-  __syncthreads();
-  // delta3 in place of H3
-  for (int o = tid; o < kSamples * kH; o += 256) {
-    const int s = o / kH, j = o % kH;
-    const float h = H3[s][j];
-    H3[s][j] = dY[s] * W[kOffW4 + j] * (1.f - h * h);
-  }
-  __syncthreads();
-  for (int o = tid; o < kH * kH; o += 256) {
-    const int j = o / kH, k = o % kH;
-    float g = 0.f;
-    for (int s = 0; s < kSamples; ++s) g = fmaf(H3[s][j], H2[s][k], g);
-    atomicAdd(&grad[kOffW3 + o], g);
-  }
-  if (tid < kH) {
-    float g = 0.f;
-    for (int s = 0; s < kSamples; ++s) g += H3[s][tid];
-    atomicAdd(&grad[kOffB3 + tid], g);
-  }
-  __syncthreads();
-  // delta2 in place of H2
-  for (int o = tid; o < kSamples * kH; o += 256) {
-    const int s = o / kH, k = o % kH;
-    float a = 0.f;
-    for (int j = 0; j < kH; ++j) a = fmaf(H3[s][j], W[kOffW3 + j * kH + k], a);
-    const float h = H2[s][k];
-    H2[s][k] = a * (1.f - h * h);
-  }
-  __syncthreads();
-  for (int o = tid; o < kH * kH; o += 256) {
-    const int j = o / kH, k = o % kH;
-    float g = 0.f;
-    for (int s = 0; s < kSamples; ++s) g = fmaf(H2[s][j], H1[s][k], g);
-    atomicAdd(&grad[kOffW2 + o], g);
-  }
-  if (tid < kH) {
-    float g = 0.f;
-    for (int s = 0; s < kSamples; ++s) g += H2[s][tid];
-    atomicAdd(&grad[kOffB2 + tid], g);
-  }
-  __syncthreads();
-  // delta1 in place of H1
-  for (int o = tid; o < kSamples * kH; o += 256) {
-    const int s = o / kH, k = o % kH;
-    float a = 0.f;
-    for (int j = 0; j < kH; ++j) a = fmaf(H2[s][j], W[kOffW2 + j * kH + k], a);
-    const float h = H1[s][k];
-    H1[s][k] = a * (1.f - h * h);
-  }
-  __syncthreads();
-  {
-    const int j = tid >> 2, c = tid & 3;  // 256 = 64 x 4 weights of layer 1
-    float g = 0.f;
-    for (int s = 0; s < kSamples; ++s) g = fmaf(H1[s][j], X[s][c], g);
-    atomicAdd(&grad[kOffW1 + j * kIn + c], g);
-  }
-  if (tid < kH) {
-    float g = 0.f;
-    for (int s = 0; s < kSamples; ++s) g += H1[s][tid];
-    atomicAdd(&grad[kOffB1 + tid], g);
-  }
+  if (part != 0 || i > kNParams) return;
+  v = ((sh[0][col] + sh[1][col]) + (sh[2][col] + sh[3][col])) + ((sh[4][col] + sh[5][col]) + (sh[6][col] + sh[7][col]));
+  if (i == kNParams) *loss = v / (float)total;
+  else if (ADAM) adam(a, i, v);
+  else grad[i] = v;
 }
 
 // Adam with bias correction; clears the gradient for the next step.
-__global__ void k_adam(float* __restrict__ p, float* __restrict__ g, float* __restrict__ m, float* __restrict__ v,
-                       int np, float lr, float b1, float b2, float eps, float c1, float c2) {
+__global__ void k_adam(AdamArgs a, float* __restrict__ g, int np) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= np) return;
-  const float gi = g[i];
-  const float mi = b1 * m[i] + (1.f - b1) * gi;
-  const float vi = b2 * v[i] + (1.f - b2) * gi * gi;
-  m[i] = mi;
-  v[i] = vi;
-  const float mh = mi / c1, vh = vi / c2;
-  p[i] = p[i] - lr * mh / (sqrtf(vh) + eps);
+  adam(a, i, g[i]);
   g[i] = 0.f;
-}
-
-__global__ void k_zero_f(float* __restrict__ p, int m) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < m) p[i] = 0.f;
 }
 
 // --------------------------------------------------------- bfloat16 inference
@@ -480,7 +557,7 @@ apx_status apx_mlp_create(apx_ctx* ctx, const float* params, const float* mu, co
     if (!(sd[c] > 0.f)) return fail(ctx, APX_EINVAL, "standard deviations must be positive");
   apx_mlp* m = new apx_mlp();
   m->device = ctx->device;
-  const size_t nf = 4 * (size_t)kNParams + 64;
+  const size_t nf = 3 * (size_t)kNParams + 61;  // the bfloat16 weights behind on 16 bytes
   const size_t nwb = kH * 16 + 2 * kH * kH + kH;
   if (m->buf.ensure(nf * sizeof(float) + nwb * sizeof(unsigned short)) != hipSuccess) {
     delete m;
@@ -490,15 +567,14 @@ apx_status apx_mlp_create(apx_ctx* ctx, const float* params, const float* mu, co
   m->params = base;
   m->m = base + kNParams;
   m->v = base + 2 * kNParams;
-  m->grad = base + 3 * kNParams;
-  m->loss = base + 4 * kNParams;
+  m->loss = base + 3 * kNParams;
   m->wb = reinterpret_cast<unsigned short*>(base + nf);
   for (int c = 0; c < 4; ++c) {
     m->st.mu[c] = mu[c];
     m->st.sd[c] = sd[c];
   }
   if (hipMemcpy(m->params, params, kNParams * sizeof(float), hipMemcpyHostToDevice) != hipSuccess ||
-      hipMemset(m->m, 0, 3 * (size_t)kNParams * sizeof(float) + 64 * sizeof(float)) != hipSuccess) {
+      hipMemset(m->m, 0, (2 * (size_t)kNParams + 1) * sizeof(float)) != hipSuccess) {
     delete m;
     return fail(ctx, APX_EDEVICE, "MLP upload");
   }
@@ -550,22 +626,51 @@ apx_status apx_mlp_forward(apx_ctx* ctx, const apx_mlp* m, const float* feat, in
   if (n < 0 || n > 0x7fffffff) return fail(ctx, APX_EINVAL, "bad sample count");
   if (n == 0) return APX_OK;
   if (!feat || !out) return fail(ctx, APX_EINVAL, "feat and out are required");
-  k_mlp_pass<false><<<blocks_for(n, kSamples), 256, 0, ctx->stream>>>(feat, nullptr, nullptr, (int)n, (int)n,
-                                                                      m->params, m->st, nullptr, nullptr, out);
+  const int blocks = (int)std::min<int64_t>(8 * kPassBlocks, blocks_for(n, kTile));
+  k_mlp_pass<false><<<blocks, 256, 0, ctx->stream>>>(feat, nullptr, nullptr, (int)n, (int)n, m->params, m->st, nullptr,
+                                                     out);
   APX_LAUNCH_CHECK(ctx);
   return APX_OK;
 }
+
+}  // extern "C"
+
+namespace {
+
+// The gradient pass over the batch: one row of sums per block in the context's scratch.
+apx_status mlp_pass(apx_ctx* ctx, const apx_mlp* m, const float* feat, const float* target, const int32_t* sel,
+                    int64_t nb, int* nblk) {
+  *nblk = (int)std::min<int64_t>(kPassBlocks, blocks_for(nb, kTile));
+  APX_ALLOC(ctx, ctx->mlp_sums, sizeof(float) * (size_t)*nblk * kSlabLd);
+  ProfScope ps(ctx, "mlp.train");
+  k_mlp_pass<true><<<*nblk, 256, 0, ctx->stream>>>(feat, target, sel, (int)nb, (int)nb, m->params, m->st,
+                                                   ctx->mlp_sums.as<float>(), nullptr);
+  APX_LAUNCH_CHECK(ctx);
+  return APX_OK;
+}
+
+// The update of one step (the step counter already advanced).
+AdamArgs adam_args(apx_mlp* m, float lr, float beta1, float beta2, float eps) {
+  return AdamArgs{m->params, m->m,  m->v, lr, beta1, beta2, eps, 1.f - powf(beta1, (float)m->step),
+                  1.f - powf(beta2, (float)m->step)};
+}
+
+constexpr int kSumBlocks = (kNParams + 1 + 31) / 32;
+
+}  // namespace
+
+extern "C" {
 
 apx_status apx_mlp_gradients(apx_ctx* ctx, apx_mlp* m, const float* feat, const float* target, const int32_t* sel,
                              int64_t nb, float* grad, float* loss) {
   if (!ctx || !m) return APX_EINVAL;
   if (nb <= 0 || nb > 0x7fffffff) return fail(ctx, APX_EINVAL, "batch size must be positive");
   if (!feat || !target || !grad || !loss) return fail(ctx, APX_EINVAL, "feat, target, grad and loss are required");
-  k_zero_f<<<blocks_for(kNParams, 256), 256, 0, ctx->stream>>>(grad, kNParams);
-  k_zero_f<<<1, 64, 0, ctx->stream>>>(loss, 1);
-  ProfScope ps(ctx, "mlp.train");
-  k_mlp_pass<true><<<blocks_for(nb, kSamples), 256, 0, ctx->stream>>>(feat, target, sel, (int)nb, (int)nb,
-                                                                     m->params, m->st, grad, loss, nullptr);
+  int nblk = 0;
+  const apx_status s = mlp_pass(ctx, m, feat, target, sel, nb, &nblk);
+  if (s != APX_OK) return s;
+  k_mlp_sum<false><<<kSumBlocks, 256, 0, ctx->stream>>>(ctx->mlp_sums.as<float>(), nblk, (int)nb, grad, loss,
+                                                        AdamArgs{});
   APX_LAUNCH_CHECK(ctx);
   return APX_OK;
 }
@@ -574,9 +679,8 @@ apx_status apx_mlp_adam_step(apx_ctx* ctx, apx_mlp* m, const float* grad, float 
                              float eps) {
   if (!ctx || !m || !grad) return APX_EINVAL;
   m->step += 1;
-  const float c1 = 1.f - powf(beta1, (float)m->step), c2 = 1.f - powf(beta2, (float)m->step);
-  k_adam<<<blocks_for(kNParams, 256), 256, 0, ctx->stream>>>(m->params, const_cast<float*>(grad), m->m, m->v,
-                                                             kNParams, lr, beta1, beta2, eps, c1, c2);
+  k_adam<<<blocks_for(kNParams, 256), 256, 0, ctx->stream>>>(adam_args(m, lr, beta1, beta2, eps),
+                                                             const_cast<float*>(grad), kNParams);
   APX_LAUNCH_CHECK(ctx);
   m->wb_valid = false;
   return APX_OK;
@@ -587,15 +691,15 @@ apx_status apx_mlp_train_step(apx_ctx* ctx, apx_mlp* m, const float* feat, const
   if (!ctx || !m) return APX_EINVAL;
   if (nb <= 0 || nb > 0x7fffffff) return fail(ctx, APX_EINVAL, "batch size must be positive");
   if (!feat || !target) return fail(ctx, APX_EINVAL, "feat and target are required");
-  float* ls = loss ? loss : m->loss;
-  k_zero_f<<<1, 64, 0, ctx->stream>>>(ls, 1);
-  {
-    ProfScope ps(ctx, "mlp.train");
-    k_mlp_pass<true><<<blocks_for(nb, kSamples), 256, 0, ctx->stream>>>(feat, target, sel, (int)nb, (int)nb,
-                                                                       m->params, m->st, m->grad, ls, nullptr);
-    APX_LAUNCH_CHECK(ctx);
-  }
-  return apx_mlp_adam_step(ctx, m, m->grad, lr, 0.9f, 0.999f, 1e-8f);
+  int nblk = 0;
+  const apx_status s = mlp_pass(ctx, m, feat, target, sel, nb, &nblk);
+  if (s != APX_OK) return s;
+  m->step += 1;
+  k_mlp_sum<true><<<kSumBlocks, 256, 0, ctx->stream>>>(ctx->mlp_sums.as<float>(), nblk, (int)nb, nullptr,
+                                                       loss ? loss : m->loss, adam_args(m, lr, 0.9f, 0.999f, 1e-8f));
+  APX_LAUNCH_CHECK(ctx);
+  m->wb_valid = false;
+  return APX_OK;
 }
 
 apx_status apx_mlp_infer_bf16(apx_ctx* ctx, apx_mlp* m, const float* feat, int64_t n, float* out) {
