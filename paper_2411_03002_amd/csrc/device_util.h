@@ -21,6 +21,53 @@ __device__ __forceinline__ int xcd_block(int b, int nb) {
   return x * q + (x < r ? x : r) + k;
 }
 
+// Row-gather kernels (EAM passes, features) give a group of 64 atoms to W waves: wave w takes the
+// neighbour batches w, w + W, ... of every row (the loads of a wave stay coalesced), and the waves'
+// partial sums meet in LDS.  One wave per 64 atoms leaves the row's chain of dependent loads exposed
+// until the atoms alone fill the card several times over.
+constexpr int row_batch(int W) { return W >= 16 ? 4 : 8; }
+// Measured for W = 1 / 4 / 16 (us).  Rows of 54, closed form, density + force: 860 atoms 63 / 24 / 19,
+// 23,220 atoms 66 / 32 / 31, 42,395 atoms 69 / 40 / 43, 130,466 atoms 95 / 77 / 103, 2,038,519 atoms
+// 935 / 884 / 1,522; features the same way (30 / 26 / 27 at 130,466, 385 / 346 / 390 at 2,038,519).
+constexpr long long kRowWide = 24576;
+inline int row_waves(long long n) { return n <= kRowWide ? 16 : 4; }
+// Rows of 78, two-exponential form: 860 atoms 104 / 45 / 25, 87,402 atoms 155 / 117 / 115, 130,466
+// atoms 161 / 149 / 155, 254,815 atoms 258 / 258 / 287, 497,686 atoms 451 / 467 / 552.
+constexpr long long kRowWide2 = 98304, kRowMid2 = 262144;
+inline int row_waves2(long long n) { return n <= kRowWide2 ? 16 : (n <= kRowMid2 ? 4 : 1); }
+
+// The atom of a thread (W = 1: a thread per atom; W > 1: lane of the block's group) and its wave's
+// place among the W.
+template <int W>
+__device__ __forceinline__ int row_atom(int block) {
+  return W == 1 ? block * (int)blockDim.x + (int)threadIdx.x : block * kWave + (int)(threadIdx.x & (kWave - 1));
+}
+template <int W>
+__device__ __forceinline__ int row_wave() {
+  return W == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+}
+inline unsigned row_blocks(long long n, int W) { return blocks_for(n, W == 1 ? 256 : kWave); }
+inline unsigned row_threads(int W) { return W == 1 ? 256u : 64u * (unsigned)W; }
+
+// Sums the N partial values of the group's W waves into wave 0's (in wave order).
+template <int W, int N>
+__device__ __forceinline__ void row_reduce(double (&v)[N], int wv) {
+  if constexpr (W > 1) {
+    __shared__ double part[W - 1][N][kWave];
+    const int lane = threadIdx.x & (kWave - 1);
+    if (wv > 0) {
+#pragma unroll
+      for (int k = 0; k < N; ++k) part[wv - 1][k][lane] = v[k];
+    }
+    __syncthreads();
+    if (wv == 0) {
+      for (int w = 0; w < W - 1; ++w)
+#pragma unroll
+        for (int k = 0; k < N; ++k) v[k] += part[w][k][lane];
+    }
+  }
+}
+
 // Minimum image of d = x_j - x_i along one axis of length L (both coordinates in
 // [lo, hi)): d -= L if d >= L/2; d += L if d < -L/2.  (Written as branches: few pairs
 // wrap, and in the thread-per-atom gathers a branch no lane takes costs less than forming

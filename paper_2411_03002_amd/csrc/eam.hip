@@ -8,6 +8,7 @@
 // with r_ij = x_j - x_i.  Both passes gather over the full neighbour list (one thread per
 // atom, neighbour-major rows read coalesced), so no atomics are needed.
 #include <cmath>
+#include <type_traits>
 
 #include "common.h"
 #include "device_util.h"
@@ -78,27 +79,27 @@ __device__ __forceinline__ void eam2_embed(const EamDev& p, double x, double& F,
   F += p.f0;
 }
 
-// Neighbours are processed in batches of kBatch: the batch's indices and positions are
-// loaded first so that their memory accesses are in flight together, then the pairs are
+// Neighbours are processed in batches of kBatch, shared among W waves (see row_waves): the batch's
+// indices and positions are loaded first so that their memory accesses are in flight together, then the pairs are
 // summed in list order (the same order as one at a time).
-constexpr int kBatch = 8;
-
-template <int KIND>
-__global__ void __launch_bounds__(256) k_eam_density(const double* __restrict__ pos, int n, BoxDev b, EamDev p,
+template <int KIND, int W>
+__global__ void __launch_bounds__(W == 1 ? 256 : 64 * W)
+k_eam_density(const double* __restrict__ pos, int n, BoxDev b, EamDev p,
                                                      const int* __restrict__ count, const int* __restrict__ idx,
                                                      int max_nb, const double* __restrict__ w,
                                                      double* __restrict__ e_site, double* __restrict__ rho_out,
                                                      double2* __restrict__ uf, const double* __restrict__ wl,
                                                      double2* __restrict__ duf) {
+  constexpr int kBatch = row_batch(W);
   __shared__ double etab[32];
   stage_exp_table(etab);
-  const int i = xcd_block(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
-  if (i >= n) return;
+  const int row = row_atom<W>(xcd_block(blockIdx.x, gridDim.x)), wv = row_wave<W>();
+  const int i = row < n ? row : n - 1;  // (a thread beyond the last atom repeats it)
   const double xi = pos[i], yi = pos[(size_t)n + i], zi = pos[2 * (size_t)n + i];
   int cnt = count[i];
   if (cnt > max_nb) cnt = max_nb;
   double rho = 0.0, pair = 0.0;
-  for (int k0 = 0; k0 < cnt; k0 += kBatch) {
+  for (int k0 = wv * kBatch; k0 < cnt; k0 += W * kBatch) {
     int jb[kBatch];
     double px[kBatch], py[kBatch], pz[kBatch];
 #pragma unroll
@@ -131,6 +132,11 @@ __global__ void __launch_bounds__(256) k_eam_density(const double* __restrict__ 
       }
     }
   }
+  double sums[2] = {rho, pair};
+  row_reduce<W, 2>(sums, wv);
+  if (row >= n || wv > 0) return;
+  rho = sums[0];
+  pair = sums[1];
   double F, Fp;
   if constexpr (KIND == APX_EAM_CLOSED) {
     const double sq = sqrt(rho);
@@ -153,22 +159,24 @@ __global__ void __launch_bounds__(256) k_eam_density(const double* __restrict__ 
 
 // SKIPZERO: pairs whose two weights are both 0 contribute exactly 0 and are not evaluated
 // (the pass over weight differences, which are 0 almost everywhere).
-template <int KIND, bool SKIPZERO = false>
-__global__ void __launch_bounds__(256) k_eam_force(const double* __restrict__ pos, int n, BoxDev b, EamDev p,
+template <int KIND, int W, bool SKIPZERO>
+__global__ void __launch_bounds__(W == 1 ? 256 : 64 * W)
+k_eam_force(const double* __restrict__ pos, int n, BoxDev b, EamDev p,
                                                    const int* __restrict__ count, const int* __restrict__ idx,
                                                    int max_nb, const double2* __restrict__ uf,
                                                    double* __restrict__ f) {
+  constexpr int kBatch = row_batch(W);
   __shared__ double etab[32];
   stage_exp_table(etab);
-  const int i = xcd_block(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
-  if (i >= n) return;
+  const int row = row_atom<W>(xcd_block(blockIdx.x, gridDim.x)), wv = row_wave<W>();
+  const int i = row < n ? row : n - 1;
   const double xi = pos[i], yi = pos[(size_t)n + i], zi = pos[2 * (size_t)n + i];
   const double2 ufs = uf[i];
   const double ui = ufs.x, ufi = ufs.y;
   int cnt = count[i];
   if (cnt > max_nb) cnt = max_nb;
   double fx = 0.0, fy = 0.0, fz = 0.0;
-  for (int k0 = 0; k0 < cnt; k0 += kBatch) {
+  for (int k0 = wv * kBatch; k0 < cnt; k0 += W * kBatch) {
     int jb[kBatch];
     double px[kBatch], py[kBatch], pz[kBatch], uj[kBatch], fj[kBatch];
 #pragma unroll
@@ -213,9 +221,12 @@ __global__ void __launch_bounds__(256) k_eam_force(const double* __restrict__ po
       }
     }
   }
-  f[i] = fx;
-  f[(size_t)n + i] = fy;
-  f[2 * (size_t)n + i] = fz;
+  double sums[3] = {fx, fy, fz};
+  row_reduce<W, 3>(sums, wv);
+  if (row >= n || wv > 0) return;
+  f[i] = sums[0];
+  f[(size_t)n + i] = sums[1];
+  f[2 * (size_t)n + i] = sums[2];
 }
 
 apx_status eam_check(apx_ctx* ctx, const apx_atoms* atoms, const apx_nlist* nl, const apx_eam_params* p) {
@@ -262,35 +273,39 @@ apx_status eam_launch(apx_ctx* ctx, const apx_atoms* atoms, const apx_nlist* nl,
   EamDev d = eam_dev(p);
   double2* uf2 = reinterpret_cast<double2*>(uf);
   double2* duf2 = reinterpret_cast<double2*>(duf);
-  {
-  ProfScope ps(ctx, "eam.density");
-  if (p->kind == APX_EAM2)
-    k_eam_density<APX_EAM2><<<blocks_for(n, 256), 256, 0, ctx->stream>>>(atoms->pos, n, b, d, nl->count, nl->idx,
-                                                                         nl->max_nb, w, e_site, rho, uf2, wl, duf2);
-  else
-    k_eam_density<APX_EAM_CLOSED><<<blocks_for(n, 256), 256, 0, ctx->stream>>>(
-        atoms->pos, n, b, d, nl->count, nl->idx, nl->max_nb, w, e_site, rho, uf2, wl, duf2);
-  APX_LAUNCH_CHECK(ctx);
+  auto passes = [&](auto kind_c, auto w_c) -> apx_status {
+    constexpr int KIND = decltype(kind_c)::value, W = decltype(w_c)::value;
+    const unsigned nb = row_blocks(n, W), nt = row_threads(W);
+    {
+      ProfScope ps(ctx, "eam.density");
+      k_eam_density<KIND, W><<<nb, nt, 0, ctx->stream>>>(atoms->pos, n, b, d, nl->count, nl->idx, nl->max_nb, w,
+                                                         e_site, rho, uf2, wl, duf2);
+      APX_LAUNCH_CHECK(ctx);
+    }
+    {
+      ProfScope ps(ctx, "eam.force");
+      k_eam_force<KIND, W, false><<<nb, nt, 0, ctx->stream>>>(atoms->pos, n, b, d, nl->count, nl->idx, nl->max_nb,
+                                                              uf2, f);
+      APX_LAUNCH_CHECK(ctx);
+    }
+    if (df) {
+      ProfScope pd(ctx, "eam.force_delta");
+      k_eam_force<KIND, W, true><<<nb, nt, 0, ctx->stream>>>(atoms->pos, n, b, d, nl->count, nl->idx, nl->max_nb,
+                                                             duf2, df);
+      APX_LAUNCH_CHECK(ctx);
+    }
+    return APX_OK;
+  };
+  using Closed = std::integral_constant<int, APX_EAM_CLOSED>;
+  using Two = std::integral_constant<int, APX_EAM2>;
+  using W16 = std::integral_constant<int, 16>;
+  using W4 = std::integral_constant<int, 4>;
+  if (p->kind != APX_EAM2) return row_waves(n) == 16 ? passes(Closed{}, W16{}) : passes(Closed{}, W4{});
+  switch (row_waves2(n)) {
+    case 16: return passes(Two{}, W16{});
+    case 4: return passes(Two{}, W4{});
+    default: return passes(Two{}, std::integral_constant<int, 1>{});
   }
-  ProfScope ps(ctx, "eam.force");
-  if (p->kind == APX_EAM2)
-    k_eam_force<APX_EAM2><<<blocks_for(n, 256), 256, 0, ctx->stream>>>(atoms->pos, n, b, d, nl->count, nl->idx,
-                                                                       nl->max_nb, uf2, f);
-  else
-    k_eam_force<APX_EAM_CLOSED><<<blocks_for(n, 256), 256, 0, ctx->stream>>>(atoms->pos, n, b, d, nl->count,
-                                                                             nl->idx, nl->max_nb, uf2, f);
-  APX_LAUNCH_CHECK(ctx);
-  if (df) {
-    ProfScope pd(ctx, "eam.force_delta");
-    if (p->kind == APX_EAM2)
-      k_eam_force<APX_EAM2, true><<<blocks_for(n, 256), 256, 0, ctx->stream>>>(atoms->pos, n, b, d, nl->count,
-                                                                               nl->idx, nl->max_nb, duf2, df);
-    else
-      k_eam_force<APX_EAM_CLOSED, true><<<blocks_for(n, 256), 256, 0, ctx->stream>>>(
-          atoms->pos, n, b, d, nl->count, nl->idx, nl->max_nb, duf2, df);
-    APX_LAUNCH_CHECK(ctx);
-  }
-  return APX_OK;
 }
 
 apx_status eam_forces_dual(apx_ctx* ctx, const apx_atoms* atoms, const apx_nlist* nl, const apx_eam_params* p,

@@ -54,25 +54,43 @@ struct apx_mlp {
 namespace apx {
 
 // ----------------------------------------------------------------- features
-__global__ void __launch_bounds__(256) k_features(const double* __restrict__ pos, int n, BoxDev b,
+template <int W>
+__global__ void __launch_bounds__(64 * W) k_features(const double* __restrict__ pos, int n, BoxDev b,
                                                   const int* __restrict__ count, const int* __restrict__ idx,
                                                   int max_nb, const double* __restrict__ rho,
                                                   const double* __restrict__ csp, const double* __restrict__ f,
                                                   float* __restrict__ feat) {
-  const int i = xcd_block(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
-  if (i >= n) return;
+  constexpr int kBatch = row_batch(W);
+  const int row = row_atom<W>(xcd_block(blockIdx.x, gridDim.x)), wv = row_wave<W>();
+  const int i = row < n ? row : n - 1;  // (a thread beyond the last atom repeats it)
   const double xi = pos[i], yi = pos[(size_t)n + i], zi = pos[2 * (size_t)n + i];
   int cnt = count[i];
   if (cnt > max_nb) cnt = max_nb;
   const double rc2 = 3.08 * 3.08;
   int coord = 0;
-  for (int k = 0; k < cnt; ++k) {
-    const int j = idx[(size_t)k * n + i];
-    const double dx = min_image(pos[j] - xi, b.L[0], b.half[0], b.per[0]);
-    const double dy = min_image(pos[(size_t)n + j] - yi, b.L[1], b.half[1], b.per[1]);
-    const double dz = min_image(pos[2 * (size_t)n + j] - zi, b.L[2], b.half[2], b.per[2]);
-    if (sq_dist_exact(dx, dy, dz) < rc2) ++coord;
+  for (int k0 = wv * kBatch; k0 < cnt; k0 += W * kBatch) {
+    int jb[kBatch];
+    double px[kBatch], py[kBatch], pz[kBatch];
+#pragma unroll
+    for (int q = 0; q < kBatch; ++q) jb[q] = k0 + q < cnt ? idx[(size_t)(k0 + q) * n + i] : i;
+#pragma unroll
+    for (int q = 0; q < kBatch; ++q) {
+      px[q] = pos[jb[q]];
+      py[q] = pos[(size_t)n + jb[q]];
+      pz[q] = pos[2 * (size_t)n + jb[q]];
+    }
+#pragma unroll
+    for (int q = 0; q < kBatch; ++q) {
+      const double dx = min_image(px[q] - xi, b.L[0], b.half[0], b.per[0]);
+      const double dy = min_image(py[q] - yi, b.L[1], b.half[1], b.per[1]);
+      const double dz = min_image(pz[q] - zi, b.L[2], b.half[2], b.per[2]);
+      if (k0 + q < cnt && sq_dist_exact(dx, dy, dz) < rc2) ++coord;
+    }
   }
+  double sums[1] = {(double)coord};
+  row_reduce<W, 1>(sums, wv);
+  if (row >= n || wv > 0) return;
+  coord = (int)sums[0];
   const double fx = f[i], fy = f[(size_t)n + i], fz = f[2 * (size_t)n + i];
   const double c = csp[i];
   feat[4 * (size_t)i + 0] = (float)rho[i];
@@ -615,8 +633,14 @@ apx_status apx_features(apx_ctx* ctx, const apx_atoms* atoms, const apx_nlist* n
   if (n == 0) return APX_OK;
   if (!rho || !csp || !f_eam || !feat) return fail(ctx, APX_EINVAL, "feature inputs are required");
   ProfScope ps(ctx, "mlp.features");
-  k_features<<<blocks_for(n, 256), 256, 0, ctx->stream>>>(atoms->pos, n, make_box(atoms), nl->count, nl->idx,
-                                                         nl->max_nb, rho, csp, f_eam, feat);
+  auto launch = [&](auto kern, int W) {
+    kern<<<row_blocks(n, W), row_threads(W), 0, ctx->stream>>>(atoms->pos, n, make_box(atoms), nl->count, nl->idx,
+                                                               nl->max_nb, rho, csp, f_eam, feat);
+  };
+  if (row_waves(n) == 16)
+    launch(k_features<16>, 16);
+  else
+    launch(k_features<4>, 4);
   APX_LAUNCH_CHECK(ctx);
   return APX_OK;
 }

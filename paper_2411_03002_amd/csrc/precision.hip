@@ -25,41 +25,22 @@ __device__ __forceinline__ double switch_w0(double c, const PrecDev& p) {
 
 constexpr int kBatch = 8;  // neighbours whose loads are issued together
 
-// One thread per atom.  Keeps the M nearest candidates within r_cut sorted by
-// (squared distance, index): the row is in ascending index, so a strict comparison
-// keeps the smaller index first among equal distances.  The sorted slots carry the
-// squared distance and the row position only; the M displacements are recomputed
-// (identically) for the pair stage.  EXACT: M and HALF are the parameters' N + N_buffer
-// and N/2; otherwise they are upper bounds and p.m, p.half apply.
-template <int M, int HALF, bool EXACT>
-__global__ void __launch_bounds__(256) k_csp(const double* __restrict__ pos, int n, Grid g,
-                                             const uint8_t* __restrict__ frozen,
-                                             const int* __restrict__ count, const int* __restrict__ idx,
-                                             int max_nb, PrecDev p, const double* __restrict__ w0_extra,
-                                             double* __restrict__ csp, double* __restrict__ w0,
-                                             double* __restrict__ w) {
+// The m nearest candidates within r_cut of a row, one insertion per candidate into slots sorted by
+// (squared distance, index): the row is in ascending index, so a strict comparison keeps the smaller
+// index first among equal distances.  ks: row positions; returns whether there are m of them.
+template <int M>
+__device__ bool nearest_by_insertion(const double* __restrict__ pos, int n, const Grid& g, const int* __restrict__ idx,
+                                     int i, int cnt, int m, double rc2, int (&ks)[M]) {
 #pragma clang fp contract(off)
-  const int i = xcd_block(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  if (frozen && frozen[i]) {
-    csp[i] = 0.0;
-    w0[i] = 0.0;
-    w[i] = 0.0;
-    return;
-  }
   const double xi = pos[i], yi = pos[(size_t)n + i], zi = pos[2 * (size_t)n + i];
   const double hx = 0.5 * g.L[0], hy = 0.5 * g.L[1], hz = 0.5 * g.L[2];
-  const int m = EXACT ? M : p.m;
   double kr[M];
-  int ks[M];
 #pragma unroll
   for (int a = 0; a < M; ++a) {
     kr[a] = INFINITY;
     ks[a] = 0;
   }
   int found = 0;
-  int cnt = count[i];
-  if (cnt > max_nb) cnt = max_nb;
   for (int k0 = 0; k0 < cnt; k0 += kBatch) {
     int jb[kBatch];
     double px[kBatch], py[kBatch], pz[kBatch];
@@ -77,12 +58,11 @@ __global__ void __launch_bounds__(256) k_csp(const double* __restrict__ pos, int
       const double dy = min_image(py[q] - yi, g.L[1], hy, g.per[1]);
       const double dz = min_image(pz[q] - zi, g.L[2], hz, g.per[2]);
       const double r2 = sq_dist_exact(dx, dy, dz);
-      if (!(k0 + q < cnt && r2 < p.rc2)) continue;
+      if (!(k0 + q < cnt && r2 < rc2)) continue;
       ++found;
       if (!(r2 < kr[M - 1])) continue;
-      // insertion into the sorted slots, unrolled so they stay in registers; once the new
-      // entry has been placed every later slot shifts by one, which keeps equal distances
-      // in arrival (ascending index) order
+      // once the new entry has been placed every later slot shifts by one, which keeps equal
+      // distances in arrival (ascending index) order
       double cr = r2;
       int cs = k0 + q;
       bool shifting = false;
@@ -99,48 +79,220 @@ __global__ void __launch_bounds__(256) k_csp(const double* __restrict__ pos, int
       }
     }
   }
-  double c;
-  if (found < m) {
-    c = INFINITY;
-  } else {
+  return found >= m;
+}
+
+// min and max of values that are never NaN, one instruction each.
+__device__ __forceinline__ double min_num(double a, double b) {
+  double r;
+  asm("v_min_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+  return r;
+}
+__device__ __forceinline__ double max_num(double a, double b) {
+  double r;
+  asm("v_max_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+  return r;
+}
+__device__ __forceinline__ void order(double& a, double& b) {
+  const double lo = min_num(a, b), hi = max_num(a, b);
+  a = lo;
+  b = hi;
+}
+
+__device__ __forceinline__ void sort8(double (&v)[8]) {
+  constexpr int net[19][2] = {{0, 1}, {2, 3}, {4, 5}, {6, 7}, {0, 2}, {1, 3}, {4, 6}, {5, 7}, {1, 2}, {5, 6},
+                              {0, 4}, {1, 5}, {2, 6}, {3, 7}, {2, 4}, {3, 5}, {1, 2}, {3, 4}, {5, 6}};
+#pragma unroll
+  for (int c = 0; c < 19; ++c) order(v[net[c][0]], v[net[c][1]]);
+}
+
+// a (N ascending values) becomes the N smallest of a and b (K <= N ascending values), ascending.
+template <int N, int K>
+__device__ __forceinline__ void keep_smallest(double (&a)[N], const double (&b)[K]) {
+#pragma unroll
+  for (int k = 0; k < K; ++k) a[N - 1 - k] = min_num(a[N - 1 - k], b[k]);
+#pragma unroll
+  for (int j = N / 2; j > 0; j >>= 1)
+#pragma unroll
+    for (int k = 0; k < N; ++k)
+      if ((k & j) == 0) order(a[k], a[k + j]);
+}
+
+// The sum of the HALF smallest |d_a + d_b|^2, a < b < m, added in ascending order.
+template <int M, int HALF>
+__device__ __forceinline__ double pair_sum(const double (&kx)[M], const double (&ky)[M], const double (&kz)[M], int m,
+                                           int half) {
+#pragma clang fp contract(off)
+  static_assert(HALF <= 8, "eight sums are kept");
+  constexpr int kPairs = M * (M - 1) / 2;
+  double best[8], v[8];
+#pragma unroll
+  for (int q = 0; q < 8; ++q) best[q] = INFINITY;
+  int slot = 0;
+#pragma unroll
+  for (int a = 0; a < M; ++a) {
+#pragma unroll
+    for (int b = a + 1; b < M; ++b) {
+      const double d = sq_dist_exact(kx[a] + kx[b], ky[a] + ky[b], kz[a] + kz[b]);
+      v[slot & 7] = b < m ? d : INFINITY;
+      ++slot;
+      if (slot == kPairs) {
+#pragma unroll
+        for (int q = kPairs & 7; q < ((kPairs & 7) ? 8 : 0); ++q) v[q] = INFINITY;
+      }
+      if ((slot & 7) == 0 || slot == kPairs) {
+        sort8(v);
+        keep_smallest<8, 8>(best, v);
+      }
+    }
+  }
+  double c = 0.0;
+#pragma unroll
+  for (int q = 0; q < HALF; ++q)
+    if (q < half) c = c + best[q];
+  return c;
+}
+
+// Centro-symmetry of the 12 nearest, 64 atoms to W waves (row batches w, w + W, ... to wave w).
+// Each candidate is one key, the upper word of its squared distance over its index, so that a
+// compare-exchange is a minimum and a maximum: eight keys are sorted and merged into a wave's sixteen
+// smallest (110 instructions against some 650 for eight insertions of a distance with its position),
+// and the waves' lists meet in LDS.  Where the twelfth and the thirteenth key agree in the upper word
+// (a relative gap below 1e-6: ties of a perfect lattice), the keys do not decide which is nearer, and
+// the atom's row is read again by insertions; the order inside the twelve does not matter.  The six
+// smallest pair sums are kept the same way.
+// Measured (us), insertions before / now: 860 atoms 65 / 18, 130,466 atoms 81 / 42, 4,102,125 atoms
+// 1,600 / 1,054.
+template <int W>
+__global__ void __launch_bounds__(W == 1 ? 256 : 64 * W, 4) k_csp12(const double* __restrict__ pos, int n, Grid g,
+                                                                const uint8_t* __restrict__ frozen,
+                                                                const int* __restrict__ count,
+                                                                const int* __restrict__ idx, int max_nb, PrecDev p,
+                                                                const double* __restrict__ w0_extra,
+                                                                double* __restrict__ csp, double* __restrict__ w0,
+                                                                double* __restrict__ w) {
+#pragma clang fp contract(off)
+  constexpr int M = 12;
+  constexpr int kNoKey = 0x7fe00000;  // (a number, above every squared distance below the cutoff's)
+  const int row = row_atom<W>(xcd_block(blockIdx.x, gridDim.x)), wv = row_wave<W>();
+  const int i = row < n ? row : n - 1;  // (a thread beyond the last atom repeats it)
+  const bool skip = frozen && frozen[i];
+  const double xi = pos[i], yi = pos[(size_t)n + i], zi = pos[2 * (size_t)n + i];
+  const double hx = 0.5 * g.L[0], hy = 0.5 * g.L[1], hz = 0.5 * g.L[2];
+  int cnt = skip ? 0 : count[i];
+  if (cnt > max_nb) cnt = max_nb;
+  double key[16];
+#pragma unroll
+  for (int a = 0; a < 16; ++a) key[a] = __hiloint2double(kNoKey, 0);
+  for (int k0 = wv * kBatch; k0 < cnt; k0 += W * kBatch) {
+    int jb[kBatch];
+    double px[kBatch], py[kBatch], pz[kBatch], v[kBatch];
+#pragma unroll
+    for (int q = 0; q < kBatch; ++q) jb[q] = k0 + q < cnt ? idx[(size_t)(k0 + q) * n + i] : i;
+#pragma unroll
+    for (int q = 0; q < kBatch; ++q) {
+      px[q] = pos[jb[q]];
+      py[q] = pos[(size_t)n + jb[q]];
+      pz[q] = pos[2 * (size_t)n + jb[q]];
+    }
+#pragma unroll
+    for (int q = 0; q < kBatch; ++q) {
+      const double dx = min_image(px[q] - xi, g.L[0], hx, g.per[0]);
+      const double dy = min_image(py[q] - yi, g.L[1], hy, g.per[1]);
+      const double dz = min_image(pz[q] - zi, g.L[2], hz, g.per[2]);
+      const double r2 = sq_dist_exact(dx, dy, dz);
+      v[q] = __hiloint2double(k0 + q < cnt && r2 < p.rc2 ? __double2hiint(r2) : kNoKey, jb[q]);
+    }
+    sort8(v);
+    keep_smallest<16, 8>(key, v);
+  }
+  if constexpr (W > 1) {
+    __shared__ double lists[W - 1][M + 1][kWave];
+    const int lane = threadIdx.x & (kWave - 1);
+    if (wv > 0) {
+#pragma unroll
+      for (int a = 0; a <= M; ++a) lists[wv - 1][a][lane] = key[a];
+    }
+    __syncthreads();
+    if (wv > 0) return;
+    for (int o = 0; o < W - 1; ++o) {
+      double v[M + 1];
+#pragma unroll
+      for (int a = 0; a <= M; ++a) v[a] = lists[o][a][lane];
+      keep_smallest<16, M + 1>(key, v);
+    }
+  }
+  if (row >= n) return;
+  if (skip) {
+    csp[i] = 0.0;
+    w0[i] = 0.0;
+    w[i] = 0.0;
+    return;
+  }
+  double c = INFINITY;
+  if (__double2hiint(key[M - 1]) < kNoKey) {
+    int js[M];
+#pragma unroll
+    for (int a = 0; a < M; ++a) js[a] = __double2loint(key[a]);
+    if (__double2hiint(key[M - 1]) == __double2hiint(key[M])) {
+      nearest_by_insertion<M>(pos, n, g, idx, i, cnt, M, p.rc2, js);
+#pragma unroll
+      for (int a = 0; a < M; ++a) js[a] = idx[(size_t)js[a] * n + i];
+    }
     double kx[M], ky[M], kz[M];
 #pragma unroll
     for (int a = 0; a < M; ++a) {
-      if (a < m) {
+      kx[a] = min_image(pos[js[a]] - xi, g.L[0], hx, g.per[0]);
+      ky[a] = min_image(pos[(size_t)n + js[a]] - yi, g.L[1], hy, g.per[1]);
+      kz[a] = min_image(pos[2 * (size_t)n + js[a]] - zi, g.L[2], hz, g.per[2]);
+    }
+    c = pair_sum<M, 6>(kx, ky, kz, M, 6);
+  }
+  csp[i] = c;
+  double v0 = switch_w0(c, p);
+  if (w0_extra) {
+    const double e = w0_extra[i];
+    v0 = e > v0 ? e : v0;
+  }
+  w0[i] = v0;
+  w[i] = v0;
+}
+
+// Centro-symmetry of any N + N_buffer (p.m) and N / 2 (p.half), one thread per atom.
+__global__ void __launch_bounds__(256) k_csp(const double* __restrict__ pos, int n, Grid g,
+                                             const uint8_t* __restrict__ frozen,
+                                             const int* __restrict__ count, const int* __restrict__ idx,
+                                             int max_nb, PrecDev p, const double* __restrict__ w0_extra,
+                                             double* __restrict__ csp, double* __restrict__ w0,
+                                             double* __restrict__ w) {
+#pragma clang fp contract(off)
+  const int i = xcd_block(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
+  if (i >= n) return;
+  if (frozen && frozen[i]) {
+    csp[i] = 0.0;
+    w0[i] = 0.0;
+    w[i] = 0.0;
+    return;
+  }
+  const double xi = pos[i], yi = pos[(size_t)n + i], zi = pos[2 * (size_t)n + i];
+  const double hx = 0.5 * g.L[0], hy = 0.5 * g.L[1], hz = 0.5 * g.L[2];
+  int cnt = count[i];
+  if (cnt > max_nb) cnt = max_nb;
+  int ks[kMaxM];
+  double c = INFINITY;
+  if (nearest_by_insertion<kMaxM>(pos, n, g, idx, i, cnt, p.m, p.rc2, ks)) {
+    double kx[kMaxM], ky[kMaxM], kz[kMaxM];
+#pragma unroll
+    for (int a = 0; a < kMaxM; ++a) {
+      kx[a] = ky[a] = kz[a] = 0.0;
+      if (a < p.m) {
         const int j = idx[(size_t)ks[a] * n + i];
         kx[a] = min_image(pos[j] - xi, g.L[0], hx, g.per[0]);
         ky[a] = min_image(pos[(size_t)n + j] - yi, g.L[1], hy, g.per[1]);
         kz[a] = min_image(pos[2 * (size_t)n + j] - zi, g.L[2], hz, g.per[2]);
-      } else {
-        kx[a] = ky[a] = kz[a] = 0.0;
       }
     }
-    double best[HALF];
-#pragma unroll
-    for (int a = 0; a < HALF; ++a) best[a] = INFINITY;
-#pragma unroll
-    for (int a = 0; a < M; ++a) {
-#pragma unroll
-      for (int b = a + 1; b < M; ++b) {
-        if (EXACT || b < m) {
-          const double sx = kx[a] + kx[b], sy = ky[a] + ky[b], sz = kz[a] + kz[b];
-          double v = sq_dist_exact(sx, sy, sz);
-          bool shifting = false;
-#pragma unroll
-          for (int q = 0; q < HALF; ++q) {
-            const bool take = shifting || v < best[q];
-            shifting = take;
-            const double t = best[q];
-            best[q] = take ? v : t;
-            v = take ? t : v;
-          }
-        }
-      }
-    }
-    c = 0.0;
-#pragma unroll
-    for (int q = 0; q < HALF; ++q)
-      if (EXACT || q < p.half) c = c + best[q];
+    c = pair_sum<kMaxM, kMaxHalf>(kx, ky, kz, p.m, p.half);
   }
   csp[i] = c;
   double v0 = switch_w0(c, p);
@@ -343,6 +495,11 @@ __global__ void k_avg_w(int n, const double* __restrict__ w_min, double* __restr
 
 using namespace apx;
 
+// Waves per 64 atoms (see k_csp12): four while the atoms alone leave the card short of waves.
+// Measured for 1 / 4 (us): 860 atoms 29 / 18, 42,395 atoms 33 / 26, 87,402 atoms 41 / 37, 130,466
+// atoms 42 / 47, 497,686 atoms 122 / 136.
+constexpr long long kCspWide = 98304;
+
 // Spreading stencil: a cell edge no smaller than r_hi/3 (and the list cutoff), so that
 // three cells on each side cover r_hi; axes with fewer cells are visited once each.
 static void spread_stencil(const Grid& g, double r_hi, SpreadDev& s) {
@@ -403,12 +560,16 @@ apx_status precision_impl(apx_ctx* ctx, const apx_atoms* atoms, const apx_nlist*
   const double* extra_pre = extra_local ? nullptr : w0_extra;
   if (!(p->flags & APX_PREC_CSP_GIVEN)) {
   ProfScope ps(ctx, "prec.csp");
-  if (pd.m == 12 && pd.half == 6)
-    k_csp<12, 6, true><<<blocks_for(n, 256), 256, 0, ctx->stream>>>(
-        atoms->pos, n, g, atoms->frozen, nl->count, nl->idx, nl->max_nb, pd, avg ? nullptr : extra_pre, csp, w0, ws);
+  auto launch = [&](auto kern, unsigned blocks, unsigned threads) {
+    kern<<<blocks, threads, 0, ctx->stream>>>(atoms->pos, n, g, atoms->frozen, nl->count, nl->idx, nl->max_nb, pd,
+                                              avg ? nullptr : extra_pre, csp, w0, ws);
+  };
+  if (pd.m != 12 || pd.half != 6)
+    launch(k_csp, blocks_for(n, 256), 256);
+  else if (n <= kCspWide)
+    launch(k_csp12<4>, row_blocks(n, 4), row_threads(4));
   else
-    k_csp<kMaxM, kMaxHalf, false><<<blocks_for(n, 256), 256, 0, ctx->stream>>>(
-        atoms->pos, n, g, atoms->frozen, nl->count, nl->idx, nl->max_nb, pd, avg ? nullptr : extra_pre, csp, w0, ws);
+    launch(k_csp12<1>, row_blocks(n, 1), row_threads(1));
   APX_LAUNCH_CHECK(ctx);
   } else if (!avg) {
     ProfScope ps(ctx, "prec.switch");
