@@ -36,10 +36,10 @@ struct AceScratch {
 };
 
 // ------------------------------------------------------------ shared helpers
-template <class T, int LMAX, bool GRAD>
-__device__ __forceinline__ void solid_harmonics(T x, T y, T z, T* S, T* Sx, T* Sy, T* Sz) {
+// Real solid harmonics S_lm of (x, y, z) with x^2 + y^2 + z^2 = 1, in the order l^2 + l + m.
+template <class T, int LMAX>
+__device__ __forceinline__ void solid_harmonics(T x, T y, T z, T* S) {
   S[0] = T(1);
-  if constexpr (GRAD) { Sx[0] = T(0); Sy[0] = T(0); Sz[0] = T(0); }
 #pragma unroll
   for (int l = 0; l < LMAX; ++l) {
     const T c = (l == 0) ? T(1) : T(sqrt((2.0 * l + 1.0) / (2.0 * l + 2.0)));
@@ -50,21 +50,9 @@ __device__ __forceinline__ void solid_harmonics(T x, T y, T z, T* S, T* Sx, T* S
     if (l == 0) {
       S[tp] = c * x * S[sll];
       S[bt] = c * y * S[sll];
-      if constexpr (GRAD) {
-        Sx[tp] = c * S[sll]; Sy[tp] = T(0); Sz[tp] = T(0);
-        Sx[bt] = T(0); Sy[bt] = c * S[sll]; Sz[bt] = T(0);
-      }
     } else {
       S[tp] = c * (x * S[sll] - y * S[slm]);
       S[bt] = c * (y * S[sll] + x * S[slm]);
-      if constexpr (GRAD) {
-        Sx[tp] = c * (S[sll] + x * Sx[sll] - y * Sx[slm]);
-        Sy[tp] = c * (x * Sy[sll] - S[slm] - y * Sy[slm]);
-        Sz[tp] = c * (x * Sz[sll] - y * Sz[slm]);
-        Sx[bt] = c * (y * Sx[sll] + S[slm] + x * Sx[slm]);
-        Sy[bt] = c * (S[sll] + y * Sy[sll] + x * Sy[slm]);
-        Sz[bt] = c * (y * Sz[sll] + x * Sz[slm]);
-      }
     }
 #pragma unroll
     for (int m = -l; m <= l; ++m) {
@@ -75,21 +63,55 @@ __device__ __forceinline__ void solid_harmonics(T x, T y, T z, T* S, T* Sx, T* S
         const int s2 = (l - 1) * (l - 1) + (l - 1) + m;
         const T b = T(sqrt((l + m) * (l - m) * 1.0) / sqrt((l + m + 1.0) * (l - m + 1.0)));
         S[dst] = a * z * S[s1] - b * S[s2];
-        if constexpr (GRAD) {
-          Sx[dst] = a * z * Sx[s1] - b * (T(2) * x * S[s2] + Sx[s2]);
-          Sy[dst] = a * z * Sy[s1] - b * (T(2) * y * S[s2] + Sy[s2]);
-          Sz[dst] = a * (S[s1] + z * Sz[s1]) - b * (T(2) * z * S[s2] + Sz[s2]);
-        }
       } else {
         S[dst] = a * z * S[s1];
-        if constexpr (GRAD) {
-          Sx[dst] = a * z * Sx[s1];
-          Sy[dst] = a * z * Sy[s1];
-          Sz[dst] = a * (S[s1] + z * Sz[s1]);
-        }
       }
     }
   }
+}
+
+// Gradient of sum_lm W_lm S_lm at (x, y, z): the recurrence above backwards, degree by degree (W is
+// used up).  S_lm of the lower degree enters with x^2 + y^2 + z^2, hence the terms in q.  It takes 130
+// operations and a second array of values, where S with three derivatives took 370 and four arrays.
+template <class T, int LMAX>
+__device__ __forceinline__ void harmonics_gradient(T x, T y, T z, const T* S, T* W, T& gx, T& gy, T& gz) {
+  T q = T(0);
+  gx = gy = gz = T(0);
+#pragma unroll
+  for (int l = LMAX - 1; l >= 0; --l) {
+    const T c = (l == 0) ? T(1) : T(sqrt((2.0 * l + 1.0) / (2.0 * l + 2.0)));
+    const int sll = l * l + 2 * l;
+    const int slm = l * l;
+    const T wt = c * W[(l + 1) * (l + 1) + 2 * (l + 1)];
+    const T wb = c * W[(l + 1) * (l + 1)];
+    gx = fma(wt, S[sll], gx);
+    gy = fma(wb, S[sll], gy);
+    if (l > 0) {
+      gx = fma(wb, S[slm], gx);
+      gy = fma(-wt, S[slm], gy);
+      W[sll] = fma(x, wt, fma(y, wb, W[sll]));
+      W[slm] = fma(x, wb, fma(-y, wt, W[slm]));
+    }
+#pragma unroll
+    for (int m = -l; m <= l; ++m) {
+      const int dst = (l + 1) * (l + 1) + (l + 1) + m;
+      const int s1 = l * l + l + m;
+      const T a = T((2.0 * l + 1.0) / sqrt((l + m + 1.0) * (l - m + 1.0)));
+      const T wa = a * W[dst];
+      gz = fma(wa, S[s1], gz);
+      if (l > 0) W[s1] = fma(wa, z, W[s1]);
+      if (m >= -(l - 1) && m <= l - 1) {
+        const int s2 = (l - 1) * (l - 1) + (l - 1) + m;
+        const T b = T(sqrt((l + m) * (l - m) * 1.0) / sqrt((l + m + 1.0) * (l - m + 1.0)));
+        const T wc = b * W[dst];
+        q = fma(wc, S[s2], q);
+        if (l > 1) W[s2] -= wc;
+      }
+    }
+  }
+  gx = fma(T(-2) * x, q, gx);
+  gy = fma(T(-2) * y, q, gy);
+  gz = fma(T(-2) * z, q, gz);
 }
 
 // Reciprocal in the evaluation type: the hardware estimate (1 ulp) in float32, two Newton
@@ -118,58 +140,69 @@ __device__ __forceinline__ void taper_t(T x, T& p, T& dp) {
 }
 
 typedef float floatx4 __attribute__((ext_vector_type(4)));
+typedef double doublex4 __attribute__((ext_vector_type(4)));
 
-// LDS layout of the atomic-base kernel: per neighbour slot (columns, row stride kStride)
-// the radial values g_k (12 rows) and solid harmonics S_lm (LM rows); A' reuses the space
-// once the contraction is done.  Float32 contracts on the matrix cores.
-template <class T, int LMAX>
+// One step of the atomic base on the matrix cores: 16 x 16 outputs, four neighbour slots.
+__device__ __forceinline__ floatx4 mfma16(float a, float b, floatx4 d) {
+  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, d, 0, 0, 0);
+}
+__device__ __forceinline__ doublex4 mfma16(double a, double b, doublex4 d) {
+  return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, d, 0, 0, 0);
+}
+
+// LDS layout of the atomic-base kernel: per neighbour slot (columns, row stride kStride: rows and the
+// slots of a step fall on distinct banks) the radial values g_k (NMAX rows) and solid harmonics S_lm;
+// A' reuses the space once the contraction is done.  48 slots at a time (42 neighbours lie within 5 A in
+// copper; more take a second round) leave room for more waves than 64 would.
+template <class T, int LMAX, int NMAX>
 struct BasisLds {
   static constexpr int LM = (LMAX + 1) * (LMAX + 1);
-  static constexpr bool kMfma = sizeof(T) == 4;
-  static constexpr int kStride = kMfma ? 66 : 65;
-  static constexpr int kGRows = 12;
-  static constexpr int kSRows = LM;
-  static constexpr size_t bytes() { return sizeof(T) * ((size_t)(kGRows + kSRows) * kStride); }
-  static_assert(12 * LM <= (kGRows + kSRows) * kStride, "A' fits in the neighbour tables");
+  static constexpr int kSlots = 48;
+  static constexpr int kStride = sizeof(T) == 4 ? 52 : 50;
+  static constexpr size_t bytes() { return sizeof(T) * (size_t)(NMAX + LM) * kStride; }
 };
 
 // ------------------------------------------------------------------ kernel 1
-template <class T, int LMAX>
+// One wave per active atom, lanes over its neighbours for the radial values and harmonics; the
+// contraction over the neighbours inside the cutoff (compacted to the front) runs on the matrix cores of
+// either type, rows = k, columns = lm.  Then a lane holds one lm of A' and mixes it for every other n, so
+// that a column is read from LDS once.
+// Bound by vector instructions in float32 and by the float64 matrix instructions (64 cycles for 1,024
+// multiply-adds, of which K x (l_max + 1)^2 of 16 x 32 outputs are used).  Measured at (10, 4) (us):
+// float32, 29,150 atoms 69 before / 44, 16,309 atoms 50 / 33; float64, 29,150 atoms 183 / 91 (on the vector
+// unit each multiply-add read two values from LDS), 3,982 atoms 35 / 21.
+template <class T, int LMAX, int NMAX>
 __global__ void __launch_bounds__(64) k_ace_basis(const double* __restrict__ pos, int n, BoxDev b,
                                                   const int* __restrict__ count, const int* __restrict__ idx,
                                                   int max_nb, const int* __restrict__ active, int n_act,
                                                   int K, T rc, T inv_h, double rc2, const T* __restrict__ Wp,
                                                   AnchorDev an, AceScratch<T> sc) {
   constexpr int LM = (LMAX + 1) * (LMAX + 1);
-  constexpr int kMaxK = 12;
-  constexpr bool MF = BasisLds<T, LMAX>::kMfma;
-  constexpr int ST = BasisLds<T, LMAX>::kStride, GR = BasisLds<T, LMAX>::kGRows, SR = BasisLds<T, LMAX>::kSRows;
+  constexpr int ST = BasisLds<T, LMAX, NMAX>::kStride, kSlots = BasisLds<T, LMAX, NMAX>::kSlots;
+  using V4 = std::conditional_t<sizeof(T) == 4, floatx4, doublex4>;
   extern __shared__ double smem_raw[];
-  T* gS = reinterpret_cast<T*>(smem_raw);  // [GR][ST]: g_k per neighbour slot
-  T* sS = gS + GR * ST;                    // [SR][ST]: S_lm per neighbour slot
-  T* Ap = gS;                              // [K*LM], after the contraction
+  T* gS = reinterpret_cast<T*>(smem_raw);  // [NMAX][ST]: g_k per neighbour slot
+  T* sS = gS + NMAX * ST;                  // [LM][ST]: S_lm per neighbour slot
+  T* Ap = gS;                              // [K][LM], after the contraction
   __shared__ double etab[32];
-  stage_exp_table(etab);
   const int q = xcd_block(blockIdx.x, gridDim.x);
   const int lane = threadIdx.x;
   const int i = active[q];
+  if (an.on) stage_exp_table(etab);
   const double xi = pos[i], yi = pos[(size_t)n + i], zi = pos[2 * (size_t)n + i];
   int cnt = count[i];
   if (cnt > max_nb) cnt = max_nb;
-  const int nout = K * LM;
-  T acc[5];
-#pragma unroll
-  for (int s = 0; s < 5; ++s) acc[s] = T(0);
-  floatx4 D0 = {0.f, 0.f, 0.f, 0.f}, D1 = {0.f, 0.f, 0.f, 0.f};
+  const int col = lane & 15, sub = lane >> 4;
+  V4 D0 = {T(0), T(0), T(0), T(0)}, D1 = {T(0), T(0), T(0), T(0)};
   double rho_a = 0.0, pair_a = 0.0;
   const T two_rc = T(2) / rc;
   for (int c0 = 0; c0 < cnt; c0 += 64) {
     const int k = c0 + lane;
-    T g[kMaxK];
+    T g[NMAX];
     T S[LM];
     bool inside = false;
 #pragma unroll
-    for (int a = 0; a < kMaxK; ++a) g[a] = T(0);
+    for (int a = 0; a < NMAX; ++a) g[a] = T(0);
 #pragma unroll
     for (int a = 0; a < LM; ++a) S[a] = T(0);
     if (k < cnt) {
@@ -189,15 +222,15 @@ __global__ void __launch_bounds__(64) k_ace_basis(const double* __restrict__ pos
         taper_t<T>((r - rc) * inv_h, ps, dps);
         T t0 = T(1), t1 = x;
         g[0] = ps;
-        if (K > 1) g[1] = x * ps;
+        g[1] = x * ps;
 #pragma unroll
-        for (int a = 2; a < kMaxK; ++a) {
+        for (int a = 2; a < NMAX; ++a) {
           const T t2 = T(2) * x * t1 - t0;
-          if (a < K) g[a] = t2 * ps;
+          g[a] = t2 * ps;
           t0 = t1;
           t1 = t2;
         }
-        solid_harmonics<T, LMAX, false>(T(dx) * ir, T(dy) * ir, T(dz) * ir, S, nullptr, nullptr, nullptr);
+        solid_harmonics<T, LMAX>(T(dx) * ir, T(dy) * ir, T(dz) * ir, S);
       }
       if (an.on && r2 < an.rc2) {
         double ps, dps;
@@ -206,84 +239,79 @@ __global__ void __launch_bounds__(64) k_ace_basis(const double* __restrict__ pos
         pair_a += exp_tab(-an.alpha * (rd - an.r0), etab) * ps;
       }
     }
-    // neighbour slot of the lane: float32 compacts the neighbours inside the cutoff to the
-    // front (the others, all zero, follow), so that the matrix steps stop after them
-    int slot = lane, steps = 0;
-    if constexpr (MF) {
-      const unsigned long long m = __ballot(inside);
-      const int nv = __popcll(m);
-      const int below = (int)__builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
-      slot = inside ? below : nv + (lane - below);
-      steps = (nv + 3) >> 2;
-    }
+    // the neighbours inside the cutoff take the first slots, the next ones (all zero) fill up the last
+    // step of four
+    const unsigned long long m = __ballot(inside);
+    const int nv = __popcll(m), steps = (nv + 3) >> 2;
+    const int below = (int)__builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
+    const int slot = inside ? below : nv + (lane - below);
+    // lane = row / column (lane % 16) and slot in the step (lane / 16); rows past NMAX and columns past
+    // LM repeat others, and what they give is not used
+    const T* ga = gS + (col < NMAX ? col : 0) * ST + sub;
+    const T* sa = sS + col * ST + sub;
+    const T* sb = sS + (16 + col < LM ? 16 + col : col) * ST + sub;
+    for (int at = 0; at < 4 * steps; at += kSlots) {
+      const int end = 4 * steps - at < kSlots ? 4 * steps - at : kSlots;
+      if (slot >= at && slot < at + end) {
 #pragma unroll
-    for (int a = 0; a < kMaxK; ++a)
-      if (a < K) gS[a * ST + slot] = g[a];
+        for (int a = 0; a < NMAX; ++a) gS[a * ST + slot - at] = g[a];
 #pragma unroll
-    for (int a = 0; a < LM; ++a) sS[a * ST + slot] = S[a];
-    __syncthreads();
-    if constexpr (MF) {
-      // A'[k][lm] += sum over 4 slots per step of g[k][slot] S[lm][slot] on the matrix
-      // cores (16 x 16 x 4 float32): lane = row/column (lane % 16) and slot in the step
-      // (lane / 16), operand rows beyond K and LM are zero; the row stride of 66 keeps
-      // the two lane halves on distinct banks
-      const int col = lane & 15, sub = lane >> 4;
-      const bool g_row = col < K, s_row = 16 + col < LM;
-      for (int st = 0; st < steps; ++st) {
-        const int sl = 4 * st + sub;
-        const float av = g_row ? gS[col * ST + sl] : 0.f;
-        D0 = __builtin_amdgcn_mfma_f32_16x16x4f32(av, sS[col * ST + sl], D0, 0, 0, 0);
-        if constexpr (LM > 16)
-          D1 = __builtin_amdgcn_mfma_f32_16x16x4f32(av, s_row ? sS[(16 + col) * ST + sl] : 0.f, D1, 0, 0, 0);
+        for (int a = 0; a < LM; ++a) sS[a * ST + slot - at] = S[a];
       }
-    } else {
-      const int lim = (cnt - c0) < 64 ? (cnt - c0) : 64;
-#pragma unroll
-      for (int s = 0; s < 5; ++s) {
-        const int o = lane + 64 * s;
-        if (o < nout) {
-          const int kk = o / LM, lm = o - kk * LM;
-          T v = acc[s];
-          for (int nb = 0; nb < lim; ++nb) v += gS[kk * ST + nb] * sS[lm * ST + nb];
-          acc[s] = v;
-        }
+      __syncthreads();
+      for (int st = 0; st < end; st += 4) {
+        const T av = ga[st];
+        D0 = mfma16(av, sa[st], D0);
+        if constexpr (LM > 16) D1 = mfma16(av, sb[st], D1);
       }
+      __syncthreads();
     }
-    __syncthreads();
   }
-  if constexpr (MF) {
-    // accumulator layout: row k = 4 (lane / 16) + r, column lane % 16 (+ 16 for D1)
-    const int col = lane & 15, sub = lane >> 4;
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int k = 4 * sub + r;
-      if (k < K) {
-        Ap[k * LM + col] = D0[r];
-        if (16 + col < LM) Ap[k * LM + 16 + col] = D1[r];
-      }
-    }
-  } else {
-#pragma unroll
-    for (int s = 0; s < 5; ++s) {
-      const int o = lane + 64 * s;
-      if (o < nout) Ap[o] = acc[s];
+  for (int r = 0; r < 4; ++r) {
+    // accumulator layout: column lane % 16 (+ 16 for D1), row 4 (lane / 16) + r in float32,
+    // 4 r + lane / 16 in float64
+    const int k = sizeof(T) == 4 ? 4 * sub + r : 4 * r + sub;
+    if (k < K) {
+      Ap[k * LM + col] = D0[r];
+      if (16 + col < LM) Ap[k * LM + 16 + col] = D1[r];
     }
   }
   __syncthreads();
-  const int na = K * LM;
-  T* Arow = sc.A + (size_t)q * sc.stride;
-  for (int o = lane; o < na; o += 64) {
-    const int nn = o / LM, lm = o - nn * LM;
+  const int half = lane >> 5, lm = lane & 31;
+  if (lm < LM) {
     int l = 0;
-    while ((l + 1) * (l + 1) <= lm) ++l;
-    const T* w = Wp + ((size_t)l * K + nn) * K;
-    T v = T(0);
-    for (int kk = 0; kk < K; ++kk) v += w[kk] * Ap[kk * LM + lm];
-    Arow[o] = v;
+#pragma unroll
+    for (int t = 1; t <= LMAX; ++t) l += lm >= t * t ? 1 : 0;
+    T a[NMAX];
+#pragma unroll
+    for (int kk = 0; kk < NMAX; ++kk) a[kk] = kk < K ? Ap[kk * LM + lm] : T(0);
+    T* Arow = sc.A + (size_t)q * sc.stride + lm;
+    constexpr int H = (NMAX + 1) / 2;
+    T v[H];
+    auto mix = [&](auto full_c) {  // (full: whole rows of the table, read in wide loads)
+      constexpr bool FULL = decltype(full_c)::value;
+      const int kc = FULL ? NMAX : K;
+      const T* wl = Wp + (size_t)l * kc * kc;
+#pragma unroll
+      for (int h = 0; h < H; ++h) {
+        const int nn = 2 * h + half, row = nn < kc ? nn : 0;
+        v[h] = T(0);
+#pragma unroll
+        for (int kk = 0; kk < NMAX; ++kk) v[h] = fma(wl[row * kc + (FULL || kk < K ? kk : 0)], a[kk], v[h]);
+      }
+    };
+    if (K == NMAX)
+      mix(std::true_type{});
+    else
+      mix(std::false_type{});
+#pragma unroll
+    for (int h = 0; h < H; ++h)
+      if (2 * h + half < K) Arow[(2 * h + half) * LM] = v[h];
   }
   if (an.on) {
-    rho_a = wave_sum(rho_a);
-    pair_a = wave_sum(pair_a);
+    rho_a = wave_sum_dpp(rho_a);
+    pair_a = wave_sum_dpp(pair_a);
     if (lane == 0) {
       const double sq = sqrt(rho_a);
       sc.e_anch[q] = (rho_a > 0.0 ? -sq : 0.0) + 0.5 * an.A * pair_a;
@@ -303,9 +331,14 @@ struct ForceLds {
   static constexpr int KP = (NMAX * (int)sizeof(T) + 15) / 16 * 16 / (int)sizeof(T);
 };
 
-// Float32 is held to 128 VGPRs, four waves per SIMD (a few registers spill; three waves left
-// the gathers' latency exposed).
-template <class T, int LMAX, int NMAX>
+// One wave per active atom, lanes over its neighbours.  The scatter is what bounds it: 162 float64
+// atomics per atom, which the L2 takes a cache line at a time.  PACKED: the wave's contributions are
+// turned in LDS so that three neighbouring lanes add the three components of one atom, 32 bytes apart
+// from the next (fp[n][4]), instead of three instructions of 64 lanes on 64 lines each; k_unpack lays the
+// sums out.  Measured at (10, 4), per component / packed (us): float32, 16,309 atoms 78 / 62, float64,
+// 29,150 atoms 176 / 129 (without any scatter 43 and 123).
+// Float32 is held to 128 VGPRs, four waves per SIMD.
+template <class T, int LMAX, int NMAX, bool PACKED>
 __global__ void __launch_bounds__(64, sizeof(T) == 4 ? 4 : 1) k_ace_force(const double* __restrict__ pos, int n, BoxDev b,
                                                   const int* __restrict__ count, const int* __restrict__ idx,
                                                   int max_nb, const int* __restrict__ active, int n_act, int K,
@@ -319,7 +352,9 @@ __global__ void __launch_bounds__(64, sizeof(T) == 4 ? 4 : 1) k_ace_force(const 
   extern __shared__ double smem_raw[];
   T* Ab2 = reinterpret_cast<T*>(smem_raw);  // [LM][KP]: Ab2[lm * KP + k], zero for k >= K
   __shared__ double etab[32];
-  stage_exp_table(etab);
+  __shared__ double turn[PACKED ? 192 : 1];
+  __shared__ int turn_j[PACKED ? 64 : 1];
+  if (an.on) stage_exp_table(etab);
   const int q = xcd_block(blockIdx.x, gridDim.x);
   const T two_rc = T(2) / rc;
   const int lane = threadIdx.x;
@@ -344,13 +379,14 @@ __global__ void __launch_bounds__(64, sizeof(T) == 4 ? 4 : 1) k_ace_force(const 
   double f2x = 0.0, f2y = 0.0, f2z = 0.0;
   for (int c0 = 0; c0 < cnt; c0 += 64) {
     const int k = c0 + lane;
+    double gx = 0.0, gy = 0.0, gz = 0.0;
+    int j = i;
     if (k < cnt) {
-      const int j = idx[(size_t)k * n + i];
+      j = idx[(size_t)k * n + i];
       const double dx = min_image_sel(pos[j] - xi, b.L[0], b.half[0], b.per[0]);
       const double dy = min_image_sel(pos[(size_t)n + j] - yi, b.L[1], b.half[1], b.per[1]);
       const double dz = min_image_sel(pos[2 * (size_t)n + j] - zi, b.L[2], b.half[2], b.per[2]);
       const double r2 = dx * dx + dy * dy + dz * dz;
-      double gx = 0.0, gy = 0.0, gz = 0.0;
       const double ird = rsq_nr(r2);
       const double rd = r2 * ird;
       if (r2 < rc2) {
@@ -378,13 +414,11 @@ __global__ void __launch_bounds__(64, sizeof(T) == 4 ? 4 : 1) k_ace_force(const 
           d0 = d1;
           d1 = d2;
         }
-        T S[LM], Sx[LM], Sy[LM], Sz[LM];
-        solid_harmonics<T, LMAX, true>(ux, uy, uz, S, Sx, Sy, Sz);
-        T radial = T(0), vx = T(0), vy = T(0), vz = T(0);
+        T S[LM], W[LM];
+        solid_harmonics<T, LMAX>(ux, uy, uz, S);
+        T radial = T(0);
 #pragma unroll
         for (int lm = 0; lm < LM; ++lm) {
-          int l = 0;
-          while ((l + 1) * (l + 1) <= lm) ++l;
           // the row is the same for every lane (broadcast); entries beyond K are zero
           T c[KP];
 #pragma unroll
@@ -407,15 +441,17 @@ __global__ void __launch_bounds__(64, sizeof(T) == 4 ? 4 : 1) k_ace_force(const 
             av = fma(c[kk], g[kk], av);
             bv = fma(c[kk], gd[kk], bv);
           }
-          radial += (bv - av * T(l) * ir) * S[lm];
-          const T ar = av * ir;
-          vx = fma(ar, Sx[lm], vx);
-          vy = fma(ar, Sy[lm], vy);
-          vz = fma(ar, Sz[lm], vz);
+          radial = fma(bv, S[lm], radial);
+          W[lm] = av;
         }
-        gx = (double)(radial * ux + vx);
-        gy = (double)(radial * uy + vy);
-        gz = (double)(radial * uz + vz);
+        // sum_lm av S_lm depends on the direction only: its gradient is the one in (x, y, z), less the
+        // part along the direction, over r
+        T vx, vy, vz;
+        harmonics_gradient<T, LMAX>(ux, uy, uz, S, W, vx, vy, vz);
+        radial -= (vx * ux + vy * uy + vz * uz) * ir;
+        gx = (double)fma(radial, ux, vx * ir);
+        gy = (double)fma(radial, uy, vy * ir);
+        gz = (double)fma(radial, uz, vz * ir);
       }
       if (an.on && r2 < an.rc2) {
         double ps, dps;
@@ -444,7 +480,7 @@ __global__ void __launch_bounds__(64, sizeof(T) == 4 ? 4 : 1) k_ace_force(const 
       gx *= wi;
       gy *= wi;
       gz *= wi;
-      if (gx != 0.0 || gy != 0.0 || gz != 0.0) {
+      if (!PACKED && (gx != 0.0 || gy != 0.0 || gz != 0.0)) {
         unsafeAtomicAdd(&f[j], -gx);
         unsafeAtomicAdd(&f[(size_t)n + j], -gy);
         unsafeAtomicAdd(&f[2 * (size_t)n + j], -gz);
@@ -453,19 +489,37 @@ __global__ void __launch_bounds__(64, sizeof(T) == 4 ? 4 : 1) k_ace_force(const 
       fiy += gy;
       fiz += gz;
     }
+    if constexpr (PACKED) {
+      turn[3 * lane] = -gx;
+      turn[3 * lane + 1] = -gy;
+      turn[3 * lane + 2] = -gz;
+      turn_j[lane] = j;
+      __syncthreads();
+#pragma unroll
+      for (int h = 0; h < 3; ++h) {
+        const int e = 64 * h + lane, s = e / 3, c = e - 3 * s;
+        const double v = turn[e];
+        if (v != 0.0) unsafeAtomicAdd(&f[4 * (size_t)turn_j[s] + c], v);
+      }
+      __syncthreads();
+    }
   }
-  fix = wave_sum(fix);
-  fiy = wave_sum(fiy);
-  fiz = wave_sum(fiz);
-  if (lane == 0) {
-    unsafeAtomicAdd(&f[i], fix);
-    unsafeAtomicAdd(&f[(size_t)n + i], fiy);
-    unsafeAtomicAdd(&f[2 * (size_t)n + i], fiz);
+  fix = wave_sum_dpp(fix);
+  fiy = wave_sum_dpp(fiy);
+  fiz = wave_sum_dpp(fiz);
+  if (PACKED ? lane < 3 : lane == 0) {
+    if constexpr (PACKED) {
+      unsafeAtomicAdd(&f[4 * (size_t)i + lane], lane == 0 ? fix : (lane == 1 ? fiy : fiz));
+    } else {
+      unsafeAtomicAdd(&f[i], fix);
+      unsafeAtomicAdd(&f[(size_t)n + i], fiy);
+      unsafeAtomicAdd(&f[2 * (size_t)n + i], fiz);
+    }
   }
   if (w2i != 0.0) {  // uniform across the wave
-    f2x = wave_sum(f2x);
-    f2y = wave_sum(f2y);
-    f2z = wave_sum(f2z);
+    f2x = wave_sum_dpp(f2x);
+    f2y = wave_sum_dpp(f2y);
+    f2z = wave_sum_dpp(f2z);
     if (lane == 0) {
       unsafeAtomicAdd(&f2[i], f2x);
       unsafeAtomicAdd(&f2[(size_t)n + i], f2y);
@@ -478,6 +532,22 @@ __global__ void k_fill_zero(double* __restrict__ p, long long m) {
   long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < m) p[i] = 0.0;
 }
+
+// f[3][n] from fp[n][4].
+__global__ void k_unpack(const double* __restrict__ fp, int n, double* __restrict__ f) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= n) return;
+  const double2 xy = reinterpret_cast<const double2*>(fp)[2 * (size_t)i];
+  f[i] = xy.x;
+  f[(size_t)n + i] = xy.y;
+  f[2 * (size_t)n + i] = fp[4 * (size_t)i + 2];
+}
+
+// Forces gathered as [n][4] first: a packed scatter saves about 1 ns per active atom; clearing the third
+// more and unpacking cost 4 us and 0.02 ns per atom.  Float32 with these passes, direct / packed (us):
+// 16,309 active atoms 78 / 67, 29,150 of 130,466 123 / 86; below 8,192 the saving is no larger than a
+// launch.
+bool packed_forces(int n, int n_act) { return n_act >= 8192 && n_act >= n / 32; }
 
 template <class T, int LMAX>
 apx_status ace_run(apx_ctx* ctx, const apx_atoms* atoms, const apx_nlist* nl, const apx_ace_model* m,
@@ -496,7 +566,9 @@ apx_status ace_run(apx_ctx* ctx, const apx_atoms* atoms, const apx_nlist* nl, co
   const size_t bytes_anch = whole(sizeof(double) * 2 * (size_t)n_act);
   const size_t bytes_slope = dc1 ? whole(sizeof(T) * (size_t)n_act) : 0;
   const size_t bytes_more = std::max(sym_scratch<T>(m, n_act), dc1 ? ace_grad_scratch(m, n_act) : 0);
-  APX_ALLOC(ctx, buf, (dc1 ? 2 : 1) * bytes_A + bytes_anch + bytes_slope + bytes_more);
+  const bool packed = packed_forces(n, n_act);
+  const size_t bytes_fp = packed ? whole(sizeof(double) * 4 * (size_t)n) : 0;
+  APX_ALLOC(ctx, buf, (dc1 ? 2 : 1) * bytes_A + bytes_anch + bytes_slope + bytes_fp + bytes_more);
   char* p = static_cast<char*>(buf.p);
   auto take = [&](size_t b) {
     char* at = p;
@@ -509,7 +581,9 @@ apx_status ace_run(apx_ctx* ctx, const apx_atoms* atoms, const apx_nlist* nl, co
   sc.e_anch = reinterpret_cast<double*>(take(bytes_anch));
   sc.fp_anch = sc.e_anch + n_act;
   T* slope = dc1 ? reinterpret_cast<T*>(take(bytes_slope)) : nullptr;
+  double* fp = packed ? reinterpret_cast<double*>(take(bytes_fp)) : nullptr;
   void* more = p;
+  if (packed) k_fill_zero<<<blocks_for(4LL * n, 256), 256, 0, ctx->stream>>>(fp, 4LL * n);
   BoxDev b = make_box(atoms);
   AnchorDev an{};
   an.on = m->anchored;
@@ -524,27 +598,37 @@ apx_status ace_run(apx_ctx* ctx, const apx_atoms* atoms, const apx_nlist* nl, co
   }
   const T rc = (T)m->r_cut, inv_h = (T)(1.0 / m->h);
   const double rc2 = m->r_cut * m->r_cut;
-  const size_t lds1 = BasisLds<T, LMAX>::bytes();
+  auto by_radial = [&](auto body) {
+    if (m->n_max <= 8) body(std::integral_constant<int, 8>{});
+    else if (m->n_max <= 10) body(std::integral_constant<int, 10>{});
+    else body(std::integral_constant<int, 12>{});
+  };
   {
-  ProfScope ps(ctx, "ace.basis");
-  k_ace_basis<T, LMAX><<<n_act, 64, lds1, ctx->stream>>>(atoms->pos, n, b, nl->count, nl->idx, nl->max_nb, active,
-                                                         n_act, m->n_max, rc, inv_h, rc2, tb.Wp, an, sc);
-  APX_LAUNCH_CHECK(ctx);
+    ProfScope ps(ctx, "ace.basis");
+    by_radial([&](auto nmax_c) {
+      constexpr int NM = decltype(nmax_c)::value;
+      k_ace_basis<T, LMAX, NM><<<n_act, 64, BasisLds<T, LMAX, NM>::bytes(), ctx->stream>>>(
+          atoms->pos, n, b, nl->count, nl->idx, nl->max_nb, active, n_act, m->n_max, rc, inv_h, rc2, tb.Wp, an, sc);
+    });
+    APX_LAUNCH_CHECK(ctx);
   }
   apx_status s = sym_products<T>(ctx, m, sc.A, B, slope, n_act, sc.e_anch, active, e_site, more);
   if (s == APX_OK && dc1) s = ace_grad<T>(ctx, m, sc.A, slope, w, active, n_act, dc1, dc2, more);
   if (s != APX_OK) return s;
   ProfScope ps(ctx, "ace.force");
-  auto force = [&](auto nmax_c) {
+  by_radial([&](auto nmax_c) {
     constexpr int NM = decltype(nmax_c)::value;
     const size_t lds3 = sizeof(T) * (size_t)ForceLds<T, NM>::KP * LM;
-    k_ace_force<T, LMAX, NM><<<n_act, 64, lds3, ctx->stream>>>(atoms->pos, n, b, nl->count, nl->idx, nl->max_nb,
-                                                               active, n_act, m->n_max, rc, inv_h, rc2, an, sc, w,
-                                                               f, w2, f2);
-  };
-  if (m->n_max <= 8) force(std::integral_constant<int, 8>{});
-  else if (m->n_max <= 10) force(std::integral_constant<int, 10>{});
-  else force(std::integral_constant<int, 12>{});
+    auto launch = [&](auto kern, double* out) {
+      kern<<<n_act, 64, lds3, ctx->stream>>>(atoms->pos, n, b, nl->count, nl->idx, nl->max_nb, active, n_act, m->n_max,
+                                             rc, inv_h, rc2, an, sc, w, out, w2, f2);
+    };
+    if (packed)
+      launch(k_ace_force<T, LMAX, NM, true>, fp);
+    else
+      launch(k_ace_force<T, LMAX, NM, false>, f);
+  });
+  if (packed) k_unpack<<<blocks_for(n, 256), 256, 0, ctx->stream>>>(fp, n, f);
   APX_LAUNCH_CHECK(ctx);
   return APX_OK;
 }
@@ -576,7 +660,7 @@ apx_status ace_impl(apx_ctx* ctx, const apx_atoms* atoms, const apx_nlist* nl, c
   if (n > 0 && (!e_site || !f)) return fail(ctx, APX_EINVAL, "e_site and f are required");
   if (n_active > 0 && !active) return fail(ctx, APX_EINVAL, "active is NULL");
   if (n > 0) {
-    k_fill_zero<<<blocks_for(3LL * n, 256), 256, 0, ctx->stream>>>(f, 3LL * n);
+    if (!packed_forces(n, (int)n_active)) k_fill_zero<<<blocks_for(3LL * n, 256), 256, 0, ctx->stream>>>(f, 3LL * n);
     k_fill_zero<<<blocks_for(n, 256), 256, 0, ctx->stream>>>(e_site, n);
     if (f2) k_fill_zero<<<blocks_for(3LL * n, 256), 256, 0, ctx->stream>>>(f2, 3LL * n);
     APX_LAUNCH_CHECK(ctx);

@@ -170,6 +170,30 @@ __device__ __forceinline__ void sparse_atomic_max(unsigned long long* p, unsigne
   if (v > __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(p, v);
 }
 
+// Sum over the wave without the LDS: pairs of lanes by quad permutations (1, 2), half-row and row
+// mirrors (the quads, then the half rows, hold equal sums by then), row and half-wave swaps.
+template <int CTRL>
+__device__ __forceinline__ double dpp_double(double v) {
+  const int lo = __double2loint(v), hi = __double2hiint(v);
+  return __hiloint2double(__builtin_amdgcn_update_dpp(hi, hi, CTRL, 0xf, 0xf, false),
+                          __builtin_amdgcn_update_dpp(lo, lo, CTRL, 0xf, 0xf, false));
+}
+__device__ __forceinline__ double wave_sum_dpp(double v) {
+  v += dpp_double<0xB1>(v);
+  v += dpp_double<0x4E>(v);
+  v += dpp_double<0x141>(v);
+  v += dpp_double<0x140>(v);
+  unsigned lo = (unsigned)__double2loint(v), hi = (unsigned)__double2hiint(v);
+  const auto l16 = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+  const auto h16 = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+  v = __hiloint2double((int)h16[0], (int)l16[0]) + __hiloint2double((int)h16[1], (int)l16[1]);
+  lo = (unsigned)__double2loint(v);
+  hi = (unsigned)__double2hiint(v);
+  const auto l32 = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
+  const auto h32 = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+  return __hiloint2double((int)h32[0], (int)l32[0]) + __hiloint2double((int)h32[1], (int)l32[1]);
+}
+
 template <class T>
 __device__ __forceinline__ T wave_sum(T v) {
 #pragma unroll

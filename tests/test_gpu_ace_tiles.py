@@ -117,3 +117,31 @@ def test_gradient_of_many_chunks(env):
         parts = sum(ops.ace_energy_forces(ctx, atoms, nl, model, p, None, "fp64", want_dc=True)[key]
                     for p in every.split(700))
         assert (one[key] - parts).abs().max().item() < 1e-12 * one[key].abs().max().item()
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("n_max,l_max,anchored", [(10, 4, True), (9, 4, False), (8, 3, True), (12, 3, False)])
+def test_dense_rows(env, precision, n_max, l_max, anchored):
+    """A crystal compressed by 15 % along each axis: more neighbours inside the cutoff than the atomic
+    base takes at a time (48), and rows of more than 64.  The tolerances are scaled by the largest force
+    over that of the crystal at rest (about 1 eV/A)."""
+    ops, ctx = env[0], env[1]
+    print(f"[case] dense rows n_max {n_max} l_max {l_max} {precision}", flush=True)
+    s = configs.slab100(4, 4, 5, seed=78, frozen_planes=0, sigma=0.05, velocities=False)
+    s = synth.System(s.pos * 0.85, s.lo * 0.85, s.hi * 0.85, s.periodic)
+    atoms = ops.device_atoms(s)
+    nl = ops.build_neighbors(ctx, atoms, 5.5, max_nb=128)
+    i, j = geometry.pairs_within(s.pos, s.lo, s.hi, s.periodic, 5.0)
+    assert np.bincount(i).max() > 64 and nl.needed > 64
+    prm = synth.ace_random(n_max, l_max, oace.num_basis(n_max, l_max), seed=6, anchored=anchored)
+    sites = np.arange(s.n)
+    w = np.random.default_rng(3).uniform(0.1, 1.0, s.n)
+    out = ops.ace_energy_forces(ctx, atoms, nl, ops.AceModel(ctx, prm),
+                                torch.as_tensor(sites.astype(np.int32), device="cuda"),
+                                torch.as_tensor(w, device="cuda"), precision)
+    pt = torch.tensor(s.pos, dtype=torch.float64, requires_grad=True)
+    e = oace.site_energies(pt, s.box, s.periodic, i, j, prm, s.n, sites)
+    (g,) = torch.autograd.grad((torch.as_tensor(w) * e).sum(), pt)
+    tol = TOL[precision] * max(1.0, float(g.abs().max()))
+    assert np.abs(out["e_site"].cpu().numpy() - e.detach().numpy()).max() < tol
+    assert np.abs(out["f"].cpu().numpy() + g.numpy()).max() < tol
