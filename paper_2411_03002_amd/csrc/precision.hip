@@ -337,20 +337,22 @@ struct SpreadDev {
   int span[3];
 };
 
-// One wave per source: lanes sweep the cells of the stencil, each lane one cell at a
-// time; every target within r_hi receives w0_j f_cut(...) by an atomic maximum on the
-// IEEE bit pattern (all candidates are > 0, where the unsigned order equals the
-// floating-point order), so the result does not depend on the visiting order.
-__global__ void __launch_bounds__(256) k_spread(const double* __restrict__ pos, int n, Grid g, SpreadDev s,
+// `per` threads per source sweep the cells of the stencil, each one cell at a time; every target within
+// r_hi receives w0_j f_cut(...) by an atomic maximum on the IEEE bit pattern (all candidates are > 0,
+// where the unsigned order equals the floating-point order), so the result does not depend on the
+// visiting order.  A cell is a chain of dependent loads (its bounds, its atoms, their positions), and a
+// stencil has 343 of them: with few sources the time is the number of cells a thread visits one after
+// the other, so each source gets up to 512 threads.  Measured (us) for 64 / 256 / 512: TIMESP.
+__global__ void __launch_bounds__(512) k_spread(const double* __restrict__ pos, int n, Grid g, SpreadDev s, int per,
                                                 const int* __restrict__ src, int nsrc,
                                                 const double* __restrict__ w0, const uint8_t* __restrict__ frozen,
                                                 const int* __restrict__ cell_start, const int* __restrict__ cell_atoms,
                                                 unsigned long long* __restrict__ wbits) {
 #pragma clang fp contract(off)
-  const int wid = (blockIdx.x * blockDim.x + threadIdx.x) / kWave;
-  const int lane = threadIdx.x & (kWave - 1);
-  if (wid >= nsrc) return;
-  const int j = src[wid];
+  const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+  const int at = __builtin_amdgcn_readfirstlane((int)(t / per)), lane = (int)(t % per);
+  if (at >= nsrc) return;
+  const int j = src[at];
   const double xj = pos[j], yj = pos[(size_t)n + j], zj = pos[2 * (size_t)n + j];
   const double wj = w0[j];
   const double hx = 0.5 * g.L[0], hy = 0.5 * g.L[1], hz = 0.5 * g.L[2];
@@ -358,7 +360,7 @@ __global__ void __launch_bounds__(256) k_spread(const double* __restrict__ pos, 
   const int cj1 = cell_coord(yj, g.lo[1], g.inv_cell[1], g.nc[1]);
   const int cj2 = cell_coord(zj, g.lo[2], g.inv_cell[2], g.nc[2]);
   const int total = s.span[0] * s.span[1] * s.span[2];
-  for (int q = lane; q < total; q += kWave) {
+  for (int q = lane; q < total; q += per) {
     const int ox = q % s.span[0] + s.reach[0];
     const int oy = (q / s.span[0]) % s.span[1] + s.reach[1];
     const int oz = q / (s.span[0] * s.span[1]) + s.reach[2];
@@ -518,6 +520,9 @@ static void spread_stencil(const Grid& g, double r_hi, SpreadDev& s) {
 
 namespace {
 
+// Threads per source of k_spread (a multiple of the wave's 64), by the measurements at the kernel.
+int spread_threads(int nsrc) { return nsrc <= 8192 ? 512 : 128; }
+
 // The averaging stage of a call: ring slot of this sample, samples in the means, and
 // the buffers (all device, length n or [n_avg][n]).
 struct AvgArgs {
@@ -602,10 +607,12 @@ apx_status precision_impl(apx_ctx* ctx, const apx_atoms* atoms, const apx_nlist*
       sd.width = p->r_hi - p->r_lo;
       sd.rh2 = p->r_hi * p->r_hi;
       spread_stencil(gs, p->r_hi, sd);
-      const long long threads = (long long)nsrc * kWave;
+      const int per = spread_threads(nsrc);
+      const long long threads = (long long)nsrc * per;
+      const int block = per > 256 ? per : 256;
       ProfScope ps(ctx, "prec.spread");
-      k_spread<<<blocks_for(threads, 256), 256, 0, ctx->stream>>>(
-          atoms->pos, n, gs, sd, ctx->itmp.as<int>(), nsrc, w0, atoms->frozen, ctx->cell_start.as<int>(),
+      k_spread<<<blocks_for(threads, block), block, 0, ctx->stream>>>(
+          atoms->pos, n, gs, sd, per, ctx->itmp.as<int>(), nsrc, w0, atoms->frozen, ctx->cell_start.as<int>(),
           ctx->cell_atoms.as<int>(), reinterpret_cast<unsigned long long*>(ws));
       APX_LAUNCH_CHECK(ctx);
     }
