@@ -46,6 +46,12 @@ Grid make_grid(const apx_atoms* a, double min_cell) {
 }
 
 // ------------------------------------------------------------------- binning
+__global__ void k_bin_clear(int* __restrict__ p, long long m, int* __restrict__ flags) {
+  const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < m) p[i] = 0;
+  else if (i < m + 4) flags[i - m] = 0;
+}
+
 __global__ void k_bin_count(const double* __restrict__ pos, int n, Grid g, int* __restrict__ cell_id,
                             int* __restrict__ counts, int* __restrict__ flags) {
   int i = blockIdx.x * blockDim.x + threadIdx.x;
@@ -77,24 +83,25 @@ apx_status bin_atoms(apx_ctx* ctx, const apx_atoms* a, const Grid& g) {
   int n = (int)a->n;
   long long nc = g.ncell();
   APX_ALLOC(ctx, ctx->cell_id, sizeof(int) * (size_t)(n > 0 ? n : 1));
-  APX_ALLOC(ctx, ctx->cell_count, sizeof(int) * (size_t)nc);
   APX_ALLOC(ctx, ctx->cell_start, sizeof(int) * (size_t)(nc + 1));
-  APX_ALLOC(ctx, ctx->cell_fill, sizeof(int) * (size_t)nc);
   APX_ALLOC(ctx, ctx->cell_atoms, sizeof(int) * (size_t)(n > 0 ? n : 1));
   APX_ALLOC(ctx, ctx->flags, sizeof(int) * 4);
-  APX_HIP(ctx, hipMemsetAsync(ctx->cell_count.p, 0, sizeof(int) * nc, ctx->stream));
-  APX_HIP(ctx, hipMemsetAsync(ctx->cell_fill.p, 0, sizeof(int) * nc, ctx->stream));
-  APX_HIP(ctx, hipMemsetAsync(ctx->flags.p, 0, sizeof(int) * 4, ctx->stream));
+  // counts and slots side by side: one launch clears them and the flags
+  APX_ALLOC(ctx, ctx->cell_count, sizeof(int) * 2 * (size_t)nc);
+  int* counts = ctx->cell_count.as<int>();
+  int* fill = counts + nc;
+  k_bin_clear<<<blocks_for(2 * nc + 4, 256), 256, 0, ctx->stream>>>(counts, 2 * nc, ctx->flags.as<int>());
+  APX_LAUNCH_CHECK(ctx);
   if (n > 0) {
-    k_bin_count<<<blocks_for(n, 256), 256, 0, ctx->stream>>>(a->pos, n, g, ctx->cell_id.as<int>(),
-                                                            ctx->cell_count.as<int>(), ctx->flags.as<int>());
+    k_bin_count<<<blocks_for(n, 256), 256, 0, ctx->stream>>>(a->pos, n, g, ctx->cell_id.as<int>(), counts,
+                                                            ctx->flags.as<int>());
     APX_LAUNCH_CHECK(ctx);
   }
-  apx_status s = scan_exclusive(ctx, ctx->cell_count.as<int>(), nc, ctx->cell_start.as<int>());
+  apx_status s = scan_exclusive(ctx, counts, nc, ctx->cell_start.as<int>());
   if (s != APX_OK) return s;
   if (n > 0) {
     k_bin_fill<<<blocks_for(n, 256), 256, 0, ctx->stream>>>(n, ctx->cell_id.as<int>(), ctx->cell_start.as<int>(),
-                                                           ctx->cell_fill.as<int>(), ctx->cell_atoms.as<int>());
+                                                           fill, ctx->cell_atoms.as<int>());
     APX_LAUNCH_CHECK(ctx);
   }
   return APX_OK;
@@ -181,23 +188,47 @@ __global__ void __launch_bounds__(kScanThreads) k_scan_apply(const int* __restri
   }
 }
 
+// The whole scan by one block, sixteen values per thread: one launch of 3 us (860 values; 9,261: 6.5)
+// against three that take 8 to 12 us and the gaps between them.
+constexpr int kScanOnePer = 16;
+constexpr int kScanOne = kScanThreads * kScanOnePer;
+
+__global__ void __launch_bounds__(kScanThreads) k_scan_one(const int* __restrict__ in, int m, int* __restrict__ out) {
+  __shared__ int sh[kScanThreads / kWave + 1];
+  const int per = (m + kScanThreads - 1) / kScanThreads;  // values per thread, at most kScanOnePer
+  const int base = (int)threadIdx.x * per;
+  int vals[kScanOnePer];
+  int s = 0;
+#pragma unroll
+  for (int k = 0; k < kScanOnePer; ++k) {
+    vals[k] = k < per && base + k < m ? in[base + k] : 0;
+    s += vals[k];
+  }
+  int tot;
+  int ex = block_exclusive_scan(s, sh, &tot);
+#pragma unroll
+  for (int k = 0; k < kScanOnePer; ++k) {
+    if (k < per && base + k < m) out[base + k] = ex;
+    ex += vals[k];
+  }
+  if (threadIdx.x == 0) out[m] = tot;
+}
+
 apx_status scan_exclusive(apx_ctx* ctx, const int* in, long long m, int* out) {
-  long long nb = (m + kScanChunk - 1) / kScanChunk;
-  if (nb < 1) nb = 1;
+  if (m <= kScanOne) {
+    k_scan_one<<<1, kScanThreads, 0, ctx->stream>>>(in, (int)m, out);
+    APX_LAUNCH_CHECK(ctx);
+    return APX_OK;
+  }
+  const long long nb = (m + kScanChunk - 1) / kScanChunk;
   APX_ALLOC(ctx, ctx->scan_tmp, sizeof(int) * (size_t)(nb + 1));
   int* sums = ctx->scan_tmp.as<int>();
-  if (m > 0) {
-    k_scan_reduce<<<(unsigned)nb, kScanThreads, 0, ctx->stream>>>(in, m, sums);
-    APX_LAUNCH_CHECK(ctx);
-  } else {
-    APX_HIP(ctx, hipMemsetAsync(sums, 0, sizeof(int), ctx->stream));
-  }
+  k_scan_reduce<<<(unsigned)nb, kScanThreads, 0, ctx->stream>>>(in, m, sums);
+  APX_LAUNCH_CHECK(ctx);
   k_scan_sums<<<1, kScanThreads, 0, ctx->stream>>>(sums, (int)nb, out + m);
   APX_LAUNCH_CHECK(ctx);
-  if (m > 0) {
-    k_scan_apply<<<(unsigned)nb, kScanThreads, 0, ctx->stream>>>(in, m, sums, out);
-    APX_LAUNCH_CHECK(ctx);
-  }
+  k_scan_apply<<<(unsigned)nb, kScanThreads, 0, ctx->stream>>>(in, m, sums, out);
+  APX_LAUNCH_CHECK(ctx);
   return APX_OK;
 }
 
