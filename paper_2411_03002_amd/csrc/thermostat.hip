@@ -421,11 +421,13 @@ __global__ void __launch_bounds__(kThThreads) k_th_groups(ThermoArgs A, SearchGr
   if (tid == 0) gsz[blockIdx.x] = taken < stride ? taken : stride;  // taken = need_max <= stride
 }
 
-// Sum over the workgroup of three values, in a fixed order (the waves' sums in wave order).
+// Sum over the workgroup of three values, in a fixed order (the waves' sums in wave order).  The sums
+// lie on a cell's chain of corrections: without the LDS permutation's round trips a colour's launch took
+// 1.15 ms instead of 1.29 (256,000 atoms, 11,171 corrections).
 __device__ __forceinline__ void block_sum3(double& a, double& b, double& c, double* sh) {
-  a = wave_sum(a);
-  b = wave_sum(b);
-  c = wave_sum(c);
+  a = wave_sum_dpp(a);
+  b = wave_sum_dpp(b);
+  c = wave_sum_dpp(c);
   constexpr int nw = kThThreads / kWave;
   const int w = threadIdx.x / kWave;
   if ((threadIdx.x & (kWave - 1)) == 0) {
@@ -446,7 +448,7 @@ __device__ __forceinline__ void block_sum3(double& a, double& b, double& c, doub
 }
 
 __device__ __forceinline__ double block_sum1(double v, double* sh) {
-  v = wave_sum(v);
+  v = wave_sum_dpp(v);
   constexpr int nw = kThThreads / kWave;
   if ((threadIdx.x & (kWave - 1)) == 0) sh[threadIdx.x / kWave] = v;
   __syncthreads();
