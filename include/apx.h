@@ -426,6 +426,13 @@ apx_status apx_mlp_forward(apx_ctx* ctx, const apx_mlp* m, const float* feat, in
  * of feat/target: grad [APX_MLP_PARAMS] and *loss (device) overwritten. */
 apx_status apx_mlp_gradients(apx_ctx* ctx, apx_mlp* m, const float* feat, const float* target,
                              const int32_t* sel, int64_t nb, float* grad, float* loss);
+/* The same with a workspace (device, apx_mlp_work_size(nb) floats, contents unspecified): faster,
+ * and the sums are added in a fixed order, so that they repeat bit for bit and are those of
+ * apx_mlp_train_step.  Neither form writes to anything but its arguments: calls on several
+ * streams are independent, for one network too, where each has its own outputs and workspace. */
+int64_t apx_mlp_work_size(int64_t nb);
+apx_status apx_mlp_gradients_ws(apx_ctx* ctx, apx_mlp* m, const float* feat, const float* target,
+                                const int32_t* sel, int64_t nb, float* grad, float* loss, float* work);
 /* Adam update of the parameters with grad (bias-corrected; the step counter is kept in m);
  * grad is cleared. */
 apx_status apx_mlp_adam_step(apx_ctx* ctx, apx_mlp* m, const float* grad, float lr, float beta1,

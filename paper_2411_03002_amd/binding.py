@@ -130,6 +130,8 @@ PROTOTYPES = {
     "apx_features": (C.c_int32, [_P, C.POINTER(Atoms), C.POINTER(NList), _P, _P, _P, _P]),
     "apx_mlp_forward": (C.c_int32, [_P, _P, _P, C.c_int64, _P]),
     "apx_mlp_gradients": (C.c_int32, [_P, _P, _P, _P, _P, C.c_int64, _P, _P]),
+    "apx_mlp_work_size": (C.c_int64, [C.c_int64]),
+    "apx_mlp_gradients_ws": (C.c_int32, [_P, _P, _P, _P, _P, C.c_int64, _P, _P, _P]),
     "apx_mlp_adam_step": (C.c_int32, [_P, _P, _P, C.c_float, C.c_float, C.c_float, C.c_float]),
     "apx_mlp_train_step": (C.c_int32, [_P, _P, _P, _P, _P, C.c_int64, C.c_float, _P]),
     "apx_mlp_infer_bf16": (C.c_int32, [_P, _P, _P, C.c_int64, _P]),

@@ -38,11 +38,12 @@ struct Std4 {
 
 struct apx_mlp {
   int device = 0;
-  apx::DevBuf buf;    // params, m, v, loss, bf16 weights
+  apx::DevBuf buf;    // params, m, v, loss, bf16 weights, sums of a training step
   float* params = nullptr;
   float* m = nullptr;
   float* v = nullptr;
   float* loss = nullptr;
+  float* sums = nullptr;         // [kPassBlocks][kSlabLd]
   unsigned short* wb = nullptr;  // bf16: W1 padded [64][16], W2 [64][64], W3 [64][64], W4 [64]
   bool wb_valid = false;
   long long step = 0;
@@ -106,14 +107,18 @@ __global__ void __launch_bounds__(64 * W) k_features(const double* __restrict__ 
 // own neuron of the layer below), the activations pass through LDS, and an accumulator's rows are
 // samples, so that a wave meets its own activations again in the backward pass.  The weight
 // gradients are products delta^T H over the samples, accumulated in registers over the tiles;
-// every block writes its own sums (no atomics) and k_mlp_sum adds them in a fixed order.
+// every block writes its own sums (no atomics) and k_mlp_sum adds them in a fixed order.  Those sums are
+// the caller's workspace or, for a training step, the network's: passes of other networks, streams and
+// contexts run at the same time.  Without a workspace the blocks add to the outputs by atomics.
 // Latency-bound (a chain of six small products a tile); at a batch of 4,096 the pass that read
 // both factors of every multiply-add from LDS took 59 us on 64 blocks and needed its outputs
-// cleared (9 us); this one 17 us on 256 blocks, the sum 4 us.
+// cleared (9 us); this one 17 us on 256 blocks, the sum 4 us.  Without a workspace 32 us on 128 blocks
+// (33 on 64, 44 on 256; 16,384 samples 88 / 59 / 57 on 64 / 128 / 256).
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 constexpr int kTile = 16;                 // samples
 constexpr int kActLd = kH + 4;            // activation rows in LDS: sixteen samples x four k on distinct banks
 constexpr int kPassBlocks = 256;          // blocks of a gradient pass
+constexpr int kAtomicBlocks = 128;        // of one without a workspace
 constexpr int kSlabLd = kNParams + 7;     // a block's sums: the parameters, then the loss
 
 __device__ __forceinline__ f32x4 mma(float a, float b, f32x4 c) {
@@ -147,11 +152,13 @@ __device__ __forceinline__ void outer(const float* delta, const float* act, int 
 }
 
 // With BWD the block writes its share of the gradient of the mean squared error (mean over
-// `total` samples) and of the error to its row of `slab`; otherwise the outputs to `out`.
-template <bool BWD>
+// `total` samples) and of the error to its row of `slab`, or adds them to grad and loss (ATOMIC);
+// otherwise the outputs to `out`.
+template <bool BWD, bool ATOMIC = false>
 __global__ void __launch_bounds__(256) k_mlp_pass(const float* __restrict__ feat, const float* __restrict__ target,
                                                   const int* __restrict__ sel, int nb, int total,
                                                   const float* __restrict__ P, Std4 st, float* __restrict__ slab,
+                                                  float* __restrict__ grad, float* __restrict__ loss,
                                                   float* __restrict__ out) {
   constexpr int NB = BWD ? 5 : 2;
   __shared__ float X[kTile][8];
@@ -262,16 +269,20 @@ __global__ void __launch_bounds__(256) k_mlp_pass(const float* __restrict__ feat
     __syncthreads();
   }
   if constexpr (BWD) {
-    float* S = slab + (size_t)blockIdx.x * kSlabLd;
+    auto put = [&](int i, float v) {
+      if constexpr (!ATOMIC) slab[(size_t)blockIdx.x * kSlabLd + i] = v;
+      else if (i == kNParams) atomicAdd(loss, v / (float)total);
+      else atomicAdd(grad + i, v);
+    };
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       const int row = 16 * wv + 4 * r + q;
 #pragma unroll
       for (int kt = 0; kt < 4; ++kt) {
-        S[kOffW2 + row * kH + 16 * kt + c] = g2[kt][q];
-        S[kOffW3 + row * kH + 16 * kt + c] = g3[kt][q];
+        put(kOffW2 + row * kH + 16 * kt + c, g2[kt][q]);
+        put(kOffW3 + row * kH + 16 * kt + c, g3[kt][q]);
       }
-      if (c < kIn) S[kOffW1 + row * kIn + c] = g1[q];
+      if (c < kIn) put(kOffW1 + row * kIn + c, g1[q]);
     }
     auto over_rows = [](float v) {
       v += __shfl_xor(v, 16, kWave);
@@ -282,17 +293,17 @@ __global__ void __launch_bounds__(256) k_mlp_pass(const float* __restrict__ feat
     gb3 = over_rows(gb3);
     g4 = over_rows(g4);
     if (r == 0) {
-      S[kOffB1 + j] = gb1;
-      S[kOffB2 + j] = gb2;
-      S[kOffB3 + j] = gb3;
-      S[kOffW4 + j] = g4;
+      put(kOffB1 + j, gb1);
+      put(kOffB2 + j, gb2);
+      put(kOffB3 + j, gb3);
+      put(kOffW4 + j, g4);
     }
     if (wv == 0) {
       gb4 = wave_sum(gb4);
       err = wave_sum(err);
       if (lane == 0) {
-        S[kOffB4] = gb4;
-        S[kNParams] = err;
+        put(kOffB4, gb4);
+        put(kNParams, err);
       }
     }
   }
@@ -332,6 +343,12 @@ __global__ void __launch_bounds__(256) k_mlp_sum(const float* __restrict__ slab,
   if (i == kNParams) *loss = v / (float)total;
   else if (ADAM) adam(a, i, v);
   else grad[i] = v;
+}
+
+__global__ void k_mlp_clear(float* __restrict__ grad, float* __restrict__ loss) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < kNParams) grad[i] = 0.f;
+  else if (i == kNParams) *loss = 0.f;
 }
 
 // Adam with bias correction; clears the gradient for the next step.
@@ -577,7 +594,9 @@ apx_status apx_mlp_create(apx_ctx* ctx, const float* params, const float* mu, co
   m->device = ctx->device;
   const size_t nf = 3 * (size_t)kNParams + 61;  // the bfloat16 weights behind on 16 bytes
   const size_t nwb = kH * 16 + 2 * kH * kH + kH;
-  if (m->buf.ensure(nf * sizeof(float) + nwb * sizeof(unsigned short)) != hipSuccess) {
+  static_assert((kH * 16 + 2 * kH * kH + kH) % 2 == 0, "the sums behind the bfloat16 weights lie on floats");
+  if (m->buf.ensure((nf + (size_t)kPassBlocks * kSlabLd) * sizeof(float) + nwb * sizeof(unsigned short)) !=
+      hipSuccess) {
     delete m;
     return fail(ctx, APX_ENOMEM, "MLP buffers");
   }
@@ -587,6 +606,7 @@ apx_status apx_mlp_create(apx_ctx* ctx, const float* params, const float* mu, co
   m->v = base + 2 * kNParams;
   m->loss = base + 3 * kNParams;
   m->wb = reinterpret_cast<unsigned short*>(base + nf);
+  m->sums = reinterpret_cast<float*>(m->wb + nwb);
   for (int c = 0; c < 4; ++c) {
     m->st.mu[c] = mu[c];
     m->st.sd[c] = sd[c];
@@ -652,7 +672,7 @@ apx_status apx_mlp_forward(apx_ctx* ctx, const apx_mlp* m, const float* feat, in
   if (!feat || !out) return fail(ctx, APX_EINVAL, "feat and out are required");
   const int blocks = (int)std::min<int64_t>(8 * kPassBlocks, blocks_for(n, kTile));
   k_mlp_pass<false><<<blocks, 256, 0, ctx->stream>>>(feat, nullptr, nullptr, (int)n, (int)n, m->params, m->st, nullptr,
-                                                     out);
+                                                     nullptr, nullptr, out);
   APX_LAUNCH_CHECK(ctx);
   return APX_OK;
 }
@@ -661,14 +681,21 @@ apx_status apx_mlp_forward(apx_ctx* ctx, const apx_mlp* m, const float* feat, in
 
 namespace {
 
-// The gradient pass over the batch: one row of sums per block in the context's scratch.
+// Blocks of a gradient pass over nb samples; each writes one row of sums.
+int pass_blocks(int64_t nb) { return (int)std::min<int64_t>(kPassBlocks, blocks_for(nb, kTile)); }
+
+// The pass over the batch: rows of sums to `slab`, or (null) sums into grad and loss.
 apx_status mlp_pass(apx_ctx* ctx, const apx_mlp* m, const float* feat, const float* target, const int32_t* sel,
-                    int64_t nb, int* nblk) {
-  *nblk = (int)std::min<int64_t>(kPassBlocks, blocks_for(nb, kTile));
-  APX_ALLOC(ctx, ctx->mlp_sums, sizeof(float) * (size_t)*nblk * kSlabLd);
+                    int64_t nb, float* slab, float* grad, float* loss) {
   ProfScope ps(ctx, "mlp.train");
-  k_mlp_pass<true><<<*nblk, 256, 0, ctx->stream>>>(feat, target, sel, (int)nb, (int)nb, m->params, m->st,
-                                                   ctx->mlp_sums.as<float>(), nullptr);
+  auto launch = [&](auto kern, int blocks) {
+    kern<<<blocks, 256, 0, ctx->stream>>>(feat, target, sel, (int)nb, (int)nb, m->params, m->st, slab, grad, loss,
+                                          nullptr);
+  };
+  if (slab)
+    launch(k_mlp_pass<true>, pass_blocks(nb));
+  else
+    launch(k_mlp_pass<true, true>, std::min(kAtomicBlocks, pass_blocks(nb)));
   APX_LAUNCH_CHECK(ctx);
   return APX_OK;
 }
@@ -685,18 +712,30 @@ constexpr int kSumBlocks = (kNParams + 1 + 31) / 32;
 
 extern "C" {
 
-apx_status apx_mlp_gradients(apx_ctx* ctx, apx_mlp* m, const float* feat, const float* target, const int32_t* sel,
-                             int64_t nb, float* grad, float* loss) {
+int64_t apx_mlp_work_size(int64_t nb) {
+  return nb <= 0 || nb > 0x7fffffff ? 0 : (int64_t)pass_blocks(nb) * kSlabLd;
+}
+
+apx_status apx_mlp_gradients_ws(apx_ctx* ctx, apx_mlp* m, const float* feat, const float* target, const int32_t* sel,
+                                int64_t nb, float* grad, float* loss, float* work) {
   if (!ctx || !m) return APX_EINVAL;
   if (nb <= 0 || nb > 0x7fffffff) return fail(ctx, APX_EINVAL, "batch size must be positive");
   if (!feat || !target || !grad || !loss) return fail(ctx, APX_EINVAL, "feat, target, grad and loss are required");
-  int nblk = 0;
-  const apx_status s = mlp_pass(ctx, m, feat, target, sel, nb, &nblk);
+  if (!work) {
+    k_mlp_clear<<<blocks_for(kNParams + 1, 256), 256, 0, ctx->stream>>>(grad, loss);
+    APX_LAUNCH_CHECK(ctx);
+    return mlp_pass(ctx, m, feat, target, sel, nb, nullptr, grad, loss);
+  }
+  const apx_status s = mlp_pass(ctx, m, feat, target, sel, nb, work, nullptr, nullptr);
   if (s != APX_OK) return s;
-  k_mlp_sum<false><<<kSumBlocks, 256, 0, ctx->stream>>>(ctx->mlp_sums.as<float>(), nblk, (int)nb, grad, loss,
-                                                        AdamArgs{});
+  k_mlp_sum<false><<<kSumBlocks, 256, 0, ctx->stream>>>(work, pass_blocks(nb), (int)nb, grad, loss, AdamArgs{});
   APX_LAUNCH_CHECK(ctx);
   return APX_OK;
+}
+
+apx_status apx_mlp_gradients(apx_ctx* ctx, apx_mlp* m, const float* feat, const float* target, const int32_t* sel,
+                             int64_t nb, float* grad, float* loss) {
+  return apx_mlp_gradients_ws(ctx, m, feat, target, sel, nb, grad, loss, nullptr);
 }
 
 apx_status apx_mlp_adam_step(apx_ctx* ctx, apx_mlp* m, const float* grad, float lr, float beta1, float beta2,
@@ -715,11 +754,10 @@ apx_status apx_mlp_train_step(apx_ctx* ctx, apx_mlp* m, const float* feat, const
   if (!ctx || !m) return APX_EINVAL;
   if (nb <= 0 || nb > 0x7fffffff) return fail(ctx, APX_EINVAL, "batch size must be positive");
   if (!feat || !target) return fail(ctx, APX_EINVAL, "feat and target are required");
-  int nblk = 0;
-  const apx_status s = mlp_pass(ctx, m, feat, target, sel, nb, &nblk);
+  const apx_status s = mlp_pass(ctx, m, feat, target, sel, nb, m->sums, nullptr, nullptr);
   if (s != APX_OK) return s;
   m->step += 1;
-  k_mlp_sum<true><<<kSumBlocks, 256, 0, ctx->stream>>>(ctx->mlp_sums.as<float>(), nblk, (int)nb, nullptr,
+  k_mlp_sum<true><<<kSumBlocks, 256, 0, ctx->stream>>>(m->sums, pass_blocks(nb), (int)nb, nullptr,
                                                        loss ? loss : m->loss, adam_args(m, lr, 0.9f, 0.999f, 1e-8f));
   APX_LAUNCH_CHECK(ctx);
   m->wb_valid = false;

@@ -520,6 +520,18 @@ class Mlp:
         ctx._check(ctx.lib.apx_mlp_create(ctx.h, p.ctypes.data, mu.ctypes.data, sd.ctypes.data, C.byref(h)))
         self.h = h
         self.loss = torch.zeros(1, dtype=torch.float32, device=ctx.torch_device)
+        self._work = {}  # stream handle -> workspace of its gradient calls
+
+    def _workspace(self, nb: int) -> torch.Tensor:
+        # one per stream, kept with the network; under capture one of the graph's own
+        n = self.ctx.lib.apx_mlp_work_size(nb)
+        if torch.cuda.is_current_stream_capturing():
+            return torch.empty(n, dtype=torch.float32, device=self.ctx.torch_device)
+        stream = torch.cuda.current_stream(self.ctx.torch_device).cuda_stream
+        work = self._work.get(stream)
+        if work is None or work.numel() < n:
+            work = self._work[stream] = torch.empty(n, dtype=torch.float32, device=self.ctx.torch_device)
+        return work
 
     def params(self) -> np.ndarray:
         out = np.empty(self.N_PARAMS, dtype=np.float32)
@@ -542,8 +554,9 @@ class Mlp:
         self.ctx.bind_stream()
         g = torch.empty(self.N_PARAMS, dtype=torch.float32, device=feat.device)
         nb = int(sel.numel()) if sel is not None else int(feat.shape[0])
-        self.ctx._check(self.ctx.lib.apx_mlp_gradients(self.ctx.h, self.h, _p(feat), _p(target), _p(sel), nb,
-                                                       _p(g), _p(self.loss)))
+        work = self._workspace(nb)
+        self.ctx._check(self.ctx.lib.apx_mlp_gradients_ws(self.ctx.h, self.h, _p(feat), _p(target), _p(sel), nb,
+                                                          _p(g), _p(self.loss), _p(work)))
         return g, self.loss
 
     def adam_step(self, grad, lr=1e-3, b1=0.9, b2=0.999, eps=1e-8):
