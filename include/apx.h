@@ -253,7 +253,9 @@ apx_status apx_ace_model_set_coeffs(apx_ctx* ctx, apx_ace_model* m, const double
  * (overwritten): -d/dx sum_{i active} w_i E_i^ACE (Appendix C eq. F_i_d, precise part);
  * w NULL means 1.  dE_dc1/dE_dc2 (device [n_basis] or NULL, overwritten):
  * d/dc of sum_i w_i E_i^ACE.  precision: APX_FP64, or APX_FP32 (basis, products and
- * adjoint in float32, energy sums and forces accumulated in float64). */
+ * adjoint in float32; the products' sums in float64 over short float32 sums where they are
+ * large, so that their rounding stays below that of compensated float32 sums; forces
+ * accumulated in float64). */
 apx_status apx_ace_energy_forces(apx_ctx* ctx, const apx_atoms* atoms, const apx_nlist* nl,
                                  const apx_ace_model* m, const double* w,
                                  const int32_t* active, int64_t n_active, int32_t precision,

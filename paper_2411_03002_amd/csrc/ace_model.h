@@ -16,14 +16,21 @@ constexpr int kSymB2 = 75, kSymPairs = 80, kSymNg = 95, kSymOff = 110;
 // Radial indices the product kernels are instantiated for.
 __host__ __device__ constexpr int sym_nmax(int n_max) { return n_max <= 8 ? 8 : (n_max <= 10 ? 10 : 12); }
 
+// Values of a row of SymTables::low.
+__host__ __device__ constexpr int sym_low(int nmax) { return 2 * nmax + 4; }
+
 template <class T>
 struct SymTables {
   const T* Wp;       // [l_max+1][n_max][n_max], W[l][n][k] * N_l / s_a
   const T* coef;     // rows of 2 sym_nmax values (c1 and c2 of n3 = 0, 1, ...), one group after the other
   const T* b1;       // [n_max][2], behind coef
+  // float32, behind coef: a row for every pair of one degree (l, then the pairs of type (l, l)):
+  // second-order c1 and c2, then c1 and c2 of the third-order functions with n3 = 0, 1, ... of
+  // degree 0 beside the pair (each function in one row)
+  const T* low;
   const int* pairs;  // atomic-base row of the l1 block | row of the l2 block << 16
   const int* off;
-  // per value of coef and b1: 2 * basis index + (0: c1, 1: c2), or -1 (zero), and its factor
+  // per value of coef, low and b1: 2 * basis index + (0: c1, 1: c2), or -1 (zero), and its factor
   const int* slot;
   const double* factor;
   int n;

@@ -77,7 +77,8 @@ int triple_index(const Catalogue& c, int P, int a, int b, int r) {
 struct SymHost {
   std::vector<int> off, pairs, slot;
   std::vector<double> factor;
-  int b1 = 0;  // first slot of the first-order pairs
+  int low = 0;  // first slot of the rows of pairs of one degree
+  int b1 = 0;   // and of the first-order pairs
 };
 
 SymHost build_sym(const Catalogue& c, int n_max, int l_max, int width) {
@@ -136,9 +137,21 @@ SymHost build_sym(const Catalogue& c, int n_max, int l_max, int width) {
         return {index2(n_max, l_max, std::min(n, n3), std::max(n, n3), L), n == n3 ? 2.0 : 1.0};
       });
   }
-  // the kernels read up to two groups ahead
-  for (int k = 0; k < 2 * width * R; ++k) put(-1, 0, 0.0);
-  for (int k = 0; k < 3 * width; ++k) s.pairs.push_back(0);
+  if (width == 1) {
+    while (s.slot.size() % 4) put(-1, 0, 0.0);
+    s.low = (int)s.slot.size();
+    for (int l = 0; l < LL; ++l)
+      for (const auto& q : label_pairs(n_max, l, l))
+        for (int o = 0; o < sym_low(sym_nmax(n_max)); ++o) {
+          const int n1 = q.first, n2 = q.second, n3 = o / 2 - 1;  // (n1 >= n2)
+          if (o < 2) put(index2(n_max, l_max, n2, n1, l), o, 1.0);
+          else if (n3 >= n_max || (l == 0 && n3 > n2)) put(-1, 0, 0.0);
+          else put(triple_index(c, P, n1 * LL + l, n2 * LL + l, n3 * LL), o, kSymScale[l][l][0]);
+        }
+  }
+  // the kernels read up to two groups, or four pairs and two rows of low, ahead
+  for (int k = 0; k < std::max(2 * width * R, 2 * sym_low(sym_nmax(n_max))); ++k) put(-1, 0, 0.0);
+  for (int k = 0; k < std::max(3 * width, 4); ++k) s.pairs.push_back(0);
   s.b1 = (int)s.slot.size();
   for (int n = 0; n < n_max; ++n)
     for (int p = 0; p < 2; ++p) put(n, p, 1.0);
@@ -268,6 +281,7 @@ apx_status model_tables(apx_ctx* ctx, apx_ace_model* m, const Catalogue& c, cons
     t.Wp = wp;
     t.coef = coef;
     t.b1 = coef + h.b1;
+    t.low = coef + h.low;
     t.off = ib + a.off;
     t.pairs = ib + a.pairs;
     t.slot = ib + a.slot;

@@ -12,7 +12,17 @@
 // cores, one pair (float32) or four (float64) per instruction.  Second-order functions join as
 // pairs whose P is the block itself.  No coupling is back-propagated: by Euler's rule for
 // homogeneous functions phi_p = A . (D3 / 3 + D2 / 2 + D1) with D_k = the derivative of the
-// k-th order part.  Against an evaluation over a minimal set of triples with an explicit
+// k-th order part.
+//
+// In float32 the accumulators round at the size of their sums, most of which are functions with a
+// block of degree 0 (an isotropic density): their terms are added last, and their energies, with the
+// second order's, are formed apart in float64 sums (low_energy); Euler's rule is left the functions
+// without such a block.  Rounding of the energy for 192 thermal environments (emulated, eV RMS), the
+// rule for every function and one accumulator / here / compensated float32 sums over the pairs of
+// triples: 1.8e-8 / 4.4e-9 / 8.0e-9 at (10, 4), 2.1e-8 / 4.1e-9 / 4.6e-9 at (12, 3), 3.0e-8 / 6.4e-9 /
+// 7.3e-9 at (6, 4).
+//
+// Against an evaluation over a minimal set of triples with an explicit
 // backward coupling (forward 30 k and backward 90 k multiply-adds per atom at n_max 10,
 // l_max 4, and float atomics on the adjoint) the coupling is evaluated for 2,160 (pair, L)
 // entries instead of 995, but forwards only (68 k vector instructions a tile), and the 235 k
@@ -53,6 +63,7 @@ struct SymArgs {
   const T* Wp;
   const T* coef;   // rows of C, see SymTables
   const T* b1;     // [n_max][2]
+  const T* low;    // rows of the pairs of one degree (float32)
   const int* pairs;
   const int* off;  // see SymTables
   T* slab;         // [split][tile][lm][2 NMAX][TA]
@@ -74,6 +85,7 @@ __device__ __forceinline__ void static_for(F&& f) {
 
 // Uniform read of a table entry through the constant address space (a scalar load).
 __device__ __forceinline__ int sld(const int* p) { return *(const __attribute__((address_space(4))) int*)p; }
+__device__ __forceinline__ float sld(const float* p) { return *(const __attribute__((address_space(4))) float*)p; }
 
 // One component's accumulators: rows o = 2 n3 + p of C (p = 0: c1, 1: c2), columns = atoms.
 // Rows 0..15 by a 16-row instruction, further rows four at a time.
@@ -151,14 +163,6 @@ struct SymAcc<float, NMAX> {
   struct Dot {
     double s16[2][4], s4[2];
   };
-  static __device__ __forceinline__ void dot_scale(Dot& s, double x) {
-#pragma unroll
-    for (int p = 0; p < 2; ++p) {
-      s.s4[p] *= x;
-#pragma unroll
-      for (int b = 0; b < 4; ++b) s.s16[p][b] *= x;
-    }
-  }
   __device__ __forceinline__ void dot(Dot& s, const float* a, int step, int n_max, int lane) const {
     const int sub = lane >> 4, col = lane & 15;
 #pragma unroll
@@ -188,9 +192,13 @@ struct SymAcc<float, NMAX> {
       }
     asm volatile("" : "+v"(s.s4[0]), "+v"(s.s4[1])::"memory");
   }
-  // sum of atom `lane` (p = 0, 1) over the wave's rows
-  static __device__ __forceinline__ void dot_reduce(Dot& s, int lane, double* red) {
+  // a wave's share of the sums: p = 0, 1 of atom `lane`
+  struct Part {
+    double e[2];
+  };
+  static __device__ __forceinline__ Part part(const Dot& s, int lane, double scale) {
     const int sub = lane >> 4;
+    Part r;
 #pragma unroll
     for (int p = 0; p < 2; ++p) {
       double v = 0.0;
@@ -201,8 +209,13 @@ struct SymAcc<float, NMAX> {
         x += __shfl_xor(x, 32, kWave);
         v = b == sub ? x : v;
       }
-      red[p * TA + lane] = v + s.s4[p];
+      r.e[p] = scale * (v + s.s4[p]);
     }
+    return r;
+  }
+  static __device__ __forceinline__ void put(const Part& s, int lane, double* red) {
+#pragma unroll
+    for (int p = 0; p < 2; ++p) red[p * TA + lane] = s.e[p];
   }
 };
 
@@ -261,7 +274,7 @@ struct SymAcc<double, NMAX> {
   struct Dot {
     double s;
   };
-  static __device__ __forceinline__ void dot_scale(Dot& s, double x) { s.s *= x; }
+  using Part = Dot;
   __device__ __forceinline__ void dot(Dot& s, const double* a, int step, int n_max, int lane) const {
     const int sub = lane >> 4, col = lane & 15;
 #pragma unroll
@@ -269,7 +282,7 @@ struct SymAcc<double, NMAX> {
 #pragma unroll
     for (int k = 0; k < NB; ++k) s.s = fma(a[min(8 + 2 * k + (sub >> 1), n_max - 1) * step + col], e[k], s.s);
   }
-  static __device__ __forceinline__ void dot_reduce(const Dot& s, int lane, double* red) {
+  static __device__ __forceinline__ void put(const Part& s, int lane, double* red) {
     const double v = s.s + __shfl_xor(s.s, 32, kWave);
     if (lane < 32) red[lane] = v;  // [p][TA]
   }
@@ -414,49 +427,136 @@ struct SymProg {
     }
   }
 
+  // s += the components of degree L >= FROM times A
+  template <int FROM>
   __device__ __forceinline__ void dots(const SymArgs<T>& g, const T* As, int lane, typename Acc::Dot& s) const {
     static_for<0, NC>([&](auto i) {
-      static_for<0, LMAX + 1>([&](auto L) {
+      static_for<FROM, LMAX + 1>([&](auto L) {
         if constexpr (holds(i, L))
           acc[slot(i, L)].dot(s, As + (L * L + L + comp(i)) * TA, LM * TA, g.n_max, lane);
       });
     });
   }
 
-  // The derivatives of the second- and third-order sums into acc, and the wave's share of the
-  // sums themselves into s.
-  __device__ __forceinline__ void sums(const SymArgs<T>& g, const T* As, int lane, int split, typename Acc::Dot& s) {
-#pragma unroll
-    for (int k = 0; k < NA; ++k) acc[k].zero();
-    static_for<0, LMAX + 1>([&](auto l2) {
-      static_for<0, l2 + 1>([&](auto l1) {
-        if constexpr (uses(l1, l2)) type<l1, l2>(g, As, lane, split);
-      });
-    });
-    // third order / 3 + second order / 2 = (both - third order / 3) / 2
-    dots(g, As, lane, s);
-    Acc::dot_scale(s, -1.0 / 3.0);
-    if (split == 0) {
-      // second order: the pairs are single blocks (n', L)
-      static_for<0, LMAX + 1>([&](auto L) {
-        if constexpr (has(L)) {
-          const T* rows = g.coef + sld(g.off + kSymB2 + L);
-          const T* al = As + (lane & (TA - 1)) + (L * L + L) * TA;
-          const int sub = lane / TA;
+  // Second order: the pairs are single blocks (n', L).
+  __device__ __forceinline__ void second_order(const SymArgs<T>& g, const T* As, int lane) {
+    static_for<0, LMAX + 1>([&](auto L) {
+      if constexpr (has(L)) {
+        const T* rows = g.coef + sld(g.off + kSymB2 + L);
+        const T* al = As + (lane & (TA - 1)) + (L * L + L) * TA;
+        const int sub = lane / TA;
 #pragma unroll 4
-          for (int p = 0; p < (g.n_max + Acc::kPairs - 1) / Acc::kPairs; ++p) {
-            const int n = p * Acc::kPairs + sub;
-            const T* an = al + (n < g.n_max ? n : 0) * LM * TA;
-            const typename Acc::Coef c = Acc::load(rows, p, Acc::lane_bytes(lane));
-            static_for<0, NC>([&](auto i) {
-              if constexpr (holds(i, L)) acc[slot(i, L)].step(c, an[comp(i) * TA]);
-            });
+        for (int p = 0; p < (g.n_max + Acc::kPairs - 1) / Acc::kPairs; ++p) {
+          const int n = p * Acc::kPairs + sub;
+          const T* an = al + (n < g.n_max ? n : 0) * LM * TA;
+          const typename Acc::Coef c = Acc::load(rows, p, Acc::lane_bytes(lane));
+          static_for<0, NC>([&](auto i) {
+            if constexpr (holds(i, L)) acc[slot(i, L)].step(c, an[comp(i) * TA]);
+          });
+        }
+      }
+    });
+  }
+
+  // The energies of the second order and of the third-order functions with a block of degree 0,
+  // float32: per label pair of one degree, sum_M A_n1 A_n2 times (the pair's second-order
+  // coefficient plus sum_n3 c A_n3,00), added in float64 two pairs at a time.  The pairs are shared
+  // among the waves and done first, while registers are free.  Bound by the scalar reads of the rows
+  // (21 KB a tile at (10, 4)): 0.14 of 5.43 ms for 821,266 atoms; 0.30 with the pairs dealt
+  // round-robin, their places behind two more reads, at the end.
+  static __device__ __forceinline__ void low_energy(const SymArgs<T>& g, const T* As, int lane, int share, int shares,
+                                                    double (&e)[2]) {
+    // (entries of a last group beyond hi are read, the tables are padded, and not added)
+    constexpr int W = sym_low(NMAX), G = 2;
+    const T* al = As + lane;
+    const int K = g.n_max, np = K * (K + 1) / 2;  // pairs of a degree
+    const int lo = np * share / shares, hi = np * (share + 1) / shares;
+    // (before the pairs of (l, l) lie l (l + 1) / 2 types of two degrees and l of one)
+    auto pairs_of = [&](int l) { return g.pairs + l * (l + 1) / 2 * K * K + l * np; };
+    int pk[LMAX + 1][G];
+    static_for<0, LMAX + 1>([&](auto l) {
+#pragma unroll
+      for (int k = 0; k < G; ++k) pk[l][k] = sld(pairs_of(l) + lo + k);
+    });
+    T A0[NMAX];
+#pragma unroll
+    for (int n = 0; n < NMAX; ++n) A0[n] = al[(n < K ? n : 0) * LM * TA];
+    static_for<0, LMAX + 1>([&](auto l) {
+      for (int p = lo; p < hi; p += G) {
+        T I[G], q[G][2];
+        const T* row = g.low + (l * np + p) * W;
+#pragma unroll
+        for (int k = 0; k < G; ++k) {
+          const T *a = al + (pk[l][k] & 0xffff) * TA, *b = al + (pk[l][k] >> 16) * TA;
+          I[k] = a[0] * b[0];
+#pragma unroll
+          for (int m = 1; m < 2 * l + 1; ++m) I[k] = fma(a[m * TA], b[m * TA], I[k]);
+          I[k] = p + k < hi ? I[k] : T(0);
+          q[k][0] = sld(row + k * W);
+          q[k][1] = sld(row + k * W + 1);
+        }
+#pragma unroll
+        for (int k = 0; k < G; ++k) pk[l][k] = sld(pairs_of(l) + p + G + k);
+#pragma unroll
+        for (int n = 0; n < NMAX; ++n) {
+#pragma unroll
+          for (int k = 0; k < G; ++k) {  // (coefficients beyond n_max are zero)
+            q[k][0] = fma(sld(row + k * W + 2 + 2 * n), A0[n], q[k][0]);
+            q[k][1] = fma(sld(row + k * W + 3 + 2 * n), A0[n], q[k][1]);
           }
         }
+        T v0 = q[0][0] * I[0], v1 = q[0][1] * I[0];
+#pragma unroll
+        for (int k = 1; k < G; ++k) {
+          v0 = fma(q[k][0], I[k], v0);
+          v1 = fma(q[k][1], I[k], v1);
+        }
+        e[0] += (double)v0;
+        e[1] += (double)v1;
+      }
+    });
+  }
+
+  // The derivatives of the second- and third-order sums into acc; returns the wave's share of the
+  // sums themselves.
+  __device__ __forceinline__ typename Acc::Part sums(const SymArgs<T>& g, const T* As, int lane, int wv, int split) {
+    typename Acc::Dot s{};
+    if constexpr (sizeof(T) == 4) {
+      double low[2] = {0.0, 0.0};
+      low_energy(g, As, lane, split * kSymWaves + wv, g.nsplit * kSymWaves, low);
+#pragma unroll
+      for (int k = 0; k < NA; ++k) acc[k].zero();
+      // without blocks of degree 0: a third of A . D; the large terms, those with one, come last
+      static_for<1, LMAX + 1>([&](auto l2) {
+        static_for<1, l2 + 1>([&](auto l1) {
+          if constexpr (uses(l1, l2)) type<l1, l2>(g, As, lane, split);
+        });
       });
+      dots<1>(g, As, lane, s);
+      typename Acc::Part e = Acc::part(s, lane, 1.0 / 3.0);
+      e.e[0] += low[0];
+      e.e[1] += low[1];
+      static_for<0, LMAX + 1>([&](auto l2) {
+        if constexpr (uses(0, l2)) type<0, l2>(g, As, lane, split);
+      });
+      if (split == 0) second_order(g, As, lane);
+      return e;
+    } else {
+#pragma unroll
+      for (int k = 0; k < NA; ++k) acc[k].zero();
+      static_for<0, LMAX + 1>([&](auto l2) {
+        static_for<0, l2 + 1>([&](auto l1) {
+          if constexpr (uses(l1, l2)) type<l1, l2>(g, As, lane, split);
+        });
+      });
+      // third order / 3 + second order / 2 = (both - third order / 3) / 2
+      dots<0>(g, As, lane, s);
+      s.s *= -1.0 / 3.0;
+      if (split == 0) second_order(g, As, lane);
+      dots<0>(g, As, lane, s);
+      s.s *= 0.5;
+      return s;
     }
-    dots(g, As, lane, s);
-    Acc::dot_scale(s, 0.5);
   }
 
   // The wave's part of a block: FUSED (one split): the combined derivative into the tile;
@@ -465,8 +565,7 @@ struct SymProg {
   static __device__ __forceinline__ void run(const SymArgs<T>& g, T* As, double* red, int wv, int lane, int split,
                                              int slab_tile) {
     SymProg w;
-    typename Acc::Dot s{};
-    w.sums(g, As, lane, split, s);
+    const typename Acc::Part s = w.sums(g, As, lane, wv, split);
     if constexpr (!FUSED) {
       T* out = g.slab + ((size_t)slab_tile * LM) * (Acc::R * TA);
       static_for<0, NC>([&](auto i) {
@@ -485,7 +584,7 @@ struct SymProg {
       }
     }
     __syncthreads();  // every wave is done with the tile: red lies over it
-    Acc::dot_reduce(s, lane, red + wv * 2 * TA);
+    Acc::put(s, lane, red + wv * 2 * TA);
     __syncthreads();
     T* fps = reinterpret_cast<T*>(red + kSymWaves * 2 * TA);
     if (wv == 0 && lane < TA) {
@@ -741,6 +840,7 @@ apx_status sym_launch(apx_ctx* ctx, const apx_ace_model* m, const T* A, T* B, T*
   g.slope = slope;
   g.coef = tb.coef;
   g.b1 = tb.b1;
+  g.low = tb.low;
   g.pairs = tb.pairs;
   g.off = tb.off;
   g.slab = static_cast<T*>(scratch);
