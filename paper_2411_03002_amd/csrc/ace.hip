@@ -548,7 +548,8 @@ __global__ void k_unpack(const double* __restrict__ fp, int n, double* __restric
 // more and unpacking cost 4 us and 0.02 ns per atom.  Float32 with these passes, direct / packed (us):
 // 16,309 active atoms 78 / 67, 29,150 of 130,466 123 / 86; below 8,192 the saving is no larger than a
 // launch.
-bool packed_forces(int n, int n_act) { return n_act >= 8192 && n_act >= n / 32; }
+constexpr int kPackedLeast = 8192, kPackedShare = 32;
+bool packed_forces(int n, int n_act) { return n_act >= kPackedLeast && n_act >= n / kPackedShare; }
 
 template <class T, int LMAX>
 apx_status ace_run(apx_ctx* ctx, const apx_atoms* atoms, const apx_nlist* nl, const apx_ace_model* m,
@@ -569,7 +570,17 @@ apx_status ace_run(apx_ctx* ctx, const apx_atoms* atoms, const apx_nlist* nl, co
   const size_t bytes_more = std::max(sym_scratch<T>(m, n_act), dc1 ? ace_grad_scratch(m, n_act) : 0);
   const bool packed = packed_forces(n, n_act);
   const size_t bytes_fp = packed ? whole(sizeof(double) * 4 * (size_t)n) : 0;
-  APX_ALLOC(ctx, buf, (dc1 ? 2 : 1) * bytes_A + bytes_anch + bytes_slope + bytes_fp + bytes_more);
+  const size_t need = (dc1 ? 2 : 1) * bytes_A + bytes_anch + bytes_slope + bytes_fp + bytes_more;
+  // What is allocated grows with n_act alone and is no less in float64 than in float32, so that after a
+  // call no other of at most its n_act allocates (and can be recorded into a graph): whatever its number
+  // of atoms, with or without coefficient gradients, and where fewer tiles' pairs are shared among blocks.
+  const size_t most = 2 * bytes_A + bytes_anch + whole(sizeof(T) * (size_t)n_act) +
+                      (n_act >= kPackedLeast ? whole(sizeof(double) * 4 * kPackedShare * ((size_t)n_act + 1)) : 0) +
+                      std::max(sym_scratch_most(m, n_act), ace_grad_scratch(m, n_act));
+  if (buf.bytes < need && buf.ensure(std::max(need, most)) != hipSuccess) {
+    (void)hipGetLastError();
+    APX_ALLOC(ctx, buf, need);
+  }
   char* p = static_cast<char*>(buf.p);
   auto take = [&](size_t b) {
     char* at = p;

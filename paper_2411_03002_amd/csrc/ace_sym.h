@@ -16,6 +16,8 @@ inline int sym_stride(int na) { return (na + 3) & ~3; }
 // Device scratch of sym_products beyond the atomic base, in bytes.
 template <class T>
 size_t sym_scratch(const apx_ace_model* m, int n_act);
+// The most that a call of at most n_act atoms takes, in either type.
+size_t sym_scratch_most(const apx_ace_model* m, int n_act);
 
 // For the atoms active[0..n_act) with the atomic base A [n_act][sym_stride(na)]:
 // e_site[active[q]] = E_q (random part plus e_anch[q]); slope[q] = F_eps'(phi2) (null: not

@@ -54,6 +54,7 @@ typedef double f64x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kSymWaves = 8;
 constexpr int kSymMaxSplit = 8;             // blocks that share a tile's pairs
+constexpr int kSymBlocks = 512;             // blocks of a launch up to which tiles are shared
 
 template <class T>
 struct SymArgs {
@@ -808,6 +809,12 @@ struct SymPlan {
   size_t slab, epart;  // bytes (one share needs neither)
 };
 
+// Bytes of one share's derivatives.
+template <class T>
+size_t share_slab(const apx_ace_model* m) {
+  return sizeof(T) * (m->l_max + 1) * (m->l_max + 1) * 2 * sym_nmax(m->n_max) * sym_tile<T>();
+}
+
 // Shares of a tile's pairs: enough blocks for two per compute unit.  A share costs the block's
 // staging and the sum over shares at the end; it pays while compute units idle.  Measured in
 // float32 at (10, 4), products + end in us by shares 1/2/4/8: 8 tiles 165/92/59/47, 63 tiles
@@ -820,9 +827,9 @@ SymPlan<T> sym_plan(const apx_ace_model* m, int n_act) {
   constexpr int TA = sym_tile<T>();
   SymPlan<T> p;
   p.tiles = (n_act + TA - 1) / TA;
-  p.split = std::max(1, std::min(kSymMaxSplit, 512 / std::max(1, p.tiles)));
+  p.split = std::max(1, std::min(kSymMaxSplit, kSymBlocks / std::max(1, p.tiles)));
   const size_t shares = p.split > 1 ? (size_t)p.split * p.tiles : 0;
-  p.slab = shares * sizeof(T) * (m->l_max + 1) * (m->l_max + 1) * 2 * sym_nmax(m->n_max) * TA;
+  p.slab = shares * share_slab<T>(m);
   p.epart = shares * sizeof(double) * 2 * TA;
   return p;
 }
@@ -879,6 +886,16 @@ template <class T>
 size_t sym_scratch(const apx_ace_model* m, int n_act) {
   const SymPlan<T> p = sym_plan<T>(m, n_act);
   return p.slab + p.epart;
+}
+
+size_t sym_scratch_most(const apx_ace_model* m, int n_act) {
+  auto most = [&](auto t) {
+    using T = decltype(t);
+    constexpr int TA = sym_tile<T>();
+    const size_t tiles = ((size_t)n_act + TA - 1) / TA;
+    return std::min<size_t>(kSymMaxSplit * tiles, kSymBlocks) * (share_slab<T>(m) + sizeof(double) * 2 * TA);
+  };
+  return std::max(most(float{}), most(double{}));
 }
 
 template <class T>
