@@ -228,8 +228,11 @@ __global__ void k_layout_coeffs(int n, const int* __restrict__ slot, const doubl
 apx_status layout_coeffs(apx_ctx* ctx, apx_ace_model* m, const double* c1, const double* c2) {
   double* c = m->c.as<double>();
   const size_t b = sizeof(double) * (size_t)m->n_basis;
-  APX_HIP(ctx, hipMemcpyAsync(c, c1, b, hipMemcpyHostToDevice, ctx->stream));
-  APX_HIP(ctx, hipMemcpyAsync(c + m->n_basis, c2, b, hipMemcpyHostToDevice, ctx->stream));
+  // On the default stream: the copies, and so the rows, wait for the evaluations queued there, which end
+  // with the rows they began with, also where the context's stream is another by now.
+  APX_HIP(ctx, hipMemcpyAsync(c, c1, b, hipMemcpyHostToDevice, nullptr));
+  APX_HIP(ctx, hipMemcpyAsync(c + m->n_basis, c2, b, hipMemcpyHostToDevice, nullptr));
+  if (ctx->stream) APX_HIP(ctx, hipStreamSynchronize(nullptr));
   k_layout_coeffs<<<blocks_for(m->s64.n, 256), 256, 0, ctx->stream>>>(m->s64.n, m->s64.slot, m->s64.factor, c,
                                                                      m->n_basis, m->coef64.as<double>());
   k_layout_coeffs<<<blocks_for(m->s32.n, 256), 256, 0, ctx->stream>>>(m->s32.n, m->s32.slot, m->s32.factor, c,
