@@ -342,7 +342,10 @@ struct SpreadDev {
 // where the unsigned order equals the floating-point order), so the result does not depend on the
 // visiting order.  A cell is a chain of dependent loads (its bounds, its atoms, their positions), and a
 // stencil has 343 of them: with few sources the time is the number of cells a thread visits one after
-// the other, so each source gets up to 512 threads.  Measured (us) for 64 / 256 / 512: TIMESP.
+// the other, so each source gets up to 512 threads; with many sources the card is full and more
+// threads find fewer atoms each.  Measured (us) for 64 / 128 / 256 / 512: 472 sources 87 / 51 / 44 / 36,
+// 3,275 sources 117 / 80 / 82 / 79, 7,114 sources 211 / 203 / 206 / 213, 27,719 sources 663 / 629 / 650 /
+// 723, 250,242 sources 5,341 / 5,448 / 6,881 / 6,628.
 __global__ void __launch_bounds__(512) k_spread(const double* __restrict__ pos, int n, Grid g, SpreadDev s, int per,
                                                 const int* __restrict__ src, int nsrc,
                                                 const double* __restrict__ w0, const uint8_t* __restrict__ frozen,
@@ -521,7 +524,7 @@ static void spread_stencil(const Grid& g, double r_hi, SpreadDev& s) {
 namespace {
 
 // Threads per source of k_spread (a multiple of the wave's 64), by the measurements at the kernel.
-int spread_threads(int nsrc) { return nsrc <= 8192 ? 512 : 128; }
+int spread_threads(int nsrc) { return nsrc <= 4096 ? 512 : 128; }
 
 // The averaging stage of a call: ring slot of this sample, samples in the means, and
 // the buffers (all device, length n or [n_avg][n]).
