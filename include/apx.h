@@ -237,9 +237,11 @@ typedef struct {
 } apx_ace_desc;
 
 int64_t apx_ace_num_basis(int32_t n_max, int32_t l_max);
-/* Work counts of a model per evaluated atom (host, no device work): out[0] label pairs,
- * out[1] third-block terms (triples), out[2] coupling terms summed over pairs,
- * out[3] sum over triples of (2L+1), out[4] product-basis size, out[5] atomic-base size. */
+/* Sizes of a model (host, no device work): out[4] the product basis, out[5] the atomic base;
+ * and the work per atom of a minimal evaluation of its third-order functions, each once as a
+ * label pair's coupling times a third block: out[0] label pairs, out[1] third-block terms
+ * (triples), out[2] coupling terms summed over pairs, out[3] sum over triples of (2L+1).
+ * (The kernels form the derivatives too, from more pairs and without a backward pass.) */
 apx_status apx_ace_model_stats(const apx_ace_model* m, int64_t* out6);
 /* Copies the descriptor's arrays to the device and builds the coupling tables. */
 apx_status apx_ace_model_create(apx_ctx* ctx, const apx_ace_desc* desc, apx_ace_model** out);

@@ -52,7 +52,7 @@ struct apx_ace_model {
   int n_max = 0, l_max = 0, na = 0;
   long long n_basis = 0;
   int npairs = 0, ntrip = 0;
-  long long coupling_terms = 0, triple_width = 0;  // per-atom work counts
+  long long coupling_terms = 0, triple_width = 0;  // of apx_ace_model_stats, as npairs and ntrip
   double r_cut = 5.0, h = 0.5, s_a = 1.0, eps = 0.1;
   int anchored = 0;
   apx_eam_params anchor{};

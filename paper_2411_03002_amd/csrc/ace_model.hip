@@ -32,8 +32,9 @@ Catalogue build_catalogue(int n_max, int l_max) {
   const int LL = l_max + 1, P = n_max * LL;
   long long v = n_max + (long long)LL * n_max * (n_max + 1) / 2;
   c.index3.assign((size_t)P * P * P, -1);
-  // work counts of the minimal evaluation, which takes the label first in degree-major order
-  // (l, then n) as the third block: the pairs of the other two, and per pair the degrees met
+  // the counts of apx_ace_model_stats, of an evaluation that takes every function once with the label
+  // first in degree-major order (l, then n) as the third block: the pairs of the other two, and per
+  // pair the degrees met (the kernels take all pairs and degrees, see ace_sym.hip)
   std::vector<unsigned char> met((size_t)P * P, 0);
   auto key = [&](int p) { return (p % LL) * n_max + p / LL; };
   for (int p1 = 0; p1 < P; ++p1)

@@ -73,7 +73,7 @@ struct SymArgs {
   const int* active;
   double* e_site;
   double eps;
-  int n_act, stride, n_max, tile0, nsplit;
+  int n_act, stride, n_max, nsplit;
 };
 
 template <int I, int N, class F>
@@ -696,7 +696,7 @@ __global__ void __launch_bounds__(kSymWaves * 64, 4) k_ace_sym(SymArgs<T> g) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int split = blockIdx.y, K = g.n_max, na = K * LM;
-  const int tile = g.tile0 + blockIdx.x;
+  const int tile = blockIdx.x;
   const int t = tid & (TA - 1), ch = tid / TA;
   const int q = tile * TA + t;
   const T* row = g.A + (size_t)q * g.stride;
@@ -870,7 +870,6 @@ apx_status sym_launch(apx_ctx* ctx, const apx_ace_model* m, const T* A, T* B, T*
     APX_LAUNCH_CHECK(ctx);
     return APX_OK;
   };
-  g.tile0 = 0;
   if (pl.split == 1) return launch(k_ace_sym<T, LMAX, NMAX, true>, pl.tiles, 1);
   const apx_status s = launch(k_ace_sym<T, LMAX, NMAX, false>, pl.tiles, pl.split);
   if (s != APX_OK) return s;

@@ -5,8 +5,8 @@
 // fast-potential part of Appendix C eq. F_i_d:
 //   F_i = -d/dx_i sum_k u_k E_k,  u = 1 - w
 //       = sum_j [ 1/2 (u_i + u_j) phi'(r_ij) + (u_i F'_i + u_j F'_j) rho'(r_ij) ] r_ij / r_ij
-// with r_ij = x_j - x_i.  Both passes gather over the full neighbour list (one thread per
-// atom, neighbour-major rows read coalesced), so no atomics are needed.
+// with r_ij = x_j - x_i.  Both passes gather over the full neighbour list (64 atoms to W waves,
+// lane = atom, neighbour-major rows read coalesced), so no atomics are needed.
 #include <cmath>
 #include <type_traits>
 
@@ -80,8 +80,9 @@ __device__ __forceinline__ void eam2_embed(const EamDev& p, double x, double& F,
 }
 
 // Neighbours are processed in batches of kBatch, shared among W waves (see row_waves): the batch's
-// indices and positions are loaded first so that their memory accesses are in flight together, then the pairs are
-// summed in list order (the same order as one at a time).
+// indices and positions are loaded first so that their memory accesses are in flight together.  Wave w
+// sums the pairs of the batches w, w + W, ... in list order, and the waves' sums are added in wave
+// order; W follows from the number of atoms, so an atom's sums depend on it to rounding.
 template <int KIND, int W>
 __global__ void __launch_bounds__(W == 1 ? 256 : 64 * W)
 k_eam_density(const double* __restrict__ pos, int n, BoxDev b, EamDev p,

@@ -296,7 +296,7 @@ class AceModel:
         self.ctx._check(self.ctx.lib.apx_ace_model_set_coeffs(self.ctx.h, self.h, c1.ctypes.data, c2.ctypes.data))
 
     def stats(self) -> dict:
-        """Per-atom work counts of the coupling tables."""
+        """Sizes of the model and the work per atom of a minimal evaluation (apx_ace_model_stats)."""
         arr = (C.c_int64 * 6)()
         self.ctx._check(self.ctx.lib.apx_ace_model_stats(self.h, arr))
         keys = ("pairs", "triples", "coupling_terms", "triple_width", "n_basis", "n_atomic_base")
