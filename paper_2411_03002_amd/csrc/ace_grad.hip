@@ -238,15 +238,17 @@ apx_status ace_grad(apx_ctx* ctx, const apx_ace_model* m, const T* A, const T* s
   const int parts = std::max(1, std::min(4, 512 / nb));
   const size_t lds = sizeof(double) * (size_t)m->na * kGradStride;
   ProfScope ps(ctx, "ace.grad");
+  const int nm = sym_nmax(m->n_max);
+  // (the most of the instantiation: the attribute is the process's, and another thread's model may be smaller)
+  const size_t most = sizeof(double) * (size_t)nm * (m->l_max + 1) * (m->l_max + 1) * kGradStride;
   auto launch = [&](auto kern) -> apx_status {
-    APX_HIP(ctx, hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    APX_HIP(ctx, hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)most));
     kern<<<dim3(nb, parts), kGradWaves * 64, lds, ctx->stream>>>(g);
     APX_LAUNCH_CHECK(ctx);
     k_ace_grad_sum<<<tb.slots / 16, 256, 0, ctx->stream>>>(g.slab, nb, tb.slots, tb.at, tb.scale, dc1, dc2);
     APX_LAUNCH_CHECK(ctx);
     return APX_OK;
   };
-  const int nm = sym_nmax(m->n_max);
   if (m->l_max == 3 && nm == 8) return launch(k_ace_grad<T, 3, 8>);
   if (m->l_max == 3 && nm == 10) return launch(k_ace_grad<T, 3, 10>);
   if (m->l_max == 3) return launch(k_ace_grad<T, 3, 12>);

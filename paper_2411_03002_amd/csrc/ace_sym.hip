@@ -29,8 +29,8 @@
 // multiply-adds with the coefficients run as 11,760 pairs of one 16x16x1 and one 4x4x1
 // instruction.  Measured, 821,266 atoms of the indentation block in float32: energy, five
 // adjoint launches, their zero fill and the back-projection took 16.9 ms; this kernel alone,
-// which does all of it, 5.5 ms (instruction issue: 0.47 M matrix and 0.37 M vector cycles a
-// tile of 64, of 0.95 M measured).  In float64, 29,150 atoms: 2,850 us in the kernel that dealt
+// which does all of it, 5.5 ms (counters: 0.48 M matrix and 0.38 M vector cycles of a SIMD for a
+// tile of 64, of 0.99 M).  In float64, 29,150 atoms: 2,850 us in the kernel that dealt
 // pairs to waves and added adjoints in LDS, 477 us here (16x16x4 and 4x4x4 instructions).
 //
 // A block holds one tile of atoms in LDS; its eight waves each own a few components (L, M)
@@ -462,9 +462,9 @@ struct SymProg {
   // The energies of the second order and of the third-order functions with a block of degree 0,
   // float32: per label pair of one degree, sum_M A_n1 A_n2 times (the pair's second-order
   // coefficient plus sum_n3 c A_n3,00), added in float64 two pairs at a time.  The pairs are shared
-  // among the waves and done first, while registers are free.  Bound by the scalar reads of the rows
-  // (21 KB a tile at (10, 4)): 0.14 of 5.43 ms for 821,266 atoms; 0.30 with the pairs dealt
-  // round-robin, their places behind two more reads, at the end.
+  // among the waves and done first, while registers are free.  Bound by vector instruction issue (30 a
+  // pair): 0.2 of 5.4 ms for 821,266 atoms at (10, 4), 10 of 230 us for 29,150; 0.1 ms more with the
+  // pairs dealt round-robin, behind two more table reads, at the end.
   static __device__ __forceinline__ void low_energy(const SymArgs<T>& g, const T* As, int lane, int share, int shares,
                                                     double (&e)[2]) {
     // (entries of a last group beyond hi are read, the tables are padded, and not added)
@@ -862,9 +862,13 @@ apx_status sym_launch(apx_ctx* ctx, const apx_ace_model* m, const T* A, T* B, T*
   g.e_site = e_site;
   g.eps = m->eps;
   // the tile and the slopes behind it; the sums' reduction and the slopes lie over the tile
-  const size_t lds = std::max(sizeof(T) * ((size_t)m->na + 1) * TA, sizeof(double) * kSymWaves * 2 * TA + sizeof(T) * TA);
+  auto lds_for = [](int na) {
+    return std::max(sizeof(T) * ((size_t)na + 1) * TA, sizeof(double) * kSymWaves * 2 * TA + sizeof(T) * TA);
+  };
+  const size_t lds = lds_for(m->na), most = lds_for(NMAX * (LMAX + 1) * (LMAX + 1));
   auto launch = [&](auto kern, int nt, int split) -> apx_status {
-    APX_HIP(ctx, hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    // (the most of the instantiation: the attribute is the process's, and another thread's model may be smaller)
+    APX_HIP(ctx, hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)most));
     ProfScope ps(ctx, "ace.products");
     kern<<<dim3(nt, split), kSymWaves * 64, lds, ctx->stream>>>(g);
     APX_LAUNCH_CHECK(ctx);
