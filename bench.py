@@ -33,16 +33,14 @@ PEAK_HBM_GBS = 8000.0
 PEAK_FP32_TFLOPS = 157.3
 PEAK_FP64_TFLOPS = 78.6
 
-# Algorithmic work of the product basis per evaluated atom: the nonzero real Gaunt entries
-# of the direct B3 contraction sum_m G A A A (B1 and B2 add under 1 %).  The energy costs
-# about 6 flops per entry, the adjoint about 10 (the three factors' adjoints).  The library
-# evaluates both from the products of label pairs and executes fewer flops than this count
-# (kernel_models gives the executed count next to it).
+# Work of the product basis per evaluated atom, by (n_max, l_max), as executed: products P_LM of
+# unordered label pairs (each multiplied with the 2 n_max coefficients of its third blocks), vector
+# operations that form them, and those of the energies formed apart (float32).
+SYM_WORK = {(10, 4): (11760, 67915, 7425)}
+# The direct B3 contraction sum_m G A A A, for scale: its nonzero real Gaunt entries, about 6 flops each
+# for the energy and 10 for the adjoint (the three factors' adjoints).  No kernel executes it.
 GAUNT_TERMS = {(10, 4): 211610, (8, 3): 33168}
-ALGO_FLOP_PER_TERM = {"ace.products": 16.0}
-# As executed at (10, 4): products P_LM of unordered label pairs (each multiplied with the 2 n_max
-# coefficients of its third blocks) and vector operations that form them.
-SYM_PRODUCTS, SYM_VECTOR_OPS = 11760, 67915
+DIRECT_FLOP_PER_TERM = {"ace.products": 16.0}
 
 # Hardware counters per launch of each kernel class on the indentation block (rocprofv3
 # --pmc FETCH_SIZE, then WRITE_SIZE; KiB per launch, a class launch being one step of its
@@ -53,22 +51,31 @@ SYM_PRODUCTS, SYM_VECTOR_OPS = 11760, 67915
 # `source_sha256` is checked at run time and the traffic is reported as null when the
 # source has changed since.
 COUNTERS = {
-    "eam.density": {"fetch_kib": 623496.4, "write_kib": 125000.0, "units": 4000000,
+    "ace.products": {"fetch_kib": 742108.0, "write_kib": 1387050.0, "units": 1137182,
+        "source": "paper_2411_03002_amd/csrc/ace_sym.hip",
+        "source_sha256": "a9b7b4b15ded5029fb5bef3be0567b6560b0abc1d21ab3c0131b40fe770fcdb2"},
+    "ace.basis": {"fetch_kib": 400138.0, "write_kib": 1137180.0, "units": 1137182,
+        "source": "paper_2411_03002_amd/csrc/ace.hip",
+        "source_sha256": "f1d17aea3d21683353a7cffcef1691caa89dfe30d96366645ae6f05db5021c8e"},
+    "ace.force": {"fetch_kib": 1041920.5, "write_kib": 1712490.0, "units": 1137182,
+        "source": "paper_2411_03002_amd/csrc/ace.hip",
+        "source_sha256": "f1d17aea3d21683353a7cffcef1691caa89dfe30d96366645ae6f05db5021c8e"},
+    "eam.density": {"fetch_kib": 654041.8, "write_kib": 125000.0, "units": 4000000,
         "source": "paper_2411_03002_amd/csrc/eam.hip",
-        "source_sha256": "183e44649344ca6889755f53585469a4634af1bab88d6b2cf9810c9fd5ba6970"},
-    "eam.force": {"fetch_kib": 821365.8, "write_kib": 93750.0, "units": 4000000,
+        "source_sha256": "e9c5aa3b2b9e4e3ce1a3d531b9579fc8219587fe6fa4cb966a61d417eaa8ba73"},
+    "eam.force": {"fetch_kib": 749226.0, "write_kib": 93750.0, "units": 4000000,
         "source": "paper_2411_03002_amd/csrc/eam.hip",
-        "source_sha256": "183e44649344ca6889755f53585469a4634af1bab88d6b2cf9810c9fd5ba6970"},
-    "nbr.build": {"fetch_kib": 185412.8, "write_kib": 1216098.9, "units": 4000000,
+        "source_sha256": "e9c5aa3b2b9e4e3ce1a3d531b9579fc8219587fe6fa4cb966a61d417eaa8ba73"},
+    "nbr.build": {"fetch_kib": 185436.5, "write_kib": 1216600.0, "units": 4000000,
         "source": "paper_2411_03002_amd/csrc/neighbors.hip",
-        "source_sha256": "03850caf5368f1ef36e179c1c420166396fada9283c442c89b4a770226a9453a"},
-    "prec.csp": {"fetch_kib": 1009092.1, "write_kib": 94062.5, "units": 4000000,
+        "source_sha256": "113aa1c0ecf0bf37b61c95bb343f694a71fc933aeba7b5c94620765e6928784b"},
+    "prec.csp": {"fetch_kib": 670822.0, "write_kib": 93750.0, "units": 4000000,
         "source": "paper_2411_03002_amd/csrc/precision.hip",
-        "source_sha256": "a7812fbabcc117a32a09dbbcdac85f910fe171945d9873000a3090c270592727"},
-    "md.kick_drift": {"fetch_kib": 187627.0, "write_kib": 185638.3, "units": 4000000,
+        "source_sha256": "3e839c3fe5250a2e0e35479c5bf73f9f9613d063a17e8a81b944c1e66c653913"},
+    "md.kick_drift": {"fetch_kib": 187626.5, "write_kib": 185635.0, "units": 4000000,
         "source": "paper_2411_03002_amd/csrc/md.hip",
-        "source_sha256": "8d7ab8f38bc1bd1152b97664fba70554bc73dfe7071e9989efb7c238119d3b53"},
-    "blend": {"fetch_kib": 132651.0, "write_kib": 125066.9, "units": 4000000,
+        "source_sha256": "75a4ea106a5b0ef3f2676aef767a58a215e6c4044a2d9d03f0d2d9f2d60296d9"},
+    "blend": {"fetch_kib": 132651.0, "write_kib": 125067.2, "units": 4000000,
         "source": "paper_2411_03002_amd/csrc/blend.hip",
         "source_sha256": "bee68539ddde7cd4a46af5411dc13e285eed2822a8bc933241cbee66b16952d9"},
 }
@@ -116,7 +123,9 @@ def kernel_models(stats, n, n_act, nb_avg, nb_act_avg, avg_samples=1):
     """
     K, LM = 10, 25
     # the projection on the radial functions (2 K flop per atomic-base value) ends the products
-    f_products = 4.0 * K * SYM_PRODUCTS + 2.0 * SYM_VECTOR_OPS + 2.0 * K * stats["n_atomic_base"]
+    products, vector_ops, low_ops = SYM_WORK[(10, 4)]
+    assert stats["n_atomic_base"] == K * LM, "the counts above are those of (10, 4)"
+    f_products = 4.0 * K * products + 2.0 * (vector_ops + low_ops) + 2.0 * K * stats["n_atomic_base"]
     f_basis = nb_act_avg * (3 * K + 4 * LM + 2 * K * LM) + 2.0 * K * stats["n_atomic_base"]
     f_force = nb_act_avg * (4 * K * LM + 12 * LM + 6 * K)
     row = 4.0 + 4.0 * nb_avg
@@ -155,12 +164,12 @@ def traffic_for(name, units):
     return (2.0 * c["fetch_kib"] + 1.0 * c["write_kib"]) * 1024.0 * units / c["units"]
 
 
-def roofline_for(name, model, launches, total_ms, algo=None, units=None):
+def roofline_for(name, model, launches, total_ms, direct=None, units=None):
     """Roofline entry of one kernel class from its measured average launch time.
 
-    ``model`` = (bound, amount per launch, unit) as implemented; ``algo`` (optional) the
-    algorithmic amount per launch that the achieved rate is quoted on (the executed one is
-    reported next to it)."""
+    ``model`` = (bound, amount per launch, unit) as implemented; ``direct`` (optional) the
+    flops per launch of the direct contraction, which no kernel executes: its rate is given
+    beside the executed one, without a fraction of the peak."""
     bound, amount, unit = model
     avg_s = total_ms / 1e3 / max(launches, 1)
     if unit == "byte":
@@ -168,22 +177,19 @@ def roofline_for(name, model, launches, total_ms, algo=None, units=None):
         return {"kernel": name, "bound": "hbm", "achieved": achieved, "peak": PEAK_HBM_GBS, "unit": "GB/s",
                 "frac": achieved / PEAK_HBM_GBS, "traffic": traffic_for(name, units),
                 "avg_ms": avg_s * 1e3, "work_per_launch": amount}
-    work = amount if algo is None else algo
-    achieved = work / avg_s / 1e12
+    achieved = amount / avg_s / 1e12
     out = {"kernel": name, "bound": "alu", "achieved": achieved, "peak": PEAK_FP32_TFLOPS, "unit": "TFLOP/s",
            "frac": achieved / PEAK_FP32_TFLOPS, "traffic": traffic_for(name, units),
-           "avg_ms": avg_s * 1e3, "work_per_launch": work}
-    if algo is not None:
-        ex = amount / avg_s / 1e12
-        out["executed"] = {"achieved": ex, "frac": ex / PEAK_FP32_TFLOPS, "work_per_launch": amount,
-                           "frac_of_unpacked_fp32": ex / (PEAK_FP32_TFLOPS / 2)}
+           "avg_ms": avg_s * 1e3, "work_per_launch": amount}
+    if direct is not None:
+        out["direct_contraction"] = {"rate": direct / avg_s / 1e12, "work_per_launch": direct}
     return out
 
 
-def algo_work(name, n_act, nm_lm=(10, 4)):
-    """Algorithmic flops per launch of the ACE product kernels (None for the others)."""
-    if name in ALGO_FLOP_PER_TERM:
-        return n_act * GAUNT_TERMS[nm_lm] * ALGO_FLOP_PER_TERM[name]
+def direct_work(name, n_act, nm_lm=(10, 4)):
+    """Flops per launch of the direct contraction for the ACE products (None for the others)."""
+    if name in DIRECT_FLOP_PER_TERM:
+        return n_act * GAUNT_TERMS[nm_lm] * DIRECT_FLOP_PER_TERM[name]
     return None
 
 
@@ -588,7 +594,7 @@ def main():
     dom = max(prof_a.items(), key=lambda kv: kv[1][1])[0]
     result["kernels"] = kern
     result["dominant_kernel"] = dom
-    roofs = {k: roofline_for(k, models[k], *prof_a[k], algo=algo_work(k, n_act),
+    roofs = {k: roofline_for(k, models[k], *prof_a[k], direct=direct_work(k, n_act),
                              units=n_act if k.startswith("ace.") else n) for k in prof_a if k in models}
     result["roofline"] = roofs.get(dom)
     result["roofline_all"] = roofs
@@ -714,7 +720,7 @@ def main():
         if "ace.products" in prof_f:
             result["roofline_full_ace_products"] = roofline_for("ace.products", mf["ace.products"],
                                                                 *prof_f["ace.products"],
-                                                                algo=algo_work("ace.products", n_f), units=n_f)
+                                                                direct=direct_work("ace.products", n_f), units=n_f)
         result["kernels_full_ace"] = {k: {"launches": v[0], "total_ms": v[1], "avg_ms": v[1] / max(v[0], 1)}
                                       for k, v in prof_f.items()}
         log(f"full ACE {dt_f / KF * 1e3:.2f} ms/step, {full:.4g} atom-steps/s, ratio {adaptive / full:.2f}")
