@@ -53,7 +53,7 @@ DIRECT_FLOP_PER_TERM = {"ace.products": 16.0}
 COUNTERS = {
     "ace.products": {"fetch_kib": 742108.0, "write_kib": 1387050.0, "units": 1137182,
         "source": "paper_2411_03002_amd/csrc/ace_sym.hip",
-        "source_sha256": "a9b7b4b15ded5029fb5bef3be0567b6560b0abc1d21ab3c0131b40fe770fcdb2"},
+        "source_sha256": "45cf6ecf40f64514ab88d5265a8759dc9f71d5cc2eaa0050bc0fe891bff88976"},
     "ace.basis": {"fetch_kib": 400138.0, "write_kib": 1137180.0, "units": 1137182,
         "source": "paper_2411_03002_amd/csrc/ace.hip",
         "source_sha256": "f1d17aea3d21683353a7cffcef1691caa89dfe30d96366645ae6f05db5021c8e"},

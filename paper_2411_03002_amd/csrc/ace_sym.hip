@@ -817,11 +817,11 @@ size_t share_slab(const apx_ace_model* m) {
 
 // Shares of a tile's pairs: enough blocks for two per compute unit.  A share costs the block's
 // staging and the sum over shares at the end; it pays while compute units idle.  Measured in
-// float32 at (10, 4), products + end in us by shares 1/2/4/8: 8 tiles 165/92/59/47, 63 tiles
-// 164/100/73/73, 125 tiles 171/107/95/143, 255 tiles 176/147/210/264, 375 tiles 226/230/257/378,
-// 938 tiles 459/529/632/957; sixteen shares were no better than eight at 1 tile and worse beyond.
-// In float64: 32 tiles 86/55/40/40, 125 tiles 87/64/57/71, 250 tiles 90/83/96/118, 500 tiles
-// 132/148/166/215.
+// float32 at (10, 4), products + end in us by shares 1/2/4/8: 8 tiles 164/94/60/44, 63 tiles
+// 165/106/75/75, 125 tiles 166/113/99/129, 255 tiles 177/156/185/271, 375 tiles 235/239/260/403,
+// 938 tiles 503/548/651/958; sixteen shares were no better than eight at 1 tile and worse beyond.
+// In float64: 32 tiles 84/54/40/38, 125 tiles 87/64/57/73, 250 tiles 88/82/96/118, 500 tiles
+// 131/148/165/217.
 template <class T>
 SymPlan<T> sym_plan(const apx_ace_model* m, int n_act) {
   constexpr int TA = sym_tile<T>();
